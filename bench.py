@@ -19,7 +19,8 @@ Every workload reports two roofline entries, both from per-launch HIP events rec
 the launch stream by the library's profile hooks over a repeat of the timed steps:
   `roofline`      the dominant matrix-core launch site family (conv forward, data gradient or
                   weight gradient): algorithmic flops / time against the MFMA peak of the
-                  instruction that family runs on (fp32 157.3 TFLOP/s, bf16 2500 TFLOP/s);
+                  instruction that family runs on (fp32 157.3 TFLOP/s, bf16 2500 TFLOP/s; fp32
+                  products made of six bf16 products: a sixth of the latter);
   `roofline_hbm`  the max-filter and routing passes: algorithmic bytes / time against 8 TB/s.
 `cpu_baseline` is the fp64 patch-by-patch oracle timed on this machine's host cores on a bounded
 sample of the same workload.
@@ -36,6 +37,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA = 157.3      # TFLOP/s, MI355X dense fp32 matrix
 PEAK_BF16_MFMA = 2500.0     # TFLOP/s, dense bf16 matrix
+PEAK_PARTS = PEAK_BF16_MFMA / 6   # TFLOP/s of fp32 products made of six bf16 products each
 PEAK_HBM = 8000.0           # GB/s, HBM3E
 HEADLINE = 3
 # pixels the oracle is timed on (about 10 s on 16 threads for the headline, a few seconds for the rest)
@@ -56,6 +58,11 @@ def read_traffic(path, kernel):
     return None
 
 
+def peak_of(site):
+    """TFLOP/s of the instruction a matrix site runs on (per fp32 product where those are made of parts)."""
+    return PEAK_BF16_MFMA if site.endswith("_bm") else PEAK_PARTS if site.endswith("_parts") else PEAK_FP32_MFMA
+
+
 def rooflines(stats, steps, ms_per_step, workload):
     """The two roofline entries from the per-site records of `steps` profiled steps."""
     by_name = {}
@@ -67,12 +74,12 @@ def rooflines(stats, steps, ms_per_step, workload):
         k["launches"] += s["launches"]
         k["flops"] += s["flops"] * s["launches"]
         k["bytes"] += s["bytes"] * s["launches"]
-    matrix = {n: v for n, v in by_name.items() if n.startswith(MATRIX_SITES) and n.endswith(("_mfma", "_bm"))}
+    matrix = {n: v for n, v in by_name.items() if n.startswith(MATRIX_SITES) and n.endswith(("_mfma", "_bm", "_parts"))}
     out = {}
     if matrix:
         name = max(matrix, key=lambda n: matrix[n]["ms"])
         dom = matrix[name]
-        peak = PEAK_BF16_MFMA if name.endswith("_bm") else PEAK_FP32_MFMA
+        peak = peak_of(name)
         achieved = dom["flops"] / (dom["ms"] * 1e-3) / 1e12
         out["roofline"] = {
             "bound": "mfma", "achieved": round(achieved, 3), "peak": peak, "unit": "TFLOP/s",
@@ -82,8 +89,7 @@ def rooflines(stats, steps, ms_per_step, workload):
             "launches_per_step": dom["launches"] // steps,
             "share_of_step": round(dom["ms"] / steps / ms_per_step, 3),
             "all_matrix_sites": {n: {"achieved": round(v["flops"] / (v["ms"] * 1e-3) / 1e12, 2),
-                                     "frac": round(v["flops"] / (v["ms"] * 1e-3) / 1e12 /
-                                                   (PEAK_BF16_MFMA if n.endswith("_bm") else PEAK_FP32_MFMA), 4),
+                                     "frac": round(v["flops"] / (v["ms"] * 1e-3) / 1e12 / peak_of(n), 4),
                                      "us_per_step": round(1e3 * v["ms"] / steps, 1)}
                                  for n, v in sorted(matrix.items())},
         }

@@ -141,13 +141,12 @@ mpcnn_status mpcnn_set_activation(mpcnn_net* net, mpcnn_activation kind);
 
 /* Tuning knob for the matrix-core convolution kernel of fp32-arithmetic layers (forward and
  * data gradient; Method, forward and backward of layer C): a workgroup computes 32 *
- * position_tiles positions of one residue class (16 * position_tiles where a layer's 16 or fewer
- * outputs put it on 16-wide tiles) and each of its waves owns tiles_per_wave of them for one
- * channel tile.  0 leaves either choice to the library's
+ * position_tiles positions of one residue class (16 * position_tiles where bf16 storage puts a
+ * layer of 16 or fewer outputs on 16-wide tiles) and each of its waves owns tiles_per_wave of them
+ * for one channel tile, or two.  0 leaves either choice to the library's
  * planner (the default), which weighs matrix-instruction time against staging per layer and
- * image size.  A pair that no kernel instance serves for a layer's channel count (the waves of
- * a workgroup, channel tiles * position_tiles / tiles_per_wave, must be 4 or 8) leaves that
- * layer on the planner's fallback kernel.  Results do not depend on the tiling: every output
+ * image size.  A pair that no kernel instance serves for a layer's channel count leaves that
+ * layer to the planner.  Results do not depend on the tiling: every output
  * element is the same sum in the same order.  Takes effect at the next forward / backward
  * call.  EINVAL unless position_tiles is 0, 2, 4, 8 or 16 and tiles_per_wave 0, 1, 2 or 4. */
 mpcnn_status mpcnn_set_conv_tiling(mpcnn_net* net, int position_tiles, int tiles_per_wave);
@@ -332,7 +331,7 @@ mpcnn_status mpcnn_get_argmax(const mpcnn_net* net, int layer, uint8_t* host, si
  * events recorded on the call's stream.  mpcnn_profile_read waits for them and
  * returns one record per launch site (kernel x layer), summed since the last
  * read: kernel name (ending in _mfma: fp32 matrix instruction, _bm: bf16 matrix
- * instruction), layer index, step of the path (1 = conv fwd, 2 = max filter,
+ * instruction, _parts: fp32 products made of six bf16 products on the latter), layer index, step of the path (1 = conv fwd, 2 = max filter,
  * 3 = class layer + softmax-CE, 4 = class layer backward, 5 = wgrad, 6 = dgrad,
  * 7 = routing, 8 = SGD, 0 = staging / reductions), launches, total milliseconds,
  * and the ALGORITHMIC work of one launch: flops = 2*M*N*K of the contraction

@@ -1,0 +1,434 @@
+// Forward / data gradient of one dilated convolution on the bf16 matrix instruction
+// (v_mfma_f32_32x32x16_bf16), for fp32 storage as well as bf16 storage.
+//
+// fp32 storage.  The bf16 instruction does 16 times the products of the fp32 one in the same time.
+// An fp32 number is EXACTLY the sum of three bf16 numbers (8 + 8 + 8 bits: x0 = bf16(x),
+// x1 = bf16(x - x0), x2 = x - x0 - x1, each difference exact), so a product of two fp32 numbers is
+// the sum of nine bf16 products, each exact in fp32.  The six with the largest factors are taken,
+//     x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0),
+// smallest first; the three left out are below 2^-26 of |x y| together, a quarter of the rounding
+// that one fp32 addition brings.  Six instructions of 32 cycles contract 16 channels where the
+// fp32 instruction takes eight of 64: 417 TFLOP/s of fp32 products at the instruction's dense peak
+// against 157.  The accumulator is rounded six times per 16 products instead of eight times, so
+// the sums come out closer, not further off (against 64-bit sums of 64 .. 1600 products of uniform
+// and of log-normal numbers, rms relative: 1.1e-7 .. 6.0e-7 and 1.0e-7 .. 2.9e-7 here, 1.4e-7 ..
+// 6.9e-7 and 1.8e-7 .. 4.8e-7 on the fp32 instruction).  Infinities, NaN and numbers above the
+// largest bf16 have no such parts and leave a result that is not finite; the epilogue looks for
+// those and computes them again with fp32 multiply-adds, so they are what they would be without parts.
+// bf16 storage.  One part, one product: same kernel.
+//
+// Tiling.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x
+// 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32.  A step contracts 16
+// channels of one tap: MO + MP operands of P parts each feed P(P+1)/2 * MO * MP instructions.  With 2 x 2
+// tiles and three parts that is 12 KB for 24 instructions, which the vector cache (weights, the same
+// for all waves of the workgroup) and the LDS (activations) deliver at 32 bytes per cycle each, well
+// below what they can; the loop alone then sustains 2.17 PFLOP/s (362 TFLOP/s of fp32 products).
+// The input halo is brought in CB channels at a time, [position][16 channels][part] in LDS with a pitch
+// that spreads 16 successive positions over all banks, so that an operand is one 128-bit read at
+// an immediate offset from one address per position tile and step.
+//
+// Latency.  Workgroups are persistent and walk (tile, channel block) items; the next item's halo is
+// loaded into registers before the current one is multiplied and split into parts on its way to LDS after it.
+// Weights run through a ring of two steps (four with one part) that never drains: the pack is in step
+// order and wraps around from a tile's last step to its first.  Two workgroups share a compute unit, so one's
+// staging, barriers and stores lie under the other's instructions.
+//
+// Summation order is the step order for every output element, whatever the tiling: equal inputs
+// give bit-equal outputs (exact pooling ties stay exact) and a position's value does not depend on
+// how the map is cut.
+#pragma once
+#include <type_traits>
+
+#include "kernels_mfma.hpp"
+
+namespace mpcnn {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// Geometry shared with the host's plan.
+constexpr int kPartsThreads = 256;   // four waves
+__host__ __device__ constexpr int parts_pitch(int parts, int CB) { return (CB / 16) * parts * 32 + 16; }   // LDS bytes of a halo position
+__host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
+__host__ __device__ constexpr int parts_items(int parts) { return parts == 3 ? 6 : 12; }                    // rounds, at most (they wait in registers)
+__host__ __device__ constexpr int parts_unit(int parts) { return parts == 3 ? 1 : 2; }                      // steps per slot of the weights' ring
+// steps of a block of nsub 16-channel chunks: whole units (the odd one out multiplies zero weights)
+__host__ __device__ constexpr int parts_block_steps(int parts, int taps, int nsub) { return (taps * nsub + parts_unit(parts) - 1) / parts_unit(parts) * parts_unit(parts); }
+__host__ __device__ constexpr int parts_steps(int parts, int CB, int taps, int rpad)                        // ... of a whole reduction
+{
+    return (rpad / CB) * parts_block_steps(parts, taps, CB / 16) + (rpad % CB ? parts_block_steps(parts, taps, rpad % CB / 16) : 0);
+}
+
+// x = x0 + x1 + x2 exactly (8 numbers at once)
+__device__ __forceinline__ void split_parts(const float (&x)[8], bf16x8 (&p)[3])
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const __bf16 a = (__bf16)x[j];
+        const float r = x[j] - (float)a;
+        const __bf16 b = (__bf16)r;
+        p[0][j] = a; p[1][j] = b; p[2][j] = (__bf16)(r - (float)b);
+    }
+}
+
+__device__ __forceinline__ unsigned parts_div(unsigned n, unsigned magic, unsigned x)
+{
+    return x == 1 ? n : __umulhi(n, magic);   // n / x for n * x < 2^32, magic = ceil(2^32 / x)
+}
+
+template <typename T, bool BACK, int CB, int WO, int WP, int MO, int MP>
+__global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a)
+{
+    static_assert(WO * WP == 4, "four waves");
+    constexpr int P = sizeof(T) == 4 ? 3 : 1;
+    constexpr int QN = CB / 8, NSUB = CB / 16, U = parts_unit(P);
+    constexpr int PITCH = parts_pitch(P, CB), RP = parts_round(CB), SI = parts_items(P);
+    constexpr int ITW = P == 3 ? 2 : 1;               // 128-bit loads per staged item (8 channels of a position)
+    constexpr unsigned kNone = 0x80000000u;           // byte offset no buffer reaches: the load returns zeros
+    const T* in_t = static_cast<const T*>(a.in);
+    const T* act_t = static_cast<const T*>(a.act);
+    T* out_t = static_cast<T*>(a.out);
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    char* ldsb = reinterpret_cast<char*>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lt = lane & 31, lg = lane >> 5;
+    // channel group turned by the workgroup's index: the waves whose tiles lie past the last channel should not
+    // sit on the same SIMDs in both workgroups of a compute unit
+    const int wo = (wave + (int)(blockIdx.x % WO)) % WO, wp = wave / WO;
+
+    const int hw = a.Tx + a.k2 - 1, hh = a.Ty + a.k - 1;
+    const int npos = hh * hw;                         // <= SI * RP
+    const int oc0 = 32 * ((blockIdx.y * WO + wo) * MO);   // first channel of this wave's tiles
+    const bool live = oc0 < a.Co;                     // uniform for the wave
+
+    // ---- staging: thread tid brings 8 channels (octet q of the block) of halo positions tid / QN + RP*u
+    const int q = tid % QN, pos0 = tid / QN;
+    char* const st_dst = ldsb + pos0 * PITCH + (q >> 1) * (P * 32) + (q & 1) * 16;
+    unsigned voff[SI];                                // byte offsets from the halo's first element (kNone: outside, or no such position)
+    u32x4 pre[SI][ITW];
+
+    struct Tile { int b, ry, rx, ty0, tx0; };
+    auto decode = [&](int t) {
+        Tile g;
+        unsigned bid = t;
+        unsigned qd = parts_div(bid, a.mg_ntx, a.ntx);
+        g.tx0 = (int)(bid - qd * a.ntx) * a.Tx; bid = qd;
+        qd = parts_div(bid, a.mg_nty, a.nty);
+        g.ty0 = (int)(bid - qd * a.nty) * a.Ty; bid = qd;
+        qd = parts_div(bid, a.mg_d2, a.d2);
+        g.rx = bid - qd * a.d2; bid = qd;
+        qd = parts_div(bid, a.mg_d, a.d);
+        g.ry = bid - qd * a.d;
+        g.b = qd;
+        return g;
+    };
+    const T* st_base = in_t;                          // the halo's first element (may lie before the tensor: only valid items are read)
+    // (an empty asm keeps what depends on the lane alone from being computed once for all tiles and held in registers
+    // beside the accumulators: there are none left)
+    auto fresh = [](int v) { asm volatile("" : "+v"(v)); return v; };
+    auto aim = [&](const Tile& g, bool any) {         // this thread's items of tile g
+        const int first = fresh(pos0);
+        const unsigned row_b = (unsigned)(a.d * a.Wi * a.Cr) * (unsigned)sizeof(T), col_b = (unsigned)(a.d2 * a.Cr) * (unsigned)sizeof(T);
+        const int iy0 = (g.ty0 + a.origin) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
+        st_base = in_t + (((long)g.b * a.Hi + iy0) * a.Wi + ix0) * a.Cr;
+#pragma unroll
+        for (int u = 0; u < SI; ++u) {
+            const unsigned pos = first + RP * u;
+            const unsigned ha = parts_div(pos, a.mg_hw, hw), hb = pos - ha * hw;
+            const int iy = iy0 + (int)ha * a.d, ix = ix0 + (int)hb * a.d2;
+            const bool ok = any && pos < (unsigned)npos && (unsigned)iy < (unsigned)a.Hi && (unsigned)ix < (unsigned)a.Wi;
+            voff[u] = ok ? ha * row_b + hb * col_b + 8u * q * (unsigned)sizeof(T) : kNone;
+        }
+    };
+    // every load is issued on every path (outside: kNone), so that the number in flight is known
+    auto issue = [&](int cb) {
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(st_base), 0, 0x7fffffff, 0x00020000);
+        const int c = CB * cb + 8 * q;                // first channel of the item
+        const int soff = CB * cb * (int)sizeof(T);
+#pragma unroll
+        for (int u = 0; u < SI; ++u) {
+            if constexpr (P == 3) {
+                pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
+                pre[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c + 4 < a.Cr ? voff[u] + 16u : kNone), soff, 0));
+            } else {
+                // (two halves: with a channel count that is 4 mod 8 the item is only 8-byte aligned, its second half another position's)
+                if (a.Cr & 7) {
+                    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
+                    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(c + 4 < a.Cr ? voff[u] + 8u : kNone), soff, 0));
+                    pre[u][0] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
+                } else
+                    pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
+            }
+        }
+    };
+    auto to_lds = [&]() {                             // (the LDS holds whole rounds)
+#pragma unroll
+        for (int u = 0; u < SI; ++u) {
+            if (RP * u >= npos) break;                // uniform
+            char* dst = st_dst + u * (RP * PITCH);
+            if constexpr (P == 3) {
+                float x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
+                bf16x8 p[3];
+                split_parts(x, p);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x8*>(dst + 32 * i) = p[i];
+            } else
+                *reinterpret_cast<u32x4*>(dst) = pre[u][0];
+        }
+    };
+
+    // ---- per lane: LDS address of the positions it feeds as the B operand, at tap 0
+    int lbase[MP];
+#pragma unroll
+    for (int p = 0; p < MP; ++p) {
+        const unsigned m = 32 * (wp * MP + p) + lt;
+        unsigned ty = parts_div(m, a.mg_tx, a.Tx), tx = m - ty * a.Tx;
+        if (ty >= (unsigned)a.Ty) { ty = 0; tx = 0; }   // padding position: any address inside
+        lbase[p] = (int)(ty * hw + tx) * PITCH + lg * 16;
+    }
+
+    // ---- weights: [step][part][lane group][CoPad][8], the step's offset a scalar
+    const int wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = parts_steps(P, CB, a.k * a.k2, a.CrPad) * wstep;   // bytes
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<v4f*>(a.wpack), 0, wend, 0x00020000);
+    const int wlane = (lg * a.CoPad + oc0 + lt) * 16;
+    int wq = 0;                                       // byte offset of the next step to fetch
+    const int nblk = (a.CrPad + CB - 1) / CB;
+
+    v16f acc[MO][MP];
+    v4f w[2][U][MO * P];                              // the ring: two slots of U steps
+    auto fetch_w = [&](int s, int u, int i) {
+#pragma unroll
+        for (int o = 0; o < MO; ++o)
+            w[s][u][o * P + i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane + 512 * o, wq + i * wpart, 0));
+    };
+    auto next_w = [&]() {
+        wq += wstep;
+        if (wq >= wend) wq = 0;
+    };
+
+    // one tile's share of one channel block
+    auto multiply = [&](int nsub) {
+        const int n = parts_block_steps(P, a.k * a.k2, nsub) / U;   // units of this block
+        int left = a.k * a.k2 * nsub;                 // steps whose activations are still to be fetched
+        int tb = 0, sub = 0, soff = 0;                // the next one's place
+        const int rowskip = (hw - a.k2) * PITCH;
+        constexpr int XS = P == 3 ? 1 : 2;            // sets of activations in registers
+        v4f x[XS][P][MP];
+        auto fetch_x = [&](int s, int i) {
+#pragma unroll
+            for (int p = 0; p < MP; ++p) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + soff + 32 * i);
+        };
+        // (past the last step: the first one's place, read for nothing or against zero weights)
+        auto next_x = [&]() {
+            soff += P * 32;
+            if (++sub == nsub) {
+                sub = 0; soff += PITCH - nsub * (P * 32);
+                if (++tb == a.k2) { tb = 0; soff += rowskip; }
+            }
+            if (--left <= 0) soff = 0;
+        };
+        auto product = [&](int s, int u, int t, int i, int j) {   // weight part i, activation part j
+#pragma unroll
+            for (int o = 0; o < MO; ++o)
+#pragma unroll
+                for (int p = 0; p < MP; ++p)
+                    acc[o][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][u][o * P + i]),
+                                                                        __builtin_bit_cast(bf16x8, x[t][j][p]), acc[o][p], 0, 0, 0);
+        };
+        auto unit = [&](int s) {
+            if constexpr (P == 3) {
+                // A step's operands are fetched for the next one as soon as they are free: the activations' third part
+                // behind the first product, its second behind the third, its first behind the last (three products
+                // before it is needed).
+                next_x();
+                product(s, 0, 0, 0, 2); fetch_x(0, 2);
+                product(s, 0, 0, 1, 1); product(s, 0, 0, 0, 1); fetch_x(0, 1);
+                product(s, 0, 0, 2, 0); fetch_w(s, 0, 2);
+                product(s, 0, 0, 1, 0); fetch_w(s, 0, 1);
+                product(s, 0, 0, 0, 0); fetch_x(0, 0); fetch_w(s, 0, 0);
+                next_w();
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    next_x(); fetch_x(u ^ 1, 0);
+                    product(s, u, u, 0, 0); fetch_w(s, u, 0);
+                    next_w();
+                }
+            }
+        };
+#pragma unroll
+        for (int i = P - 1; i >= 0; --i) fetch_x(0, i);
+        // Units two by two.  The first pair stands before the loop: behind it the next halo's loads are older than
+        // every weight in flight, so the loop's waits count weights only.
+        int s = 0;
+        if (n >= 2) {
+            unit(0); unit(1);
+            for (s = 2; s + 2 <= n; s += 2) { unit(0); unit(1); }
+        }
+        if (s < n) {                                  // an odd unit: the ring's slots change places
+            unit(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < MO * P; ++i) { const v4f t = w[0][u][i]; w[0][u][i] = w[1][u][i]; w[1][u][i] = t; }
+        }
+    };
+
+    // ---- result of one element: the sum v, and the bias (forward) or the output whose slope multiplies it (data gradient)
+    const bool curved = a.mode == kFwdTanh || a.mode == kDgradTanh;   // uniform
+    auto finish = [&](float v, float y) {
+        if constexpr (BACK) return curved ? v * squash_slope(y, a.logistic) : v;
+        else return curved ? squash(v + y, a.logistic) : v + y;
+    };
+    // ---- epilogue of tile g: register 4n + z of tile (o, p) is channel oc0 + 32o + 8n + 4lg + z of position
+    // 32*(wp*MP + p) + lt
+    auto epilogue = [&](const Tile& g, int fh, int fw) {
+        const bool vec = (a.Co & 3) == 0;             // uniform
+        const int col = fresh(lt);
+#pragma unroll
+        for (int p = 0; p < MP; ++p) {
+            const unsigned m = 32 * (wp * MP + p) + col;
+            const int ty = (int)parts_div(m, a.mg_tx, a.Tx), tx = (int)m - ty * a.Tx;
+            const int fy = g.ty0 + ty, fx = g.tx0 + tx;
+            const bool pos_ok = ty < a.Ty && fy < fh && fx < fw;
+            const long pos_off = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co;
+#pragma unroll
+            for (int o = 0; o < MO; ++o) {
+                v4f yv[4];
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const int oc = oc0 + 32 * o + 8 * n + 4 * lg;
+                    yv[n] = (v4f){0.f, 0.f, 0.f, 0.f};
+                    if (!pos_ok || oc >= a.Co || (BACK && !curved)) continue;
+                    if (vec) {
+                        if (BACK) yv[n] = load4(act_t + pos_off + oc);
+                        else yv[n] = (v4f){a.bias[oc], a.bias[oc + 1], a.bias[oc + 2], a.bias[oc + 3]};
+                    } else {
+                        for (int z = 0; z < 4; ++z)
+                            if (oc + z < a.Co) yv[n][z] = BACK ? load1(act_t + pos_off + oc + z) : a.bias[oc + z];
+                    }
+                }
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const int oc = oc0 + 32 * o + 8 * n + 4 * lg;
+                    if (!pos_ok || oc >= a.Co) continue;
+                    v4f r;
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) r[z] = finish(acc[o][p][4 * n + z], yv[n][z]);
+                    if (vec) store4(out_t + pos_off + oc, r);
+                    else for (int z = 0; z < 4; ++z) if (oc + z < a.Co) store1(out_t + pos_off + oc + z, r[z]);
+                }
+            }
+        }
+    };
+    // A sum that is not finite came from infinities, NaN or numbers without parts (or is one that overflows):
+    // once more, with fp32 multiply-adds over the taps and channels in step order.
+    auto repair = [&](const Tile& g, int fh, int fw, const unsigned (&bad)[MO][MP]) {
+        for (int e = 0; e < MO * MP * 16; ++e) {
+            const int o = e / (MP * 16), p = (e / 16) % MP, r = e & 15;
+            unsigned mask = 0;
+#pragma unroll
+            for (int oo = 0; oo < MO; ++oo)
+#pragma unroll
+                for (int pp = 0; pp < MP; ++pp) mask = (oo == o && pp == p) ? bad[oo][pp] : mask;
+            const int oc = oc0 + 32 * o + 8 * (r >> 2) + 4 * lg + (r & 3);
+            const unsigned m = 32 * (wp * MP + p) + lt;
+            const int ty = (int)parts_div(m, a.mg_tx, a.Tx), tx = (int)m - ty * a.Tx;
+            const int fy = g.ty0 + ty, fx = g.tx0 + tx;
+            if (!((mask >> r) & 1u) || oc >= a.Co || ty >= a.Ty || fy >= fh || fx >= fw) continue;
+            const int ci = BACK ? a.Co : a.Cr, co = BACK ? a.Cr : a.Co;   // the raw weights are [tap][layer input][layer output]
+            float sum = 0.f;
+            for (int ta = 0; ta < a.k; ++ta)
+                for (int tb = 0; tb < a.k2; ++tb) {
+                    const int iy = (fy + ta + a.origin) * a.d + g.ry, ix = (fx + tb + a.origin2) * a.d2 + g.rx;
+                    if (iy < 0 || ix < 0 || iy >= a.Hi || ix >= a.Wi) continue;
+                    const T* src = in_t + (((long)g.b * a.Hi + iy) * a.Wi + ix) * a.Cr;
+                    const int tap = ta * a.k2 + tb;
+                    const float* wr = BACK ? a.wraw + ((long)(a.k * a.k2 - 1 - tap) * ci + oc) * co : a.wraw + (long)tap * ci * co + oc;
+                    for (int c = 0; c < a.Cr; ++c) sum = fmaf(load1(src + c), wr[BACK ? c : c * co], sum);
+                }
+            const long off = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co + oc;
+            const float y = BACK ? (curved ? load1(act_t + off) : 0.f) : a.bias[oc];
+            store1(out_t + off, finish(sum, y));
+        }
+    };
+
+    // ---- walk the tiles
+    int t = blockIdx.x;
+    if (t >= a.tiles_total) return;                   // (uniform; the host launches no such workgroup)
+    Tile cur = decode(t);
+    aim(cur, true);
+    issue(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)                       // (a reduction of one slot: the same steps twice)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) fetch_w(s, u, i);
+            next_w();
+        }
+    to_lds();
+    __syncthreads();
+    for (; t < a.tiles_total; t += gridDim.x) {
+#pragma unroll
+        for (int o = 0; o < MO; ++o)
+#pragma unroll
+            for (int p = 0; p < MP; ++p)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[o][p][r] = 0.f;
+        Tile nxt = cur;
+        for (int cb = 0; cb < nblk; ++cb) {
+            // the next item's halo starts its trip
+            const bool last = cb + 1 == nblk;
+            if (last) {
+                const int tn = t + gridDim.x;
+                nxt = decode(tn < a.tiles_total ? tn : t);
+                aim(nxt, tn < a.tiles_total);
+            }
+            issue(last ? 0 : cb + 1);
+            const int left = (a.CrPad - cb * CB) / 16;
+            const int nsub = left < NSUB ? left : NSUB;
+            if (live) multiply(nsub);
+            if (last && live) {
+                const int fh = cur.ry < a.Ho ? (int)parts_div(a.Ho - cur.ry + a.d - 1, a.mg_d, a.d) : 0;   // extent of this residue class
+                const int fw = cur.rx < a.Wo ? (int)parts_div(a.Wo - cur.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
+                bool odd = false;
+                if constexpr (P == 3) {
+                    float z = 0.f;                    // NaN as soon as one of the sums is not finite
+#pragma unroll
+                    for (int o = 0; o < MO; ++o)
+#pragma unroll
+                        for (int p = 0; p < MP; ++p)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) z = fmaf(acc[o][p][r], 0.f, z);
+                    odd = __any(z != z);
+                }
+                epilogue(cur, fh, fw);
+                if constexpr (P == 3) {
+                    if (odd) {
+                        unsigned bad[MO][MP];
+#pragma unroll
+                        for (int o = 0; o < MO; ++o)
+#pragma unroll
+                            for (int p = 0; p < MP; ++p) {
+                                bad[o][p] = 0;
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) bad[o][p] |= __builtin_isfinite(acc[o][p][r]) ? 0u : 1u << r;
+                            }
+                        repair(cur, fh, fw, bad);
+                    }
+                }
+            }
+            __syncthreads();   // every wave has left this block's halo
+            to_lds();
+            __syncthreads();
+        }
+        cur = nxt;
+    }
+}
+
+}  // namespace mpcnn

@@ -46,7 +46,8 @@ struct ConvArgs {
     // persistent kernels (conv_tp_kernel): number of tiles to walk, and ceil(2^32 / x) of the
     // divisors they use (n / x == umulhi(n, magic) for n * x < 2^32, x > 1)
     int tiles_total;
-    unsigned mg_cq, mg_hw, mg_tx, mg_ntx, mg_nty, mg_d;
+    unsigned mg_cq, mg_hw, mg_tx, mg_ntx, mg_nty, mg_d, mg_d2;
+    const float* wraw;   // [k*k2][layer input][layer output], the parameters as they are (conv_parts_kernel: sums that are not finite)
 };
 
 template <int W> struct MfmaAcc;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels_conv_parts.hpp"   // the order of its steps
 #include "storage.hpp"
 
 namespace mpcnn {
@@ -60,6 +61,50 @@ __global__ void pack_weights_bf16_kernel(const float* __restrict__ W, bf16* __re
             if (r < Co && oo < Ci) v = W[((long)(kk - 1 - tap) * Ci + oo) * Co + r];
         }
         P[e] = (bf16)v;
+    }
+}
+
+// The packs of conv_parts_kernel, P parts per number: steps in the order that kernel takes them - channel
+// blocks of CB, in a block the taps, in a tap its 16-channel chunks -
+//   Q[step][part][g][o][s] = part of W[..][16*ch + 8*g + s][..], s < 8.
+// One thread: one (step, g, o), 8 numbers and P 128-bit stores.
+template <int P>
+__global__ void pack_parts_kernel(const float* __restrict__ W, bf16* __restrict__ Q, int kk, int Ci, int Co,
+                                  int RPad, int OPad, int CB, int dgrad)
+{
+    const int nsub_full = CB / 16, blk_steps = parts_block_steps(P, kk, nsub_full);
+    const long total = (long)parts_steps(P, CB, kk, RPad) * 2 * OPad;
+    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
+        const int oo = (int)(e % OPad);
+        const int g = (int)((e / OPad) & 1), step = (int)(e / (2 * OPad));
+        const int blk = step / blk_steps, r = step - blk * blk_steps;
+        const int left = RPad / 16 - blk * nsub_full, nsub = left < nsub_full ? left : nsub_full;
+        const int tap = r / nsub, ch = blk * nsub_full + (r - tap * nsub);   // (tap == kk: the step of zeros that fills a unit)
+        bf16 parts[P][8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int c = 16 * ch + 8 * g + s;   // index along the reduced dimension
+            float v = 0.f;
+            if (tap >= kk) v = 0.f;
+            else if (!dgrad) {
+                if (c < Ci && oo < Co) v = W[((long)tap * Ci + c) * Co + oo];
+            } else {
+                if (c < Co && oo < Ci) v = W[((long)(kk - 1 - tap) * Ci + oo) * Co + c];
+            }
+#pragma unroll
+            for (int i = 0; i < P; ++i) {        // v = the sum of its parts, exactly
+                parts[i][s] = (bf16)v;
+                v -= (float)parts[i][s];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            typedef bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+            bf16x8_t o;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) o[s] = parts[i][s];
+            *reinterpret_cast<bf16x8_t*>(Q + ((((long)step * P + i) * 2 + g) * OPad + oo) * 8) = o;
+        }
     }
 }
 

@@ -23,6 +23,7 @@
 #include "kernels_direct.hpp"
 #include "launchers.hpp"
 #include "kernels_conv_bf16.hpp"    // tp_items
+#include "kernels_conv_parts.hpp"   // its LDS geometry (no instance is built here)
 #include "kernels_wgrad_tr.hpp"     // its LDS geometry
 #include "kernels_wgrad_bf16.hpp"   // its LDS geometry, which the planner shares (no instance is built here)
 #include "kernels_pack.hpp"
@@ -113,6 +114,7 @@ struct Layer {
     bool class_fused = false;             // last FC handled by class_layer_kernel
     ChanTiling fwd_ct{}, dgrad_ct{};
     bool fwd_bm = false, dgrad_bm = false; // bf16 storage: multiply on the bf16 matrix instruction
+    bool parts = false;                   // fp32 storage: conv_parts_kernel, three bf16 parts per number
     int fwd_rpad = 0, dgrad_rpad = 0;     // reduced channels padded to 16
     size_t fwd_pack_off = 0, fwd_pack_len = 0, dgrad_pack_off = 0, dgrad_pack_len = 0;
 };
@@ -122,6 +124,8 @@ struct TilePlan {
     int MP = 0;           // > 0: conv_ts_kernel (result tiles dealt out to the waves), MP position tiles per wave
     size_t lds = 0;
     bool ok = false;
+    int CB = 0, wgs = 0;  // CB > 0: conv_parts_kernel, CB channels per block, wgs workgroups per channel group walking the tiles
+    mpcnn::PartsInstance in{};
 };
 struct WgradPlan {
     bool ok = false;
@@ -410,6 +414,58 @@ TilePlan plan_conv_tiles(int B, int out_r, int out_c, int d, int d2, int k, int 
     return best;
 }
 
+// Channels per block of conv_parts_kernel: 32, or 16 where a layer reduces over no more.
+inline int parts_block(int rpad) { return rpad <= 16 ? 16 : 32; }
+
+// Tile plan of conv_parts_kernel (P parts per number, es bytes per stored element).  Cost of the busiest compute unit
+// in cycles: its tiles' matrix instructions on its four SIMDs, a quarter of their staging and stores (most of it lies under
+// the other resident workgroup's instructions), and one tile's staging in full at the start.
+TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, int k, int k2, int cr, int rpad, int co,
+                         const ChanTiling& ct, int P, size_t es, bool back, int hint_pt, int hint_mp)
+{
+    TilePlan best;
+    double best_cost = 0;
+    const int fh = ceil_div(out_r, d), fw = ceil_div(out_c, d2);
+    const int CB = parts_block(rpad), steps = k * k2 * rpad / 16, nblk = ceil_div(rpad, CB);
+    const int RP = mpcnn::parts_round(CB);
+    const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);
+    for (const mpcnn::PartsInstance& in : mpcnn::kPartsInstances) {
+        const int PT = in.WP * in.MP, per_wave = in.MO * in.MP;
+        if (in.WO * in.MO != ct.OT) continue;
+        // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
+        if (in.MO == 2 && ceil_div(co, 32) % 2) continue;
+        if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
+        const double eff = per_wave >= 4 ? 1.0 : (per_wave == 2 ? 1.08 : 1.3);
+        const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
+        for (int ty = 1; ty <= std::min(fh, 32 * PT); ++ty)
+            for (int tx = 1; tx <= std::min(fw, 32 * PT / ty); ++tx) {
+                const int npos = (ty + k - 1) * (tx + k2 - 1), rounds = ceil_div(npos, RP);
+                if (rounds > mpcnn::parts_items(P)) break;
+                const size_t lds = rounds * RP * pitch;
+                if (lds > (size_t)80 * 1024) break;
+                // (byte offsets inside a tile's halo are 31 bits)
+                if (((size_t)(ty + k - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) break;
+                const int nty = ceil_div(fh, ty), ntx = ceil_div(fw, tx);
+                const long tiles = (long)B * d * d2 * nty * ntx;
+                if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
+                const long wgs = std::min<long>(tiles, std::max(1, 2 * kNumCU / ct.split));
+                const double per_wg = (double)((tiles + wgs - 1) / wgs);
+                const double per_cu = per_wg * std::ceil((double)wgs * ct.split / kNumCU);
+                const double t_rest = (double)npos * cr * es / 10 + 2500.0 * nblk + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
+                const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * t_mul + 0.25 * t_rest) + t_rest;
+                if (!best.ok || cost < best_cost) {
+                    best.PT = PT; best.NW = 4; best.MP = in.MP; best.Ty = ty; best.Tx = tx;
+                    best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
+                    best.CB = CB; best.wgs = (int)wgs; best.in = in;
+                    best_cost = cost;
+                }
+            }
+    }
+    if (!best.ok && (hint_pt || hint_mp))   // a pair that no instance serves
+        return plan_conv_parts(B, in_c, out_r, out_c, d, d2, k, k2, cr, rpad, co, ct, P, es, back, 0, 0);
+    return best;
+}
+
 unsigned magic_of(unsigned x) { return x <= 1 ? 0u : (unsigned)(((1ull << 32) + x - 1) / x); }
 
 WgradPlan plan_wgrad(const Layer& ly, int B, int in_r, int in_c, int out_r, int out_c, bool bm)
@@ -653,7 +709,10 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         size_t bytes = es * (size_t)B * r * c * ly.cout;
         max_act = std::max(max_act, bytes);
         if (ly.kind == MPCNN_MP) continue;
-        if (ly.fwd_mfma) g->fwd[l] = plan_conv_tiles(B, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.fwd_rpad, ly.fwd_ct, ly.fwd_bm, net->hint_pt, net->hint_mp);
+        if (ly.fwd_mfma && ly.parts)
+            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct, 3, es, false,
+                                        net->hint_pt, net->hint_mp);
+        else if (ly.fwd_mfma) g->fwd[l] = plan_conv_tiles(B, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.fwd_rpad, ly.fwd_ct, ly.fwd_bm, net->hint_pt, net->hint_mp);
         if (training && ly.class_fused) {
             g->partial_n[l] = class_blocks(net, (long)B * r * c);
             g->partial_len[l] = ly.p_len;
@@ -814,16 +873,27 @@ void persistent_grid(mpcnn::ConvArgs* a, dim3* grid, int split)
     grid->x = (unsigned)std::min<long>(grid->x, std::max(1, 2 * kNumCU / split));
 }
 
+// conv_parts_kernel: the plan's workgroups walk the tiles; its divisors' magic numbers
+void parts_grid(mpcnn::ConvArgs* a, dim3* grid, const TilePlan& tp)
+{
+    a->tiles_total = (int)grid->x;
+    a->mg_hw = magic_of((unsigned)(a->Tx + a->k2 - 1)); a->mg_tx = magic_of((unsigned)a->Tx);
+    a->mg_ntx = magic_of((unsigned)a->ntx); a->mg_nty = magic_of((unsigned)a->nty);
+    a->mg_d = magic_of((unsigned)a->d); a->mg_d2 = magic_of((unsigned)a->d2);
+    grid->x = (unsigned)tp.wgs;
+}
+
 // (the kernel instances live in launch_*.hip, one translation unit per family)
 template <typename T>
 bool launch_conv_mfma(const mpcnn::ConvArgs& a, const ChanTiling& ct, const TilePlan& tp, dim3 grid,
                       hipStream_t st, bool bm = false)
 {
+    if (tp.CB > 0)
+        return a.mode >= mpcnn::kDgradTanh ? mpcnn::launch_conv_parts_f32_back(a, tp.CB, tp.in, grid, tp.lds, st)
+                                           : mpcnn::launch_conv_parts_f32_fwd(a, tp.CB, tp.in, grid, tp.lds, st);
     if (bm) return ct.W == 32 && mpcnn::launch_conv_bm(a, ct.OT, tp.PT, tp.NW, tp.MP, grid, tp.lds, st);
-    if constexpr (std::is_same<T, float>::value)
-        return mpcnn::launch_conv_f32(a, ct.W, ct.OT, tp.PT, tp.NW, tp.MP, grid, tp.lds, st);
-    else
-        return mpcnn::launch_conv_b16(a, ct.W, ct.OT, tp.PT, tp.NW, tp.MP, grid, tp.lds, st);
+    if constexpr (std::is_same<T, float>::value) return false;
+    else return mpcnn::launch_conv_b16(a, ct.W, ct.OT, tp.PT, tp.NW, tp.MP, grid, tp.lds, st);
 }
 template <typename T>
 bool launch_wgrad_mfma(const mpcnn::WgradArgs& a, int hl, dim3 grid, size_t lds, hipStream_t st)
@@ -866,7 +936,7 @@ bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipS
 mpcnn_status set_lds_attrs(bool bf16_storage)
 {
     if (bf16_storage) { HIP_TRY(mpcnn::conv_attrs_b16()); HIP_TRY(mpcnn::wgrad_attrs_b16()); }
-    else { HIP_TRY(mpcnn::conv_attrs_f32()); HIP_TRY(mpcnn::wgrad_attrs_f32()); }
+    else { HIP_TRY(mpcnn::conv_parts_attrs_f32_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_f32_back()); HIP_TRY(mpcnn::wgrad_attrs_f32()); }
     return MPCNN_OK;
 }
 
@@ -925,6 +995,19 @@ mpcnn_status refresh_packs(mpcnn_net* net, hipStream_t st)
         const Layer& ly = net->layers[l];
         if (ly.kind == MPCNN_MP) continue;
         const float* Wc = net->d_wread + ly.p_off;
+        if (ly.parts) {
+            if (ly.fwd_mfma)
+                LAUNCH("pack_weights", l, 0, 0, 10.0 * ly.fwd_pack_len,
+                       mpcnn::pack_parts_kernel<3><<<grid_for((long)ly.fwd_pack_len / 12), 256, 0, st>>>(
+                           Wc, (mpcnn::bf16*)(net->d_packs + ly.fwd_pack_off), ly.k * ly.k2, ly.cin, ly.cout, ly.fwd_rpad,
+                           ly.fwd_ct.pad, parts_block(ly.fwd_rpad), 0));
+            if (ly.dgrad_mfma && l > 0)
+                LAUNCH("pack_weights", l, 0, 0, 10.0 * ly.dgrad_pack_len,
+                       mpcnn::pack_parts_kernel<3><<<grid_for((long)ly.dgrad_pack_len / 12), 256, 0, st>>>(
+                           Wc, (mpcnn::bf16*)(net->d_packs + ly.dgrad_pack_off), ly.k * ly.k2, ly.cin, ly.cout, ly.dgrad_rpad,
+                           ly.dgrad_ct.pad, parts_block(ly.dgrad_rpad), 1));
+            continue;
+        }
         if (ly.fwd_mfma && ly.fwd_bm)
             LAUNCH("pack_weights", l, 0, 0, 6.0 * ly.fwd_pack_len,
                    mpcnn::pack_weights_bf16_kernel<<<grid_for((long)ly.fwd_pack_len), 256, 0, st>>>(
@@ -1044,9 +1127,10 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.Ty = tp.Ty; a.Tx = tp.Tx; a.nty = tp.nty; a.ntx = tp.ntx;
                 a.mode = ly.tanh_out ? kFwdTanh : kFwdLinear; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.fwd_ct.split);
-                if (ly.fwd_bm) persistent_grid(&a, &grid, ly.fwd_ct.split);
+                if (tp.CB > 0) { parts_grid(&a, &grid, tp); a.wraw = Wk; }
+                else if (ly.fwd_bm) persistent_grid(&a, &grid, ly.fwd_ct.split);
                 bool launched = false;
-                LAUNCH(ly.fwd_bm ? "conv_fwd_bm" : "conv_fwd_mfma", l, step, flops, bytes,
+                LAUNCH(tp.CB > 0 ? "conv_fwd_parts" : ly.fwd_bm ? "conv_fwd_bm" : "conv_fwd_mfma", l, step, flops, bytes,
                        launched = launch_conv_mfma<T>(a, ly.fwd_ct, tp, grid, st, ly.fwd_bm));
                 if (!launched)   // a plan without a kernel instance: a planner bug, never a silent skip
                     return fail(MPCNN_EUNSUPPORTED, "layer %zu: no convolution kernel instance for its forward plan", l);
@@ -1260,9 +1344,10 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                 a.Ty = tp.Ty; a.Tx = tp.Tx; a.nty = tp.nty; a.ntx = tp.ntx;
                 a.mode = below_tanh ? kDgradTanh : kDgradPlain; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.dgrad_ct.split);
-                if (ly.dgrad_bm) persistent_grid(&a, &grid, ly.dgrad_ct.split);
+                if (tp.CB > 0) { parts_grid(&a, &grid, tp); a.wraw = Wk; }
+                else if (ly.dgrad_bm) persistent_grid(&a, &grid, ly.dgrad_ct.split);
                 bool launched = false;
-                LAUNCH(ly.dgrad_bm ? "conv_dgrad_bm" : "conv_dgrad_mfma", li, dstep, flops, dbytes,
+                LAUNCH(tp.CB > 0 ? "conv_dgrad_parts" : ly.dgrad_bm ? "conv_dgrad_bm" : "conv_dgrad_mfma", li, dstep, flops, dbytes,
                        launched = launch_conv_mfma<T>(a, ly.dgrad_ct, tp, grid, st, ly.dgrad_bm));
                 if (!launched)
                     return fail(MPCNN_EUNSUPPORTED, "layer %zu: no convolution kernel instance for its data-gradient plan", li);
@@ -1473,22 +1558,23 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
             ly.dgrad_mfma = l > 0 && ly.cout % 4 == 0 && ly.cout >= 8 && ly.cin >= 8;
             ly.wgrad_mfma = !ly.class_fused;   // any shape: gradient rows are tiled in parameter order
             // (the convolution kernels address a layer's weight pack by 32-bit byte offsets)
-            const size_t pack_bound = (size_t)ly.k * ly.k2 * (ceil_div(std::max(ly.cin, ly.cout), 32) * 32 + 32) *
-                                      (ceil_div(std::max(ly.cin, ly.cout), 32) * 32 + 32) * 4;
+            const size_t pack_bound = (size_t)ly.k * ly.k2 * (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) *
+                                      (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) * (net->bf16 ? 4 : 6);
             if (pack_bound >= (1ull << 31)) ly.fwd_mfma = ly.dgrad_mfma = false;
             // bf16 storage with channel counts that are multiples of 8: the bf16 matrix instruction
             ly.fwd_bm = net->bf16 && !ly.rect && ly.fwd_mfma && ly.cin % 8 == 0;
             ly.dgrad_bm = net->bf16 && !ly.rect && ly.dgrad_mfma && ly.cout % 8 == 0;
+            ly.parts = !net->bf16;
             if (ly.fwd_mfma) {
-                ly.fwd_ct = ly.fwd_bm ? chan_tiling_w(ly.cout, 32) : chan_tiling(ly.cout);
+                ly.fwd_ct = ly.fwd_bm || ly.parts ? chan_tiling_w(ly.cout, 32) : chan_tiling(ly.cout);
                 ly.fwd_rpad = ceil_div(ly.cin, 16) * 16;
-                ly.fwd_pack_len = (size_t)ly.k * ly.k2 * ly.fwd_rpad * ly.fwd_ct.pad;
+                ly.fwd_pack_len = (size_t)ly.k * ly.k2 * ly.fwd_rpad * ly.fwd_ct.pad * (ly.parts ? 3 : 2) / 2;   // in floats
                 ly.fwd_pack_off = pack; pack += ly.fwd_pack_len;
             }
             if (ly.dgrad_mfma) {
-                ly.dgrad_ct = ly.dgrad_bm ? chan_tiling_w(ly.cin, 32) : chan_tiling(ly.cin);
+                ly.dgrad_ct = ly.dgrad_bm || ly.parts ? chan_tiling_w(ly.cin, 32) : chan_tiling(ly.cin);
                 ly.dgrad_rpad = ceil_div(ly.cout, 16) * 16;
-                ly.dgrad_pack_len = (size_t)ly.k * ly.k2 * ly.dgrad_rpad * ly.dgrad_ct.pad;
+                ly.dgrad_pack_len = (size_t)ly.k * ly.k2 * ly.dgrad_rpad * ly.dgrad_ct.pad * (ly.parts ? 3 : 2) / 2;
                 ly.dgrad_pack_off = pack; pack += ly.dgrad_pack_len;
             }
         }
@@ -1564,6 +1650,12 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
     };
     auto conv = [&](const char* what, const Layer& ly, const TilePlan& tp, const ChanTiling& ct, bool bm) {
         if (!tp.ok) { put("  %s: plain kernel\n", what); return; }
+        if (tp.CB > 0) {
+            put("  %s: bf16 MFMA, three parts per number, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
+                "tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what, ct.OT, ct.split, tp.PT, tp.in.WO,
+                tp.in.WP, tp.in.MO, tp.in.MP, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
+            return;
+        }
         put("  %s: %s %d-wide x %d channel tiles x %d groups, %d position tiles (%d per wave), %d waves, tile %d x %d of a "
             "residue class, %d x %d tiles, %zu B LDS\n", what,
             bm ? "bf16 MFMA, tile per wave," : (tp.MP > 0 ? "fp32 MFMA, tile per wave," : "fp32 MFMA, split reduction,"),

@@ -1,0 +1,108 @@
+"""fp32 convolutions and weight gradients whose products are made of bf16 parts (csrc/kernels_conv_parts.hpp,
+csrc/kernels_wgrad_parts.hpp): shapes at the edges of their tiles, channel blocks and groups against the oracle,
+numbers that have no parts, and the distance from 64-bit sums."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1302_1690_amd import mpcnn, workloads as wl
+from test_gpu_parity import full_parity
+
+pytestmark = pytest.mark.gpu
+C, MP, FC = wl.C, wl.MP, wl.FC
+
+# channel counts 4 mod 8, one past a block of 16 / 32 channels, one past a group of 4 channel tiles; filters of
+# side 1, 2, 3, 5; maps of a few positions up to several ragged tiles
+EDGES = [
+    ("quads", ((C, 12, 3), (MP, 0, 2), (C, 20, 2), (FC, 36, 0), (FC, 3, 0)), 14, 31, 38),
+    ("past_a_group", ((C, 8, 3), (C, 132, 3), (MP, 0, 2), (C, 36, 2), (FC, 8, 0), (FC, 2, 0)), 14, 40, 33),
+    ("units", ((C, 16, 3), (MP, 0, 2), (FC, 44, 0), (FC, 10, 0), (FC, 9, 0), (FC, 2, 0)), 4, 37, 41),
+    ("wide_filter", ((C, 40, 2), (C, 17, 5), (MP, 0, 3), (C, 24, 2), (FC, 33, 0), (FC, 2, 0)), 12, 52, 47),
+    ("one_position", ((C, 16, 3), (MP, 0, 2), (C, 32, 3), (FC, 64, 0), (FC, 2, 0)), 10, 10, 10),
+]
+
+
+@pytest.mark.parametrize("name,layers,patch,height,width", EDGES, ids=[e[0] for e in EDGES])
+def test_tile_and_channel_edges(name, layers, patch, height, width):
+    full_parity(wl.Workload("parts_" + name, layers, patch, 1, layers[-1][1], 2, height, width, 0.2, "ellipses",
+                            seed_image=1141, seed_label=2141, seed_param=3141), with_pixw=True)
+
+
+def activations(net, layers, image, params):
+    """The library's output of the second layer and, from its first layer's, the sums behind it in 64 bits: the
+    sum, the sum of the products' sizes, and the root of the sum of their squares."""
+    B, _, H, W = image.shape
+    net.set_params(params)
+    net.seg_backward(image, torch.zeros((B, H, W), dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    x, y = net.get_activation(B, H, W, 0), net.get_activation(B, H, W, 1)
+    (_, m0, k0), (_, m1, k1) = layers[0], layers[1]
+    at = m0 * k0 * k0 + m0
+    w = torch.from_numpy(params[at:at + m1 * m0 * k1 * k1].reshape(m1, m0, k1, k1)).double()
+    b = torch.from_numpy(params[at + w.numel():at + w.numel() + m1]).double()
+    x64 = torch.from_numpy(x).double().permute(0, 3, 1, 2)
+    conv = torch.nn.functional.conv2d
+    sums = (conv(x64, w, b), conv(x64.abs(), w.abs(), b.abs()), conv(x64 * x64, w * w, b * b).sqrt())
+    return (y,) + tuple(t.permute(0, 2, 3, 1).numpy() for t in sums)
+
+
+def test_sums_are_as_close_as_fp32_ones():
+    """tanh of a sum of 576 products in 36 steps of six instructions.  A rounding moves the running sum by at most 2^-24
+    of its size, so 216 of them by at most 216 2^-24 of the products' absolute sum; in the root mean square, by
+    sqrt(216 / 3) 2^-24 of the running sum's root mean square, which random signs keep below the root of the sum of
+    squares.  What is left out of the products is 2^-26 of each; the hardware exp2 and reciprocal bring 2e-7 (1.2e-7 rms).
+    576 fp32 additions one after the other would be allowed sqrt(576 / 3)."""
+    layers = ((C, 64, 3), (C, 96, 3), (FC, 8, 0), (FC, 2, 0))
+    net = mpcnn.Net(layers, 1, 6)
+    rng = np.random.default_rng(5)
+    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, 40, 43)).astype(np.float32)).cuda()
+    params = (0.05 * rng.standard_normal(net.param_count) * np.exp(rng.standard_normal(net.param_count))).astype(np.float32)
+    y, pre, mass, spread = activations(net, layers, image, params)
+    err = np.abs(y - np.tanh(pre))
+    assert (err <= (216 * 2.0 ** -24 + 2.0 ** -26) * mass + 2e-7).all()
+    rms = lambda v: np.sqrt((v ** 2).mean())
+    assert rms(err) <= np.hypot(np.sqrt(216 / 3) * 2.0 ** -24 * rms(spread) + 2.0 ** -26 * rms(spread), 1.2e-7)
+    net.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.395e38])
+def test_numbers_without_parts(value):
+    """Infinities, NaN and numbers above the largest bf16 in a layer's weights reach the outputs that use
+    them as fp32 arithmetic has it, and no others."""
+    layers = ((C, 16, 3), (C, 40, 3), (FC, 8, 0), (FC, 2, 0))
+    net = mpcnn.Net(layers, 1, 6)
+    rng = np.random.default_rng(6)
+    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, 30, 27)).astype(np.float32)).cuda()
+    params = rng.uniform(-0.2, 0.2, net.param_count).astype(np.float32)
+    at = 16 * 9 + 16
+    params[at + (37 * 16 + 5) * 9 + 4] = value           # map 37, channel 5, middle tap
+    y, pre, _, _ = activations(net, layers, image, params)
+    want = np.tanh(pre)
+    assert np.array_equal(np.isnan(y), np.isnan(want))
+    ok = ~np.isnan(want)
+    assert np.isfinite(y[ok]).all() and np.abs(y[ok] - want[ok]).max() <= 1e-6
+    net.close()
+
+
+def test_delta_that_is_not_finite_stays_where_it_is():
+    """A pixel weight of NaN: the deltas of the positions its patch covers are NaN, every activation and the other
+    pixels' probabilities are what they were."""
+    layers = ((C, 16, 3), (C, 32, 3), (FC, 24, 0), (FC, 2, 0))
+    net = mpcnn.Net(layers, 1, 6)
+    rng = np.random.default_rng(7)
+    B, H, W = 1, 24, 29
+    image = torch.from_numpy(rng.uniform(0, 1, (B, 1, H, W)).astype(np.float32)).cuda()
+    labels = torch.zeros((B, H, W), dtype=torch.int32, device="cuda")
+    net.set_params(rng.uniform(-0.2, 0.2, net.param_count).astype(np.float32))
+    out = []
+    for bad in (False, True):
+        pixw = torch.ones((B, H, W), device="cuda")
+        if bad:
+            pixw[0, 10, 12] = float("nan")
+        probs = torch.empty((B, 2, H - 5, W - 5), device="cuda")
+        net.seg_backward(image, labels, pixw=pixw, probs=probs)
+        out.append((probs.cpu().numpy(), net.get_grads()))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.isfinite(out[0][1]).all() and np.isnan(out[1][1]).all()
+    net.close()
