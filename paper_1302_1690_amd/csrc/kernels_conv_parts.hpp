@@ -60,15 +60,22 @@ __host__ __device__ constexpr int parts_steps(int parts, int CB, int taps, int r
     return (rpad / CB) * parts_block_steps(parts, taps, CB / 16) + (rpad % CB ? parts_block_steps(parts, taps, rpad % CB / 16) : 0);
 }
 
-// x = x0 + x1 + x2 exactly (8 numbers at once)
-__device__ __forceinline__ void split_parts(const float (&x)[8], bf16x8 (&p)[3])
+// x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: three conversions, four shifts or masks and four
+// subtractions each)
+__device__ __forceinline__ void split_parts(const float (&x)[8], u32x4 (&p)[3])
 {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const __bf16 a = (__bf16)x[j];
-        const float r = x[j] - (float)a;
-        const __bf16 b = (__bf16)r;
-        p[0][j] = a; p[1][j] = b; p[2][j] = (__bf16)(r - (float)b);
+    for (int j = 0; j < 4; ++j) {
+        float lo = x[2 * j], hi = x[2 * j + 1];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+            p[i][j] = two;
+            lo -= __builtin_bit_cast(float, two << 16);
+            hi -= __builtin_bit_cast(float, two & 0xffff0000u);
+        }
     }
 }
 
@@ -172,10 +179,10 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 float x[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
-                bf16x8 p[3];
+                u32x4 p[3];
                 split_parts(x, p);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x8*>(dst + 32 * i) = p[i];
+                for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
             } else
                 *reinterpret_cast<u32x4*>(dst) = pre[u][0];
         }

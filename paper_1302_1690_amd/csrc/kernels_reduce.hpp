@@ -20,7 +20,9 @@ struct ReduceSeg {
     float* out;
     long plen;          // floats per partial
     int items, n, block0;
-    int tiled, Nt, rows_total, Co;   // tiled: 0 flat, 1 tiled, 2 the per-workgroup loss shares (fp64), 3 tiled with the bias as row rows_total
+    int tiled, Nt, rows_total, Co;   // tiled: 0 flat, 1 tiled, 2 the per-workgroup loss shares (fp64), 3 tiled with the bias as row rows_total,
+                                     // 4 tiled with row tiles of two units (wgrad_parts_kernel), which the rest describes
+    int RT, ppg, tpg, ntg, Ci, kk;   // row tiles, planes and taps per group, groups along the taps; layer inputs, taps
 };
 struct ReduceArgs {
     ReduceSeg seg[kMaxReduceSegs];
@@ -125,11 +127,19 @@ __global__ __launch_bounds__(256) void reduce_all_kernel(ReduceArgs a)
         if (e < tile_items) {
             const int tile = e >> 8, r4 = (e >> 6) & 3, l = e & 63;
             const int mt = tile / sg.Nt, nt = tile - mt * sg.Nt;
-            const int row0 = 32 * mt + 8 * r4 + 4 * (l >> 5), oc = 32 * nt + (l & 31);
+            const int oc = 32 * nt + (l & 31);
+            int row0 = 32 * mt + 8 * r4 + 4 * (l >> 5), valid = rows_out - row0;
+            if (sg.tiled == 4) {   // a unit = 16 channels of one tap
+                const int grp = mt / sg.RT, sub = 8 * r4 + 4 * (l >> 5), lu = 2 * (mt - grp * sg.RT) + (sub >> 4);
+                const int pl = lu / sg.tpg, tap = (grp % sg.ntg) * sg.tpg + lu - pl * sg.tpg;
+                const int c = 16 * ((grp / sg.ntg) * sg.ppg + pl) + (sub & 15);
+                row0 = tap * sg.Ci + c;
+                valid = lu < sg.ppg * sg.tpg && tap < sg.kk ? sg.Ci - c : 0;
+            }
             if (oc < sg.Co)
 #pragma unroll
                 for (int z = 0; z < 4; ++z)
-                    if (row0 + z < rows_out) {
+                    if (z < valid) {
                         float* o = sg.out + (long)(row0 + z) * sg.Co + oc;
                         *o = a.accumulate ? *o + r[z] : r[z];
                     }

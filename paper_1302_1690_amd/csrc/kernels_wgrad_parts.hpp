@@ -1,0 +1,392 @@
+// Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_bf16, every fp32
+// number as the sum of three bf16 parts, six products each (kernels_conv_parts.hpp has the arithmetic and its
+// accuracy; here too the sums come out closer to the 64-bit ones than on the fp32 instruction).
+//
+//   dW[tap][c][o] = sum over positions of in[pos + tap][c] * dY[pos][o]        (Alg. 2)
+//
+// As in the other weight-gradient kernels the result is tiny and the contraction runs over all positions:
+// blockIdx.x = slab of tiles, the workgroup's share of the result stays in accumulators for the whole
+// slab, reduce_all_kernel adds the slabs.  The instruction contracts 16 positions, a lane supplying 8 of
+// them for ONE gradient row or output channel; the transposing LDS read (ds_read_b64_tr_b16, see
+// kernels_wgrad_tr.hpp) gives that from channels-last tiles.
+//
+// Layout.  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
+// position: the 16 lanes that read 4 positions together meet no bank twice, and with a plane pitch of 128 mod 256
+// bytes neither do the 32 of two planes).  Parts, the second half of an operand and successive chunks are immediates.  A
+// gradient row tile is two UNITS of 16 rows, a unit being (plane, tap): the two halves of the lanes
+// address their units separately, so 16-channel layers fill row tiles with two taps and 100 channels pad
+// to 112, not 128.
+//
+// Waves.  Eight waves = wm (row tiles) x wn (column tiles) x wk (positions), each with PM x 1 result
+// tiles: a chunk of 16 positions is PM + 1 operands of three parts for 6 PM instructions, 70 bytes per cycle of
+// LDS reads for PM = 8 with the matrix pipes full.  The operands of row tile p + 1 are fetched while p is multiplied.
+// Two LDS buffers: tile t + 1 is split into parts and written while tile t is multiplied, one barrier per tile;
+// of the two waves of a SIMD one writes before it multiplies and the other after, so that one's
+// conversions lie under the other's instructions.
+//
+// Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), before (fp32 instruction) and
+// now: 985, 1780, 1210, 2030 us -> 506, 967, 683, 1243 us (206, 208, 204, 148 TFLOP/s; what the split instruction sustains on
+// random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 50-70 % at the clock the power
+// limit leaves.  The conversions decide the rest: with every item's address worked out per tile and numbers
+// converted one by one (480 vector instructions per thread and tile of 32 positions instead of 300) it was 575, 1062, 811, 1540.
+#pragma once
+#include "kernels_conv_parts.hpp"
+#include "kernels_wgrad_tr.hpp"
+
+namespace mpcnn {
+
+constexpr int kWpThreads = 512;
+constexpr int kWpItems = 4;       // 8-channel items per thread and tile, at most
+constexpr int kWpMaxTiles = 9;    // row tiles per wave
+constexpr int kWpPos = 96;        // LDS bytes of a position of one plane
+
+struct WgradPartsArgs {
+    const float* in;     // [B][Hi][Wi][Ci]  layer input
+    const float* dY;     // [B][Ho][Wo][Co]  delta w.r.t. the layer's pre-activation
+    float* partial;      // [slab][group][row tile][column tile][4][64 lanes][4], then [Nt*32] bias sums
+    int B, Hi, Wi, Ci, Ho, Wo, Co;
+    int k, k2, d, d2;    // filter rows, columns; spacing of rows, columns
+    int R, nch;          // tile = R rows x 16*nch columns of one residue class
+    int nty, ntx, tiles_total, tiles_per_slab;
+    int Nt, RT;          // 32-column tiles of the result; row tiles of a group
+    int wm, wn, wk;      // wm * wn * wk = 8
+    int ppg, tpg, ntg;   // planes and taps per group; groups along the taps (blockIdx.y = plane group * ntg + tap group)
+    unsigned mg_nqh, mg_hwp, mg_txp, mg_tpg, mg_k2, mg_ntx, mg_nty, mg_d, mg_d2;   // ceil(2^32 / x)
+};
+
+// LDS geometry shared with the host's plan (bytes)
+struct WpGeom { int hh, hwp, hplane, dplane, halo_b, buf_b, nh, nd; };   // nh, nd: items of the halo (rounded up to whole waves) and of the delta tile
+__host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg, int wn)
+{
+    WpGeom g;
+    g.hh = R + k - 1; g.hwp = 16 * nch + k2 - 1;
+    g.hplane = (((g.hh * g.hwp + 3) / 8) * 8 + 4) * kWpPos;       // positions = 4 mod 8, at least hh * hwp
+    g.dplane = (16 * R * nch + 4) * kWpPos;
+    g.halo_b = 2 * wn * g.dplane;
+    g.buf_b = g.halo_b + ppg * g.hplane;
+    g.nh = (g.hh * g.hwp * 2 * ppg + 63) / 64 * 64;
+    g.nd = 16 * R * nch * 4 * wn;
+    return g;
+}
+
+template <int PM>
+__global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsArgs a)
+{
+    constexpr int SI = kWpItems;
+    constexpr unsigned kNone = 0x80000000u;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    char* ldsb = reinterpret_cast<char*>(lds);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = a.wn;
+    const int nidx = wave & (wn - 1);
+    const int midx = __builtin_amdgcn_readfirstlane((wave / wn) % a.wm);
+    const int kidx = __builtin_amdgcn_readfirstlane(wave / (wn * a.wm));
+    const WpGeom g = wp_geom(a.R, a.nch, a.k, a.k2, a.ppg, wn);
+    const int txp = 16 * a.nch;
+    const int p0 = (blockIdx.y / a.ntg) * a.ppg, tap0 = (blockIdx.y % a.ntg) * a.tpg;   // first plane, first tap of the group
+    const int nt = blockIdx.z * wn + nidx;
+    const bool active = midx * PM < a.RT && nt < a.Nt;
+
+    // ---- staging items: it = tid + 512 u; below nh the halo, a whole wave at a time, then the delta tile.  What an item
+    // is never changes, so its place is worked out once; a tile inside the tensors (most) takes every load
+    // at the item's offset from a scalar base, the others check its coordinates.
+    const int nqh = 2 * a.ppg, nqd = 4 * wn;
+    const int qd = tid & (nqd - 1);                   // octet of this thread's delta items (512 and nh are multiples of nqd)
+    unsigned i_off[SI];                               // bytes from the tile's first element (kNone: no such item)
+    unsigned i_yx[SI];                                // row << 16 | column in the halo / the tile; top bit: only the first four channels exist
+    unsigned i_dst[SI];                               // bytes in a buffer
+    const bool whole = (a.Ci & 7) == 0 && (a.Co & 7) == 0;   // no item has only four channels (uniform)
+#pragma unroll
+    for (int u = 0; u < SI; ++u) {
+        const int first = kWpThreads * u + 64 * wave;  // uniform
+        unsigned y, x;
+        int left;                                      // channels from the item's first on
+        if (first < g.nh) {
+            const unsigned it = first + lane;
+            const unsigned pos = parts_div(it, a.mg_nqh, nqh), q = it - pos * nqh;
+            y = parts_div(pos, a.mg_hwp, g.hwp); x = pos - y * g.hwp;
+            left = a.Ci - (16 * p0 + 8 * (int)q);
+            const bool ok = y < (unsigned)g.hh && left > 0;
+            i_off[u] = ok ? 4u * ((y * a.d * a.Wi + x * a.d2) * a.Ci + 16 * p0 + 8 * q) : kNone;
+            // (what lies past the halo's last position goes to the padding of the last delta plane)
+            i_dst[u] = y < (unsigned)g.hh ? g.halo_b + (q >> 1) * g.hplane + pos * kWpPos + (q & 1) * 16 : g.halo_b - kWpPos;
+        } else {
+            const unsigned m = (unsigned)(first - g.nh + lane) / (unsigned)nqd;
+            y = parts_div(m, a.mg_txp, txp); x = m - y * txp;
+            const int oc = 32 * wn * blockIdx.z + 8 * qd;
+            left = a.Co - oc;
+            const bool ok = y < (unsigned)a.R && left > 0;
+            i_off[u] = ok ? 4u * ((y * a.d * a.Wo + x * a.d2) * a.Co + oc) : kNone;
+            i_dst[u] = (qd >> 1) * g.dplane + m * kWpPos + (qd & 1) * 16;
+        }
+        i_yx[u] = (left <= 4 ? 0x80000000u : 0u) | (y << 16) | x;
+    }
+    u32x4 pre[SI][2];
+    float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
+#pragma unroll
+    for (int j = 0; j < 8; ++j) bsum[j] = 0.f;
+    struct Tile { int b, ry, rx, ty0, tx0, rows, cols; };
+    auto decode = [&](int tile) {
+        Tile t;
+        unsigned bid = tile;
+        unsigned qq = parts_div(bid, a.mg_ntx, a.ntx);
+        t.tx0 = (int)(bid - qq * a.ntx) * txp; bid = qq;
+        qq = parts_div(bid, a.mg_nty, a.nty);
+        t.ty0 = (int)(bid - qq * a.nty) * a.R; bid = qq;
+        qq = parts_div(bid, a.mg_d2, a.d2);
+        t.rx = bid - qq * a.d2; bid = qq;
+        qq = parts_div(bid, a.mg_d, a.d);
+        t.ry = bid - qq * a.d;
+        t.b = qq;
+        const int fh = t.ry < a.Ho ? (int)parts_div(a.Ho - t.ry + a.d - 1, a.mg_d, a.d) : 0;
+        const int fw = t.rx < a.Wo ? (int)parts_div(a.Wo - t.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
+        t.rows = fh - t.ty0; t.cols = fw - t.tx0;     // of the tile inside its residue class (may be <= 0, or more than the tile's)
+        return t;
+    };
+    // loads of tile `tile` (all issued on every path; what lies outside comes as zeros)
+    auto issue = [&](int tile, bool any) {
+        const Tile t = decode(tile);
+        const int y0 = t.ty0 * a.d + t.ry, x0 = t.tx0 * a.d2 + t.rx;
+        const __amdgpu_buffer_rsrc_t in_r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(a.in + (((long)t.b * a.Hi + y0) * a.Wi + x0) * a.Ci), 0, 0x7fffffff, 0x00020000);
+        const __amdgpu_buffer_rsrc_t dy_r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(a.dY + (((long)t.b * a.Ho + y0) * a.Wo + x0) * a.Co), 0, 0x7fffffff, 0x00020000);
+        const bool inside = any && t.rows >= a.R && t.cols >= txp && y0 + (g.hh - 1) * a.d < a.Hi && x0 + (g.hwp - 1) * a.d2 < a.Wi;
+#pragma unroll
+        for (int u = 0; u < SI; ++u) {
+            const bool halo = kWpThreads * u + 64 * wave < g.nh;   // uniform
+            const __amdgpu_buffer_rsrc_t r = halo ? in_r : dy_r;
+            unsigned off = i_off[u];
+            if (!inside) {
+                const int y = (int)(i_yx[u] >> 16) & 0x7fff, x = (int)(i_yx[u] & 0xffffu);
+                const bool ok = any && (halo ? y0 + y * a.d < a.Hi && x0 + x * a.d2 < a.Wi : y < t.rows && x < t.cols);
+                off = ok ? off : kNone;
+            }
+            const unsigned off4 = whole || !(i_yx[u] >> 31) ? off : kNone;
+            pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+            pre[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off4, 16, 0));
+        }
+    };
+    auto to_lds = [&](char* buf) {
+#pragma unroll
+        for (int u = 0; u < SI; ++u) {
+            const int first = kWpThreads * u + 64 * wave;   // uniform
+            if (first >= g.nh + g.nd) break;
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
+            if (first >= g.nh)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) bsum[j] += x[j];
+            u32x4 p[3];
+            split_parts(x, p);
+            char* dst = buf + i_dst[u];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
+        }
+    };
+
+    // ---- operand addresses: this lane's position and channels inside a plane, and its unit of every row tile
+    const unsigned lds_base = (unsigned)reinterpret_cast<size_t>(lds);
+    const int grp = lane >> 4, r16 = lane & 15;
+    const unsigned lane_b = lds_base + (unsigned)((8 * (grp >> 1) + (r16 >> 2)) * kWpPos + (r16 & 3) * 8);
+    const int kk = a.k * a.k2, units = a.ppg * a.tpg;
+    unsigned av[PM];
+#pragma unroll
+    for (int p = 0; p < PM; ++p) {
+        const unsigned lu = 2 * (midx * PM + p) + (grp & 1);
+        const unsigned pl = parts_div(lu, a.mg_tpg, a.tpg), tap = tap0 + lu - pl * a.tpg;
+        const unsigned ta = parts_div(tap, a.mg_k2, a.k2), tb = tap - ta * a.k2;
+        const bool ok = lu < (unsigned)units && tap < (unsigned)kk;   // (else: any address inside, never stored)
+        av[p] = lane_b + g.halo_b + (ok ? pl * g.hplane + (ta * g.hwp + tb) * kWpPos : 0u);
+    }
+    const unsigned bv = lane_b + (unsigned)(2 * nidx + (grp & 1)) * (unsigned)g.dplane;
+
+    v16f acc[PM];
+#pragma unroll
+    for (int p = 0; p < PM; ++p)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[p][r] = 0.f;
+
+    struct Op { tr_bf16x8 part[3]; };
+    auto fetch = [&](unsigned addr) {
+        typedef tr_bf16x4 __attribute__((address_space(3))) * lds_ptr;
+        Op o;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const tr_bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(uintptr_t)(addr + 32 * i));
+            const tr_bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(uintptr_t)(addr + 32 * i + 4 * kWpPos));
+            o.part[i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+        return o;
+    };
+    auto mul = [&](const Op& A, const Op& Bo, v16f& c) {
+#define MPCNN_MUL(i, j) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.part[i], Bo.part[j], c, 0, 0, 0)
+        MPCNN_MUL(2, 0); MPCNN_MUL(0, 2); MPCNN_MUL(1, 1); MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); MPCNN_MUL(0, 0);
+#undef MPCNN_MUL
+    };
+    // one tile: the chunks (row, 16 columns) that hold positions, dealt to the wk waves
+    auto multiply = [&](int cur, int rows, int cols) {
+        rows = rows < a.R ? rows : a.R;
+        int nc = (cols + 15) >> 4;
+        nc = nc < a.nch ? nc : a.nch;
+        if (rows <= 0 || nc <= 0) return;
+        const int total = rows * nc;
+        int row = 0, cc = kidx;
+        while (cc >= nc) { cc -= nc; ++row; }
+        const int n = (total - kidx + a.wk - 1) / a.wk;   // this wave's chunks
+        if (n <= 0) return;
+        unsigned ao = 0, bo = 0;
+        auto place = [&]() {
+            ao = (unsigned)(cur * g.buf_b + (row * g.hwp + 16 * cc) * kWpPos);
+            bo = (unsigned)(cur * g.buf_b + (row * txp + 16 * cc) * kWpPos);
+        };
+        place();
+        Op A[2], Bq[2];
+        Bq[0] = fetch(bv + bo);
+        A[0] = fetch(av[0] + ao);
+        int left = n;
+        // two chunks per round: where PM is odd the operand slots change places from one to the next
+        for (;;) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                --left;
+#pragma unroll
+                for (int p = 0; p < PM; ++p) {
+                    const int s = (half * PM + p) & 1;
+                    if (p + 1 < PM) A[s ^ 1] = fetch(av[p + 1] + ao);
+                    else {
+                        if (left > 0) {
+                            cc += a.wk;
+                            while (cc >= nc) { cc -= nc; ++row; }
+                            place();
+                        }
+                        Bq[half ^ 1] = fetch(bv + bo);
+                        A[s ^ 1] = fetch(av[0] + ao);
+                    }
+                    mul(A[s], Bq[half], acc[p]);
+                    __builtin_amdgcn_sched_barrier(0);   // (else the reads of many row tiles are moved up, out of registers)
+                }
+                if (left == 0) return;
+            }
+        }
+    };
+
+    // ---- walk the slab.  Waves 0-3 (one per SIMD) write tile t + 1, loaded a whole tile ahead, before they multiply
+    // tile t; waves 4-7 load it before and write it after.
+    const int tile_begin = blockIdx.x * a.tiles_per_slab;
+    int tile_end = tile_begin + a.tiles_per_slab;
+    if (tile_end > a.tiles_total) tile_end = a.tiles_total;
+    const bool early = wave < 4;
+    if (tile_begin < tile_end) {
+        issue(tile_begin, true);
+        to_lds(ldsb);
+    }
+    if (early) issue(tile_begin + 1 < tile_end ? tile_begin + 1 : tile_begin, tile_begin + 1 < tile_end);
+    __syncthreads();
+    int cur = 0;
+    for (int tile = tile_begin; tile < tile_end; ++tile, cur ^= 1) {
+        char* other = ldsb + (cur ^ 1) * g.buf_b;
+        const bool more = tile + 1 < tile_end;
+        if (early) {
+            if (more) to_lds(other);
+            issue(tile + 2 < tile_end ? tile + 2 : tile, tile + 2 < tile_end);
+        } else
+            issue(more ? tile + 1 : tile, more);
+        if (active) {
+            const Tile t = decode(tile);
+            multiply(cur, t.rows, t.cols);
+        }
+        if (!early && more) to_lds(other);
+        __syncthreads();
+    }
+
+    // ---- partial sums of the waves that shared result tiles (wk > 1) meet in LDS, in a fixed order
+    v4f* lds4 = reinterpret_cast<v4f*>(lds);
+    for (int s = a.wk >> 1; s >= 1; s >>= 1) {
+        if (kidx >= s && kidx < 2 * s) {
+            v4f* dst = lds4 + ((((kidx - s) * a.wm + midx) * wn + nidx) * (PM * 4)) * 64 + lane;
+#pragma unroll
+            for (int p = 0; p < PM; ++p)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
+                    dst[(p * 4 + r4) * 64] = (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
+        }
+        __syncthreads();
+        if (kidx < s) {
+            const v4f* src = lds4 + (((kidx * a.wm + midx) * wn + nidx) * (PM * 4)) * 64 + lane;
+#pragma unroll
+            for (int p = 0; p < PM; ++p)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const v4f v = src[(p * 4 + r4) * 64];
+                    acc[p][4 * r4] += v[0]; acc[p][4 * r4 + 1] += v[1];
+                    acc[p][4 * r4 + 2] += v[2]; acc[p][4 * r4 + 3] += v[3];
+                }
+        }
+        __syncthreads();
+    }
+
+    // ---- this slab's partial sums, result tiles as the accumulator registers hold them
+    const int groups = gridDim.y;
+    const long plen = (long)groups * a.RT * a.Nt * 1024 + a.Nt * 32;
+    float* out = a.partial + (long)blockIdx.x * plen;
+    if (active && kidx == 0) {
+        float z = 0.f;                                // NaN as soon as one of the sums is not finite
+#pragma unroll
+        for (int p = 0; p < PM; ++p)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z = fmaf(acc[p][r], 0.f, z);
+        const bool odd = __any(z != z);
+#pragma unroll
+        for (int p = 0; p < PM; ++p)
+            if (midx * PM + p < a.RT) {
+                v4f* dst = reinterpret_cast<v4f*>(out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024) + lane;
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
+                    dst[r4 * 64] = (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
+            }
+        if (odd) {
+            // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more,
+            // with fp32 multiply-adds over the slab's positions.
+            for (int e = 0; e < PM * 16; ++e) {
+                const int p = e >> 4, r = e & 15;
+                const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int lu = 2 * (midx * PM + p) + (row >> 4);
+                const int pl = lu / a.tpg, tap = tap0 + lu - pl * a.tpg, c = 16 * (p0 + pl) + (row & 15), oc = 32 * nt + (lane & 31);
+                if (midx * PM + p >= a.RT || lu >= units || tap >= kk || c >= a.Ci || oc >= a.Co) continue;
+                float* const o = out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024 + ((r >> 2) * 64 + lane) * 4 + (r & 3);
+                if (__builtin_isfinite(*o)) continue;
+                const int ta = tap / a.k2, tb = tap - ta * a.k2;
+                float sum = 0.f;
+                for (int tile = tile_begin; tile < tile_end && sum == sum; ++tile) {
+                    const Tile t = decode(tile);
+                    for (int y = 0; y < a.R && y < t.rows; ++y)
+                        for (int x = 0; x < txp && x < t.cols; ++x) {
+                            const int oy = (t.ty0 + y) * a.d + t.ry, ox = (t.tx0 + x) * a.d2 + t.rx;
+                            sum = fmaf(a.in[(((long)t.b * a.Hi + oy + ta * a.d) * a.Wi + ox + tb * a.d2) * a.Ci + c],
+                                       a.dY[(((long)t.b * a.Ho + oy) * a.Wo + ox) * a.Co + oc], sum);
+                        }
+                }
+                *o = sum;
+            }
+        }
+    }
+    // ---- bias gradient = column sums of the delta tiles: the threads of one channel octet in thread order
+    if (blockIdx.y == 0) {
+        __syncthreads();
+        float* sums = lds;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sums[tid * 8 + j] = bsum[j];
+        __syncthreads();
+        if (tid < 32 * wn) {
+            const int q = tid >> 3, j = tid & 7, bt = blockIdx.z * wn + (tid >> 5);
+            float s = 0.f;
+            for (int i = q; i < kWpThreads; i += nqd) s += sums[i * 8 + j];
+            if (bt < a.Nt) out[(long)groups * a.RT * a.Nt * 1024 + bt * 32 + (tid & 31)] = s;
+        }
+    }
+}
+
+}  // namespace mpcnn

@@ -1,0 +1,30 @@
+// Instances of wgrad_parts_kernel: row tiles per wave.
+#include "kernels_wgrad_parts.hpp"
+#include "launchers.hpp"
+
+namespace mpcnn {
+namespace {
+#define INSTANCES(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9)
+}  // namespace
+
+bool launch_wgrad_parts(const WgradPartsArgs& a, int PM, dim3 grid, size_t lds, hipStream_t st)
+{
+#define CASE(n) if (PM == n) { wgrad_parts_kernel<n><<<grid, kWpThreads, lds, st>>>(a); return true; }
+    INSTANCES(CASE)
+#undef CASE
+    return false;
+}
+
+hipError_t wgrad_parts_attrs()
+{
+    hipError_t e = hipSuccess;
+#define ATTR(n)                                                                              \
+    if (e == hipSuccess)                                                                     \
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_parts_kernel<n>),       \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    INSTANCES(ATTR)
+#undef ATTR
+    return e;
+}
+
+}  // namespace mpcnn

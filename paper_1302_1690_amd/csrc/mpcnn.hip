@@ -136,6 +136,7 @@ struct WgradPlan {
     size_t lds = 0;
     size_t plen = 0;      // floats per partial result (tiled layout)
     int hl = 0;           // halo items per loading thread and tile (fp32 matrix instruction kernel)
+    int PM = 0, R = 0, nch = 0, RT = 0, ppg = 0, tpg = 0, ntg = 0;   // PM > 0: wgrad_parts_kernel (gm x gn groups, tile R rows x 16 nch columns)
     // direct kernel fallback
     int rows_per_chunk = 0, chunks = 0;
     bool l0m = false;     // the image layer's own kernel (l0_wgrad_mfma_kernel): `chunks` workgroups, flat partial results
@@ -468,6 +469,66 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
 
 unsigned magic_of(unsigned x) { return x <= 1 ? 0u : (unsigned)(((1ull << 32) + x - 1) / x); }
 
+// Plan of wgrad_parts_kernel.  Candidates: how the result's row tiles (units of 16 channels of one tap) and column
+// tiles are dealt to groups of workgroups and to the eight waves, and the tile of positions.  Cost in cycles of the
+// busiest compute unit: its tiles' matrix instructions (two waves share a SIMD's), half of what taking a tile in costs
+// (its conversions lie under the other wave's instructions, not all of them), a barrier, and the share of the closing
+// reduce, which reads every slab's partial result at about 7 bytes per cycle and compute unit.
+// `bound`, if given, receives the most floats of partial sums any map size can ask for.
+WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, size_t* bound)
+{
+    WgradPlan best;
+    double best_cost = -1;
+    const int planes = ceil_div(ly.cin, 16), kk = ly.k * ly.k2, Nt = ceil_div(ly.cout, 32);
+    const int fh = ceil_div(out_r, ly.dil), fw = ceil_div(out_c, ly.dil2);
+    if (bound) *bound = 0;
+    for (int wn : {1, 2, 4, 8}) {
+        if (wn >= 2 * Nt) continue;
+        const int gn = ceil_div(Nt, wn);
+        for (int ppg = 1; ppg <= planes; ++ppg)
+            for (int groups_t = 1; groups_t <= (ppg == 1 ? kk : 1); ++groups_t) {
+                const int tpg = ceil_div(kk, groups_t), ntg = ceil_div(kk, tpg), gm = ceil_div(planes, ppg) * ntg;
+                if (ntg != groups_t || gm * gn > kNumCU) continue;
+                const int RT = ceil_div(ppg * tpg, 2), target = kNumCU / (gm * gn);
+                const size_t plen = (size_t)gm * RT * Nt * 1024 + (size_t)Nt * 32;
+                for (int wm = 1; wm <= 8 / wn; wm *= 2) {
+                    const int wk = 8 / (wn * wm), PM = ceil_div(RT, wm);
+                    if (PM > mpcnn::kWpMaxTiles || (wm > 1 && ceil_div(RT, PM) <= wm / 2)) continue;
+                    if (bound) *bound = std::max(*bound, (size_t)target * plen);
+                    for (int R : {1, 2, 4, 8})
+                        for (int nch = 1; nch <= 4; ++nch) {
+                            if (R * nch < wk || (R > 1 && R / 2 >= fh) || (nch > 1 && 16 * (nch - 1) >= fw)) continue;
+                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn);
+                            size_t lds = std::max((size_t)2 * g.buf_b, (size_t)16 * 1024);
+                            if (wk > 1) lds = std::max(lds, (size_t)4 * PM * 4096);
+                            if (lds > (size_t)160 * 1024 || g.nh + g.nd > mpcnn::kWpItems * mpcnn::kWpThreads) continue;
+                            // (byte offsets inside a tile are 31 bits)
+                            if (((size_t)g.hh * ly.dil * in_c + (size_t)g.hwp * ly.dil2) * ly.cin * 4 >= (1ull << 31) ||
+                                ((size_t)R * ly.dil * out_c + (size_t)16 * nch * ly.dil2) * ly.cout * 4 >= (1ull << 31)) continue;
+                            const int nty = ceil_div(fh, R), ntx = ceil_div(fw, 16 * nch);
+                            const long tiles = (long)B * ly.dil * ly.dil2 * nty * ntx;
+                            if (tiles * std::max(std::max(ntx, nty), std::max(ly.dil, ly.dil2)) >= (1l << 31)) continue;
+                            const long tps = (tiles + target - 1) / target, slabs = (tiles + tps - 1) / tps;
+                            const double chunks = (double)fh / nty * ceil_div(fw, 16) / ntx / wk;   // of a wave and tile, on average
+                            const double t_mul = chunks * PM * 6 * 32 * 2;
+                            const double t_load = (g.nh + g.nd) * (32.0 / 10 + 75.0 * 6 / 256);
+                            const double cost = tps * (std::max(t_mul, 0.5 * t_load) + 0.5 * t_load + 800.0) + (double)slabs * plen * 4 / (7.0 * kNumCU);
+                            if (best_cost < 0 || cost < best_cost) {
+                                best_cost = cost;
+                                best.PM = PM; best.R = R; best.nch = nch; best.RT = RT; best.ppg = ppg; best.tpg = tpg; best.ntg = ntg;
+                                best.wm = wm; best.wn = wn; best.wk = wk; best.gm = gm; best.gn = gn; best.Nt = Nt;
+                                best.nty = nty; best.ntx = ntx; best.tiles_total = (int)tiles; best.tiles_per_slab = (int)tps;
+                                best.slabs = (int)slabs; best.lds = lds; best.plen = plen; best.ok = true;
+                            }
+                        }
+                }
+            }
+    }
+    return best;
+}
+// layers that kernel takes: fp32 storage, 128-bit items of both tensors, more than a sliver of input channels
+inline bool wgrad_parts_layer(const Layer& ly, bool bf16) { return !bf16 && ly.wgrad_mfma && ly.cin % 4 == 0 && ly.cin >= 8 && ly.cout % 4 == 0; }
+
 WgradPlan plan_wgrad(const Layer& ly, int B, int in_r, int in_c, int out_r, int out_c, bool bm)
 {
     WgradPlan w;
@@ -717,9 +778,13 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
             g->partial_n[l] = class_blocks(net, (long)B * r * c);
             g->partial_len[l] = ly.p_len;
         } else if (training) {
-            if (ly.dgrad_mfma && l > 0)
+            if (ly.dgrad_mfma && l > 0 && ly.parts)
+                g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct, 3, es,
+                                              true, net->hint_pt, net->hint_mp);
+            else if (ly.dgrad_mfma && l > 0)
                 g->dgrad[l] = plan_conv_tiles(B, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.dgrad_rpad, ly.dgrad_ct, ly.dgrad_bm, net->hint_pt, net->hint_mp);
-            g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
+            if (wgrad_parts_layer(ly, net->bf16)) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, nullptr);
+            if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
             g->partial_n[l] = w.ok ? w.slabs : w.chunks;
             g->partial_len[l] = w.plen;
@@ -800,6 +865,11 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
                                               (size_t)ceil_div((int)rows_w + 1, 32) * Nt * 1024);
                 alloc_f = std::max((size_t)kNumCU * tiled,
                                    (size_t)std::max(kDirectWgradChunks, 2 * kNumCU) * ly.p_len);
+                if (wgrad_parts_layer(ly, net->bf16)) {
+                    size_t bound = 0;
+                    (void)plan_wgrad_parts(ly, 1, 1, 1, 1, &bound);
+                    alloc_f = std::max(alloc_f, bound);
+                }
                 alloc_f = std::max(alloc_f, (size_t)g->partial_n[l] * g->partial_len[l]);
             }
             off = align_up(off + sizeof(float) * alloc_f);
@@ -936,7 +1006,8 @@ bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipS
 mpcnn_status set_lds_attrs(bool bf16_storage)
 {
     if (bf16_storage) { HIP_TRY(mpcnn::conv_attrs_b16()); HIP_TRY(mpcnn::wgrad_attrs_b16()); }
-    else { HIP_TRY(mpcnn::conv_parts_attrs_f32_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_f32_back()); HIP_TRY(mpcnn::wgrad_attrs_f32()); }
+    else { HIP_TRY(mpcnn::conv_parts_attrs_f32_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_f32_back());
+           HIP_TRY(mpcnn::wgrad_attrs_f32()); HIP_TRY(mpcnn::wgrad_parts_attrs()); }
     return MPCNN_OK;
 }
 
@@ -1283,7 +1354,27 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
             // parameter gradient: partial sums over slabs of positions, then a fixed-order sum
             const WgradPlan& wp = g.wgrad[li];
             float* partial = (float*)(ws + g.partial_off[li]);
-            if (wp.ok) {
+            if (wp.ok && wp.PM > 0) {
+                if constexpr (kF32) {
+                    WgradPartsArgs a{};
+                    a.in = A; a.dY = dY; a.partial = partial;
+                    a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ci = Ci; a.Ho = Ho; a.Wo = Wo; a.Co = ly.cout;
+                    a.k = ly.k; a.k2 = ly.k2; a.d = ly.dil; a.d2 = ly.dil2;
+                    a.R = wp.R; a.nch = wp.nch; a.nty = wp.nty; a.ntx = wp.ntx;
+                    a.tiles_total = wp.tiles_total; a.tiles_per_slab = wp.tiles_per_slab;
+                    a.Nt = wp.Nt; a.RT = wp.RT; a.wm = wp.wm; a.wn = wp.wn; a.wk = wp.wk;
+                    a.ppg = wp.ppg; a.tpg = wp.tpg; a.ntg = wp.ntg;
+                    a.mg_nqh = magic_of(2 * wp.ppg); a.mg_hwp = magic_of(16 * wp.nch + ly.k2 - 1); a.mg_txp = magic_of(16 * wp.nch);
+                    a.mg_tpg = magic_of(wp.tpg); a.mg_k2 = magic_of(ly.k2); a.mg_ntx = magic_of(wp.ntx); a.mg_nty = magic_of(wp.nty);
+                    a.mg_d = magic_of(ly.dil); a.mg_d2 = magic_of(ly.dil2);
+                    dim3 grid((unsigned)wp.slabs, (unsigned)wp.gm, (unsigned)wp.gn);
+                    bool launched = false;
+                    LAUNCH("wgrad_parts", li, wstep, flops, es * (n_in + n_out) + 4.0 * ly.p_len,
+                           launched = mpcnn::launch_wgrad_parts(a, wp.PM, grid, wp.lds, st));
+                    if (!launched)
+                        return fail(MPCNN_EUNSUPPORTED, "layer %zu: no weight-gradient kernel instance for its plan", li);
+                }
+            } else if (wp.ok) {
                 WgradArgs a{};
                 a.in = A; a.dY = dY; a.partial = partial;
                 a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ci = Ci;
@@ -1377,8 +1468,9 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
         sg.out = net->d_grads + ly.p_off;
         sg.plen = (long)g.partial_len[l]; sg.n = g.partial_n[l];
         const WgradPlan& wp = g.wgrad[l];
-        sg.tiled = wp.ok ? (wp.bm ? 3 : 1) : 0;
-        sg.items = wp.ok ? wp.Mt * wp.Nt * 256 + (wp.bm ? 0 : wp.Nt * 8) : (int)ly.p_len;
+        sg.tiled = wp.ok ? (wp.PM > 0 ? 4 : wp.bm ? 3 : 1) : 0;
+        sg.items = !wp.ok ? (int)ly.p_len : (wp.PM > 0 ? wp.gm * wp.RT : wp.Mt) * wp.Nt * 256 + (wp.bm ? 0 : wp.Nt * 8);
+        sg.RT = wp.RT; sg.ppg = wp.ppg; sg.tpg = wp.tpg; sg.ntg = wp.ntg; sg.Ci = ly.cin; sg.kk = ly.k * ly.k2;
         sg.Nt = wp.Nt; sg.rows_total = ly.k * ly.k2 * ly.cin; sg.Co = ly.cout;
         sg.block0 = ra.total_blocks;
         ra.total_blocks += (sg.items + 63) / 64;
@@ -1683,6 +1775,10 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         if (l == 0 && g.l0_fused) put("  weight gradient: fused with the routing of the pool above, %d workgroups\n", g.l0_blocks);
         else if (w.l0m) put("  weight gradient: image-layer kernel on the fp32 MFMA, %d tiles of 8 x 32, %d workgroups\n", w.tiles_total, w.chunks);
         else if (!w.ok) put("  weight gradient: plain kernel, %d chunks\n", w.chunks);
+        else if (w.PM > 0)
+            put("  weight gradient: bf16 MFMA, three parts per number, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
+                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg,
+                w.R, 16 * w.nch, w.tiles_total, w.slabs, w.tiles_per_slab, w.lds);
         else
             put("  weight gradient: %s MFMA, %d x %d result tiles, waves %d x %d x %d (rows x columns x tile rows), %d row "
                 "tiles per wave, %d x %d workgroup groups, tile 4 x %d (%d), %d tiles in %d slabs of %d, %zu B LDS\n",

@@ -19,6 +19,8 @@ EDGES = [
     ("past_a_group", ((C, 8, 3), (C, 132, 3), (MP, 0, 2), (C, 36, 2), (FC, 8, 0), (FC, 2, 0)), 14, 40, 33),
     ("units", ((C, 16, 3), (MP, 0, 2), (FC, 44, 0), (FC, 10, 0), (FC, 9, 0), (FC, 2, 0)), 4, 37, 41),
     ("wide_filter", ((C, 40, 2), (C, 17, 5), (MP, 0, 3), (C, 24, 2), (FC, 33, 0), (FC, 2, 0)), 12, 52, 47),
+    # weight gradient: 8 and 7 column tiles, 27 and 58 units, several groups of workgroups
+    ("groups", ((C, 48, 3), (C, 232, 3), (MP, 0, 2), (C, 200, 2), (FC, 12, 0), (FC, 2, 0)), 14, 34, 52),
     ("one_position", ((C, 16, 3), (MP, 0, 2), (C, 32, 3), (FC, 64, 0), (FC, 2, 0)), 10, 10, 10),
 ]
 
