@@ -87,8 +87,7 @@ typedef struct {
  * at the end; C or MP after an FC), EUNSUPPORTED (a pool with k*k > 255; more than 16 classes).
  * Every legal net is accepted with either storage type; layers whose shape the matrix-core and
  * fused kernels do not take (channel counts that are not multiples of 4, fewer than 8 channels,
- * class layers with more than 4 classes or 256 inputs) run on plain kernels; layers behind a
- * rectangular pool multiply on the fp32 matrix instruction with either storage type.
+ * class layers with more than 4 classes or 256 inputs) run on plain kernels.
  */
 mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers_host, int n_layers, int in_channels,
                               int patch, mpcnn_dtype dtype, mpcnn_net** out);
@@ -139,10 +138,9 @@ mpcnn_status mpcnn_set_loss(mpcnn_net* net, mpcnn_loss kind);
 typedef enum { MPCNN_TANH = 0, MPCNN_LOGISTIC = 1 } mpcnn_activation;
 mpcnn_status mpcnn_set_activation(mpcnn_net* net, mpcnn_activation kind);
 
-/* Tuning knob for the matrix-core convolution kernel of fp32-arithmetic layers (forward and
+/* Tuning knob for the matrix-core convolution kernel (forward and
  * data gradient; Method, forward and backward of layer C): a workgroup computes 32 *
- * position_tiles positions of one residue class (16 * position_tiles where bf16 storage puts a
- * layer of 16 or fewer outputs on 16-wide tiles) and each of its waves owns tiles_per_wave of them
+ * position_tiles positions of one residue class and each of its waves owns tiles_per_wave of them
  * for one channel tile, or two.  0 leaves either choice to the library's
  * planner (the default), which weighs matrix-instruction time against staging per layer and
  * image size.  A pair that no kernel instance serves for a layer's channel count leaves that

@@ -30,8 +30,21 @@
 // Latency.  Workgroups are persistent and walk (tile, channel block) items; the next item's halo is
 // loaded into registers before the current one is multiplied and split into parts on its way to LDS after it.
 // Weights run through a ring of two steps (four with one part) that never drains: the pack is in step
-// order and wraps around from a tile's last step to its first.  Two workgroups share a compute unit, so one's
-// staging, barriers and stores lie under the other's instructions.
+// order - chunks of 16 channels, the taps of each, whatever CB is - and wraps around from a tile's last step to its first.
+// Two workgroups share a compute unit, so one's staging, barriers and stores lie under the other's
+// instructions.  A block costs two barriers and, as a wave's loads return in order, a wait of its weights behind the halo:
+// where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels.
+//
+// Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
+//   fp32, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 (fp32 instruction) -> 461, 870, 666, 1110 (226, 231, 209, 165 TFLOP/s);
+//     data gradient 1060, 1790, 1250, 1880 -> 490, 851, 628, 981 (213, 236, 221, 187).  The loop sustains 240-260 on random
+//     data (362 on zero weights: the power limit takes the clock down to 1.7-2.1 GHz).
+//   bf16, 2 x 2048 x 2048: forward 1156, 1982, 1845, 4009 (two kernels of one part before) -> 1095, 1746, 1725, 3211;
+//     data gradient 1021, 1898, 1501, 2580 -> 947, 1799, 1446, 2430.  Matrix pipes busy 20-50 %: a tile's tanh, stores
+//     and halo take as long as its instructions.
+//   The bias from LDS instead of memory (its loads queued behind the halo's) took the bf16 forward from 8.8 to 7.9 ms.
+// Tried and dropped: 2 x 4 tiles per wave with one part (registers spill; 3.4 ms for the last layer's data gradient), three
+// workgroups per compute unit (the same, 3.9 ms for its forward).
 //
 // Summation order is the step order for every output element, whatever the tiling: equal inputs
 // give bit-equal outputs (exact pooling ties stay exact) and a position's value does not depend on
@@ -52,13 +65,7 @@ constexpr int kPartsThreads = 256;   // four waves
 __host__ __device__ constexpr int parts_pitch(int parts, int CB) { return (CB / 16) * parts * 32 + 16; }   // LDS bytes of a halo position
 __host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
 __host__ __device__ constexpr int parts_items(int parts) { return parts == 3 ? 6 : 12; }                    // rounds, at most (they wait in registers)
-__host__ __device__ constexpr int parts_unit(int parts) { return parts == 3 ? 1 : 2; }                      // steps per slot of the weights' ring
-// steps of a block of nsub 16-channel chunks: whole units (the odd one out multiplies zero weights)
-__host__ __device__ constexpr int parts_block_steps(int parts, int taps, int nsub) { return (taps * nsub + parts_unit(parts) - 1) / parts_unit(parts) * parts_unit(parts); }
-__host__ __device__ constexpr int parts_steps(int parts, int CB, int taps, int rpad)                        // ... of a whole reduction
-{
-    return (rpad / CB) * parts_block_steps(parts, taps, CB / 16) + (rpad % CB ? parts_block_steps(parts, taps, rpad % CB / 16) : 0);
-}
+__host__ __device__ constexpr int parts_ring(int parts) { return parts == 3 ? 2 : 4; }                      // steps of weights in registers
 
 // x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: three conversions, four shifts or masks and four
 // subtractions each)
@@ -89,7 +96,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 {
     static_assert(WO * WP == 4, "four waves");
     constexpr int P = sizeof(T) == 4 ? 3 : 1;
-    constexpr int QN = CB / 8, NSUB = CB / 16, U = parts_unit(P);
+    constexpr int QN = CB / 8, NSUB = CB / 16, NS = parts_ring(P);
     constexpr int PITCH = parts_pitch(P, CB), RP = parts_round(CB), SI = parts_items(P);
     constexpr int ITW = P == 3 ? 2 : 1;               // 128-bit loads per staged item (8 channels of a position)
     constexpr unsigned kNone = 0x80000000u;           // byte offset no buffer reaches: the load returns zeros
@@ -188,6 +195,14 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         }
     };
 
+    // ---- the bias of the workgroup's channels, behind the halo's whole rounds
+    float* const bias_l = reinterpret_cast<float*>(ldsb + (npos + RP - 1) / RP * (RP * PITCH));
+    if constexpr (!BACK)
+        if (tid < 32 * WO * MO) {
+            const int c = 32 * (int)blockIdx.y * WO * MO + tid;
+            bias_l[tid] = c < a.Co ? a.bias[c] : 0.f;
+        }
+
     // ---- per lane: LDS address of the positions it feeds as the B operand, at tap 0
     int lbase[MP];
 #pragma unroll
@@ -198,91 +213,97 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         lbase[p] = (int)(ty * hw + tx) * PITCH + lg * 16;
     }
 
-    // ---- weights: [step][part][lane group][CoPad][8], the step's offset a scalar
-    const int wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = parts_steps(P, CB, a.k * a.k2, a.CrPad) * wstep;   // bytes
+    // ---- weights: [16-channel chunk][tap][part][lane group][CoPad][8], the step's offset a scalar
+    const int wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = a.k * a.k2 * (a.CrPad / 16) * wstep;   // bytes
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<v4f*>(a.wpack), 0, wend, 0x00020000);
     const int wlane = (lg * a.CoPad + oc0 + lt) * 16;
     int wq = 0;                                       // byte offset of the next step to fetch
     const int nblk = (a.CrPad + CB - 1) / CB;
 
     v16f acc[MO][MP];
-    v4f w[2][U][MO * P];                              // the ring: two slots of U steps
-    auto fetch_w = [&](int s, int u, int i) {
+    v4f w[NS][MO * P];                                // the ring
+    auto fetch_w = [&](int s, int i) {
 #pragma unroll
         for (int o = 0; o < MO; ++o)
-            w[s][u][o * P + i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane + 512 * o, wq + i * wpart, 0));
+            w[s][o * P + i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane + 512 * o, wq + i * wpart, 0));
     };
     auto next_w = [&]() {
         wq += wstep;
         if (wq >= wend) wq = 0;
     };
 
-    // one tile's share of one channel block
+    // one tile's share of one channel block: its 16-channel chunks one after the other, the taps of each
     auto multiply = [&](int nsub) {
-        const int n = parts_block_steps(P, a.k * a.k2, nsub) / U;   // units of this block
-        int left = a.k * a.k2 * nsub;                 // steps whose activations are still to be fetched
-        int tb = 0, sub = 0, soff = 0;                // the next one's place
-        const int rowskip = (hw - a.k2) * PITCH;
+        const int taps = a.k * a.k2, n = taps * nsub; // steps of this block
+        int left = n;                                 // steps whose activations are still to be fetched
+        int ta = 0, tb = 0, soff = 0;                 // the next one's place
+        const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (a.k * hw) * PITCH;
         constexpr int XS = P == 3 ? 1 : 2;            // sets of activations in registers
         v4f x[XS][P][MP];
         auto fetch_x = [&](int s, int i) {
 #pragma unroll
             for (int p = 0; p < MP; ++p) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + soff + 32 * i);
         };
-        // (past the last step: the first one's place, read for nothing or against zero weights)
+        // (past the last step: the first one's place, read for nothing)
         auto next_x = [&]() {
-            soff += P * 32;
-            if (++sub == nsub) {
-                sub = 0; soff += PITCH - nsub * (P * 32);
-                if (++tb == a.k2) { tb = 0; soff += rowskip; }
+            soff += PITCH;
+            if (++tb == a.k2) {
+                tb = 0; soff += rowskip;
+                if (++ta == a.k) { ta = 0; soff += subskip; }
             }
             if (--left <= 0) soff = 0;
         };
-        auto product = [&](int s, int u, int t, int i, int j) {   // weight part i, activation part j
+        auto product = [&](int s, int t, int i, int j) {   // weight part i, activation part j
 #pragma unroll
             for (int o = 0; o < MO; ++o)
 #pragma unroll
                 for (int p = 0; p < MP; ++p)
-                    acc[o][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][u][o * P + i]),
+                    acc[o][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][o * P + i]),
                                                                         __builtin_bit_cast(bf16x8, x[t][j][p]), acc[o][p], 0, 0, 0);
         };
-        auto unit = [&](int s) {
+        auto step = [&](int s) {
+            next_x();
             if constexpr (P == 3) {
                 // A step's operands are fetched for the next one as soon as they are free: the activations' third part
                 // behind the first product, its second behind the third, its first behind the last (three products
                 // before it is needed).
-                next_x();
-                product(s, 0, 0, 0, 2); fetch_x(0, 2);
-                product(s, 0, 0, 1, 1); product(s, 0, 0, 0, 1); fetch_x(0, 1);
-                product(s, 0, 0, 2, 0); fetch_w(s, 0, 2);
-                product(s, 0, 0, 1, 0); fetch_w(s, 0, 1);
-                product(s, 0, 0, 0, 0); fetch_x(0, 0); fetch_w(s, 0, 0);
-                next_w();
+                product(s, 0, 0, 2); fetch_x(0, 2);
+                product(s, 0, 1, 1); product(s, 0, 0, 1); fetch_x(0, 1);
+                product(s, 0, 2, 0); fetch_w(s, 2);
+                product(s, 0, 1, 0); fetch_w(s, 1);
+                product(s, 0, 0, 0); fetch_x(0, 0); fetch_w(s, 0);
             } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    next_x(); fetch_x(u ^ 1, 0);
-                    product(s, u, u, 0, 0); fetch_w(s, u, 0);
-                    next_w();
-                }
+                fetch_x((s & 1) ^ 1, 0);
+                product(s, s & 1, 0, 0); fetch_w(s, 0);
             }
+            next_w();
         };
 #pragma unroll
         for (int i = P - 1; i >= 0; --i) fetch_x(0, i);
-        // Units two by two.  The first pair stands before the loop: behind it the next halo's loads are older than
+        // Whole turns of the ring.  The first stands before the loop: behind it the next halo's loads are older than
         // every weight in flight, so the loop's waits count weights only.
         int s = 0;
-        if (n >= 2) {
-            unit(0); unit(1);
-            for (s = 2; s + 2 <= n; s += 2) { unit(0); unit(1); }
-        }
-        if (s < n) {                                  // an odd unit: the ring's slots change places
-            unit(0);
+        if (n >= NS) {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int i = 0; i < NS; ++i) step(i);
+            for (s = NS; s + NS <= n; s += NS)
 #pragma unroll
-                for (int i = 0; i < MO * P; ++i) { const v4f t = w[0][u][i]; w[0][u][i] = w[1][u][i]; w[1][u][i] = t; }
+                for (int i = 0; i < NS; ++i) step(i);
         }
+        // the rest of a turn; the ring's slots then change places, so that the next block starts at slot 0 again
+#pragma unroll
+        for (int i = 0; i < NS - 1; ++i)
+            if (s + i < n) step(i);
+#pragma unroll
+        for (int i = 0; i < NS - 1; ++i)
+            if (s + i < n)
+#pragma unroll
+                for (int j = 0; j < MO * P; ++j) {
+                    const v4f t = w[0][j];
+#pragma unroll
+                    for (int r = 0; r + 1 < NS; ++r) w[r][j] = w[r + 1][j];
+                    w[NS - 1][j] = t;
+                }
     };
 
     // ---- result of one element: the sum v, and the bias (forward) or the output whose slope multiplies it (data gradient)
@@ -292,44 +313,53 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         else return curved ? squash(v + y, a.logistic) : v + y;
     };
     // ---- epilogue of tile g: register 4n + z of tile (o, p) is channel oc0 + 32o + 8n + 4lg + z of position
-    // 32*(wp*MP + p) + lt
+    // 32*(wp*MP + p) + lt.  The bias waits in LDS; what the data gradient reads (the outputs whose slope
+    // multiplies it) is fetched one position tile ahead, so that its trip lies under the tile before.
     auto epilogue = [&](const Tile& g, int fh, int fw) {
         const bool vec = (a.Co & 3) == 0;             // uniform
         const int col = fresh(lt);
-#pragma unroll
-        for (int p = 0; p < MP; ++p) {
+        const bool reads = BACK && curved;            // uniform
+        long pos_off[2];
+        bool pos_ok[2];
+        typedef T raw4 __attribute__((ext_vector_type(4)));
+        raw4 y[2][MO][4];
+        auto place = [&](int p) {
             const unsigned m = 32 * (wp * MP + p) + col;
             const int ty = (int)parts_div(m, a.mg_tx, a.Tx), tx = (int)m - ty * a.Tx;
             const int fy = g.ty0 + ty, fx = g.tx0 + tx;
-            const bool pos_ok = ty < a.Ty && fy < fh && fx < fw;
-            const long pos_off = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co;
+            pos_ok[p & 1] = ty < a.Ty && fy < fh && fx < fw;
+            pos_off[p & 1] = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co;
+            if (reads)
 #pragma unroll
-            for (int o = 0; o < MO; ++o) {
-                v4f yv[4];
+                for (int o = 0; o < MO; ++o)
 #pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    const int oc = oc0 + 32 * o + 8 * n + 4 * lg;
-                    yv[n] = (v4f){0.f, 0.f, 0.f, 0.f};
-                    if (!pos_ok || oc >= a.Co || (BACK && !curved)) continue;
-                    if (vec) {
-                        if (BACK) yv[n] = load4(act_t + pos_off + oc);
-                        else yv[n] = (v4f){a.bias[oc], a.bias[oc + 1], a.bias[oc + 2], a.bias[oc + 3]};
-                    } else {
-                        for (int z = 0; z < 4; ++z)
-                            if (oc + z < a.Co) yv[n][z] = BACK ? load1(act_t + pos_off + oc + z) : a.bias[oc + z];
+                    for (int n = 0; n < 4; ++n) {
+                        const int oc = oc0 + 32 * o + 8 * n + 4 * lg;
+                        raw4& v = y[p & 1][o][n];
+                        v = (raw4){0, 0, 0, 0};
+                        if (!pos_ok[p & 1] || oc >= a.Co) continue;
+                        if (vec) v = *reinterpret_cast<const raw4*>(act_t + pos_off[p & 1] + oc);
+                        else for (int z = 0; z < 4; ++z) if (oc + z < a.Co) v[z] = act_t[pos_off[p & 1] + oc + z];
                     }
-                }
+        };
+        place(0);
+#pragma unroll
+        for (int p = 0; p < MP; ++p) {
+            if (p + 1 < MP) place(p + 1);
+#pragma unroll
+            for (int o = 0; o < MO; ++o)
 #pragma unroll
                 for (int n = 0; n < 4; ++n) {
                     const int oc = oc0 + 32 * o + 8 * n + 4 * lg;
-                    if (!pos_ok || oc >= a.Co) continue;
-                    v4f r;
+                    if (!pos_ok[p & 1] || oc >= a.Co) continue;
+                    v4f yv = __builtin_convertvector(y[p & 1][o][n], v4f), r;
+                    if constexpr (!BACK) yv = *reinterpret_cast<const v4f*>(bias_l + (oc - 32 * (int)blockIdx.y * WO * MO));
 #pragma unroll
-                    for (int z = 0; z < 4; ++z) r[z] = finish(acc[o][p][4 * n + z], yv[n][z]);
-                    if (vec) store4(out_t + pos_off + oc, r);
-                    else for (int z = 0; z < 4; ++z) if (oc + z < a.Co) store1(out_t + pos_off + oc + z, r[z]);
+                    for (int z = 0; z < 4; ++z) r[z] = finish(acc[o][p][4 * n + z], yv[z]);
+                    T* const dst = out_t + pos_off[p & 1] + oc;
+                    if (vec) store4(dst, r);
+                    else for (int z = 0; z < 4; ++z) if (oc + z < a.Co) store1(dst + z, r[z]);
                 }
-            }
         }
     };
     // A sum that is not finite came from infinities, NaN or numbers without parts (or is one that overflows):
@@ -371,13 +401,11 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     aim(cur, true);
     issue(0);
 #pragma unroll
-    for (int s = 0; s < 2; ++s)                       // (a reduction of one slot: the same steps twice)
+    for (int s = 0; s < NS; ++s) {                    // the ring's first steps
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int i = 0; i < P; ++i) fetch_w(s, u, i);
-            next_w();
-        }
+        for (int i = 0; i < P; ++i) fetch_w(s, i);
+        next_w();
+    }
     to_lds();
     __syncthreads();
     for (; t < a.tiles_total; t += gridDim.x) {

@@ -10,7 +10,7 @@
 // one matrix instruction per position tile and nothing else.  An odd k*C is padded by one value that
 // meets a zero weight.  The maps' operand, the whole filter bank, stays in registers (one word per step).
 // A workgroup's tile is 4 MP rows x 32 columns of positions: wave w owns rows w*MP .. w*MP + MP - 1,
-// a lane one column.  Result layout and epilogue as in conv_ts_kernel.
+// a lane one column.  Result layout and epilogue as in conv_parts_kernel.
 #pragma once
 #include "kernels_mfma.hpp"
 
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(256) void first_layer_mfma_kernel(FirstMfmaArgs a)
         for (int j = 0; j < SR; ++j)
 #pragma unroll
             for (int p = 0; p < MP; ++p)
-                acc[p] = mfma_f32<32>(w[u * SR + j], base[(p + u) * HWC + 2 * j], acc[p]);
+                acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[u * SR + j], base[(p + u) * HWC + 2 * j], acc[p], 0, 0, 0);
 
     // ---- epilogue: register 4n + z of position tile p is map oc0 + 8n + 4lg + z of position (row w*MP + p, column lt)
     const int x = x0 + lt;

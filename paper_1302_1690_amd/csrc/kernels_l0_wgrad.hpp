@@ -135,7 +135,7 @@ __global__ __launch_bounds__(256) void l0_wgrad_mfma_kernel(L0WgradArgs a)
                 const float bv = db[2 * s * 32];
                 bsum += bv;
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt] = mfma_f32<32>(xa[roff[mt] + 2 * s * C], bv, acc[mt]);
+                for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[roff[mt] + 2 * s * C], bv, acc[mt], 0, 0, 0);
             }
         }
         __syncthreads();

@@ -3,21 +3,15 @@
 #include "launchers.hpp"
 
 namespace mpcnn {
-namespace {
-typedef float T;
-#define INSTANCES(X) \
-    X(1, 4, 1, 1) X(1, 4, 1, 2) X(2, 2, 1, 1) X(2, 2, 1, 2) X(1, 4, 2, 2) X(4, 1, 1, 2) X(4, 1, 1, 4) X(2, 2, 2, 2)
-}  // namespace
 
-bool launch_conv_parts_f32_fwd(const ConvArgs& a, int CB, const PartsInstance& in, dim3 grid, size_t lds, hipStream_t st)
+bool launch_conv_parts_f32_fwd(const ConvArgs& a, const PartsInstance& in, dim3 grid, size_t lds, hipStream_t st)
 {
-#define CASE(o, p, mo, mp)                                                                                          \
-    if (in.WO == o && in.WP == p && in.MO == mo && in.MP == mp) {                                                   \
-        if (CB == 16) conv_parts_kernel<T, false, 16, o, p, mo, mp><<<grid, kPartsThreads, lds, st>>>(a);          \
-        else conv_parts_kernel<T, false, 32, o, p, mo, mp><<<grid, kPartsThreads, lds, st>>>(a);                   \
-        return true;                                                                                                \
+#define CASE(cb, wo, wp, mo, mp)                                                                       \
+    if (in.CB == cb && in.WO == wo && in.WP == wp && in.MO == mo && in.MP == mp) {                     \
+        conv_parts_kernel<float, false, cb, wo, wp, mo, mp><<<grid, kPartsThreads, lds, st>>>(a);      \
+        return true;                                                                                   \
     }
-    INSTANCES(CASE)
+    MPCNN_PARTS3(CASE)
 #undef CASE
     return false;
 }
@@ -25,13 +19,11 @@ bool launch_conv_parts_f32_fwd(const ConvArgs& a, int CB, const PartsInstance& i
 hipError_t conv_parts_attrs_f32_fwd()
 {
     hipError_t e = hipSuccess;
-#define ATTR(...)                                                                            \
-    if (e == hipSuccess)                                                                     \
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&__VA_ARGS__),                 \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
-#define BOTH(o, p, mo, mp) ATTR(conv_parts_kernel<T, false, 16, o, p, mo, mp>); ATTR(conv_parts_kernel<T, false, 32, o, p, mo, mp>);
-    INSTANCES(BOTH)
-#undef BOTH
+#define ATTR(cb, wo, wp, mo, mp)                                                                                       \
+    if (e == hipSuccess)                                                                                               \
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_parts_kernel<float, false, cb, wo, wp, mo, mp>),   \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    MPCNN_PARTS3(ATTR)
 #undef ATTR
     return e;
 }

@@ -22,7 +22,6 @@
 #include "../../include/mpcnn.h"
 #include "kernels_direct.hpp"
 #include "launchers.hpp"
-#include "kernels_conv_bf16.hpp"    // tp_items
 #include "kernels_conv_parts.hpp"   // its LDS geometry (no instance is built here)
 #include "kernels_wgrad_tr.hpp"     // its LDS geometry
 #include "kernels_wgrad_bf16.hpp"   // its LDS geometry, which the planner shares (no instance is built here)
@@ -64,16 +63,15 @@ mpcnn_status fail(mpcnn_status st, const char* fmt, ...)
 constexpr int kLossBlocks = 2048;         // most per-workgroup loss shares (= most workgroups of the class-layer kernel)
 constexpr int kSoftmaxBlocks = 512;       // workgroups of the unfused softmax kernel
 constexpr int kDirectWgradChunks = 512;   // split of the position reduction, direct kernel
-constexpr size_t kConvLdsCap = 64 * 1024; // halo bytes per workgroup (two workgroups per CU)
 constexpr size_t kWgradLdsCap = 144 * 1024;
 constexpr int kNumCU = 256;
 
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Output-channel tiling of the MFMA kernels: tiles of W channels, OT tiles per workgroup,
-// `split` groups of them (blockIdx.y / z), `pad` = channels covered.
-struct ChanTiling { int W, OT, split, pad; };
+// Output-channel tiling of the convolution kernel: tiles of 32 channels, OT tiles per workgroup,
+// `split` groups of them (blockIdx.y), `pad` = channels covered.
+struct ChanTiling { int OT, split, pad; };
 ChanTiling tile_channels(int channels, int W, const int* allowed, int n_allowed)
 {
     const int max_ot = allowed[n_allowed - 1];
@@ -82,19 +80,12 @@ ChanTiling tile_channels(int channels, int W, const int* allowed, int n_allowed)
     const int per = ceil_div(tiles, split);
     int OT = max_ot;
     for (int i = 0; i < n_allowed; ++i) if (allowed[i] >= per) { OT = allowed[i]; break; }
-    return {W, OT, split, OT * split * W};
+    return {OT, split, OT * split * W};
 }
-ChanTiling chan_tiling_w(int channels, int W)   // forward / data-gradient kernel instances
+ChanTiling chan_tiling(int channels)   // convolution kernel instances
 {
     static const int allowed[] = {1, 2, 4};
-    return tile_channels(channels, W, allowed, 3);
-}
-// 32-wide MFMA tiles run at the full fp32 matrix rate, 16-wide ones at about 0.87 of it:
-// take whichever wastes less once its padding is counted.
-ChanTiling chan_tiling(int channels)
-{
-    const ChanTiling a = chan_tiling_w(channels, 16), b = chan_tiling_w(channels, 32);
-    return (a.pad / 0.87 < b.pad) ? a : b;
+    return tile_channels(channels, 32, allowed, 3);
 }
 
 struct Layer {
@@ -113,19 +104,15 @@ struct Layer {
     bool fwd_mfma = false, dgrad_mfma = false, wgrad_mfma = false;
     bool class_fused = false;             // last FC handled by class_layer_kernel
     ChanTiling fwd_ct{}, dgrad_ct{};
-    bool fwd_bm = false, dgrad_bm = false; // bf16 storage: multiply on the bf16 matrix instruction
-    bool parts = false;                   // fp32 storage: conv_parts_kernel, three bf16 parts per number
     int fwd_rpad = 0, dgrad_rpad = 0;     // reduced channels padded to 16
     size_t fwd_pack_off = 0, fwd_pack_len = 0, dgrad_pack_off = 0, dgrad_pack_len = 0;
 };
 
-struct TilePlan {
-    int PT = 0, NW = 4, Ty = 0, Tx = 0, nty = 0, ntx = 0;
-    int MP = 0;           // > 0: conv_ts_kernel (result tiles dealt out to the waves), MP position tiles per wave
+struct TilePlan {          // conv_parts_kernel: 32 PT positions per workgroup, `wgs` workgroups per channel group walk the tiles
+    int PT = 0, Ty = 0, Tx = 0, nty = 0, ntx = 0, wgs = 0;
+    mpcnn::PartsInstance in{};
     size_t lds = 0;
     bool ok = false;
-    int CB = 0, wgs = 0;  // CB > 0: conv_parts_kernel, CB channels per block, wgs workgroups per channel group walking the tiles
-    mpcnn::PartsInstance in{};
 };
 struct WgradPlan {
     bool ok = false;
@@ -276,148 +263,6 @@ struct ProfScope {
     } while (0)
 
 // ------------------------------------------------------------------ planning
-// Ty x Tx tile (<= max_pos positions) of a residue class with extents fh x fw: fewest
-// tiles first, then the smallest halo; the halo must fit `lds_cap`.
-bool choose_tile(int fh, int fw, int max_pos, int k, int k2, size_t pitch_bytes, size_t extra_bytes,
-                 size_t lds_cap, int* Ty, int* Tx)
-{
-    long best_tiles = -1, best_halo = 0;
-    for (int ty = 1; ty <= std::min(fh, max_pos); ++ty) {
-        for (int tx = 1; tx <= std::min(fw, max_pos / ty); ++tx) {
-            long halo = (long)(ty + k - 1) * (tx + k2 - 1);
-            if ((size_t)halo * pitch_bytes + extra_bytes > lds_cap) continue;
-            long tiles = (long)ceil_div(fh, ty) * ceil_div(fw, tx);
-            if (best_tiles < 0 || tiles < best_tiles || (tiles == best_tiles && halo < best_halo)) {
-                best_tiles = tiles; best_halo = halo; *Ty = ty; *Tx = tx;
-            }
-        }
-    }
-    return best_tiles > 0;
-}
-
-// Tile plan of the convolution kernels for a map of out_r x out_c positions, a k x k2 filter (rows x columns)
-// with taps d rows / d2 columns apart (k2 != k or d2 != d: a rectangular pool, or a layer behind one).
-TilePlan plan_conv_tiles(int B, int out_r, int out_c, int d, int d2, int k, int k2, int rpad, const ChanTiling& ct, bool bm,
-                         int hint_pt = 0, int hint_mp = 0)
-{
-    TilePlan best;
-    double best_cost = 0;
-    const int fh = ceil_div(out_r, d), fw = ceil_div(out_c, d2);
-    const size_t pitch = bm ? 16 * (size_t)(rpad / 8 + 1) : sizeof(float) * (rpad + 4);   // one halo position in LDS
-    if (!bm && (ct.W == 32 || ct.OT == 1)) {
-        // conv_ts_kernel: W*PT positions x W*OT channels, OT*PT/MP waves (16-wide: one channel tile, 32 cycles
-        // per instruction; 32-wide: 64 cycles).  Cost of the busiest CU:
-        // its workgroups' matrix instructions one after the other, plus, once per round of
-        // co-resident workgroups, what is not hidden behind another's multiplications
-        // (staging the halo at ~8 bytes per cycle, a memory round trip, the stores).
-        const bool w16 = ct.W == 16;
-        const int steps = k * k2 * (rpad / (w16 ? 16 : 8));
-        for (int PT : {2, 4, 8, 16})
-            for (int MP : {1, 2, 4}) {
-                const int NW = ct.OT * PT / MP;
-                if (PT % MP || (NW != 4 && NW != 8)) continue;
-                const bool built4 = (ct.OT == 4 && (PT == 4 || PT == 8)) || (ct.OT == 2 && PT == 8) || (ct.OT == 1 && PT == 16);
-                if (w16 ? PT < 4 : (MP == 4 ? !built4 : PT > 8)) continue;   // (the instances that are built)
-                // four tiles per wave pay where the reduction is long: with 64 steps (2 x 2 taps of 128 channels) the
-                // longer epilogue and the fewer workgroups per compute unit cost more than the weight fetches saved
-                // (measured: 2012 -> 2074 us; 9 taps of 64 channels, 72 steps: 1242 -> 1185 us)
-                if (!w16 && MP == 4 && steps < 72 && hint_mp != 4) continue;
-                if ((hint_pt && PT != hint_pt) || (hint_mp && MP != hint_mp)) continue;
-                // measured: a wave with one tile spends ~12 % more per instruction on operand
-                // fetches than one with two
-                const double t_mul1 = (double)steps * 4 * ct.OT * PT * (w16 ? 32 : 64) / 4 * (MP >= 4 ? 0.94 : (MP >= 2 ? 1.0 : 1.12));   // (a weight fetch per 4 MP instructions: each costs the matrix pipe about 100 cycles)
-                for (int ty = 1; ty <= std::min(fh, ct.W * PT); ++ty)
-                    for (int tx = 1; tx <= std::min(fw, ct.W * PT / ty); ++tx) {
-                        const size_t lds = std::max((size_t)(ty + k - 1) * (tx + k2 - 1) * pitch, (size_t)1024);
-                        if (lds > (size_t)150 * 1024) break;
-                        const int nty = ceil_div(fh, ty), ntx = ceil_div(fw, tx);
-                        const double wgs = (double)B * d * d2 * nty * ntx * ct.split;
-                        const int together = (int)std::max<size_t>(1, std::min<size_t>(16 / NW, (size_t)(160 * 1024) / lds));
-                        const double per_cu = std::ceil(wgs / kNumCU);
-                        // fewer than 8 waves on the CU leave SIMDs idle in every wait
-                        const double t_mul = t_mul1 * (NW * std::min<double>(together, per_cu) >= 8 ? 1.0 : 1.25);
-                        const double t_rest = 4000.0 + (double)lds / 8;
-                        const double cost = per_cu * t_mul + std::ceil(per_cu / together) * t_rest;
-                        if (!best.ok || cost < best_cost) {
-                            best.PT = PT; best.NW = NW; best.MP = MP; best.Ty = ty; best.Tx = tx;
-                            best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
-                            best_cost = cost;
-                        }
-                    }
-            }
-        if (best.ok) return best;
-    }
-    if (bm) {
-        // conv_ts_kernel on the bf16 matrix instruction (32 cycles per instruction, 16 channels
-        // of a tap per step).  The instruction stream of a workgroup is an eighth of the fp32
-        // one, so staging and stores weigh 8 times more: large tiles, MP = 4 where possible (a wave
-        // with 2 position tiles asks the vector cache for twice the weights per instruction: the
-        // cache, not the matrix pipe, then sets the pace), two workgroups per compute unit.
-        const int steps = k * k * (rpad / 16);
-        // (the kernel forms element offsets inside one image in 32 bits)
-        if ((size_t)(out_r + (k - 1) * d) * (out_c + (k - 1) * d) * rpad >= (1ull << 31)) return best;
-        for (int PT : {2, 4, 8, 16})
-            for (int MP : {2, 4}) {
-                const int NW = ct.OT * PT / MP;
-                if (PT % MP || (NW != 4 && NW != 8)) continue;
-                const double t_mul1 = (double)steps * ct.OT * PT * 32 / 4 * (MP == 4 ? 1.0 : 1.6);
-                for (int ty = 1; ty <= std::min(fh, 32 * PT); ++ty)
-                    for (int tx = 1; tx <= std::min(fw, 32 * PT / ty); ++tx) {
-                        const size_t lds = std::max((size_t)(ty + k - 1) * (tx + k - 1) * pitch, (size_t)1024);
-                        if (lds > (size_t)150 * 1024) break;
-                        // a thread holds its share of the next tile's halo in registers
-                        if ((long)(ty + k - 1) * (tx + k - 1) * (rpad / 8) > (long)mpcnn::tp_items(MP) * 64 * NW) break;
-                        const int nty = ceil_div(fh, ty), ntx = ceil_div(fw, tx);
-                        const double wgs = (double)B * d * d * nty * ntx * ct.split;
-                        const int together = (int)std::max<size_t>(1, std::min<size_t>(8 / NW, (size_t)(160 * 1024) / lds));
-                        const double per_cu = std::ceil(wgs / kNumCU);
-                        const double t_rest = 4000.0 + (double)lds / 8 + 32.0 * ct.OT * PT * 16;   // + the stores
-                        // co-resident workgroups hide each other's staging and stores; alone, a
-                        // workgroup pays for them in full
-                        const double cost = together >= 2 ? per_cu * t_mul1 + std::ceil(per_cu / together) * t_rest
-                                                          : per_cu * (t_mul1 + t_rest);
-                        if (!best.ok || cost < best_cost) {
-                            best.PT = PT; best.NW = NW; best.MP = MP; best.Ty = ty; best.Tx = tx;
-                            best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
-                            best_cost = cost;
-                        }
-                    }
-            }
-        return best;
-    }
-    const int regs_per_tile = ct.W * ct.W / 64;
-    for (int PT : {64 / ct.W, 128 / ct.W}) {            // 64 or 128 positions per workgroup
-        if (ct.OT * PT * regs_per_tile > (ct.W == 16 ? 64 : 128)) continue;  // accumulator registers per lane
-        for (int NW : {4, 8}) {
-            TilePlan p;
-            p.PT = PT; p.NW = NW;
-            if (!choose_tile(fh, fw, ct.W * PT, k, k2, pitch, 0, kConvLdsCap, &p.Ty, &p.Tx)) continue;
-            p.nty = ceil_div(fh, p.Ty); p.ntx = ceil_div(fw, p.Tx);
-            size_t halo = (size_t)(p.Ty + k - 1) * (p.Tx + k2 - 1) * pitch;
-            size_t part = (size_t)NW * ct.OT * (ct.W / 4) * (ct.W + 1) * 4 * sizeof(float);
-            p.lds = std::max(halo, part);
-            if (p.lds > 150 * 1024) continue;
-            if (NW == 8 && k * k2 * (rpad / (256 / ct.W)) < 16) continue;   // too few reduction steps to split 8 ways
-            p.ok = true;
-            // Measured: two co-resident 4-wave workgroups with large tiles (LDS allows no more than
-            // two) only overlap well once their phases have drifted apart, i.e. over many rounds;
-            // for a few rounds one 8-wave workgroup per CU is faster.  Small tiles: 4 waves.
-            const double wgs = (double)B * d * d2 * p.nty * p.ntx * ct.split;
-            const double per_cu = wgs / kNumCU;
-            const int steps = k * k2 * (rpad / (256 / ct.W));
-            const bool want8 = ct.W == 32 && ct.OT * PT >= 4 && steps >= 64 && per_cu < 8;
-            if ((NW == 8) != want8) continue;
-            const double rounds = NW == 8 ? std::ceil(per_cu) : std::ceil(per_cu / 2);
-            const double cost = rounds * (ct.W * PT / 16 + 1.0);
-            if (!best.ok || cost < best_cost) { best = p; best_cost = cost; }
-        }
-    }
-    return best;
-}
-
-// Channels per block of conv_parts_kernel: 32, or 16 where a layer reduces over no more.
-inline int parts_block(int rpad) { return rpad <= 16 ? 16 : 32; }
-
 // Tile plan of conv_parts_kernel (P parts per number, es bytes per stored element).  Cost of the busiest compute unit
 // in cycles: its tiles' matrix instructions on its four SIMDs, a quarter of their staging and stores (most of it lies under
 // the other resident workgroup's instructions), and one tile's staging in full at the start.
@@ -427,22 +272,25 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
     TilePlan best;
     double best_cost = 0;
     const int fh = ceil_div(out_r, d), fw = ceil_div(out_c, d2);
-    const int CB = parts_block(rpad), steps = k * k2 * rpad / 16, nblk = ceil_div(rpad, CB);
-    const int RP = mpcnn::parts_round(CB);
-    const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);
-    for (const mpcnn::PartsInstance& in : mpcnn::kPartsInstances) {
+    const int steps = k * k2 * rpad / 16;
+    const mpcnn::PartsInstance* const list = P == 3 ? mpcnn::kParts3 : mpcnn::kParts1;
+    const int n_list = P == 3 ? (int)(sizeof(mpcnn::kParts3) / sizeof(list[0])) : (int)(sizeof(mpcnn::kParts1) / sizeof(list[0]));
+    for (int li = 0; li < n_list; ++li) {
+        const mpcnn::PartsInstance& in = list[li];
+        const int CB = in.CB, RP = mpcnn::parts_round(CB), nblk = ceil_div(rpad, CB);
+        const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);
         const int PT = in.WP * in.MP, per_wave = in.MO * in.MP;
-        if (in.WO * in.MO != ct.OT) continue;
+        if (in.WO * in.MO != ct.OT || (CB > 16 && rpad <= CB / 2)) continue;
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
         if (in.MO == 2 && ceil_div(co, 32) % 2) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
-        const double eff = per_wave >= 4 ? 1.0 : (per_wave == 2 ? 1.08 : 1.3);
+        const double eff = P == 3 ? (per_wave >= 4 ? 1.0 : (per_wave == 2 ? 1.08 : 1.3)) : (per_wave >= 4 ? 1.0 : 1.5);
         const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
         for (int ty = 1; ty <= std::min(fh, 32 * PT); ++ty)
             for (int tx = 1; tx <= std::min(fw, 32 * PT / ty); ++tx) {
                 const int npos = (ty + k - 1) * (tx + k2 - 1), rounds = ceil_div(npos, RP);
                 if (rounds > mpcnn::parts_items(P)) break;
-                const size_t lds = rounds * RP * pitch;
+                const size_t lds = rounds * RP * pitch + 32 * ct.OT * sizeof(float);   // the halo, the bias
                 if (lds > (size_t)80 * 1024) break;
                 // (byte offsets inside a tile's halo are 31 bits)
                 if (((size_t)(ty + k - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) break;
@@ -455,9 +303,9 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                 const double t_rest = (double)npos * cr * es / 10 + 2500.0 * nblk + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
                 const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * t_mul + 0.25 * t_rest) + t_rest;
                 if (!best.ok || cost < best_cost) {
-                    best.PT = PT; best.NW = 4; best.MP = in.MP; best.Ty = ty; best.Tx = tx;
+                    best.PT = PT; best.Ty = ty; best.Tx = tx;
                     best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
-                    best.CB = CB; best.wgs = (int)wgs; best.in = in;
+                    best.wgs = (int)wgs; best.in = in;
                     best_cost = cost;
                 }
             }
@@ -770,19 +618,16 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         size_t bytes = es * (size_t)B * r * c * ly.cout;
         max_act = std::max(max_act, bytes);
         if (ly.kind == MPCNN_MP) continue;
-        if (ly.fwd_mfma && ly.parts)
-            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct, 3, es, false,
+        if (ly.fwd_mfma)
+            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct, net->bf16 ? 1 : 3, es, false,
                                         net->hint_pt, net->hint_mp);
-        else if (ly.fwd_mfma) g->fwd[l] = plan_conv_tiles(B, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.fwd_rpad, ly.fwd_ct, ly.fwd_bm, net->hint_pt, net->hint_mp);
         if (training && ly.class_fused) {
             g->partial_n[l] = class_blocks(net, (long)B * r * c);
             g->partial_len[l] = ly.p_len;
         } else if (training) {
-            if (ly.dgrad_mfma && l > 0 && ly.parts)
-                g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct, 3, es,
-                                              true, net->hint_pt, net->hint_mp);
-            else if (ly.dgrad_mfma && l > 0)
-                g->dgrad[l] = plan_conv_tiles(B, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.dgrad_rpad, ly.dgrad_ct, ly.dgrad_bm, net->hint_pt, net->hint_mp);
+            if (ly.dgrad_mfma && l > 0)
+                g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
+                                              net->bf16 ? 1 : 3, es, true, net->hint_pt, net->hint_mp);
             if (wgrad_parts_layer(ly, net->bf16)) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, nullptr);
             if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
@@ -933,16 +778,6 @@ inline int grid_for(long total, int block = 256, int cap = 1 << 20)
 }
 
 // ------------------------------------------------------------------ MFMA launches
-// conv_tp_kernel: workgroups walk the tiles, two of them per compute unit; its divisors' magic numbers
-void persistent_grid(mpcnn::ConvArgs* a, dim3* grid, int split)
-{
-    a->tiles_total = (int)grid->x;
-    a->mg_cq = magic_of((unsigned)(a->CrPad / 8)); a->mg_hw = magic_of((unsigned)(a->Tx + a->k - 1));
-    a->mg_tx = magic_of((unsigned)a->Tx); a->mg_ntx = magic_of((unsigned)a->ntx);
-    a->mg_nty = magic_of((unsigned)a->nty); a->mg_d = magic_of((unsigned)a->d);
-    grid->x = (unsigned)std::min<long>(grid->x, std::max(1, 2 * kNumCU / split));
-}
-
 // conv_parts_kernel: the plan's workgroups walk the tiles; its divisors' magic numbers
 void parts_grid(mpcnn::ConvArgs* a, dim3* grid, const TilePlan& tp)
 {
@@ -955,15 +790,13 @@ void parts_grid(mpcnn::ConvArgs* a, dim3* grid, const TilePlan& tp)
 
 // (the kernel instances live in launch_*.hip, one translation unit per family)
 template <typename T>
-bool launch_conv_mfma(const mpcnn::ConvArgs& a, const ChanTiling& ct, const TilePlan& tp, dim3 grid,
-                      hipStream_t st, bool bm = false)
+bool launch_conv(const mpcnn::ConvArgs& a, const TilePlan& tp, dim3 grid, hipStream_t st)
 {
-    if (tp.CB > 0)
-        return a.mode >= mpcnn::kDgradTanh ? mpcnn::launch_conv_parts_f32_back(a, tp.CB, tp.in, grid, tp.lds, st)
-                                           : mpcnn::launch_conv_parts_f32_fwd(a, tp.CB, tp.in, grid, tp.lds, st);
-    if (bm) return ct.W == 32 && mpcnn::launch_conv_bm(a, ct.OT, tp.PT, tp.NW, tp.MP, grid, tp.lds, st);
-    if constexpr (std::is_same<T, float>::value) return false;
-    else return mpcnn::launch_conv_b16(a, ct.W, ct.OT, tp.PT, tp.NW, tp.MP, grid, tp.lds, st);
+    const bool back = a.mode >= mpcnn::kDgradTanh;
+    if constexpr (std::is_same<T, float>::value)
+        return (back ? mpcnn::launch_conv_parts_f32_back : mpcnn::launch_conv_parts_f32_fwd)(a, tp.in, grid, tp.lds, st);
+    else
+        return (back ? mpcnn::launch_conv_parts_b16_back : mpcnn::launch_conv_parts_b16_fwd)(a, tp.in, grid, tp.lds, st);
 }
 template <typename T>
 bool launch_wgrad_mfma(const mpcnn::WgradArgs& a, int hl, dim3 grid, size_t lds, hipStream_t st)
@@ -1005,7 +838,7 @@ bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipS
 // Kernels that may ask for more than 64 KiB of dynamic LDS must say so once.
 mpcnn_status set_lds_attrs(bool bf16_storage)
 {
-    if (bf16_storage) { HIP_TRY(mpcnn::conv_attrs_b16()); HIP_TRY(mpcnn::wgrad_attrs_b16()); }
+    if (bf16_storage) { HIP_TRY(mpcnn::conv_parts_attrs_b16_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_b16_back()); HIP_TRY(mpcnn::wgrad_attrs_b16()); }
     else { HIP_TRY(mpcnn::conv_parts_attrs_f32_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_f32_back());
            HIP_TRY(mpcnn::wgrad_attrs_f32()); HIP_TRY(mpcnn::wgrad_parts_attrs()); }
     return MPCNN_OK;
@@ -1066,39 +899,16 @@ mpcnn_status refresh_packs(mpcnn_net* net, hipStream_t st)
         const Layer& ly = net->layers[l];
         if (ly.kind == MPCNN_MP) continue;
         const float* Wc = net->d_wread + ly.p_off;
-        if (ly.parts) {
-            if (ly.fwd_mfma)
-                LAUNCH("pack_weights", l, 0, 0, 10.0 * ly.fwd_pack_len,
-                       mpcnn::pack_parts_kernel<3><<<grid_for((long)ly.fwd_pack_len / 12), 256, 0, st>>>(
-                           Wc, (mpcnn::bf16*)(net->d_packs + ly.fwd_pack_off), ly.k * ly.k2, ly.cin, ly.cout, ly.fwd_rpad,
-                           ly.fwd_ct.pad, parts_block(ly.fwd_rpad), 0));
-            if (ly.dgrad_mfma && l > 0)
-                LAUNCH("pack_weights", l, 0, 0, 10.0 * ly.dgrad_pack_len,
-                       mpcnn::pack_parts_kernel<3><<<grid_for((long)ly.dgrad_pack_len / 12), 256, 0, st>>>(
-                           Wc, (mpcnn::bf16*)(net->d_packs + ly.dgrad_pack_off), ly.k * ly.k2, ly.cin, ly.cout, ly.dgrad_rpad,
-                           ly.dgrad_ct.pad, parts_block(ly.dgrad_rpad), 1));
-            continue;
-        }
-        if (ly.fwd_mfma && ly.fwd_bm)
-            LAUNCH("pack_weights", l, 0, 0, 6.0 * ly.fwd_pack_len,
-                   mpcnn::pack_weights_bf16_kernel<<<grid_for((long)ly.fwd_pack_len), 256, 0, st>>>(
-                       Wc, (mpcnn::bf16*)(net->d_packs + ly.fwd_pack_off), ly.k * ly.k2, ly.cin, ly.cout,
-                       ly.fwd_rpad, ly.fwd_ct.pad, 0));
-        else if (ly.fwd_mfma)
-            LAUNCH("pack_weights", l, 0, 0, 8.0 * ly.fwd_pack_len,
-                   mpcnn::pack_weights_kernel<<<grid_for((long)ly.fwd_pack_len), 256, 0, st>>>(
-                       Wc, net->d_packs + ly.fwd_pack_off, ly.k * ly.k2, ly.cin, ly.cout, ly.fwd_rpad,
-                       ly.fwd_ct.pad, 64 / ly.fwd_ct.W, 0));
-        if (ly.dgrad_mfma && l > 0 && ly.dgrad_bm)
-            LAUNCH("pack_weights", l, 0, 0, 6.0 * ly.dgrad_pack_len,
-                   mpcnn::pack_weights_bf16_kernel<<<grid_for((long)ly.dgrad_pack_len), 256, 0, st>>>(
-                       Wc, (mpcnn::bf16*)(net->d_packs + ly.dgrad_pack_off), ly.k * ly.k2, ly.cin, ly.cout,
-                       ly.dgrad_rpad, ly.dgrad_ct.pad, 1));
-        else if (ly.dgrad_mfma && l > 0)
-            LAUNCH("pack_weights", l, 0, 0, 8.0 * ly.dgrad_pack_len,
-                   mpcnn::pack_weights_kernel<<<grid_for((long)ly.dgrad_pack_len), 256, 0, st>>>(
-                       Wc, net->d_packs + ly.dgrad_pack_off, ly.k * ly.k2, ly.cin, ly.cout,
-                       ly.dgrad_rpad, ly.dgrad_ct.pad, 64 / ly.dgrad_ct.W, 1));
+        auto pack = [&](size_t off, size_t len, int rpad, int opad, int back) {
+            mpcnn::bf16* const out = (mpcnn::bf16*)(net->d_packs + off);
+            const int kk = ly.k * ly.k2, wgs = grid_for((long)(len / (net->bf16 ? 4 : 12)));
+            if (net->bf16) mpcnn::pack_parts_kernel<1><<<wgs, 256, 0, st>>>(Wc, out, kk, ly.cin, ly.cout, rpad, opad, back);
+            else mpcnn::pack_parts_kernel<3><<<wgs, 256, 0, st>>>(Wc, out, kk, ly.cin, ly.cout, rpad, opad, back);
+        };
+        if (ly.fwd_mfma)
+            LAUNCH("pack_weights", l, 0, 0, 4.0 * (ly.fwd_pack_len + ly.p_len), pack(ly.fwd_pack_off, ly.fwd_pack_len, ly.fwd_rpad, ly.fwd_ct.pad, 0));
+        if (ly.dgrad_mfma && l > 0)
+            LAUNCH("pack_weights", l, 0, 0, 4.0 * (ly.dgrad_pack_len + ly.p_len), pack(ly.dgrad_pack_off, ly.dgrad_pack_len, ly.dgrad_rpad, ly.dgrad_ct.pad, 1));
     }
     HIP_TRY(hipGetLastError());
     net->packs_stale = false;
@@ -1198,11 +1008,9 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.Ty = tp.Ty; a.Tx = tp.Tx; a.nty = tp.nty; a.ntx = tp.ntx;
                 a.mode = ly.tanh_out ? kFwdTanh : kFwdLinear; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.fwd_ct.split);
-                if (tp.CB > 0) { parts_grid(&a, &grid, tp); a.wraw = Wk; }
-                else if (ly.fwd_bm) persistent_grid(&a, &grid, ly.fwd_ct.split);
+                parts_grid(&a, &grid, tp); a.wraw = Wk;
                 bool launched = false;
-                LAUNCH(tp.CB > 0 ? "conv_fwd_parts" : ly.fwd_bm ? "conv_fwd_bm" : "conv_fwd_mfma", l, step, flops, bytes,
-                       launched = launch_conv_mfma<T>(a, ly.fwd_ct, tp, grid, st, ly.fwd_bm));
+                LAUNCH(kF32 ? "conv_fwd_parts" : "conv_fwd_bm", l, step, flops, bytes, launched = launch_conv<T>(a, tp, grid, st));
                 if (!launched)   // a plan without a kernel instance: a planner bug, never a silent skip
                     return fail(MPCNN_EUNSUPPORTED, "layer %zu: no convolution kernel instance for its forward plan", l);
             } else if (!kF32 && l == 0 && ly.dil == 1 && Ci <= 4 && ly.cout <= 64 && (ly.k == 3 || ly.k == 5 || ly.k == 7)) {
@@ -1435,11 +1243,9 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                 a.Ty = tp.Ty; a.Tx = tp.Tx; a.nty = tp.nty; a.ntx = tp.ntx;
                 a.mode = below_tanh ? kDgradTanh : kDgradPlain; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.dgrad_ct.split);
-                if (tp.CB > 0) { parts_grid(&a, &grid, tp); a.wraw = Wk; }
-                else if (ly.dgrad_bm) persistent_grid(&a, &grid, ly.dgrad_ct.split);
+                parts_grid(&a, &grid, tp); a.wraw = Wk;
                 bool launched = false;
-                LAUNCH(tp.CB > 0 ? "conv_dgrad_parts" : ly.dgrad_bm ? "conv_dgrad_bm" : "conv_dgrad_mfma", li, dstep, flops, dbytes,
-                       launched = launch_conv_mfma<T>(a, ly.dgrad_ct, tp, grid, st, ly.dgrad_bm));
+                LAUNCH(kF32 ? "conv_dgrad_parts" : "conv_dgrad_bm", li, dstep, flops, dbytes, launched = launch_conv<T>(a, tp, grid, st));
                 if (!launched)
                     return fail(MPCNN_EUNSUPPORTED, "layer %zu: no convolution kernel instance for its data-gradient plan", li);
             } else {
@@ -1651,22 +1457,19 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
             ly.wgrad_mfma = !ly.class_fused;   // any shape: gradient rows are tiled in parameter order
             // (the convolution kernels address a layer's weight pack by 32-bit byte offsets)
             const size_t pack_bound = (size_t)ly.k * ly.k2 * (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) *
-                                      (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) * (net->bf16 ? 4 : 6);
+                                      (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) * 6;
             if (pack_bound >= (1ull << 31)) ly.fwd_mfma = ly.dgrad_mfma = false;
-            // bf16 storage with channel counts that are multiples of 8: the bf16 matrix instruction
-            ly.fwd_bm = net->bf16 && !ly.rect && ly.fwd_mfma && ly.cin % 8 == 0;
-            ly.dgrad_bm = net->bf16 && !ly.rect && ly.dgrad_mfma && ly.cout % 8 == 0;
-            ly.parts = !net->bf16;
+            auto pack_floats = [&](int rpad, int pad) { return (size_t)ly.k * ly.k2 * (rpad / 16) * (net->bf16 ? 1 : 3) * 2 * pad * 4; };
             if (ly.fwd_mfma) {
-                ly.fwd_ct = ly.fwd_bm || ly.parts ? chan_tiling_w(ly.cout, 32) : chan_tiling(ly.cout);
+                ly.fwd_ct = chan_tiling(ly.cout);
                 ly.fwd_rpad = ceil_div(ly.cin, 16) * 16;
-                ly.fwd_pack_len = (size_t)ly.k * ly.k2 * ly.fwd_rpad * ly.fwd_ct.pad * (ly.parts ? 3 : 2) / 2;   // in floats
+                ly.fwd_pack_len = pack_floats(ly.fwd_rpad, ly.fwd_ct.pad);
                 ly.fwd_pack_off = pack; pack += ly.fwd_pack_len;
             }
             if (ly.dgrad_mfma) {
-                ly.dgrad_ct = ly.dgrad_bm || ly.parts ? chan_tiling_w(ly.cin, 32) : chan_tiling(ly.cin);
+                ly.dgrad_ct = chan_tiling(ly.cin);
                 ly.dgrad_rpad = ceil_div(ly.cout, 16) * 16;
-                ly.dgrad_pack_len = (size_t)ly.k * ly.k2 * ly.dgrad_rpad * ly.dgrad_ct.pad * (ly.parts ? 3 : 2) / 2;
+                ly.dgrad_pack_len = pack_floats(ly.dgrad_rpad, ly.dgrad_ct.pad);
                 ly.dgrad_pack_off = pack; pack += ly.dgrad_pack_len;
             }
         }
@@ -1740,18 +1543,12 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         va_end(ap);
         if (n > 0) used = std::min(cap - 1, used + (size_t)n);
     };
-    auto conv = [&](const char* what, const Layer& ly, const TilePlan& tp, const ChanTiling& ct, bool bm) {
+    auto conv = [&](const char* what, const TilePlan& tp, const ChanTiling& ct) {
         if (!tp.ok) { put("  %s: plain kernel\n", what); return; }
-        if (tp.CB > 0) {
-            put("  %s: bf16 MFMA, three parts per number, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
-                "tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what, ct.OT, ct.split, tp.PT, tp.in.WO,
-                tp.in.WP, tp.in.MO, tp.in.MP, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
-            return;
-        }
-        put("  %s: %s %d-wide x %d channel tiles x %d groups, %d position tiles (%d per wave), %d waves, tile %d x %d of a "
-            "residue class, %d x %d tiles, %zu B LDS\n", what,
-            bm ? "bf16 MFMA, tile per wave," : (tp.MP > 0 ? "fp32 MFMA, tile per wave," : "fp32 MFMA, split reduction,"),
-            ct.W, ct.OT, ct.split, tp.PT, tp.MP, tp.MP > 0 ? ct.OT * tp.PT / tp.MP : tp.NW, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.lds);
+        put("  %s: bf16 MFMA, %s, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
+            "%d channels per block, tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what,
+            net->bf16 ? "one part per number" : "three parts per number", ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
+            tp.in.CB, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
     };
     put("workspace %zu bytes\n", g.total);
     for (size_t l = 0; l < net->layers.size(); ++l) {
@@ -1768,9 +1565,9 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
                  (long)B * g.rows[l] * g.cols[l] < (1l << 31) / 32)
             put("  forward: image-layer kernel on the fp32 MFMA\n");
         else
-            conv("forward", ly, g.fwd[l], ly.fwd_ct, ly.fwd_bm);
+            conv("forward", g.fwd[l], ly.fwd_ct);
         if (!training) continue;
-        if (l > 0) conv("data gradient", ly, g.dgrad[l], ly.dgrad_ct, ly.dgrad_bm);
+        if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct);
         const WgradPlan& w = g.wgrad[l];
         if (l == 0 && g.l0_fused) put("  weight gradient: fused with the routing of the pool above, %d workgroups\n", g.l0_blocks);
         else if (w.l0m) put("  weight gradient: image-layer kernel on the fp32 MFMA, %d tiles of 8 x 32, %d workgroups\n", w.tiles_total, w.chunks);

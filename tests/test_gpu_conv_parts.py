@@ -1,5 +1,5 @@
-"""fp32 convolutions and weight gradients whose products are made of bf16 parts (csrc/kernels_conv_parts.hpp,
-csrc/kernels_wgrad_parts.hpp): shapes at the edges of their tiles, channel blocks and groups against the oracle,
+"""Convolutions (either storage type) and fp32 weight gradients on the bf16 matrix instruction, fp32 numbers as sums of
+bf16 parts (csrc/kernels_conv_parts.hpp, csrc/kernels_wgrad_parts.hpp): shapes at the edges of their tiles, channel blocks and groups against the oracle,
 numbers that have no parts, and the distance from 64-bit sums."""
 import numpy as np
 import pytest
@@ -25,9 +25,10 @@ EDGES = [
 ]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("name,layers,patch,height,width", EDGES, ids=[e[0] for e in EDGES])
-def test_tile_and_channel_edges(name, layers, patch, height, width):
-    full_parity(wl.Workload("parts_" + name, layers, patch, 1, layers[-1][1], 2, height, width, 0.2, "ellipses",
+def test_tile_and_channel_edges(name, layers, patch, height, width, dtype):
+    full_parity(wl.Workload("parts_" + name, layers, patch, 1, layers[-1][1], 2, height, width, 0.2, "ellipses", dtype=dtype,
                             seed_image=1141, seed_label=2141, seed_param=3141), with_pixw=True)
 
 
