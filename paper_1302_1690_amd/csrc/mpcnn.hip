@@ -205,6 +205,8 @@ struct mpcnn_net {
     float* d_packs = nullptr;
     bool packs_stale = true;
     int device = -1;
+    float* h_stage = nullptr;     // pinned host memory for one parameter vector: set / get of parameters and gradients
+    mutable std::mutex stage_mu;  // (gets are const calls)
     bool lds_attr_set = false;
     // plans of the sizes seen so far (oldest dropped first)
     mutable std::vector<std::pair<GeomKey, std::shared_ptr<const Geom>>> geoms;
@@ -895,21 +897,29 @@ mpcnn_status refresh_packs(mpcnn_net* net, hipStream_t st)
     }
     net->wread_stale = false;
     if (!net->packs_stale || !net->d_packs) { net->packs_stale = false; return MPCNN_OK; }
+    mpcnn::PackArgs pa{};
+    pa.W = net->d_wread; pa.Q = net->d_packs;
+    double bytes = 0;
+    auto flush = [&]() {
+        if (!pa.n_seg) return;
+        LAUNCH("pack_weights", -1, 0, 0, bytes,
+               net->bf16 ? mpcnn::pack_parts_kernel<1><<<(unsigned)pa.total_blocks, 256, 0, st>>>(pa)
+                         : mpcnn::pack_parts_kernel<3><<<(unsigned)pa.total_blocks, 256, 0, st>>>(pa));
+        pa.n_seg = pa.total_blocks = 0; bytes = 0;
+    };
+    auto add = [&](const Layer& ly, size_t off, size_t len, int rpad, int opad, int back) {
+        if (pa.n_seg == mpcnn::kMaxPackSegs) flush();
+        pa.seg[pa.n_seg++] = {(long)ly.p_off, (long)off, ly.k * ly.k2, ly.cin, ly.cout, rpad, opad, back, pa.total_blocks};
+        pa.total_blocks += (int)((len / (net->bf16 ? 4 : 12) + 255) / 256);   // 16 bytes per part and thread
+        bytes += 4.0 * (len + ly.p_len);
+    };
     for (size_t l = 0; l < net->layers.size(); ++l) {
         const Layer& ly = net->layers[l];
         if (ly.kind == MPCNN_MP) continue;
-        const float* Wc = net->d_wread + ly.p_off;
-        auto pack = [&](size_t off, size_t len, int rpad, int opad, int back) {
-            mpcnn::bf16* const out = (mpcnn::bf16*)(net->d_packs + off);
-            const int kk = ly.k * ly.k2, wgs = grid_for((long)(len / (net->bf16 ? 4 : 12)));
-            if (net->bf16) mpcnn::pack_parts_kernel<1><<<wgs, 256, 0, st>>>(Wc, out, kk, ly.cin, ly.cout, rpad, opad, back);
-            else mpcnn::pack_parts_kernel<3><<<wgs, 256, 0, st>>>(Wc, out, kk, ly.cin, ly.cout, rpad, opad, back);
-        };
-        if (ly.fwd_mfma)
-            LAUNCH("pack_weights", l, 0, 0, 4.0 * (ly.fwd_pack_len + ly.p_len), pack(ly.fwd_pack_off, ly.fwd_pack_len, ly.fwd_rpad, ly.fwd_ct.pad, 0));
-        if (ly.dgrad_mfma && l > 0)
-            LAUNCH("pack_weights", l, 0, 0, 4.0 * (ly.dgrad_pack_len + ly.p_len), pack(ly.dgrad_pack_off, ly.dgrad_pack_len, ly.dgrad_rpad, ly.dgrad_ct.pad, 1));
+        if (ly.fwd_mfma) add(ly, ly.fwd_pack_off, ly.fwd_pack_len, ly.fwd_rpad, ly.fwd_ct.pad, 0);
+        if (ly.dgrad_mfma && l > 0) add(ly, ly.dgrad_pack_off, ly.dgrad_pack_len, ly.dgrad_rpad, ly.dgrad_ct.pad, 1);
     }
+    flush();
     HIP_TRY(hipGetLastError());
     net->packs_stale = false;
     return MPCNN_OK;
@@ -1295,35 +1305,21 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
     return MPCNN_OK;
 }
 
-// host parameter order W[o][c][u][v], b[o]  <->  device order W[u][v][c][o], b[o]
-void to_device_order(const mpcnn_net* net, const float* host, float* dev_order)
+// One parameter vector between its device order W[u][v][c][o], b[o] and pinned host memory in host order
+// W[o][c][u][v], b[o]; waits for it.
+mpcnn_status order_params(const mpcnn_net* net, float* dev, bool to_host)
 {
+    mpcnn::ParamOrder a{};
     for (const Layer& ly : net->layers) {
         if (ly.kind == MPCNN_MP) continue;
-        const int kk = ly.k * ly.k2, ci = ly.cin, co = ly.cout;
-        const float* src = host + ly.p_off;
-        float* dst = dev_order + ly.p_off;
-        for (int o = 0; o < co; ++o)
-            for (int c = 0; c < ci; ++c)
-                for (int t = 0; t < kk; ++t)
-                    dst[((size_t)t * ci + c) * co + o] = src[((size_t)o * ci + c) * kk + t];
-        memcpy(dst + (size_t)kk * ci * co, src + (size_t)kk * ci * co, sizeof(float) * co);
+        a.off[a.n_seg] = (long)ly.p_off; a.ci[a.n_seg] = ly.cin; a.co[a.n_seg] = ly.cout; a.kk[a.n_seg] = ly.k * ly.k2;
+        ++a.n_seg;
     }
-}
-
-void to_host_order(const mpcnn_net* net, const float* dev_order, float* host)
-{
-    for (const Layer& ly : net->layers) {
-        if (ly.kind == MPCNN_MP) continue;
-        const int kk = ly.k * ly.k2, ci = ly.cin, co = ly.cout;
-        const float* src = dev_order + ly.p_off;
-        float* dst = host + ly.p_off;
-        for (int o = 0; o < co; ++o)
-            for (int c = 0; c < ci; ++c)
-                for (int t = 0; t < kk; ++t)
-                    dst[((size_t)o * ci + c) * kk + t] = src[((size_t)t * ci + c) * co + o];
-        memcpy(dst + (size_t)kk * ci * co, src + (size_t)kk * ci * co, sizeof(float) * co);
-    }
+    a.off[a.n_seg] = (long)net->n_params;
+    mpcnn::params_order_kernel<<<grid_for((long)net->n_params, 256, 1024), 256>>>(dev, net->h_stage, a, to_host ? 1 : 0);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(nullptr));
+    return MPCNN_OK;
 }
 
 void lbfgs_free(mpcnn_net* net)
@@ -1342,12 +1338,13 @@ mpcnn_status read_back(const mpcnn_net* net, const float* dev, float* host, size
     if (!net || !host) return fail(MPCNN_EINVAL, "null argument");
     if (n != net->n_params) return fail(MPCNN_EINVAL, "n = %zu, net has %zu parameters", n, net->n_params);
     if (!dev) return fail(MPCNN_EINVAL, "parameters were never set");
-    std::vector<float> tmp(n);
     HIP_TRY(hipSetDevice(net->device));
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(tmp.data(), dev, sizeof(float) * n, hipMemcpyDeviceToHost));
-    to_host_order(net, tmp.data(), host);
-    return MPCNN_OK;
+    std::lock_guard<std::mutex> lock(net->stage_mu);
+    if (!net->h_stage) return fail(MPCNN_ENOMEM, "no pinned host memory");
+    const mpcnn_status rc = order_params(net, const_cast<float*>(dev), true);
+    if (rc == MPCNN_OK) memcpy(host, net->h_stage, sizeof(float) * n);
+    return rc;
 }
 
 // The plan for these sizes: from the net's cache, or made now and kept (same != 0: the
@@ -1499,6 +1496,7 @@ void mpcnn_net_destroy(mpcnn_net* net)
         (void)hipFree(net->d_params);
         (void)hipFree(net->d_grads);
         (void)hipFree(net->d_packs);
+        (void)hipHostFree(net->h_stage);
     }
     for (auto& p : net->pending) { (void)hipEventDestroy(p.e0); (void)hipEventDestroy(p.e1); }
     for (auto e : net->pool) (void)hipEventDestroy(e);
@@ -1593,6 +1591,7 @@ mpcnn_status mpcnn_set_params(mpcnn_net* net, const float* params_host, size_t n
         HIP_TRY(hipGetDevice(&net->device));
         HIP_TRY(hipMalloc((void**)&net->d_params, sizeof(float) * n));
         HIP_TRY(hipMalloc((void**)&net->d_grads, sizeof(float) * n));
+        HIP_TRY(hipHostMalloc((void**)&net->h_stage, sizeof(float) * n, hipHostMallocDefault));
         HIP_TRY(hipMemset(net->d_grads, 0, sizeof(float) * n));
         if (net->pack_len) HIP_TRY(hipMalloc((void**)&net->d_packs, sizeof(float) * net->pack_len));
         if (net->bf16) HIP_TRY(hipMalloc((void**)&net->d_wread, sizeof(float) * n));
@@ -1610,11 +1609,15 @@ mpcnn_status mpcnn_set_params(mpcnn_net* net, const float* params_host, size_t n
         rc = scratch_address(net->device, &unused);
         if (rc != MPCNN_OK) return rc;
     }
-    std::vector<float> tmp(n);
-    to_device_order(net, params_host, tmp.data());
     HIP_TRY(hipSetDevice(net->device));
     HIP_TRY(hipDeviceSynchronize());
-    HIP_TRY(hipMemcpy(net->d_params, tmp.data(), sizeof(float) * n, hipMemcpyHostToDevice));
+    {
+        std::lock_guard<std::mutex> lock(net->stage_mu);
+        if (!net->h_stage) return fail(MPCNN_ENOMEM, "no pinned host memory");
+        memcpy(net->h_stage, params_host, sizeof(float) * n);
+        const mpcnn_status rc = order_params(net, net->d_params, false);
+        if (rc != MPCNN_OK) return rc;
+    }
     net->packs_stale = true; net->wread_stale = true;
     net->lb_head = net->lb_count = 0; net->lb_have_prev = false;   // a new starting point has no history
     return MPCNN_OK;
