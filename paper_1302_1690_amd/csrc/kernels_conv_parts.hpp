@@ -38,10 +38,11 @@
 // Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
 //   fp32, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 (fp32 instruction) -> 461, 870, 666, 1110 (226, 231, 209, 165 TFLOP/s);
 //     data gradient 1060, 1790, 1250, 1880 -> 490, 851, 628, 981 (213, 236, 221, 187).  The loop sustains 240-260 on random
-//     data (362 on zero weights: the power limit takes the clock down to 1.7-2.1 GHz).
+//     data, 362 on zero weights with the same instructions: what a power limit would do.
 //   bf16, 2 x 2048 x 2048: forward 1156, 1982, 1845, 4009 (two kernels of one part before) -> 1095, 1746, 1725, 3211;
-//     data gradient 1021, 1898, 1501, 2580 -> 947, 1799, 1446, 2430.  Matrix pipes busy 20-50 %: a tile's tanh, stores
-//     and halo take as long as its instructions.
+//     data gradient 1021, 1898, 1501, 2580 -> 947, 1799, 1446, 2430.  Matrix pipes busy 20-50 %: without the next
+//     halo's loads the forward takes 861, 1379, 1377, 2578, without stores 996, 1633, 1550, 2766, without tanh 1083, 1745, 1724,
+//     3184, without the multiplications 595, 694, 1010, 2563 (1131, 1798, 1817, 3357 whole in that run).
 //   The bias from LDS instead of memory (its loads queued behind the halo's) took the bf16 forward from 8.8 to 7.9 ms.
 // Tried and dropped: 2 x 4 tiles per wave with one part (registers spill; 3.4 ms for the last layer's data gradient), three
 // workgroups per compute unit (the same, 3.9 ms for its forward).

@@ -26,8 +26,8 @@
 //
 // Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), before (fp32 instruction) and
 // now: 985, 1780, 1210, 2030 us -> 506, 967, 683, 1243 us (206, 208, 204, 148 TFLOP/s; what the split instruction sustains on
-// random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 50-70 % at the clock the power
-// limit leaves.  The conversions decide the rest: with every item's address worked out per tile and numbers
+// random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 50-70 %.
+// The conversions decide the rest: with every item's address worked out per tile and numbers
 // converted one by one (480 vector instructions per thread and tile of 32 positions instead of 300) it was 575, 1062, 811, 1540.
 #pragma once
 #include "kernels_conv_parts.hpp"

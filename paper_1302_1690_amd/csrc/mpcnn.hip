@@ -288,29 +288,37 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
         const double eff = P == 3 ? (per_wave >= 4 ? 1.0 : (per_wave == 2 ? 1.08 : 1.3)) : (per_wave >= 4 ? 1.0 : 1.5);
         const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
-        for (int ty = 1; ty <= std::min(fh, 32 * PT); ++ty)
-            for (int tx = 1; tx <= std::min(fw, 32 * PT / ty); ++tx) {
-                const int npos = (ty + k - 1) * (tx + k2 - 1), rounds = ceil_div(npos, RP);
-                if (rounds > mpcnn::parts_items(P)) break;
-                const size_t lds = rounds * RP * pitch + 32 * ct.OT * sizeof(float);   // the halo, the bias
-                if (lds > (size_t)80 * 1024) break;
-                // (byte offsets inside a tile's halo are 31 bits)
-                if (((size_t)(ty + k - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) break;
-                const int nty = ceil_div(fh, ty), ntx = ceil_div(fw, tx);
-                const long tiles = (long)B * d * d2 * nty * ntx;
-                if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
-                const long wgs = std::min<long>(tiles, std::max(1, 2 * kNumCU / ct.split));
-                const double per_wg = (double)((tiles + wgs - 1) / wgs);
-                const double per_cu = per_wg * std::ceil((double)wgs * ct.split / kNumCU);
-                const double t_rest = (double)npos * cr * es / 10 + 2500.0 * nblk + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
-                const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * t_mul + 0.25 * t_rest) + t_rest;
-                if (!best.ok || cost < best_cost) {
-                    best.PT = PT; best.Ty = ty; best.Tx = tx;
-                    best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
-                    best.wgs = (int)wgs; best.in = in;
-                    best_cost = cost;
-                }
+        // (tiles that share a residue class's rows, and its columns, as evenly as their number allows; of those with ty rows
+        // the widest that fits)
+        const int lds_pos = (int)(((size_t)80 * 1024 - 32 * ct.OT * sizeof(float)) / (RP * pitch)) * RP;
+        const int max_pos = std::min(lds_pos, mpcnn::parts_items(P) * RP);       // positions of the halo
+        int last_ty = 0;
+        for (int ny = fh; ny >= ceil_div(fh, std::min(fh, 32 * PT)); --ny) {
+            const int ty = ceil_div(fh, ny);
+            if (ty == last_ty) continue;
+            last_ty = ty;
+            const int room = std::min(std::min(fw, 32 * PT / ty), max_pos / (ty + k - 1) - (k2 - 1));
+            if (room < 1) continue;
+            const int ntx = ceil_div(fw, room), tx = ceil_div(fw, ntx), nty = ceil_div(fh, ty);
+            const int npos = (ty + k - 1) * (tx + k2 - 1);
+            const size_t lds = ceil_div(npos, RP) * RP * pitch + 32 * ct.OT * sizeof(float);   // the halo in whole rounds, the bias
+            // (byte offsets inside a tile's halo are 31 bits)
+            if (((size_t)(ty + k - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) continue;
+            const long tiles = (long)B * d * d2 * nty * ntx;
+            if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
+            const long wgs = std::min<long>(tiles, std::max(1, 2 * kNumCU / ct.split));
+            const double per_cu = std::ceil((double)tiles * ct.split / kNumCU);
+            const double t_rest = (double)npos * cr * es / 10 + 2500.0 * nblk + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
+            // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
+            // the pitch keeps only successive positions on different LDS banks)
+            const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
+            if (!best.ok || cost < best_cost) {
+                best.PT = PT; best.Ty = ty; best.Tx = tx;
+                best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
+                best.wgs = (int)wgs; best.in = in;
+                best_cost = cost;
             }
+        }
     }
     if (!best.ok && (hint_pt || hint_mp))   // a pair that no instance serves
         return plan_conv_parts(B, in_c, out_r, out_c, d, d2, k, k2, cr, rpad, co, ct, P, es, back, 0, 0);
