@@ -14,6 +14,7 @@
 // one partial result in parameter order, bias row last (added by reduce_all_kernel, flat segments).
 #pragma once
 #include "kernels_mfma.hpp"
+#include "kernels_wgrad_tr.hpp"
 
 namespace mpcnn {
 
@@ -167,6 +168,152 @@ __global__ __launch_bounds__(256) void l0_wgrad_mfma_kernel(L0WgradArgs a)
     for (int e = tid; e < (ROWS + 1) * 32; e += 256) {
         const int row = e >> 5, o = e & 31;
         if (o < nco) part[(long)row * a.Co + oc0 + o] = row < ROWS ? red[row * 32 + o] : red[MT * 1024 + o];
+    }
+}
+
+// The same gradient with bf16 storage on v_mfma_f32_32x32x16_bf16, for map counts that are a multiple of 8 (deltas are
+// staged as raw 128-bit copies; other counts stay on the kernel above).  16 positions of a tile row per instruction, a lane supplying 8 of
+// them for ONE gradient row or ONE map; image, deltas and their products are exact here, sums are fp32 as above.
+//   maps: the delta tile is [position][32 maps], read with the transposing LDS read (kernels_wgrad_tr.hpp).
+//   gradient rows: 8 successive columns of one channel, shifted by the tap - a read at any multiple of 2 bytes, which the LDS
+// serves lane by lane.  So the tile is kept K times, copy v shifted by v columns: LDS row hy*(K*C) + v*C + c holds channel
+// c of image row hy at columns v .. v + 31.  Gradient row m = (u*K + v)*C + c of tile row ty is then LDS row ty*(K*C) + m,
+// an aligned 128-bit read, and a pitch of 80 bytes spreads 8 successive rows over all banks.
+//   bias: gradient row K*K*C (there is always one left in the last row tile) reads ones, whatever the tile row.
+// Bound: memory (deltas once: about 100 us of the case below at a device copy's rate).  Measured on 2 x 2048 x 2048, 3 channels, k5,
+// 32 maps: 1066 us (74 TFLOP/s on the fp32 instruction) -> 166 us, 472 TFLOP/s, 3.3 TB/s.
+constexpr int kL0bPitch = 80;   // bytes of an LDS row: 32 columns, 16 bytes of padding
+
+template <int K, int C>
+__global__ __launch_bounds__(256, 2) void l0_wgrad_bm_kernel(L0WgradArgs a)
+{
+    constexpr int R = K * C, ROWS = K * R, MT = (ROWS + 31) / 32;
+    static_assert(ROWS % 32 != 0, "a row tile has room for the bias row");
+    constexpr int TY = kL0wTy, TX = kL0wTx, HH = TY + K - 1, HW = TX + K - 1, HWC = HW * C;
+    static_assert(TX == 32 && K <= 7 && 2 * (TX + K - 1) <= kL0bPitch, "two instructions per tile row");
+    constexpr int XROWS = (TY - 1) * R + 32 * MT;           // LDS rows that are read (past HH*R: by gradient rows that don't exist)
+    constexpr int XA = 16;                                  // the first row's left neighbours
+    constexpr int ONES = XA + XROWS * kL0bPitch, DB = ONES + kL0bPitch, DBYTES = TY * TX * 64;
+    constexpr int RED = (MT * 1024) * 4;
+    constexpr int BYTES = DB + DBYTES > RED ? DB + DBYTES : RED;
+    static_assert(DB % 16 == 0 && XROWS >= HH * R && BYTES <= 64 * 1024, "LDS layout");
+    __shared__ __attribute__((aligned(16))) char smem[BYTES];
+    const unsigned short* in_t = static_cast<const unsigned short*>(a.in);      // bf16, moved as they are
+    const bf16* dy_t = static_cast<const bf16*>(a.dY);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lt = lane & 31, lg = lane >> 5;
+    const int oc0 = 32 * blockIdx.y;
+    const int nco = a.Co - oc0 < 32 ? a.Co - oc0 : 32;      // maps of this slice
+
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    // every byte that is read is written: rows of gradient rows that don't exist hold zeros, the ones row ones
+    for (int e = tid; e < DB / 4; e += 256) reinterpret_cast<unsigned*>(smem)[e] = e >= ONES / 4 ? 0x3f803f80u : 0u;
+
+    v16f acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[mt][r] = 0.f;
+
+    // A tile's values wait in registers while the tile before it is multiplied.
+    constexpr int XN = (HH * HWC + 255) / 256;              // image values per thread
+    constexpr int DN = TY * TX * 4 / 256;                   // items of 8 deltas
+    unsigned short xr[XN];
+    u4 dr[DN];
+    auto fetch = [&](int t) {
+        int bid = t;
+        const int txi = bid % a.ntx; bid /= a.ntx;
+        const int tyi = bid % a.nty;
+        const int b = bid / a.nty;
+        const int y0 = tyi * TY, x0 = txi * TX;
+        // outside the image, outside the map, maps past the last: zeros
+        const unsigned short* img = in_t + (long)b * a.Hi * a.Wi * C;
+#pragma unroll
+        for (int i = 0; i < XN; ++i) {
+            const int e = tid + 256 * i;
+            const int hy = e / HWC, hx = e - hy * HWC;
+            const int iy = y0 + hy, ie = x0 * C + hx;
+            const bool ok = e < HH * HWC && iy < a.Hi && ie < a.Wi * C;
+            xr[i] = img[ok ? (long)iy * a.Wi * C + ie : 0];
+            if (!ok) xr[i] = 0;
+        }
+        const bf16* dyb = dy_t + (long)b * a.Ho * a.Wo * a.Co;
+#pragma unroll
+        for (int i = 0; i < DN; ++i) {
+            const int e = tid + 256 * i, pos = e >> 2, q = e & 3;
+            const int y = y0 + pos / TX, x = x0 + pos % TX;
+            const bool ok = y < a.Ho && x < a.Wo && 8 * q < nco;
+            dr[i] = *reinterpret_cast<const u4*>(dyb + (ok ? ((long)y * a.Wo + x) * a.Co + oc0 + 8 * q : 0));
+            if (!ok) dr[i] = (u4){0u, 0u, 0u, 0u};
+        }
+    };
+    auto deposit = [&]() {
+#pragma unroll
+        for (int i = 0; i < XN; ++i) {
+            const int e = tid + 256 * i;
+            const int hy = e / HWC, hx = e - hy * HWC, col = hx / C, c = hx - col * C;
+            // (columns a copy has no place for, up to K - 1 on either side, fall into the padding of its row or of the one before)
+            char* p = smem + XA + (hy * R + c) * kL0bPitch + 2 * col;
+            if (i + 1 < XN || e < HH * HWC) {
+#pragma unroll
+                for (int v = 0; v < K; ++v) *reinterpret_cast<unsigned short*>(p + v * (C * kL0bPitch - 2)) = xr[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < DN; ++i) *reinterpret_cast<u4*>(smem + DB + (tid + 256 * i) * 16) = dr[i];
+    };
+    // operands: gradient row 32 mt + lt, columns 8 lg ..; maps as kernels_wgrad_tr.hpp lays them out
+    const int grp = lane >> 4, r16 = lane & 15;
+    const unsigned lds_base = (unsigned)reinterpret_cast<size_t>(smem);
+    const unsigned bbase = lds_base + DB + (unsigned)((8 * (grp >> 1) + (r16 >> 2)) * 64 + (16 * (grp & 1) + 4 * (r16 & 3)) * 2);
+    const bool bias_lane = 32 * (MT - 1) + lt == ROWS;      // of the last row tile
+    fetch(blockIdx.x);                                      // (the launch has no more workgroups than tiles)
+    __syncthreads();                                        // the cleared LDS
+    for (int t = blockIdx.x; t < a.tiles_total; t += gridDim.x) {
+        deposit();
+        __syncthreads();
+        const int tn = t + gridDim.x;
+        fetch(tn < a.tiles_total ? tn : t);                 // (a last tile fetches itself again: same loads on every path)
+        // ---- this wave's two tile rows: 2 x 16 positions each
+#pragma unroll
+        for (int rw = 0; rw < 2; ++rw) {
+            const int ty = 2 * wave + rw;
+            const int xa = XA + (ty * R + lt) * kL0bPitch + 16 * lg;
+            const int xl = bias_lane ? ONES + 16 * lg : xa + (MT - 1) * 32 * kL0bPitch;
+            const unsigned ba = bbase + (unsigned)(ty * TX * 64);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const tr_bf16x8 bv = s ? tr_fetch<1024>(ba) : tr_fetch<0>(ba);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const int off = (mt == MT - 1 ? xl : xa + mt * 32 * kL0bPitch) + 32 * s;
+                    acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const tr_bf16x8*>(smem + off), bv, acc[mt], 0, 0, 0);
+                }
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- the four waves' sums meet in LDS, wave after wave; then one partial result in parameter order
+    float* red = reinterpret_cast<float*>(smem);            // [MT*32 rows][32 maps]; row ROWS is the bias
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = 32 * mt + 8 * (r >> 2) + 4 * lg + (r & 3);   // register 4n + z: row 8n + 4lg + z, column lt
+                    float* p = red + row * 32 + lt;
+                    *p = w == 0 ? acc[mt][r] : *p + acc[mt][r];
+                }
+        }
+        __syncthreads();
+    }
+    float* part = a.partial + (long)blockIdx.x * ((long)ROWS + 1) * a.Co;
+    for (int e = tid; e < (ROWS + 1) * 32; e += 256) {
+        const int row = e >> 5, o = e & 31;
+        if (o < nco) part[(long)row * a.Co + oc0 + o] = red[row * 32 + o];
     }
 }
 

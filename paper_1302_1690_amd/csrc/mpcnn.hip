@@ -384,6 +384,9 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
     }
     return best;
 }
+// The image layer's weight gradient multiplies on the bf16 instruction where both operands are bf16 and a position's
+// deltas are whole 128-bit items; with fp32 storage, and for other map counts, on the fp32 one.
+inline bool l0_wgrad_on_bm(const Layer& ly, bool bf16) { return bf16 && ly.cout % 8 == 0; }
 // layers that kernel takes: fp32 storage, 128-bit items of both tensors, more than a sliver of input channels
 inline bool wgrad_parts_layer(const Layer& ly, bool bf16) { return !bf16 && ly.wgrad_mfma && ly.cin % 4 == 0 && ly.cin >= 8 && ly.cout % 4 == 0; }
 
@@ -845,6 +848,13 @@ bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipS
 #undef CASE
     return false;
 }
+bool launch_l0_wgrad_bm(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipStream_t st)
+{
+#define CASE(kk, cc) if (k == kk && ci == cc) { mpcnn::l0_wgrad_bm_kernel<kk, cc><<<grid, 256, 0, st>>>(a); return true; }
+    CASE(3, 1) CASE(5, 1) CASE(7, 1) CASE(3, 3) CASE(5, 3) CASE(7, 3)
+#undef CASE
+    return false;
+}
 // Kernels that may ask for more than 64 KiB of dynamic LDS must say so once.
 mpcnn_status set_lds_attrs(bool bf16_storage)
 {
@@ -1237,8 +1247,13 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                 a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ho = Ho; a.Wo = Wo; a.Co = ly.cout;
                 a.nty = ceil_div(Ho, mpcnn::kL0wTy); a.ntx = ceil_div(Wo, mpcnn::kL0wTx); a.tiles_total = wp.tiles_total;
                 bool launched = false;
-                LAUNCH("wgrad_image_mfma", li, wstep, flops, es * (n_in + n_out) + 4.0 * ly.p_len,
-                       launched = launch_l0_wgrad<T>(a, ly.k, Ci, dim3((unsigned)wp.chunks, (unsigned)ceil_div(ly.cout, 32)), st));
+                const dim3 grid((unsigned)wp.chunks, (unsigned)ceil_div(ly.cout, 32));
+                if (l0_wgrad_on_bm(ly, !kF32))
+                    LAUNCH("wgrad_image_bm", li, wstep, flops, es * (n_in + n_out) + 4.0 * ly.p_len,
+                           launched = launch_l0_wgrad_bm(a, ly.k, Ci, grid, st));
+                else
+                    LAUNCH("wgrad_image_mfma", li, wstep, flops, es * (n_in + n_out) + 4.0 * ly.p_len,
+                           launched = launch_l0_wgrad<T>(a, ly.k, Ci, grid, st));
                 if (!launched) return fail(MPCNN_EUNSUPPORTED, "layer 0: no image-layer weight-gradient kernel instance");
             } else {
                 dim3 grid((unsigned)((ly.p_len + 255) / 256), (unsigned)wp.chunks);
@@ -1576,7 +1591,8 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct);
         const WgradPlan& w = g.wgrad[l];
         if (l == 0 && g.l0_fused) put("  weight gradient: fused with the routing of the pool above, %d workgroups\n", g.l0_blocks);
-        else if (w.l0m) put("  weight gradient: image-layer kernel on the fp32 MFMA, %d tiles of 8 x 32, %d workgroups\n", w.tiles_total, w.chunks);
+        else if (w.l0m) put("  weight gradient: image-layer kernel on the %s MFMA, %d tiles of 8 x 32, %d workgroups\n",
+                            l0_wgrad_on_bm(ly, net->bf16) ? "bf16" : "fp32", w.tiles_total, w.chunks);
         else if (!w.ok) put("  weight gradient: plain kernel, %d chunks\n", w.chunks);
         else if (w.PM > 0)
             put("  weight gradient: bf16 MFMA, three parts per number, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
