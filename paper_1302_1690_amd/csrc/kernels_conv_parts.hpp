@@ -24,7 +24,8 @@
 // for all waves of the workgroup) and the LDS (activations) deliver at 32 bytes per cycle each, well
 // below what they can; the loop alone then sustains 2.17 PFLOP/s (362 TFLOP/s of fp32 products).
 // The input halo is brought in CB channels at a time, [position][16 channels][part] in LDS with a pitch
-// that spreads 16 successive positions over all banks, so that an operand is one 128-bit read at
+// that spreads 16 successive positions of one halo row over all banks (a tile's 32 positions lie in several rows: counters read
+// 10-60 % of the LDS cycles as conflicts), so that an operand is one 128-bit read at
 // an immediate offset from one address per position tile and step.
 //
 // Latency.  Workgroups are persistent and walk (tile, channel block) items; the next item's halo is
@@ -40,7 +41,7 @@
 //     data gradient 1060, 1790, 1250, 1880 -> 490, 851, 628, 981 (213, 236, 221, 187).  The loop sustains 240-260 on random
 //     data, 362 on zero weights with the same instructions: what a power limit would do.
 //   bf16, 2 x 2048 x 2048: forward 1156, 1982, 1845, 4009 (two kernels of one part before) -> 1095, 1746, 1725, 3211;
-//     data gradient 1021, 1898, 1501, 2580 -> 947, 1799, 1446, 2430.  Matrix pipes busy 20-50 %: without the next
+//     data gradient 1021, 1898, 1501, 2580 -> 947, 1799, 1446, 2430.  Matrix pipes busy 26-46 %: without the next
 //     halo's loads the forward takes 861, 1379, 1377, 2578, without stores 996, 1633, 1550, 2766, without tanh 1083, 1745, 1724,
 //     3184, without the multiplications 595, 694, 1010, 2563 (1131, 1798, 1817, 3357 whole in that run).
 //   The bias from LDS instead of memory (its loads queued behind the halo's) took the bf16 forward from 8.8 to 7.9 ms.

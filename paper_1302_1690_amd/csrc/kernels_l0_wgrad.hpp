@@ -180,8 +180,8 @@ __global__ __launch_bounds__(256) void l0_wgrad_mfma_kernel(L0WgradArgs a)
 // c of image row hy at columns v .. v + 31.  Gradient row m = (u*K + v)*C + c of tile row ty is then LDS row ty*(K*C) + m,
 // an aligned 128-bit read, and a pitch of 80 bytes spreads 8 successive rows over all banks.
 //   bias: gradient row K*K*C (there is always one left in the last row tile) reads ones, whatever the tile row.
-// Bound: memory (deltas once: about 100 us of the case below at a device copy's rate).  Measured on 2 x 2048 x 2048, 3 channels, k5,
-// 32 maps: 1066 us (74 TFLOP/s on the fp32 instruction) -> 166 us, 472 TFLOP/s, 3.3 TB/s.
+// Bound: memory (deltas once: about 100 us of the case below at a device copy's rate).  Measured on 2 x 2048 x 2048, 3 channels, k7,
+// 32 maps: 1066 us (74 TFLOP/s on the fp32 instruction) -> 166 us, 472 TFLOP/s, 3.5 TB/s.
 constexpr int kL0bPitch = 80;   // bytes of an LDS row: 32 columns, 16 bytes of padding
 
 template <int K, int C>

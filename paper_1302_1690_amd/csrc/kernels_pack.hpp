@@ -67,7 +67,8 @@ __global__ __launch_bounds__(256) void pack_parts_kernel(PackArgs a)
 
 // Parameters or gradients between the device order (layer by layer W[tap][c][o], b[o]) and the host order
 // (W[o][c][tap], b[o]).  `host` is pinned host memory, accessed in order; the scattered side is the device's, which
-// its L2 holds.  On the host the same permutation of 90 K numbers took about 60 us, the copy through pageable
+// its L2 holds.  blockIdx.y picks the layer, so that its place and sizes are uniform (looked up per number they are
+// loads of the argument segment, one after the other).  On the host the same permutation of 90 K numbers took about 60 us, the copy through pageable
 // memory another 20.
 constexpr int kMaxParamSegs = 48;
 struct ParamOrder {
@@ -77,19 +78,17 @@ struct ParamOrder {
 };
 __global__ void params_order_kernel(float* __restrict__ dev, float* __restrict__ host, ParamOrder a, int to_host)
 {
-    const long total = a.off[a.n_seg];
-    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-        int s = 0;
-        while (s + 1 < a.n_seg && e >= a.off[s + 1]) ++s;
-        const int ci = a.ci[s], co = a.co[s], kk = a.kk[s];
-        const long i = e - a.off[s];
+    const int s = blockIdx.y;
+    const long off = a.off[s], n = a.off[s + 1] - off;
+    const int ci = a.ci[s], co = a.co[s], kk = a.kk[s];
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
         long j = i;                       // biases keep their place
         if (i < (long)co * ci * kk) {
             const int q = (int)(i / kk), t = (int)(i - (long)q * kk), o = q / ci, c = q - o * ci;
             j = ((long)t * ci + c) * co + o;
         }
-        if (to_host) host[e] = dev[a.off[s] + j];
-        else dev[a.off[s] + j] = host[e];
+        if (to_host) host[off + i] = dev[off + j];
+        else dev[off + j] = host[off + i];
     }
 }
 

@@ -12,7 +12,7 @@
 //
 // Layout.  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
 // position: the 16 lanes that read 4 positions together meet no bank twice, and with a plane pitch of 128 mod 256
-// bytes neither do the 32 of two planes).  Parts, the second half of an operand and successive chunks are immediates.  A
+// bytes neither do the 32 of two planes; counters, stores included, still read 26-42 % of the LDS cycles as conflicts).  Parts, the second half of an operand and successive chunks are immediates.  A
 // gradient row tile is two UNITS of 16 rows, a unit being (plane, tap): the two halves of the lanes
 // address their units separately, so 16-channel layers fill row tiles with two taps and 100 channels pad
 // to 112, not 128.

@@ -1339,7 +1339,9 @@ mpcnn_status order_params(const mpcnn_net* net, float* dev, bool to_host)
         ++a.n_seg;
     }
     a.off[a.n_seg] = (long)net->n_params;
-    mpcnn::params_order_kernel<<<grid_for((long)net->n_params, 256, 1024), 256>>>(dev, net->h_stage, a, to_host ? 1 : 0);
+    long longest = 1;
+    for (int i = 0; i < a.n_seg; ++i) longest = std::max(longest, a.off[i + 1] - a.off[i]);
+    mpcnn::params_order_kernel<<<dim3((unsigned)grid_for(longest, 256, 1024), (unsigned)a.n_seg), 256>>>(dev, net->h_stage, a, to_host ? 1 : 0);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(nullptr));
     return MPCNN_OK;
@@ -1356,6 +1358,12 @@ void lbfgs_free(mpcnn_net* net)
     net->lb_have_prev = false;
 }
 
+// Vectors up to this size are read back in device order and permuted here.  Reading alone the kernel is faster at any size
+// (319 numbers 22 -> 14.5 us, 90 K 48 -> 29), but waiting for it behind a training step of a tiny net is not: whole call with
+// 319 numbers 128.4 us with a copy, 131.4 with the kernel.  Between the two sizes nothing was measured; the permutation of 2048
+// numbers takes the host 1 to 2 us.
+constexpr size_t kCopyBackMax = 2048;
+
 mpcnn_status read_back(const mpcnn_net* net, const float* dev, float* host, size_t n)
 {
     if (!net || !host) return fail(MPCNN_EINVAL, "null argument");
@@ -1365,6 +1373,20 @@ mpcnn_status read_back(const mpcnn_net* net, const float* dev, float* host, size
     HIP_TRY(hipDeviceSynchronize());
     std::lock_guard<std::mutex> lock(net->stage_mu);
     if (!net->h_stage) return fail(MPCNN_ENOMEM, "no pinned host memory");
+    if (n <= kCopyBackMax) {
+        HIP_TRY(hipMemcpy(net->h_stage, dev, sizeof(float) * n, hipMemcpyDeviceToHost));
+        for (const Layer& ly : net->layers) {
+            if (ly.kind == MPCNN_MP) continue;
+            const int kk = ly.k * ly.k2, ci = ly.cin, co = ly.cout;
+            const float* src = net->h_stage + ly.p_off;
+            float* dst = host + ly.p_off;
+            for (int o = 0; o < co; ++o)
+                for (int c = 0; c < ci; ++c)
+                    for (int t = 0; t < kk; ++t) dst[((size_t)o * ci + c) * kk + t] = src[((size_t)t * ci + c) * co + o];
+            memcpy(dst + (size_t)kk * ci * co, src + (size_t)kk * ci * co, sizeof(float) * co);
+        }
+        return MPCNN_OK;
+    }
     const mpcnn_status rc = order_params(net, const_cast<float*>(dev), true);
     if (rc == MPCNN_OK) memcpy(host, net->h_stage, sizeof(float) * n);
     return rc;
