@@ -1372,7 +1372,6 @@ mpcnn_status read_back(const mpcnn_net* net, const float* dev, float* host, size
     HIP_TRY(hipSetDevice(net->device));
     HIP_TRY(hipDeviceSynchronize());
     std::lock_guard<std::mutex> lock(net->stage_mu);
-    if (!net->h_stage) return fail(MPCNN_ENOMEM, "no pinned host memory");
     if (n <= kCopyBackMax) {
         HIP_TRY(hipMemcpy(net->h_stage, dev, sizeof(float) * n, hipMemcpyDeviceToHost));
         for (const Layer& ly : net->layers) {
@@ -1430,6 +1429,34 @@ mpcnn_status scratch_address(int dev, void** out)
     }
     *out = g_scratch_ptr[dev];
     return MPCNN_OK;
+}
+
+// What set_params allocates on its first call: parameters, gradients, weight packs (all of it, or free_params).
+// d_params being there is what every other call takes for all of it.
+void free_params(mpcnn_net* net)
+{
+    if (net->d_wread != net->d_params) (void)hipFree(net->d_wread);
+    (void)hipFree(net->d_params);
+    (void)hipFree(net->d_grads);
+    (void)hipFree(net->d_packs);
+    (void)hipHostFree(net->h_stage);
+    net->d_params = net->d_grads = net->d_packs = net->d_wread = net->h_stage = nullptr;
+}
+mpcnn_status alloc_params(mpcnn_net* net)
+{
+    const size_t bytes = sizeof(float) * net->n_params;
+    HIP_TRY(hipGetDevice(&net->device));
+    HIP_TRY(hipMalloc((void**)&net->d_params, bytes));
+    HIP_TRY(hipMalloc((void**)&net->d_grads, bytes));
+    HIP_TRY(hipHostMalloc((void**)&net->h_stage, bytes, hipHostMallocDefault));
+    HIP_TRY(hipMemset(net->d_grads, 0, bytes));
+    if (net->pack_len) HIP_TRY(hipMalloc((void**)&net->d_packs, sizeof(float) * net->pack_len));
+    if (net->bf16) HIP_TRY(hipMalloc((void**)&net->d_wread, bytes));
+    else net->d_wread = net->d_params;
+    const mpcnn_status rc = set_lds_attrs(net->bf16);
+    if (rc != MPCNN_OK) return rc;
+    void* unused = nullptr;   // (the static workspace's address on this device, for later calls)
+    return scratch_address(net->device, &unused);
 }
 
 }  // namespace
@@ -1531,17 +1558,13 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
 void mpcnn_net_destroy(mpcnn_net* net)
 {
     if (!net) return;
-    if (net->d_params || net->d_grads || net->d_packs) {
+    if (net->d_params) {
         (void)hipSetDevice(net->device);
         (void)hipDeviceSynchronize();
-        if (net->d_wread && net->d_wread != net->d_params) (void)hipFree(net->d_wread);
         (void)hipFree(net->d_params0);
         (void)hipFree(net->d_scalar);
         lbfgs_free(net);
-        (void)hipFree(net->d_params);
-        (void)hipFree(net->d_grads);
-        (void)hipFree(net->d_packs);
-        (void)hipHostFree(net->h_stage);
+        free_params(net);
     }
     for (auto& p : net->pending) { (void)hipEventDestroy(p.e0); (void)hipEventDestroy(p.e1); }
     for (auto e : net->pool) (void)hipEventDestroy(e);
@@ -1634,16 +1657,12 @@ mpcnn_status mpcnn_set_params(mpcnn_net* net, const float* params_host, size_t n
     if (!net || !params_host) return fail(MPCNN_EINVAL, "null argument");
     if (n != net->n_params) return fail(MPCNN_EINVAL, "n = %zu, net has %zu parameters", n, net->n_params);
     if (!net->d_params) {
-        HIP_TRY(hipGetDevice(&net->device));
-        HIP_TRY(hipMalloc((void**)&net->d_params, sizeof(float) * n));
-        HIP_TRY(hipMalloc((void**)&net->d_grads, sizeof(float) * n));
-        HIP_TRY(hipHostMalloc((void**)&net->h_stage, sizeof(float) * n, hipHostMallocDefault));
-        HIP_TRY(hipMemset(net->d_grads, 0, sizeof(float) * n));
-        if (net->pack_len) HIP_TRY(hipMalloc((void**)&net->d_packs, sizeof(float) * net->pack_len));
-        if (net->bf16) HIP_TRY(hipMalloc((void**)&net->d_wread, sizeof(float) * n));
-        else net->d_wread = net->d_params;
-        mpcnn_status rc = set_lds_attrs(net->bf16);
-        if (rc != MPCNN_OK) return rc;
+        const mpcnn_status rc = alloc_params(net);
+        if (rc != MPCNN_OK) {   // nothing stays: the next call starts from here again
+            free_params(net);
+            (void)hipGetLastError();   // (a failed allocation is not the next launch's error)
+            return rc;
+        }
         const Layer& last = net->layers.back();
         if (last.class_fused) {
             const int kv = last.cin <= 128 ? 2 : 4;
@@ -1651,15 +1670,11 @@ mpcnn_status mpcnn_set_params(mpcnn_net* net, const float* params_host, size_t n
             if (occ > 0) net->class_max_blocks = std::min(kLossBlocks, kNumCU * occ);
         }
         net->geoms.clear();   // plans made before this point counted the class layer's shares differently
-        void* unused = nullptr;   // (the static workspace's address on this device, for later calls)
-        rc = scratch_address(net->device, &unused);
-        if (rc != MPCNN_OK) return rc;
     }
     HIP_TRY(hipSetDevice(net->device));
     HIP_TRY(hipDeviceSynchronize());
     {
         std::lock_guard<std::mutex> lock(net->stage_mu);
-        if (!net->h_stage) return fail(MPCNN_ENOMEM, "no pinned host memory");
         memcpy(net->h_stage, params_host, sizeof(float) * n);
         const mpcnn_status rc = order_params(net, net->d_params, false);
         if (rc != MPCNN_OK) return rc;
