@@ -2,27 +2,34 @@
 // (v_mfma_f32_32x32x16_bf16), for fp32 storage as well as bf16 storage.
 //
 // fp32 storage.  The bf16 instruction does 16 times the products of the fp32 one in the same time.
-// An fp32 number is EXACTLY the sum of three bf16 numbers (8 + 8 + 8 bits: x0 = bf16(x),
-// x1 = bf16(x - x0), x2 = x - x0 - x1, each difference exact), so a product of two fp32 numbers is
+// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits: x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1, each
+// difference exact; so is the sum, down to 2^-110, below which x2 would need bits that bf16 does not have).  A product of two fp32 numbers is
 // the sum of nine bf16 products, each exact in fp32.  The six with the largest factors are taken,
 //     x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0),
-// smallest first; the three left out are below 2^-26 of |x y| together, a quarter of the rounding
-// that one fp32 addition brings.  Six instructions of 32 cycles contract 16 channels where the
-// fp32 instruction takes eight of 64: 417 TFLOP/s of fp32 products at the instruction's dense peak
-// against 157.  The accumulator is rounded six times per 16 products instead of eight times, so
-// the sums come out closer, not further off (against 64-bit sums of 64 .. 1600 products of uniform
-// and of log-normal numbers, rms relative: 1.1e-7 .. 6.0e-7 and 1.0e-7 .. 2.9e-7 here, 1.4e-7 ..
-// 6.9e-7 and 1.8e-7 .. 4.8e-7 on the fp32 instruction).  Infinities, NaN and numbers above the
-// largest bf16 have no such parts and leave a result that is not finite; the epilogue looks for
+// smallest first.  The three left out are below 2^-24 of |x y| together in the worst case, as much as the rounding of one
+// fp32 addition; for uniform numbers 0.36 * 2^-26 in the root mean square (measured), a third of that rounding's.
+// Six instructions of 32 cycles contract 16 channels where the fp32 instruction takes eight of 64: 417 TFLOP/s of
+// fp32 products at the instruction's dense peak against 157.
+//
+// Two accumulators per tile: x0 y0 in one, the five smaller products, 2^-8 of it, in the other.  The instruction rounds its sum
+// twice (8 products each time), and before that cuts addends off some ten bits below the last bit of the largest, towards
+// minus infinity: a result is on average 0.004 of a last bit too low (0.07 where the products are the larger ones), whatever its sign.
+// In one accumulator that was 12 roundings per 16 channels, and 1600 products came out 8e-8 too low on average; a gradient
+// adds such an offset up over all positions of an image, where its own terms cancel (gradients of a pool-free net, 96 x 110: 1.3e-5 off, 1.9e-6
+// with the fp32 instruction).  With two, the roundings of the second are 2^-8 as large.  Against 64-bit sums of 64, 256,
+// 1600 products of uniform numbers, rms relative: 4.5e-8, 8.1e-8, 2.2e-7 (1.1e-7, 2.3e-7, 6.1e-7 in one accumulator, 1.4e-7, 2.9e-7, 7.1e-7 on the
+// fp32 instruction), on average 1e-9 off to one side at most; those gradients 1.8e-6.
+//
+// Infinities, NaN and numbers above the largest bf16 have no such parts and leave a result that is not finite; the epilogue looks for
 // those and computes them again with fp32 multiply-adds, so they are what they would be without parts.
-// bf16 storage.  One part, one product: same kernel.
+// bf16 storage.  One part, one product, one accumulator: same kernel.
 //
 // Tiling.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x
 // 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32.  A step contracts 16
-// channels of one tap: MO + MP operands of P parts each feed P(P+1)/2 * MO * MP instructions.  With 2 x 2
-// tiles and three parts that is 12 KB for 24 instructions, which the vector cache (weights, the same
-// for all waves of the workgroup) and the LDS (activations) deliver at 32 bytes per cycle each, well
-// below what they can; the loop alone then sustains 2.17 PFLOP/s (362 TFLOP/s of fp32 products).
+// channels of one tap: MO + MP operands of P parts each feed P(P+1)/2 * MO * MP instructions.  With 1 x 2
+// tiles and three parts that is 9 KB for 12 instructions, from the vector cache (weights, the same
+// for all waves of the workgroup that share channels) and the LDS (activations), 8 and 16 bytes per cycle and wave; 2 x 2 tiles (12 KB for
+// 24 instructions) would need 128 more registers than a wave of two per SIMD has.
 // The input halo is brought in CB channels at a time, [position][16 channels][part] in LDS with a pitch
 // that spreads 16 successive positions of one halo row over all banks (a tile's 32 positions lie in several rows: counters read
 // 10-60 % of the LDS cycles as conflicts), so that an operand is one 128-bit read at
@@ -222,7 +229,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     int wq = 0;                                       // byte offset of the next step to fetch
     const int nblk = (a.CrPad + CB - 1) / CB;
 
-    v16f acc[MO][MP];
+    v16f acc[MO][MP], low[P == 3 ? MO : 1][P == 3 ? MP : 1];   // low: the five smaller products of three parts
     v4f w[NS][MO * P];                                // the ring
     auto fetch_w = [&](int s, int i) {
 #pragma unroll
@@ -259,9 +266,11 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 #pragma unroll
             for (int o = 0; o < MO; ++o)
 #pragma unroll
-                for (int p = 0; p < MP; ++p)
-                    acc[o][p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][o * P + i]),
-                                                                        __builtin_bit_cast(bf16x8, x[t][j][p]), acc[o][p], 0, 0, 0);
+                for (int p = 0; p < MP; ++p) {
+                    v16f& sum = i + j > 0 ? low[o][p] : acc[o][p];
+                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][o * P + i]),
+                                                                  __builtin_bit_cast(bf16x8, x[t][j][p]), sum, 0, 0, 0);
+                }
         };
         auto step = [&](int s) {
             next_x();
@@ -416,7 +425,10 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 #pragma unroll
             for (int p = 0; p < MP; ++p)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[o][p][r] = 0.f;
+                for (int r = 0; r < 16; ++r) {
+                    acc[o][p][r] = 0.f;
+                    if constexpr (P == 3) low[o][p][r] = 0.f;
+                }
         Tile nxt = cur;
         for (int cb = 0; cb < nblk; ++cb) {
             // the next item's halo starts its trip
@@ -435,6 +447,10 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 const int fw = cur.rx < a.Wo ? (int)parts_div(a.Wo - cur.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
                 bool odd = false;
                 if constexpr (P == 3) {
+#pragma unroll
+                    for (int o = 0; o < MO; ++o)
+#pragma unroll
+                        for (int p = 0; p < MP; ++p) acc[o][p] += low[o][p];
                     float z = 0.f;                    // NaN as soon as one of the sums is not finite
 #pragma unroll
                     for (int o = 0; o < MO; ++o)

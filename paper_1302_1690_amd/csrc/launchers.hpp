@@ -14,12 +14,10 @@ namespace mpcnn {
 // instances that are built (wide blocks only where a tile is small enough for them: 64 channels, 192 halo positions
 // with fp32 storage and 384 with bf16; 128 channels, 192):
 struct PartsInstance { int CB, WO, WP, MO, MP; };
-#define MPCNN_PARTS3(X) /* fp32 storage */                                                                             \
-    X(16, 1, 4, 1, 1) X(16, 1, 4, 1, 2) X(16, 2, 2, 1, 1) X(16, 2, 2, 1, 2) X(16, 1, 4, 2, 2) X(16, 4, 1, 1, 2)          \
-    X(16, 2, 2, 2, 2)                                                                                                    \
-    X(32, 1, 4, 1, 1) X(32, 1, 4, 1, 2) X(32, 2, 2, 1, 1) X(32, 2, 2, 1, 2) X(32, 1, 4, 2, 2)                            \
-    X(32, 4, 1, 1, 2) X(32, 4, 1, 1, 4) X(32, 2, 2, 2, 2)                                                                \
-    X(64, 1, 4, 1, 1) X(64, 2, 2, 1, 1) X(64, 2, 2, 1, 2) X(64, 4, 1, 1, 2) X(64, 4, 1, 1, 4) X(64, 2, 2, 2, 2)
+#define MPCNN_PARTS3(X) /* fp32 storage (two accumulators per tile: no room for four tiles) */                         \
+    X(16, 1, 4, 1, 1) X(16, 1, 4, 1, 2) X(16, 2, 2, 1, 1) X(16, 2, 2, 1, 2) X(16, 4, 1, 1, 2)                           \
+    X(32, 1, 4, 1, 1) X(32, 1, 4, 1, 2) X(32, 2, 2, 1, 1) X(32, 2, 2, 1, 2) X(32, 4, 1, 1, 2)                           \
+    X(64, 1, 4, 1, 1) X(64, 2, 2, 1, 1) X(64, 2, 2, 1, 2) X(64, 4, 1, 1, 2)
 #define MPCNN_PARTS1(X) /* bf16 storage */                                                                             \
     X(16, 1, 4, 1, 2) X(16, 1, 4, 1, 4) X(16, 2, 2, 1, 2) X(16, 2, 2, 1, 4) X(16, 1, 4, 2, 2) X(16, 4, 1, 1, 4)          \
     X(32, 1, 4, 1, 2) X(32, 1, 4, 1, 4) X(32, 2, 2, 1, 2) X(32, 2, 2, 1, 4) X(32, 1, 4, 2, 2)                            \

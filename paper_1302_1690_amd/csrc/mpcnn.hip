@@ -286,7 +286,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
         if (in.MO == 2 && ceil_div(co, 32) % 2) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
-        const double eff = P == 3 ? (per_wave >= 4 ? 1.0 : (per_wave == 2 ? 1.08 : 1.3)) : (per_wave >= 4 ? 1.0 : 1.5);
+        const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? 1.0 : 1.5);
         const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
         // (tiles that share a residue class's rows, and its columns, as evenly as their number allows; of those with ty rows
         // the widest that fits)

@@ -51,10 +51,11 @@ def activations(net, layers, image, params):
 
 
 def test_sums_are_as_close_as_fp32_ones():
-    """tanh of a sum of 576 products in 36 steps of six instructions.  A rounding moves the running sum by at most 2^-24
-    of its size, so 216 of them by at most 216 2^-24 of the products' absolute sum; in the root mean square, by
-    sqrt(216 / 3) 2^-24 of the running sum's root mean square, which random signs keep below the root of the sum of
-    squares.  What is left out of the products is 2^-26 of each; the hardware exp2 and reciprocal bring 2e-7 (1.2e-7 rms).
+    """tanh of a sum of 576 products in 36 steps of one instruction for the leading products and five for those 2^-8 as large,
+    two roundings each: 72 (1 + 5 / 256) of them count.  One moves the running sum by at most 2^-24
+    of its size, so all by at most 74 2^-24 of the products' absolute sum; in the root mean square, by
+    sqrt(74 / 3) 2^-24 of the running sum's root mean square, which random signs keep below the root of the sum of
+    squares.  What is left out of a product is at most 2^-24 of it (2^-26 rms); the hardware exp2 and reciprocal bring 2e-7 (1.2e-7 rms).
     576 fp32 additions one after the other would be allowed sqrt(576 / 3)."""
     layers = ((C, 64, 3), (C, 96, 3), (FC, 8, 0), (FC, 2, 0))
     net = mpcnn.Net(layers, 1, 6)
@@ -63,9 +64,9 @@ def test_sums_are_as_close_as_fp32_ones():
     params = (0.05 * rng.standard_normal(net.param_count) * np.exp(rng.standard_normal(net.param_count))).astype(np.float32)
     y, pre, mass, spread = activations(net, layers, image, params)
     err = np.abs(y - np.tanh(pre))
-    assert (err <= (216 * 2.0 ** -24 + 2.0 ** -26) * mass + 2e-7).all()
+    assert (err <= (74 + 1) * 2.0 ** -24 * mass + 2e-7).all()
     rms = lambda v: np.sqrt((v ** 2).mean())
-    assert rms(err) <= np.hypot(np.sqrt(216 / 3) * 2.0 ** -24 * rms(spread) + 2.0 ** -26 * rms(spread), 1.2e-7)
+    assert rms(err) <= np.hypot(np.hypot(np.sqrt(74 / 3) * 2.0 ** -24, 2.0 ** -26) * rms(spread), 1.2e-7)
     net.close()
 
 
@@ -109,3 +110,50 @@ def test_delta_that_is_not_finite_stays_where_it_is():
     assert np.array_equal(out[0][0], out[1][0])
     assert np.isfinite(out[0][1]).all() and np.isnan(out[1][1]).all()
     net.close()
+
+
+def test_sums_are_not_off_to_one_side():
+    """Bias gradients sum deltas over 8000 positions whose signs are random: what rounding leaves of each sums to sqrt(8000) of
+    it, an offset to one side to 8000 of it.  Layers without pools (no ties), labels at random; the 64-bit
+    values from autograd.  Allowed is what fp32 additions may leave, two products each: a delta is the sum of up to 1600 products, in the root mean
+    square off by sqrt(800 / 3) 2^-24 of the running sum's root mean square, at most the sum's own: 1.0e-6.  Each of the two convolutions
+    below adds as much again (so sqrt(3) of it), and the positions' errors, independent of each other, their root of squares.  Twice that is
+    allowed; with one accumulator for all six products, whose results are 8e-8 too low, the error is 1e-5."""
+    layers = ((C, 32, 5), (C, 64, 5), (C, 64, 3), (FC, 100, 0), (FC, 2, 0))
+    patch, H, W = 14, 96, 110
+    net = mpcnn.Net(layers, 1, patch)
+    ratios = []
+    for seed in range(2):
+        rng = np.random.default_rng(seed)
+        image = torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32))
+        labels = torch.from_numpy(rng.integers(0, 2, (1, H, W)).astype(np.int32))
+        params = rng.uniform(-0.05, 0.05, net.param_count).astype(np.float32)
+        net.set_params(params)
+        net.seg_backward(image.cuda(), labels.cuda())
+        grads = net.get_grads().astype(np.float64)
+        x, at, side, ci, fc, pre, places = image.double(), 0, patch, 1, False, [], []
+        for i, (kind, m, k) in enumerate(layers):
+            k = k if kind == C else (1 if fc else side)
+            w = torch.from_numpy(params[at:at + m * ci * k * k].astype(np.float64).reshape(m, ci, k, k))
+            at += w.numel()
+            x = torch.nn.functional.conv2d(x, w, torch.from_numpy(params[at:at + m].astype(np.float64)))
+            if i == 0:
+                x.requires_grad_()
+            else:
+                x.retain_grad()
+            pre.append(x)
+            places.append(slice(at, at + m))
+            at += m
+            if i < len(layers) - 1:
+                x = torch.tanh(x)
+            side, ci, fc = (side - k + 1 if kind == C else 1), m, fc or kind == FC
+        c = (patch - 1) // 2
+        target = labels[:, c:c + x.shape[2], c:c + x.shape[3]].long()
+        torch.nn.functional.cross_entropy(x, target, reduction="sum").backward()
+        for layer in range(3):
+            delta = pre[layer].grad[0]                     # [maps, rows, columns]
+            off = grads[places[layer]] - delta.sum((1, 2)).numpy()
+            ratios.append(np.sqrt((off ** 2).sum() / float((delta ** 2).sum())))
+    print("error of the bias gradients over the root of the deltas' squares:", " ".join("%.2e" % r for r in ratios), flush=True)
+    net.close()
+    assert max(ratios) <= 2 * np.sqrt(3) * np.sqrt(800 / 3) * 2.0 ** -24
