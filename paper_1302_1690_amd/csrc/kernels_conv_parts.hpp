@@ -3,8 +3,8 @@
 //
 // fp32 storage.  The bf16 instruction does 16 times the products of the fp32 one in the same time.
 // An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits: x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1, each
-// difference exact; so is the sum, down to 2^-110, below which x2 would need bits that bf16 does not have).  A product of two fp32 numbers is
-// the sum of nine bf16 products, each exact in fp32.  The six with the largest factors are taken,
+// difference exact, and so is the sum: numbers are split 2^16 times as large, as below 2^-110 x2 would need bits that bf16 does
+// not have).  A product of two fp32 numbers is the sum of nine bf16 products, each exact in fp32.  The six with the largest factors are taken,
 //     x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0),
 // smallest first.  The three left out are below 2^-24 of |x y| together in the worst case, as much as the rounding of one
 // fp32 addition; for uniform numbers 0.36 * 2^-26 in the root mean square (measured), a third of that rounding's.
@@ -20,7 +20,7 @@
 // 1600 products of uniform numbers, rms relative: 4.5e-8, 8.1e-8, 2.2e-7 (1.1e-7, 2.3e-7, 6.1e-7 in one accumulator, 1.4e-7, 2.9e-7, 7.1e-7 on the
 // fp32 instruction), on average 1e-9 off to one side at most; those gradients 1.8e-6.
 //
-// Infinities, NaN and numbers above the largest bf16 have no such parts and leave a result that is not finite; the epilogue looks for
+// Infinities, NaN and numbers above 2^-16 of the largest bf16 have no such parts and leave a result that is not finite, as do sums above 2^96; the epilogue looks for
 // those and computes them again with fp32 multiply-adds, so they are what they would be without parts.
 // bf16 storage.  One part, one product, one accumulator: same kernel.
 //
@@ -76,7 +76,11 @@ __host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (
 __host__ __device__ constexpr int parts_items(int parts) { return parts == 3 ? 6 : 12; }                    // rounds, at most (they wait in registers)
 __host__ __device__ constexpr int parts_ring(int parts) { return parts == 3 ? 2 : 4; }                      // steps of weights in registers
 
-// x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: three conversions, four shifts or masks and four
+// Numbers are split kPartsUp times as large, and sums of products are brought back by kPartsDown: bf16's last bit lies
+// at 2^-133, fp32's at 2^-149.
+constexpr float kPartsUp = 0x1p16f, kPartsDown = 0x1p-32f;
+
+// kPartsUp x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: two multiplications, three conversions, four shifts or masks and four
 // subtractions each)
 __device__ __forceinline__ void split_parts(const float (&x)[8], u32x4 (&p)[3])
 {
@@ -84,7 +88,7 @@ __device__ __forceinline__ void split_parts(const float (&x)[8], u32x4 (&p)[3])
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        float lo = x[2 * j], hi = x[2 * j + 1];
+        float lo = kPartsUp * x[2 * j], hi = kPartsUp * x[2 * j + 1];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
@@ -319,9 +323,10 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 
     // ---- result of one element: the sum v, and the bias (forward) or the output whose slope multiplies it (data gradient)
     const bool curved = a.mode == kFwdTanh || a.mode == kDgradTanh;   // uniform
-    auto finish = [&](float v, float y) {
-        if constexpr (BACK) return curved ? v * squash_slope(y, a.logistic) : v;
-        else return curved ? squash(v + y, a.logistic) : v + y;
+    constexpr float kDown = P == 3 ? kPartsDown : 1.f;
+    auto finish = [&](float v, float down, float y) {   // (down: a power of two)
+        if constexpr (BACK) return curved ? down * v * squash_slope(y, a.logistic) : down * v;
+        else return curved ? squash(fmaf(v, down, y), a.logistic) : fmaf(v, down, y);
     };
     // ---- epilogue of tile g: register 4n + z of tile (o, p) is channel oc0 + 32o + 8n + 4lg + z of position
     // 32*(wp*MP + p) + lt.  The bias waits in LDS; what the data gradient reads (the outputs whose slope
@@ -366,7 +371,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                     v4f yv = __builtin_convertvector(y[p & 1][o][n], v4f), r;
                     if constexpr (!BACK) yv = *reinterpret_cast<const v4f*>(bias_l + (oc - 32 * (int)blockIdx.y * WO * MO));
 #pragma unroll
-                    for (int z = 0; z < 4; ++z) r[z] = finish(acc[o][p][4 * n + z], yv[z]);
+                    for (int z = 0; z < 4; ++z) r[z] = finish(acc[o][p][4 * n + z], kDown, yv[z]);
                     T* const dst = out_t + pos_off[p & 1] + oc;
                     if (vec) store4(dst, r);
                     else for (int z = 0; z < 4; ++z) if (oc + z < a.Co) store1(dst + z, r[z]);
@@ -401,7 +406,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 }
             const long off = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co + oc;
             const float y = BACK ? (curved ? load1(act_t + off) : 0.f) : a.bias[oc];
-            store1(out_t + off, finish(sum, y));
+            store1(out_t + off, finish(sum, 1.f, y));
         }
     };
 

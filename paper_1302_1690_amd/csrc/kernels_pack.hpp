@@ -4,7 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "storage.hpp"
+#include "kernels_conv_parts.hpp"
 
 namespace mpcnn {
 
@@ -48,6 +48,7 @@ __global__ __launch_bounds__(256) void pack_parts_kernel(PackArgs a)
             } else {
                 if (c < Co && oo < Ci) v = W[((long)(kk - 1 - tap) * Ci + oo) * Co + c];
             }
+            if constexpr (P == 3) v *= kPartsUp;
 #pragma unroll
             for (int i = 0; i < P; ++i) {        // v = the sum of its parts, exactly
                 parts[i][s] = (bf16)v;

@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
                 v4f* dst = reinterpret_cast<v4f*>(out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024) + lane;
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4)
-                    dst[r4 * 64] = (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
+                    dst[r4 * 64] = kPartsDown * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
             }
         if (odd) {
             // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more,

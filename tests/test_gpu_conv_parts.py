@@ -157,3 +157,48 @@ def test_sums_are_not_off_to_one_side():
     print("error of the bias gradients over the root of the deltas' squares:", " ".join("%.2e" % r for r in ratios), flush=True)
     net.close()
     assert max(ratios) <= 2 * np.sqrt(3) * np.sqrt(800 / 3) * 2.0 ** -24
+
+
+def gradients(layers, patch, params, pixw=None):
+    net = mpcnn.Net(layers, 1, patch)
+    rng = np.random.default_rng(11)
+    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, 40, 37)).astype(np.float32)).cuda()
+    labels = torch.from_numpy(rng.integers(0, 2, (1, 40, 37)).astype(np.int32)).cuda()
+    net.set_params(params)
+    net.seg_backward(image, labels, pixw=None if pixw is None else torch.full((1, 40, 37), pixw, device="cuda"))
+    grads = net.get_grads().astype(np.float64)
+    net.close()
+    return grads
+
+
+SMALL = ((C, 16, 3), (C, 40, 3), (FC, 24, 0), (FC, 2, 0))   # patch 8, no pools
+
+
+def close_layers(got, want, layers, patch):
+    """Largest relative distance (2-norm) of a layer's gradient."""
+    side, ci, at, worst, fc = patch, 1, 0, 0.0, False
+    for kind, m, k in layers:
+        k = k if kind == C else (1 if fc else side)
+        n = m * ci * k * k + m
+        worst = max(worst, np.linalg.norm(got[at:at + n] - want[at:at + n]) / np.linalg.norm(want[at:at + n]))
+        at, ci, fc, side = at + n, m, fc or kind == FC, side - k + 1
+    return worst
+
+
+def test_small_numbers_keep_their_bits():
+    """Everything behind the forward pass is linear in the pixel weights, and the delta below a layer in its weights: made a
+    power of two smaller, every fp32 operation rounds as before, until numbers are subnormal and off by 2^-150 each.
+    Pixel weights of 2^-114: deltas from 2^-115 to 2^-125, of which 2^-133 (the last bit of bf16) would be 2^-18 to 2^-8.
+    A gradient adds 1000 products of them, whose 2^-150 are below 2^-24 of the deltas' size each: 2^-20 allows for all."""
+    rng = np.random.default_rng(12)
+    params = rng.uniform(-0.2, 0.2, mpcnn.Net(SMALL, 1, 8).param_count).astype(np.float32)
+    small = gradients(SMALL, 8, params, 2.0 ** -114)
+    assert close_layers(small * 2.0 ** 114, gradients(SMALL, 8, params, 1.0), SMALL, 8) <= 2.0 ** -20
+    # the second layer's weights at 2^-40 and 2^-114 of these: the layers above see its biases either way
+    at = 16 * 9 + 16
+    got = []
+    for e in (-40, -114):
+        p = params.copy()
+        p[at:at + 40 * 16 * 9] *= np.float32(2.0 ** e)
+        got.append(gradients(SMALL, 8, p)[:at] * 2.0 ** -e)
+    assert np.linalg.norm(got[1] - got[0]) <= 2.0 ** -20 * np.linalg.norm(got[0])
