@@ -378,35 +378,70 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 }
         }
     };
-    // A sum that is not finite came from infinities, NaN or numbers without parts (or is one that overflows):
-    // once more, with fp32 multiply-adds over the taps and channels in step order.
+    // A sum that is not finite came from infinities, NaN or numbers without parts (or is one that overflows): once more, with
+    // fp32 multiply-adds over the taps and channels in step order, four channels of one position tile at a time (more would take
+    // registers from the loop above).  Bound by the trips of its loads, about the tile's own time for every four channels that need it;
+    // where everything is NaN (a net that diverged) over after one value.
     auto repair = [&](const Tile& g, int fh, int fw, const unsigned (&bad)[MO][MP]) {
-        for (int e = 0; e < MO * MP * 16; ++e) {
-            const int o = e / (MP * 16), p = (e / 16) % MP, r = e & 15;
-            unsigned mask = 0;
+        const int ci = BACK ? a.Co : a.Cr, co = BACK ? a.Cr : a.Co;   // the raw weights are [tap][layer input][layer output]
 #pragma unroll
-            for (int oo = 0; oo < MO; ++oo)
-#pragma unroll
-                for (int pp = 0; pp < MP; ++pp) mask = (oo == o && pp == p) ? bad[oo][pp] : mask;
-            const int oc = oc0 + 32 * o + 8 * (r >> 2) + 4 * lg + (r & 3);
+        for (int p = 0; p < MP; ++p) {
             const unsigned m = 32 * (wp * MP + p) + lt;
             const int ty = (int)parts_div(m, a.mg_tx, a.Tx), tx = (int)m - ty * a.Tx;
             const int fy = g.ty0 + ty, fx = g.tx0 + tx;
-            if (!((mask >> r) & 1u) || oc >= a.Co || ty >= a.Ty || fy >= fh || fx >= fw) continue;
-            const int ci = BACK ? a.Co : a.Cr, co = BACK ? a.Cr : a.Co;   // the raw weights are [tap][layer input][layer output]
-            float sum = 0.f;
-            for (int ta = 0; ta < a.k; ++ta)
-                for (int tb = 0; tb < a.k2; ++tb) {
-                    const int iy = (fy + ta + a.origin) * a.d + g.ry, ix = (fx + tb + a.origin2) * a.d2 + g.rx;
-                    if (iy < 0 || ix < 0 || iy >= a.Hi || ix >= a.Wi) continue;
-                    const T* src = in_t + (((long)g.b * a.Hi + iy) * a.Wi + ix) * a.Cr;
-                    const int tap = ta * a.k2 + tb;
-                    const float* wr = BACK ? a.wraw + ((long)(a.k * a.k2 - 1 - tap) * ci + oc) * co : a.wraw + (long)tap * ci * co + oc;
-                    for (int c = 0; c < a.Cr; ++c) sum = fmaf(load1(src + c), wr[BACK ? c : c * co], sum);
+            const bool exists = ty < a.Ty && fy < fh && fx < fw;
+            const int iy0 = (fy + a.origin) * a.d + g.ry, ix0 = (fx + a.origin2) * a.d2 + g.rx;
+            const long off = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co;
+            const T* const img = in_t + (long)g.b * a.Hi * a.Wi * a.Cr;
+            // a NaN among the values: NaN whatever else, and written already (the first tap inside the map stands for all)
+            bool explained = !exists;
+            if (exists) {
+                const int y = iy0 < 0 ? iy0 + (-iy0 + a.d - 1) / a.d * a.d : iy0, x = ix0 < 0 ? ix0 + (-ix0 + a.d2 - 1) / a.d2 * a.d2 : ix0;
+                if (y < a.Hi && x < a.Wi) {           // (a map smaller than the spacing has positions no tap reaches)
+                    const float v = load1(img + ((long)y * a.Wi + x) * a.Cr);
+                    explained = v != v;
                 }
-            const long off = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co + oc;
-            const float y = BACK ? (curved ? load1(act_t + off) : 0.f) : a.bias[oc];
-            store1(out_t + off, finish(sum, 1.f, y));
+            }
+            for (int on = 0; on < 4 * MO; ++on) {
+                unsigned mask = 0;
+#pragma unroll
+                for (int o = 0; o < MO; ++o) mask = on >> 2 == o ? bad[o][p] >> (4 * (on & 3)) & 15u : mask;
+                const int oc = oc0 + 32 * (on >> 2) + 8 * (on & 3) + 4 * lg, left = a.Co - oc;   // the lane's four channels, those that exist
+                if (explained || left <= 0) mask = 0;
+                if (!__any(mask != 0)) continue;
+                v4f sum = {0.f, 0.f, 0.f, 0.f};
+                bool more = true;                     // a sum that is wanted and not NaN yet
+                for (int tap = 0; tap < a.k * a.k2 && more; ++tap) {
+                    const int ta = tap / a.k2, tb = tap - ta * a.k2;
+                    const int iy = iy0 + ta * a.d, ix = ix0 + tb * a.d2;
+                    const bool here = mask && iy >= 0 && ix >= 0 && iy < a.Hi && ix < a.Wi;
+                    if (here) {
+                        const T* src = img + ((long)iy * a.Wi + ix) * a.Cr;
+                        const float* wr = BACK ? a.wraw + ((long)(a.k * a.k2 - 1 - tap) * ci + oc) * co : a.wraw + (long)tap * ci * co + oc;
+#pragma unroll 1
+                        for (int c = 0; c < a.Cr; c += 4) {
+                            const v4f v = load4(src + c);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                                for (int z = 0; z < 4; ++z)           // (a channel that does not exist: the first one's weight again)
+                                    sum[z] = fmaf(v[e], wr[(z < left ? z : 0) * (BACK ? co : 1)], sum[z]);
+                                wr += BACK ? 1 : co;
+                            }
+                        }
+                    }
+                    bool open = false;
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) open |= ((mask >> z) & 1u) && sum[z] == sum[z];
+                    more = __any(open);
+                }
+#pragma unroll
+                for (int z = 0; z < 4; ++z)
+                    if (((mask >> z) & 1u) && z < left) {
+                        const float y = BACK ? (curved ? load1(act_t + off + oc + z) : 0.f) : a.bias[oc + z];
+                        store1(out_t + off + oc + z, finish(sum[z], 1.f, y));
+                    }
+            }
         }
     };
 

@@ -348,28 +348,62 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
                     dst[r4 * 64] = kPartsDown * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
             }
         if (odd) {
-            // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more,
-            // with fp32 multiply-adds over the slab's positions.
-            for (int e = 0; e < PM * 16; ++e) {
-                const int p = e >> 4, r = e & 15;
-                const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int lu = 2 * (midx * PM + p) + (row >> 4);
-                const int pl = lu / a.tpg, tap = tap0 + lu - pl * a.tpg, c = 16 * (p0 + pl) + (row & 15), oc = 32 * nt + (lane & 31);
-                if (midx * PM + p >= a.RT || lu >= units || tap >= kk || c >= a.Ci || oc >= a.Co) continue;
-                float* const o = out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024 + ((r >> 2) * 64 + lane) * 4 + (r & 3);
-                if (__builtin_isfinite(*o)) continue;
-                const int ta = tap / a.k2, tb = tap - ta * a.k2;
-                float sum = 0.f;
-                for (int tile = tile_begin; tile < tile_end && sum == sum; ++tile) {
+            // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more, with fp32
+            // multiply-adds over the slab's positions, four gradient rows at a time.  Bound by the trips of its loads, about a tenth
+            // of the slab's own time for every four rows that need it; where everything is NaN (a net that diverged) over after one value.
+            const int oc = 32 * nt + (lane & 31);
+            const bool column = oc < a.Co;
+            auto delta = [&](const Tile& t, int y, int x) {
+                return a.dY + (((long)t.b * a.Ho + (t.ty0 + y) * a.d + t.ry) * a.Wo + (t.tx0 + x) * a.d2 + t.rx) * a.Co + oc;
+            };
+            // a NaN among the column's deltas: NaN whatever else, and written already (the slab's first position stands for all)
+            bool explained = !column;
+            for (int tile = tile_begin; tile < tile_end; ++tile) {
+                const Tile t = decode(tile);
+                if (t.rows <= 0 || t.cols <= 0) continue;
+                if (column) { const float v = *delta(t, 0, 0); explained = v != v; }
+                break;
+            }
+            for (int e = 0; e < PM * 4; ++e) {
+                const int p = e >> 2, n = e & 3;
+                if (midx * PM + p >= a.RT) break;
+                const unsigned lu = 2 * (midx * PM + p) + (n >> 1);
+                const unsigned pl = parts_div(lu, a.mg_tpg, a.tpg), tap = tap0 + lu - pl * a.tpg;
+                const unsigned ta = parts_div(tap, a.mg_k2, a.k2), tb = tap - ta * a.k2;
+                const int c = 16 * (p0 + (int)pl) + 8 * (n & 1) + 4 * (lane >> 5);
+                if (lu >= (unsigned)units || tap >= (unsigned)kk) continue;
+                v4f* const dst = reinterpret_cast<v4f*>(out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024) + lane + 64 * n;
+                v4f was = *dst, sum = {0.f, 0.f, 0.f, 0.f};
+                unsigned bad = 0;
+#pragma unroll
+                for (int z = 0; z < 4; ++z) bad |= __builtin_isfinite(was[z]) ? 0u : 1u << z;
+                if (explained || c >= a.Ci) bad = 0;
+                bool more = __any(bad != 0);          // a sum that is wanted and not NaN yet
+                if (!more) continue;
+                for (int tile = tile_begin; tile < tile_end && more; ++tile) {
                     const Tile t = decode(tile);
-                    for (int y = 0; y < a.R && y < t.rows; ++y)
-                        for (int x = 0; x < txp && x < t.cols; ++x) {
-                            const int oy = (t.ty0 + y) * a.d + t.ry, ox = (t.tx0 + x) * a.d2 + t.rx;
-                            sum = fmaf(a.in[(((long)t.b * a.Hi + oy + ta * a.d) * a.Wi + ox + tb * a.d2) * a.Ci + c],
-                                       a.dY[(((long)t.b * a.Ho + oy) * a.Wo + ox) * a.Co + oc], sum);
+                    const int cols = t.cols < txp ? t.cols : txp;
+                    for (int y = 0; y < a.R && y < t.rows && more; ++y) {
+                        if (bad) {
+                            const float* src = a.in + (((long)t.b * a.Hi + (t.ty0 + y + (int)ta) * a.d + t.ry) * a.Wi + (t.tx0 + (int)tb) * a.d2 + t.rx) * a.Ci + c;
+                            const float* dy = delta(t, y, 0);
+#pragma unroll 4
+                            for (int x = 0; x < cols; ++x) {
+                                const v4f v = *reinterpret_cast<const v4f*>(src + (long)x * a.d2 * a.Ci);
+                                const float d = dy[(long)x * a.d2 * a.Co];
+#pragma unroll
+                                for (int z = 0; z < 4; ++z) sum[z] = fmaf(v[z], d, sum[z]);
+                            }
                         }
+                        bool open = false;
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) open |= ((bad >> z) & 1u) && sum[z] == sum[z];
+                        more = __any(open);
+                    }
                 }
-                *o = sum;
+#pragma unroll
+                for (int z = 0; z < 4; ++z) was[z] = (bad >> z) & 1u ? sum[z] : was[z];
+                if (bad) *dst = was;
             }
         }
     }

@@ -202,3 +202,77 @@ def test_small_numbers_keep_their_bits():
         p[at:at + 40 * 16 * 9] *= np.float32(2.0 ** e)
         got.append(gradients(SMALL, 8, p)[:at] * 2.0 ** -e)
     assert np.linalg.norm(got[1] - got[0]) <= 2.0 ** -20 * np.linalg.norm(got[0])
+
+
+WIDE = ((C, 48, 3), (C, 132, 3), (C, 72, 2), (FC, 40, 0), (FC, 2, 0))   # patch 8, no pools; several planes, taps and groups
+
+
+def test_deltas_without_parts():
+    """Pixel weights of 2^114: no delta has parts, so every element of the data gradients (borders included) and of the weight
+    gradients is computed again with fp32 multiply-adds, and stays below the largest fp32 number.  They are 2^114 times those of
+    pixel weights 1, whose sums are taken in another order: two sums of up to 1200 products, each off by
+    sqrt(1200 / 3) 2^-24 of the running sum, four layers deep: 2^-17 allows twice that."""
+    rng = np.random.default_rng(13)
+    params = rng.uniform(-0.1, 0.1, mpcnn.Net(WIDE, 1, 8).param_count).astype(np.float32)
+    big = gradients(WIDE, 8, params, 2.0 ** 114)
+    assert np.isfinite(big).all()
+    assert close_layers(big * 2.0 ** -114, gradients(WIDE, 8, params, 1.0), WIDE, 8) <= 2.0 ** -17
+
+
+def test_weights_without_parts_in_the_data_gradient():
+    """A weight that has no parts: its map is saturated, its delta 0 and 0 times the weight 0, so the deltas below are what they are
+    without it: as far from those of a weight of 2^100 (which has parts, saturates as well) as the rounding of sums in another order (above)."""
+    rng = np.random.default_rng(14)
+    params = rng.uniform(-0.1, 0.1, mpcnn.Net(WIDE, 1, 8).param_count).astype(np.float32)
+    at = 48 * 9 + 48 + 132 * 48 * 9 + 132 + (37 * 132 + 45) * 4 + 1   # third layer: map 37, channel 45, tap 1
+    got = []
+    for value in (2.0 ** 100, 3.395e38):
+        params[at] = value
+        got.append(gradients(WIDE, 8, params))
+    assert np.isfinite(got[0]).all() and np.isfinite(got[1]).all()
+    assert close_layers(got[1], got[0], WIDE, 8) <= 2.0 ** -17
+
+
+def test_a_net_that_diverged_is_not_slow():
+    """Training steps with parameters that are all NaN, and with one infinite weight per layer, against finite ones: the sums that are not
+    finite are computed again, which takes as long as a value, or as the few maps that need it (times before that was so:
+    see the factor that is printed)."""
+    cfg = wl.crop(wl.CONFIGS[3], 1, 330, 340)
+    img, lab = wl.make_inputs(cfg)
+    params = wl.make_params(cfg)
+    image, labels = torch.from_numpy(img).cuda(), torch.from_numpy(lab).cuda()
+    one = params.copy()
+    for layer in (2, 4, 6):
+        at = sum(m * ci * k * k + m for ci, m, k in wl_layers(cfg)[:layer // 2])
+        one[at + 3] = np.inf
+    ms = []
+    for p in (params, np.full_like(params, np.nan), one):
+        net = mpcnn.Net(cfg.layers, cfg.in_channels, cfg.patch)
+        net.set_params(p)
+        net.seg_backward(image, labels)
+        torch.cuda.synchronize()
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            net.seg_backward(image, labels)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ms.append(best)
+        net.close()
+    print("finite, NaN, one infinite weight per layer: %.2f, %.2f, %.2f ms (x %.2f, %.2f)" % (*ms, ms[1] / ms[0], ms[2] / ms[0]), flush=True)
+    assert ms[1] <= 1.5 * ms[0] and ms[2] <= 20 * ms[0]
+
+
+def wl_layers(cfg):
+    """(inputs, maps, filter side) of the layers with parameters."""
+    side, ci, fc, out = cfg.patch, cfg.in_channels, False, []
+    for kind, m, k in cfg.layers:
+        if kind == MP:
+            side //= k
+            continue
+        k = k if kind == C else (1 if fc else side)
+        out.append((ci, m, k))
+        ci, fc, side = m, fc or kind == FC, side - k + 1
+    return out
