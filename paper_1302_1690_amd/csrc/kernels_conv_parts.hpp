@@ -41,7 +41,8 @@
 // order - chunks of 16 channels, the taps of each, whatever CB is - and wraps around from a tile's last step to its first.
 // Two workgroups share a compute unit, so one's staging, barriers and stores lie under the other's
 // instructions.  A block costs two barriers and, as a wave's loads return in order, a wait of its weights behind the halo:
-// where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels.
+// where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels.  Where it is large, its halo would leave
+// a tile of few positions, or none: blocks are then 16 channels of kr filter rows, in step order as well.
 //
 // Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
 //   fp32, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 (fp32 instruction) -> 461, 870, 666, 1110 (226, 231, 209, 165 TFLOP/s);
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     // sit on the same SIMDs in both workgroups of a compute unit
     const int wo = (wave + (int)(blockIdx.x % WO)) % WO, wp = wave / WO;
 
-    const int hw = a.Tx + a.k2 - 1, hh = a.Ty + a.k - 1;
+    const int hw = a.Tx + a.k2 - 1, hh = a.Ty + a.kr - 1;
     const int npos = hh * hw;                         // <= SI * RP
     const int oc0 = 32 * ((blockIdx.y * WO + wo) * MO);   // first channel of this wave's tiles
     const bool live = oc0 < a.Co;                     // uniform for the wave
@@ -155,10 +156,10 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     // (an empty asm keeps what depends on the lane alone from being computed once for all tiles and held in registers
     // beside the accumulators: there are none left)
     auto fresh = [](int v) { asm volatile("" : "+v"(v)); return v; };
-    auto aim = [&](const Tile& g, bool any) {         // this thread's items of tile g
+    auto aim = [&](const Tile& g, bool any, int row0) {   // this thread's items of tile g, filter rows row0 ..
         const int first = fresh(pos0);
         const unsigned row_b = (unsigned)(a.d * a.Wi * a.Cr) * (unsigned)sizeof(T), col_b = (unsigned)(a.d2 * a.Cr) * (unsigned)sizeof(T);
-        const int iy0 = (g.ty0 + a.origin) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
+        const int iy0 = (g.ty0 + a.origin + row0) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
         st_base = in_t + (((long)g.b * a.Hi + iy0) * a.Wi + ix0) * a.Cr;
 #pragma unroll
         for (int u = 0; u < SI; ++u) {
@@ -246,11 +247,11 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     };
 
     // one tile's share of one channel block: its 16-channel chunks one after the other, the taps of each
-    auto multiply = [&](int nsub) {
-        const int taps = a.k * a.k2, n = taps * nsub; // steps of this block
+    auto multiply = [&](int rows, int nsub) {
+        const int taps = rows * a.k2, n = taps * nsub;   // steps of this block
         int left = n;                                 // steps whose activations are still to be fetched
         int ta = 0, tb = 0, soff = 0;                 // the next one's place
-        const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (a.k * hw) * PITCH;
+        const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (rows * hw) * PITCH;
         constexpr int XS = P == 3 ? 1 : 2;            // sets of activations in registers
         v4f x[XS][P][MP];
         auto fetch_x = [&](int s, int i) {
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
             soff += PITCH;
             if (++tb == a.k2) {
                 tb = 0; soff += rowskip;
-                if (++ta == a.k) { ta = 0; soff += subskip; }
+                if (++ta == rows) { ta = 0; soff += subskip; }
             }
             if (--left <= 0) soff = 0;
         };
@@ -449,7 +450,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     int t = blockIdx.x;
     if (t >= a.tiles_total) return;                   // (uniform; the host launches no such workgroup)
     Tile cur = decode(t);
-    aim(cur, true);
+    aim(cur, true, 0);
     issue(0);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {                    // the ring's first steps
@@ -470,18 +471,23 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                     if constexpr (P == 3) low[o][p][r] = 0.f;
                 }
         Tile nxt = cur;
-        for (int cb = 0; cb < nblk; ++cb) {
+        int cb = 0, row0 = 0;                         // channel block, first filter row
+        bool last;
+        do {
             // the next item's halo starts its trip
-            const bool last = cb + 1 == nblk;
+            int cn = cb, rn = row0 + a.kr;
+            if (rn >= a.k) { rn = 0; ++cn; }
+            last = cn == nblk;
             if (last) {
                 const int tn = t + gridDim.x;
                 nxt = decode(tn < a.tiles_total ? tn : t);
-                aim(nxt, tn < a.tiles_total);
-            }
-            issue(last ? 0 : cb + 1);
-            const int left = (a.CrPad - cb * CB) / 16;
-            const int nsub = left < NSUB ? left : NSUB;
-            if (live) multiply(nsub);
+                aim(nxt, tn < a.tiles_total, 0);
+                cn = 0;
+            } else if (a.kr < a.k)
+                aim(cur, true, rn);
+            issue(cn);
+            const int chunks = (a.CrPad - cb * CB) / 16, rows = a.k - row0;
+            if (live) multiply(rows < a.kr ? rows : a.kr, chunks < NSUB ? chunks : NSUB);
             if (last && live) {
                 const int fh = cur.ry < a.Ho ? (int)parts_div(a.Ho - cur.ry + a.d - 1, a.mg_d, a.d) : 0;   // extent of this residue class
                 const int fw = cur.rx < a.Wo ? (int)parts_div(a.Wo - cur.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
@@ -519,7 +525,8 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
             __syncthreads();   // every wave has left this block's halo
             to_lds();
             __syncthreads();
-        }
+            cb = cn; row0 = rn;
+        } while (!last);
         cur = nxt;
     }
 }

@@ -26,6 +26,7 @@ struct ConvArgs {
     int B, Hi, Wi, Cr, CrPad;   // CrPad: Cr rounded up to a multiple of 16
     int Ho, Wo, Co, CoPad;
     int k, d;            // filter rows and the spacing of rows
+    int kr;              // filter rows of a block: k, or fewer (blocks of 16 channels only)
     int k2, d2;          // filter columns and the spacing of columns (they differ from k, d behind a rectangular pool)
     int origin, origin2; // halo origin (rows, columns) in fragment units relative to the tile: 0 forward, -(k-1), -(k2-1) dgrad
     int Ty, Tx, nty, ntx;

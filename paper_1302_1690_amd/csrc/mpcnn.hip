@@ -109,7 +109,7 @@ struct Layer {
 };
 
 struct TilePlan {          // conv_parts_kernel: 32 PT positions per workgroup, `wgs` workgroups per channel group walk the tiles
-    int PT = 0, Ty = 0, Tx = 0, nty = 0, ntx = 0, wgs = 0;
+    int PT = 0, Ty = 0, Tx = 0, nty = 0, ntx = 0, wgs = 0, kr = 0;
     mpcnn::PartsInstance in{};
     size_t lds = 0;
     bool ok = false;
@@ -288,35 +288,41 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
         const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? 1.0 : 1.5);
         const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
-        // (tiles that share a residue class's rows, and its columns, as evenly as their number allows; of those with ty rows
-        // the widest that fits)
         const int lds_pos = (int)(((size_t)80 * 1024 - 32 * ct.OT * sizeof(float)) / (RP * pitch)) * RP;
         const int max_pos = std::min(lds_pos, mpcnn::parts_items(P) * RP);       // positions of the halo
-        int last_ty = 0;
-        for (int ny = fh; ny >= ceil_div(fh, std::min(fh, 32 * PT)); --ny) {
-            const int ty = ceil_div(fh, ny);
-            if (ty == last_ty) continue;
-            last_ty = ty;
-            const int room = std::min(std::min(fw, 32 * PT / ty), max_pos / (ty + k - 1) - (k2 - 1));
-            if (room < 1) continue;
-            const int ntx = ceil_div(fw, room), tx = ceil_div(fw, ntx), nty = ceil_div(fh, ty);
-            const int npos = (ty + k - 1) * (tx + k2 - 1);
-            const size_t lds = ceil_div(npos, RP) * RP * pitch + 32 * ct.OT * sizeof(float);   // the halo in whole rounds, the bias
-            // (byte offsets inside a tile's halo are 31 bits)
-            if (((size_t)(ty + k - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) continue;
-            const long tiles = (long)B * d * d2 * nty * ntx;
-            if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
-            const long wgs = std::min<long>(tiles, std::max(1, 2 * kNumCU / ct.split));
-            const double per_cu = std::ceil((double)tiles * ct.split / kNumCU);
-            const double t_rest = (double)npos * cr * es / 10 + 2500.0 * nblk + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
-            // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
-            // the pitch keeps only successive positions on different LDS banks)
-            const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
-            if (!best.ok || cost < best_cost) {
-                best.PT = PT; best.Ty = ty; best.Tx = tx;
-                best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
-                best.wgs = (int)wgs; best.in = in;
-                best_cost = cost;
+        // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640 positions (fp32)
+        // holds a 25 x 25 filter and one position; in rows it holds any.  (MEASURED)
+        for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128}) {
+            if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
+            const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
+            // (tiles that share a residue class's rows, and its columns, as evenly as their number allows; of those with ty rows
+            // the widest that fits)
+            int last_ty = 0;
+            for (int ny = fh; ny >= ceil_div(fh, std::min(fh, 32 * PT)); --ny) {
+                const int ty = ceil_div(fh, ny);
+                if (ty == last_ty) continue;
+                last_ty = ty;
+                const int room = std::min(std::min(fw, 32 * PT / ty), max_pos / (ty + kr - 1) - (k2 - 1));
+                if (room < 1) continue;
+                const int ntx = ceil_div(fw, room), tx = ceil_div(fw, ntx), nty = ceil_div(fh, ty);
+                const int npos = (ty + kr - 1) * (tx + k2 - 1);
+                const size_t lds = ceil_div(npos, RP) * RP * pitch + 32 * ct.OT * sizeof(float);   // the halo in whole rounds, the bias
+                // (byte offsets inside a tile's halo are 31 bits)
+                if (((size_t)(ty + kr - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) continue;
+                const long tiles = (long)B * d * d2 * nty * ntx;
+                if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
+                const long wgs = std::min<long>(tiles, std::max(1, 2 * kNumCU / ct.split));
+                const double per_cu = std::ceil((double)tiles * ct.split / kNumCU);
+                const double t_rest = (double)nkr * npos * cr * es / 10 + 2500.0 * nblk * nkr + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
+                // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
+                // the pitch keeps only successive positions on different LDS banks)
+                const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
+                if (!best.ok || cost < best_cost) {
+                    best.PT = PT; best.Ty = ty; best.Tx = tx; best.kr = kr;
+                    best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
+                    best.wgs = (int)wgs; best.in = in;
+                    best_cost = cost;
+                }
             }
         }
     }
@@ -794,7 +800,7 @@ inline int grid_for(long total, int block = 256, int cap = 1 << 20)
 // conv_parts_kernel: the plan's workgroups walk the tiles; its divisors' magic numbers
 void parts_grid(mpcnn::ConvArgs* a, dim3* grid, const TilePlan& tp)
 {
-    a->tiles_total = (int)grid->x;
+    a->tiles_total = (int)grid->x; a->kr = tp.kr;
     a->mg_hw = magic_of((unsigned)(a->Tx + a->k2 - 1)); a->mg_tx = magic_of((unsigned)a->Tx);
     a->mg_ntx = magic_of((unsigned)a->ntx); a->mg_nty = magic_of((unsigned)a->nty);
     a->mg_d = magic_of((unsigned)a->d); a->mg_d2 = magic_of((unsigned)a->d2);
@@ -1612,9 +1618,9 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
     auto conv = [&](const char* what, const TilePlan& tp, const ChanTiling& ct) {
         if (!tp.ok) { put("  %s: plain kernel\n", what); return; }
         put("  %s: bf16 MFMA, %s, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
-            "%d channels per block, tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what,
+            "%d channels and %d filter rows per block, tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what,
             net->bf16 ? "one part per number" : "three parts per number", ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
-            tp.in.CB, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
+            tp.in.CB, tp.kr, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
     };
     put("workspace %zu bytes\n", g.total);
     for (size_t l = 0; l < net->layers.size(); ++l) {

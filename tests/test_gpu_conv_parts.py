@@ -25,8 +25,18 @@ EDGES = [
 ]
 
 
+# filters whose halo is taken in blocks of fewer rows: the whole patch left of a layer (spacing 1 and 2), several channel blocks, a last
+# block of one row, 8 channels in a block of 16
+LARGE = [
+    ("rows_of_26", ((C, 16, 3), (C, 12, 26), (MP, 0, 2), (FC, 8, 0), (FC, 2, 0)), 30, 47, 52),
+    ("rows_of_33", ((C, 20, 2), (C, 36, 33), (FC, 8, 0), (FC, 2, 0)), 35, 50, 46),
+    ("fc_over_30", ((C, 8, 5), (MP, 0, 2), (FC, 32, 0), (FC, 2, 0)), 64, 77, 82),
+    ("rows_of_45", ((C, 8, 3), (C, 8, 45), (FC, 8, 0), (FC, 2, 0)), 49, 58, 61),
+]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("name,layers,patch,height,width", EDGES, ids=[e[0] for e in EDGES])
+@pytest.mark.parametrize("name,layers,patch,height,width", EDGES + LARGE, ids=[e[0] for e in EDGES + LARGE])
 def test_tile_and_channel_edges(name, layers, patch, height, width, dtype):
     full_parity(wl.Workload("parts_" + name, layers, patch, 1, layers[-1][1], 2, height, width, 0.2, "ellipses", dtype=dtype,
                             seed_image=1141, seed_label=2141, seed_param=3141), with_pixw=True)

@@ -1,0 +1,27 @@
+"""Which kernels the planner gives to convolutions (no GPU): large filters stay on the matrix cores."""
+import pytest
+
+from paper_1302_1690_amd import mpcnn, workloads as wl
+
+C, MP, FC = wl.C, wl.MP, wl.FC
+
+
+def conv_lines(layers, patch, size, dtype, layer):
+    net = mpcnn.Net(layers, 1, patch, dtype)
+    plan = net.plan_describe(1, size, size, True)
+    net.close()
+    own = plan[plan.index("layer %d:" % layer):plan.index("layer %d:" % (layer + 1))]
+    return [line for line in own.splitlines() if "forward:" in line or "data gradient:" in line]
+
+
+@pytest.mark.parametrize("dtype", [mpcnn.F32, mpcnn.BF16])
+@pytest.mark.parametrize("channels", [8, 12, 16, 32, 64])
+def test_large_filters_are_on_the_matrix_cores(channels, dtype):
+    """Up to 48 x 48; those whose halo holds fewer positions than a workgroup's tile in blocks of fewer rows."""
+    for k in (2, 7, 8, 20, 25, 26, 33, 43, 48):
+        lines = conv_lines(((C, channels, 3), (C, 32, k), (MP, 0, 2), (FC, 16, 0), (FC, 2, 0)), k + 6, 2 * k + 90, dtype, 1)
+        assert len(lines) == 2
+        for line in lines:
+            assert "plain" not in line, (k, line)
+            rows = int(line.split(" filter rows")[0].split()[-1])
+            assert rows == k if k < 8 else 1 <= rows <= k, (k, line)
