@@ -75,7 +75,8 @@ constexpr int kPartsThreads = 256;   // four waves
 __host__ __device__ constexpr int parts_pitch(int parts, int CB) { return (CB / 16) * parts * 32 + 16; }   // LDS bytes of a halo position
 __host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
 __host__ __device__ constexpr int parts_items(int parts) { return parts == 3 ? 6 : 12; }                    // rounds, at most (they wait in registers)
-__host__ __device__ constexpr int parts_ring(int parts) { return parts == 3 ? 2 : 4; }                      // steps of weights in registers
+// steps of weights in registers: 512 cycles of a wave's instructions and more, a trip from L2
+__host__ __device__ constexpr int parts_ring(int parts, int tiles) { return parts == 3 ? (tiles > 1 ? 2 : 4) : (tiles > 2 ? 4 : 8); }
 
 // Numbers are split kPartsUp times as large, and sums of products are brought back by kPartsDown: bf16's last bit lies
 // at 2^-133, fp32's at 2^-149.
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 {
     static_assert(WO * WP == 4, "four waves");
     constexpr int P = sizeof(T) == 4 ? 3 : 1;
-    constexpr int QN = CB / 8, NSUB = CB / 16, NS = parts_ring(P);
+    constexpr int QN = CB / 8, NSUB = CB / 16, NS = parts_ring(P, MO * MP);
     constexpr int PITCH = parts_pitch(P, CB), RP = parts_round(CB), SI = parts_items(P);
     constexpr int ITW = P == 3 ? 2 : 1;               // 128-bit loads per staged item (8 channels of a position)
     constexpr unsigned kNone = 0x80000000u;           // byte offset no buffer reaches: the load returns zeros
@@ -252,7 +253,8 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         int left = n;                                 // steps whose activations are still to be fetched
         int ta = 0, tb = 0, soff = 0;                 // the next one's place
         const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (rows * hw) * PITCH;
-        constexpr int XS = P == 3 ? 1 : 2;            // sets of activations in registers
+        static_assert(NS % (P == 3 ? 1 : MO * MP > 2 ? 2 : 4) == 0, "a turn of the ring uses each set as often");
+        constexpr int XS = P == 3 ? 1 : MO * MP > 2 ? 2 : 4;   // sets of activations in registers: XS - 1 steps ahead, a trip from LDS
         v4f x[XS][P][MP];
         auto fetch_x = [&](int s, int i) {
 #pragma unroll
@@ -260,10 +262,19 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         };
         // (past the last step: the first one's place, read for nothing)
         auto next_x = [&]() {
-            soff += PITCH;
-            if (++tb == a.k2) {
-                tb = 0; soff += rowskip;
-                if (++ta == rows) { ta = 0; soff += subskip; }
+            ++tb;
+            if constexpr (P == 3) {
+                soff += PITCH;
+                if (tb == a.k2) {
+                    tb = 0; soff += rowskip;
+                    if (++ta == rows) { ta = 0; soff += subskip; }
+                }
+            } else {                                  // (no branches: a step is a few instructions)
+                const bool row = tb == a.k2;
+                tb = row ? 0 : tb; ta += row ? 1 : 0;
+                soff += row ? PITCH + rowskip : PITCH;
+                const bool sub = ta == rows;
+                ta = sub ? 0 : ta; soff += sub ? subskip : 0;
             }
             if (--left <= 0) soff = 0;
         };
@@ -278,8 +289,8 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 }
         };
         auto step = [&](int s) {
-            next_x();
             if constexpr (P == 3) {
+                next_x();
                 // A step's operands are fetched for the next one as soon as they are free: the activations' third part
                 // behind the first product, its second behind the third, its first behind the last (three products
                 // before it is needed).
@@ -289,13 +300,19 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 product(s, 0, 1, 0); fetch_w(s, 1);
                 product(s, 0, 0, 0); fetch_x(0, 0); fetch_w(s, 0);
             } else {
-                fetch_x((s & 1) ^ 1, 0);
-                product(s, s & 1, 0, 0); fetch_w(s, 0);
+                fetch_x((s + XS - 1) % XS, 0);
+                next_x();
+                product(s, s % XS, 0, 0); fetch_w(s, 0);
             }
             next_w();
         };
+        if constexpr (P == 3) {
 #pragma unroll
-        for (int i = P - 1; i >= 0; --i) fetch_x(0, i);
+            for (int i = P - 1; i >= 0; --i) fetch_x(0, i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < XS - 1; ++i) { fetch_x(i, 0); next_x(); }
+        }
         // Whole turns of the ring.  The first stands before the loop: behind it the next halo's loads are older than
         // every weight in flight, so the loop's waits count weights only.
         int s = 0;
@@ -307,18 +324,20 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 for (int i = 0; i < NS; ++i) step(i);
         }
         // the rest of a turn; the ring's slots then change places, so that the next block starts at slot 0 again
+        const int rest = n - s;
 #pragma unroll
         for (int i = 0; i < NS - 1; ++i)
-            if (s + i < n) step(i);
+            if (i < rest) step(i);
 #pragma unroll
-        for (int i = 0; i < NS - 1; ++i)
-            if (s + i < n)
+        for (int by = 1; by < NS; by *= 2)
+            if (rest & by)
 #pragma unroll
                 for (int j = 0; j < MO * P; ++j) {
-                    const v4f t = w[0][j];
+                    v4f t[NS];
 #pragma unroll
-                    for (int r = 0; r + 1 < NS; ++r) w[r][j] = w[r + 1][j];
-                    w[NS - 1][j] = t;
+                    for (int r = 0; r < NS; ++r) t[r] = w[(r + by) % NS][j];
+#pragma unroll
+                    for (int r = 0; r < NS; ++r) w[r][j] = t[r];
                 }
     };
 

@@ -291,7 +291,9 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         const int lds_pos = (int)(((size_t)80 * 1024 - 32 * ct.OT * sizeof(float)) / (RP * pitch)) * RP;
         const int max_pos = std::min(lds_pos, mpcnn::parts_items(P) * RP);       // positions of the halo
         // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640 positions (fp32)
-        // holds a 25 x 25 filter and one position; in rows it holds any.  (MEASURED)
+        // holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions, forward / data gradient,
+        // microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32 x 32 16304 / 56978 (plain kernel) ->
+        // 696 / 805; bf16 32 x 32 274 / 412 -> 272 / 271, 40 x 40 24336 / 88069 (plain kernel) -> 419 / 418.  12 x 12 and less: whole is as fast.)
         for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128}) {
             if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
             const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
