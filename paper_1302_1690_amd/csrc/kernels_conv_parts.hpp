@@ -82,6 +82,16 @@ __host__ __device__ constexpr int parts_ring(int parts, int tiles) { return part
 // at 2^-133, fp32's at 2^-149.
 constexpr float kPartsUp = 0x1p16f, kPartsDown = 0x1p-32f;
 
+// One part: LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
+__host__ __device__ constexpr int parts_sets(int parts, int tiles) { return parts == 3 ? 1 : tiles > 2 ? 2 : 4; }   // activations in registers
+constexpr int kPartsTabAhead = 2;
+__host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps)
+{
+    return parts == 3 ? 0 : taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
+}
+// steps of weights that follow the last in a pack, the first ones again: the ring runs ahead without a look at the end
+__host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4 : 8; }
+
 // kPartsUp x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: two multiplications, three conversions, four shifts or masks and four
 // subtractions each)
 __device__ __forceinline__ void split_parts(const float (&x)[8], u32x4 (&p)[3])
@@ -218,6 +228,16 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
             bias_l[tid] = c < a.Co ? a.bias[c] : 0.f;
         }
 
+    // ---- one part: the LDS offsets of a block's steps, behind the bias
+    int* const table = reinterpret_cast<int*>(bias_l + 32 * WO * MO);
+    if constexpr (P == 1) {
+        const int taps = a.kr * a.k2, all = taps * ((CB < a.CrPad ? CB : a.CrPad) / 16);
+        for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kPartsThreads) {
+            const int sub = i / taps, r = i - sub * taps, ta = r / a.k2, tb = r - ta * a.k2;
+            table[i] = i < all ? (ta * hw + tb) * PITCH + sub * 32 : 0;
+        }
+    }
+
     // ---- per lane: LDS address of the positions it feeds as the B operand, at tap 0
     int lbase[MP];
 #pragma unroll
@@ -230,11 +250,12 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 
     // ---- weights: [16-channel chunk][tap][part][lane group][CoPad][8], the step's offset a scalar
     const int wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = a.k * a.k2 * (a.CrPad / 16) * wstep;   // bytes
-    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<v4f*>(a.wpack), 0, wend, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<v4f*>(a.wpack), 0, wend + parts_ahead(P) * wstep, 0x00020000);
     const int wlane = (lg * a.CoPad + oc0 + lt) * 16;
     int wq = 0;                                       // byte offset of the next step to fetch
     const int nblk = (a.CrPad + CB - 1) / CB;
 
+    int head[P == 1 ? parts_sets(P, MO * MP) - 1 + kPartsTabAhead : 1];   // the table's first entries
     v16f acc[MO][MP], low[P == 3 ? MO : 1][P == 3 ? MP : 1];   // low: the five smaller products of three parts
     v4f w[NS][MO * P];                                // the ring
     auto fetch_w = [&](int s, int i) {
@@ -242,42 +263,33 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         for (int o = 0; o < MO; ++o)
             w[s][o * P + i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane + 512 * o, wq + i * wpart, 0));
     };
-    auto next_w = [&]() {
-        wq += wstep;
-        if (wq >= wend) wq = 0;
-    };
+    auto next_w = [&]() { wq += wstep; };
 
     // one tile's share of one channel block: its 16-channel chunks one after the other, the taps of each
     auto multiply = [&](int rows, int nsub) {
         const int taps = rows * a.k2, n = taps * nsub;   // steps of this block
-        int left = n;                                 // steps whose activations are still to be fetched
-        int ta = 0, tb = 0, soff = 0;                 // the next one's place
-        const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (rows * hw) * PITCH;
-        static_assert(NS % (P == 3 ? 1 : MO * MP > 2 ? 2 : 4) == 0, "a turn of the ring uses each set as often");
-        constexpr int XS = P == 3 ? 1 : MO * MP > 2 ? 2 : 4;   // sets of activations in registers: XS - 1 steps ahead, a trip from LDS
+        constexpr int XS = parts_sets(P, MO * MP), TS = kPartsTabAhead;
+        static_assert(NS % XS == 0 && NS % TS == 0, "a turn of the ring uses each set as often");
         v4f x[XS][P][MP];
-        auto fetch_x = [&](int s, int i) {
+        auto fetch_x = [&](int s, int i, int off) {
 #pragma unroll
-            for (int p = 0; p < MP; ++p) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + soff + 32 * i);
+            for (int p = 0; p < MP; ++p) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + off + 32 * i);
         };
-        // (past the last step: the first one's place, read for nothing)
+        // three parts: the next step's place, counted (past the last one: the first one's, read for nothing)
+        int left = n, ta = 0, tb = 0, soff = 0;
+        const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (rows * hw) * PITCH;
         auto next_x = [&]() {
-            ++tb;
-            if constexpr (P == 3) {
-                soff += PITCH;
-                if (tb == a.k2) {
-                    tb = 0; soff += rowskip;
-                    if (++ta == rows) { ta = 0; soff += subskip; }
-                }
-            } else {                                  // (no branches: a step is a few instructions)
-                const bool row = tb == a.k2;
-                tb = row ? 0 : tb; ta += row ? 1 : 0;
-                soff += row ? PITCH + rowskip : PITCH;
-                const bool sub = ta == rows;
-                ta = sub ? 0 : ta; soff += sub ? subskip : 0;
+            soff += PITCH;
+            if (++tb == a.k2) {
+                tb = 0; soff += rowskip;
+                if (++ta == rows) { ta = 0; soff += subskip; }
             }
             if (--left <= 0) soff = 0;
         };
+        // one part: from the table.  A step is two or four instructions of 32 cycles, and a wave alone on its SIMD issues something every four to
+        // five cycles: counting cost 21 scalar instructions per step, twice what the matrix pipe leaves time for.
+        const int* tv = table;
+        int at[TS];
         auto product = [&](int s, int t, int i, int j) {   // weight part i, activation part j
 #pragma unroll
             for (int o = 0; o < MO; ++o)
@@ -294,24 +306,26 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 // A step's operands are fetched for the next one as soon as they are free: the activations' third part
                 // behind the first product, its second behind the third, its first behind the last (three products
                 // before it is needed).
-                product(s, 0, 0, 2); fetch_x(0, 2);
-                product(s, 0, 1, 1); product(s, 0, 0, 1); fetch_x(0, 1);
+                product(s, 0, 0, 2); fetch_x(0, 2, soff);
+                product(s, 0, 1, 1); product(s, 0, 0, 1); fetch_x(0, 1, soff);
                 product(s, 0, 2, 0); fetch_w(s, 2);
                 product(s, 0, 1, 0); fetch_w(s, 1);
-                product(s, 0, 0, 0); fetch_x(0, 0); fetch_w(s, 0);
-            } else {
-                fetch_x((s + XS - 1) % XS, 0);
-                next_x();
+                product(s, 0, 0, 0); fetch_x(0, 0, soff); fetch_w(s, 0);
+            } else {                                  // activations XS - 1 steps ahead, their places TS more
+                fetch_x((s + XS - 1) % XS, 0, at[s % TS]);
+                at[s % TS] = tv[s + XS - 1 + TS];
                 product(s, s % XS, 0, 0); fetch_w(s, 0);
             }
             next_w();
         };
         if constexpr (P == 3) {
 #pragma unroll
-            for (int i = P - 1; i >= 0; --i) fetch_x(0, i);
+            for (int i = P - 1; i >= 0; --i) fetch_x(0, i, 0);
         } else {
 #pragma unroll
-            for (int i = 0; i < XS - 1; ++i) { fetch_x(i, 0); next_x(); }
+            for (int i = 0; i < XS - 1; ++i) fetch_x(i, 0, head[i]);
+#pragma unroll
+            for (int i = 0; i < TS; ++i) at[i] = head[XS - 1 + i];
         }
         // Whole turns of the ring.  The first stands before the loop: behind it the next halo's loads are older than
         // every weight in flight, so the loop's waits count weights only.
@@ -319,9 +333,12 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         if (n >= NS) {
 #pragma unroll
             for (int i = 0; i < NS; ++i) step(i);
-            for (s = NS; s + NS <= n; s += NS)
+            for (s = NS; s + NS <= n; s += NS) {
+                tv += NS;
 #pragma unroll
                 for (int i = 0; i < NS; ++i) step(i);
+            }
+            tv += NS;
         }
         // the rest of a turn; the ring's slots then change places, so that the next block starts at slot 0 again
         const int rest = n - s;
@@ -479,6 +496,9 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     }
     to_lds();
     __syncthreads();
+    if constexpr (P == 1)
+#pragma unroll
+        for (int i = 0; i < parts_sets(P, MO * MP) - 1 + kPartsTabAhead; ++i) head[i] = table[i];
     for (; t < a.tiles_total; t += gridDim.x) {
 #pragma unroll
         for (int o = 0; o < MO; ++o)
@@ -546,6 +566,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
             __syncthreads();
             cb = cn; row0 = rn;
         } while (!last);
+        wq -= live ? wend : 0;                        // (the ring holds the first steps again)
         cur = nxt;
     }
 }

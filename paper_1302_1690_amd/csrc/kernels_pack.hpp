@@ -33,7 +33,8 @@ __global__ __launch_bounds__(256) void pack_parts_kernel(PackArgs a)
     const float* __restrict__ W = a.W + sg.w_off;
     bf16* __restrict__ Q = reinterpret_cast<bf16*>(a.Q + sg.q_off);
     const int kk = sg.kk, Ci = sg.Ci, Co = sg.Co, OPad = sg.OPad, dgrad = sg.dgrad;
-    const long total = (long)kk * (sg.RPad / 16) * 2 * OPad, e = (long)((int)blockIdx.x - sg.block0) * 256 + threadIdx.x;
+    const int steps = kk * (sg.RPad / 16);
+    const long total = (long)steps * 2 * OPad, e = (long)((int)blockIdx.x - sg.block0) * 256 + threadIdx.x;
     if (e < total) {
         const int oo = (int)(e % OPad);
         const int g = (int)((e / OPad) & 1), step = (int)(e / (2 * OPad));
@@ -62,6 +63,8 @@ __global__ __launch_bounds__(256) void pack_parts_kernel(PackArgs a)
 #pragma unroll
             for (int s = 0; s < 8; ++s) o[s] = parts[i][s];
             *reinterpret_cast<bf16x8_t*>(Q + ((((long)step * P + i) * 2 + g) * OPad + oo) * 8) = o;
+            for (int again = step + steps; again < steps + parts_ahead(P); again += steps)   // the ring's lead past the last step
+                *reinterpret_cast<bf16x8_t*>(Q + ((((long)again * P + i) * 2 + g) * OPad + oo) * 8) = o;
         }
     }
 }

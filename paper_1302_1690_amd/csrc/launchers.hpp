@@ -22,7 +22,7 @@ struct PartsInstance { int CB, WO, WP, MO, MP; };
     X(16, 1, 4, 1, 2) X(16, 1, 4, 1, 4) X(16, 2, 2, 1, 2) X(16, 2, 2, 1, 4) X(16, 1, 4, 2, 2) X(16, 4, 1, 1, 4)          \
     X(32, 1, 4, 1, 2) X(32, 1, 4, 1, 4) X(32, 2, 2, 1, 2) X(32, 2, 2, 1, 4) X(32, 1, 4, 2, 2)                            \
     X(32, 4, 1, 1, 2) X(32, 4, 1, 1, 4) X(32, 2, 2, 2, 2)                                                                \
-    X(64, 2, 2, 1, 2) X(64, 2, 2, 1, 4) X(64, 1, 4, 2, 2) X(64, 4, 1, 1, 2) X(64, 4, 1, 1, 4) X(64, 2, 2, 2, 2)          \
+    X(64, 1, 4, 1, 2) X(64, 2, 2, 1, 2) X(64, 2, 2, 1, 4) X(64, 1, 4, 2, 2) X(64, 4, 1, 1, 2) X(64, 4, 1, 1, 4) X(64, 2, 2, 2, 2)          \
     X(128, 2, 2, 1, 2) X(128, 4, 1, 1, 2) X(128, 4, 1, 1, 4) X(128, 2, 2, 2, 2)
 #define MPCNN_PARTS_ROW(cb, wo, wp, mo, mp) {cb, wo, wp, mo, mp},
 constexpr PartsInstance kParts3[] = {MPCNN_PARTS3(MPCNN_PARTS_ROW)};

@@ -286,10 +286,9 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
         if (in.MO == 2 && ceil_div(co, 32) % 2) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
-        const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? 1.0 : 1.5);
+        const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
+        const double alone = P == 3 ? 1.15 : 1.4;
         const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
-        const int lds_pos = (int)(((size_t)80 * 1024 - 32 * ct.OT * sizeof(float)) / (RP * pitch)) * RP;
-        const int max_pos = std::min(lds_pos, mpcnn::parts_items(P) * RP);       // positions of the halo
         // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640 positions (fp32)
         // holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions, forward / data gradient,
         // microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32 x 32 16304 / 56978 (plain kernel) ->
@@ -297,6 +296,10 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128}) {
             if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
             const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
+            const size_t beside = (32 * ct.OT + mpcnn::parts_table(P, CB, rpad, kr * k2)) * sizeof(float);   // the bias, the steps' places
+            if (beside + RP * pitch > (size_t)80 * 1024) continue;
+            const int lds_pos = (int)(((size_t)80 * 1024 - beside) / (RP * pitch)) * RP;
+            const int max_pos = std::min(lds_pos, mpcnn::parts_items(P) * RP);       // positions of the halo
             // (tiles that share a residue class's rows, and its columns, as evenly as their number allows; of those with ty rows
             // the widest that fits)
             int last_ty = 0;
@@ -308,7 +311,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                 if (room < 1) continue;
                 const int ntx = ceil_div(fw, room), tx = ceil_div(fw, ntx), nty = ceil_div(fh, ty);
                 const int npos = (ty + kr - 1) * (tx + k2 - 1);
-                const size_t lds = ceil_div(npos, RP) * RP * pitch + 32 * ct.OT * sizeof(float);   // the halo in whole rounds, the bias
+                const size_t lds = ceil_div(npos, RP) * RP * pitch + beside;   // the halo in whole rounds
                 // (byte offsets inside a tile's halo are 31 bits)
                 if (((size_t)(ty + kr - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) continue;
                 const long tiles = (long)B * d * d2 * nty * ntx;
@@ -318,7 +321,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                 const double t_rest = (double)nkr * npos * cr * es / 10 + 2500.0 * nblk * nkr + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
                 // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
                 // the pitch keeps only successive positions on different LDS banks)
-                const double cost = per_cu * ((per_cu < 2 ? 1.15 : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
+                const double cost = per_cu * ((per_cu < 2 ? alone : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
                 if (!best.ok || cost < best_cost) {
                     best.PT = PT; best.Ty = ty; best.Tx = tx; best.kr = kr;
                     best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
@@ -1536,7 +1539,8 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
             const size_t pack_bound = (size_t)ly.k * ly.k2 * (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) *
                                       (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) * 6;
             if (pack_bound >= (1ull << 31)) ly.fwd_mfma = ly.dgrad_mfma = false;
-            auto pack_floats = [&](int rpad, int pad) { return (size_t)ly.k * ly.k2 * (rpad / 16) * (net->bf16 ? 1 : 3) * 2 * pad * 4; };
+            const int parts = net->bf16 ? 1 : 3;
+            auto pack_floats = [&](int rpad, int pad) { return ((size_t)ly.k * ly.k2 * (rpad / 16) + mpcnn::parts_ahead(parts)) * parts * 2 * pad * 4; };
             if (ly.fwd_mfma) {
                 ly.fwd_ct = chan_tiling(ly.cout);
                 ly.fwd_rpad = ceil_div(ly.cin, 16) * 16;
