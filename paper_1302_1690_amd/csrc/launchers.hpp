@@ -18,11 +18,11 @@ struct PartsInstance { int CB, WO, WP, MO, MP; };
     X(16, 1, 4, 1, 1) X(16, 1, 4, 1, 2) X(16, 2, 2, 1, 1) X(16, 2, 2, 1, 2) X(16, 4, 1, 1, 2)                           \
     X(32, 1, 4, 1, 1) X(32, 1, 4, 1, 2) X(32, 2, 2, 1, 1) X(32, 2, 2, 1, 2) X(32, 4, 1, 1, 2)                           \
     X(64, 1, 4, 1, 1) X(64, 2, 2, 1, 1) X(64, 2, 2, 1, 2) X(64, 4, 1, 1, 2)
-#define MPCNN_PARTS1(X) /* bf16 storage */                                                                             \
-    X(16, 1, 4, 1, 2) X(16, 1, 4, 1, 4) X(16, 2, 2, 1, 2) X(16, 2, 2, 1, 4) X(16, 1, 4, 2, 2) X(16, 4, 1, 1, 4)          \
-    X(32, 1, 4, 1, 2) X(32, 1, 4, 1, 4) X(32, 2, 2, 1, 2) X(32, 2, 2, 1, 4) X(32, 1, 4, 2, 2)                            \
-    X(32, 4, 1, 1, 2) X(32, 4, 1, 1, 4) X(32, 2, 2, 2, 2)                                                                \
-    X(64, 1, 4, 1, 2) X(64, 2, 2, 1, 2) X(64, 2, 2, 1, 4) X(64, 1, 4, 2, 2) X(64, 4, 1, 1, 2) X(64, 4, 1, 1, 4) X(64, 2, 2, 2, 2)          \
+#define MPCNN_PARTS1(X) /* bf16 storage (two channel tiles: 2 x 2 per wave where there is a choice, 4 operands per 4 instructions, not 5) */ \
+    X(16, 1, 4, 1, 2) X(16, 1, 4, 1, 4) X(16, 2, 2, 1, 2) X(16, 1, 4, 2, 2) X(16, 4, 1, 1, 4)                           \
+    X(32, 1, 4, 1, 2) X(32, 1, 4, 1, 4) X(32, 2, 2, 1, 2) X(32, 1, 4, 2, 2)                                             \
+    X(32, 4, 1, 1, 2) X(32, 4, 1, 1, 4) X(32, 2, 2, 2, 2)                                                               \
+    X(64, 1, 4, 1, 2) X(64, 2, 2, 1, 2) X(64, 1, 4, 2, 2) X(64, 4, 1, 1, 2) X(64, 4, 1, 1, 4) X(64, 2, 2, 2, 2)          \
     X(128, 2, 2, 1, 2) X(128, 4, 1, 1, 2) X(128, 4, 1, 1, 4) X(128, 2, 2, 2, 2)
 #define MPCNN_PARTS_ROW(cb, wo, wp, mo, mp) {cb, wo, wp, mo, mp},
 constexpr PartsInstance kParts3[] = {MPCNN_PARTS3(MPCNN_PARTS_ROW)};

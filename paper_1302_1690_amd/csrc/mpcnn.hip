@@ -286,6 +286,9 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
         if (in.MO == 2 && ceil_div(co, 32) % 2) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
+        // Time per matrix instruction against the best instance's.  One part: with four tiles 2 x 2 are ahead of 1 x 4 (2 x 600 x 640, deep net: 110, 169,
+        // 152 us against 117, 182, 159; even on 2 x 2048 x 2048), with two tiles 1.17 to 1.3 times as long on large maps; three parts: two tiles
+        // against one.  A workgroup alone on its compute unit, its waits in the open, takes 1.4 times as long with one part.
         const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
         const double alone = P == 3 ? 1.15 : 1.4;
         const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;

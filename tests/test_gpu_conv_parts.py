@@ -1,6 +1,9 @@
 """Convolutions (either storage type) and fp32 weight gradients on the bf16 matrix instruction, fp32 numbers as sums of
 bf16 parts (csrc/kernels_conv_parts.hpp, csrc/kernels_wgrad_parts.hpp): shapes at the edges of their tiles, channel blocks and groups against the oracle,
 numbers that have no parts, and the distance from 64-bit sums."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -286,3 +289,56 @@ def wl_layers(cfg):
         out.append((ci, m, k))
         ci, fc, side = m, fc or kind == FC, side - k + 1
     return out
+
+
+# channel counts that give every pair of block width (16, 32, 64, 128 input channels) and channel tiles (1, 2, 4, an odd number)
+# in both directions
+CHANNELS = [(16, 16, 64, 64, 32, 128, 128, 96), (16, 128, 64, 96, 32, 32, 64, 128, 32), (16, 96, 128, 16, 32, 64, 16)]
+HINTS = {"f32": [(0, 0), (4, 1), (8, 2), (2, 1), (4, 2), (2, 2)], "bf16": [(0, 0), (8, 2), (16, 4), (4, 2), (2, 2), (4, 4)]}
+
+
+def instances(dtype):
+    """The tuples the library is built with, from its list."""
+    text = open(os.path.join(os.path.dirname(mpcnn.__file__), "csrc", "launchers.hpp")).read()
+    at = text.index("#define MPCNN_PARTS%d(" % (1 if dtype == "bf16" else 3))
+    found = re.findall(r"X\((\d+), (\d+), (\d+), (\d+), (\d+)\)", text[at:text.index("#define", at + 8)])
+    return {tuple(int(v) for v in f) for f in found}
+
+
+def reached(plan):
+    """(direction, (channels per block, waves along channels, along positions, tiles per wave along both)) of a plan's convolutions."""
+    return {(m[1], (int(m[6]), int(m[2]), int(m[3]), int(m[4]), int(m[5])))
+            for m in re.finditer(r"(forward|data gradient): bf16 MFMA.*?waves (\d) x (\d) of (\d) x (\d) tiles, (\d+) channels", plan)}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_every_instance_gives_the_same_bits(dtype):
+    """Every instance the library is built with, in both directions: probabilities and gradients do not depend on which one runs, as every
+    sum is taken in the same order (the planner's own choice is held against the oracle above)."""
+    got = set()
+    for channels in CHANNELS:
+        # (narrower blocks than the channels allow: filters whose halo has no room for more)
+        for k, size in ((3, 40), (11, 20)) if channels is CHANNELS[0] else ((3, 40),):
+            layers = tuple((C, c, k) for c in channels) + ((FC, 8, 0), (FC, 2, 0))
+            patch = len(channels) * (k - 1) + 2
+            H, W = patch + size, patch + size + 7
+            net = mpcnn.Net(layers, 1, patch, mpcnn.BF16 if dtype == "bf16" else mpcnn.F32)
+            rng = np.random.default_rng(patch)
+            scale = np.concatenate([np.full(m * ci * f * f + m, 1.5 / np.sqrt(m * f * f))
+                                    for ci, m, f in zip((1,) + channels + (8,), channels + (8, 2), (k,) * len(channels) + (2, 1))])
+            net.set_params((scale * rng.uniform(-1, 1, net.param_count)).astype(np.float32))
+            image = torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda()
+            labels = torch.from_numpy(rng.integers(0, 2, (1, H, W)).astype(np.int32)).cuda()
+            first = None
+            for hint in HINTS[dtype]:
+                net.set_conv_tiling(*hint)
+                got |= reached(net.plan_describe(1, H, W, True))
+                probs = torch.empty((1, 2, H - patch + 1, W - patch + 1), device="cuda")
+                net.seg_backward(image, labels, probs=probs)
+                out = (probs.cpu().numpy(), net.get_grads())
+                first = first or out
+                assert np.isfinite(out[1]).all() and np.any(out[1])
+                assert np.array_equal(out[0], first[0]) and np.array_equal(out[1], first[1]), (channels, k, hint)
+            net.close()
+    want = {(d, i) for d in ("forward", "data gradient") for i in instances(dtype)}
+    assert got == want, sorted(want - got)

@@ -8,6 +8,8 @@ pooling window's two best candidates count as tied when within 2^-7 (more where 
 rounding a layer inherits is larger: `tau_of`).  How many windows may be resolved the other
 way than the oracle's is bounded (`check_tie_budget`).
 """
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -382,19 +384,34 @@ def test_first_pool_routing_fused_with_image_layer_gradient():
                             seed_image=1113, seed_label=2113, seed_param=3113), squash="logistic")
 
 
+def tilings(cfg, hint):
+    """(position tiles per workgroup, per wave) of the matrix-core convolutions of `cfg` under a tiling hint."""
+    net = mpcnn.Net(cfg.layers, cfg.in_channels, cfg.patch, mpcnn.BF16 if cfg.dtype == "bf16" else mpcnn.F32)
+    net.set_conv_tiling(*hint)
+    plan = net.plan_describe(cfg.batch, cfg.height, cfg.width, True)
+    net.close()
+    return {(int(m[1]), int(m[2])) for m in re.finditer(r"(\d+) position tiles, waves \d x \d of \d x (\d) tiles", plan)}
+
+
 def test_every_conv_tiling():
-    """Every instance of the matrix-core convolution kernel (position tiles per workgroup x
-    tiles per wave, for layers of 1, 2 and 4 channel tiles; fp32 and bf16 storage) against the
-    oracle: config 1's net has 32-, 64- and 100-map layers in both directions."""
-    for pt, mp in ((2, 1), (2, 2), (4, 1), (4, 2), (8, 1), (8, 2), (4, 4), (8, 4), (16, 2), (16, 4)):
+    """Every pair of position tiles per workgroup and per wave that the matrix-core convolution kernel has an instance for, with
+    either storage type, against the oracle; the plan shows that a layer took it.  Config 1's net has 32-, 64- and 100-map
+    layers in both directions; with bf16 storage 36 -> 100 maps (4 channel tiles forward, 2 backward) and 100 -> 32."""
+    for pt, mp in ((2, 1), (4, 1), (2, 2), (4, 2), (8, 2)):
         say("conv tiling: %d position tiles, %d per wave" % (pt, mp))
-        full_parity(wl.crop(wl.CONFIGS[1], 1, 75, 81), check_layers=False, tiling=(pt, mp))
-        # bf16 storage, channel counts that keep the layers on the fp32 matrix instruction
-        # (36 -> 100 maps: 4 channel tiles forward, 2 backward; 100 -> 32: 1 tile forward)
-        layers = ((C, 36, 3), (MP, 0, 2), (C, 100, 3), (MP, 0, 2), (FC, 32, 0), (FC, 3, 0))
-        full_parity(wl.Workload("bf16_odd_tiling", layers, 14, 3, 3, 1, 47, 40, 0.25, "ellipses", dtype="bf16",
-                                seed_image=1114, seed_label=2114, seed_param=3114), check_layers=False,
-                    tiling=(pt, mp))
+        cfg = wl.crop(wl.CONFIGS[1], 1, 75, 81)
+        assert (pt, mp) in tilings(cfg, (pt, mp))
+        full_parity(cfg, check_layers=False, tiling=(pt, mp))
+    layers = ((C, 36, 3), (MP, 0, 2), (C, 100, 3), (MP, 0, 2), (FC, 32, 0), (FC, 3, 0))
+    cfg = wl.Workload("bf16_odd_tiling", layers, 14, 3, 3, 1, 47, 40, 0.25, "ellipses", dtype="bf16",
+                      seed_image=1114, seed_label=2114, seed_param=3114)
+    for pt, mp in ((2, 2), (4, 2), (8, 2), (4, 4), (16, 4)):
+        say("conv tiling: %d position tiles, %d per wave, bf16" % (pt, mp))
+        assert (pt, mp) in tilings(cfg, (pt, mp))
+        full_parity(cfg, check_layers=False, tiling=(pt, mp))
+    # pairs that no instance serves leave every layer to the planner
+    for pair in ((8, 1), (16, 2), (2, 4)):
+        assert tilings(cfg, pair) == tilings(cfg, (0, 0))
     net = mpcnn.Net(wl.CONFIGS[0].layers, wl.CONFIGS[0].in_channels, wl.CONFIGS[0].patch)
     for bad in ((3, 1), (2, 3), (-2, 0), (32, 2), (8, 8)):
         with pytest.raises(mpcnn.MpcnnError):
@@ -472,13 +489,8 @@ def test_image_taken_in_bands():
             net.seg_backward_banded(d_img, d_lab, band_rows, d_pw, p_b, l_b)
             torch.cuda.synchronize()
             say("case %s bands of %d rows (%d output rows)" % (cfg.name, band_rows, cfg.out_h))
-            # fp32 storage: every position is computed with the same operations whatever the
-            # tiling, same bits.  bf16 storage: the bf16 kernels split the reduction over 4 or 8
-            # waves depending on the map's size, so a stored value can round the other way
-            if cfg.dtype == "bf16":
-                assert np.abs(p_b.cpu().numpy() - probs).max() <= 0.1 * tol_of(cfg)
-            else:
-                assert np.array_equal(p_b.cpu().numpy(), probs)
+            # every position is computed with the same operations whatever the tiling: same bits
+            assert np.array_equal(p_b.cpu().numpy(), probs)
             assert np.abs(p_b.cpu().numpy() - ref["probs"]).max() <= tol_of(cfg)
             assert abs(float(l_b.item()) - ref["loss"]) <= 0.1 * tol_of(cfg) * abs(ref["loss"])
             check_grads(cfg, net.get_grads(), ref["grads"])
