@@ -248,20 +248,25 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         lbase[p] = (int)(ty * hw + tx) * PITCH + lg * 16;
     }
 
-    // ---- weights: [16-channel chunk][tap][part][lane group][CoPad][8], the step's offset a scalar
-    const int wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = a.k * a.k2 * (a.CrPad / 16) * wstep;   // bytes
-    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<v4f*>(a.wpack), 0, wend + parts_ahead(P) * wstep, 0x00020000);
-    const int wlane = (lg * a.CoPad + oc0 + lt) * 16;
-    int wq = 0;                                       // byte offset of the next step to fetch
+    // ---- weights: [16-channel chunk][tap][part][lane group][CoPad][8], the step's place a scalar pointer
+    const long wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = (long)a.k * a.k2 * (a.CrPad / 16) * wstep;   // bytes
+    const unsigned wlane = (lg * a.CoPad + oc0 + lt) * 16;
+    const char* wq = reinterpret_cast<const char*>(a.wpack);   // the next step to fetch
     const int nblk = (a.CrPad + CB - 1) / CB;
 
     int head[P == 1 ? parts_sets(P, MO * MP) - 1 + kPartsTabAhead : 1];   // the table's first entries
     v16f acc[MO][MP], low[P == 3 ? MO : 1][P == 3 ? MP : 1];   // low: the five smaller products of three parts
     v4f w[NS][MO * P];                                // the ring
     auto fetch_w = [&](int s, int i) {
+        if constexpr (P == 1) {
 #pragma unroll
-        for (int o = 0; o < MO; ++o)
-            w[s][o * P + i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane + 512 * o, wq + i * wpart, 0));
+            for (int o = 0; o < MO; ++o) w[s][o] = *reinterpret_cast<const v4f*>(wq + wlane + 512 * o);
+        } else {                                      // (through a descriptor: the parts' offsets are scalars, no registers beside the lane's)
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wq), 0, 0x7fffffff, 0x00020000);
+#pragma unroll
+            for (int o = 0; o < MO; ++o)
+                w[s][o * P + i] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, (int)wlane + 512 * o, i * (int)wpart, 0));
+        }
     };
     auto next_w = [&]() { wq += wstep; };
 

@@ -1538,9 +1538,9 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
             ly.fwd_mfma = !last && ly.cin % 4 == 0 && ly.cin >= 8 && ly.cout >= 8;
             ly.dgrad_mfma = l > 0 && ly.cout % 4 == 0 && ly.cout >= 8 && ly.cin >= 8;
             ly.wgrad_mfma = !ly.class_fused;   // any shape: gradient rows are tiled in parameter order
-            // (the convolution kernels address a layer's weight pack by 32-bit byte offsets)
-            const size_t pack_bound = (size_t)ly.k * ly.k2 * (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) *
-                                      (ceil_div(std::max(ly.cin, ly.cout), 128) * 128) * 6;
+            // (of a layer with 2 GiB of parameters there are no packs besides)
+            const size_t pack_bound = (size_t)ly.k * ly.k2 * (ceil_div(std::max(ly.cin, ly.cout), 32) * 32 + 32) *
+                                      (ceil_div(std::max(ly.cin, ly.cout), 32) * 32 + 32) * 4;
             if (pack_bound >= (1ull << 31)) ly.fwd_mfma = ly.dgrad_mfma = false;
             const int parts = net->bf16 ? 1 : 3;
             auto pack_floats = [&](int rpad, int pad) { return ((size_t)ly.k * ly.k2 * (rpad / 16) + mpcnn::parts_ahead(parts)) * parts * 2 * pad * 4; };

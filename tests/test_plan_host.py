@@ -1,4 +1,4 @@
-"""Which kernels the planner gives to convolutions (no GPU): large filters stay on the matrix cores."""
+"""Which kernels the planner gives to convolutions (no GPU): large filters and wide layers stay on the matrix cores."""
 import pytest
 
 from paper_1302_1690_amd import mpcnn, workloads as wl
@@ -25,3 +25,11 @@ def test_large_filters_are_on_the_matrix_cores(channels, dtype):
             assert "plain" not in line, (k, line)
             rows = int(line.split(" filter rows")[0].split()[-1])
             assert rows == k if k < 8 else 1 <= rows <= k, (k, line)
+
+
+@pytest.mark.parametrize("dtype", [mpcnn.F32, mpcnn.BF16])
+@pytest.mark.parametrize("k,cin,cout", [(5, 4000, 4000), (5, 4500, 64), (9, 2048, 2400), (1, 22000, 8)])
+def test_wide_layers_are_on_the_matrix_cores(k, cin, cout, dtype):
+    """Layers of up to 2 GiB of parameters (their packs are larger: rounded up, and three parts of two bytes per number with fp32 storage)."""
+    for line in conv_lines(((C, cin, 3), (C, cout, k), (FC, 16, 0), (FC, 2, 0)), k + 4, k + 20, dtype, 1):
+        assert "plain" not in line, line
