@@ -96,4 +96,12 @@ __global__ void params_order_kernel(float* __restrict__ dev, float* __restrict__
     }
 }
 
+// A few numbers that travel with the launch, written in place
+constexpr int kCarried = 960;
+struct CarriedNumbers { int n; float v[kCarried]; };
+__global__ void write_numbers_kernel(float* __restrict__ dst, CarriedNumbers c)
+{
+    for (int i = threadIdx.x; i < c.n; i += blockDim.x) dst[i] = c.v[i];
+}
+
 }  // namespace mpcnn

@@ -205,7 +205,7 @@ struct mpcnn_net {
     float* d_packs = nullptr;
     bool packs_stale = true;
     int device = -1;
-    float* h_stage = nullptr;     // pinned host memory for one parameter vector: set / get of parameters and gradients
+    float* h_stage = nullptr;     // pinned host memory for one parameter vector: set / get of parameters and gradients (longer than kSmallVector)
     mutable std::mutex stage_mu;  // (gets are const calls)
     bool lds_attr_set = false;
     // plans of the sizes seen so far (oldest dropped first)
@@ -1372,11 +1372,30 @@ void lbfgs_free(mpcnn_net* net)
     net->lb_have_prev = false;
 }
 
-// Vectors up to this size are read back in device order and permuted here.  Reading alone the kernel is faster at any size
-// (319 numbers 22 -> 14.5 us, 90 K 48 -> 29), but waiting for it behind a training step of a tiny net is not: whole call with
-// 319 numbers 128.4 us with a copy, 131.4 with the kernel.  Between the two sizes nothing was measured; the permutation of 2048
-// numbers takes the host 1 to 2 us.
-constexpr size_t kCopyBackMax = 2048;
+// Vectors up to this size are permuted here: read back by a copy, written by launches that carry the numbers as arguments.  Longer ones are
+// permuted by the GPU, out of and into pinned memory.  The line lies where pinned memory is not worth its allocation, some 100 us per net.
+// Microseconds, copy / GPU: read back alone 22 / 15 at 128 .. 2446 numbers, 12 / 15 at 4790, 18 / 17 at 22 K, 40 / 27 at 83 K (a copy of up to
+// 16 KB takes the runtime twice as long as a larger one); behind a training step 104 / 105 at 128, 132 / 131 at 1292, 117 / 117 at
+// 2446, 123 / 123 at 4790, 146 / 143 at 22 K.
+constexpr size_t kSmallVector = 2048;
+
+// One vector between host order W[o][c][u][v], b[o] and device order W[u][v][c][o], b[o], both on the host
+void permute_params(const mpcnn_net* net, const float* src, float* dst, bool to_host)
+{
+    for (const Layer& ly : net->layers) {
+        if (ly.kind == MPCNN_MP) continue;
+        const int kk = ly.k * ly.k2, ci = ly.cin, co = ly.cout;
+        const float* s = src + ly.p_off;
+        float* d = dst + ly.p_off;
+        for (int o = 0; o < co; ++o)
+            for (int c = 0; c < ci; ++c)
+                for (int t = 0; t < kk; ++t) {
+                    const size_t host = ((size_t)o * ci + c) * kk + t, dev = ((size_t)t * ci + c) * co + o;
+                    d[to_host ? host : dev] = s[to_host ? dev : host];
+                }
+        memcpy(d + (size_t)kk * ci * co, s + (size_t)kk * ci * co, sizeof(float) * co);
+    }
+}
 
 mpcnn_status read_back(const mpcnn_net* net, const float* dev, float* host, size_t n)
 {
@@ -1385,21 +1404,13 @@ mpcnn_status read_back(const mpcnn_net* net, const float* dev, float* host, size
     if (!dev) return fail(MPCNN_EINVAL, "parameters were never set");
     HIP_TRY(hipSetDevice(net->device));
     HIP_TRY(hipDeviceSynchronize());
-    std::lock_guard<std::mutex> lock(net->stage_mu);
-    if (n <= kCopyBackMax) {
-        HIP_TRY(hipMemcpy(net->h_stage, dev, sizeof(float) * n, hipMemcpyDeviceToHost));
-        for (const Layer& ly : net->layers) {
-            if (ly.kind == MPCNN_MP) continue;
-            const int kk = ly.k * ly.k2, ci = ly.cin, co = ly.cout;
-            const float* src = net->h_stage + ly.p_off;
-            float* dst = host + ly.p_off;
-            for (int o = 0; o < co; ++o)
-                for (int c = 0; c < ci; ++c)
-                    for (int t = 0; t < kk; ++t) dst[((size_t)o * ci + c) * kk + t] = src[((size_t)t * ci + c) * co + o];
-            memcpy(dst + (size_t)kk * ci * co, src + (size_t)kk * ci * co, sizeof(float) * co);
-        }
+    if (n <= kSmallVector) {
+        float tmp[kSmallVector];
+        HIP_TRY(hipMemcpy(tmp, dev, sizeof(float) * n, hipMemcpyDeviceToHost));
+        permute_params(net, tmp, host, true);
         return MPCNN_OK;
     }
+    std::lock_guard<std::mutex> lock(net->stage_mu);
     const mpcnn_status rc = order_params(net, const_cast<float*>(dev), true);
     if (rc == MPCNN_OK) memcpy(host, net->h_stage, sizeof(float) * n);
     return rc;
@@ -1462,7 +1473,7 @@ mpcnn_status alloc_params(mpcnn_net* net)
     HIP_TRY(hipGetDevice(&net->device));
     HIP_TRY(hipMalloc((void**)&net->d_params, bytes));
     HIP_TRY(hipMalloc((void**)&net->d_grads, bytes));
-    HIP_TRY(hipHostMalloc((void**)&net->h_stage, bytes, hipHostMallocDefault));
+    if (net->n_params > kSmallVector) HIP_TRY(hipHostMalloc((void**)&net->h_stage, bytes, hipHostMallocDefault));
     HIP_TRY(hipMemset(net->d_grads, 0, bytes));
     if (net->pack_len) HIP_TRY(hipMalloc((void**)&net->d_packs, sizeof(float) * net->pack_len));
     if (net->bf16) HIP_TRY(hipMalloc((void**)&net->d_wread, bytes));
@@ -1688,7 +1699,18 @@ mpcnn_status mpcnn_set_params(mpcnn_net* net, const float* params_host, size_t n
     }
     HIP_TRY(hipSetDevice(net->device));
     HIP_TRY(hipDeviceSynchronize());
-    {
+    if (n <= kSmallVector) {
+        float tmp[kSmallVector];
+        permute_params(net, params_host, tmp, false);
+        for (size_t at = 0; at < n; at += mpcnn::kCarried) {
+            mpcnn::CarriedNumbers c;
+            c.n = (int)std::min<size_t>(mpcnn::kCarried, n - at);
+            memcpy(c.v, tmp + at, sizeof(float) * c.n);
+            mpcnn::write_numbers_kernel<<<1, 256>>>(net->d_params + at, c);
+        }
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(nullptr));
+    } else {
         std::lock_guard<std::mutex> lock(net->stage_mu);
         memcpy(net->h_stage, params_host, sizeof(float) * n);
         const mpcnn_status rc = order_params(net, net->d_params, false);
