@@ -401,6 +401,10 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
 // The image layer's weight gradient multiplies on the bf16 instruction where both operands are bf16 and a position's
 // deltas are whole 128-bit items; with fp32 storage, and for other map counts, on the fp32 one.
 inline bool l0_wgrad_on_bm(const Layer& ly, bool bf16) { return bf16 && ly.cout % 8 == 0; }
+// A launch of wgrad_parts_kernel takes some 6 us more than one of wgrad_mfma_kernel whatever it computes (512 threads, both tiles converted, up to eight
+// waves' sums to meet): 16 -> 16 channels, 2 x 2 taps, 1300 positions (2.6 MFLOP) 15.0 us against 8.8, 16 -> 16, 3 x 3, 2700 positions (12 MFLOP) 16.3
+// against 12.6; 32 -> 100, 2 x 2, 2600 positions (67 MFLOP) 17.4 against 14.8, but 2 us less in the reduce for its fewer slabs.
+constexpr double kPartsWgradFlops = 4e7;
 // layers that kernel takes: fp32 storage, 128-bit items of both tensors, more than a sliver of input channels
 inline bool wgrad_parts_layer(const Layer& ly, bool bf16) { return !bf16 && ly.wgrad_mfma && ly.cin % 4 == 0 && ly.cin >= 8 && ly.cout % 4 == 0; }
 
@@ -655,7 +659,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
             if (ly.dgrad_mfma && l > 0)
                 g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
                                               net->bf16 ? 1 : 3, es, true, net->hint_pt, net->hint_mp);
-            if (wgrad_parts_layer(ly, net->bf16)) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, nullptr);
+            if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= kPartsWgradFlops) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, nullptr);
             if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
             g->partial_n[l] = w.ok ? w.slabs : w.chunks;

@@ -25,6 +25,9 @@ EDGES = [
     # weight gradient: 8 and 7 column tiles, 27 and 58 units, several groups of workgroups
     ("groups", ((C, 48, 3), (C, 232, 3), (MP, 0, 2), (C, 200, 2), (FC, 12, 0), (FC, 2, 0)), 14, 34, 52),
     ("one_position", ((C, 16, 3), (MP, 0, 2), (C, 32, 3), (FC, 64, 0), (FC, 2, 0)), 10, 10, 10),
+    # the first and the third on maps large enough for the weight gradient in three parts
+    ("quads_many", ((C, 12, 3), (MP, 0, 2), (C, 20, 2), (FC, 36, 0), (FC, 3, 0)), 14, 151, 158),
+    ("units_many", ((C, 16, 3), (MP, 0, 2), (FC, 44, 0), (FC, 10, 0), (FC, 9, 0), (FC, 2, 0)), 4, 117, 131),
 ]
 
 
@@ -175,10 +178,10 @@ def test_sums_are_not_off_to_one_side():
 def gradients(layers, patch, params, pixw=None):
     net = mpcnn.Net(layers, 1, patch)
     rng = np.random.default_rng(11)
-    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, 40, 37)).astype(np.float32)).cuda()
-    labels = torch.from_numpy(rng.integers(0, 2, (1, 40, 37)).astype(np.int32)).cuda()
+    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, 72, 71)).astype(np.float32)).cuda()
+    labels = torch.from_numpy(rng.integers(0, 2, (1, 72, 71)).astype(np.int32)).cuda()
     net.set_params(params)
-    net.seg_backward(image, labels, pixw=None if pixw is None else torch.full((1, 40, 37), pixw, device="cuda"))
+    net.seg_backward(image, labels, pixw=None if pixw is None else torch.full((1, 72, 71), pixw, device="cuda"))
     grads = net.get_grads().astype(np.float64)
     net.close()
     return grads
@@ -202,7 +205,7 @@ def test_small_numbers_keep_their_bits():
     """Everything behind the forward pass is linear in the pixel weights, and the delta below a layer in its weights: made a
     power of two smaller, every fp32 operation rounds as before, until numbers are subnormal and off by 2^-150 each.
     Pixel weights of 2^-114: deltas from 2^-115 to 2^-125, of which 2^-133 (the last bit of bf16) would be 2^-18 to 2^-8.
-    A gradient adds 1000 products of them, whose 2^-150 are below 2^-24 of the deltas' size each: 2^-20 allows for all."""
+    A gradient adds 4700 products of them, whose 2^-150 are below 2^-24 of the deltas' size each: 2^-20 allows for all."""
     rng = np.random.default_rng(12)
     params = rng.uniform(-0.2, 0.2, mpcnn.Net(SMALL, 1, 8).param_count).astype(np.float32)
     small = gradients(SMALL, 8, params, 2.0 ** -114)
@@ -223,8 +226,8 @@ WIDE = ((C, 48, 3), (C, 132, 3), (C, 72, 2), (FC, 40, 0), (FC, 2, 0))   # patch 
 def test_deltas_without_parts():
     """Pixel weights of 2^114: no delta has parts, so every element of the data gradients (borders included) and of the weight
     gradients is computed again with fp32 multiply-adds, and stays below the largest fp32 number.  They are 2^114 times those of
-    pixel weights 1, whose sums are taken in another order: two sums of up to 1200 products, each off by
-    sqrt(1200 / 3) 2^-24 of the running sum, four layers deep: 2^-17 allows twice that."""
+    pixel weights 1, whose sums are taken in another order: two sums of up to 4700 products, each off by
+    sqrt(4700 / 3) 2^-24 of the running sum, 2.4e-6 each; 2^-17 allows twice that on both sides."""
     rng = np.random.default_rng(13)
     params = rng.uniform(-0.1, 0.1, mpcnn.Net(WIDE, 1, 8).param_count).astype(np.float32)
     big = gradients(WIDE, 8, params, 2.0 ** 114)
@@ -238,6 +241,7 @@ def test_weights_without_parts_in_the_data_gradient():
     rng = np.random.default_rng(14)
     params = rng.uniform(-0.1, 0.1, mpcnn.Net(WIDE, 1, 8).param_count).astype(np.float32)
     at = 48 * 9 + 48 + 132 * 48 * 9 + 132 + (37 * 132 + 45) * 4 + 1   # third layer: map 37, channel 45, tap 1
+    params[48 * 9 + 48 + 132 * 48 * 9 + 45] = 4.0                     # (channel 45 is nowhere near 0)
     got = []
     for value in (2.0 ** 100, 3.395e38):
         params[at] = value

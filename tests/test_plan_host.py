@@ -1,4 +1,5 @@
-"""Which kernels the planner gives to convolutions (no GPU): large filters and wide layers stay on the matrix cores."""
+"""Which kernels the planner gives to convolutions (no GPU): large filters and wide layers stay on the matrix cores; the weight gradient's
+kernel by the size of its work."""
 import pytest
 
 from paper_1302_1690_amd import mpcnn, workloads as wl
@@ -33,3 +34,14 @@ def test_wide_layers_are_on_the_matrix_cores(k, cin, cout, dtype):
     """Layers of up to 2 GiB of parameters (their packs are larger: rounded up, and three parts of two bytes per number with fp32 storage)."""
     for line in conv_lines(((C, cin, 3), (C, cout, k), (FC, 16, 0), (FC, 2, 0)), k + 4, k + 20, dtype, 1):
         assert "plain" not in line, line
+
+
+@pytest.mark.parametrize("size,parts", [(10, False), (40, False), (71, True), (300, True)])
+def test_weight_gradient_kernel_by_its_work(size, parts):
+    """16 -> 40 channels, 3 x 3: from 4e7 operations on in three parts per number."""
+    net = mpcnn.Net(((C, 16, 3), (C, 40, 3), (FC, 24, 0), (FC, 2, 0)), 1, 8)
+    plan = net.plan_describe(1, size, size, True)
+    net.close()
+    own = plan[plan.index("layer 1:"):plan.index("layer 2:")]
+    assert ("weight gradient: bf16 MFMA, three parts" in own) == parts, own
+    assert ("weight gradient: fp32 MFMA" in own) != parts, own
