@@ -92,15 +92,15 @@ __host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps
 // steps of weights that follow the last in a pack, the first ones again: the ring runs ahead without a look at the end
 __host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4 : 8; }
 
-// kPartsUp x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: two multiplications, three conversions, four shifts or masks and four
+// up x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: two multiplications, three conversions, four shifts or masks and four
 // subtractions each)
-__device__ __forceinline__ void split_parts(const float (&x)[8], u32x4 (&p)[3])
+__device__ __forceinline__ void split_parts(const float (&x)[8], u32x4 (&p)[3], float up = kPartsUp)
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        float lo = kPartsUp * x[2 * j], hi = kPartsUp * x[2 * j + 1];
+        float lo = up * x[2 * j], hi = up * x[2 * j + 1];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             const unsigned two = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2));

@@ -1,6 +1,11 @@
 // Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_bf16, every fp32
-// number as the sum of three bf16 parts, six products each (kernels_conv_parts.hpp has the arithmetic and its
-// accuracy; here too the sums come out closer to the 64-bit ones than on the fp32 instruction).
+// number as the sum of three bf16 parts, six products each (kernels_conv_parts.hpp has the arithmetic).
+//
+// Accuracy.  All six products go to one accumulator, as there is no room for two, and the instruction's results are a little too low
+// whatever their sign: over the slabs of a large map such offsets add up where roundings cancel.  So every other slab has the signs
+// of its deltas turned, and its sums' signs turned back.  Error of the gradient in the 2-norm, fp32 instruction / without turns / now: 32 -> 64 k5 on 1024 x 1024
+// 1.3e-7 / 1.8e-7 / 1.0e-7, with cancelling deltas 1.6e-6 / 2.3e-6 / 1.4e-6; 64 -> 128 k3 2.0e-7 / 2.5e-7 / 1.6e-7 and 2.8e-6 / 4.5e-6 / 1.9e-6;
+// 128 -> 200 k2 on 700 x 640 2.9e-7 / 1.7e-7 / 1.1e-7 and 1.1e-6 / 1.2e-6 / 6.3e-7.
 //
 //   dW[tap][c][o] = sum over positions of in[pos + tap][c] * dY[pos][o]        (Alg. 2)
 //
@@ -123,6 +128,8 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
         i_yx[u] = (left <= 4 ? 0x80000000u : 0u) | (y << 16) | x;
     }
     u32x4 pre[SI][2];
+    // signs of this slab's deltas (see Accuracy above)
+    const float turn = blockIdx.x & 1 ? -1.f : 1.f;
     float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
 #pragma unroll
     for (int j = 0; j < 8; ++j) bsum[j] = 0.f;
@@ -180,7 +187,7 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
 #pragma unroll
                 for (int j = 0; j < 8; ++j) bsum[j] += x[j];
             u32x4 p[3];
-            split_parts(x, p);
+            split_parts(x, p, first >= g.nh ? turn * kPartsUp : kPartsUp);
             char* dst = buf + i_dst[u];
 #pragma unroll
             for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
@@ -345,7 +352,7 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
                 v4f* dst = reinterpret_cast<v4f*>(out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024) + lane;
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4)
-                    dst[r4 * 64] = kPartsDown * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
+                    dst[r4 * 64] = turn * kPartsDown * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
             }
         if (odd) {
             // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more, with fp32

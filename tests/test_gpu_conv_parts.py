@@ -175,6 +175,37 @@ def test_sums_are_not_off_to_one_side():
     assert max(ratios) <= 2 * np.sqrt(3) * np.sqrt(800 / 3) * 2.0 ** -24
 
 
+def test_weight_gradients_are_not_off_to_one_side():
+    """A weight gradient of 32 -> 64 channels, 5 x 5, summed over a million positions in many slabs, against 64-bit sums of the library's own
+    activations and the deltas that follow from them.  All labels are one class, so that a slab's sums are large and keep their
+    sign.  The errors of 64 output channels, each with deltas of its own, average to an eighth of their size where none leans
+    to one side; four times that is allowed.  With every slab's results a little too low the average is 0.57 of their size."""
+    ci, co, k, side = 32, 64, 5, 1024
+    net = mpcnn.Net(((C, ci, 3), (C, co, k), (FC, 2, 0)), 1, k + 2)
+    rng = np.random.default_rng(3)
+    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, side, side)).astype(np.float32)).cuda()
+    params = (rng.uniform(-1, 1, net.param_count) * 0.1).astype(np.float32)
+    net.set_params(params)
+    net.seg_backward(image, torch.zeros((1, side, side), dtype=torch.int32, device="cuda"))
+    grads = net.get_grads().astype(np.float64)
+    x, h = (torch.from_numpy(net.get_activation(1, side, side, l)[0]).cuda() for l in (0, 1))
+    net.close()
+    rows, cols = h.shape[:2]
+    h = h.reshape(-1, co).double()
+    first = ci * 9 + ci
+    last = first + co * ci * k * k + co
+    w = torch.from_numpy(params[last:last + 2 * co].reshape(2, co)).cuda().double()
+    b = torch.from_numpy(params[last + 2 * co:]).cuda().double()
+    d = torch.softmax(torch.mm(h, w.t().contiguous()) + b, 1)
+    d[:, 0] -= 1
+    d = (torch.mm(d, w) * (1 - h * h)).t().contiguous()
+    want = torch.stack([torch.mm(d, x[u:u + rows, v:v + cols].reshape(-1, ci).double()) for u in range(k) for v in range(k)], 2)
+    err = grads[first:last - co] - want.cpu().numpy().ravel()
+    mean, rms = err.mean(), np.sqrt((err ** 2).mean())
+    print("weight gradient: error %.2e of its size, on average %.2f of that to one side" % (np.linalg.norm(err) / np.linalg.norm(want.cpu().numpy()), mean / rms), flush=True)
+    assert abs(mean) <= 0.5 * rms
+
+
 def gradients(layers, patch, params, pixw=None):
     net = mpcnn.Net(layers, 1, patch)
     rng = np.random.default_rng(11)
