@@ -42,15 +42,21 @@ def test_roofline_roll_up():
 
 
 def test_committed_counter_summaries_cover_the_benched_sites():
-    """profiles/traffic_<workload>.txt: one line per launch site with the HBM-side bytes per launch; the
-    headline's matrix sites and the pool sites must be there, and near or above the algorithmic bytes."""
+    """profiles/traffic_<workload>.txt: one line per launch site with the HBM-side bytes per launch; the sites of
+    the three contractions and of the pools must be there, and no site that the library has no launch for."""
     for idx in (1, 2, 3, 4):
         cfg = wl.CONFIGS[idx]
         path = os.path.join(ROOT, "profiles", "traffic_%s.txt" % cfg.name)
         assert os.path.exists(path), path
-        for site in ("maxfilter_fwd", "maxfilter_bwd", "conv_fwd_bm" if cfg.dtype == "bf16" else "conv_fwd_mfma"):
+        kind = "bm" if cfg.dtype == "bf16" else "parts"
+        for site in ["maxfilter_fwd", "maxfilter_bwd"] + [s + kind for s in ("conv_fwd_", "conv_dgrad_", "wgrad_")]:
             v = bench.read_traffic(path, site)
             assert v is not None and v > 0, (path, site)
+        source = open(os.path.join(ROOT, "paper_1302_1690_amd", "csrc", "mpcnn.hip")).read()
+        for line in open(path):
+            if not line.startswith("#"):
+                site = line.split()[0]
+                assert '"%s"' % site in source, (path, site)
     assert bench.read_traffic(os.path.join(ROOT, "profiles", "no_such_file.txt"), "x") is None
 
 
