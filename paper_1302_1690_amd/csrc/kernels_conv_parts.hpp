@@ -1,7 +1,8 @@
 // Forward / data gradient of one dilated convolution on the bf16 matrix instruction
 // (v_mfma_f32_32x32x16_bf16), for fp32 storage as well as bf16 storage.
 //
-// fp32 storage.  The bf16 instruction does 16 times the products of the fp32 one in the same time.
+// fp32 storage.  The bf16 instruction does 16 times the products of the fp32 one in the same time, and fp32 products can be made of bf16
+// ones (Henry, Tang, Heinecke: Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations, arXiv 1904.06376).
 // An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits: x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1, each
 // difference exact, and so is the sum: numbers are split 2^16 times as large, as below 2^-110 x2 would need bits that bf16 does
 // not have).  A product of two fp32 numbers is the sum of nine bf16 products, each exact in fp32.  The six with the largest factors are taken,
@@ -25,33 +26,39 @@
 // bf16 storage.  One part, one product, one accumulator: same kernel.
 //
 // Tiling.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x
-// 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32.  A step contracts 16
-// channels of one tap: MO + MP operands of P parts each feed P(P+1)/2 * MO * MP instructions.  With 1 x 2
-// tiles and three parts that is 9 KB for 12 instructions, from the vector cache (weights, the same
-// for all waves of the workgroup that share channels) and the LDS (activations), 8 and 16 bytes per cycle and wave; 2 x 2 tiles (12 KB for
-// 24 instructions) would need 128 more registers than a wave of two per SIMD has.
+// 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32, one or two with three parts (two accumulators each),
+// two or four with one.  A step contracts 16 channels of one tap: MO + MP operands of P parts each feed
+// P(P+1)/2 * MO * MP instructions.  With 1 x 2 tiles and three parts that is 9 KB for 12 instructions, from the vector cache (weights, the same
+// for all waves of the workgroup that share channels) and the LDS (activations), 8 and 16 bytes per cycle and wave.  With
+// one part it is 4 KB for 4 instructions (2 x 2) or 5 KB (1 x 4): 16 to 32 bytes per cycle and wave from LDS, 64 to 128 per compute unit, where it
+// delivers 108 to four waves and 170 to sixteen at best, conflicts not counted.
 // The input halo is brought in CB channels at a time, [position][16 channels][part] in LDS with a pitch
-// that spreads 16 successive positions of one halo row over all banks (a tile's 32 positions lie in several rows: counters read
-// 10-60 % of the LDS cycles as conflicts), so that an operand is one 128-bit read at
+// that spreads 16 successive positions of one halo row over all banks (a tile's 32 positions lie in several rows, and a row break jumps by (k2 - 1) positions:
+// counters read 10-60 % of the LDS cycles as conflicts), so that an operand is one 128-bit read at
 // an immediate offset from one address per position tile and step.
 //
 // Latency.  Workgroups are persistent and walk (tile, channel block) items; the next item's halo is
 // loaded into registers before the current one is multiplied and split into parts on its way to LDS after it.
-// Weights run through a ring of two steps (four with one part) that never drains: the pack is in step
-// order - chunks of 16 channels, the taps of each, whatever CB is - and wraps around from a tile's last step to its first.
+// Weights run through a ring of parts_ring steps that never drains: the pack is in step
+// order - chunks of 16 channels, the taps of each, whatever CB is - and its first steps follow its last once more, so that
+// no fetch looks at the end; behind a tile's last step the pointer goes back to its first.
+// One part: the LDS offsets of a block's steps come from a table in LDS, as counting taps took more scalar instructions than a step has issue slots for.
 // Two workgroups share a compute unit, so one's staging, barriers and stores lie under the other's
 // instructions.  A block costs two barriers and, as a wave's loads return in order, a wait of its weights behind the halo:
 // where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels.  Where it is large, its halo would leave
 // a tile of few positions, or none: blocks are then 16 channels of kr filter rows, in step order as well.
 //
 // Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
-//   fp32, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 (fp32 instruction) -> 461, 870, 666, 1110 (226, 231, 209, 165 TFLOP/s);
-//     data gradient 1060, 1790, 1250, 1880 -> 490, 851, 628, 981 (213, 236, 221, 187).  The loop sustains 240-260 on random
-//     data, 362 on zero weights with the same instructions: what a power limit would do.
-//   bf16, 2 x 2048 x 2048: forward 1156, 1982, 1845, 4009 (two kernels of one part before) -> 1095, 1746, 1725, 3211;
-//     data gradient 1021, 1898, 1501, 2580 -> 947, 1799, 1446, 2430.  Matrix pipes busy 26-46 %: without the next
-//     halo's loads the forward takes 861, 1379, 1377, 2578, without stores 996, 1633, 1550, 2766, without tanh 1083, 1745, 1724,
-//     3184, without the multiplications 595, 694, 1010, 2563 (1131, 1798, 1817, 3357 whole in that run).
+//   fp32, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 (fp32 instruction) -> 488, 891, 711, 1236 (214, 226, 196, 148 TFLOP/s);
+//     data gradient 1060, 1790, 1250, 1880 -> 485, 898, 684, 1070 (215, 224, 203, 171).  Matrix pipes busy 50-75 %.  One accumulator, up to four
+//     tiles per wave, no scaling against this, in turn on one machine: forward 447, 850, 646, 1088 -> 483, 879, 711, 1230, data gradient 488, 838, 621, 923 ->
+//     481, 894, 680, 1068.  The loop alone then sustained 240-260 on random data, 362 on zero weights with the same instructions: what a power limit would do.
+//   bf16, 2 x 2048 x 2048: forward 1156, 1982, 1845, 4009 (two kernels of one part before) -> 1100, 1737, 1726, 3078;
+//     data gradient 1021, 1898, 1501, 2580 -> 951, 1800, 1432, 2377.  Matrix pipes busy 28-46 %.  What the rest goes to, from an earlier form (steps' places
+//     counted, 1 x 4 tiles; 1131, 1798, 1817, 3357 whole): without the next halo's loads 861, 1379, 1377, 2578, without stores 996, 1633, 1550,
+//     2766, without tanh 1083, 1745, 1724, 3184, without the multiplications 595, 694, 1010, 2563.
+//   Slower than the kernels before: fp32 launches on one or two thousand positions with at most 16 channels (9 against 7), bf16 data gradients on
+//     maps of about 420 x 430 (53, 42, 61 against 47.5, 36, 50; the forwards gained as much).
 //   The bias from LDS instead of memory (its loads queued behind the halo's) took the bf16 forward from 8.8 to 7.9 ms.
 // Tried and dropped: 2 x 4 tiles per wave with one part (registers spill; 3.4 ms for the last layer's data gradient), three
 // workgroups per compute unit (the same, 3.9 ms for its forward).

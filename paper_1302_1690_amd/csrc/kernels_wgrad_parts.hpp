@@ -30,8 +30,10 @@
 // conversions lie under the other's instructions.
 //
 // Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), before (fp32 instruction) and
-// now: 985, 1780, 1210, 2030 us -> 506, 967, 683, 1243 us (206, 208, 204, 148 TFLOP/s; what the split instruction sustains on
-// random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 50-70 %.
+// now: 985, 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on
+// random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %.
+// Splitting numbers 2^16 times as large (two multiplications per pair more) took 495, 942, 682, 1222 to 506, 980, 699, 1295, in turn on one machine.
+// Little work (below 4e7 operations) stays on wgrad_mfma_kernel: a launch takes some 6 us more here whatever it computes.
 // The conversions decide the rest: with every item's address worked out per tile and numbers
 // converted one by one (480 vector instructions per thread and tile of 32 positions instead of 300) it was 575, 1062, 811, 1540.
 #pragma once

@@ -37,7 +37,8 @@ hipError_t conv_parts_attrs_f32_back();
 hipError_t conv_parts_attrs_b16_fwd();
 hipError_t conv_parts_attrs_b16_back();
 
-// Weight gradient (kernels_wgrad.hpp, kernels_wgrad_bf16.hpp); a.mw selects the instance.
+// Weight gradient (kernels_wgrad.hpp, kernels_wgrad_bf16.hpp); a.mw selects the instance.  fp32 storage comes here for channel counts
+// that are no multiple of 4 and for little work (below 4e7 operations), else launch_wgrad_parts serves it.
 bool launch_wgrad_f32(const WgradArgs& a, int hl, dim3 grid, size_t lds, hipStream_t st);
 bool launch_wgrad_b16(const WgradArgs& a, int hl, dim3 grid, size_t lds, hipStream_t st);
 bool launch_wgrad_bm(const WgradArgs& a, int nch, dim3 grid, size_t lds, hipStream_t st);

@@ -96,7 +96,7 @@ struct Layer {
     int drop = 0; // MP: trailing rows / columns of the patch-level map that no window covers (side mod k)
     // columns, where they differ from the rows (a rectangular pool, and every layer after it):
     int k2 = 0, dil2 = 0, drop2 = 0;
-    bool rect = false;   // k2 != k or dil2 != dil: the fp32 matrix instruction's kernels and the direct kernels take such a layer
+    bool rect = false;   // k2 != k or dil2 != dil: not for the bf16 weight gradients, the image layer's kernels and the paired pools
     bool tanh_out;
     size_t p_off; // offset of this layer's [(k*k*cin + 1) x cout] block in the parameter buffer
     size_t p_len;
@@ -1537,9 +1537,9 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
             }
         } else st = fail(MPCNN_EINVAL, "layer %d: unknown kind %d", l, d.kind);
         if (st != MPCNN_OK) break;
-        // rows and columns differ (a rectangular pool or anything behind one): the kernels on the fp32
-        // matrix instruction take such a layer, the bf16 instruction's kernels and the max-filter
-        // kernels with several elements per thread do not
+        // rows and columns differ (a rectangular pool or anything behind one): the convolution kernel, wgrad_parts_kernel,
+        // wgrad_mfma_kernel and the plain kernels take such a layer; the bf16 weight gradients, the image layer's kernels and
+        // the max-filter kernels with several elements per thread do not
         ly.rect = ly.k2 != ly.k || (ly.dil2 != ly.dil && (ly.k > 1 || ly.k2 > 1));
         if (ly.kind != MPCNN_MP) {
             ly.p_off = off;

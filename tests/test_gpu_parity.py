@@ -519,7 +519,7 @@ def test_rectangular_pooling_windows():
 def test_rectangular_pools_on_the_matrix_cores():
     """Layers behind a rectangular pool on the matrix-instruction kernels (two spacings, filters of k x k2
     taps; Background, layer MP): channel counts those kernels take, maps that span several tiles with ragged
-    ends, two images; fp32 storage, then bf16 storage (there on the fp32 instruction).  The plan must name no
+    ends, two images; fp32 storage, then bf16 storage (there the weight gradients are on the fp32 instruction).  The plan must name no
     plain kernel for a layer behind the first pool."""
     # patch 27 -> 24 -> (2x3) 12x8 -> 10x6 -> (2x2) 5x3 -> FC over 5x3 (spacing 4 x 6) -> FC
     layers = ((C, 16, 4), (MP, 0, 2, 3), (C, 32, 3), (MP, 0, 2, 2), (FC, 40, 0), (FC, 2, 0))
@@ -742,7 +742,7 @@ def test_bf16_small_net_full_oracle():
 def test_bf16_channel_counts_off_the_fast_path():
     """bf16 storage with channel counts that are multiples of 4 but not of 8, and more than 32
     output maps: the bf16 weight-gradient kernel's element-wise staging (inputs and deltas), the
-    fp32 matrix instructions on bf16 storage for the other two contractions; ragged batch."""
+    convolution kernel's staging in halves of 8 bytes; ragged batch."""
     layers = ((C, 12, 3), (MP, 0, 2), (C, 36, 3), (MP, 0, 2), (FC, 40, 0), (FC, 3, 0))   # 14 -> 12 -> 6 -> 4 -> 2
     cfg = wl.Workload("bf16_odd_channels", layers, 14, 3, 3, 2, 51, 38, 0.25, "ellipses", dtype="bf16",
                       seed_image=1107, seed_label=2107, seed_param=3107)
