@@ -23,6 +23,19 @@
 //
 // Infinities, NaN and numbers above 2^-16 of the largest bf16 have no such parts and leave a result that is not finite, as do sums above 2^96; the epilogue looks for
 // those and computes them again with fp32 multiply-adds, so they are what they would be without parts.
+//
+// fp32 storage, sums of kHalfLeast products and more: two fp16 parts per number (11 + 11 bits and a sign), three products of
+// v_mfma_f32_32x32x16_f16, x0 y0 in one accumulator and x0 y1 + x1 y0 in another - half the instructions of three bf16 parts.  Two parts lose
+// the last bit of one number in four, and x1 y1 is left out: 7.5e-8 of a sum of products of random signs, whatever its length.  That is
+// more than three parts lose by rounding in short sums and less in long ones, if those roundings become fewer at the same time: after a run of 8 to 16 steps (half_run)
+// the leading products' accumulator is added to a total and starts again from 0.  Against 64-bit sums, rms relative, three parts / two without
+// runs / two, products of random signs: K = 64 4.5e-8 / 8.9e-8 / 8.9e-8; 288 8.5e-8 / 1.30e-7 / 1.09e-7; 400 1.01e-7 / 1.47e-7 / 1.12e-7; 576 1.23e-7 / 1.69e-7 / 1.15e-7;
+// 800 1.47e-7 / 1.94e-7 / 1.17e-7; 1600 2.18e-7 / 2.64e-7 / 1.25e-7; of equal signs, K = 576, 1600: 1.23e-7 / 1.19e-7 / 5.2e-8, 2.22e-7 / 2.21e-7 / 6.4e-8.
+// Hence kHalfLeast, where the two are equal.  Errors of whole calls are what they were or smaller (gradients of a pool-free net, 96 x 110, bias gradients over the root
+// of the deltas' squares: 1.25e-6 .. 1.55e-6 with three parts, 4.4e-7 .. 5.4e-7 with two).
+// fp16 reaches from 2^-24 to 2^16, so numbers are raised by powers of two, one per tensor (ranges.hpp); numbers below 2^-16 of a tensor's largest lose bits below
+// 2^-40 of that.  Where this could matter - weights most of which are that small, infinities - the launch takes three parts, as do
+// shorter sums: a uniform choice at the kernel's start, from what the weights' packing and the writer of the deltas left, so a plan holds for either.
 // bf16 storage.  One part, one product, one accumulator: same kernel.
 //
 // Tiling.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x
@@ -49,7 +62,9 @@
 // a tile of few positions, or none: blocks are then 16 channels of kr filter rows, in step order as well.
 //
 // Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
-//   fp32, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 (fp32 instruction) -> 488, 891, 711, 1236 (214, 226, 196, 148 TFLOP/s);
+//   fp32, 1 x 1024 x 1024, three parts -> two: forward 485, 869, 707, 1281 -> 331, 574, 506, 925 (315, 351, 275, 199 TFLOP/s); data gradient 485, 886, 691, 1075 ->
+//     320, 581, 473, 785 (326, 346, 294, 234).  A loop of these operands alone sustains 342 on random data (1.03 PFLOP/s of instructions), 221 in three parts.
+//   fp32 instruction -> three parts, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 -> 488, 891, 711, 1236 (214, 226, 196, 148 TFLOP/s);
 //     data gradient 1060, 1790, 1250, 1880 -> 485, 898, 684, 1070 (215, 224, 203, 171).  Matrix pipes busy 50-75 %.  One accumulator, up to four
 //     tiles per wave, no scaling against this, in turn on one machine: forward 447, 850, 646, 1088 -> 483, 879, 711, 1230, data gradient 488, 838, 621, 923 ->
 //     481, 894, 680, 1068.  The loop alone then sustained 240-260 on random data, 362 on zero weights with the same instructions: what a power limit would do.
@@ -70,10 +85,12 @@
 #include <type_traits>
 
 #include "kernels_mfma.hpp"
+#include "ranges.hpp"
 
 namespace mpcnn {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
@@ -81,23 +98,49 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kPartsThreads = 256;   // four waves
 __host__ __device__ constexpr int parts_pitch(int parts, int CB) { return (CB / 16) * parts * 32 + 16; }   // LDS bytes of a halo position
 __host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
-__host__ __device__ constexpr int parts_items(int parts) { return parts == 3 ? 6 : 12; }                    // rounds, at most (they wait in registers)
+__host__ __device__ constexpr int parts_items(int parts) { return parts == 1 ? 12 : 6; }                    // rounds, at most (they wait in registers)
 // steps of weights in registers: 512 cycles of a wave's instructions and more, a trip from L2
-__host__ __device__ constexpr int parts_ring(int parts, int tiles) { return parts == 3 ? (tiles > 1 ? 2 : 4) : (tiles > 2 ? 4 : 8); }
+__host__ __device__ constexpr int parts_ring(int parts, int tiles) { return parts == 3 ? (tiles > 1 ? 2 : 4) : (tiles > (parts == 2 ? 1 : 2) ? 4 : 8); }
 
 // Numbers are split kPartsUp times as large, and sums of products are brought back by kPartsDown: bf16's last bit lies
 // at 2^-133, fp32's at 2^-149.
 constexpr float kPartsUp = 0x1p16f, kPartsDown = 0x1p-32f;
 
 // One part: LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
-__host__ __device__ constexpr int parts_sets(int parts, int tiles) { return parts == 3 ? 1 : tiles > 2 ? 2 : 4; }   // activations in registers
+__host__ __device__ constexpr int parts_sets(int parts, int tiles) { return parts == 3 ? 1 : parts == 2 || tiles > 2 ? 2 : 4; }   // activations in registers
 constexpr int kPartsTabAhead = 2;
 __host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps)
 {
-    return parts == 3 ? 0 : taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
+    return parts != 1 ? 0 : taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
 }
 // steps of weights that follow the last in a pack, the first ones again: the ring runs ahead without a look at the end
 __host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4 : 8; }
+
+// Two fp16 parts of fp32 numbers.  Numbers are first made 2^n times as large (ranges.hpp), the same n for a whole tensor.
+// up x = x0 + x1 but for what x1's 11 bits do not hold: at most one last bit of x, 0 for three numbers of four (8 numbers at once, in pairs:
+// two multiplications, two conversions and two subtractions each)
+__device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2], float up)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const f16x2 h = __builtin_convertvector((f32x2){up * x[2 * j], up * x[2 * j + 1]}, f16x2);
+        const f16x2 l = __builtin_convertvector((f32x2){fmaf(up, x[2 * j], -(float)h[0]), fmaf(up, x[2 * j + 1], -(float)h[1])}, f16x2);
+        p[0][j] = __builtin_bit_cast(unsigned, h);
+        p[1][j] = __builtin_bit_cast(unsigned, l);
+    }
+}
+// Steps between two additions of a tile's leading sums to its total (kernel below): whole filter rows of at most 16 taps, or whole chunks of
+// fewer taps until they are 8 steps.  A function of the filter alone.  `period`: steps after which the lengths repeat.
+constexpr int kHalfLeast = 512;   // fewest products of a sum that two fp16 parts are taken for
+struct HalfRun { int period, length; };
+__host__ __device__ inline HalfRun half_run(int k, int k2)
+{
+    const int taps = k * k2;
+    if (taps <= 16) { const int whole = taps * ((8 + taps - 1) / taps); return {whole, whole}; }
+    return {taps, k < 8 && k2 <= 8 ? k2 * (16 / k2) : k2};
+}
 
 // up x = x0 + x1 + x2 exactly (8 numbers at once, in pairs: two multiplications, three conversions, four shifts or masks and four
 // subtractions each)
@@ -123,14 +166,22 @@ __device__ __forceinline__ unsigned parts_div(unsigned n, unsigned magic, unsign
     return x == 1 ? n : __umulhi(n, magic);   // n / x for n * x < 2^32, magic = ceil(2^32 / x)
 }
 
-template <typename T, bool BACK, int CB, int WO, int WP, int MO, int MP>
-__global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a)
+// Weights that two fp16 parts do not suit: not finite, or with more than half a sum's number of them 2^-14 and less of the largest
+// (each loses the bits below 2^-40 of the largest, which is more than fp32 does once it is below 2^-16 of it)
+__device__ __forceinline__ bool weights_wide(const ConvArgs& a)
+{
+    return a.w_peak && (a.w_peak[0] >= kNoPeak || 2 * a.w_peak[1] >= (unsigned)a.small_limit);
+}
+
+template <typename T, int P, bool BACK, int CB, int WO, int WP, int MO, int MP>
+__device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_peak)
 {
     static_assert(WO * WP == 4, "four waves");
-    constexpr int P = sizeof(T) == 4 ? 3 : 1;
+    constexpr bool kF32 = sizeof(T) == 4;
+    static_assert(kF32 ? P == 2 || P == 3 : P == 1, "parts of the storage type");
     constexpr int QN = CB / 8, NSUB = CB / 16, NS = parts_ring(P, MO * MP);
     constexpr int PITCH = parts_pitch(P, CB), RP = parts_round(CB), SI = parts_items(P);
-    constexpr int ITW = P == 3 ? 2 : 1;               // 128-bit loads per staged item (8 channels of a position)
+    constexpr int ITW = kF32 ? 2 : 1;               // 128-bit loads per staged item (8 channels of a position)
     constexpr unsigned kNone = 0x80000000u;           // byte offset no buffer reaches: the load returns zeros
     const T* in_t = static_cast<const T*>(a.in);
     const T* act_t = static_cast<const T*>(a.act);
@@ -148,6 +199,11 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     const int npos = hh * hw;                         // <= SI * RP
     const int oc0 = 32 * ((blockIdx.y * WO + wo) * MO);   // first channel of this wave's tiles
     const bool live = oc0 < a.Co;                     // uniform for the wave
+
+    // ---- two parts: what numbers are raised by, and their products' sums lowered by
+    const int in_raise = P != 2 ? 0 : BACK ? raise_of(in_peak, a.in_margin) : kActRaise;
+    const float in_up = P == 2 ? power_of_two(in_raise) : 1.f;
+    const Lower down = P == 2 ? lower_by(in_raise + raise_of(*a.w_peak, 0)) : Lower{1.f, 1.f};
 
     // ---- staging: thread tid brings 8 channels (octet q of the block) of halo positions tid / QN + RP*u
     const int q = tid % QN, pos0 = tid / QN;
@@ -195,7 +251,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         const int soff = CB * cb * (int)sizeof(T);
 #pragma unroll
         for (int u = 0; u < SI; ++u) {
-            if constexpr (P == 3) {
+            if constexpr (kF32) {
                 pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
                 pre[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c + 4 < a.Cr ? voff[u] + 16u : kNone), soff, 0));
             } else {
@@ -214,14 +270,15 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         for (int u = 0; u < SI; ++u) {
             if (RP * u >= npos) break;                // uniform
             char* dst = st_dst + u * (RP * PITCH);
-            if constexpr (P == 3) {
+            if constexpr (kF32) {
                 float x[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
-                u32x4 p[3];
-                split_parts(x, p);
+                u32x4 p[P];
+                if constexpr (P == 2) split_halves(x, p, in_up);
+                else split_parts(x, p);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
+                for (int i = 0; i < P; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
             } else
                 *reinterpret_cast<u32x4*>(dst) = pre[u][0];
         }
@@ -258,11 +315,15 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     // ---- weights: [16-channel chunk][tap][part][lane group][CoPad][8], the step's place a scalar pointer
     const long wpart = 2 * a.CoPad * 16, wstep = P * wpart, wend = (long)a.k * a.k2 * (a.CrPad / 16) * wstep;   // bytes
     const unsigned wlane = (lg * a.CoPad + oc0 + lt) * 16;
-    const char* wq = reinterpret_cast<const char*>(a.wpack);   // the next step to fetch
+    const char* wq = reinterpret_cast<const char*>(P == 2 ? a.wpack2 : a.wpack);   // the next step to fetch
     const int nblk = (a.CrPad + CB - 1) / CB;
 
     int head[P == 1 ? parts_sets(P, MO * MP) - 1 + kPartsTabAhead : 1];   // the table's first entries
-    v16f acc[MO][MP], low[P == 3 ? MO : 1][P == 3 ? MP : 1];   // low: the five smaller products of three parts
+    v16f acc[MO][MP], low[kF32 ? MO : 1][kF32 ? MP : 1];   // low: the smaller products
+    v16f tot[P == 2 ? MO : 1][P == 2 ? MP : 1];       // two parts: the runs of leading products before the present one
+    int phase = 0;                                    // two parts: the ring's slot of the next step,
+    const HalfRun run = half_run(a.k, a.k2);
+    int run_left = 0, period_left = 0;                // and the steps left of a run and of a period
     v4f w[NS][MO * P];                                // the ring
     auto fetch_w = [&](int s, int i) {
         if constexpr (P == 1) {
@@ -277,6 +338,22 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
     };
     auto next_w = [&]() { wq += wstep; };
 
+    // two parts: a run of leading products joins the total
+    auto new_run = [&]() {
+        run_left = run.length < period_left ? run.length : period_left;
+        period_left -= run.length < period_left ? run.length : period_left;
+        if (period_left == 0) period_left = run.period;
+    };
+    auto add_run = [&]() {
+#pragma unroll
+        for (int o = 0; o < (P == 2 ? MO : 0); ++o)
+#pragma unroll
+            for (int p = 0; p < MP; ++p)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) { tot[o][p][r] += acc[o][p][r]; acc[o][p][r] = 0.f; }
+        new_run();
+    };
+
     // one tile's share of one channel block: its 16-channel chunks one after the other, the taps of each
     auto multiply = [&](int rows, int nsub) {
         const int taps = rows * a.k2, n = taps * nsub;   // steps of this block
@@ -287,7 +364,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 #pragma unroll
             for (int p = 0; p < MP; ++p) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + off + 32 * i);
         };
-        // three parts: the next step's place, counted (past the last one: the first one's, read for nothing)
+        // two and three parts: the next step's place, counted (past the last one: the first one's, read for nothing)
         int left = n, ta = 0, tb = 0, soff = 0;
         const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (rows * hw) * PITCH;
         auto next_x = [&]() {
@@ -308,8 +385,12 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 #pragma unroll
                 for (int p = 0; p < MP; ++p) {
                     v16f& sum = i + j > 0 ? low[o][p] : acc[o][p];
-                    sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][o * P + i]),
-                                                                  __builtin_bit_cast(bf16x8, x[t][j][p]), sum, 0, 0, 0);
+                    if constexpr (P == 2)
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w[s][o * P + i]),
+                                                                     __builtin_bit_cast(f16x8, x[t][j][p]), sum, 0, 0, 0);
+                    else
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s][o * P + i]),
+                                                                      __builtin_bit_cast(bf16x8, x[t][j][p]), sum, 0, 0, 0);
                 }
         };
         auto step = [&](int s) {
@@ -323,6 +404,12 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 product(s, 0, 2, 0); fetch_w(s, 2);
                 product(s, 0, 1, 0); fetch_w(s, 1);
                 product(s, 0, 0, 0); fetch_x(0, 0, soff); fetch_w(s, 0);
+            } else if constexpr (P == 2) {            // activations a whole step ahead
+                next_x();
+                fetch_x((s + 1) % XS, 1, soff); fetch_x((s + 1) % XS, 0, soff);
+                product(s, s % XS, 0, 1); product(s, s % XS, 1, 0); fetch_w(s, 1);
+                product(s, s % XS, 0, 0); fetch_w(s, 0);
+                if (--run_left == 0) add_run();
             } else {                                  // activations XS - 1 steps ahead, their places TS more
                 fetch_x((s + XS - 1) % XS, 0, at[s % TS]);
                 at[s % TS] = tv[s + XS - 1 + TS];
@@ -330,10 +417,32 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
             }
             next_w();
         };
+        if constexpr (P == 2) {
+            // The ring is entered at the slot where the last block left it, so that no slot changes its place: the rest of that turn, whole
+            // turns, and a part of one.
+#pragma unroll
+            for (int t = 0; t < XS; ++t)
+                if (phase % XS == t) { fetch_x(t, 1, 0); fetch_x(t, 0, 0); }
+            const int first = n < NS - phase ? n : NS - phase;
+#pragma unroll
+            for (int i = 0; i < NS; ++i)
+                if (phase <= i && i < phase + first) step(i);
+            int more = n - first;
+            phase = phase + first == NS ? 0 : phase + first;
+            for (; more >= NS; more -= NS) {
+#pragma unroll
+                for (int i = 0; i < NS; ++i) step(i);
+            }
+#pragma unroll
+            for (int i = 0; i < NS - 1; ++i)
+                if (i < more) step(i);
+            phase += more;
+            return;
+        }
         if constexpr (P == 3) {
 #pragma unroll
             for (int i = P - 1; i >= 0; --i) fetch_x(0, i, 0);
-        } else {
+        } else if constexpr (P == 1) {
 #pragma unroll
             for (int i = 0; i < XS - 1; ++i) fetch_x(i, 0, head[i]);
 #pragma unroll
@@ -372,7 +481,7 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 
     // ---- result of one element: the sum v, and the bias (forward) or the output whose slope multiplies it (data gradient)
     const bool curved = a.mode == kFwdTanh || a.mode == kDgradTanh;   // uniform
-    constexpr float kDown = P == 3 ? kPartsDown : 1.f;
+    float peak = 0.f;                                 // data gradient: largest magnitude of what this thread has written
     auto finish = [&](float v, float down, float y) {   // (down: a power of two)
         if constexpr (BACK) return curved ? down * v * squash_slope(y, a.logistic) : down * v;
         else return curved ? squash(fmaf(v, down, y), a.logistic) : fmaf(v, down, y);
@@ -420,7 +529,14 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                     v4f yv = __builtin_convertvector(y[p & 1][o][n], v4f), r;
                     if constexpr (!BACK) yv = *reinterpret_cast<const v4f*>(bias_l + (oc - 32 * (int)blockIdx.y * WO * MO));
 #pragma unroll
-                    for (int z = 0; z < 4; ++z) r[z] = finish(acc[o][p][4 * n + z], kDown, yv[z]);
+                    for (int z = 0; z < 4; ++z) {
+                        float v = acc[o][p][4 * n + z];
+                        if constexpr (P == 2) v *= down.first;
+                        r[z] = finish(v, P == 2 ? down.second : P == 3 ? kPartsDown : 1.f, yv[z]);
+                    }
+                    if constexpr (kF32 && BACK)
+#pragma unroll
+                        for (int z = 0; z < 4; ++z) peak = larger(peak, r[z]);   // (of a channel that does not exist: 0)
                     T* const dst = out_t + pos_off[p & 1] + oc;
                     if (vec) store4(dst, r);
                     else for (int z = 0; z < 4; ++z) if (oc + z < a.Co) store1(dst + z, r[z]);
@@ -488,7 +604,9 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 for (int z = 0; z < 4; ++z)
                     if (((mask >> z) & 1u) && z < left) {
                         const float y = BACK ? (curved ? load1(act_t + off + oc + z) : 0.f) : a.bias[oc + z];
-                        store1(out_t + off + oc + z, finish(sum[z], 1.f, y));
+                        const float v = finish(sum[z], 1.f, y);
+                        peak = larger(peak, v);
+                        store1(out_t + off + oc + z, v);
                     }
             }
         }
@@ -519,8 +637,10 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     acc[o][p][r] = 0.f;
-                    if constexpr (P == 3) low[o][p][r] = 0.f;
+                    if constexpr (kF32) low[o][p][r] = 0.f;
+                    if constexpr (P == 2) tot[o][p][r] = 0.f;
                 }
+        if constexpr (P == 2) { period_left = run.period; new_run(); }
         Tile nxt = cur;
         int cb = 0, row0 = 0;                         // channel block, first filter row
         bool last;
@@ -543,11 +663,15 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
                 const int fh = cur.ry < a.Ho ? (int)parts_div(a.Ho - cur.ry + a.d - 1, a.mg_d, a.d) : 0;   // extent of this residue class
                 const int fw = cur.rx < a.Wo ? (int)parts_div(a.Wo - cur.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
                 bool odd = false;
-                if constexpr (P == 3) {
+                if constexpr (kF32)
 #pragma unroll
                     for (int o = 0; o < MO; ++o)
 #pragma unroll
-                        for (int p = 0; p < MP; ++p) acc[o][p] += low[o][p];
+                        for (int p = 0; p < MP; ++p) {
+                            acc[o][p] += low[o][p];
+                            if constexpr (P == 2) acc[o][p] += tot[o][p];
+                        }
+                if constexpr (P == 3) {
                     float z = 0.f;                    // NaN as soon as one of the sums is not finite
 #pragma unroll
                     for (int o = 0; o < MO; ++o)
@@ -581,6 +705,30 @@ __global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a
         wq -= live ? wend : 0;                        // (the ring holds the first steps again)
         cur = nxt;
     }
+    if (kF32 && BACK && a.out_peak) {                 // (uniform)
+        unsigned* const four = reinterpret_cast<unsigned*>(lds);   // (the last barrier above is behind every read of the LDS)
+        unsigned most = wave_largest(bits_of(peak));
+        if (lane == 0) four[wave] = most;
+        __syncthreads();
+        if (tid == 0) {
+            for (int i = 1; i < 4; ++i) most = four[i] > most ? four[i] : most;
+            // (weights that are wide may leave a map of deltas far below the others')
+            a.out_peak[blockIdx.y * gridDim.x + blockIdx.x] = weights_wide(a) ? kNoPeak : most;
+        }
+    }
+}
+
+// fp32 storage: in two parts where everything is known to suit them
+template <typename T, bool BACK, int CB, int WO, int WP, int MO, int MP>
+__global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a)
+{
+    if constexpr (sizeof(T) == 4) {
+        unsigned peak = kNoPeak;
+        if (a.wpack2) peak = weights_wide(a) ? kNoPeak : BACK ? peak_of(a.in_peak, a.in_words) : 0;
+        if (peak < kNoPeak) conv_parts_body<T, 2, BACK, CB, WO, WP, MO, MP>(a, peak);
+        else conv_parts_body<T, 3, BACK, CB, WO, WP, MO, MP>(a, peak);
+    } else
+        conv_parts_body<T, 1, BACK, CB, WO, WP, MO, MP>(a, 0);
 }
 
 }  // namespace mpcnn

@@ -10,6 +10,7 @@
 #include <stdint.h>
 
 #include "kernels_mfma.hpp"
+#include "ranges.hpp"
 
 namespace mpcnn {
 
@@ -445,6 +446,7 @@ struct ClassArgs {
     int B, Ho, Wo, H, W, ctr, K, tanh_below;
     int probs_rows;        // rows of the probs array (Ho, or the whole image's when this call covers a band)
     int mse;               // linear outputs + half the squared error instead of softmax + cross-entropy
+    unsigned* peak;        // the words of dH (ranges.hpp), or null (fp32 storage, training)
 };
 
 // a3 + a4 in one pass over h: class logits z = W h + b, softmax, probabilities out; in
@@ -520,6 +522,7 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
 #pragma unroll
     for (int o = 0; o < NCLS; ++o) { bias[o] = a.Wk[(long)a.K * NCLS + o]; gb[o] = 0.f; }
     double my_loss = 0.0;
+    float peak = 0.f;
     // slope of the squashing function below in terms of its output y, as sl0 + y (sl1 + y sl2):
     // none 1, tanh 1 - y^2, logistic y (1 - y) - the same roundings as the direct forms, no selects
     const float sl0 = a.tanh_below == 2 ? 0.f : 1.f, sl1 = a.tanh_below == 2 ? 1.f : 0.f,
@@ -650,6 +653,7 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
                         gw[v][s][o] = fmaf(hv[v][s], dz[o], gw[v][s][o]);
                     }
                     dh[v][s] = g * fmaf(hv[v][s], fmaf(hv[v][s], sl2, sl1), sl0);
+                    if constexpr (sizeof(T) == 4) peak = larger(peak, dh[v][s]);   // (0 past channel K)
                 }
             }
             if (dh_t && live)   // (no delta buffer: loss only)
@@ -666,6 +670,8 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
         if (iy >= a.Ho) { iy -= a.Ho; ++b; }
         b += sb;
     }
+    unsigned most = 0;
+    if constexpr (TRAIN && sizeof(T) == 4) most = wave_largest(bits_of(peak));
     if (TRAIN) {
         // sum the 16 position groups of the workgroup: 4 per wave by shuffles, waves through LDS
         constexpr int NV = KV * 4 * NCLS + NCLS;
@@ -686,8 +692,13 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
         }
         my_loss += __shfl_xor(my_loss, 16, 64);   // only lanes with j == 0 hold a share
         my_loss += __shfl_xor(my_loss, 32, 64);
-        if ((tid & 63) == 0) lred[wave] = my_loss;
+        __shared__ unsigned pred[4];
+        if ((tid & 63) == 0) { lred[wave] = my_loss; pred[wave] = most; }
         __syncthreads();
+        if (sizeof(T) == 4 && a.peak && tid == 0) {
+            for (int i = 1; i < 4; ++i) most = pred[i] > most ? pred[i] : most;
+            a.peak[blockIdx.x] = most;
+        }
         float* out = a.partial + (long)blockIdx.x * ((long)a.K + 1) * NCLS;
         for (int e = tid; a.partial && e < NV * 16; e += 256) {
             const int i = e >> 4, jj = e & 15;

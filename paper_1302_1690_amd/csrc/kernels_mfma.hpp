@@ -36,6 +36,13 @@ struct ConvArgs {
     // (n / x == umulhi(n, magic) for n * x < 2^32, x > 1)
     int tiles_total;
     unsigned mg_hw, mg_tx, mg_ntx, mg_nty, mg_d, mg_d2;
+    // fp32 storage, two fp16 parts per number (conv_parts_kernel): weights in step order, or null: not for this launch; largest magnitude of the
+    // weights and number of small ones (pack_weights_kernel), or null; data gradient: the input's in_words words (ranges.hpp; its numbers are at most
+    // 2^in_margin times as large), the output's words, or null
+    const v4f* wpack2;
+    const unsigned *w_peak, *in_peak;
+    unsigned* out_peak;
+    int in_words, in_margin, small_limit;
     const float* wraw;   // [k*k2][layer input][layer output], the parameters as they are (conv_parts_kernel: sums that are not finite)
 };
 

@@ -61,6 +61,7 @@ mpcnn_status fail(mpcnn_status st, const char* fmt, ...)
     } while (0)
 
 constexpr int kLossBlocks = 2048;         // most per-workgroup loss shares (= most workgroups of the class-layer kernel)
+static_assert(kLossBlocks <= mpcnn::kDeltaWords, "each has a word");
 constexpr int kSoftmaxBlocks = 512;       // workgroups of the unfused softmax kernel
 constexpr int kDirectWgradChunks = 512;   // split of the position reduction, direct kernel
 constexpr size_t kWgradLdsCap = 144 * 1024;
@@ -106,6 +107,9 @@ struct Layer {
     ChanTiling fwd_ct{}, dgrad_ct{};
     int fwd_rpad = 0, dgrad_rpad = 0;     // reduced channels padded to 16
     size_t fwd_pack_off = 0, fwd_pack_len = 0, dgrad_pack_off = 0, dgrad_pack_len = 0;
+    // fp32 storage: sums long enough for two fp16 parts per number (mpcnn_net_create), whose packs lie beside the others
+    bool fwd_half = false, dgrad_half = false;
+    size_t fwd_half_off = 0, fwd_half_len = 0, dgrad_half_off = 0, dgrad_half_len = 0;
 };
 
 struct TilePlan {          // conv_parts_kernel: 32 PT positions per workgroup, `wgs` workgroups per channel group walk the tiles
@@ -150,6 +154,11 @@ struct Geom {
     std::vector<int> partial_n;
     std::vector<size_t> partial_len;  // floats per partial result
     size_t loss_partial_off = 0;
+    // Largest magnitudes of the deltas (ranges.hpp).  Layer whose words hold those of the delta at layer l's output, -1: nobody notes them (pools take them from
+    // above); number of the words, octaves that routing passes may add, place of the words.  `squashed`: layer l's output is a squashing function's
+    std::vector<int> delta_peak, delta_words, delta_margin;
+    std::vector<bool> squashed;
+    size_t delta_words_off = 0;
     // first convolution followed by a pool: routing through the pool and the convolution's
     // parameter gradient run as one kernel (l0_wgrad_fused_kernel), in l0_blocks workgroups
     bool l0_fused = false;
@@ -203,6 +212,8 @@ struct mpcnn_net {
     bool wread_stale = true;
     float* d_grads = nullptr;
     float* d_packs = nullptr;
+    bool halves = false;          // some layer has packs of two fp16 parts,
+    unsigned* d_words = nullptr;  // and every layer kPeakWords words (kernels_pack.hpp)
     bool packs_stale = true;
     int device = -1;
     float* h_stage = nullptr;     // pinned host memory for one parameter vector: set / get of parameters and gradients (longer than kSmallVector)
@@ -265,11 +276,11 @@ struct ProfScope {
     } while (0)
 
 // ------------------------------------------------------------------ planning
-// Tile plan of conv_parts_kernel (P parts per number, es bytes per stored element).  Cost of the busiest compute unit
+// Tile plan of conv_parts_kernel (P parts per number, mults products per step and tile - three parts' plans serve two parts as well -, es bytes per stored element).  Cost of the busiest compute unit
 // in cycles: its tiles' matrix instructions on its four SIMDs, a quarter of their staging and stores (most of it lies under
 // the other resident workgroup's instructions), and one tile's staging in full at the start.
 TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, int k, int k2, int cr, int rpad, int co,
-                         const ChanTiling& ct, int P, size_t es, bool back, int hint_pt, int hint_mp)
+                         const ChanTiling& ct, int P, int mults, size_t es, bool back, int hint_pt, int hint_mp)
 {
     TilePlan best;
     double best_cost = 0;
@@ -291,7 +302,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         // against one.  A workgroup alone on its compute unit, its waits in the open, takes 1.4 times as long with one part.
         const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
         const double alone = P == 3 ? 1.15 : 1.4;
-        const double t_mul = (double)steps * (P * (P + 1) / 2) * ct.OT * PT * 8.0 * eff;
+        const double t_mul = (double)steps * mults * ct.OT * PT * 8.0 * eff;
         // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640 positions (fp32)
         // holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions, forward / data gradient,
         // microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32 x 32 16304 / 56978 (plain kernel) ->
@@ -335,7 +346,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         }
     }
     if (!best.ok && (hint_pt || hint_mp))   // a pair that no instance serves
-        return plan_conv_parts(B, in_c, out_r, out_c, d, d2, k, k2, cr, rpad, co, ct, P, es, back, 0, 0);
+        return plan_conv_parts(B, in_c, out_r, out_c, d, d2, k, k2, cr, rpad, co, ct, P, mults, es, back, 0, 0);
     return best;
 }
 
@@ -617,6 +628,27 @@ int class_blocks(const mpcnn_net* net, long positions)
     return (int)std::min<long>(want, (positions + 15) / 16);
 }
 
+// Whose largest magnitudes a pass notes, and which tensors squashing functions bound
+void plan_peaks(const mpcnn_net* net, Geom* g)
+{
+    const size_t L = net->layers.size();
+    g->delta_peak.assign(L, -1); g->delta_words.assign(L, 0); g->delta_margin.assign(L, 0); g->squashed.assign(L, false);
+    for (size_t l = 0; l < L; ++l) g->squashed[l] = net->layers[l].kind == MPCNN_MP ? l > 0 && g->squashed[l - 1] : net->layers[l].tanh_out;
+    if (!net->halves || !g->training) return;
+    for (size_t l = L - 1; l > 0; --l) {   // the delta at layer l - 1's output
+        const Layer& ly = net->layers[l];
+        if (ly.kind == MPCNN_MP) {         // every element belongs to at most k x k2 windows
+            g->delta_peak[l - 1] = g->delta_peak[l];
+            g->delta_words[l - 1] = g->delta_words[l];
+            g->delta_margin[l - 1] = g->delta_margin[l];
+            for (int w = 1; w < ly.k * ly.k2; w *= 2) ++g->delta_margin[l - 1];
+        } else {
+            g->delta_words[l - 1] = ly.class_fused ? g->partial_n[l] : g->dgrad[l].ok ? g->dgrad[l].wgs * ly.dgrad_ct.split : 0;
+            if (g->delta_words[l - 1] > 0 && g->delta_words[l - 1] <= mpcnn::kDeltaWords) g->delta_peak[l - 1] = (int)l - 1;
+        }
+    }
+}
+
 bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g, bool mirrored = false,
                bool fixed_partials = false)
 {
@@ -650,7 +682,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         max_act = std::max(max_act, bytes);
         if (ly.kind == MPCNN_MP) continue;
         if (ly.fwd_mfma)
-            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct, net->bf16 ? 1 : 3, es, false,
+            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct, net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false,
                                         net->hint_pt, net->hint_mp);
         if (training && ly.class_fused) {
             g->partial_n[l] = class_blocks(net, (long)B * r * c);
@@ -658,7 +690,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         } else if (training) {
             if (ly.dgrad_mfma && l > 0)
                 g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
-                                              net->bf16 ? 1 : 3, es, true, net->hint_pt, net->hint_mp);
+                                              net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.dgrad_half ? 3 : 6, es, true, net->hint_pt, net->hint_mp);
             if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= kPartsWgradFlops) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, nullptr);
             if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
@@ -758,6 +790,8 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         for (size_t l = 0; l < L; ++l) g->act_off[l] = buf[l & 1];
     }
     g->loss_partial_off = off; off = align_up(off + sizeof(double) * kLossBlocks);
+    plan_peaks(net, g);
+    if (net->halves && training) { g->delta_words_off = off; off = align_up(off + sizeof(unsigned) * mpcnn::kDeltaWords * L); }
     g->total = off;
     g->label_h = H; g->probs_rows = r; g->accumulate = false;
     return true;
@@ -936,29 +970,53 @@ mpcnn_status refresh_packs(mpcnn_net* net, hipStream_t st)
     mpcnn::PackArgs pa{};
     pa.W = net->d_wread; pa.Q = net->d_packs;
     double bytes = 0;
+    bool first = false;
     auto flush = [&]() {
         if (!pa.n_seg) return;
+        if (first)
+            LAUNCH("weight_peaks", -1, 0, 0, 4.0 * net->n_params,
+                   (mpcnn::weight_peaks_kernel<<<dim3(mpcnn::kPeakParts, (unsigned)pa.n_seg), 256, 0, st>>>(pa)));
         LAUNCH("pack_weights", -1, 0, 0, bytes,
-               net->bf16 ? mpcnn::pack_parts_kernel<1><<<(unsigned)pa.total_blocks, 256, 0, st>>>(pa)
-                         : mpcnn::pack_parts_kernel<3><<<(unsigned)pa.total_blocks, 256, 0, st>>>(pa));
-        pa.n_seg = pa.total_blocks = 0; bytes = 0;
+               net->bf16 ? mpcnn::pack_weights_kernel<true><<<(unsigned)pa.total_blocks, 256, 0, st>>>(pa)
+                         : mpcnn::pack_weights_kernel<false><<<(unsigned)pa.total_blocks, 256, 0, st>>>(pa));
+        pa.n_seg = pa.total_blocks = 0; bytes = 0; first = false;
     };
-    auto add = [&](const Layer& ly, size_t off, size_t len, int rpad, int opad, int back) {
+    auto add = [&](size_t l, size_t off, size_t len, int rpad, int opad, int back, int parts, bool notes) {
         if (pa.n_seg == mpcnn::kMaxPackSegs) flush();
-        pa.seg[pa.n_seg++] = {(long)ly.p_off, (long)off, ly.k * ly.k2, ly.cin, ly.cout, rpad, opad, back, pa.total_blocks};
-        pa.total_blocks += (int)((len / (net->bf16 ? 4 : 12) + 255) / 256);   // 16 bytes per part and thread
+        const Layer& ly = net->layers[l];
+        notes = notes && net->halves;
+        first = first || notes;
+        pa.seg[pa.n_seg++] = {(long)ly.p_off, (long)off, net->halves ? net->d_words + mpcnn::kPeakWords * l : nullptr, ly.k * ly.k2, ly.cin, ly.cout, rpad, opad, back,
+                              pa.total_blocks, parts, notes ? 1 : 0};
+        pa.total_blocks += (int)((len / (4 * parts) + 255) / 256);   // 16 bytes per part and thread
         bytes += 4.0 * (len + ly.p_len);
     };
+    const int parts = net->bf16 ? 1 : 3;
     for (size_t l = 0; l < net->layers.size(); ++l) {
         const Layer& ly = net->layers[l];
         if (ly.kind == MPCNN_MP) continue;
-        if (ly.fwd_mfma) add(ly, ly.fwd_pack_off, ly.fwd_pack_len, ly.fwd_rpad, ly.fwd_ct.pad, 0);
-        if (ly.dgrad_mfma && l > 0) add(ly, ly.dgrad_pack_off, ly.dgrad_pack_len, ly.dgrad_rpad, ly.dgrad_ct.pad, 1);
+        if (ly.fwd_mfma) add(l, ly.fwd_pack_off, ly.fwd_pack_len, ly.fwd_rpad, ly.fwd_ct.pad, 0, parts, true);
+        if (ly.dgrad_mfma && l > 0) add(l, ly.dgrad_pack_off, ly.dgrad_pack_len, ly.dgrad_rpad, ly.dgrad_ct.pad, 1, parts, !ly.fwd_mfma);
+        if (ly.fwd_half) add(l, ly.fwd_half_off, ly.fwd_half_len, ly.fwd_rpad, ly.fwd_ct.pad, 0, 2, false);
+        if (ly.dgrad_half) add(l, ly.dgrad_half_off, ly.dgrad_half_len, ly.dgrad_rpad, ly.dgrad_ct.pad, 1, 2, false);
     }
     flush();
     HIP_TRY(hipGetLastError());
     net->packs_stale = false;
     return MPCNN_OK;
+}
+
+// Words of the delta at layer l's output, null where nobody notes them
+unsigned* delta_words(const Geom& g, char* ws, size_t l)
+{
+    return g.training && g.delta_peak[l] >= 0 ? (unsigned*)(ws + g.delta_words_off) + mpcnn::kDeltaWords * g.delta_peak[l] : nullptr;
+}
+// What conv_parts_kernel has to know of a layer's weights
+void weights_of(mpcnn::ConvArgs* a, const mpcnn_net* net, size_t l)
+{
+    const Layer& ly = net->layers[l];
+    a->w_peak = net->d_words + mpcnn::kPeakWords * l;
+    a->small_limit = ly.k * ly.k2 * std::min(ly.cin, ly.cout);
 }
 
 // Forward through every layer; in training mode everything is kept for the backward.
@@ -1030,6 +1088,7 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
             a.probs_rows = g.probs_rows;
             a.K = Ci; a.tanh_below = (l > 0 && net->layers[l - 1].tanh_out) ? 1 + net->logistic : 0;
             a.mse = net->loss_kind == MPCNN_LOSS_MSE;
+            a.peak = l > 0 ? delta_words(g, ws, l - 1) : nullptr;
             const int blocks = class_blocks(net, M);
             const bool train = labels != nullptr;
             const double flops = 2.0 * M * Ci * ly.cout * (train ? 3.0 : 1.0);
@@ -1055,6 +1114,10 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.mode = ly.tanh_out ? kFwdTanh : kFwdLinear; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.fwd_ct.split);
                 parts_grid(&a, &grid, tp); a.wraw = Wk;
+                if (ly.fwd_half && l > 0 && g.squashed[l - 1]) {
+                    weights_of(&a, net, l);
+                    a.wpack2 = (const v4f*)(net->d_packs + ly.fwd_half_off);
+                }
                 bool launched = false;
                 LAUNCH(kF32 ? "conv_fwd_parts" : "conv_fwd_bm", l, step, flops, bytes, launched = launch_conv<T>(a, tp, grid, st));
                 if (!launched)   // a plan without a kernel instance: a planner bug, never a silent skip
@@ -1295,6 +1358,12 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                 a.mode = below_tanh ? kDgradTanh : kDgradPlain; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.dgrad_ct.split);
                 parts_grid(&a, &grid, tp); a.wraw = Wk;
+                if (net->halves) {
+                    weights_of(&a, net, li);
+                    a.out_peak = delta_words(g, ws, li - 1);
+                    a.in_peak = delta_words(g, ws, li); a.in_words = g.delta_words[li]; a.in_margin = g.delta_margin[li];
+                    if (ly.dgrad_half && a.in_peak) a.wpack2 = (const v4f*)(net->d_packs + ly.dgrad_half_off);
+                }
                 bool launched = false;
                 LAUNCH(kF32 ? "conv_dgrad_parts" : "conv_dgrad_bm", li, dstep, flops, dbytes, launched = launch_conv<T>(a, tp, grid, st));
                 if (!launched)
@@ -1468,8 +1537,10 @@ void free_params(mpcnn_net* net)
     (void)hipFree(net->d_params);
     (void)hipFree(net->d_grads);
     (void)hipFree(net->d_packs);
+    (void)hipFree(net->d_words);
     (void)hipHostFree(net->h_stage);
     net->d_params = net->d_grads = net->d_packs = net->d_wread = net->h_stage = nullptr;
+    net->d_words = nullptr;
 }
 mpcnn_status alloc_params(mpcnn_net* net)
 {
@@ -1480,6 +1551,7 @@ mpcnn_status alloc_params(mpcnn_net* net)
     if (net->n_params > kSmallVector) HIP_TRY(hipHostMalloc((void**)&net->h_stage, bytes, hipHostMallocDefault));
     HIP_TRY(hipMemset(net->d_grads, 0, bytes));
     if (net->pack_len) HIP_TRY(hipMalloc((void**)&net->d_packs, sizeof(float) * net->pack_len));
+    if (net->halves) HIP_TRY(hipMalloc((void**)&net->d_words, sizeof(unsigned) * mpcnn::kPeakWords * net->layers.size()));
     if (net->bf16) HIP_TRY(hipMalloc((void**)&net->d_wread, bytes));
     else net->d_wread = net->d_params;
     const mpcnn_status rc = set_lds_attrs(net->bf16);
@@ -1571,6 +1643,14 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
                 ly.dgrad_pack_len = pack_floats(ly.dgrad_rpad, ly.dgrad_ct.pad);
                 ly.dgrad_pack_off = pack; pack += ly.dgrad_pack_len;
             }
+            // Two fp16 parts per number lose a last bit of one number in four; in a sum whose runs of leading products are added up (kernels_conv_parts.hpp)
+            // that is less than what three parts' roundings come to from about 500 products on.
+            auto half_floats = [&](int rpad, int pad) { return ((size_t)ly.k * ly.k2 * (rpad / 16) + mpcnn::parts_ahead(2)) * 2 * 2 * pad * 4; };
+            ly.fwd_half = !net->bf16 && ly.fwd_mfma && l > 0 && (long)ly.k * ly.k2 * ly.cin >= mpcnn::kHalfLeast;
+            ly.dgrad_half = !net->bf16 && ly.dgrad_mfma && (long)ly.k * ly.k2 * ly.cout >= mpcnn::kHalfLeast;
+            if (ly.fwd_half) { ly.fwd_half_len = half_floats(ly.fwd_rpad, ly.fwd_ct.pad); ly.fwd_half_off = pack; pack += ly.fwd_half_len; }
+            if (ly.dgrad_half) { ly.dgrad_half_len = half_floats(ly.dgrad_rpad, ly.dgrad_ct.pad); ly.dgrad_half_off = pack; pack += ly.dgrad_half_len; }
+            net->halves = net->halves || ly.fwd_half || ly.dgrad_half;
         }
         ch = ly.cout;
         net->layers.push_back(ly);
@@ -1639,11 +1719,11 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         va_end(ap);
         if (n > 0) used = std::min(cap - 1, used + (size_t)n);
     };
-    auto conv = [&](const char* what, const TilePlan& tp, const ChanTiling& ct) {
+    auto conv = [&](const char* what, const TilePlan& tp, const ChanTiling& ct, bool half) {
         if (!tp.ok) { put("  %s: plain kernel\n", what); return; }
         put("  %s: bf16 MFMA, %s, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
             "%d channels and %d filter rows per block, tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what,
-            net->bf16 ? "one part per number" : "three parts per number", ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
+            net->bf16 ? "one part per number" : half ? "three parts per number or two of fp16" : "three parts per number", ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
             tp.in.CB, tp.kr, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
     };
     put("workspace %zu bytes\n", g.total);
@@ -1661,9 +1741,9 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
                  (long)B * g.rows[l] * g.cols[l] < (1l << 31) / 32)
             put("  forward: image-layer kernel on the fp32 MFMA\n");
         else
-            conv("forward", g.fwd[l], ly.fwd_ct);
+            conv("forward", g.fwd[l], ly.fwd_ct, ly.fwd_half);
         if (!training) continue;
-        if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct);
+        if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct, ly.dgrad_half);
         const WgradPlan& w = g.wgrad[l];
         if (l == 0 && g.l0_fused) put("  weight gradient: fused with the routing of the pool above, %d workgroups\n", g.l0_blocks);
         else if (w.l0m) put("  weight gradient: image-layer kernel on the %s MFMA, %d tiles of 8 x 32, %d workgroups\n",

@@ -1,0 +1,109 @@
+"""fp32 convolutions and weight gradients in two fp16 parts per number (csrc/ranges.hpp, csrc/kernels_conv_parts.hpp, csrc/kernels_wgrad_parts.hpp):
+every length of the runs in which leading products are summed, and numbers that two parts do not suit, against 64-bit sums."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1302_1690_amd import mpcnn, workloads as wl
+from test_gpu_conv_parts import close_layers
+
+pytestmark = pytest.mark.gpu
+C, FC = wl.C, wl.FC
+
+# filters and channels of the layer behind the first: sums of 512 products and a few more in both directions; runs of 8 chunks (1 x 1), two chunks, a
+# chunk, filter rows of a chunk (two, three, one) and, from 8 rows on, filter rows in blocks of fewer rows
+SHAPES = [(1, 516, 520), (2, 128, 132), (3, 60, 64), (4, 32, 36), (5, 24, 40), (6, 16, 20), (7, 12, 16), (8, 8, 12), (11, 8, 8), (26, 8, 8)]
+
+
+def gradient64(layers, patch, params, image, labels):
+    """The flat gradient in 64 bits, pool-free nets with tanh and cross-entropy."""
+    tensors, at, side, ci, fc = [], 0, patch, 1, False
+    x = torch.from_numpy(image).double()
+    for i, (kind, m, k) in enumerate(layers):
+        k = k if kind == C else (1 if fc else side)
+        n = m * ci * k * k
+        w = torch.from_numpy(params[at:at + n].astype(np.float64).reshape(m, ci, k, k)).requires_grad_()
+        b = torch.from_numpy(params[at + n:at + n + m].astype(np.float64)).requires_grad_()
+        tensors += [w, b]
+        x = torch.nn.functional.conv2d(x, w, b)
+        if i < len(layers) - 1:
+            x = torch.tanh(x)
+        at += n + m
+        side, ci, fc = (side - k + 1 if kind == C else 1), m, fc or kind == FC
+    c = (patch - 1) // 2
+    target = torch.from_numpy(labels)[:, c:c + x.shape[2], c:c + x.shape[3]].long()
+    torch.nn.functional.cross_entropy(x, target, reduction="sum").backward()
+    return torch.cat([t.grad.reshape(-1) for t in tensors]).numpy()
+
+
+def case(k, c0, c1, size, seed=3):
+    layers = ((C, c0, 3), (C, c1, k), (FC, 24, 0), (FC, 2, 0))
+    patch = k + 4
+    rng = np.random.default_rng(seed)
+    H, W = patch + size, patch + size + 5
+    image = rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)
+    labels = rng.integers(0, 2, (1, H, W)).astype(np.int32)
+    params, ci = [], 1
+    for m, f in ((c0, 3), (c1, k), (24, 3), (2, 1)):
+        params.append(rng.uniform(-1, 1, m * ci * f * f + m) * 1.5 / np.sqrt(ci * f * f))
+        ci = m
+    return layers, patch, np.concatenate(params).astype(np.float32), image, labels
+
+
+def gradient(layers, patch, params, image, labels):
+    net = mpcnn.Net(layers, 1, patch)
+    net.set_params(params)
+    net.seg_backward(torch.from_numpy(image).cuda(), torch.from_numpy(labels).cuda())
+    got = net.get_grads().astype(np.float64)
+    plan = net.plan_describe(1, image.shape[2], image.shape[3], True)
+    net.close()
+    return got, plan
+
+
+# A gradient's terms are products of activations and deltas, each of which has passed up to three sums: a sum's error is at most as large as
+# that of fp32 additions, sqrt(K / 3) 2^-24 of its terms' root of squares (K <= 5408: 2.6e-6), the squashing function's 1.2e-7 of 1, which a slope
+# (1 - y^2 where y is near 1) carries over whole.  Five of the larger ones together:
+BOUND = 5 * np.sqrt(5408 / 3) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("k,c0,c1", SHAPES)
+def test_runs_of_every_length(k, c0, c1):
+    args = case(k, c0, c1, 34)
+    got, plan = gradient(*args)
+    assert plan.count("three parts per number or two of fp16") >= 2, plan
+    assert close_layers(got, gradient64(*args), args[0], args[1]) <= BOUND
+
+
+@pytest.mark.parametrize("what", ["tiny_input_map", "one_large_weight", "a_large_map"])
+def test_numbers_that_do_not_suit_two_parts(what):
+    """A map whose weights are 2^-24 of the others, one weight 2^20 times and
+    a map 2^30 times the others: as close to 64 bits as ordinary numbers."""
+    layers, patch, params, image, labels = case(3, 60, 64, 70)
+    first = 60 * 9 + 60
+    second = params[first:first + 64 * 60 * 9].reshape(64, 60, 9)      # (a view)
+    if what == "tiny_input_map":
+        second[:, 3] *= 2.0 ** -24
+    elif what == "one_large_weight":
+        second[10, 20, 4] = 2.0 ** 20
+    else:
+        second[5] *= 2.0 ** 30
+    got, _ = gradient(layers, patch, params, image, labels)
+    assert close_layers(got, gradient64(layers, patch, params, image, labels), layers, patch) <= BOUND
+
+
+def test_deltas_of_very_different_sizes():
+    """Pixel weights from 2^-60 to 1 within one image, and the same 2^-80 times as large: powers of two, so the second gradient is the first's but for
+    the rounding of what is 2^-40 of the largest deltas and less."""
+    layers, patch, params, image, labels = case(3, 60, 64, 70)
+    rng = np.random.default_rng(5)
+    pixw = torch.from_numpy((2.0 ** rng.integers(-60, 1, labels.shape)).astype(np.float32)).cuda()
+    got = []
+    for scale in (1.0, 2.0 ** -80):
+        net = mpcnn.Net(layers, 1, patch)
+        net.set_params(params)
+        net.seg_backward(torch.from_numpy(image).cuda(), torch.from_numpy(labels).cuda(), pixw=pixw * scale)
+        got.append(net.get_grads().astype(np.float64) / scale)
+        net.close()
+    assert np.isfinite(got[0]).all()
+    assert close_layers(got[1], got[0], layers, patch) <= BOUND
