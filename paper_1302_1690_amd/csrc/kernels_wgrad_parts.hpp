@@ -1,5 +1,6 @@
-// Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_bf16, every fp32
-// number as the sum of three bf16 parts, six products each (kernels_conv_parts.hpp has the arithmetic).
+// Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_f16, every fp32 number as the sum of two fp16
+// parts, three products each, or, where the numbers do not suit fp16 (ranges.hpp), on v_mfma_f32_32x32x16_bf16 in three bf16 parts, six products
+// each (kernels_conv_parts.hpp has the arithmetic of both).  The accumulator's roundings, half as many with two parts, make up for the bits that two parts lose.
 //
 // Accuracy.  All six products go to one accumulator, as there is no room for two, and the instruction's results are a little too low
 // whatever their sign: over the slabs of a large map such offsets add up where roundings cancel.  So every other slab has the signs
@@ -15,7 +16,7 @@
 // them for ONE gradient row or output channel; the transposing LDS read (ds_read_b64_tr_b16, see
 // kernels_wgrad_tr.hpp) gives that from channels-last tiles.
 //
-// Layout.  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
+// Layout (three parts; two: 64 bytes per position, planes shifted by 32).  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
 // position: the 16 lanes that read 4 positions together meet no bank twice, and with a plane pitch of 128 mod 256
 // bytes neither do the 32 of two planes; counters, stores included, still read 26-42 % of the LDS cycles as conflicts).  Parts, the second half of an operand and successive chunks are immediates.  A
 // gradient row tile is two UNITS of 16 rows, a unit being (plane, tap): the two halves of the lanes
@@ -29,8 +30,9 @@
 // of the two waves of a SIMD one writes before it multiplies and the other after, so that one's
 // conversions lie under the other's instructions.
 //
-// Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), before (fp32 instruction) and
-// now: 985, 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on
+// Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), three parts -> two: 522, 1005, 710, 1325 us -> 324, 620, 478,
+// 845 (322, 325, 291, 217 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7, 1.01e-7, with cancelling deltas 1.36e-6, 1.93e-6, 6.3e-7 -> 1.28e-6, 1.72e-6, 5.5e-7.
+// Before (fp32 instruction) and in three parts: 985, 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on
 // random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %.
 // Splitting numbers 2^16 times as large (two multiplications per pair more) took 495, 942, 682, 1222 to 506, 980, 699, 1295, in turn on one machine.
 // Little work (below 4e7 operations) stays on wgrad_mfma_kernel: a launch takes some 6 us more here whatever it computes.
@@ -45,7 +47,7 @@ namespace mpcnn {
 constexpr int kWpThreads = 512;
 constexpr int kWpItems = 4;       // 8-channel items per thread and tile, at most
 constexpr int kWpMaxTiles = 9;    // row tiles per wave
-constexpr int kWpPos = 96;        // LDS bytes of a position of one plane
+__host__ __device__ constexpr int wp_pos(int parts) { return 32 * parts; }   // LDS bytes of a position of one plane
 
 struct WgradPartsArgs {
     const float* in;     // [B][Hi][Wi][Ci]  layer input
@@ -58,17 +60,24 @@ struct WgradPartsArgs {
     int Nt, RT;          // 32-column tiles of the result; row tiles of a group
     int wm, wn, wk;      // wm * wn * wk = 8
     int ppg, tpg, ntg;   // planes and taps per group; groups along the taps (blockIdx.y = plane group * ntg + tap group)
+    const unsigned* dy_peak;             // dY's dy_words words (ranges.hpp), or null: not known, or `in` is no output of a squashing function
+    int dy_words, dy_margin;             // dY is at most 2^dy_margin times as large as they say
     unsigned mg_nqh, mg_hwp, mg_txp, mg_tpg, mg_k2, mg_ntx, mg_nty, mg_d, mg_d2;   // ceil(2^32 / x)
 };
 
 // LDS geometry shared with the host's plan (bytes)
 struct WpGeom { int hh, hwp, hplane, dplane, halo_b, buf_b, nh, nd; };   // nh, nd: items of the halo (rounded up to whole waves) and of the delta tile
-__host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg, int wn)
+__host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg, int wn, int parts)
 {
     WpGeom g;
     g.hh = R + k - 1; g.hwp = 16 * nch + k2 - 1;
-    g.hplane = (((g.hh * g.hwp + 3) / 8) * 8 + 4) * kWpPos;       // positions = 4 mod 8, at least hh * hwp
-    g.dplane = (16 * R * nch + 4) * kWpPos;
+    if (parts == 3) {
+        g.hplane = (((g.hh * g.hwp + 3) / 8) * 8 + 4) * wp_pos(3);       // positions = 4 mod 8, at least hh * hwp
+        g.dplane = (16 * R * nch + 4) * wp_pos(3);
+    } else {                                                             // a plane's 32 bytes fall between another's (and 64 to drop items into)
+        g.hplane = g.hh * g.hwp * wp_pos(2) + 96;
+        g.dplane = 16 * R * nch * wp_pos(2) + 96;
+    }
     g.halo_b = 2 * wn * g.dplane;
     g.buf_b = g.halo_b + ppg * g.hplane;
     g.nh = (g.hh * g.hwp * 2 * ppg + 63) / 64 * 64;
@@ -76,9 +85,10 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
     return g;
 }
 
-template <int PM>
-__global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsArgs a)
+template <int PM, int P>
+__device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigned dy_peak)
 {
+    constexpr int kWpPos = wp_pos(P);
     constexpr int SI = kWpItems;
     constexpr unsigned kNone = 0x80000000u;
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -89,7 +99,7 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
     const int nidx = wave & (wn - 1);
     const int midx = __builtin_amdgcn_readfirstlane((wave / wn) % a.wm);
     const int kidx = __builtin_amdgcn_readfirstlane(wave / (wn * a.wm));
-    const WpGeom g = wp_geom(a.R, a.nch, a.k, a.k2, a.ppg, wn);
+    const WpGeom g = wp_geom(a.R, a.nch, a.k, a.k2, a.ppg, wn, P);
     const int txp = 16 * a.nch;
     const int p0 = (blockIdx.y / a.ntg) * a.ppg, tap0 = (blockIdx.y % a.ntg) * a.tpg;   // first plane, first tap of the group
     const int nt = blockIdx.z * wn + nidx;
@@ -132,6 +142,10 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
     u32x4 pre[SI][2];
     // signs of this slab's deltas (see Accuracy above)
     const float turn = blockIdx.x & 1 ? -1.f : 1.f;
+    // what numbers are split after being multiplied by, and what takes their products' sums back
+    const int in_raise = P == 2 ? kActRaise : 0, dy_raise = P == 2 ? raise_of(dy_peak, a.dy_margin) : 0;
+    const float in_up = P == 2 ? power_of_two(in_raise) : kPartsUp, dy_up = turn * (P == 2 ? power_of_two(dy_raise) : kPartsUp);
+    const Lower down = P == 2 ? lower_by(in_raise + dy_raise) : Lower{kPartsDown, 1.f};
     float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
 #pragma unroll
     for (int j = 0; j < 8; ++j) bsum[j] = 0.f;
@@ -188,11 +202,13 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
             if (first >= g.nh)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) bsum[j] += x[j];
-            u32x4 p[3];
-            split_parts(x, p, first >= g.nh ? turn * kPartsUp : kPartsUp);
+            u32x4 p[P];
+            const float up = first >= g.nh ? dy_up : in_up;
+            if constexpr (P == 2) split_halves(x, p, up);
+            else split_parts(x, p, up);
             char* dst = buf + i_dst[u];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
+            for (int i = 0; i < P; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
         }
     };
 
@@ -218,12 +234,12 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[p][r] = 0.f;
 
-    struct Op { tr_bf16x8 part[3]; };
+    struct Op { tr_bf16x8 part[P]; };
     auto fetch = [&](unsigned addr) {
         typedef tr_bf16x4 __attribute__((address_space(3))) * lds_ptr;
         Op o;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < P; ++i) {
             const tr_bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(uintptr_t)(addr + 32 * i));
             const tr_bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(uintptr_t)(addr + 32 * i + 4 * kWpPos));
             o.part[i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -231,8 +247,14 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
         return o;
     };
     auto mul = [&](const Op& A, const Op& Bo, v16f& c) {
+        if constexpr (P == 2) {
+#define MPCNN_MUL(i, j) c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, A.part[i]), __builtin_bit_cast(f16x8, Bo.part[j]), c, 0, 0, 0)
+            MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); MPCNN_MUL(0, 0);
+#undef MPCNN_MUL
+            return;
+        }
 #define MPCNN_MUL(i, j) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.part[i], Bo.part[j], c, 0, 0, 0)
-        MPCNN_MUL(2, 0); MPCNN_MUL(0, 2); MPCNN_MUL(1, 1); MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); MPCNN_MUL(0, 0);
+        MPCNN_MUL(P - 1, 0); MPCNN_MUL(0, P - 1); MPCNN_MUL(1, 1); MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); MPCNN_MUL(0, 0);
 #undef MPCNN_MUL
     };
     // one tile: the chunks (row, 16 columns) that hold positions, dealt to the wk waves
@@ -347,14 +369,14 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
         for (int p = 0; p < PM; ++p)
 #pragma unroll
             for (int r = 0; r < 16; ++r) z = fmaf(acc[p][r], 0.f, z);
-        const bool odd = __any(z != z);
+        const bool odd = P == 3 && __any(z != z);      // (two parts: every number is finite, and no sum overflows)
 #pragma unroll
         for (int p = 0; p < PM; ++p)
             if (midx * PM + p < a.RT) {
                 v4f* dst = reinterpret_cast<v4f*>(out + (((long)blockIdx.y * a.RT + midx * PM + p) * a.Nt + nt) * 1024) + lane;
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4)
-                    dst[r4 * 64] = turn * kPartsDown * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]};
+                    dst[r4 * 64] = down.second * (turn * down.first * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]});
             }
         if (odd) {
             // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more, with fp32
@@ -430,6 +452,16 @@ __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsAr
             if (bt < a.Nt) out[(long)groups * a.RT * a.Nt * 1024 + bt * 32 + (tid & 31)] = s;
         }
     }
+}
+
+// In two parts where both tensors suit them
+template <int PM>
+__global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsArgs a)
+{
+    unsigned peak = kNoPeak;
+    if (a.dy_peak) peak = peak_of(a.dy_peak, a.dy_words);
+    if (peak < kNoPeak) wgrad_parts_body<PM, 2>(a, peak);
+    else wgrad_parts_body<PM, 3>(a, peak);
 }
 
 }  // namespace mpcnn

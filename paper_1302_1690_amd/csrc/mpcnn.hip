@@ -358,7 +358,7 @@ unsigned magic_of(unsigned x) { return x <= 1 ? 0u : (unsigned)(((1ull << 32) + 
 // (its conversions lie under the other wave's instructions, not all of them), a barrier, and the share of the closing
 // reduce, which reads every slab's partial result at about 7 bytes per cycle and compute unit.
 // `bound`, if given, receives the most floats of partial sums any map size can ask for.
-WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, size_t* bound)
+WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, bool half, size_t* bound)
 {
     WgradPlan best;
     double best_cost = -1;
@@ -381,7 +381,7 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
                     for (int R : {1, 2, 4, 8})
                         for (int nch = 1; nch <= 4; ++nch) {
                             if (R * nch < wk || (R > 1 && R / 2 >= fh) || (nch > 1 && 16 * (nch - 1) >= fw)) continue;
-                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn);
+                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn, 3);
                             size_t lds = std::max((size_t)2 * g.buf_b, (size_t)16 * 1024);
                             if (wk > 1) lds = std::max(lds, (size_t)4 * PM * 4096);
                             if (lds > (size_t)160 * 1024 || g.nh + g.nd > mpcnn::kWpItems * mpcnn::kWpThreads) continue;
@@ -393,8 +393,8 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
                             if (tiles * std::max(std::max(ntx, nty), std::max(ly.dil, ly.dil2)) >= (1l << 31)) continue;
                             const long tps = (tiles + target - 1) / target, slabs = (tiles + tps - 1) / tps;
                             const double chunks = (double)fh / nty * ceil_div(fw, 16) / ntx / wk;   // of a wave and tile, on average
-                            const double t_mul = chunks * PM * 6 * 32 * 2;
-                            const double t_load = (g.nh + g.nd) * (32.0 / 10 + 75.0 * 6 / 256);
+                            const double t_mul = chunks * PM * (half ? 3 : 6) * 32 * 2;
+                            const double t_load = (g.nh + g.nd) * (32.0 / 10 + (half ? 40.0 : 75.0) * 6 / 256);
                             const double cost = tps * (std::max(t_mul, 0.5 * t_load) + 0.5 * t_load + 800.0) + (double)slabs * plen * 4 / (7.0 * kNumCU);
                             if (best_cost < 0 || cost < best_cost) {
                                 best_cost = cost;
@@ -691,7 +691,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
             if (ly.dgrad_mfma && l > 0)
                 g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
                                               net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.dgrad_half ? 3 : 6, es, true, net->hint_pt, net->hint_mp);
-            if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= kPartsWgradFlops) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, nullptr);
+            if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= kPartsWgradFlops) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, net->halves, nullptr);
             if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
             g->partial_n[l] = w.ok ? w.slabs : w.chunks;
@@ -775,7 +775,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
                                    (size_t)std::max(kDirectWgradChunks, 2 * kNumCU) * ly.p_len);
                 if (wgrad_parts_layer(ly, net->bf16)) {
                     size_t bound = 0;
-                    (void)plan_wgrad_parts(ly, 1, 1, 1, 1, &bound);
+                    (void)plan_wgrad_parts(ly, 1, 1, 1, 1, net->halves, &bound);
                     alloc_f = std::max(alloc_f, bound);
                 }
                 alloc_f = std::max(alloc_f, (size_t)g->partial_n[l] * g->partial_len[l]);
@@ -1281,6 +1281,8 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                     a.tiles_total = wp.tiles_total; a.tiles_per_slab = wp.tiles_per_slab;
                     a.Nt = wp.Nt; a.RT = wp.RT; a.wm = wp.wm; a.wn = wp.wn; a.wk = wp.wk;
                     a.ppg = wp.ppg; a.tpg = wp.tpg; a.ntg = wp.ntg;
+                    a.dy_peak = delta_words(g, ws, li); a.dy_words = g.delta_words[li]; a.dy_margin = g.delta_margin[li];
+                    if (li == 0 || !g.squashed[li - 1]) a.dy_peak = nullptr;
                     a.mg_nqh = magic_of(2 * wp.ppg); a.mg_hwp = magic_of(16 * wp.nch + ly.k2 - 1); a.mg_txp = magic_of(16 * wp.nch);
                     a.mg_tpg = magic_of(wp.tpg); a.mg_k2 = magic_of(ly.k2); a.mg_ntx = magic_of(wp.ntx); a.mg_nty = magic_of(wp.nty);
                     a.mg_d = magic_of(ly.dil); a.mg_d2 = magic_of(ly.dil2);
