@@ -100,7 +100,7 @@ __host__ __device__ constexpr int parts_pitch(int parts, int CB) { return (CB / 
 __host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
 __host__ __device__ constexpr int parts_items(int parts) { return parts == 1 ? 12 : 6; }                    // rounds, at most (they wait in registers)
 // steps of weights in registers: 512 cycles of a wave's instructions and more, a trip from L2
-__host__ __device__ constexpr int parts_ring(int parts, int tiles) { return parts == 3 ? (tiles > 1 ? 2 : 4) : (tiles > (parts == 2 ? 1 : 2) ? 4 : 8); }
+__host__ __device__ constexpr int parts_ring(int parts, int tiles) { return parts == 3 ? (tiles > 1 ? 2 : 4) : (parts == 2 || tiles > 2 ? 4 : 8); }
 
 // Numbers are split kPartsUp times as large, and sums of products are brought back by kPartsDown: bf16's last bit lies
 // at 2^-133, fp32's at 2^-149.
@@ -134,6 +134,7 @@ __device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2],
 // Steps between two additions of a tile's leading sums to its total (kernel below): whole filter rows of at most 16 taps, or whole chunks of
 // fewer taps until they are 8 steps.  A function of the filter alone.  `period`: steps after which the lengths repeat.
 constexpr int kHalfLeast = 512;   // fewest products of a sum that two fp16 parts are taken for
+__host__ __device__ inline bool half_filter(int k, int k2) { return k * k2 >= 4 && (k < 8 || k2 >= 4); }   // blocks of four steps at least
 struct HalfRun { int period, length; };
 __host__ __device__ inline HalfRun half_run(int k, int k2)
 {
@@ -407,6 +408,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             } else if constexpr (P == 2) {            // activations a whole step ahead
                 next_x();
                 fetch_x((s + 1) % XS, 1, soff); fetch_x((s + 1) % XS, 0, soff);
+                __builtin_amdgcn_sched_barrier(0);    // (else the reads sink to where they are used, and every step waits for them)
                 product(s, s % XS, 0, 1); product(s, s % XS, 1, 0); fetch_w(s, 1);
                 product(s, s % XS, 0, 0); fetch_w(s, 0);
                 if (--run_left == 0) add_run();
@@ -423,20 +425,29 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
 #pragma unroll
             for (int t = 0; t < XS; ++t)
                 if (phase % XS == t) { fetch_x(t, 1, 0); fetch_x(t, 0, 0); }
-            const int first = n < NS - phase ? n : NS - phase;
-#pragma unroll
-            for (int i = 0; i < NS; ++i)
-                if (phase <= i && i < phase + first) step(i);
-            int more = n - first;
-            phase = phase + first == NS ? 0 : phase + first;
+            // (A block has four steps at least, and nothing branches around a step: on every path into the loop as many loads follow a slot's.)
+            static_assert(NS == 4, "slots");
+            if (phase < 3) {
+                if (phase < 2) {
+                    if (phase < 1) step(0);
+                    step(1);
+                }
+                step(2);
+            }
+            step(3);
+            int more = n - (NS - phase);
             for (; more >= NS; more -= NS) {
 #pragma unroll
                 for (int i = 0; i < NS; ++i) step(i);
             }
-#pragma unroll
-            for (int i = 0; i < NS - 1; ++i)
-                if (i < more) step(i);
-            phase += more;
+            if (more > 0) {
+                step(0);
+                if (more > 1) {
+                    step(1);
+                    if (more > 2) step(2);
+                }
+            }
+            phase = more;
             return;
         }
         if constexpr (P == 3) {

@@ -1648,8 +1648,8 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
             // Two fp16 parts per number lose a last bit of one number in four; in a sum whose runs of leading products are added up (kernels_conv_parts.hpp)
             // that is less than what three parts' roundings come to from about 500 products on.
             auto half_floats = [&](int rpad, int pad) { return ((size_t)ly.k * ly.k2 * (rpad / 16) + mpcnn::parts_ahead(2)) * 2 * 2 * pad * 4; };
-            ly.fwd_half = !net->bf16 && ly.fwd_mfma && l > 0 && (long)ly.k * ly.k2 * ly.cin >= mpcnn::kHalfLeast;
-            ly.dgrad_half = !net->bf16 && ly.dgrad_mfma && (long)ly.k * ly.k2 * ly.cout >= mpcnn::kHalfLeast;
+            ly.fwd_half = !net->bf16 && ly.fwd_mfma && l > 0 && mpcnn::half_filter(ly.k, ly.k2) && (long)ly.k * ly.k2 * ly.cin >= mpcnn::kHalfLeast;
+            ly.dgrad_half = !net->bf16 && ly.dgrad_mfma && mpcnn::half_filter(ly.k, ly.k2) && (long)ly.k * ly.k2 * ly.cout >= mpcnn::kHalfLeast;
             if (ly.fwd_half) { ly.fwd_half_len = half_floats(ly.fwd_rpad, ly.fwd_ct.pad); ly.fwd_half_off = pack; pack += ly.fwd_half_len; }
             if (ly.dgrad_half) { ly.dgrad_half_len = half_floats(ly.dgrad_rpad, ly.dgrad_ct.pad); ly.dgrad_half_off = pack; pack += ly.dgrad_half_len; }
             net->halves = net->halves || ly.fwd_half || ly.dgrad_half;

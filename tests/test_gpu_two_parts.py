@@ -11,8 +11,8 @@ from test_gpu_conv_parts import close_layers
 pytestmark = pytest.mark.gpu
 C, FC = wl.C, wl.FC
 
-# filters and channels of the layer behind the first: sums of 512 products and a few more in both directions; runs of 8 chunks (1 x 1), two chunks, a
-# chunk, filter rows of a chunk (two, three, one) and, from 8 rows on, filter rows in blocks of fewer rows
+# filters and channels of the layer behind the first: sums of 512 products and a few more in both directions; three parts (1 x 1: blocks of fewer than four
+# steps), runs of two chunks, a chunk, filter rows of a chunk (two, three, one) and, from 8 rows on, filter rows in blocks of fewer rows
 SHAPES = [(1, 516, 520), (2, 128, 132), (3, 60, 64), (4, 32, 36), (5, 24, 40), (6, 16, 20), (7, 12, 16), (8, 8, 12), (11, 8, 8), (26, 8, 8)]
 
 
@@ -71,7 +71,7 @@ BOUND = 5 * np.sqrt(5408 / 3) * 2.0 ** -24
 def test_runs_of_every_length(k, c0, c1):
     args = case(k, c0, c1, 34)
     got, plan = gradient(*args)
-    assert plan.count("three parts per number or two of fp16") >= 2, plan
+    assert plan.count("three parts per number or two of fp16") >= (2 if k > 1 else 0), plan
     assert close_layers(got, gradient64(*args), args[0], args[1]) <= BOUND
 
 
