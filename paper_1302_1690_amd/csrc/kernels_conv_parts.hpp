@@ -39,44 +39,45 @@
 // bf16 storage.  One part, one product, one accumulator: same kernel.
 //
 // Tiling.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x
-// 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32, one or two with three parts (two accumulators each),
-// two or four with one.  A step contracts 16 channels of one tap: MO + MP operands of P parts each feed
-// P(P+1)/2 * MO * MP instructions.  With 1 x 2 tiles and three parts that is 9 KB for 12 instructions, from the vector cache (weights, the same
-// for all waves of the workgroup that share channels) and the LDS (activations), 8 and 16 bytes per cycle and wave.  With
-// one part it is 4 KB for 4 instructions (2 x 2) or 5 KB (1 x 4): 16 to 32 bytes per cycle and wave from LDS, 64 to 128 per compute unit, where it
-// delivers 108 to four waves and 170 to sixteen at best, conflicts not counted.
-// The input halo is brought in CB channels at a time, [position][16 channels][part] in LDS with a pitch
-// that spreads 16 successive positions of one halo row over all banks (a tile's 32 positions lie in several rows, and a row break jumps by (k2 - 1) positions:
-// counters read 10-60 % of the LDS cycles as conflicts), so that an operand is one 128-bit read at
-// an immediate offset from one address per position tile and step.
+// 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32, one or two with two and three parts (two accumulators each and, with two parts, a
+// total), two, four or eight with one.  A step contracts 16 channels of one tap: MO + MP operands of P parts each feed 6 (three parts), 3 or 1
+// instructions per tile.  Weights come through the vector cache, 1 KB per operand and wave, activations from LDS, 1 KB each.  What a product
+// costs in such bytes decides the rate of one part: counters show the vector cache taking 0.6 of an access per cycle with 2 x 2 tiles (0.5 KB of weights per instruction, every
+// wave its own) and waiting for L2 a third to a half of the time; 2 x 4 tiles take half of that (2 x 2048 x 2048, forward 1096, 1745, 1763, 3383 -> 954, 1541, 1519, 3103 us, data
+// gradient -, 1763, 1468, 2542 -> -, 1570, 1324, 2204) but need maps that give two workgroups of them to every compute unit.
+// The input halo is brought in CB channels at a time.
 //
-// Latency.  Workgroups are persistent and walk (tile, channel block) items; the next item's halo is
-// loaded into registers before the current one is multiplied and split into parts on its way to LDS after it.
+// Latency.  Workgroups are persistent and walk (tile, channel block) items.  Two and three parts: the next item's halo is
+// loaded into registers before the current one is multiplied and split into parts on its way to LDS after it, two workgroups share a compute unit,
+// so one's staging, barriers and stores lie under the other's instructions.  One part: the halo goes from memory to LDS without a stop in registers, once every wave has left
+// the last one, under the epilogue and under the other workgroups' instructions: without halo registers three workgroups of four tiles per wave share a
+// compute unit (3 x 501 x 389, 100 maps: forward 43, 57, 119 -> 32, 43, 101 us, data gradient 54, 55, 117 -> 44, 41, 90 with what else changed), or two of eight.
+// (64-byte pieces of a position per four lanes: with 16 bytes of 64 positions per instruction, which needs no change of places in LDS, the cache takes four times the accesses, and the
+// last layer's forward 3338 instead of 3040 us.)
 // Weights run through a ring of parts_ring steps that never drains: the pack is in step
 // order - chunks of 16 channels, the taps of each, whatever CB is - and its first steps follow its last once more, so that
 // no fetch looks at the end; behind a tile's last step the pointer goes back to its first.
 // One part: the LDS offsets of a block's steps come from a table in LDS, as counting taps took more scalar instructions than a step has issue slots for.
-// Two workgroups share a compute unit, so one's staging, barriers and stores lie under the other's
-// instructions.  A block costs two barriers and, as a wave's loads return in order, a wait of its weights behind the halo:
+// A block costs two barriers and, as a wave's loads return in order, a wait of its weights behind the halo:
 // where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels.  Where it is large, its halo would leave
 // a tile of few positions, or none: blocks are then 16 channels of kr filter rows, in step order as well.
 //
 // Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
-//   fp32, 1 x 1024 x 1024, three parts -> two: forward 485, 869, 707, 1281 -> 331, 574, 506, 925 (315, 351, 275, 199 TFLOP/s); data gradient 485, 886, 691, 1075 ->
-//     320, 581, 473, 785 (326, 346, 294, 234).  A loop of these operands alone sustains 342 on random data (1.03 PFLOP/s of instructions), 221 in three parts.
+//   fp32, 1 x 1024 x 1024, three parts -> two: forward 485, 869, 707, 1281 -> 317, 555, 481, 868 (328, 362, 289, 212 TFLOP/s); data gradient 485, 886, 691, 1075 ->
+//     306, 552, 446, 727 (341, 365, 312, 253).  A loop of these operands alone sustains 342 on random data (1.03 PFLOP/s of instructions), 221 in three parts; the
+//     clock under these launches is 1.9-2.1 GHz (busy counter over time; 2.4-2.6 under the pools), matrix pipes busy 34-58 %: power bounds the first two layers, the
+//     last one's waits for halo and stores the others.
 //   fp32 instruction -> three parts, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 -> 488, 891, 711, 1236 (214, 226, 196, 148 TFLOP/s);
 //     data gradient 1060, 1790, 1250, 1880 -> 485, 898, 684, 1070 (215, 224, 203, 171).  Matrix pipes busy 50-75 %.  One accumulator, up to four
 //     tiles per wave, no scaling against this, in turn on one machine: forward 447, 850, 646, 1088 -> 483, 879, 711, 1230, data gradient 488, 838, 621, 923 ->
 //     481, 894, 680, 1068.  The loop alone then sustained 240-260 on random data, 362 on zero weights with the same instructions: what a power limit would do.
-//   bf16, 2 x 2048 x 2048: forward 1156, 1982, 1845, 4009 (two kernels of one part before) -> 1100, 1737, 1726, 3078;
-//     data gradient 1021, 1898, 1501, 2580 -> 951, 1800, 1432, 2377.  Matrix pipes busy 28-46 %.  What the rest goes to, from an earlier form (steps' places
-//     counted, 1 x 4 tiles; 1131, 1798, 1817, 3357 whole): without the next halo's loads 861, 1379, 1377, 2578, without stores 996, 1633, 1550,
-//     2766, without tanh 1083, 1745, 1724, 3184, without the multiplications 595, 694, 1010, 2563.
-//   Slower than the kernels before: fp32 launches on one or two thousand positions with at most 16 channels (9 against 7), bf16 data gradients on
-//     maps of about 420 x 430 (53, 42, 61 against 47.5, 36, 50; the forwards gained as much).
+//   bf16, 2 x 2048 x 2048, 2 x 2 tiles with the halo through registers -> now: forward 1078, 1739, 1708, 3071 -> 902, 1502, 1518, 2999 (938, 1108, 773, 531 TFLOP/s); data gradient
+//     953, 1790, 1443, 2387 -> 884, 1480, 1248, 2011 (958, 1124, 940, 791).  What the last layer's forward goes to (one image, 1814): without stores 1249, without the
+//     next halos 1255, without tanh 1807, without fetching weights 1616, without the multiplications 1390, without the first three 1029.
+//   Slower than the fp32 instruction's kernel: fp32 launches on one or two thousand positions with at most 16 channels (9 against 7).
 //   The bias from LDS instead of memory (its loads queued behind the halo's) took the bf16 forward from 8.8 to 7.9 ms.
-// Tried and dropped: 2 x 4 tiles per wave with one part (registers spill; 3.4 ms for the last layer's data gradient), three
-// workgroups per compute unit (the same, 3.9 ms for its forward).
+// Tried and dropped: planes of 8 channels in LDS for two and three parts (no row break conflicts where tiles are 32 wide; even), tiles walked residue column first and in
+// bands per XCD (so that neighbours in memory are worked on together; even), two and three parts' stores by 64 bytes per position (even).
 //
 // Summation order is the step order for every output element, whatever the tiling: equal inputs
 // give bit-equal outputs (exact pooling ties stay exact) and a position's value does not depend on
@@ -96,9 +97,20 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // Geometry shared with the host's plan.
 constexpr int kPartsThreads = 256;   // four waves
-__host__ __device__ constexpr int parts_pitch(int parts, int CB) { return (CB / 16) * parts * 32 + 16; }   // LDS bytes of a halo position
 __host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
-__host__ __device__ constexpr int parts_items(int parts) { return parts == 1 ? 12 : 6; }                    // rounds, at most (they wait in registers)
+__host__ __device__ constexpr int parts_wgs(int parts, int tiles) { return parts == 1 && tiles <= 4 ? 3 : 2; }   // workgroups that share a compute unit
+__host__ __device__ constexpr int parts_items(int parts, int tiles)                                         // rounds, at most: what waits in registers; one part: fits in LDS
+{
+    return parts > 1 ? 6 : parts_wgs(1, tiles) == 3 ? 12 : 18;
+}
+// The halo in LDS.  Two and three parts: [position][16 channels][part].  One part: groups of 32 channels (16 where a block has no more), a position's octets
+// of a group together - 64 (32) bytes, as the memory holds them.  Octet j of position p sits in place j ^ (p / 4) % 4 (j ^ (p / 8) % 2): 16
+// successive positions meet no bank twice.
+__host__ __device__ constexpr int parts_group(int CB) { return CB < 32 ? 2 : 4; }                           // octets of a group
+__host__ __device__ constexpr int parts_pitch(int parts, int CB)                                            // bytes of a position, in all groups together
+{
+    return parts == 1 ? CB * 2 : (CB / 16) * parts * 32 + 16;
+}
 // steps of weights in registers: 512 cycles of a wave's instructions and more, a trip from L2
 __host__ __device__ constexpr int parts_ring(int parts, int tiles) { return parts == 3 ? (tiles > 1 ? 2 : 4) : (parts == 2 || tiles > 2 ? 4 : 8); }
 
@@ -181,8 +193,8 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     constexpr bool kF32 = sizeof(T) == 4;
     static_assert(kF32 ? P == 2 || P == 3 : P == 1, "parts of the storage type");
     constexpr int QN = CB / 8, NSUB = CB / 16, NS = parts_ring(P, MO * MP);
-    constexpr int PITCH = parts_pitch(P, CB), RP = parts_round(CB), SI = parts_items(P);
-    constexpr int ITW = kF32 ? 2 : 1;               // 128-bit loads per staged item (8 channels of a position)
+    constexpr int RP = parts_round(CB), SI = parts_items(P, MO * MP), PITCH = parts_pitch(P, CB);
+    constexpr int GO = parts_group(CB), POSB = 16 * GO;   // one part: octets of a group, bytes of a position in it
     constexpr unsigned kNone = 0x80000000u;           // byte offset no buffer reaches: the load returns zeros
     const T* in_t = static_cast<const T*>(a.in);
     const T* act_t = static_cast<const T*>(a.act);
@@ -198,6 +210,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
 
     const int hw = a.Tx + a.k2 - 1, hh = a.Ty + a.kr - 1;
     const int npos = hh * hw;                         // <= SI * RP
+    const int GB = (npos + RP - 1) / RP * (RP * POSB);   // one part: bytes of a group (whole kilobytes, as `swapped` wants)
     const int oc0 = 32 * ((blockIdx.y * WO + wo) * MO);   // first channel of this wave's tiles
     const bool live = oc0 < a.Co;                     // uniform for the wave
 
@@ -209,8 +222,8 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     // ---- staging: thread tid brings 8 channels (octet q of the block) of halo positions tid / QN + RP*u
     const int q = tid % QN, pos0 = tid / QN;
     char* const st_dst = ldsb + pos0 * PITCH + (q >> 1) * (P * 32) + (q & 1) * 16;
-    unsigned voff[SI];                                // byte offsets from the halo's first element (kNone: outside, or no such position)
-    u32x4 pre[SI][ITW];
+    unsigned voff[P == 1 ? 1 : SI];                   // byte offsets from the halo's first element (kNone: outside, or no such position)
+    u32x4 pre[P == 1 ? 1 : SI][2];
 
     struct Tile { int b, ry, rx, ty0, tx0; };
     auto decode = [&](int t) {
@@ -255,14 +268,6 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             if constexpr (kF32) {
                 pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
                 pre[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c + 4 < a.Cr ? voff[u] + 16u : kNone), soff, 0));
-            } else {
-                // (two halves: with a channel count that is 4 mod 8 the item is only 8-byte aligned, its second half another position's)
-                if (a.Cr & 7) {
-                    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
-                    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)(c + 4 < a.Cr ? voff[u] + 8u : kNone), soff, 0));
-                    pre[u][0] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
-                } else
-                    pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(c < a.Cr ? voff[u] : kNone), soff, 0));
             }
         }
     };
@@ -280,9 +285,46 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 else split_parts(x, p);
 #pragma unroll
                 for (int i = 0; i < P; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
-            } else
-                *reinterpret_cast<u32x4*>(dst) = pre[u][0];
+            }
         }
+    };
+    // One part needs no conversion: the halo goes from memory to LDS without a stop in registers, 1 KB per instruction - the octets of a group of
+    // 16 (32) positions, which lie together in memory too - the waves in turn.  What lies outside comes as zeros.
+    constexpr int LP = 64 / GO;                       // positions of an instruction
+    auto swapped = [](int at) { return at ^ (at >> 4 & 16 * (GO - 1)); };   // place of an octet, from position * POSB + 16 * octet
+    auto bring = [&](const Tile& g, bool any, int row0, int cb) {
+        typedef __attribute__((address_space(3))) void* lds_ptr;
+        const unsigned row_b = (unsigned)(a.d * a.Wi * a.Cr) * (unsigned)sizeof(T), col_b = (unsigned)(a.d2 * a.Cr) * (unsigned)sizeof(T);
+        const int iy0 = (g.ty0 + a.origin + row0) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T*>(in_t + (((long)g.b * a.Hi + iy0) * a.Wi + ix0) * a.Cr), 0, 0x7fffffff, 0x00020000);
+        const int mine = lane / GO;
+        const unsigned oct = (unsigned)(swapped(mine * POSB + lane % GO * 16) >> 4) % GO;   // (LP positions on, an octet's place is the same)
+        for (int at = LP * wave; at < npos; at += 4 * LP) {
+            const unsigned pos = at + mine;
+            const unsigned ha = parts_div(pos, a.mg_hw, hw), hb = pos - ha * hw;
+            const int iy = iy0 + (int)ha * a.d, ix = ix0 + (int)hb * a.d2;
+            const bool ok = any && pos < (unsigned)npos && (unsigned)iy < (unsigned)a.Hi && (unsigned)ix < (unsigned)a.Wi;
+            const unsigned off = ha * row_b + hb * col_b + 16 * oct;
+#pragma unroll
+            for (int j = 0; j < QN / GO; ++j) {
+                const int c = CB * cb + 8 * GO * j;   // the group's first channel
+                if (c >= a.CrPad) break;              // (no step reads it)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr)(ldsb + j * GB + at * POSB), 16,
+                                                         (int)(ok && c + 8 * (int)oct < a.Cr ? off : kNone), c * (int)sizeof(T), 0, 0);
+            }
+        }
+    };
+    // The halo is there; with a channel count that is 4 mod 8 the last octet's second half is another position's: zeros
+    // (behind an epilogue of whole pieces: without waiting for its stores, which a wave issues after the halo)
+    auto brought = [&](int cb, bool stored) {
+        constexpr int kStores = 2 * MO * MP;
+        if (BACK && stored) __builtin_amdgcn_s_waitcnt(0x0f70 | (kStores & 15) | kStores >> 4 << 14);   // vmcnt(kStores)
+        else __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
+        const int oct = (a.Cr >> 3) - cb * QN;
+        if ((a.Cr & 7) && oct >= 0 && oct < QN)
+            for (int at = LP * wave; at < npos; at += 4 * LP)
+                if (lane < LP) *reinterpret_cast<u32x2*>(ldsb + oct / GO * GB + swapped((at + lane) * POSB + oct % GO * 16) + 8) = (u32x2){0, 0};
     };
 
     // ---- the bias of the workgroup's channels, behind the halo's whole rounds
@@ -299,7 +341,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         const int taps = a.kr * a.k2, all = taps * ((CB < a.CrPad ? CB : a.CrPad) / 16);
         for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kPartsThreads) {
             const int sub = i / taps, r = i - sub * taps, ta = r / a.k2, tb = r - ta * a.k2;
-            table[i] = i < all ? (ta * hw + tb) * PITCH + sub * 32 : 0;
+            table[i] = i < all ? (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16 : 0;
         }
     }
 
@@ -310,7 +352,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         const unsigned m = 32 * (wp * MP + p) + lt;
         unsigned ty = parts_div(m, a.mg_tx, a.Tx), tx = m - ty * a.Tx;
         if (ty >= (unsigned)a.Ty) { ty = 0; tx = 0; }   // padding position: any address inside
-        lbase[p] = (int)(ty * hw + tx) * PITCH + lg * 16;
+        lbase[p] = P == 1 ? (int)(ty * hw + tx) * POSB + lg * 16 : (int)(ty * hw + tx) * PITCH + lg * 16;
     }
 
     // ---- weights: [16-channel chunk][tap][part][lane group][CoPad][8], the step's place a scalar pointer
@@ -322,9 +364,9 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     int head[P == 1 ? parts_sets(P, MO * MP) - 1 + kPartsTabAhead : 1];   // the table's first entries
     v16f acc[MO][MP], low[kF32 ? MO : 1][kF32 ? MP : 1];   // low: the smaller products
     v16f tot[P == 2 ? MO : 1][P == 2 ? MP : 1];       // two parts: the runs of leading products before the present one
-    int phase = 0;                                    // two parts: the ring's slot of the next step,
+    int phase = 0;                                    // the ring's slot of the next step (multiply, phased); two parts:
     const HalfRun run = half_run(a.k, a.k2);
-    int run_left = 0, period_left = 0;                // and the steps left of a run and of a period
+    int run_left = 0, period_left = 0;                // the steps left of a run and of a period
     v4f w[NS][MO * P];                                // the ring
     auto fetch_w = [&](int s, int i) {
         if constexpr (P == 1) {
@@ -356,6 +398,8 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     };
 
     // one tile's share of one channel block: its 16-channel chunks one after the other, the taps of each
+    // Phased (two parts; eight tiles per wave): the ring is entered at the slot where the last block left it, and no slot changes its place.
+    constexpr bool kPhased = P == 2 || MO * MP > 4;
     auto multiply = [&](int rows, int nsub) {
         const int taps = rows * a.k2, n = taps * nsub;   // steps of this block
         constexpr int XS = parts_sets(P, MO * MP), TS = kPartsTabAhead;
@@ -363,7 +407,9 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         v4f x[XS][P][MP];
         auto fetch_x = [&](int s, int i, int off) {
 #pragma unroll
-            for (int p = 0; p < MP; ++p) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + off + 32 * i);
+            for (int p = 0; p < MP; ++p)
+                if constexpr (P == 1) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + swapped(lbase[p] + off));
+                else x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + off + 32 * i);
         };
         // two and three parts: the next step's place, counted (past the last one: the first one's, read for nothing)
         int left = n, ta = 0, tb = 0, soff = 0;
@@ -419,12 +465,16 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             }
             next_w();
         };
-        if constexpr (P == 2) {
-            // The ring is entered at the slot where the last block left it, so that no slot changes its place: the rest of that turn, whole
-            // turns, and a part of one.
+        if constexpr (kPhased) {
+            // the rest of a turn, whole turns, and a part of one
 #pragma unroll
             for (int t = 0; t < XS; ++t)
-                if (phase % XS == t) { fetch_x(t, 1, 0); fetch_x(t, 0, 0); }
+                if (phase % XS == t) {
+                    static_assert(XS == 2 && TS == 2, "the other set, the other place");
+                    if constexpr (P == 2) { fetch_x(t, 1, 0); fetch_x(t, 0, 0); }
+                    else { fetch_x(t, 0, head[0]); at[t] = head[1]; at[t ^ 1] = head[2]; }
+                }
+            tv -= phase;
             // (A block has four steps at least, and nothing branches around a step: on every path into the loop as many loads follow a slot's.)
             static_assert(NS == 4, "slots");
             if (phase < 3) {
@@ -437,9 +487,11 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             step(3);
             int more = n - (NS - phase);
             for (; more >= NS; more -= NS) {
+                tv += NS;
 #pragma unroll
                 for (int i = 0; i < NS; ++i) step(i);
             }
+            tv += NS;
             if (more > 0) {
                 step(0);
                 if (more > 1) {
@@ -554,6 +606,113 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 }
         }
     };
+    // The same with bf16 storage, where an instruction would write 16 bytes of each of 32 positions, and the caches take such pieces one by one.  Lanes
+    // change places with each other first, so that four hold 64 successive bytes of a position and an instruction writes 16 positions:
+    // part h of a tile is positions 16h .. 16h + 15, a lane's piece 8 channels of position 16h + lane % 16.  (2 x 2048 x 2048, forward: 890, 1477, 1496, 3022 -> 873, 1473,
+    // 1413, 2954 us; fp32, 32 bytes of 32 positions: no gain.)
+    // The bias waits in LDS; what the data gradient reads (the outputs whose slope multiplies it) is fetched a part ahead, so
+    // that its trip lies under the part before.
+    auto epilogue_pieces = [&](const Tile& g, int fh, int fw) {
+      if constexpr (!kF32) {
+        constexpr int W = 8;                          // channels of a piece
+        typedef T piece __attribute__((ext_vector_type(W)));
+        typedef T quad __attribute__((ext_vector_type(4)));
+        const bool vec = (a.Co & 3) == 0, whole = a.Co % W == 0;   // uniform
+        const int side = fresh(lane);
+        const int lch = 16 * (side >> 4 & 1) + 8 * (side >> 5);   // the lane's first channel
+        const bool reads = BACK && curved;            // uniform
+        // bf16 data gradients issue their stores on every path, and brought waits for the halo without them (2 x 2048 x 2048, us: 2055, 1263, 1481, 881 ->
+        // 2041, 1218, 1449, 870; forwards, whose squashing function then runs for channels that do not exist too: 873, 1473, 1413, 2954 -> 896, 1478, 1479, 3073)
+        constexpr bool kCounted = BACK;
+        long pos_off[2];
+        bool pos_ok[2];
+        piece y[2][MO];
+        unsigned near[2];                             // bytes from the tile's first position
+        auto place = [&](int i) {                     // part i & 1 of position tile i / 2
+            const unsigned m = 32 * (wp * MP + (i >> 1)) + 16 * (i & 1) + (side & 15);
+            const int ty = (int)parts_div(m, a.mg_tx, a.Tx), tx = (int)m - ty * a.Tx;
+            const int fy = g.ty0 + ty, fx = g.tx0 + tx;
+            pos_ok[i & 1] = ty < a.Ty && fy < fh && fx < fw;
+            pos_off[i & 1] = (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co;
+            near[i & 1] = (unsigned)(ty * a.d * a.Wo + tx * a.d2) * (unsigned)a.Co * (unsigned)sizeof(T);
+            if (reads)
+#pragma unroll
+                for (int o = 0; o < MO; ++o) {
+                    const int oc = oc0 + 32 * o + lch;
+                    piece& v = y[i & 1][o];
+#pragma unroll
+                    for (int z = 0; z < W; ++z) v[z] = 0;
+                    if (!pos_ok[i & 1] || oc >= a.Co) continue;
+                    const T* const src = act_t + pos_off[i & 1] + oc;
+                    if (whole) v = *reinterpret_cast<const piece*>(src);
+                    else
+#pragma unroll
+                        for (int q = 0; q < W; q += 4) {
+                            if (oc + q >= a.Co) continue;
+                            if (vec) {
+                                const quad f = *reinterpret_cast<const quad*>(src + q);
+#pragma unroll
+                                for (int z = 0; z < 4; ++z) v[q + z] = f[z];
+                            } else
+                                for (int z = 0; z < 4; ++z) if (oc + q + z < a.Co) v[q + z] = src[q + z];
+                        }
+                }
+        };
+        auto swap = [](auto op, v16f& t, int i, int j) {
+            const auto r = op(__builtin_bit_cast(unsigned, (float)t[i]), __builtin_bit_cast(unsigned, (float)t[j]));
+            t[i] = __builtin_bit_cast(float, (unsigned)r[0]); t[j] = __builtin_bit_cast(float, (unsigned)r[1]);
+        };
+        auto half = [](unsigned u, unsigned v) { return __builtin_amdgcn_permlane32_swap(u, v, false, false); };   // lanes 32.. of u with 0.. of v
+        auto row = [](unsigned u, unsigned v) { return __builtin_amdgcn_permlane16_swap(u, v, false, false); };    // odd rows of u with even rows of v
+        const __amdgpu_buffer_rsrc_t out_r = __builtin_amdgcn_make_buffer_rsrc(
+            out_t + (((long)g.b * a.Ho + (g.ty0 * a.d + g.ry)) * a.Wo + (g.tx0 * a.d2 + g.rx)) * a.Co, 0, 0x7fffffff, 0x00020000);
+        place(0);
+#pragma unroll
+        for (int i = 0; i < 2 * MP; ++i) {
+            if (i + 1 < 2 * MP) place(i + 1);
+            const int p = i >> 1, h = i & 1;
+            if (h == 0)
+#pragma unroll
+                for (int o = 0; o < MO; ++o) {
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) { swap(half, acc[o][p], z, 4 + z); swap(half, acc[o][p], 8 + z, 12 + z); }
+#pragma unroll
+                    for (int z = 0; z < 8; ++z) swap(row, acc[o][p], z, z + 8);
+                }
+#pragma unroll
+            for (int o = 0; o < MO; ++o) {
+                const int oc = oc0 + 32 * o + lch;
+                const bool exists = pos_ok[h] && oc < a.Co;
+                if (!kCounted && !exists) continue;
+                float r[W];
+                const int own = fresh(oc - 32 * (int)blockIdx.y * WO * MO);
+#pragma unroll
+                for (int z = 0; z < W; ++z) {
+                    float yv;
+                    if constexpr (BACK) yv = (float)y[h][o][z];
+                    else yv = bias_l[own + z];
+                    r[z] = finish(acc[o][p][8 * h + z], 1.f, yv);
+                }
+                piece v;
+#pragma unroll
+                for (int z = 0; z < W; ++z) v[z] = (T)r[z];
+                T* const dst = out_t + pos_off[h] + oc;
+                if (kCounted && whole) {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out_r, (int)(exists ? near[h] + 2u * (unsigned)oc : kNone), 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);   // (else the pieces are worked on side by side, out of registers)
+                } else if (whole)
+                    *reinterpret_cast<piece*>(dst) = v;
+                else if (exists)
+#pragma unroll
+                    for (int q = 0; q < W; q += 4) {
+                        if (oc + q >= a.Co) continue;
+                        if (vec) store4(dst + q, (v4f){r[q], r[q + 1], r[q + 2], r[q + 3]});
+                        else for (int z = 0; z < 4; ++z) if (oc + q + z < a.Co) store1(dst + q + z, r[q + z]);
+                    }
+            }
+        }
+      }
+    };
     // A sum that is not finite came from infinities, NaN or numbers without parts (or is one that overflows): once more, with
     // fp32 multiply-adds over the taps and channels in step order, four channels of one position tile at a time (more would take
     // registers from the loop above).  Bound by the trips of its loads, about the tile's own time for every four channels that need it;
@@ -627,15 +786,16 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     int t = blockIdx.x;
     if (t >= a.tiles_total) return;                   // (uniform; the host launches no such workgroup)
     Tile cur = decode(t);
-    aim(cur, true, 0);
-    issue(0);
+    if constexpr (P == 1) bring(cur, true, 0, 0);
+    else { aim(cur, true, 0); issue(0); }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {                    // the ring's first steps
 #pragma unroll
         for (int i = 0; i < P; ++i) fetch_w(s, i);
         next_w();
     }
-    to_lds();
+    if constexpr (P == 1) brought(0, false);
+    else to_lds();
     __syncthreads();
     if constexpr (P == 1)
 #pragma unroll
@@ -663,13 +823,17 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             if (last) {
                 const int tn = t + gridDim.x;
                 nxt = decode(tn < a.tiles_total ? tn : t);
-                aim(nxt, tn < a.tiles_total, 0);
+                if constexpr (P != 1) aim(nxt, tn < a.tiles_total, 0);
                 cn = 0;
-            } else if (a.kr < a.k)
+            } else if (P != 1 && a.kr < a.k)
                 aim(cur, true, rn);
-            issue(cn);
+            if constexpr (P != 1) issue(cn);
             const int chunks = (a.CrPad - cb * CB) / 16, rows = a.k - row0;
             if (live) multiply(rows < a.kr ? rows : a.kr, chunks < NSUB ? chunks : NSUB);
+            if constexpr (P == 1) {                   // one part: under the epilogue, and under the other workgroups' instructions
+                __syncthreads();                      // every wave has left this block's halo
+                bring(last ? nxt : cur, !last || t + (int)gridDim.x < a.tiles_total, rn, cn);
+            }
             if (last && live) {
                 const int fh = cur.ry < a.Ho ? (int)parts_div(a.Ho - cur.ry + a.d - 1, a.mg_d, a.d) : 0;   // extent of this residue class
                 const int fw = cur.rx < a.Wo ? (int)parts_div(a.Wo - cur.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
@@ -692,7 +856,8 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                             for (int r = 0; r < 16; ++r) z = fmaf(acc[o][p][r], 0.f, z);
                     odd = __any(z != z);
                 }
-                epilogue(cur, fh, fw);
+                if constexpr (kF32) epilogue(cur, fh, fw);
+                else epilogue_pieces(cur, fh, fw);
                 if constexpr (P == 3) {
                     if (odd) {
                         unsigned bad[MO][MP];
@@ -708,8 +873,14 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                     }
                 }
             }
-            __syncthreads();   // every wave has left this block's halo
-            to_lds();
+            if constexpr (P == 1) {
+                int stored = BACK && last && live && (a.Co & 7) == 0;
+                if constexpr (BACK) asm volatile("" : "+s"(stored));   // (else the paths with and without an epilogue are compiled apart, and spill)
+                brought(cn, stored != 0);
+            } else {
+                __syncthreads();                      // every wave has left this block's halo
+                to_lds();
+            }
             __syncthreads();
             cb = cn; row0 = rn;
         } while (!last);
@@ -731,7 +902,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
 
 // fp32 storage: in two parts where everything is known to suit them
 template <typename T, bool BACK, int CB, int WO, int WP, int MO, int MP>
-__global__ __launch_bounds__(kPartsThreads, 2) void conv_parts_kernel(ConvArgs a)
+__global__ __launch_bounds__(kPartsThreads, parts_wgs(sizeof(T) == 4 ? 3 : 1, MO * MP)) void conv_parts_kernel(ConvArgs a)
 {
     if constexpr (sizeof(T) == 4) {
         unsigned peak = kNoPeak;

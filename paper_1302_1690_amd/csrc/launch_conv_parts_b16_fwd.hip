@@ -12,6 +12,7 @@ bool launch_conv_parts_b16_fwd(const ConvArgs& a, const PartsInstance& in, dim3 
         return true;                                                                                   \
     }
     MPCNN_PARTS1(CASE)
+    MPCNN_PARTS1_WIDE(CASE)
 #undef CASE
     return false;
 }
@@ -24,6 +25,7 @@ hipError_t conv_parts_attrs_b16_fwd()
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_parts_kernel<bf16, false, cb, wo, wp, mo, mp>),   \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     MPCNN_PARTS1(ATTR)
+    MPCNN_PARTS1_WIDE(ATTR)
 #undef ATTR
     return e;
 }

@@ -24,9 +24,11 @@ struct PartsInstance { int CB, WO, WP, MO, MP; };
     X(32, 4, 1, 1, 2) X(32, 4, 1, 1, 4) X(32, 2, 2, 2, 2)                                                               \
     X(64, 1, 4, 1, 2) X(64, 2, 2, 1, 2) X(64, 1, 4, 2, 2) X(64, 4, 1, 1, 2) X(64, 4, 1, 1, 4) X(64, 2, 2, 2, 2)          \
     X(128, 2, 2, 1, 2) X(128, 4, 1, 1, 2) X(128, 4, 1, 1, 4) X(128, 2, 2, 2, 2)
+// bf16 storage, eight tiles per wave: large maps (two workgroups per compute unit instead of three; never by a tiling hint)
+#define MPCNN_PARTS1_WIDE(X) X(32, 1, 4, 2, 4) X(64, 1, 4, 2, 4) X(32, 2, 2, 2, 4) X(64, 2, 2, 2, 4) X(128, 2, 2, 2, 4)
 #define MPCNN_PARTS_ROW(cb, wo, wp, mo, mp) {cb, wo, wp, mo, mp},
 constexpr PartsInstance kParts3[] = {MPCNN_PARTS3(MPCNN_PARTS_ROW)};
-constexpr PartsInstance kParts1[] = {MPCNN_PARTS1(MPCNN_PARTS_ROW)};
+constexpr PartsInstance kParts1[] = {MPCNN_PARTS1(MPCNN_PARTS_ROW) MPCNN_PARTS1_WIDE(MPCNN_PARTS_ROW)};
 #undef MPCNN_PARTS_ROW
 bool launch_conv_parts_f32_fwd(const ConvArgs& a, const PartsInstance& in, dim3 grid, size_t lds, hipStream_t st);
 bool launch_conv_parts_f32_back(const ConvArgs& a, const PartsInstance& in, dim3 grid, size_t lds, hipStream_t st);

@@ -291,16 +291,18 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
     for (int li = 0; li < n_list; ++li) {
         const mpcnn::PartsInstance& in = list[li];
         const int CB = in.CB, RP = mpcnn::parts_round(CB), nblk = ceil_div(rpad, CB);
-        const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);
-        const int PT = in.WP * in.MP, per_wave = in.MO * in.MP;
+        const int PT = in.WP * in.MP, per_wave = in.MO * in.MP, resident = mpcnn::parts_wgs(P, per_wave);
+        const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);   // (two parts take less)
         if (in.WO * in.MO != ct.OT || (CB > 16 && rpad <= CB / 2)) continue;
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
-        if (in.MO == 2 && ceil_div(co, 32) % 2) continue;
+        if (in.MO == 2 && per_wave <= 4 && ceil_div(co, 32) % 2) continue;
+        if (per_wave > 4 && (hint_pt || hint_mp || !mpcnn::half_filter(k, k2))) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
-        // Time per matrix instruction against the best instance's.  One part: with four tiles 2 x 2 are ahead of 1 x 4 (2 x 600 x 640, deep net: 110, 169,
-        // 152 us against 117, 182, 159; even on 2 x 2048 x 2048), with two tiles 1.17 to 1.3 times as long on large maps; three parts: two tiles
+        // Time per matrix instruction against four tiles' per wave.  One part: 2 x 4 tiles take 0.86-0.88 of the time (2 x 2048 x 2048, us, 2 x 2 against 2 x 4: forward 1096,
+        // 1745, 1763, 3383 against 954, 1541, 1519, 3103; on 3 x 501 x 389 and smaller, where they are two rounds and less, even: 103 against 100.5), 2 x 2 are ahead of 1 x 4
+        // (2 x 600 x 640, deep net: 110, 169, 152 us against 117, 182, 159), two tiles take 1.17 to 1.3 times as long on large maps; three parts: two tiles
         // against one.  A workgroup alone on its compute unit, its waits in the open, takes 1.4 times as long with one part.
-        const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave >= 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
+        const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave > 4 ? 0.88 : per_wave == 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
         const double alone = P == 3 ? 1.15 : 1.4;
         const double t_mul = (double)steps * mults * ct.OT * PT * 8.0 * eff;
         // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640 positions (fp32)
@@ -311,9 +313,10 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
             if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
             const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
             const size_t beside = (32 * ct.OT + mpcnn::parts_table(P, CB, rpad, kr * k2)) * sizeof(float);   // the bias, the steps' places
-            if (beside + RP * pitch > (size_t)80 * 1024) continue;
-            const int lds_pos = (int)(((size_t)80 * 1024 - beside) / (RP * pitch)) * RP;
-            const int max_pos = std::min(lds_pos, mpcnn::parts_items(P) * RP);       // positions of the halo
+            const size_t room_lds = (size_t)160 * 1024 / resident;
+            if (beside + RP * pitch > room_lds) continue;
+            const int lds_pos = (int)((room_lds - beside) / (RP * pitch)) * RP;
+            const int max_pos = std::min(lds_pos, mpcnn::parts_items(P, per_wave) * RP);   // positions of the halo
             // (tiles that share a residue class's rows, and its columns, as evenly as their number allows; of those with ty rows
             // the widest that fits)
             int last_ty = 0;
@@ -328,13 +331,14 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                 const size_t lds = ceil_div(npos, RP) * RP * pitch + beside;   // the halo in whole rounds
                 // (byte offsets inside a tile's halo are 31 bits)
                 if (((size_t)(ty + kr - 1) * d * in_c + (size_t)(tx + k2 - 1) * d2) * cr * es >= (1ull << 31)) continue;
+                if (P == 1 && ((size_t)ty * d * out_c + (size_t)tx * d2) * co * es >= (1ull << 31)) continue;
                 const long tiles = (long)B * d * d2 * nty * ntx;
                 if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
-                const long wgs = std::min<long>(tiles, std::max(1, 2 * kNumCU / ct.split));
+                const long wgs = std::min<long>(tiles, std::max(1, resident * kNumCU / ct.split));
                 const double per_cu = std::ceil((double)tiles * ct.split / kNumCU);
                 const double t_rest = (double)nkr * npos * cr * es / 10 + 2500.0 * nblk * nkr + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
                 // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
-                // the pitch keeps only successive positions on different LDS banks)
+                // only successive positions are sure to lie on different LDS banks)
                 const double cost = per_cu * ((per_cu < 2 ? alone : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
                 if (!best.ok || cost < best_cost) {
                     best.PT = PT; best.Ty = ty; best.Tx = tx; best.kr = kr;

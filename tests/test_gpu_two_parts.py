@@ -1,12 +1,16 @@
 """fp32 convolutions and weight gradients in two fp16 parts per number (csrc/ranges.hpp, csrc/kernels_conv_parts.hpp, csrc/kernels_wgrad_parts.hpp):
-every length of the runs in which leading products are summed, and numbers that two parts do not suit, against 64-bit sums."""
+every length of the runs in which leading products are summed, and numbers that two parts do not suit, against 64-bit sums.  bf16 convolutions of eight tiles
+per wave against those of fewer."""
+import os
+import re
+
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 from paper_1302_1690_amd import mpcnn, workloads as wl
-from test_gpu_conv_parts import close_layers
+from test_gpu_conv_parts import close_layers, reached
 
 pytestmark = pytest.mark.gpu
 C, FC = wl.C, wl.FC
@@ -107,3 +111,44 @@ def test_deltas_of_very_different_sizes():
         net.close()
     assert np.isfinite(got[0]).all()
     assert close_layers(got[1], got[0], layers, patch) <= BOUND
+
+
+# bf16 storage, eight tiles per wave (only where maps are large, never by a tiling hint): nets whose layers reach every such instance in both directions
+WIDE_MAPS = [((C, 64, 3), (C, 64, 3), (C, 128, 3), (C, 64, 3)), ((C, 32, 3), (C, 128, 5), (C, 32, 5)), ((C, 64, 3), (C, 64, 5), (C, 64, 5)),
+             ((C, 128, 3), (C, 128, 2), (C, 200, 2), (C, 128, 2))]
+
+
+def test_eight_tiles_per_wave_give_the_same_bits():
+    """Against narrower tiles (a hint), which are held against the oracle: every sum is taken in the same order.  Both sides of a
+    ragged map, channel counts that leave a tile empty (200 of 256) included."""
+    wide, got = set(), set()
+    text = open(os.path.join(os.path.dirname(mpcnn.__file__), "csrc", "launchers.hpp")).read()
+    for f in re.findall(r"X\((\d+), (\d+), (\d+), (\d+), (\d+)\)", text[text.index("#define MPCNN_PARTS1_WIDE("):].split("#define", 2)[1]):
+        wide.add(tuple(int(v) for v in f))
+    assert wide
+    for convs in WIDE_MAPS:
+        layers = convs + ((FC, 8, 0), (FC, 2, 0))
+        patch = sum(k - 1 for _, _, k in convs) + 2
+        H, W = patch + 840, patch + 930
+        net = mpcnn.Net(layers, 1, patch, mpcnn.BF16)
+        rng = np.random.default_rng(patch)
+        params, ci = [], 1
+        for kind, m, k in layers:
+            f = k if kind == C else (2 if m == 8 else 1)
+            params.append(rng.uniform(-1, 1, m * ci * f * f + m) * 1.5 / np.sqrt(ci * f * f))
+            ci = m
+        net.set_params(np.concatenate(params).astype(np.float32))
+        image = torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda()
+        labels = torch.from_numpy(rng.integers(0, 2, (1, H, W)).astype(np.int32)).cuda()
+        out = []
+        for hint in ((0, 0), (4, 2)):
+            net.set_conv_tiling(*hint)
+            here = reached(net.plan_describe(1, H, W, True)) if hint == (0, 0) else set()
+            got |= {r for r in here if r[1] in wide}
+            probs = torch.empty((1, 2, H - patch + 1, W - patch + 1), device="cuda")
+            net.seg_backward(image, labels, probs=probs)
+            out.append((probs.cpu().numpy(), net.get_grads()))
+        net.close()
+        assert np.isfinite(out[0][1]).all() and np.any(out[0][1])
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]), convs
+    assert got == {(d, i) for d in ("forward", "data gradient") for i in wide}, got
