@@ -141,7 +141,12 @@ __global__ __launch_bounds__(512, 1) void wgrad_tr_kernel(WgradArgs a)
         const int dq_shift = 3 + (wn >> 1);             // 8 wn items of output channels per position
         const int h_items = hh * hwp * cq;
         const int d_items = (4 * TxP) << dq_shift;
-        const bool vec_dy = (a.Co & 7) == 0;
+        // Deltas come in items of 8 channels where their count is a multiple of 4 as well (64-bit aligned then): a last item of 4
+        // channels starts 4 earlier and its halves change places.  Channel by channel (what other counts still take) the loads of 100
+        // channels were the layer's time: 3 x 501 x 389, 64 -> 100, 3 x 3, 232 -> 114 us (477 TFLOP/s); 64 -> 100 on 600 x 611 145 -> 68; 32 -> 60, 5 x 5, 700 x 711 164 -> 65.
+        const bool vec_dy = (a.Co & 3) == 0;
+        const int dq = ltid & ((1 << dq_shift) - 1);    // this thread's item of every position (256 is a multiple of their number)
+        const bool half_item = vec_dy && 64 * (int)blockIdx.z * wn + 8 * dq + 8 > a.Co;
         // items decoded once: they are the same for every tile
         unsigned h_yx[HL];   // (halo row * d) << 16 | halo col * d
         int h_dst[HL];       // byte offset in a buffer, -1 = none
@@ -171,7 +176,7 @@ __global__ __launch_bounds__(512, 1) void wgrad_tr_kernel(WgradArgs a)
                 const int oc = 64 * blockIdx.z * wn + 8 * q;
                 d_tyx[u] = (ty << 16) | tx;
                 d_dst[u] = (int)(((q >> 2) * g.dplane + m) * 64 + (q & 3) * 16);
-                if (tx < (unsigned)a.Tx && oc < a.Co) d_rel[u] = 2 * ((int)((ty * a.d * a.Wo + tx * a.d) * a.Co) + oc);
+                if (tx < (unsigned)a.Tx && oc < a.Co) d_rel[u] = 2 * ((int)((ty * a.d * a.Wo + tx * a.d) * a.Co) + oc) - (half_item ? 8 : 0);
                 else {
                     // never inside (a column past the tile's width, a channel past the last): zero in both
                     // buffers now, never stored again
@@ -183,8 +188,8 @@ __global__ __launch_bounds__(512, 1) void wgrad_tr_kernel(WgradArgs a)
             }
         }
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-        auto load8 = [](const bf16* p, bool vec, int nvalid) -> u32x4 {   // nvalid: channels that exist
-            if (vec) return *reinterpret_cast<const u32x4*>(p);
+        typedef unsigned u32x4_at8 __attribute__((ext_vector_type(4), aligned(8)));
+        auto load8 = [](const bf16* p, int nvalid) -> u32x4 {   // nvalid: channels that exist
             u32x4 r = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int z = 0; z < 8; ++z)
@@ -238,16 +243,19 @@ __global__ __launch_bounds__(512, 1) void wgrad_tr_kernel(WgradArgs a)
                 const int ty = (int)(d_tyx[u] >> 16), tx = (int)(d_tyx[u] & 0xffffu);
                 const bool ok = d_dst[u] >= 0 && ty < t.rows && tx < t.cols;
                 const unsigned off = ok ? (unsigned)(dbase + (d_rel[u] >> 1)) : 0u;
-                if (vec_dy) dr[u] = *reinterpret_cast<const u32x4*>(dy_b + off);
-                else dr[u] = load8(dy_b + off, false, ok ? a.Co - (d_rel[u] >> 1) % a.Co : 0);   // (rare: channel count not a multiple of 8)
+                if (vec_dy) dr[u] = *reinterpret_cast<const u32x4_at8*>(dy_b + off);
+                else dr[u] = load8(dy_b + off, ok ? a.Co - (d_rel[u] >> 1) % a.Co : 0);   // (rare: channel count not a multiple of 4)
                 if (!ok) dr[u] = (u32x4){0u, 0u, 0u, 0u};
             }
 #pragma unroll
             for (int u = 0; u < HL; ++u)
                 if (h_dst[u] >= 0) *reinterpret_cast<u32x4*>(buf + h_dst[u]) = hr[u];
 #pragma unroll
-            for (int u = 0; u < DL; ++u)
+            for (int u = 0; u < DL; ++u) {
+                dr[u][0] = half_item ? dr[u][2] : dr[u][0];   // (the other half goes to columns that nothing reads)
+                dr[u][1] = half_item ? dr[u][3] : dr[u][1];
                 if (d_dst[u] >= 0) *reinterpret_cast<u32x4*>(buf + d_dst[u]) = dr[u];
+            }
         };
         __builtin_amdgcn_s_setprio(3);
         if (tile_begin < tile_end) stage(tile_begin, ldsb);

@@ -152,3 +152,45 @@ def test_eight_tiles_per_wave_give_the_same_bits():
         assert np.isfinite(out[0][1]).all() and np.any(out[0][1])
         assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]), convs
     assert got == {(d, i) for d in ("forward", "data gradient") for i in wide}, got
+
+
+# bf16 storage, layers behind the first.  Transposing reads: deltas whose last item has four channels
+BF16_WGRAD = [(64, 100, 3), (32, 36, 5), (96, 140, 2)]
+
+
+@pytest.mark.parametrize("cin,cout,k", BF16_WGRAD)
+def test_bf16_weight_gradient(cin, cout, k):
+    """Deltas that are known exactly: the classes' biases saturate the softmax, so the last deltas are 0 or 1 and the layer's are a power of two
+    times 1 - y y, rounded once.  Products of bf16 numbers are exact in fp32; an instruction adds 16 of them with two roundings (one of them to below), eight waves and
+    every slab's sum is added once, so a gradient is off by at most (2 x instructions of a slab + 8 + slabs) 2^-23 of its products' absolute sum; one
+    position that is missing or counted twice moves all gradients of its channel, by 1 / 17000 of that sum."""
+    layers, patch = ((C, cin, 3), (C, cout, k), (FC, 2, 0)), k + 2
+    H, W = patch + 120, patch + 141
+    net = mpcnn.Net(layers, 1, patch, mpcnn.BF16)
+    plan = net.plan_describe(1, H, W, True)
+    r, c, slabs, tiles = [int(v) for v in re.findall(r"weight gradient: bf16 .*MFMA, .* tile (\d+) x (\d+).*, \d+ tiles in (\d+) slabs of (\d+)", plan)[-1]]
+    rng = np.random.default_rng(cin)
+    params = rng.uniform(-0.1, 0.1, net.param_count).astype(np.float32)
+    w = np.zeros((2, cout), np.float32)
+    w[0] = rng.choice([-1.0, 1.0], cout) * 2.0 ** -rng.integers(4, 7, cout)
+    params[-2 * cout - 2:-2] = w.ravel()
+    params[-2:] = 1000, -1000
+    labels = rng.integers(0, 2, (1, H, W)).astype(np.int32)
+    net.set_params(params)
+    net.seg_backward(torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda(), torch.from_numpy(labels).cuda())
+    got = net.get_grads().astype(np.float64)
+    x, y = (torch.from_numpy(net.get_activation(1, H, W, i)[0]).double() for i in (0, 1))
+    net.close()
+    R, Q = y.shape[:2]
+    at = (patch - 1) // 2
+    t = torch.from_numpy(labels[0, at:at + R, at:at + Q]).double()[..., None]
+    dy = (t * torch.from_numpy(w[0]).double() * (1 - y * y)).float().bfloat16().double().reshape(-1, cout)
+    part = lambda u, v: x[u:u + R, v:v + Q].reshape(-1, cin)
+    taps = [(u, v) for u in range(k) for v in range(k)]
+    want, mass = (torch.stack([f(dy).t().contiguous() @ f(part(u, v)) for u, v in taps], -1).flatten().numpy() for f in (lambda z: z, torch.abs))
+    first = cin * 9 + cin
+    bound = (2 * tiles * r * -(-c // 16) + slabs + 8) * 2.0 ** -23
+    assert (np.abs(got[first:first + want.size] - want) <= bound * mass).all()
+    assert bound < 1.0 / (R * Q) and np.any(want)
+    bias = got[first + want.size:first + want.size + cout] - dy.sum(0).numpy()
+    assert (np.abs(bias) <= (R * Q) * 2.0 ** -24 * dy.abs().sum(0).numpy()).all()
