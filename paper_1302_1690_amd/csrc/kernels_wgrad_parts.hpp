@@ -2,6 +2,10 @@
 // parts, three products each, or, where the numbers do not suit fp16 (ranges.hpp), on v_mfma_f32_32x32x16_bf16 in three bf16 parts, six products
 // each (kernels_conv_parts.hpp has the arithmetic of both).  The accumulator's roundings, half as many with two parts, make up for the bits that two parts lose.
 //
+// bf16 storage: one part, one product, raw copies, for the layers that wgrad_tr_kernel does not take (input channels no multiple of 32, or 32 maps and fewer, which went to
+// the fp32 instruction).  Bound by its operand reads: PM + 1 of a kilobyte for PM products, half of the LDS's rate times the matrix pipes'.  3 x 501 x 389, 16 -> 32, 5 x 5:
+// 150 -> 48 us (94 -> 295 TFLOP/s); error in the 2-norm on 1500 x 1400 4.1e-8 -> 2.7e-8, 48 -> 64 k4 on 700 x 640 3.9e-8 -> 3.0e-8, smaller maps 2.3e-8 to 3.2e-8 both.
+//
 // Accuracy.  All six products go to one accumulator, as there is no room for two, and the instruction's results are a little too low
 // whatever their sign: over the slabs of a large map such offsets add up where roundings cancel.  So every other slab has the signs
 // of its deltas turned, and its sums' signs turned back.  Error of the gradient in the 2-norm, fp32 instruction / without turns / now: 32 -> 64 k5 on 1024 x 1024
@@ -16,7 +20,7 @@
 // them for ONE gradient row or output channel; the transposing LDS read (ds_read_b64_tr_b16, see
 // kernels_wgrad_tr.hpp) gives that from channels-last tiles.
 //
-// Layout (three parts; two: 64 bytes per position, planes shifted by 32).  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
+// Layout (three parts; two: 64 bytes per position, planes shifted by 32; one: 32 bytes per position, planes by 128 mod 256).  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
 // position: the 16 lanes that read 4 positions together meet no bank twice, and with a plane pitch of 128 mod 256
 // bytes neither do the 32 of two planes; counters, stores included, still read 26-42 % of the LDS cycles as conflicts).  Parts, the second half of an operand and successive chunks are immediates.  A
 // gradient row tile is two UNITS of 16 rows, a unit being (plane, tap): the two halves of the lanes
@@ -50,8 +54,8 @@ constexpr int kWpMaxTiles = 9;    // row tiles per wave
 __host__ __device__ constexpr int wp_pos(int parts) { return 32 * parts; }   // LDS bytes of a position of one plane
 
 struct WgradPartsArgs {
-    const float* in;     // [B][Hi][Wi][Ci]  layer input
-    const float* dY;     // [B][Ho][Wo][Co]  delta w.r.t. the layer's pre-activation
+    const void* in;      // [B][Hi][Wi][Ci]  layer input (fp32, or bf16: the kernel's template parameter T)
+    const void* dY;      // [B][Ho][Wo][Co]  delta w.r.t. the layer's pre-activation
     float* partial;      // [slab][group][row tile][column tile][4][64 lanes][4], then [Nt*32] bias sums
     int B, Hi, Wi, Ci, Ho, Wo, Co;
     int k, k2, d, d2;    // filter rows, columns; spacing of rows, columns
@@ -71,7 +75,10 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
 {
     WpGeom g;
     g.hh = R + k - 1; g.hwp = 16 * nch + k2 - 1;
-    if (parts == 3) {
+    if (parts == 1) {                                                    // positions follow each other by 32 bytes, planes by 128 mod 256
+        g.hplane = (g.hh * g.hwp * wp_pos(1) + 127) / 256 * 256 + 128;
+        g.dplane = 16 * R * nch * wp_pos(1) + 128;
+    } else if (parts == 3) {
         g.hplane = (((g.hh * g.hwp + 3) / 8) * 8 + 4) * wp_pos(3);       // positions = 4 mod 8, at least hh * hwp
         g.dplane = (16 * R * nch + 4) * wp_pos(3);
     } else {                                                             // a plane's 32 bytes fall between another's (and 64 to drop items into)
@@ -85,11 +92,16 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
     return g;
 }
 
-template <int PM, int P>
+template <int PM, int P, typename T>
 __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigned dy_peak)
 {
     constexpr int kWpPos = wp_pos(P);
     constexpr int SI = kWpItems;
+    constexpr bool kF32 = sizeof(T) == 4;
+    static_assert(kF32 ? P == 2 || P == 3 : P == 1, "parts of the storage type");
+    constexpr unsigned ES = sizeof(T);
+    const T* const in_t = static_cast<const T*>(a.in);
+    const T* const dy_t = static_cast<const T*>(a.dY);
     constexpr unsigned kNone = 0x80000000u;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     char* ldsb = reinterpret_cast<char*>(lds);
@@ -125,7 +137,7 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
             y = parts_div(pos, a.mg_hwp, g.hwp); x = pos - y * g.hwp;
             left = a.Ci - (16 * p0 + 8 * (int)q);
             const bool ok = y < (unsigned)g.hh && left > 0;
-            i_off[u] = ok ? 4u * ((y * a.d * a.Wi + x * a.d2) * a.Ci + 16 * p0 + 8 * q) : kNone;
+            i_off[u] = ok ? ES * ((y * a.d * a.Wi + x * a.d2) * a.Ci + 16 * p0 + 8 * q) : kNone;
             // (what lies past the halo's last position goes to the padding of the last delta plane)
             i_dst[u] = y < (unsigned)g.hh ? g.halo_b + (q >> 1) * g.hplane + pos * kWpPos + (q & 1) * 16 : g.halo_b - kWpPos;
         } else {
@@ -134,18 +146,18 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
             const int oc = 32 * wn * blockIdx.z + 8 * qd;
             left = a.Co - oc;
             const bool ok = y < (unsigned)a.R && left > 0;
-            i_off[u] = ok ? 4u * ((y * a.d * a.Wo + x * a.d2) * a.Co + oc) : kNone;
+            i_off[u] = ok ? ES * ((y * a.d * a.Wo + x * a.d2) * a.Co + oc) : kNone;
             i_dst[u] = (qd >> 1) * g.dplane + m * kWpPos + (qd & 1) * 16;
         }
         i_yx[u] = (left <= 4 ? 0x80000000u : 0u) | (y << 16) | x;
     }
-    u32x4 pre[SI][2];
+    u32x4 pre[SI][kF32 ? 2 : 1];
     // signs of this slab's deltas (see Accuracy above)
     const float turn = blockIdx.x & 1 ? -1.f : 1.f;
     // what numbers are split after being multiplied by, and what takes their products' sums back
     const int in_raise = P == 2 ? kActRaise : 0, dy_raise = P == 2 ? raise_of(dy_peak, a.dy_margin) : 0;
     const float in_up = P == 2 ? power_of_two(in_raise) : kPartsUp, dy_up = turn * (P == 2 ? power_of_two(dy_raise) : kPartsUp);
-    const Lower down = P == 2 ? lower_by(in_raise + dy_raise) : Lower{kPartsDown, 1.f};
+    const Lower down = P == 2 ? lower_by(in_raise + dy_raise) : Lower{P == 3 ? kPartsDown : 1.f, 1.f};
     float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
 #pragma unroll
     for (int j = 0; j < 8; ++j) bsum[j] = 0.f;
@@ -172,9 +184,9 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
         const Tile t = decode(tile);
         const int y0 = t.ty0 * a.d + t.ry, x0 = t.tx0 * a.d2 + t.rx;
         const __amdgpu_buffer_rsrc_t in_r = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(a.in + (((long)t.b * a.Hi + y0) * a.Wi + x0) * a.Ci), 0, 0x7fffffff, 0x00020000);
+            const_cast<T*>(in_t + (((long)t.b * a.Hi + y0) * a.Wi + x0) * a.Ci), 0, 0x7fffffff, 0x00020000);
         const __amdgpu_buffer_rsrc_t dy_r = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(a.dY + (((long)t.b * a.Ho + y0) * a.Wo + x0) * a.Co), 0, 0x7fffffff, 0x00020000);
+            const_cast<T*>(dy_t + (((long)t.b * a.Ho + y0) * a.Wo + x0) * a.Co), 0, 0x7fffffff, 0x00020000);
         const bool inside = any && t.rows >= a.R && t.cols >= txp && y0 + (g.hh - 1) * a.d < a.Hi && x0 + (g.hwp - 1) * a.d2 < a.Wi;
 #pragma unroll
         for (int u = 0; u < SI; ++u) {
@@ -187,8 +199,16 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
                 off = ok ? off : kNone;
             }
             const unsigned off4 = whole || !(i_yx[u] >> 31) ? off : kNone;
-            pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
-            pre[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off4, 16, 0));
+            if constexpr (kF32) {
+                pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+                pre[u][1] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off4, 16, 0));
+            } else if (whole)
+                pre[u][0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+            else {                                     // (two halves: the second may be another position's)
+                const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+                const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off4, 8, 0));
+                pre[u][0] = (u32x4){lo[0], lo[1], hi[0], hi[1]};
+            }
         }
     };
     auto to_lds = [&](char* buf) {
@@ -198,14 +218,18 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
             if (first >= g.nh + g.nd) break;
             float x[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
+            for (int j = 0; j < 8; ++j) {
+                if constexpr (kF32) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
+                else x[j] = (float)__builtin_bit_cast(bf16x8, pre[u][0])[j];
+            }
             if (first >= g.nh)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) bsum[j] += x[j];
             u32x4 p[P];
             const float up = first >= g.nh ? dy_up : in_up;
             if constexpr (P == 2) split_halves(x, p, up);
-            else split_parts(x, p, up);
+            else if constexpr (P == 3) split_parts(x, p, up);
+            else p[0] = pre[u][0] ^ (first >= g.nh && blockIdx.x & 1 ? 0x80008000u : 0u);   // (the deltas' turned signs)
             char* dst = buf + i_dst[u];
 #pragma unroll
             for (int i = 0; i < P; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
@@ -254,7 +278,8 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
             return;
         }
 #define MPCNN_MUL(i, j) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.part[i], Bo.part[j], c, 0, 0, 0)
-        MPCNN_MUL(P - 1, 0); MPCNN_MUL(0, P - 1); MPCNN_MUL(1, 1); MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); MPCNN_MUL(0, 0);
+        if constexpr (P == 3) { MPCNN_MUL(2, 0); MPCNN_MUL(0, 2); MPCNN_MUL(1, 1); MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); }
+        MPCNN_MUL(0, 0);
 #undef MPCNN_MUL
     };
     // one tile: the chunks (row, 16 columns) that hold positions, dealt to the wk waves
@@ -378,21 +403,21 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
                 for (int r4 = 0; r4 < 4; ++r4)
                     dst[r4 * 64] = down.second * (turn * down.first * (v4f){acc[p][4 * r4], acc[p][4 * r4 + 1], acc[p][4 * r4 + 2], acc[p][4 * r4 + 3]});
             }
-        if (odd) {
+        if constexpr (P == 3) if (odd) {
             // A sum that is not finite came from infinities, NaN or numbers without parts (or overflows): once more, with fp32
             // multiply-adds over the slab's positions, four gradient rows at a time.  Bound by the trips of its loads, about a tenth
             // of the slab's own time for every four rows that need it; where everything is NaN (a net that diverged) over after one value.
             const int oc = 32 * nt + (lane & 31);
             const bool column = oc < a.Co;
             auto delta = [&](const Tile& t, int y, int x) {
-                return a.dY + (((long)t.b * a.Ho + (t.ty0 + y) * a.d + t.ry) * a.Wo + (t.tx0 + x) * a.d2 + t.rx) * a.Co + oc;
+                return dy_t + (((long)t.b * a.Ho + (t.ty0 + y) * a.d + t.ry) * a.Wo + (t.tx0 + x) * a.d2 + t.rx) * a.Co + oc;
             };
             // a NaN among the column's deltas: NaN whatever else, and written already (the slab's first position stands for all)
             bool explained = !column;
             for (int tile = tile_begin; tile < tile_end; ++tile) {
                 const Tile t = decode(tile);
                 if (t.rows <= 0 || t.cols <= 0) continue;
-                if (column) { const float v = *delta(t, 0, 0); explained = v != v; }
+                if (column) { const float v = load1(delta(t, 0, 0)); explained = v != v; }
                 break;
             }
             for (int e = 0; e < PM * 4; ++e) {
@@ -416,12 +441,12 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
                     const int cols = t.cols < txp ? t.cols : txp;
                     for (int y = 0; y < a.R && y < t.rows && more; ++y) {
                         if (bad) {
-                            const float* src = a.in + (((long)t.b * a.Hi + (t.ty0 + y + (int)ta) * a.d + t.ry) * a.Wi + (t.tx0 + (int)tb) * a.d2 + t.rx) * a.Ci + c;
-                            const float* dy = delta(t, y, 0);
+                            const T* src = in_t + (((long)t.b * a.Hi + (t.ty0 + y + (int)ta) * a.d + t.ry) * a.Wi + (t.tx0 + (int)tb) * a.d2 + t.rx) * a.Ci + c;
+                            const T* dy = delta(t, y, 0);
 #pragma unroll 4
                             for (int x = 0; x < cols; ++x) {
-                                const v4f v = *reinterpret_cast<const v4f*>(src + (long)x * a.d2 * a.Ci);
-                                const float d = dy[(long)x * a.d2 * a.Co];
+                                const v4f v = load4(src + (long)x * a.d2 * a.Ci);
+                                const float d = load1(dy + (long)x * a.d2 * a.Co);
 #pragma unroll
                                 for (int z = 0; z < 4; ++z) sum[z] = fmaf(v[z], d, sum[z]);
                             }
@@ -454,14 +479,17 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
     }
 }
 
-// In two parts where both tensors suit them
-template <int PM>
+// fp32 storage: in two parts where both tensors suit them
+template <int PM, typename T>
 __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsArgs a)
 {
-    unsigned peak = kNoPeak;
-    if (a.dy_peak) peak = peak_of(a.dy_peak, a.dy_words);
-    if (peak < kNoPeak) wgrad_parts_body<PM, 2>(a, peak);
-    else wgrad_parts_body<PM, 3>(a, peak);
+    if constexpr (sizeof(T) == 4) {
+        unsigned peak = kNoPeak;
+        if (a.dy_peak) peak = peak_of(a.dy_peak, a.dy_words);
+        if (peak < kNoPeak) wgrad_parts_body<PM, 2, T>(a, peak);
+        else wgrad_parts_body<PM, 3, T>(a, peak);
+    } else
+        wgrad_parts_body<PM, 1, T>(a, 0);
 }
 
 }  // namespace mpcnn

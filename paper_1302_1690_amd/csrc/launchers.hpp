@@ -45,8 +45,8 @@ bool launch_wgrad_f32(const WgradArgs& a, int hl, dim3 grid, size_t lds, hipStre
 bool launch_wgrad_b16(const WgradArgs& a, int hl, dim3 grid, size_t lds, hipStream_t st);
 bool launch_wgrad_bm(const WgradArgs& a, int nch, dim3 grid, size_t lds, hipStream_t st);
 bool launch_wgrad_tr(const WgradArgs& a, int nch, dim3 grid, size_t lds, hipStream_t st);   // kernels_wgrad_tr.hpp
-bool launch_wgrad_parts(const WgradPartsArgs& a, int PM, dim3 grid, size_t lds, hipStream_t st);   // fp32 storage, kernels_wgrad_parts.hpp
-hipError_t wgrad_parts_attrs();
+template <typename T> bool launch_wgrad_parts(const WgradPartsArgs& a, int PM, dim3 grid, size_t lds, hipStream_t st);   // kernels_wgrad_parts.hpp
+template <typename T> hipError_t wgrad_parts_attrs();
 
 // Kernels that may ask for more than 64 KiB of dynamic LDS must say so once per device.
 hipError_t wgrad_attrs_f32();

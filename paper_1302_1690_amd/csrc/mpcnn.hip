@@ -362,10 +362,11 @@ unsigned magic_of(unsigned x) { return x <= 1 ? 0u : (unsigned)(((1ull << 32) + 
 // (its conversions lie under the other wave's instructions, not all of them), a barrier, and the share of the closing
 // reduce, which reads every slab's partial result at about 7 bytes per cycle and compute unit.
 // `bound`, if given, receives the most floats of partial sums any map size can ask for.
-WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, bool half, size_t* bound)
+WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, int parts, bool half, size_t* bound)
 {
     WgradPlan best;
     double best_cost = -1;
+    const size_t es = parts == 1 ? 2 : 4;
     const int planes = ceil_div(ly.cin, 16), kk = ly.k * ly.k2, Nt = ceil_div(ly.cout, 32);
     const int fh = ceil_div(out_r, ly.dil), fw = ceil_div(out_c, ly.dil2);
     if (bound) *bound = 0;
@@ -385,20 +386,20 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
                     for (int R : {1, 2, 4, 8})
                         for (int nch = 1; nch <= 4; ++nch) {
                             if (R * nch < wk || (R > 1 && R / 2 >= fh) || (nch > 1 && 16 * (nch - 1) >= fw)) continue;
-                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn, 3);
+                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn, parts);
                             size_t lds = std::max((size_t)2 * g.buf_b, (size_t)16 * 1024);
                             if (wk > 1) lds = std::max(lds, (size_t)4 * PM * 4096);
                             if (lds > (size_t)160 * 1024 || g.nh + g.nd > mpcnn::kWpItems * mpcnn::kWpThreads) continue;
                             // (byte offsets inside a tile are 31 bits)
-                            if (((size_t)g.hh * ly.dil * in_c + (size_t)g.hwp * ly.dil2) * ly.cin * 4 >= (1ull << 31) ||
-                                ((size_t)R * ly.dil * out_c + (size_t)16 * nch * ly.dil2) * ly.cout * 4 >= (1ull << 31)) continue;
+                            if (((size_t)g.hh * ly.dil * in_c + (size_t)g.hwp * ly.dil2) * ly.cin * es >= (1ull << 31) ||
+                                ((size_t)R * ly.dil * out_c + (size_t)16 * nch * ly.dil2) * ly.cout * es >= (1ull << 31)) continue;
                             const int nty = ceil_div(fh, R), ntx = ceil_div(fw, 16 * nch);
                             const long tiles = (long)B * ly.dil * ly.dil2 * nty * ntx;
                             if (tiles * std::max(std::max(ntx, nty), std::max(ly.dil, ly.dil2)) >= (1l << 31)) continue;
                             const long tps = (tiles + target - 1) / target, slabs = (tiles + tps - 1) / tps;
                             const double chunks = (double)fh / nty * ceil_div(fw, 16) / ntx / wk;   // of a wave and tile, on average
-                            const double t_mul = chunks * PM * (half ? 3 : 6) * 32 * 2;
-                            const double t_load = (g.nh + g.nd) * (32.0 / 10 + (half ? 40.0 : 75.0) * 6 / 256);
+                            const double t_mul = chunks * PM * (parts == 1 ? 1.5 : half ? 3 : 6) * 32 * 2;   // (one part: bound by its operand reads)
+                            const double t_load = (g.nh + g.nd) * (8.0 * es / 10 + (parts == 1 ? 15.0 : half ? 40.0 : 75.0) * 6 / 256);
                             const double cost = tps * (std::max(t_mul, 0.5 * t_load) + 0.5 * t_load + 800.0) + (double)slabs * plen * 4 / (7.0 * kNumCU);
                             if (best_cost < 0 || cost < best_cost) {
                                 best_cost = cost;
@@ -420,8 +421,24 @@ inline bool l0_wgrad_on_bm(const Layer& ly, bool bf16) { return bf16 && ly.cout 
 // waves' sums to meet): 16 -> 16 channels, 2 x 2 taps, 1300 positions (2.6 MFLOP) 15.0 us against 8.8, 16 -> 16, 3 x 3, 2700 positions (12 MFLOP) 16.3
 // against 12.6; 32 -> 100, 2 x 2, 2600 positions (67 MFLOP) 17.4 against 14.8, but 2 us less in the reduce for its fewer slabs.
 constexpr double kPartsWgradFlops = 4e7;
-// layers that kernel takes: fp32 storage, 128-bit items of both tensors, more than a sliver of input channels
-inline bool wgrad_parts_layer(const Layer& ly, bool bf16) { return !bf16 && ly.wgrad_mfma && ly.cin % 4 == 0 && ly.cin >= 8 && ly.cout % 4 == 0; }
+// With bf16 storage, one part (us there -> here): in place of wgrad_mfma_kernel (32 maps or fewer, rectangular filters) 16 -> 32, 5 x 5, 2.8e8 operations 17.5 -> 20.4, 4.7e8
+// 21.2 -> 21.0, 1.7e10 171 -> 51; 16 -> 16, 3 x 3, 1.1e8 16.4 -> 18.5, 4.3e8 24.3 -> 20.9; 64 -> 32 1.4e10 141 -> 49.  Of wgrad_bm_kernel where both counts are multiples of 8:
+// 16 -> 64, 5 x 5, 2.2e9 22.5 -> 25.0, 4.8e9 30.0 -> 27.8; 48 -> 64, 4 x 4, 4.1e9 29.5 -> 32.7, 9.2e9 45 -> 34, 1.4e11 426 -> 260; 40 -> 200, 2 x 2, 3.2e10 144 -> 146.  Other counts
+// that kernel takes channel by channel: 12 -> 100, 4 x 4, 7.8e7 28.0 -> 21.6, 6.3e9 120 -> 43; 100 -> 36, 1 x 1, 6.7e8 72 -> 24.
+constexpr double kPart1WgradFlops = 4e8, kPart1WgradFlopsBm = 4.5e9;
+// layers that kernel takes: 128-bit (bf16: 64-bit) items of both tensors, more than a sliver of input channels; with bf16 storage those that
+// wgrad_tr_kernel does not take, which is ahead (two column tiles per wave, seven operands for ten products: 64 -> 64, 5 x 5, 2 x 2048 x 2048 1842 against 2304 us)
+inline bool wgrad_tr_layer(const Layer& ly) { return !ly.rect && ly.cout > 32 && ly.cin % 32 == 0; }
+inline bool wgrad_parts_layer(const Layer& ly, bool bf16)
+{
+    return ly.wgrad_mfma && ly.cin % 4 == 0 && ly.cin >= 8 && ly.cout % 4 == 0 && !(bf16 && wgrad_tr_layer(ly));
+}
+inline double parts_wgrad_least(const Layer& ly, bool bf16)
+{
+    if (!bf16) return kPartsWgradFlops;
+    if (ly.rect || ly.cout <= 32) return kPart1WgradFlops;
+    return ly.cin % 8 || ly.cout % 8 ? kPartsWgradFlops : kPart1WgradFlopsBm;
+}
 
 WgradPlan plan_wgrad(const Layer& ly, int B, int in_r, int in_c, int out_r, int out_c, bool bm)
 {
@@ -695,7 +712,8 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
             if (ly.dgrad_mfma && l > 0)
                 g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
                                               net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.dgrad_half ? 3 : 6, es, true, net->hint_pt, net->hint_mp);
-            if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= kPartsWgradFlops) g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, net->halves, nullptr);
+            if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= parts_wgrad_least(ly, net->bf16))
+                g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, net->bf16 ? 1 : 3, net->halves, nullptr);
             if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
             g->partial_n[l] = w.ok ? w.slabs : w.chunks;
@@ -779,7 +797,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
                                    (size_t)std::max(kDirectWgradChunks, 2 * kNumCU) * ly.p_len);
                 if (wgrad_parts_layer(ly, net->bf16)) {
                     size_t bound = 0;
-                    (void)plan_wgrad_parts(ly, 1, 1, 1, 1, net->halves, &bound);
+                    (void)plan_wgrad_parts(ly, 1, 1, 1, 1, net->bf16 ? 1 : 3, net->halves, &bound);
                     alloc_f = std::max(alloc_f, bound);
                 }
                 alloc_f = std::max(alloc_f, (size_t)g->partial_n[l] * g->partial_len[l]);
@@ -914,9 +932,9 @@ bool launch_l0_wgrad_bm(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, h
 // Kernels that may ask for more than 64 KiB of dynamic LDS must say so once.
 mpcnn_status set_lds_attrs(bool bf16_storage)
 {
-    if (bf16_storage) { HIP_TRY(mpcnn::conv_parts_attrs_b16_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_b16_back()); HIP_TRY(mpcnn::wgrad_attrs_b16()); }
+    if (bf16_storage) { HIP_TRY(mpcnn::conv_parts_attrs_b16_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_b16_back()); HIP_TRY(mpcnn::wgrad_attrs_b16()); HIP_TRY(mpcnn::wgrad_parts_attrs<mpcnn::bf16>()); }
     else { HIP_TRY(mpcnn::conv_parts_attrs_f32_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_f32_back());
-           HIP_TRY(mpcnn::wgrad_attrs_f32()); HIP_TRY(mpcnn::wgrad_parts_attrs()); }
+           HIP_TRY(mpcnn::wgrad_attrs_f32()); HIP_TRY(mpcnn::wgrad_parts_attrs<float>()); }
     return MPCNN_OK;
 }
 
@@ -1276,7 +1294,7 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
             const WgradPlan& wp = g.wgrad[li];
             float* partial = (float*)(ws + g.partial_off[li]);
             if (wp.ok && wp.PM > 0) {
-                if constexpr (kF32) {
+                {
                     WgradPartsArgs a{};
                     a.in = A; a.dY = dY; a.partial = partial;
                     a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ci = Ci; a.Ho = Ho; a.Wo = Wo; a.Co = ly.cout;
@@ -1292,8 +1310,8 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                     a.mg_d = magic_of(ly.dil); a.mg_d2 = magic_of(ly.dil2);
                     dim3 grid((unsigned)wp.slabs, (unsigned)wp.gm, (unsigned)wp.gn);
                     bool launched = false;
-                    LAUNCH("wgrad_parts", li, wstep, flops, es * (n_in + n_out) + 4.0 * ly.p_len,
-                           launched = mpcnn::launch_wgrad_parts(a, wp.PM, grid, wp.lds, st));
+                    LAUNCH(kF32 ? "wgrad_parts" : "wgrad_bm", li, wstep, flops, es * (n_in + n_out) + 4.0 * ly.p_len,
+                           launched = mpcnn::launch_wgrad_parts<T>(a, wp.PM, grid, wp.lds, st));
                     if (!launched)
                         return fail(MPCNN_EUNSUPPORTED, "layer %zu: no weight-gradient kernel instance for its plan", li);
                 }
@@ -1756,8 +1774,8 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
                             l0_wgrad_on_bm(ly, net->bf16) ? "bf16" : "fp32", w.tiles_total, w.chunks);
         else if (!w.ok) put("  weight gradient: plain kernel, %d chunks\n", w.chunks);
         else if (w.PM > 0)
-            put("  weight gradient: bf16 MFMA, three parts per number, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
-                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg,
+            put("  weight gradient: bf16 MFMA, %s per number, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
+                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", net->bf16 ? "one part" : "three parts", w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg,
                 w.R, 16 * w.nch, w.tiles_total, w.slabs, w.tiles_per_slab, w.lds);
         else
             put("  weight gradient: %s MFMA, %d x %d result tiles, waves %d x %d x %d (rows x columns x tile rows), %d row "

@@ -154,12 +154,15 @@ def test_eight_tiles_per_wave_give_the_same_bits():
     assert got == {(d, i) for d in ("forward", "data gradient") for i in wide}, got
 
 
-# bf16 storage, layers behind the first.  Transposing reads: deltas whose last item has four channels
-BF16_WGRAD = [(64, 100, 3), (32, 36, 5), (96, 140, 2)]
+# bf16 storage, layers behind the first.  Transposing reads: deltas whose last item has four channels.  One part per number: maps and channels 4 mod 8, a plane and half a
+# unit past one, several groups of workgroups, filter sides 1 to 7
+BF16_WGRAD = [(64, 100, 3, "tr"), (32, 36, 5, "tr"), (96, 140, 2, "tr"), (12, 28, 7, "one"), (16, 32, 5, "one"), (40, 100, 3, "one"), (64, 32, 3, "one"),
+              (8, 48, 7, "bm"), (8, 32, 7, "one"), (36, 260, 1, "one"), (100, 36, 3, "one"), (48, 120, 5, "one")]
+KERNEL = {"tr": "transposing reads", "one": "one part per number", "bm": "result tiles"}
 
 
-@pytest.mark.parametrize("cin,cout,k", BF16_WGRAD)
-def test_bf16_weight_gradient(cin, cout, k):
+@pytest.mark.parametrize("cin,cout,k,kernel", BF16_WGRAD)
+def test_bf16_weight_gradient(cin, cout, k, kernel):
     """Deltas that are known exactly: the classes' biases saturate the softmax, so the last deltas are 0 or 1 and the layer's are a power of two
     times 1 - y y, rounded once.  Products of bf16 numbers are exact in fp32; an instruction adds 16 of them with two roundings (one of them to below), eight waves and
     every slab's sum is added once, so a gradient is off by at most (2 x instructions of a slab + 8 + slabs) 2^-23 of its products' absolute sum; one
@@ -168,6 +171,7 @@ def test_bf16_weight_gradient(cin, cout, k):
     H, W = patch + 120, patch + 141
     net = mpcnn.Net(layers, 1, patch, mpcnn.BF16)
     plan = net.plan_describe(1, H, W, True)
+    assert KERNEL[kernel] in [line for line in plan.splitlines() if "weight gradient" in line][1]
     r, c, slabs, tiles = [int(v) for v in re.findall(r"weight gradient: bf16 .*MFMA, .* tile (\d+) x (\d+).*, \d+ tiles in (\d+) slabs of (\d+)", plan)[-1]]
     rng = np.random.default_rng(cin)
     params = rng.uniform(-0.1, 0.1, net.param_count).astype(np.float32)
