@@ -1,6 +1,7 @@
 // Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_f16, every fp32 number as the sum of two fp16
 // parts, three products each, or, where the numbers do not suit fp16 (ranges.hpp), on v_mfma_f32_32x32x16_bf16 in three bf16 parts, six products
-// each (kernels_conv_parts.hpp has the arithmetic of both).  The accumulator's roundings, half as many with two parts, make up for the bits that two parts lose.
+// each (kernels_conv_parts.hpp has the arithmetic of both).  The accumulator's roundings, half as many with two parts, make up for the bits that two parts lose once a wave adds some 144 positions;
+// shorter chains take three parts (plan_wgrad_parts has the errors on both sides).
 //
 // bf16 storage: one part, one product, raw copies, for the layers that wgrad_tr_kernel does not take (input channels no multiple of 32, or 32 maps and fewer, which went to
 // the fp32 instruction).  Bound by its operand reads: PM + 1 of a kilobyte for PM products, half of the LDS's rate times the matrix pipes'.  3 x 501 x 389, 16 -> 32, 5 x 5:

@@ -128,6 +128,8 @@ struct WgradPlan {
     size_t plen = 0;      // floats per partial result (tiled layout)
     int hl = 0;           // halo items per loading thread and tile (fp32 matrix instruction kernel)
     int PM = 0, R = 0, nch = 0, RT = 0, ppg = 0, tpg = 0, ntg = 0;   // PM > 0: wgrad_parts_kernel (gm x gn groups, tile R rows x 16 nch columns)
+    double chain = 0;     // ... positions that a wave adds into one accumulator
+    bool two = false;     // ... in two fp16 parts where the deltas suit them
     // direct kernel fallback
     int rows_per_chunk = 0, chunks = 0;
     bool l0m = false;     // the image layer's own kernel (l0_wgrad_mfma_kernel): `chunks` workgroups, flat partial results
@@ -362,11 +364,12 @@ unsigned magic_of(unsigned x) { return x <= 1 ? 0u : (unsigned)(((1ull << 32) + 
 // (its conversions lie under the other wave's instructions, not all of them), a barrier, and the share of the closing
 // reduce, which reads every slab's partial result at about 7 bytes per cycle and compute unit.
 // `bound`, if given, receives the most floats of partial sums any map size can ask for.
-WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, int parts, bool half, size_t* bound)
+WgradPlan plan_wgrad_parts_in(const Layer& ly, int B, int in_c, int out_r, int out_c, int parts, size_t* bound)
 {
     WgradPlan best;
     double best_cost = -1;
     const size_t es = parts == 1 ? 2 : 4;
+    const bool two = parts == 2;
     const int planes = ceil_div(ly.cin, 16), kk = ly.k * ly.k2, Nt = ceil_div(ly.cout, 32);
     const int fh = ceil_div(out_r, ly.dil), fw = ceil_div(out_c, ly.dil2);
     if (bound) *bound = 0;
@@ -386,7 +389,7 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
                     for (int R : {1, 2, 4, 8})
                         for (int nch = 1; nch <= 4; ++nch) {
                             if (R * nch < wk || (R > 1 && R / 2 >= fh) || (nch > 1 && 16 * (nch - 1) >= fw)) continue;
-                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn, parts);
+                            const mpcnn::WpGeom g = mpcnn::wp_geom(R, nch, ly.k, ly.k2, ppg, wn, two ? 3 : parts);   // (two parts' plans serve three as well)
                             size_t lds = std::max((size_t)2 * g.buf_b, (size_t)16 * 1024);
                             if (wk > 1) lds = std::max(lds, (size_t)4 * PM * 4096);
                             if (lds > (size_t)160 * 1024 || g.nh + g.nd > mpcnn::kWpItems * mpcnn::kWpThreads) continue;
@@ -398,21 +401,30 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
                             if (tiles * std::max(std::max(ntx, nty), std::max(ly.dil, ly.dil2)) >= (1l << 31)) continue;
                             const long tps = (tiles + target - 1) / target, slabs = (tiles + tps - 1) / tps;
                             const double chunks = (double)fh / nty * ceil_div(fw, 16) / ntx / wk;   // of a wave and tile, on average
-                            const double t_mul = chunks * PM * (parts == 1 ? 1.5 : half ? 3 : 6) * 32 * 2;   // (one part: bound by its operand reads)
-                            const double t_load = (g.nh + g.nd) * (8.0 * es / 10 + (parts == 1 ? 15.0 : half ? 40.0 : 75.0) * 6 / 256);
+                            const double t_mul = chunks * PM * (parts == 1 ? 1.5 : two ? 3 : 6) * 32 * 2;   // (one part: bound by its operand reads)
+                            const double t_load = (g.nh + g.nd) * (8.0 * es / 10 + (parts == 1 ? 15.0 : two ? 40.0 : 75.0) * 6 / 256);
                             const double cost = tps * (std::max(t_mul, 0.5 * t_load) + 0.5 * t_load + 800.0) + (double)slabs * plen * 4 / (7.0 * kNumCU);
                             if (best_cost < 0 || cost < best_cost) {
                                 best_cost = cost;
                                 best.PM = PM; best.R = R; best.nch = nch; best.RT = RT; best.ppg = ppg; best.tpg = tpg; best.ntg = ntg;
                                 best.wm = wm; best.wn = wn; best.wk = wk; best.gm = gm; best.gn = gn; best.Nt = Nt;
                                 best.nty = nty; best.ntx = ntx; best.tiles_total = (int)tiles; best.tiles_per_slab = (int)tps;
-                                best.slabs = (int)slabs; best.lds = lds; best.plen = plen; best.ok = true;
+                                best.slabs = (int)slabs; best.lds = lds; best.plen = plen; best.chain = 16 * chunks * tps; best.two = two; best.ok = true;
                             }
                         }
                 }
             }
     }
     return best;
+}
+// fp32 storage, `half` (two fp16 parts may be used): they are where a wave of the three parts' plan adds at least kHalfChain positions into one accumulator.  What two parts leave
+// out is 5e-8 of a gradient (2-norm) whatever the length, what three parts' six products are rounded by grows with it.  Three / two parts: 16 positions 2.7e-8 / 4.6e-8 and 64 2.7e-8 / 5.0e-8
+// (32 -> 64, 5 x 5), 112 3.9e-8 / 4.6e-8 (128 -> 200, 2 x 2), 128 4.2e-8 / 4.9e-8, 160 6.5e-8 / 4.7e-8 (64 -> 128, 3 x 3), 256 1.24e-7 / 4.9e-8, 640 3.5e-7 / 5.3e-8, 3904 1.9e-6 / 1.05e-6.
+constexpr double kHalfChain = 144;
+WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, bool bf16, bool half)
+{
+    const WgradPlan w = plan_wgrad_parts_in(ly, B, in_c, out_r, out_c, bf16 ? 1 : 3, nullptr);
+    return half && w.ok && w.chain >= kHalfChain ? plan_wgrad_parts_in(ly, B, in_c, out_r, out_c, 2, nullptr) : w;
 }
 // The image layer's weight gradient multiplies on the bf16 instruction where both operands are bf16 and a position's
 // deltas are whole 128-bit items; with fp32 storage, and for other map counts, on the fp32 one.
@@ -713,7 +725,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
                 g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
                                               net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.dgrad_half ? 3 : 6, es, true, net->hint_pt, net->hint_mp);
             if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= parts_wgrad_least(ly, net->bf16))
-                g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, net->bf16 ? 1 : 3, net->halves, nullptr);
+                g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, net->bf16, net->halves);
             if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
             const WgradPlan& w = g->wgrad[l];
             g->partial_n[l] = w.ok ? w.slabs : w.chunks;
@@ -797,7 +809,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
                                    (size_t)std::max(kDirectWgradChunks, 2 * kNumCU) * ly.p_len);
                 if (wgrad_parts_layer(ly, net->bf16)) {
                     size_t bound = 0;
-                    (void)plan_wgrad_parts(ly, 1, 1, 1, 1, net->bf16 ? 1 : 3, net->halves, &bound);
+                    (void)plan_wgrad_parts_in(ly, 1, 1, 1, 1, net->bf16 ? 1 : 3, &bound);
                     alloc_f = std::max(alloc_f, bound);
                 }
                 alloc_f = std::max(alloc_f, (size_t)g->partial_n[l] * g->partial_len[l]);
@@ -1304,7 +1316,7 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                     a.Nt = wp.Nt; a.RT = wp.RT; a.wm = wp.wm; a.wn = wp.wn; a.wk = wp.wk;
                     a.ppg = wp.ppg; a.tpg = wp.tpg; a.ntg = wp.ntg;
                     a.dy_peak = delta_words(g, ws, li); a.dy_words = g.delta_words[li]; a.dy_margin = g.delta_margin[li];
-                    if (li == 0 || !g.squashed[li - 1]) a.dy_peak = nullptr;
+                    if (li == 0 || !g.squashed[li - 1] || !wp.two) a.dy_peak = nullptr;
                     a.mg_nqh = magic_of(2 * wp.ppg); a.mg_hwp = magic_of(16 * wp.nch + ly.k2 - 1); a.mg_txp = magic_of(16 * wp.nch);
                     a.mg_tpg = magic_of(wp.tpg); a.mg_k2 = magic_of(ly.k2); a.mg_ntx = magic_of(wp.ntx); a.mg_nty = magic_of(wp.nty);
                     a.mg_d = magic_of(ly.dil); a.mg_d2 = magic_of(ly.dil2);
@@ -1774,8 +1786,8 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
                             l0_wgrad_on_bm(ly, net->bf16) ? "bf16" : "fp32", w.tiles_total, w.chunks);
         else if (!w.ok) put("  weight gradient: plain kernel, %d chunks\n", w.chunks);
         else if (w.PM > 0)
-            put("  weight gradient: bf16 MFMA, %s per number, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
-                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", net->bf16 ? "one part" : "three parts", w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg,
+            put("  weight gradient: bf16 MFMA, %s, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
+                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", net->bf16 ? "one part per number" : w.two ? "three parts per number or two of fp16" : "three parts per number", w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg,
                 w.R, 16 * w.nch, w.tiles_total, w.slabs, w.tiles_per_slab, w.lds);
         else
             put("  weight gradient: %s MFMA, %d x %d result tiles, waves %d x %d x %d (rows x columns x tile rows), %d row "

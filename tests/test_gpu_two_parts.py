@@ -13,7 +13,7 @@ from paper_1302_1690_amd import mpcnn, workloads as wl
 from test_gpu_conv_parts import close_layers, reached
 
 pytestmark = pytest.mark.gpu
-C, FC = wl.C, wl.FC
+C, MP, FC = wl.C, wl.MP, wl.FC
 
 # filters and channels of the layer behind the first: sums of 512 products and a few more in both directions; three parts (1 x 1: blocks of fewer than four
 # steps), runs of two chunks, a chunk, filter rows of a chunk (two, three, one) and, from 8 rows on, filter rows in blocks of fewer rows
@@ -157,7 +157,8 @@ def test_eight_tiles_per_wave_give_the_same_bits():
 # bf16 storage, layers behind the first.  Transposing reads: deltas whose last item has four channels.  One part per number: maps and channels 4 mod 8, a plane and half a
 # unit past one, several groups of workgroups, filter sides 1 to 7
 BF16_WGRAD = [(64, 100, 3, "tr"), (32, 36, 5, "tr"), (96, 140, 2, "tr"), (12, 28, 7, "one"), (16, 32, 5, "one"), (40, 100, 3, "one"), (64, 32, 3, "one"),
-              (8, 48, 7, "bm"), (8, 32, 7, "one"), (36, 260, 1, "one"), (100, 36, 3, "one"), (48, 120, 5, "one")]
+              (8, 48, 7, "bm"), (8, 32, 7, "one"), (36, 260, 1, "one"), (100, 36, 3, "one"), (48, 120, 5, "one"),
+              (80, 32, (3, 2), "one"), (40, 100, (3, 2), "one")]      # (behind a pool of 2 x 3)
 KERNEL = {"tr": "transposing reads", "one": "one part per number", "bm": "result tiles"}
 
 
@@ -167,7 +168,9 @@ def test_bf16_weight_gradient(cin, cout, k, kernel):
     times 1 - y y, rounded once.  Products of bf16 numbers are exact in fp32; an instruction adds 16 of them with two roundings (one of them to below), eight waves and
     every slab's sum is added once, so a gradient is off by at most (2 x instructions of a slab + 8 + slabs) 2^-23 of its products' absolute sum; one
     position that is missing or counted twice moves all gradients of its channel, by 1 / 17000 of that sum."""
-    layers, patch = ((C, cin, 3), (C, cout, k), (FC, 2, 0)), k + 2
+    rect = isinstance(k, tuple)
+    layers, patch = (((C, cin, 3), (MP, 0, 2, 3), (FC, cout, 0), (FC, 2, 0)), 8) if rect else (((C, cin, 3), (C, cout, k), (FC, 2, 0)), k + 2)
+    (k, k2), (d, d2) = (k, (2, 3)) if rect else ((k, k), (1, 1))
     H, W = patch + 120, patch + 141
     net = mpcnn.Net(layers, 1, patch, mpcnn.BF16)
     plan = net.plan_describe(1, H, W, True)
@@ -183,14 +186,14 @@ def test_bf16_weight_gradient(cin, cout, k, kernel):
     net.set_params(params)
     net.seg_backward(torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda(), torch.from_numpy(labels).cuda())
     got = net.get_grads().astype(np.float64)
-    x, y = (torch.from_numpy(net.get_activation(1, H, W, i)[0]).double() for i in (0, 1))
+    x, y = (torch.from_numpy(net.get_activation(1, H, W, i)[0]).double() for i in ((1, 2) if rect else (0, 1)))
     net.close()
     R, Q = y.shape[:2]
     at = (patch - 1) // 2
     t = torch.from_numpy(labels[0, at:at + R, at:at + Q]).double()[..., None]
     dy = (t * torch.from_numpy(w[0]).double() * (1 - y * y)).float().bfloat16().double().reshape(-1, cout)
-    part = lambda u, v: x[u:u + R, v:v + Q].reshape(-1, cin)
-    taps = [(u, v) for u in range(k) for v in range(k)]
+    part = lambda u, v: x[u * d:u * d + R, v * d2:v * d2 + Q].reshape(-1, cin)
+    taps = [(u, v) for u in range(k) for v in range(k2)]
     want, mass = (torch.stack([f(dy).t().contiguous() @ f(part(u, v)) for u, v in taps], -1).flatten().numpy() for f in (lambda z: z, torch.abs))
     first = cin * 9 + cin
     bound = (2 * tiles * r * -(-c // 16) + slabs + 8) * 2.0 ** -23
@@ -198,3 +201,42 @@ def test_bf16_weight_gradient(cin, cout, k, kernel):
     assert bound < 1.0 / (R * Q) and np.any(want)
     bias = got[first + want.size:first + want.size + cout] - dy.sum(0).numpy()
     assert (np.abs(bias) <= (R * Q) * 2.0 ** -24 * dy.abs().sum(0).numpy()).all()
+
+
+# fp32 storage: chains of positions on either side of the line from which two parts are taken
+CHAINS = [(32, 64, 5, 58, 61, False), (16, 36, 5, 100, 110, False), (64, 128, 3, 200, 190, True), (20, 44, 4, 420, 390, True)]
+
+
+@pytest.mark.parametrize("cin,cout,k,R,Q,two", CHAINS)
+def test_fp32_weight_gradient(cin, cout, k, R, Q, two):
+    """Deltas that are known exactly: saturated classes, and a layer whose weights are so small that all slopes are 1.  A chunk of 16 positions is six instructions
+    of two roundings and a truncation each at most, so a gradient is off by at most (18 x chunks of a wave + 8 + slabs) 2^-24 of its products' absolute sum, and by
+    2^-22 for what two parts leave out of a product."""
+    layers, patch = ((C, cin, 3), (C, cout, k), (FC, 2, 0)), k + 2
+    H, W = R + patch - 1, Q + patch - 1
+    net = mpcnn.Net(layers, 1, patch)
+    line = [line for line in net.plan_describe(1, H, W, True).splitlines() if "weight gradient" in line][1]
+    assert "three parts per number" in line and ("or two of fp16" in line) == two, line
+    wk, r, c, slabs, tiles = [int(v) for v in re.search(r"x (\d+) waves .* tile (\d+) x (\d+), \d+ tiles in (\d+) slabs of (\d+)", line).groups()]
+    rng = np.random.default_rng(cin)
+    params = rng.uniform(-0.7, 0.7, net.param_count).astype(np.float32)
+    first = cin * 9 + cin
+    n = cout * cin * k * k
+    params[first:first + n + cout] *= 1e-12
+    w = np.zeros((2, cout), np.float32)
+    w[0] = rng.uniform(-1, 1, cout)
+    params[-2 * cout - 2:-2] = w.ravel()
+    params[-2:] = 1000, -1000
+    labels = rng.integers(0, 2, (1, H, W)).astype(np.int32)
+    net.set_params(params)
+    net.seg_backward(torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda(), torch.from_numpy(labels).cuda())
+    got = net.get_grads().astype(np.float64)[first:first + n]
+    x = torch.from_numpy(net.get_activation(1, H, W, 0)[0]).double()
+    net.close()
+    at = (patch - 1) // 2
+    dy = (torch.from_numpy(labels[0, at:at + R, at:at + Q]).double()[..., None] * torch.from_numpy(w[0]).double()).reshape(-1, cout)
+    taps = [x[u:u + R, v:v + Q].reshape(-1, cin) for u in range(k) for v in range(k)]
+    want, mass = (torch.stack([f(dy).t().contiguous() @ f(t) for t in taps], -1).flatten().numpy() for f in (lambda z: z, torch.abs))
+    assert (np.abs(got - want) <= ((18 * tiles * r * (c // 16) // wk + 8 + slabs) * 2.0 ** -24 + 2.0 ** -22) * mass).all()
+    # two parts in the 2-norm: 5e-8, measured over chains of 144 to 640 positions, and twice that
+    assert np.linalg.norm(got - want) <= 1e-7 * np.linalg.norm(want)
