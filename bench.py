@@ -20,7 +20,7 @@ the launch stream by the library's profile hooks over a repeat of the timed step
   `roofline`      the dominant matrix-core launch site family (conv forward, data gradient or
                   weight gradient): algorithmic flops / time against the MFMA peak of the
                   instruction that family runs on (fp32 157.3 TFLOP/s, bf16 2500 TFLOP/s; fp32
-                  products made of six bf16 products: a sixth of the latter);
+                  products made of three fp16 products: a third of the latter);
   `roofline_hbm`  the max-filter and routing passes: algorithmic bytes / time against 8 TB/s.
 `cpu_baseline` is the fp64 patch-by-patch oracle timed on this machine's host cores on a bounded
 sample of the same workload.
@@ -37,7 +37,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA = 157.3      # TFLOP/s, MI355X dense fp32 matrix
 PEAK_BF16_MFMA = 2500.0     # TFLOP/s, dense bf16 matrix
-PEAK_PARTS = PEAK_BF16_MFMA / 6   # TFLOP/s of fp32 products made of six bf16 products each
+PEAK_PARTS = PEAK_BF16_MFMA / 3   # TFLOP/s of fp32 products made of three fp16 products each (layers of short sums take six bf16 products)
 PEAK_HBM = 8000.0           # GB/s, HBM3E
 HEADLINE = 3
 # pixels the oracle is timed on (about 10 s on 16 threads for the headline, a few seconds for the rest)
