@@ -131,14 +131,14 @@ __host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4
 // Two fp16 parts of fp32 numbers.  Numbers are first made 2^n times as large (ranges.hpp), the same n for a whole tensor.
 // up x = x0 + x1 but for what x1's 11 bits do not hold: at most one last bit of x, 0 for three numbers of four (8 numbers at once, in pairs:
 // two multiplications, two conversions and two subtractions each)
-__device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2], float up)
+__device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2], const float (&up)[8])
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const f16x2 h = __builtin_convertvector((f32x2){up * x[2 * j], up * x[2 * j + 1]}, f16x2);
-        const f16x2 l = __builtin_convertvector((f32x2){fmaf(up, x[2 * j], -(float)h[0]), fmaf(up, x[2 * j + 1], -(float)h[1])}, f16x2);
+        const f16x2 h = __builtin_convertvector((f32x2){up[2 * j] * x[2 * j], up[2 * j + 1] * x[2 * j + 1]}, f16x2);
+        const f16x2 l = __builtin_convertvector((f32x2){fmaf(up[2 * j], x[2 * j], -(float)h[0]), fmaf(up[2 * j + 1], x[2 * j + 1], -(float)h[1])}, f16x2);
         p[0][j] = __builtin_bit_cast(unsigned, h);
         p[1][j] = __builtin_bit_cast(unsigned, l);
     }
@@ -281,7 +281,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
 #pragma unroll
                 for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
                 u32x4 p[P];
-                if constexpr (P == 2) split_halves(x, p, in_up);
+                if constexpr (P == 2) split_halves(x, p, {in_up, in_up, in_up, in_up, in_up, in_up, in_up, in_up});
                 else split_parts(x, p);
 #pragma unroll
                 for (int i = 0; i < P; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];

@@ -67,6 +67,7 @@ struct WgradPartsArgs {
     int ppg, tpg, ntg;   // planes and taps per group; groups along the taps (blockIdx.y = plane group * ntg + tap group)
     const unsigned* dy_peak;             // dY's dy_words words (ranges.hpp), or null: not known, or `in` is no output of a squashing function
     int dy_words, dy_margin;             // dY is at most 2^dy_margin times as large as they say
+    int logistic;                        // that function
     unsigned mg_nqh, mg_hwp, mg_txp, mg_tpg, mg_k2, mg_ntx, mg_nty, mg_d, mg_d2;   // ceil(2^32 / x)
 };
 
@@ -93,8 +94,93 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
     return g;
 }
 
+// ---- two parts: what deltas are raised by.  One power of two per map (column of the result, where it is undone), so that a map far below the others keeps its
+// bits.  The largest of a map's deltas is not known; that of all of them is (ranges.hpp), and a sample of positions shows what a map has.  One that reaches within
+// kWpSampled octaves of the largest of all is raised like that.  What was found in one below goes to 2^kWpPlace, with room for numbers 2^12 times as large;
+// if there are larger ones, infinities appear in the sums and three parts do the work again, as they do at once where the sample is not finite or nothing but zeros.
+// Two parts of a number have all their bits down to 2^-3 and an error of 2^-26 (rms) below, so of a map's deltas those that matter lose nothing.
+// 64 -> 128, 3 x 3, deltas 2^-20, 2^-24, 2^-30, 2^-40 of the others': error of a map's gradient 6e-7, 2e-6, 1e-3, 1 with one power of two for all, 1e-7 and less in each now.
+// 64 -> 100, 3 x 3, 213 x 213 positions: 42 us without samples, 45 with.
+constexpr int kWpSampled = 12, kWpPlace = 4, kWpSamples = 8;
+
+// Whether any thread of the workgroup says so (*word: in LDS, for this alone)
+__device__ __forceinline__ bool any_thread(bool yes, unsigned* word)
+{
+    __syncthreads();
+    if (threadIdx.x == 0) *word = 0;
+    __syncthreads();
+    if (yes) atomicOr(word, 1u);
+    __syncthreads();
+    const bool any = *word != 0;
+    __syncthreads();
+    return any;
+}
+// Bits of the largest magnitudes of 4 quads channels from c0 on (none past C, a multiple of 4) at kWpSamples * (512 / quads) positions spread over a tensor
+// [positions][C], left in most[] (which is clear)
+__device__ __forceinline__ void sample_maps(const float* t, long positions, int C, int c0, int quads, unsigned* most)
+{
+    for (int q0 = 0; q0 < quads; q0 += kWpThreads) {
+        const unsigned nq = quads - q0 < kWpThreads ? quads - q0 : kWpThreads, rows = kWpThreads / nq, row = threadIdx.x / nq, q = q0 + threadIdx.x - row * nq;
+        const int c = c0 + 4 * (int)q;
+        if (row < rows && c < C) {
+            const float stretch = (float)positions / (float)(kWpSamples * rows);
+            v4f v[kWpSamples];
+#pragma unroll
+            for (int j = 0; j < kWpSamples; ++j) {    // (all at once)
+                // (inside their stretches the positions are irregular: in step with no map's rows or columns)
+                const unsigned n = row + rows * j;
+                const long at = (long)(((float)n + (float)(n * 40503u & 0xffffu) * 0x1p-16f) * stretch);
+                v[j] = *reinterpret_cast<const v4f*>(t + (at < positions ? at : positions - 1) * C + c);
+            }
+            unsigned m[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < kWpSamples; ++j)
+#pragma unroll
+                for (int z = 0; z < 4; ++z) {
+                    const unsigned b = bits_of(v[j][z]) & 0x7fffffffu;   // (a NaN is above infinity)
+                    m[z] = b > m[z] ? b : m[z];
+                }
+#pragma unroll
+            for (int z = 0; z < 4; ++z) atomicMax(most + 4 * q + z, m[z]);
+        }
+    }
+}
+// The factors of this workgroup's columns with the slab's sign, left in up[32 wn] (three words behind them are used too); `one`: that of all columns but those that need their own.
+// Logistic outputs may be small in a whole map: all of this workgroup's have to reach 2^-12 in the sample.
+enum Raised { kNotRaised, kRaisedAlike, kRaisedEach };
+__device__ __forceinline__ Raised raise_maps(const WgradPartsArgs& a, float turn, float* up, unsigned* most, float& one)
+{
+    const int cols = 32 * a.wn, c0 = 16 * ((blockIdx.y / a.ntg) * a.ppg), n = a.Ci - c0 < 16 * a.ppg ? a.Ci - c0 : 16 * a.ppg;
+    unsigned* const some = reinterpret_cast<unsigned*>(up + cols);   // columns that are not 0 / numbers that do not suit / columns with a factor of their own
+    for (int i = threadIdx.x; i < cols + (a.logistic ? n : 0); i += kWpThreads) most[i] = 0;
+    if (threadIdx.x < 3) some[threadIdx.x] = 0;
+    __syncthreads();
+    sample_maps(static_cast<const float*>(a.dY), (long)a.B * a.Ho * a.Wo, a.Co, cols * blockIdx.z, cols / 4, most);
+    if (a.logistic) sample_maps(static_cast<const float*>(a.in), (long)a.B * a.Hi * a.Wi, a.Ci, c0, n / 4, most + cols);
+    const unsigned peak = peak_of(a.dy_peak, a.dy_words);
+    const int all = raise_of(peak, a.dy_margin);
+    __syncthreads();
+    for (int i = threadIdx.x; i < cols + (a.logistic ? n : 0); i += kWpThreads) {
+        const unsigned m = most[i];
+        bool odd = peak >= kNoPeak || m >= kNoPeak;
+        if (i < cols) {
+            const int e = (int)(m >> 23) - 127, own = kWpPlace - e < 127 ? kWpPlace - e : 127;
+            const bool alike = e + all >= 14 - kWpSampled || cols * (int)blockIdx.z + i >= a.Co;
+            up[i] = turn * power_of_two(alike ? all : own);
+            if (m > 0) some[0] = 1;
+            if (!alike) some[2] = 1;
+        } else
+            odd |= m < bits_of(0x1p-12f);
+        if (odd) some[1] = 1;
+    }
+    __syncthreads();
+    one = turn * power_of_two(all);
+    return !some[0] || some[1] ? kNotRaised : some[2] ? kRaisedEach : kRaisedAlike;
+}
+
+// Two parts: false if a sum is not finite (nothing is lost: three parts write every result again)
 template <int PM, int P, typename T>
-__device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigned dy_peak)
+__device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
 {
     constexpr int kWpPos = wp_pos(P);
     constexpr int SI = kWpItems;
@@ -156,9 +242,12 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
     // signs of this slab's deltas (see Accuracy above)
     const float turn = blockIdx.x & 1 ? -1.f : 1.f;
     // what numbers are split after being multiplied by, and what takes their products' sums back
-    const int in_raise = P == 2 ? kActRaise : 0, dy_raise = P == 2 ? raise_of(dy_peak, a.dy_margin) : 0;
-    const float in_up = P == 2 ? power_of_two(in_raise) : kPartsUp, dy_up = turn * (P == 2 ? power_of_two(dy_raise) : kPartsUp);
-    const Lower down = P == 2 ? lower_by(in_raise + dy_raise) : Lower{P == 3 ? kPartsDown : 1.f, 1.f};
+    const float in_up = P == 2 ? power_of_two(kActRaise) : kPartsUp;
+    float dy_up = turn * kPartsUp;
+    bool each = false;                                // two parts: not all columns' factors are dy_up (uniform)
+    // (two parts: the columns' factors and three words lie behind two parts' two buffers, 128 wn + 12 bytes; the plan has room for three parts' buffers, whose 4 wn delta
+    // planes alone are larger by 32 * 16 + 288 bytes and more each)
+    float* const col_up = reinterpret_cast<float*>(ldsb + 2 * g.buf_b);
     float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
 #pragma unroll
     for (int j = 0; j < 8; ++j) bsum[j] = 0.f;
@@ -228,8 +317,15 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
                 for (int j = 0; j < 8; ++j) bsum[j] += x[j];
             u32x4 p[P];
             const float up = first >= g.nh ? dy_up : in_up;
-            if constexpr (P == 2) split_halves(x, p, up);
-            else if constexpr (P == 3) split_parts(x, p, up);
+            if constexpr (P == 2) {
+                if (first >= g.nh && each) {
+                    float ups[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) ups[j] = col_up[8 * qd + j];
+                    split_halves(x, p, ups);
+                } else
+                    split_halves(x, p, {up, up, up, up, up, up, up, up});
+            } else if constexpr (P == 3) split_parts(x, p, up);
             else p[0] = pre[u][0] ^ (first >= g.nh && blockIdx.x & 1 ? 0x80008000u : 0u);   // (the deltas' turned signs)
             char* dst = buf + i_dst[u];
 #pragma unroll
@@ -336,10 +432,15 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
     int tile_end = tile_begin + a.tiles_per_slab;
     if (tile_end > a.tiles_total) tile_end = a.tiles_total;
     const bool early = wave < 4;
-    if (tile_begin < tile_end) {
-        issue(tile_begin, true);
-        to_lds(ldsb);
+    if (tile_begin < tile_end) issue(tile_begin, true);
+    float mine = 0.f;                                 // two parts: the factor of this lane's column of the result
+    if constexpr (P == 2) {
+        const int raised = __builtin_amdgcn_readfirstlane(raise_maps(a, turn, col_up, reinterpret_cast<unsigned*>(lds), dy_up));
+        if (raised == kNotRaised) return false;
+        each = raised == kRaisedEach;
+        mine = col_up[32 * nidx + (lane & 31)];
     }
+    if (tile_begin < tile_end) to_lds(ldsb);
     if (early) issue(tile_begin + 1 < tile_end ? tile_begin + 1 : tile_begin, tile_begin + 1 < tile_end);
     __syncthreads();
     int cur = 0;
@@ -389,13 +490,15 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
     const int groups = gridDim.y;
     const long plen = (long)groups * a.RT * a.Nt * 1024 + a.Nt * 32;
     float* out = a.partial + (long)blockIdx.x * plen;
+    bool odd = false;
     if (active && kidx == 0) {
         float z = 0.f;                                // NaN as soon as one of the sums is not finite
 #pragma unroll
         for (int p = 0; p < PM; ++p)
 #pragma unroll
             for (int r = 0; r < 16; ++r) z = fmaf(acc[p][r], 0.f, z);
-        const bool odd = P == 3 && __any(z != z);      // (two parts: every number is finite, and no sum overflows)
+        odd = __any(z != z);
+        const Lower down = P == 2 ? lower_by(kActRaise + (int)(bits_of(mine) >> 23 & 255) - 127) : Lower{P == 3 ? kPartsDown : 1.f, 1.f};
 #pragma unroll
         for (int p = 0; p < PM; ++p)
             if (midx * PM + p < a.RT) {
@@ -478,6 +581,7 @@ __device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigne
             if (bt < a.Nt) out[(long)groups * a.RT * a.Nt * 1024 + bt * 32 + (tid & 31)] = s;
         }
     }
+    return P != 2 || !any_thread(odd, reinterpret_cast<unsigned*>(lds));
 }
 
 // fp32 storage: in two parts where both tensors suit them
@@ -485,12 +589,9 @@ template <int PM, typename T>
 __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsArgs a)
 {
     if constexpr (sizeof(T) == 4) {
-        unsigned peak = kNoPeak;
-        if (a.dy_peak) peak = peak_of(a.dy_peak, a.dy_words);
-        if (peak < kNoPeak) wgrad_parts_body<PM, 2, T>(a, peak);
-        else wgrad_parts_body<PM, 3, T>(a, peak);
+        if (!a.dy_peak || !wgrad_parts_body<PM, 2, T>(a)) wgrad_parts_body<PM, 3, T>(a);
     } else
-        wgrad_parts_body<PM, 1, T>(a, 0);
+        wgrad_parts_body<PM, 1, T>(a);
 }
 
 }  // namespace mpcnn

@@ -240,3 +240,96 @@ def test_fp32_weight_gradient(cin, cout, k, R, Q, two):
     assert (np.abs(got - want) <= ((18 * tiles * r * (c // 16) // wk + 8 + slabs) * 2.0 ** -24 + 2.0 ** -22) * mass).all()
     # two parts in the 2-norm: 5e-8, measured over chains of 144 to 640 positions, and twice that
     assert np.linalg.norm(got - want) <= 1e-7 * np.linalg.norm(want)
+
+
+def known_deltas(cin, cout, k, R, Q, class_weights, bias=None, pixw=None, logistic=False):
+    """A layer's weight gradient [maps, inputs, taps], the same in 64 bits, and its plan, from deltas that are known exactly: saturated classes, and a layer whose weights are so
+    small that all slopes are 1 (logistic: 1/4).  The inputs are the library's own."""
+    layers, patch = ((C, cin, 3), (C, cout, k), (FC, 2, 0)), k + 2
+    H, W = R + patch - 1, Q + patch - 1
+    net = mpcnn.Net(layers, 1, patch)
+    net.set_activation("logistic" if logistic else "tanh")
+    rng = np.random.default_rng(cin)
+    params = rng.uniform(-0.7, 0.7, net.param_count).astype(np.float32)
+    first = cin * 9 + cin
+    n = cout * cin * k * k
+    if bias is not None:
+        params[cin * 9:first] = bias
+    params[first:first + n + cout] *= 1e-12
+    w = np.zeros((2, cout), np.float32)
+    w[0] = class_weights
+    params[-2 * cout - 2:-2] = w.ravel()
+    params[-2:] = 1000, -1000
+    labels = rng.integers(0, 2, (1, H, W)).astype(np.int32)
+    net.set_params(params)
+    plan = [line for line in net.plan_describe(1, H, W, True).splitlines() if "weight gradient" in line][1]
+    net.seg_backward(torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda(), torch.from_numpy(labels).cuda(),
+                     pixw=None if pixw is None else torch.from_numpy(pixw).cuda())
+    got = net.get_grads().astype(np.float64)[first:first + n].reshape(cout, cin, k * k)
+    x = torch.from_numpy(net.get_activation(1, H, W, 0)[0]).double()
+    net.close()
+    at = (patch - 1) // 2
+    t = torch.from_numpy(labels[0, at:at + R, at:at + Q]).double()
+    if pixw is not None:
+        t = t * torch.from_numpy(pixw[0, at:at + R, at:at + Q]).double()
+    dy = (t[..., None] * torch.from_numpy(w[0]).double()).reshape(-1, cout) * (0.25 if logistic else 1.0)
+    want = torch.stack([dy.t().contiguous() @ x[u:u + R, v:v + Q].reshape(-1, cin) for u in range(k) for v in range(k)], -1).numpy()
+    return got, want, plan
+
+
+def by_map(got, want, axes):
+    return np.sqrt(((got - want) ** 2).sum(axes)) / np.sqrt((want ** 2).sum(axes))
+
+
+# Two parts of a delta are off by 2^-23 of it at most, here the same for all positions of a map whose deltas are 0 or one number; activations, products left
+# out and sums bring 5e-8 in the 2-norm (measured over chains of 144 to 640 positions, csrc/mpcnn.hip, kHalfChain)
+MAP_BOUND = 2.0 ** -23 + 5e-8
+WGRAD = (64, 128, 3, 200, 190)
+
+
+def test_weight_gradient_of_maps_far_below_the_others():
+    """Deltas of every eighth map 2^-9 to 2^-100 of the others': each map's gradient as close to 64 bits as the others'."""
+    rng = np.random.default_rng(1)
+    w = rng.choice([-1.0, 1.0], 128) * rng.uniform(0.5, 1, 128)
+    w[::8] *= 2.0 ** -np.array([9, 11, 12, 13, 14, 16, 18, 20, 22, 24, 26, 30, 35, 40, 60, 100])
+    got, want, plan = known_deltas(*WGRAD, w)
+    assert "or two of fp16" in plan, plan
+    err = by_map(got, want, (1, 2))
+    print("maps 2^-9 .. 2^-100 of the others:", " ".join("%.1e" % e for e in err[::8]), "others:", "%.1e" % np.delete(err, np.s_[::8]).max(), flush=True)
+    assert err.max() <= MAP_BOUND
+
+
+def test_weight_gradient_of_maps_that_stand_out_in_few_positions():
+    """Pixel weights of 2^-17 but for three positions of 1, and some maps 2^-20 of the others: what a sample of positions shows of a map is far from its largest.  One of
+    the three stands in an accumulator for the rest of a slab, 10 chunks of six products with two roundings each: sqrt(120 / 3) 2^-24 besides."""
+    rng = np.random.default_rng(2)
+    w = rng.choice([-1.0, 1.0], 128) * rng.uniform(0.5, 1, 128)
+    w[::8] *= 2.0 ** -20
+    w[1] = 0
+    pixw = np.full((1, 204, 194), 2.0 ** -17, np.float32)
+    pixw[0, [40, 90, 177], [61, 33, 150]] = 1
+    got, want, _ = known_deltas(*WGRAD, w, pixw=pixw)
+    assert not got[1].any()
+    keep = np.arange(128) != 1
+    assert by_map(got[keep], want[keep], (1, 2)).max() <= MAP_BOUND + np.sqrt(40) * 2.0 ** -24
+
+
+def test_weight_gradient_of_few_labels():
+    """Deltas that are zero but in a corner that a sample may not see."""
+    pixw = np.zeros((1, 204, 194), np.float32)
+    pixw[0, 150:155, 11:17] = 1
+    got, want, _ = known_deltas(*WGRAD, np.linspace(0.1, 1, 128), pixw=pixw)
+    assert by_map(got, want, (1, 2)).max() <= MAP_BOUND
+
+
+@pytest.mark.parametrize("low", [False, True])
+def test_weight_gradient_of_logistic_maps(low):
+    """Logistic outputs keep their precision however small they are: maps of biases 0 to -60 (outputs down to 2^-87), every input map by itself."""
+    bias = np.zeros(64)
+    if low:
+        bias[::4] = -np.array([4, 6, 8, 10, 12, 14, 16, 18, 20, 22, 24, 28, 32, 40, 50, 60])
+    got, want, plan = known_deltas(*WGRAD, np.random.default_rng(3).uniform(0.2, 1, 128), bias=bias, logistic=True)
+    assert "or two of fp16" in plan, plan
+    err = by_map(got, want, (0, 2))
+    print("input maps:", " ".join("%.1e" % e for e in err[::4]), flush=True)
+    assert err.max() <= MAP_BOUND and by_map(got, want, (1, 2)).max() <= MAP_BOUND
