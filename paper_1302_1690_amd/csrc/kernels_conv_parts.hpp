@@ -27,14 +27,16 @@
 // fp32 storage, sums of kHalfLeast products and more: two fp16 parts per number (11 + 11 bits and a sign), three products of
 // v_mfma_f32_32x32x16_f16, x0 y0 in one accumulator and x0 y1 + x1 y0 in another - half the instructions of three bf16 parts.  Two parts lose
 // the last bit of one number in four, and x1 y1 is left out: 7.5e-8 of a sum of products of random signs, whatever its length.  That is
-// more than three parts lose by rounding in short sums and less in long ones, if those roundings become fewer at the same time: after a run of 8 to 16 steps (half_run)
+// more than three parts lose by rounding in short sums and less in long ones, if those roundings become fewer at the same time: after a run of steps (half_run)
 // the leading products' accumulator is added to a total and starts again from 0.  Against 64-bit sums, rms relative, three parts / two without
 // runs / two, products of random signs: K = 64 4.5e-8 / 8.9e-8 / 8.9e-8; 288 8.5e-8 / 1.30e-7 / 1.09e-7; 400 1.01e-7 / 1.47e-7 / 1.12e-7; 576 1.23e-7 / 1.69e-7 / 1.15e-7;
 // 800 1.47e-7 / 1.94e-7 / 1.17e-7; 1600 2.18e-7 / 2.64e-7 / 1.25e-7; of equal signs, K = 576, 1600: 1.23e-7 / 1.19e-7 / 5.2e-8, 2.22e-7 / 2.21e-7 / 6.4e-8.
 // Hence kHalfLeast, where the two are equal.  Errors of whole calls are what they were or smaller (gradients of a pool-free net, 96 x 110, bias gradients over the root
 // of the deltas' squares: 1.25e-6 .. 1.55e-6 with three parts, 4.4e-7 .. 5.4e-7 with two).
-// fp16 reaches from 2^-24 to 2^16, so numbers are raised by powers of two, one per tensor (ranges.hpp); numbers below 2^-16 of a tensor's largest lose bits below
-// 2^-40 of that.  Where this could matter - weights most of which are that small, infinities - the launch takes three parts, as do
+// fp16 reaches from 2^-24 to 2^16, so weights and deltas are raised by powers of two, one per tensor, and second parts by 2^11 more (their products have an accumulator of their
+// own): numbers below 2^-28 of a tensor's largest lose bits below 2^-51 of that.  Activations stay as they are: tanh's are multiples of 2^-24, of logistic ones what is below 2^-36 is
+// lost.  The launch takes three parts where this could matter or not be known (infinities; a map's worth of weights 2^-26 of the largest, weights_wide; logistic outputs under weights of 16 and more,
+// weights_large; deltas that such weights have made, ranges.hpp), as do
 // shorter sums: a uniform choice at the kernel's start, from what the weights' packing and the writer of the deltas left, so a plan holds for either.
 // bf16 storage.  One part, one product, one accumulator: same kernel.
 //
@@ -81,7 +83,8 @@
 //
 // Summation order is the step order for every output element, whatever the tiling: equal inputs
 // give bit-equal outputs (exact pooling ties stay exact) and a position's value does not depend on
-// how the map is cut.
+// how the map is cut.  A data gradient in two parts does depend on the tensor's largest delta: by powers of two that change no bit of numbers down to 2^-28 of it, and by the choice of three parts
+// for the whole tensor where it is infinite.
 #pragma once
 #include <type_traits>
 
@@ -129,8 +132,9 @@ __host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps
 __host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4 : 8; }
 
 // Two fp16 parts of fp32 numbers.  Numbers are first made 2^n times as large (ranges.hpp), the same n for a whole tensor.
-// up x = x0 + x1 but for what x1's 11 bits do not hold: at most one last bit of x, 0 for three numbers of four (8 numbers at once, in pairs:
-// two multiplications, two conversions and two subtractions each)
+// up x = x0 + x1 / LOW_UP but for what x1's 11 bits do not hold: at most one last bit of x, 0 for three numbers of four (8 numbers at once, in pairs:
+// two multiplications, two conversions and two subtractions each; two multiplications more where LOW_UP is not 1)
+template <bool LOW_UP>
 __device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2], const float (&up)[8])
 {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -138,13 +142,15 @@ __device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2],
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const f16x2 h = __builtin_convertvector((f32x2){up[2 * j] * x[2 * j], up[2 * j + 1] * x[2 * j + 1]}, f16x2);
-        const f16x2 l = __builtin_convertvector((f32x2){fmaf(up[2 * j], x[2 * j], -(float)h[0]), fmaf(up[2 * j + 1], x[2 * j + 1], -(float)h[1])}, f16x2);
+        f32x2 rest = {fmaf(up[2 * j], x[2 * j], -(float)h[0]), fmaf(up[2 * j + 1], x[2 * j + 1], -(float)h[1])};
+        if constexpr (LOW_UP) rest *= kLowUp;
+        const f16x2 l = __builtin_convertvector(rest, f16x2);
         p[0][j] = __builtin_bit_cast(unsigned, h);
         p[1][j] = __builtin_bit_cast(unsigned, l);
     }
 }
-// Steps between two additions of a tile's leading sums to its total (kernel below): whole filter rows of at most 16 taps, or whole chunks of
-// fewer taps until they are 8 steps.  A function of the filter alone.  `period`: steps after which the lengths repeat.
+// Steps between two additions of a tile's leading sums to its total (kernel below): whole chunks of at most 16 taps until they are 8 steps (8 to 16), of larger filters whole rows while they are 16 taps at
+// most (12 to 16) or, of those with 8 rows or 9 columns and more, a row (4 to k2 steps).  A function of the filter alone.  `period`: steps after which the lengths repeat.
 constexpr int kHalfLeast = 512;   // fewest products of a sum that two fp16 parts are taken for
 __host__ __device__ inline bool half_filter(int k, int k2) { return k * k2 >= 4 && (k < 8 || k2 >= 4); }   // blocks of four steps at least
 struct HalfRun { int period, length; };
@@ -179,12 +185,15 @@ __device__ __forceinline__ unsigned parts_div(unsigned n, unsigned magic, unsign
     return x == 1 ? n : __umulhi(n, magic);   // n / x for n * x < 2^32, magic = ceil(2^32 / x)
 }
 
-// Weights that two fp16 parts do not suit: not finite, or with more than half a sum's number of them 2^-14 and less of the largest
-// (each loses the bits below 2^-40 of the largest, which is more than fp32 does once it is below 2^-16 of it)
+// Weights that two fp16 parts do not suit: not finite, or with half a sum's number and more, counted over the layer, kSmallOctaves below the largest (one
+// output or input map of such weights is enough; a few of them beside larger ones do not matter to any sum)
 __device__ __forceinline__ bool weights_wide(const ConvArgs& a)
 {
     return a.w_peak && (a.w_peak[0] >= kNoPeak || 2 * a.w_peak[1] >= (unsigned)a.small_limit);
 }
+// Two parts of activations as they are hold multiples of 2^-24, which tanh leaves, whole; of logistic outputs, however small, they lose bits below 2^-36 (rms 2^-37): of no account
+// in a sum that is squashed, known to 2^-24, but under weights that make up for it.  10^4 products and weights of 16 are off by 2^-26.
+__device__ __forceinline__ bool weights_large(const ConvArgs& a) { return a.logistic && a.w_peak[0] >= bits_of(16.f); }
 
 template <typename T, int P, bool BACK, int CB, int WO, int WP, int MO, int MP>
 __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_peak)
@@ -215,7 +224,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     const bool live = oc0 < a.Co;                     // uniform for the wave
 
     // ---- two parts: what numbers are raised by, and their products' sums lowered by
-    const int in_raise = P != 2 ? 0 : BACK ? raise_of(in_peak, a.in_margin) : kActRaise;
+    const int in_raise = P == 2 && BACK ? raise_of(in_peak, a.in_margin) : 0;   // (activations as they are)
     const float in_up = P == 2 ? power_of_two(in_raise) : 1.f;
     const Lower down = P == 2 ? lower_by(in_raise + raise_of(*a.w_peak, 0)) : Lower{1.f, 1.f};
 
@@ -281,7 +290,10 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
 #pragma unroll
                 for (int j = 0; j < 8; ++j) x[j] = __builtin_bit_cast(v4f, pre[u][j >> 2])[j & 3];
                 u32x4 p[P];
-                if constexpr (P == 2) split_halves(x, p, {in_up, in_up, in_up, in_up, in_up, in_up, in_up, in_up});
+                if constexpr (P == 2) {
+                    const float up = BACK ? in_up : 1.f;
+                    split_halves<true>(x, p, {up, up, up, up, up, up, up, up});
+                }
                 else split_parts(x, p);
 #pragma unroll
                 for (int i = 0; i < P; ++i) *reinterpret_cast<u32x4*>(dst + 32 * i) = p[i];
@@ -843,8 +855,12 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                     for (int o = 0; o < MO; ++o)
 #pragma unroll
                         for (int p = 0; p < MP; ++p) {
-                            acc[o][p] += low[o][p];
-                            if constexpr (P == 2) acc[o][p] += tot[o][p];
+                            if constexpr (P == 2) {
+                                acc[o][p] += tot[o][p];
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) acc[o][p][r] = fmaf(low[o][p][r], kLowDown, acc[o][p][r]);   // (as whole vectors: spills)
+                            } else
+                                acc[o][p] += low[o][p];
                         }
                 if constexpr (P == 3) {
                     float z = 0.f;                    // NaN as soon as one of the sums is not finite
@@ -906,7 +922,7 @@ __global__ __launch_bounds__(kPartsThreads, parts_wgs(sizeof(T) == 4 ? 3 : 1, MO
 {
     if constexpr (sizeof(T) == 4) {
         unsigned peak = kNoPeak;
-        if (a.wpack2) peak = weights_wide(a) ? kNoPeak : BACK ? peak_of(a.in_peak, a.in_words) : 0;
+        if (a.wpack2) peak = weights_wide(a) || (!BACK && weights_large(a)) ? kNoPeak : BACK ? peak_of(a.in_peak, a.in_words) : 0;
         if (peak < kNoPeak) conv_parts_body<T, 2, BACK, CB, WO, WP, MO, MP>(a, peak);
         else conv_parts_body<T, 3, BACK, CB, WO, WP, MO, MP>(a, peak);
     } else

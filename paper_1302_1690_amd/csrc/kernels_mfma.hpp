@@ -19,7 +19,7 @@ enum ConvMode { kFwdTanh = 0, kFwdLinear = 1, kDgradTanh = 2, kDgradPlain = 3 };
 struct ConvArgs {
     // tensors are fp32 or bf16 (the kernel's template parameter T)
     const void* in;      // [B][Hi][Wi][Cr]   tensor the taps read (activations, or deltas for dgrad)
-    const v4f* wpack;    // weights in step order (pack_parts_kernel)
+    const v4f* wpack;    // weights in step order (pack_weights_kernel)
     const float* bias;   // [Co]   (forward modes)
     const void* act;     // [B][Ho][Wo][Co] tanh output at the positions written (kDgradTanh)
     void* out;           // [B][Ho][Wo][Co]

@@ -82,12 +82,13 @@ __device__ __forceinline__ void pack_segment(const PackArgs& a, const PackSeg& s
             } else {
                 if (c < Co && oo < Ci) v = W[((long)(kk - 1 - tap) * Ci + oo) * Co + c];
             }
-            if (sg.first && peak < kNoPeak) small += v != 0.f && bits_of(fabsf(v)) < peak && (peak - bits_of(fabsf(v))) >> 23 >= 14;   // (14 octaves and more below)
+            if (sg.first && peak < kNoPeak) small += v != 0.f && bits_of(fabsf(v)) < peak && (peak - bits_of(fabsf(v))) >> 23 >= kSmallOctaves;
             if constexpr (P != 1) v *= up;
 #pragma unroll
             for (int i = 0; i < P; ++i) {        // three parts: v is their sum, exactly
                 parts[i][s] = (Part)v;
                 v -= (float)parts[i][s];
+                if constexpr (P == 2) v *= kLowUp;
             }
         }
 #pragma unroll

@@ -322,9 +322,9 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
                     float ups[8];
 #pragma unroll
                     for (int j = 0; j < 8; ++j) ups[j] = col_up[8 * qd + j];
-                    split_halves(x, p, ups);
+                    split_halves<false>(x, p, ups);
                 } else
-                    split_halves(x, p, {up, up, up, up, up, up, up, up});
+                    split_halves<false>(x, p, {up, up, up, up, up, up, up, up});
             } else if constexpr (P == 3) split_parts(x, p, up);
             else p[0] = pre[u][0] ^ (first >= g.nh && blockIdx.x & 1 ? 0x80008000u : 0u);   // (the deltas' turned signs)
             char* dst = buf + i_dst[u];
