@@ -36,7 +36,7 @@
 // fp16 reaches from 2^-24 to 2^16, so weights and deltas are raised by powers of two, one per tensor, and second parts by 2^11 more (their products have an accumulator of their
 // own): numbers below 2^-28 of a tensor's largest lose bits below 2^-51 of that.  Activations stay as they are: tanh's are multiples of 2^-24, of logistic ones what is below 2^-36 is
 // lost.  The launch takes three parts where this could matter or not be known (infinities; a map's worth of weights 2^-26 of the largest, weights_wide; logistic outputs under weights of 16 and more,
-// weights_large; deltas that such weights have made, ranges.hpp), as do
+// weights_large; deltas that such weights, or such of the class layer, have made, ranges.hpp), as do
 // shorter sums: a uniform choice at the kernel's start, from what the weights' packing and the writer of the deltas left, so a plan holds for either.
 // bf16 storage.  One part, one product, one accumulator: same kernel.
 //

@@ -671,7 +671,28 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
         b += sb;
     }
     unsigned most = 0;
-    if constexpr (TRAIN && sizeof(T) == 4) most = wave_largest(bits_of(peak));
+    if constexpr (TRAIN && sizeof(T) == 4) {
+        most = wave_largest(bits_of(peak));
+        if (a.peak) {
+            // a map of which the classes see far less than of another has deltas that far below the other's: not for two parts of one raised power (as the
+            // data gradient's kernel, weights_wide)
+            unsigned large = 0, small = 0;            // (small: turned round, so that the smallest comes out as the largest)
+#pragma unroll
+            for (int v = 0; v < KV; ++v)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int o = 0; o < NCLS; ++o) m = larger(m, w[v][s][o]);
+                    if (m > 0.f) {
+                        large = bits_of(m) > large ? bits_of(m) : large;
+                        small = kNoPeak - bits_of(m) > small ? kNoPeak - bits_of(m) : small;
+                    }
+                }
+            large = wave_largest(large); small = kNoPeak - wave_largest(small);
+            if (large > small && (large - small) >> 23 >= (unsigned)kSmallOctaves) most = kNoPeak;
+        }
+    }
     if (TRAIN) {
         // sum the 16 position groups of the workgroup: 4 per wave by shuffles, waves through LDS
         constexpr int NV = KV * 4 * NCLS + NCLS;

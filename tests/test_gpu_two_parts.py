@@ -110,14 +110,15 @@ def test_runs_of_every_length(k, c0, c1):
 # how the numbers of a layer are spread, and whose gradients show it
 SPREADS = {"tiny_input_map": (2.0 ** -24, [(0, "out", 3), (1, "in", 3)]), "tinier_input_map": (2.0 ** -60, [(0, "out", 3), (1, "in", 3)]), "tiny_output_map": (2.0 ** -24, [(1, "out", 7), (2, "in", 7)]),
            "one_large_weight": (2.0 ** 20, []), "a_large_map": (2.0 ** 30, []), "class_weight": (2.0 ** -30, [(2, "out", 9)]),
-           "class_weight_and_its_own_maps": (2.0 ** -30, [(2, "out", 9)] + [(1, "out", i) for i in range(4)])}
+           "class_weight_and_its_own_maps": (2.0 ** -30, [(2, "out", 9)] + [(1, "out", i) for i in range(4)]),
+           "tiny_class_weight_and_its_own_maps": (2.0 ** -60, [(2, "out", 9)] + [(1, "out", i) for i in range(4)])}
 
 
 @pytest.mark.parametrize("what", list(SPREADS))
 @pytest.mark.parametrize("logistic", [False, True])
 def test_numbers_that_do_not_suit_two_parts(what, logistic):
     """Input maps whose weights are 2^-24 and 2^-60 of the others, an output map of which the layer above sees 2^-24, one weight of 2^20, a map 2^30 times the others, a hidden unit whose
-    class weights are 2^-30 of the others, and one on which maps of the layer below depend alone.  Layers as a whole (bound), and the maps concerned by themselves: labels are random, so that a map's
+    class weights are 2^-30 or 2^-60 of the others, and one on which maps of the layer below depend alone.  Layers as a whole (bound), and the maps concerned by themselves: labels are random, so that a map's
     gradient over N positions is what is left of N terms, of the order of their root, and errors that all positions share (2e-7 of a term, at most 4e-7) may be sqrt(N) as large."""
     hidden = 128
     layers, patch, params, image, labels = case(3, 60, 64, 70 if "large" in what else 200, hidden=hidden)
