@@ -682,6 +682,11 @@ void plan_peaks(const mpcnn_net* net, Geom* g)
     }
 }
 
+// Which launches of a layer may work in two fp16 parts: input bounded by a squashing function, deltas whose largest magnitude is noted
+bool squashed_input(const Geom& g, size_t l) { return l > 0 && g.squashed[l - 1]; }
+bool two_part_forward(const mpcnn_net* net, const Geom& g, size_t l) { return net->layers[l].fwd_half && squashed_input(g, l); }
+bool two_part_dgrad(const mpcnn_net* net, const Geom& g, size_t l) { return net->layers[l].dgrad_half && g.delta_peak[l] >= 0; }
+
 bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g, bool mirrored = false,
                bool fixed_partials = false)
 {
@@ -724,15 +729,21 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
             if (ly.dgrad_mfma && l > 0)
                 g->dgrad[l] = plan_conv_parts(B, c, in_r, in_c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cout, ly.dgrad_rpad, ly.cin, ly.dgrad_ct,
                                               net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.dgrad_half ? 3 : 6, es, true, net->hint_pt, net->hint_mp);
-            if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * r * c * ly.cout * ly.k * ly.k2 * ly.cin >= parts_wgrad_least(ly, net->bf16))
-                g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, r, c, net->bf16, net->halves);
-            if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, r, c, net->bf16);
-            const WgradPlan& w = g->wgrad[l];
-            g->partial_n[l] = w.ok ? w.slabs : w.chunks;
-            g->partial_len[l] = w.plen;
         }
     }
     if (r != H - net->patch + 1 || c != W - net->patch + 1) return false;
+    plan_peaks(net, g);
+    for (size_t l = 0; training && l < L; ++l) {
+        const Layer& ly = net->layers[l];
+        if (ly.kind == MPCNN_MP || ly.class_fused) continue;
+        const int in_r = l ? g->rows[l - 1] : H, in_c = l ? g->cols[l - 1] : W, out_r = g->rows[l], out_c = g->cols[l];
+        if (wgrad_parts_layer(ly, net->bf16) && 2.0 * B * out_r * out_c * ly.cout * ly.k * ly.k2 * ly.cin >= parts_wgrad_least(ly, net->bf16))
+            g->wgrad[l] = plan_wgrad_parts(ly, B, in_c, out_r, out_c, net->bf16, squashed_input(*g, l) && g->delta_peak[l] >= 0);
+        if (!g->wgrad[l].ok) g->wgrad[l] = plan_wgrad(ly, B, in_r, in_c, out_r, out_c, net->bf16);
+        const WgradPlan& w = g->wgrad[l];
+        g->partial_n[l] = w.ok ? w.slabs : w.chunks;
+        g->partial_len[l] = w.plen;
+    }
     g->l0_fused = false;
     if (training && L >= 2) {
         const Layer& l0 = net->layers[0];
@@ -824,7 +835,6 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         for (size_t l = 0; l < L; ++l) g->act_off[l] = buf[l & 1];
     }
     g->loss_partial_off = off; off = align_up(off + sizeof(double) * kLossBlocks);
-    plan_peaks(net, g);
     if (net->halves && training) { g->delta_words_off = off; off = align_up(off + sizeof(unsigned) * mpcnn::kDeltaWords * L); }
     g->total = off;
     g->label_h = H; g->probs_rows = r; g->accumulate = false;
@@ -1148,7 +1158,7 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.mode = ly.tanh_out ? kFwdTanh : kFwdLinear; a.logistic = net->logistic;
                 dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.fwd_ct.split);
                 parts_grid(&a, &grid, tp); a.wraw = Wk;
-                if (ly.fwd_half && l > 0 && g.squashed[l - 1]) {
+                if (two_part_forward(net, g, l)) {
                     weights_of(&a, net, l);
                     a.wpack2 = (const v4f*)(net->d_packs + ly.fwd_half_off);
                 }
@@ -1316,7 +1326,7 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                     a.Nt = wp.Nt; a.RT = wp.RT; a.wm = wp.wm; a.wn = wp.wn; a.wk = wp.wk;
                     a.ppg = wp.ppg; a.tpg = wp.tpg; a.ntg = wp.ntg;
                     a.dy_peak = delta_words(g, ws, li); a.dy_words = g.delta_words[li]; a.dy_margin = g.delta_margin[li]; a.logistic = net->logistic;
-                    if (li == 0 || !g.squashed[li - 1] || !wp.two) a.dy_peak = nullptr;
+                    if (!wp.two) a.dy_peak = nullptr;
                     a.mg_nqh = magic_of(2 * wp.ppg); a.mg_hwp = magic_of(16 * wp.nch + ly.k2 - 1); a.mg_txp = magic_of(16 * wp.nch);
                     a.mg_tpg = magic_of(wp.tpg); a.mg_k2 = magic_of(ly.k2); a.mg_ntx = magic_of(wp.ntx); a.mg_nty = magic_of(wp.nty);
                     a.mg_d = magic_of(ly.dil); a.mg_d2 = magic_of(ly.dil2);
@@ -1398,7 +1408,7 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                     weights_of(&a, net, li);
                     a.out_peak = delta_words(g, ws, li - 1);
                     a.in_peak = delta_words(g, ws, li); a.in_words = g.delta_words[li]; a.in_margin = g.delta_margin[li];
-                    if (ly.dgrad_half && a.in_peak) a.wpack2 = (const v4f*)(net->d_packs + ly.dgrad_half_off);
+                    if (two_part_dgrad(net, g, li)) a.wpack2 = (const v4f*)(net->d_packs + ly.dgrad_half_off);
                 }
                 bool launched = false;
                 LAUNCH(kF32 ? "conv_dgrad_parts" : "conv_dgrad_bm", li, dstep, flops, dbytes, launched = launch_conv<T>(a, tp, grid, st));
@@ -1777,9 +1787,9 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
                  (long)B * g.rows[l] * g.cols[l] < (1l << 31) / 32)
             put("  forward: image-layer kernel on the fp32 MFMA\n");
         else
-            conv("forward", g.fwd[l], ly.fwd_ct, ly.fwd_half);
+            conv("forward", g.fwd[l], ly.fwd_ct, two_part_forward(net, g, l));
         if (!training) continue;
-        if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct, ly.dgrad_half);
+        if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct, two_part_dgrad(net, g, l));
         const WgradPlan& w = g.wgrad[l];
         if (l == 0 && g.l0_fused) put("  weight gradient: fused with the routing of the pool above, %d workgroups\n", g.l0_blocks);
         else if (w.l0m) put("  weight gradient: image-layer kernel on the %s MFMA, %d tiles of 8 x 32, %d workgroups\n",

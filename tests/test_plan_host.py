@@ -45,3 +45,21 @@ def test_weight_gradient_kernel_by_its_work(size, parts):
     own = plan[plan.index("layer 1:"):plan.index("layer 2:")]
     assert ("weight gradient: bf16 MFMA, three parts" in own) == parts, own
     assert ("weight gradient: fp32 MFMA" in own) != parts, own
+
+
+@pytest.mark.parametrize("classes", [2, 4, 5])
+def test_two_parts_where_a_launch_may_take_them(classes):
+    """Five classes are not the fused class layer's, so nobody notes how large the deltas above the hidden layer are: three parts there, planned and said; two in the layer below, whose deltas
+    a data gradient has written."""
+    net = mpcnn.Net(((C, 64, 3), (C, 64, 3), (FC, 128, 0), (FC, classes, 0)), 1, 7)
+    plan = net.plan_describe(1, 210, 200, True)
+    net.close()
+    said = {}
+    for layer in (1, 2):
+        own = plan[plan.index("layer %d:" % layer):plan.index("layer %d:" % (layer + 1))]
+        for line in own.splitlines():
+            if "MFMA" in line:
+                said[layer, line.split(":")[0].strip()] = "or two of fp16" in line
+    known = classes <= 4
+    assert said[1, "forward"] and said[1, "data gradient"] and said[2, "forward"], plan
+    assert said[2, "data gradient"] == known and said[2, "weight gradient"] == known, plan
