@@ -227,6 +227,8 @@ def test_data_gradients_in_two_parts():
 # bf16 storage, eight tiles per wave (only where maps are large, never by a tiling hint): nets whose layers reach every such instance in both directions
 WIDE_MAPS = [((C, 64, 3), (C, 64, 3), (C, 128, 3), (C, 64, 3)), ((C, 32, 3), (C, 128, 5), (C, 32, 5)), ((C, 64, 3), (C, 64, 5), (C, 64, 5)),
              ((C, 128, 3), (C, 128, 2), (C, 200, 2), (C, 128, 2))]
+# channel counts 4 mod 8 (half an octet of the halo is another position's, stores of four channels), and a rectangular filter behind a pool of 2 x 3
+WIDE_RAGGED = [(((C, 60, 3), (C, 100, 3), (C, 36, 3), (C, 60, 3), (FC, 8, 0), (FC, 2, 0)), 10), (((C, 60, 3), (MP, 0, 2, 3), (FC, 100, 0), (FC, 8, 0), (FC, 2, 0)), 8)]
 
 
 def test_eight_tiles_per_wave_give_the_same_bits():
@@ -263,6 +265,24 @@ def test_eight_tiles_per_wave_give_the_same_bits():
         assert np.isfinite(out[0][1]).all() and np.any(out[0][1])
         assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]), convs
     assert got == {(d, i) for d in ("forward", "data gradient") for i in wide}, got
+    for layers, patch in WIDE_RAGGED:
+        H, W = patch + 840, patch + 930
+        net = mpcnn.Net(layers, 1, patch, mpcnn.BF16)
+        rng = np.random.default_rng(patch)
+        net.set_params(rng.uniform(-0.1, 0.1, net.param_count).astype(np.float32))
+        image = torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda()
+        labels = torch.from_numpy(rng.integers(0, 2, (1, H, W)).astype(np.int32)).cuda()
+        out = []
+        for hint in ((0, 0), (4, 2)):
+            net.set_conv_tiling(*hint)
+            here = {d for d, i in reached(net.plan_describe(1, H, W, True)) if i in wide}
+            assert here == ({"forward", "data gradient"} if hint == (0, 0) else set()), net.plan_describe(1, H, W, True)
+            probs = torch.empty((1, 2, H - patch + 1, W - patch + 1), device="cuda")
+            net.seg_backward(image, labels, probs=probs)
+            out.append((probs.cpu().numpy(), net.get_grads()))
+        net.close()
+        assert np.isfinite(out[0][1]).all() and np.any(out[0][1])
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]), layers
 
 
 # bf16 storage, layers behind the first.  Transposing reads: deltas whose last item has four channels.  One part per number: maps and channels 4 mod 8, a plane and half a
