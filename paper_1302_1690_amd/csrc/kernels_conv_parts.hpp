@@ -1,90 +1,62 @@
-// Forward / data gradient of one dilated convolution on the bf16 matrix instruction
-// (v_mfma_f32_32x32x16_bf16), for fp32 storage as well as bf16 storage.
+// Forward / data gradient of one dilated convolution on the 16-bit matrix instructions (v_mfma_f32_32x32x16_f16 and _bf16, 16 times the products
+// of the fp32 instruction in the same time), for fp32 storage, whose numbers become sums of two or three 16-bit parts, and for bf16 storage.
 //
-// fp32 storage.  The bf16 instruction does 16 times the products of the fp32 one in the same time, and fp32 products can be made of bf16
-// ones (Henry, Tang, Heinecke: Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations, arXiv 1904.06376).
-// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 bits: x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1, each
-// difference exact, and so is the sum: numbers are split 2^16 times as large, as below 2^-110 x2 would need bits that bf16 does
-// not have).  A product of two fp32 numbers is the sum of nine bf16 products, each exact in fp32.  The six with the largest factors are taken,
-//     x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0),
-// smallest first.  The three left out are below 2^-24 of |x y| together in the worst case, as much as the rounding of one
-// fp32 addition; for uniform numbers 0.36 * 2^-26 in the root mean square (measured), a third of that rounding's.
-// Six instructions of 32 cycles contract 16 channels where the fp32 instruction takes eight of 64: 417 TFLOP/s of
-// fp32 products at the instruction's dense peak against 157.
+// THREE bf16 PARTS (fp32 storage).  x = x0 + x1 + x2 exactly (8 + 8 + 8 bits; Henry, Tang, Heinecke: Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations, arXiv 1904.06376), split 2^16 times as large, as below 2^-110 x2 would need bits
+// that bf16 does not have. Of the nine products, each exact in fp32, six are taken: x0 y0 in one accumulator, x0 y1 + x1 y0 + (x1 y1 + x0
+// y2 + x2 y0) in another.  The three left out are below 2^-24 of |x y| together, 0.36 * 2^-26 in the root mean square.  Two accumulators
+// because the instruction rounds its sum twice and before that cuts addends off some ten bits below the largest's last, towards minus
+// infinity: with one, 1600 products came out 8e-8 too low on average whatever their sign, which a gradient adds up over all positions while
+// its own terms cancel; the second's offset is 2^-8 of that. Infinities, NaN and numbers above 2^-16 of the largest bf16 have no parts and
+// leave sums that are not finite, as do sums above 2^96; the epilogue finds those and computes them again with fp32 multiply-adds.
 //
-// Two accumulators per tile: x0 y0 in one, the five smaller products, 2^-8 of it, in the other.  The instruction rounds its sum
-// twice (8 products each time), and before that cuts addends off some ten bits below the last bit of the largest, towards
-// minus infinity: a result is on average 0.004 of a last bit too low (0.07 where the products are the larger ones), whatever its sign.
-// In one accumulator that was 12 roundings per 16 channels, and 1600 products came out 8e-8 too low on average; a gradient
-// adds such an offset up over all positions of an image, where its own terms cancel (gradients of a pool-free net, 96 x 110: 1.3e-5 off, 1.9e-6
-// with the fp32 instruction).  With two, the roundings of the second are 2^-8 as large.  Against 64-bit sums of 64, 256,
-// 1600 products of uniform numbers, rms relative: 4.5e-8, 8.1e-8, 2.2e-7 (1.1e-7, 2.3e-7, 6.1e-7 in one accumulator, 1.4e-7, 2.9e-7, 7.1e-7 on the
-// fp32 instruction), on average 1e-9 off to one side at most; those gradients 1.8e-6.
+// TWO fp16 PARTS (fp32 storage, sums of kHalfLeast products and more).  11 + 11 bits and a sign; three products, x0 y0 in one accumulator and
+// x0 y1 + x1 y0 in another: half the instructions.  One number in four loses its last bit and x1 y1 is left out, 7.5e-8 of a sum of random signs
+// whatever its length; in exchange there are fewer roundings, as the leading accumulator joins a total after every run of steps (half_run) and starts
+// from 0.  Against 64 bits, rms relative, three parts / two without runs / two:
+//   K = 64 4.5e-8 / 8.9e-8 / 8.9e-8; 288 8.5e-8 / 1.30e-7 / 1.09e-7; 400 1.01e-7 / 1.47e-7 / 1.12e-7; 576 1.23e-7 / 1.69e-7 / 1.15e-7;
+//   800 1.47e-7 / 1.94e-7 / 1.17e-7; 1600 2.18e-7 / 2.64e-7 / 1.25e-7; equal signs 576, 1600: 1.23e-7 / 1.19e-7 / 5.2e-8, 2.22e-7 / 2.21e-7 / 6.4e-8.
+// Hence kHalfLeast, where the two are equal.  (The bit that a weight loses is the same at every position: of nets without pools, whose
+// gradients show it, these are 1.1 to 1.5 times as far off as with three parts, where few positions carry most of the deltas 2.2 times; 96
+// x 110 pixels, five layers, a third.) fp16 reaches from 2^-24 to 2^16, so weights and deltas are raised by powers of two, one per tensor
+// (ranges.hpp), and second parts by 2^11 more, their products having an accumulator of their own: numbers below 2^-28 of a tensor's largest
+// lose bits below 2^-51 of that.  Activations stay as they are: tanh's are multiples of 2^-24, of logistic ones what is below 2^-36 is
+// lost.  The launch takes three parts where this could matter or is not known: a uniform choice at its start (conv_parts_kernel;
+// weights_wide, weights_large), so a plan holds for either.
 //
-// Infinities, NaN and numbers above 2^-16 of the largest bf16 have no such parts and leave a result that is not finite, as do sums above 2^96; the epilogue looks for
-// those and computes them again with fp32 multiply-adds, so they are what they would be without parts.
+// ONE PART (bf16 storage).  One product, one accumulator.
 //
-// fp32 storage, sums of kHalfLeast products and more: two fp16 parts per number (11 + 11 bits and a sign), three products of
-// v_mfma_f32_32x32x16_f16, x0 y0 in one accumulator and x0 y1 + x1 y0 in another - half the instructions of three bf16 parts.  Two parts lose
-// the last bit of one number in four, and x1 y1 is left out: 7.5e-8 of a sum of products of random signs, whatever its length.  That is
-// more than three parts lose by rounding in short sums and less in long ones, if those roundings become fewer at the same time: after a run of steps (half_run)
-// the leading products' accumulator is added to a total and starts again from 0.  Against 64-bit sums, rms relative, three parts / two without
-// runs / two, products of random signs: K = 64 4.5e-8 / 8.9e-8 / 8.9e-8; 288 8.5e-8 / 1.30e-7 / 1.09e-7; 400 1.01e-7 / 1.47e-7 / 1.12e-7; 576 1.23e-7 / 1.69e-7 / 1.15e-7;
-// 800 1.47e-7 / 1.94e-7 / 1.17e-7; 1600 2.18e-7 / 2.64e-7 / 1.25e-7; of equal signs, K = 576, 1600: 1.23e-7 / 1.19e-7 / 5.2e-8, 2.22e-7 / 2.21e-7 / 6.4e-8.
-// Hence kHalfLeast, where the two are equal.  Errors of whole calls are what they were or smaller (gradients of a pool-free net, 96 x 110, bias gradients over the root
-// of the deltas' squares: 1.25e-6 .. 1.55e-6 with three parts, 4.4e-7 .. 5.4e-7 with two).
-// fp16 reaches from 2^-24 to 2^16, so weights and deltas are raised by powers of two, one per tensor, and second parts by 2^11 more (their products have an accumulator of their
-// own): numbers below 2^-28 of a tensor's largest lose bits below 2^-51 of that.  Activations stay as they are: tanh's are multiples of 2^-24, of logistic ones what is below 2^-36 is
-// lost.  The launch takes three parts where this could matter or not be known (infinities; a map's worth of weights 2^-26 of the largest, weights_wide; logistic outputs under weights of 16 and more,
-// weights_large; deltas that such weights, or such of the class layer, have made, ranges.hpp), as do
-// shorter sums: a uniform choice at the kernel's start, from what the weights' packing and the writer of the deltas left, so a plan holds for either.
-// bf16 storage.  One part, one product, one accumulator: same kernel.
+// TILING.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x 32*WO*MO output channels; a wave
+// owns MO x MP result tiles of 32 x 32, one or two with two and three parts, two, four or eight with one.  A step contracts 16 channels of
+// one tap: MO + MP operands of P parts each feed 6 (three parts), 3 or 1 instructions per tile.  Weights come through the vector cache,
+// activations from LDS, 1 KB per operand and wave. What a product costs in such bytes decides the rate of one part: with 2 x 2 tiles the
+// vector cache takes 0.6 of an access per cycle and waits for L2 a third to a half of the time; 2 x 4 tiles take half of that (2 x 2048 x
+// 2048, forward 1096, 1745, 1763, 3383 -> 954, 1541, 1519, 3103 us) but need maps that give two workgroups of them to every compute unit. A
+// halo is brought in CB channels at a time.  Where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels,
+// as a block costs two barriers and a wait of its weights behind the halo; where it is large they are 16 channels of kr filter rows.
 //
-// Tiling.  A workgroup (4 waves) owns 32*WP*MP positions of ONE residue class (see kernels_mfma.hpp) x
-// 32*WO*MO output channels; a wave owns MO x MP result tiles of 32 x 32, one or two with two and three parts (two accumulators each and, with two parts, a
-// total), two, four or eight with one.  A step contracts 16 channels of one tap: MO + MP operands of P parts each feed 6 (three parts), 3 or 1
-// instructions per tile.  Weights come through the vector cache, 1 KB per operand and wave, activations from LDS, 1 KB each.  What a product
-// costs in such bytes decides the rate of one part: counters show the vector cache taking 0.6 of an access per cycle with 2 x 2 tiles (0.5 KB of weights per instruction, every
-// wave its own) and waiting for L2 a third to a half of the time; 2 x 4 tiles take half of that (2 x 2048 x 2048, forward 1096, 1745, 1763, 3383 -> 954, 1541, 1519, 3103 us, data
-// gradient -, 1763, 1468, 2542 -> -, 1570, 1324, 2204) but need maps that give two workgroups of them to every compute unit.
-// The input halo is brought in CB channels at a time.
+// LATENCY.  Workgroups are persistent and walk (tile, channel block) items.  Two and three parts: the next item's halo is loaded into
+// registers before the current one is multiplied and split on its way to LDS after it; two workgroups share a compute unit.  One part: the
+// halo goes from memory to LDS without a stop in registers, once every wave has left the last one, in 64-byte pieces of a position per four
+// lanes (16 bytes of 64 positions: the last layer's forward 3338 instead of 3040 us), which leaves registers for three workgroups of four
+// tiles per wave, or two of eight. Weights run through a ring of parts_ring steps that never drains: the pack is in step order - chunks of
+// 16 channels, the taps of each, whatever CB is - and its first steps follow its last once more, so that no fetch looks at the end; behind
+// a tile's last step the pointer goes back to its first. One part: the LDS offsets of a block's steps come from a table in LDS, as counting
+// taps took more scalar instructions than a step has issue slots for. The bias waits in LDS (its loads queued behind the halo's: bf16
+// forward 8.8 -> 7.9 ms).
 //
-// Latency.  Workgroups are persistent and walk (tile, channel block) items.  Two and three parts: the next item's halo is
-// loaded into registers before the current one is multiplied and split into parts on its way to LDS after it, two workgroups share a compute unit,
-// so one's staging, barriers and stores lie under the other's instructions.  One part: the halo goes from memory to LDS without a stop in registers, once every wave has left
-// the last one, under the epilogue and under the other workgroups' instructions: without halo registers three workgroups of four tiles per wave share a
-// compute unit (3 x 501 x 389, 100 maps: forward 43, 57, 119 -> 32, 43, 101 us, data gradient 54, 55, 117 -> 44, 41, 90 with what else changed), or two of eight.
-// (64-byte pieces of a position per four lanes: with 16 bytes of 64 positions per instruction, which needs no change of places in LDS, the cache takes four times the accesses, and the
-// last layer's forward 3338 instead of 3040 us.)
-// Weights run through a ring of parts_ring steps that never drains: the pack is in step
-// order - chunks of 16 channels, the taps of each, whatever CB is - and its first steps follow its last once more, so that
-// no fetch looks at the end; behind a tile's last step the pointer goes back to its first.
-// One part: the LDS offsets of a block's steps come from a table in LDS, as counting taps took more scalar instructions than a step has issue slots for.
-// A block costs two barriers and, as a wave's loads return in order, a wait of its weights behind the halo:
-// where the filter is small (2 x 2 taps: 8 steps per 32 channels) blocks are 64 or 128 channels.  Where it is large, its halo would leave
-// a tile of few positions, or none: blocks are then 16 channels of kr filter rows, in step order as well.
-//
-// Measured, deep net (layers 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds before -> now:
-//   fp32, 1 x 1024 x 1024, three parts -> two: forward 485, 869, 707, 1281 -> 317, 555, 481, 868 (328, 362, 289, 212 TFLOP/s); data gradient 485, 886, 691, 1075 ->
-//     306, 552, 446, 727 (341, 365, 312, 253).  A loop of these operands alone sustains 342 on random data (1.03 PFLOP/s of instructions), 221 in three parts; the
-//     clock under these launches is 1.9-2.1 GHz (busy counter over time; 2.4-2.6 under the pools), matrix pipes busy 34-58 %: power bounds the first two layers, the
-//     last one's waits for halo and stores the others.
-//   fp32 instruction -> three parts, 1 x 1024 x 1024: forward 838, 1602, 1194, 1956 -> 488, 891, 711, 1236 (214, 226, 196, 148 TFLOP/s);
-//     data gradient 1060, 1790, 1250, 1880 -> 485, 898, 684, 1070 (215, 224, 203, 171).  Matrix pipes busy 50-75 %.  One accumulator, up to four
-//     tiles per wave, no scaling against this, in turn on one machine: forward 447, 850, 646, 1088 -> 483, 879, 711, 1230, data gradient 488, 838, 621, 923 ->
-//     481, 894, 680, 1068.  The loop alone then sustained 240-260 on random data, 362 on zero weights with the same instructions: what a power limit would do.
-//   bf16, 2 x 2048 x 2048, 2 x 2 tiles with the halo through registers -> now: forward 1078, 1739, 1708, 3071 -> 902, 1502, 1518, 2999 (938, 1108, 773, 531 TFLOP/s); data gradient
-//     953, 1790, 1443, 2387 -> 884, 1480, 1248, 2011 (958, 1124, 940, 791).  What the last layer's forward goes to (one image, 1814): without stores 1249, without the
-//     next halos 1255, without tanh 1807, without fetching weights 1616, without the multiplications 1390, without the first three 1029.
+// MEASURED, deep net (32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds:
+//   fp32, 1 x 1024 x 1024, fp32 instruction / three parts / two: forward 838, 1602, 1194, 1956 / 485, 869, 707, 1281 / 319, 555, 480, 889 (326, 362, 290, 207
+//     TFLOP/s); data gradient 1060, 1790, 1250, 1880 / 485, 886, 691, 1075 / 311, 568, 453, 745 (335, 355, 307, 247).  A loop of two parts' operands alone
+//     sustains 342, of three parts' 221; the clock under these launches is 1.9-2.1 GHz: power bounds the first two layers, waits for halo and stores the others.
+//   bf16, 2 x 2048 x 2048: forward 902, 1502, 1518, 2999 (938, 1108, 773, 531 TFLOP/s), data gradient 884, 1480, 1248, 2011 (958, 1124, 940, 791).  The last
+//     layer's forward, one image, 1814 whole: without stores 1249, without the next halos 1255, without weights 1616, without the multiplications 1390.
 //   Slower than the fp32 instruction's kernel: fp32 launches on one or two thousand positions with at most 16 channels (9 against 7).
-//   The bias from LDS instead of memory (its loads queued behind the halo's) took the bf16 forward from 8.8 to 7.9 ms.
-// Tried and dropped: planes of 8 channels in LDS for two and three parts (no row break conflicts where tiles are 32 wide; even), tiles walked residue column first and in
-// bands per XCD (so that neighbours in memory are worked on together; even), two and three parts' stores by 64 bytes per position (even).
 //
-// Summation order is the step order for every output element, whatever the tiling: equal inputs
-// give bit-equal outputs (exact pooling ties stay exact) and a position's value does not depend on
-// how the map is cut.  A data gradient in two parts does depend on the tensor's largest delta: by powers of two that change no bit of numbers down to 2^-28 of it, and by the choice of three parts
-// for the whole tensor where it is infinite.
+// Summation order is the step order for every output element, whatever the tiling: equal inputs give bit-equal outputs (exact pooling ties
+// stay exact) and a position's value does not depend on how the map is cut.  A data gradient in two parts does depend on the tensor's
+// largest delta: by powers of two that change no bit of numbers down to 2^-28 of it, and by the choice of three parts for the whole tensor
+// where it is infinite.
 #pragma once
 #include <type_traits>
 
@@ -106,9 +78,9 @@ __host__ __device__ constexpr int parts_items(int parts, int tiles)             
 {
     return parts > 1 ? 6 : parts_wgs(1, tiles) == 3 ? 12 : 18;
 }
-// The halo in LDS.  Two and three parts: [position][16 channels][part].  One part: groups of 32 channels (16 where a block has no more), a position's octets
-// of a group together - 64 (32) bytes, as the memory holds them.  Octet j of position p sits in place j ^ (p / 4) % 4 (j ^ (p / 8) % 2): 16
-// successive positions meet no bank twice.
+// The halo in LDS.  Two and three parts: [position][16 channels][part].  One part: groups of 32 channels (16 where a block has no more), a
+// position's octets of a group together - 64 (32) bytes, as the memory holds them.  Octet j of position p sits in place j ^ (p / 4) % 4 (j
+// ^ (p / 8) % 2): 16 successive positions meet no bank twice.
 __host__ __device__ constexpr int parts_group(int CB) { return CB < 32 ? 2 : 4; }                           // octets of a group
 __host__ __device__ constexpr int parts_pitch(int parts, int CB)                                            // bytes of a position, in all groups together
 {
@@ -149,8 +121,9 @@ __device__ __forceinline__ void split_halves(const float (&x)[8], u32x4 (&p)[2],
         p[1][j] = __builtin_bit_cast(unsigned, l);
     }
 }
-// Steps between two additions of a tile's leading sums to its total (kernel below): whole chunks of at most 16 taps until they are 8 steps (8 to 16), of larger filters whole rows while they are 16 taps at
-// most (12 to 16) or, of those with 8 rows or 9 columns and more, a row (4 to k2 steps).  A function of the filter alone.  `period`: steps after which the lengths repeat.
+// Steps between two additions of a tile's leading sums to its total (kernel below): whole chunks of at most 16 taps until they are 8 steps
+// (8 to 16), of larger filters whole rows while they are 16 taps at most (12 to 16) or, of those with 8 rows or 9 columns and more, a row
+// (4 to k2 steps).  A function of the filter alone.  `period`: steps after which the lengths repeat.
 constexpr int kHalfLeast = 512;   // fewest products of a sum that two fp16 parts are taken for
 __host__ __device__ inline bool half_filter(int k, int k2) { return k * k2 >= 4 && (k < 8 || k2 >= 4); }   // blocks of four steps at least
 struct HalfRun { int period, length; };
@@ -185,14 +158,15 @@ __device__ __forceinline__ unsigned parts_div(unsigned n, unsigned magic, unsign
     return x == 1 ? n : __umulhi(n, magic);   // n / x for n * x < 2^32, magic = ceil(2^32 / x)
 }
 
-// Weights that two fp16 parts do not suit: not finite, or with half a sum's number and more, counted over the layer, kSmallOctaves below the largest (one
-// output or input map of such weights is enough; a few of them beside larger ones do not matter to any sum)
+// Weights that two fp16 parts do not suit: not finite, or with half a sum's number and more, counted over the layer, kSmallOctaves below
+// the largest (one output or input map of such weights is enough; a few of them beside larger ones do not matter to any sum)
 __device__ __forceinline__ bool weights_wide(const ConvArgs& a)
 {
     return a.w_peak && (a.w_peak[0] >= kNoPeak || 2 * a.w_peak[1] >= (unsigned)a.small_limit);
 }
-// Two parts of activations as they are hold multiples of 2^-24, which tanh leaves, whole; of logistic outputs, however small, they lose bits below 2^-36 (rms 2^-37): of no account
-// in a sum that is squashed, known to 2^-24, but under weights that make up for it.  10^4 products and weights of 16 are off by 2^-26.
+// Two parts of activations as they are hold multiples of 2^-24, which tanh leaves, whole; of logistic outputs, however small, they lose
+// bits below 2^-36 (rms 2^-37): of no account in a sum that is squashed, known to 2^-24, but under weights that make up for it.  10^4
+// products and weights of 16 are off by 2^-26.
 __device__ __forceinline__ bool weights_large(const ConvArgs& a) { return a.logistic && a.w_peak[0] >= bits_of(16.f); }
 
 template <typename T, int P, bool BACK, int CB, int WO, int WP, int MO, int MP>
@@ -618,12 +592,11 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 }
         }
     };
-    // The same with bf16 storage, where an instruction would write 16 bytes of each of 32 positions, and the caches take such pieces one by one.  Lanes
-    // change places with each other first, so that four hold 64 successive bytes of a position and an instruction writes 16 positions:
-    // part h of a tile is positions 16h .. 16h + 15, a lane's piece 8 channels of position 16h + lane % 16.  (2 x 2048 x 2048, forward: 890, 1477, 1496, 3022 -> 873, 1473,
-    // 1413, 2954 us; fp32, 32 bytes of 32 positions: no gain.)
-    // The bias waits in LDS; what the data gradient reads (the outputs whose slope multiplies it) is fetched a part ahead, so
-    // that its trip lies under the part before.
+    // The same with bf16 storage, where an instruction would write 16 bytes of each of 32 positions, and the caches take such pieces one by
+    // one.  Lanes change places with each other first, so that four hold 64 successive bytes of a position and an instruction writes 16
+    // positions: part h of a tile is positions 16h .. 16h + 15, a lane's piece 8 channels of position 16h + lane % 16.  (2 x 2048 x 2048,
+    // forward: 890, 1477, 1496, 3022 -> 873, 1473, 1413, 2954 us; fp32, 32 bytes of 32 positions: no gain.) The bias waits in LDS; what the
+    // data gradient reads (the outputs whose slope multiplies it) is fetched a part ahead, so that its trip lies under the part before.
     auto epilogue_pieces = [&](const Tile& g, int fh, int fw) {
       if constexpr (!kF32) {
         constexpr int W = 8;                          // channels of a piece
@@ -633,8 +606,9 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         const int side = fresh(lane);
         const int lch = 16 * (side >> 4 & 1) + 8 * (side >> 5);   // the lane's first channel
         const bool reads = BACK && curved;            // uniform
-        // bf16 data gradients issue their stores on every path, and brought waits for the halo without them (2 x 2048 x 2048, us: 2055, 1263, 1481, 881 ->
-        // 2041, 1218, 1449, 870; forwards, whose squashing function then runs for channels that do not exist too: 873, 1473, 1413, 2954 -> 896, 1478, 1479, 3073)
+        // bf16 data gradients issue their stores on every path, and brought waits for the halo without them (2 x 2048 x 2048, us: 2055,
+        // 1263, 1481, 881 -> 2041, 1218, 1449, 870; forwards, whose squashing function then runs for channels that do not exist too: 873,
+        // 1473, 1413, 2954 -> 896, 1478, 1479, 3073)
         constexpr bool kCounted = BACK;
         long pos_off[2];
         bool pos_ok[2];

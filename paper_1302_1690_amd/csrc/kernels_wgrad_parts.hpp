@@ -1,17 +1,18 @@
-// Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_f16, every fp32 number as the sum of two fp16
-// parts, three products each, or, where the numbers do not suit fp16 (ranges.hpp), on v_mfma_f32_32x32x16_bf16 in three bf16 parts, six products
-// each (kernels_conv_parts.hpp has the arithmetic of both).  The accumulator's roundings, half as many with two parts, make up for the bits that two parts lose once a wave adds some 144 positions;
-// shorter chains take three parts (plan_wgrad_parts has the errors on both sides).
+// Weight gradient of one dilated convolution with fp32 storage on v_mfma_f32_32x32x16_f16, every fp32 number as the sum of two fp16 parts,
+// three products each, or, where the numbers do not suit fp16 (ranges.hpp), on v_mfma_f32_32x32x16_bf16 in three bf16 parts, six products
+// each (kernels_conv_parts.hpp has the arithmetic of both).  The accumulator's roundings, half as many with two parts, make up for the bits
+// that two parts lose once a wave adds some 144 positions; shorter chains take three parts (plan_wgrad_parts has the errors on both sides).
 //
-// bf16 storage: one part, one product, raw copies, for the layers that wgrad_tr_kernel does not take (input channels no multiple of 32, or 32 maps and fewer, which went to
-// the fp32 instruction).  Bound by its operand reads: PM + 1 of a kilobyte for PM products, half of the LDS's rate times the matrix pipes'.  3 x 501 x 389, 16 -> 32, 5 x 5:
-// 150 -> 48 us (94 -> 295 TFLOP/s); error in the 2-norm on 1500 x 1400 4.1e-8 -> 2.7e-8, 48 -> 64 k4 on 700 x 640 3.9e-8 -> 3.0e-8, smaller maps 2.3e-8 to 3.2e-8 both.
+// bf16 storage: one part, one product, raw copies, for the layers that wgrad_tr_kernel does not take (input channels no multiple of 32, or
+// 32 maps and fewer, which went to the fp32 instruction).  Bound by its operand reads: PM + 1 of a kilobyte for PM products, half of the
+// LDS's rate times the matrix pipes'.  3 x 501 x 389, 16 -> 32, 5 x 5: 150 -> 48 us (94 -> 295 TFLOP/s); error in the 2-norm on 1500 x 1400
+// 4.1e-8 -> 2.7e-8, 48 -> 64 k4 on 700 x 640 3.9e-8 -> 3.0e-8, smaller maps 2.3e-8 to 3.2e-8 both.
 //
 // Accuracy.  All six products go to one accumulator, as there is no room for two, and the instruction's results are a little too low
-// whatever their sign: over the slabs of a large map such offsets add up where roundings cancel.  So every other slab has the signs
-// of its deltas turned, and its sums' signs turned back.  Error of the gradient in the 2-norm, fp32 instruction / without turns / now: 32 -> 64 k5 on 1024 x 1024
-// 1.3e-7 / 1.8e-7 / 1.0e-7, with cancelling deltas 1.6e-6 / 2.3e-6 / 1.4e-6; 64 -> 128 k3 2.0e-7 / 2.5e-7 / 1.6e-7 and 2.8e-6 / 4.5e-6 / 1.9e-6;
-// 128 -> 200 k2 on 700 x 640 2.9e-7 / 1.7e-7 / 1.1e-7 and 1.1e-6 / 1.2e-6 / 6.3e-7.
+// whatever their sign: over the slabs of a large map such offsets add up where roundings cancel.  So every other slab has the signs of its
+// deltas turned, and its sums' signs turned back.  Error of the gradient in the 2-norm, fp32 instruction / without turns / now: 32 -> 64 k5
+// on 1024 x 1024 1.3e-7 / 1.8e-7 / 1.0e-7, with cancelling deltas 1.6e-6 / 2.3e-6 / 1.4e-6; 64 -> 128 k3 2.0e-7 / 2.5e-7 / 1.6e-7 and
+// 2.8e-6 / 4.5e-6 / 1.9e-6; 128 -> 200 k2 on 700 x 640 2.9e-7 / 1.7e-7 / 1.1e-7 and 1.1e-6 / 1.2e-6 / 6.3e-7.
 //
 //   dW[tap][c][o] = sum over positions of in[pos + tap][c] * dY[pos][o]        (Alg. 2)
 //
@@ -21,12 +22,12 @@
 // them for ONE gradient row or output channel; the transposing LDS read (ds_read_b64_tr_b16, see
 // kernels_wgrad_tr.hpp) gives that from channels-last tiles.
 //
-// Layout (three parts; two: 64 bytes per position, planes shifted by 32; one: 32 bytes per position, planes by 128 mod 256).  Both tiles sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per
-// position: the 16 lanes that read 4 positions together meet no bank twice, and with a plane pitch of 128 mod 256
-// bytes neither do the 32 of two planes; counters, stores included, still read 26-42 % of the LDS cycles as conflicts).  Parts, the second half of an operand and successive chunks are immediates.  A
-// gradient row tile is two UNITS of 16 rows, a unit being (plane, tap): the two halves of the lanes
-// address their units separately, so 16-channel layers fill row tiles with two taps and 100 channels pad
-// to 112, not 128.
+// Layout (three parts; two: 64 bytes per position, planes shifted by 32; one: 32 bytes per position, planes by 128 mod 256).  Both tiles
+// sit in LDS as planes of 16 channels, [plane][position][part][16 channels] (96 bytes per position: the 16 lanes that read 4 positions
+// together meet no bank twice, and with a plane pitch of 128 mod 256 bytes neither do the 32 of two planes; counters, stores included,
+// still read 26-42 % of the LDS cycles as conflicts).  Parts, the second half of an operand and successive chunks are immediates.  A
+// gradient row tile is two UNITS of 16 rows, a unit being (plane, tap): the two halves of the lanes address their units separately, so
+// 16-channel layers fill row tiles with two taps and 100 channels pad to 112, not 128.
 //
 // Waves.  Eight waves = wm (row tiles) x wn (column tiles) x wk (positions), each with PM x 1 result
 // tiles: a chunk of 16 positions is PM + 1 operands of three parts for 6 PM instructions, 70 bytes per cycle of
@@ -35,14 +36,15 @@
 // of the two waves of a SIMD one writes before it multiplies and the other after, so that one's
 // conversions lie under the other's instructions.
 //
-// Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), three parts -> two: 522, 1005, 710, 1325 us -> 324, 620, 478,
-// 845 (322, 325, 291, 217 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7, 1.01e-7, with cancelling deltas 1.36e-6, 1.93e-6, 6.3e-7 -> 1.28e-6, 1.72e-6, 5.5e-7.
-// Before (fp32 instruction) and in three parts: 985, 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on
-// random data is 240-260, the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %.
-// Splitting numbers 2^16 times as large (two multiplications per pair more) took 495, 942, 682, 1222 to 506, 980, 699, 1295, in turn on one machine.
-// Little work (below 4e7 operations) stays on wgrad_mfma_kernel: a launch takes some 6 us more here whatever it computes.
-// The conversions decide the rest: with every item's address worked out per tile and numbers
-// converted one by one (480 vector instructions per thread and tile of 32 positions instead of 300) it was 575, 1062, 811, 1540.
+// Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), three parts -> two: 522, 1005, 710,
+// 1325 us -> 324, 620, 478, 845 (322, 325, 291, 217 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
+// 1.01e-7, with cancelling deltas 1.36e-6, 1.93e-6, 6.3e-7 -> 1.28e-6, 1.72e-6, 5.5e-7. Before (fp32 instruction) and in three parts: 985,
+// 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on random data is 240-260,
+// the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %. Splitting numbers 2^16 times as large (two
+// multiplications per pair more) took 495, 942, 682, 1222 to 506, 980, 699, 1295, in turn on one machine. Little work (below 4e7
+// operations) stays on wgrad_mfma_kernel: a launch takes some 6 us more here whatever it computes. The conversions decide the rest: with
+// every item's address worked out per tile and numbers converted one by one (480 vector instructions per thread and tile of 32 positions
+// instead of 300) it was 575, 1062, 811, 1540.
 #pragma once
 #include "kernels_conv_parts.hpp"
 #include "kernels_wgrad_tr.hpp"
@@ -94,13 +96,14 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
     return g;
 }
 
-// ---- two parts: what deltas are raised by.  One power of two per map (column of the result, where it is undone), so that a map far below the others keeps its
-// bits.  The largest of a map's deltas is not known; that of all of them is (ranges.hpp), and a sample of positions shows what a map has.  One that reaches within
-// kWpSampled octaves of the largest of all is raised like that.  What was found in one below goes to 2^kWpPlace, with room for numbers 2^12 times as large;
-// if there are larger ones, infinities appear in the sums and three parts do the work again, as they do at once where the sample is not finite or nothing but zeros.
-// Two parts of a number have all their bits down to 2^-3 and an error of 2^-26 (rms) below, so of a map's deltas those that matter lose nothing.
-// 64 -> 128, 3 x 3, deltas 2^-20, 2^-24, 2^-30, 2^-40 of the others': error of a map's gradient 6e-7, 2e-6, 1e-3, 1 with one power of two for all, 1e-7 and less in each now.
-// 64 -> 100, 3 x 3, 213 x 213 positions: 42 us without samples, 45 with.
+// ---- two parts: what deltas are raised by.  One power of two per map (column of the result, where it is undone), so that a map far below
+// the others keeps its bits.  The largest of a map's deltas is not known; that of all of them is (ranges.hpp), and a sample of positions
+// shows what a map has.  One that reaches within kWpSampled octaves of the largest of all is raised like that.  What was found in one below
+// goes to 2^kWpPlace, with room for numbers 2^12 times as large; if there are larger ones, infinities appear in the sums and three parts do
+// the work again, as they do at once where the sample is not finite or nothing but zeros. Two parts of a number have all their bits down to
+// 2^-3 and an error of 2^-26 (rms) below, so of a map's deltas those that matter lose nothing. 64 -> 128, 3 x 3, deltas 2^-20, 2^-24,
+// 2^-30, 2^-40 of the others': error of a map's gradient 6e-7, 2e-6, 1e-3, 1 with one power of two for all, 1e-7 and less in each now. 64
+// -> 100, 3 x 3, 213 x 213 positions: 42 us without samples, 45 with.
 constexpr int kWpSampled = 12, kWpPlace = 4, kWpSamples = 8;
 
 // Whether any thread of the workgroup says so (*word: in LDS, for this alone)
@@ -115,8 +118,8 @@ __device__ __forceinline__ bool any_thread(bool yes, unsigned* word)
     __syncthreads();
     return any;
 }
-// Bits of the largest magnitudes of 4 quads channels from c0 on (none past C, a multiple of 4) at kWpSamples * (512 / quads) positions spread over a tensor
-// [positions][C], left in most[] (which is clear)
+// Bits of the largest magnitudes of 4 quads channels from c0 on (none past C, a multiple of 4) at kWpSamples * (512 / quads) positions
+// spread over a tensor [positions][C], left in most[] (which is clear)
 __device__ __forceinline__ void sample_maps(const float* t, long positions, int C, int c0, int quads, unsigned* most)
 {
     for (int q0 = 0; q0 < quads; q0 += kWpThreads) {
@@ -145,8 +148,9 @@ __device__ __forceinline__ void sample_maps(const float* t, long positions, int 
         }
     }
 }
-// The factors of this workgroup's columns with the slab's sign, left in up[32 wn] (three words behind them are used too); `one`: that of all columns but those that need their own.
-// Logistic outputs may be small in a whole map: all of this workgroup's have to reach 2^-12 in the sample.
+// The factors of this workgroup's columns with the slab's sign, left in up[32 wn] (three words behind them are used too); `one`: that of
+// all columns but those that need their own. Logistic outputs may be small in a whole map: all of this workgroup's have to reach 2^-12 in
+// the sample.
 enum Raised { kNotRaised, kRaisedAlike, kRaisedEach };
 __device__ __forceinline__ Raised raise_maps(const WgradPartsArgs& a, float turn, float* up, unsigned* most, float& one)
 {
@@ -245,8 +249,8 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
     const float in_up = P == 2 ? power_of_two(kActRaise) : kPartsUp;
     float dy_up = turn * kPartsUp;
     bool each = false;                                // two parts: not all columns' factors are dy_up (uniform)
-    // (two parts: the columns' factors and three words lie behind two parts' two buffers, 128 wn + 12 bytes; the plan has room for three parts' buffers, whose 4 wn delta
-    // planes alone are larger by 32 * 16 + 288 bytes and more each)
+    // (two parts: the columns' factors and three words lie behind two parts' two buffers, 128 wn + 12 bytes; the plan has room for three
+    // parts' buffers, whose 4 wn delta planes alone are larger by 32 * 16 + 288 bytes and more each)
     float* const col_up = reinterpret_cast<float*>(ldsb + 2 * g.buf_b);
     float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
 #pragma unroll

@@ -156,8 +156,9 @@ struct Geom {
     std::vector<int> partial_n;
     std::vector<size_t> partial_len;  // floats per partial result
     size_t loss_partial_off = 0;
-    // Largest magnitudes of the deltas (ranges.hpp).  Layer whose words hold those of the delta at layer l's output, -1: nobody notes them (pools take them from
-    // above); number of the words, octaves that routing passes may add, place of the words.  `squashed`: layer l's output is a squashing function's
+    // Largest magnitudes of the deltas (ranges.hpp).  Layer whose words hold those of the delta at layer l's output, -1: nobody notes them
+    // (pools take them from above); number of the words, octaves that routing passes may add, place of the words.  `squashed`: layer l's
+    // output is a squashing function's
     std::vector<int> delta_peak, delta_words, delta_margin;
     std::vector<bool> squashed;
     size_t delta_words_off = 0;
@@ -278,9 +279,10 @@ struct ProfScope {
     } while (0)
 
 // ------------------------------------------------------------------ planning
-// Tile plan of conv_parts_kernel (P parts per number, mults products per step and tile - three parts' plans serve two parts as well -, es bytes per stored element).  Cost of the busiest compute unit
-// in cycles: its tiles' matrix instructions on its four SIMDs, a quarter of their staging and stores (most of it lies under
-// the other resident workgroup's instructions), and one tile's staging in full at the start.
+// Tile plan of conv_parts_kernel (P parts per number, mults
+// products per step and tile - three parts' plans serve two parts as well -, es bytes per stored element).  Cost of the busiest compute
+// unit in cycles: its tiles' matrix instructions on its four SIMDs, a quarter of their staging and stores (most of it lies under the other
+// resident workgroup's instructions), and one tile's staging in full at the start.
 TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, int k, int k2, int cr, int rpad, int co,
                          const ChanTiling& ct, int P, int mults, size_t es, bool back, int hint_pt, int hint_mp)
 {
@@ -300,17 +302,19 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         if (in.MO == 2 && per_wave <= 4 && ceil_div(co, 32) % 2) continue;
         if (per_wave > 4 && (hint_pt || hint_mp || !mpcnn::half_filter(k, k2))) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
-        // Time per matrix instruction against four tiles' per wave.  One part: 2 x 4 tiles take 0.86-0.88 of the time (2 x 2048 x 2048, us, 2 x 2 against 2 x 4: forward 1096,
-        // 1745, 1763, 3383 against 954, 1541, 1519, 3103; on 3 x 501 x 389 and smaller, where they are two rounds and less, even: 103 against 100.5), 2 x 2 are ahead of 1 x 4
-        // (2 x 600 x 640, deep net: 110, 169, 152 us against 117, 182, 159), two tiles take 1.17 to 1.3 times as long on large maps; three parts: two tiles
-        // against one.  A workgroup alone on its compute unit, its waits in the open, takes 1.4 times as long with one part.
+        // Time per matrix instruction against four tiles' per wave.  One part: 2 x 4 tiles take 0.86-0.88 of the time (2 x 2048 x 2048, us,
+        // 2 x 2 against 2 x 4: forward 1096, 1745, 1763, 3383 against 954, 1541, 1519, 3103; on 3 x 501 x 389 and smaller, where they are
+        // two rounds and less, even: 103 against 100.5), 2 x 2 are ahead of 1 x 4 (2 x 600 x 640, deep net: 110, 169, 152 us against 117,
+        // 182, 159), two tiles take 1.17 to 1.3 times as long on large maps; three parts: two tiles against one.  A workgroup alone on its
+        // compute unit, its waits in the open, takes 1.4 times as long with one part.
         const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave > 4 ? 0.88 : per_wave == 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
         const double alone = P == 3 ? 1.15 : 1.4;
         const double t_mul = (double)steps * mults * ct.OT * PT * 8.0 * eff;
-        // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640 positions (fp32)
-        // holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions, forward / data gradient,
-        // microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32 x 32 16304 / 56978 (plain kernel) ->
-        // 696 / 805; bf16 32 x 32 274 / 412 -> 272 / 271, 40 x 40 24336 / 88069 (plain kernel) -> 419 / 418.  12 x 12 and less: whole is as fast.)
+        // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640
+        // positions (fp32) holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions,
+        // forward / data gradient, microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32
+        // x 32 16304 / 56978 (plain kernel) -> 696 / 805; bf16 32 x 32 274 / 412 -> 272 / 271, 40 x 40 24336 / 88069 (plain kernel) -> 419
+        // / 418.  12 x 12 and less: whole is as fast.)
         for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128}) {
             if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
             const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
@@ -417,9 +421,11 @@ WgradPlan plan_wgrad_parts_in(const Layer& ly, int B, int in_c, int out_r, int o
     }
     return best;
 }
-// fp32 storage, `half` (two fp16 parts may be used): they are where a wave of the three parts' plan adds at least kHalfChain positions into one accumulator.  What two parts leave
-// out is 5e-8 of a gradient (2-norm) whatever the length, what three parts' six products are rounded by grows with it.  Three / two parts: 16 positions 2.7e-8 / 4.6e-8 and 64 2.7e-8 / 5.0e-8
-// (32 -> 64, 5 x 5), 112 3.9e-8 / 4.6e-8 (128 -> 200, 2 x 2), 128 4.2e-8 / 4.9e-8, 160 6.5e-8 / 4.7e-8 (64 -> 128, 3 x 3), 256 1.24e-7 / 4.9e-8, 640 3.5e-7 / 5.3e-8, 3904 1.9e-6 / 1.05e-6.
+// fp32 storage, `half` (two fp16 parts may be used): they are where a wave of the three parts' plan adds at least kHalfChain positions into
+// one accumulator.  What two parts leave out is 5e-8 of a gradient (2-norm) whatever the length, what three parts' six products are rounded
+// by grows with it.  Three / two parts: 16 positions 2.7e-8 / 4.6e-8 and 64 2.7e-8 / 5.0e-8 (32 -> 64, 5 x 5), 112 3.9e-8 / 4.6e-8 (128 ->
+// 200, 2 x 2), 128 4.2e-8 / 4.9e-8, 160 6.5e-8 / 4.7e-8 (64 -> 128, 3 x 3), 256 1.24e-7 / 4.9e-8, 640 3.5e-7 / 5.3e-8, 3904 1.9e-6 /
+// 1.05e-6.
 constexpr double kHalfChain = 144;
 WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_c, bool bf16, bool half)
 {
@@ -429,17 +435,20 @@ WgradPlan plan_wgrad_parts(const Layer& ly, int B, int in_c, int out_r, int out_
 // The image layer's weight gradient multiplies on the bf16 instruction where both operands are bf16 and a position's
 // deltas are whole 128-bit items; with fp32 storage, and for other map counts, on the fp32 one.
 inline bool l0_wgrad_on_bm(const Layer& ly, bool bf16) { return bf16 && ly.cout % 8 == 0; }
-// A launch of wgrad_parts_kernel takes some 6 us more than one of wgrad_mfma_kernel whatever it computes (512 threads, both tiles converted, up to eight
-// waves' sums to meet): 16 -> 16 channels, 2 x 2 taps, 1300 positions (2.6 MFLOP) 15.0 us against 8.8, 16 -> 16, 3 x 3, 2700 positions (12 MFLOP) 16.3
-// against 12.6; 32 -> 100, 2 x 2, 2600 positions (67 MFLOP) 17.4 against 14.8, but 2 us less in the reduce for its fewer slabs.
+// A launch of wgrad_parts_kernel takes some 6 us more than one of wgrad_mfma_kernel whatever it computes (512 threads, both tiles
+// converted, up to eight waves' sums to meet): 16 -> 16 channels, 2 x 2 taps, 1300 positions (2.6 MFLOP) 15.0 us against 8.8, 16 -> 16, 3 x
+// 3, 2700 positions (12 MFLOP) 16.3 against 12.6; 32 -> 100, 2 x 2, 2600 positions (67 MFLOP) 17.4 against 14.8, but 2 us less in the
+// reduce for its fewer slabs.
 constexpr double kPartsWgradFlops = 4e7;
-// With bf16 storage, one part (us there -> here): in place of wgrad_mfma_kernel (32 maps or fewer, rectangular filters) 16 -> 32, 5 x 5, 2.8e8 operations 17.5 -> 20.4, 4.7e8
-// 21.2 -> 21.0, 1.7e10 171 -> 51; 16 -> 16, 3 x 3, 1.1e8 16.4 -> 18.5, 4.3e8 24.3 -> 20.9; 64 -> 32 1.4e10 141 -> 49.  Of wgrad_bm_kernel where both counts are multiples of 8:
-// 16 -> 64, 5 x 5, 2.2e9 22.5 -> 25.0, 4.8e9 30.0 -> 27.8; 48 -> 64, 4 x 4, 4.1e9 29.5 -> 32.7, 9.2e9 45 -> 34, 1.4e11 426 -> 260; 40 -> 200, 2 x 2, 3.2e10 144 -> 146.  Other counts
-// that kernel takes channel by channel: 12 -> 100, 4 x 4, 7.8e7 28.0 -> 21.6, 6.3e9 120 -> 43; 100 -> 36, 1 x 1, 6.7e8 72 -> 24.
+// With bf16 storage, one part (us there -> here): in place of wgrad_mfma_kernel (32 maps or fewer, rectangular filters) 16 -> 32, 5 x 5,
+// 2.8e8 operations 17.5 -> 20.4, 4.7e8 21.2 -> 21.0, 1.7e10 171 -> 51; 16 -> 16, 3 x 3, 1.1e8 16.4 -> 18.5, 4.3e8 24.3 -> 20.9; 64 -> 32
+// 1.4e10 141 -> 49.  Of wgrad_bm_kernel where both counts are multiples of 8: 16 -> 64, 5 x 5, 2.2e9 22.5 -> 25.0, 4.8e9 30.0 -> 27.8; 48
+// -> 64, 4 x 4, 4.1e9 29.5 -> 32.7, 9.2e9 45 -> 34, 1.4e11 426 -> 260; 40 -> 200, 2 x 2, 3.2e10 144 -> 146.  Other counts that kernel takes
+// channel by channel: 12 -> 100, 4 x 4, 7.8e7 28.0 -> 21.6, 6.3e9 120 -> 43; 100 -> 36, 1 x 1, 6.7e8 72 -> 24.
 constexpr double kPart1WgradFlops = 4e8, kPart1WgradFlopsBm = 4.5e9;
-// layers that kernel takes: 128-bit (bf16: 64-bit) items of both tensors, more than a sliver of input channels; with bf16 storage those that
-// wgrad_tr_kernel does not take, which is ahead (two column tiles per wave, seven operands for ten products: 64 -> 64, 5 x 5, 2 x 2048 x 2048 1842 against 2304 us)
+// layers that kernel takes: 128-bit (bf16: 64-bit) items of both tensors, more than a sliver of input channels; with bf16 storage those
+// that wgrad_tr_kernel does not take, which is ahead (two column tiles per wave, seven operands for ten products: 64 -> 64, 5 x 5, 2 x 2048
+// x 2048 1842 against 2304 us)
 inline bool wgrad_tr_layer(const Layer& ly) { return !ly.rect && ly.cout > 32 && ly.cin % 32 == 0; }
 inline bool wgrad_parts_layer(const Layer& ly, bool bf16)
 {
@@ -720,8 +729,8 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         max_act = std::max(max_act, bytes);
         if (ly.kind == MPCNN_MP) continue;
         if (ly.fwd_mfma)
-            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct, net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false,
-                                        net->hint_pt, net->hint_mp);
+            g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct,
+                                        net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false, net->hint_pt, net->hint_mp);
         if (training && ly.class_fused) {
             g->partial_n[l] = class_blocks(net, (long)B * r * c);
             g->partial_len[l] = ly.p_len;
@@ -954,7 +963,8 @@ bool launch_l0_wgrad_bm(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, h
 // Kernels that may ask for more than 64 KiB of dynamic LDS must say so once.
 mpcnn_status set_lds_attrs(bool bf16_storage)
 {
-    if (bf16_storage) { HIP_TRY(mpcnn::conv_parts_attrs_b16_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_b16_back()); HIP_TRY(mpcnn::wgrad_attrs_b16()); HIP_TRY(mpcnn::wgrad_parts_attrs<mpcnn::bf16>()); }
+    if (bf16_storage) { HIP_TRY(mpcnn::conv_parts_attrs_b16_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_b16_back());
+                        HIP_TRY(mpcnn::wgrad_attrs_b16()); HIP_TRY(mpcnn::wgrad_parts_attrs<mpcnn::bf16>()); }
     else { HIP_TRY(mpcnn::conv_parts_attrs_f32_fwd()); HIP_TRY(mpcnn::conv_parts_attrs_f32_back());
            HIP_TRY(mpcnn::wgrad_attrs_f32()); HIP_TRY(mpcnn::wgrad_parts_attrs<float>()); }
     return MPCNN_OK;
@@ -1689,8 +1699,8 @@ mpcnn_status mpcnn_net_create(const mpcnn_layer_desc* layers, int n_layers, int 
                 ly.dgrad_pack_len = pack_floats(ly.dgrad_rpad, ly.dgrad_ct.pad);
                 ly.dgrad_pack_off = pack; pack += ly.dgrad_pack_len;
             }
-            // Two fp16 parts per number lose a last bit of one number in four; in a sum whose runs of leading products are added up (kernels_conv_parts.hpp)
-            // that is less than what three parts' roundings come to from about 500 products on.
+            // Two fp16 parts per number lose a last bit of one number in four; in a sum whose runs of leading products are added up
+            // (kernels_conv_parts.hpp) that is less than what three parts' roundings come to from about 500 products on.
             auto half_floats = [&](int rpad, int pad) { return ((size_t)ly.k * ly.k2 * (rpad / 16) + mpcnn::parts_ahead(2)) * 2 * 2 * pad * 4; };
             ly.fwd_half = !net->bf16 && ly.fwd_mfma && l > 0 && mpcnn::half_filter(ly.k, ly.k2) && (long)ly.k * ly.k2 * ly.cin >= mpcnn::kHalfLeast;
             ly.dgrad_half = !net->bf16 && ly.dgrad_mfma && mpcnn::half_filter(ly.k, ly.k2) && (long)ly.k * ly.k2 * ly.cout >= mpcnn::kHalfLeast;
@@ -1765,11 +1775,14 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         va_end(ap);
         if (n > 0) used = std::min(cap - 1, used + (size_t)n);
     };
+    auto parts = [&](bool half) {
+        return net->bf16 ? "one part per number" : half ? "three parts per number or two of fp16" : "three parts per number";
+    };
     auto conv = [&](const char* what, const TilePlan& tp, const ChanTiling& ct, bool half) {
         if (!tp.ok) { put("  %s: plain kernel\n", what); return; }
         put("  %s: bf16 MFMA, %s, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
             "%d channels and %d filter rows per block, tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what,
-            net->bf16 ? "one part per number" : half ? "three parts per number or two of fp16" : "three parts per number", ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
+            parts(half), ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
             tp.in.CB, tp.kr, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
     };
     put("workspace %zu bytes\n", g.total);
@@ -1797,8 +1810,8 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         else if (!w.ok) put("  weight gradient: plain kernel, %d chunks\n", w.chunks);
         else if (w.PM > 0)
             put("  weight gradient: bf16 MFMA, %s, %d x %d x %d waves (rows x columns x positions) of %d row tiles, %d x %d workgroup "
-                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", net->bf16 ? "one part per number" : w.two ? "three parts per number or two of fp16" : "three parts per number", w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg,
-                w.R, 16 * w.nch, w.tiles_total, w.slabs, w.tiles_per_slab, w.lds);
+                "groups (%d planes, %d taps), tile %d x %d, %d tiles in %d slabs of %d, %zu B LDS\n", parts(w.two),
+                w.wm, w.wn, w.wk, w.PM, w.gm, w.gn, w.ppg, w.tpg, w.R, 16 * w.nch, w.tiles_total, w.slabs, w.tiles_per_slab, w.lds);
         else
             put("  weight gradient: %s MFMA, %d x %d result tiles, waves %d x %d x %d (rows x columns x tile rows), %d row "
                 "tiles per wave, %d x %d workgroup groups, tile 4 x %d (%d), %d tiles in %d slabs of %d, %zu B LDS\n",

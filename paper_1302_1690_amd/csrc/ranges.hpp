@@ -1,14 +1,14 @@
 // Powers of two that bring numbers into the range of fp16, for kernels that work on fp16 parts of fp32 numbers (2^-24 to 2^16).
 //
-// Activations of squashing functions are at most 1 in size: 2^14 times as large, or as they are (kernels_conv_parts.hpp).  tanh's are multiples of some 2^-24 (storage.hpp,
-// squash); logistic ones keep their precision however small they are.
-// Weights: a layer's largest magnitude is found when its weights are packed (kernels_pack.hpp).
-// Deltas may have any size.  Whoever writes a tensor of them notes the largest magnitude it has written, as the bits of |x| (which as
-// unsigned numbers have the same order): each workgroup stores one word into the caller's workspace, a reader takes the
-// largest of the words.  Every word is stored in every pass: nothing to clear, and no atomics (2048 waves that end together
-// take 20 us to meet in one word).  A word at or above kNoPeak, as an infinity leaves it or a writer whose weights may put maps too far below each other, says that the tensor does not
-// suit fp16 parts of one power of two.  The weight gradient looks at the maps themselves (kernels_wgrad_parts.hpp).
-// NaN is passed over: it is one in any number of parts, and so is every sum it belongs to.
+// Activations of squashing functions are at most 1 in size: 2^14 times as large, or as they are (kernels_conv_parts.hpp).  tanh's are
+// multiples of some 2^-24 (storage.hpp, squash); logistic ones keep their precision however small they are. Weights: a layer's largest
+// magnitude is found when its weights are packed (kernels_pack.hpp). Deltas may have any size.  Whoever writes a tensor of them notes the
+// largest magnitude it has written, as the bits of |x| (which as unsigned numbers have the same order): each workgroup stores one word into
+// the caller's workspace, a reader takes the largest of the words.  Every word is stored in every pass: nothing to clear, and no atomics
+// (2048 waves that end together take 20 us to meet in one word).  A word at or above kNoPeak, as an infinity leaves it or a writer whose
+// weights may put maps too far below each other, says that the tensor does not suit fp16 parts of one power of two.  The weight gradient
+// looks at the maps themselves (kernels_wgrad_parts.hpp). NaN is passed over: it is one in any number of parts, and so is every sum it
+// belongs to.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -16,8 +16,9 @@ namespace mpcnn {
 
 constexpr unsigned kNoPeak = 0x7f800000u;      // infinity
 constexpr int kActRaise = 14;
-// Where products with a second part have an accumulator of their own (kernels_conv_parts.hpp), second parts are raised by 2^11 more, to the size of the
-// first: numbers down to 2^-28 of the tensor's largest then keep all bits that two parts hold, smaller ones lose those below 2^-51 of it (2^-16 and 2^-40 without).
+// Where products with a second part have an accumulator of their own (kernels_conv_parts.hpp), second parts are raised by 2^11 more, to the
+// size of the first: numbers down to 2^-28 of the tensor's largest then keep all bits that two parts hold, smaller ones lose those below
+// 2^-51 of it (2^-16 and 2^-40 without).
 constexpr float kLowUp = 0x1p11f, kLowDown = 0x1p-11f;
 constexpr int kSmallOctaves = 26;              // weights that far below the largest are counted as small (weights_wide)
 constexpr int kDeltaWords = 2048;              // of a tensor, at most
