@@ -37,7 +37,7 @@
 // conversions lie under the other's instructions.
 //
 // Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), three parts -> two: 522, 1005, 710,
-// 1325 us -> 324, 620, 478, 845 (322, 325, 291, 217 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
+// 1325 us -> 330, 616, 474, 851 (316, 327, 293, 215 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
 // 1.01e-7, with cancelling deltas 1.36e-6, 1.93e-6, 6.3e-7 -> 1.28e-6, 1.72e-6, 5.5e-7. Before (fp32 instruction) and in three parts: 985,
 // 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on random data is 240-260,
 // the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %. Splitting numbers 2^16 times as large (two
@@ -248,6 +248,8 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
     // what numbers are split after being multiplied by, and what takes their products' sums back
     const float in_up = P == 2 ? power_of_two(kActRaise) : kPartsUp;
     float dy_up = turn * kPartsUp;
+    // the factors of this thread's octet of deltas, where registers are left (128 -> 200, 2 x 2, 1024 x 1024: 852 us; read from LDS for every item 890)
+    float own_up[8] = {};
     bool each = false;                                // two parts: not all columns' factors are dy_up (uniform)
     // (two parts: the columns' factors and three words lie behind two parts' two buffers, 128 wn + 12 bytes; the plan has room for three
     // parts' buffers, whose 4 wn delta planes alone are larger by 32 * 16 + 288 bytes and more each)
@@ -325,7 +327,7 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
                 if (first >= g.nh && each) {
                     float ups[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) ups[j] = col_up[8 * qd + j];
+                    for (int j = 0; j < 8; ++j) ups[j] = PM < 9 ? own_up[j] : col_up[8 * qd + j];
                     split_halves<false>(x, p, ups);
                 } else
                     split_halves<false>(x, p, {up, up, up, up, up, up, up, up});
@@ -442,6 +444,8 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
         const int raised = __builtin_amdgcn_readfirstlane(raise_maps(a, turn, col_up, reinterpret_cast<unsigned*>(lds), dy_up));
         if (raised == kNotRaised) return false;
         each = raised == kRaisedEach;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) own_up[j] = col_up[8 * qd + j];
         mine = col_up[32 * nidx + (lane & 31)];
     }
     if (tile_begin < tile_end) to_lds(ldsb);
