@@ -118,35 +118,40 @@ __device__ __forceinline__ bool any_thread(bool yes, unsigned* word)
     __syncthreads();
     return any;
 }
-// Bits of the largest magnitudes of 4 quads channels from c0 on (none past C, a multiple of 4) at kWpSamples * (512 / quads) positions
-// spread over a tensor [positions][C], left in most[] (which is clear)
-__device__ __forceinline__ void sample_maps(const float* t, long positions, int C, int c0, int quads, unsigned* most)
+// A sample of a tensor [positions][C]: this thread's quad of the `quads` from channel c0 on (up to 512; C a multiple of 4) at kWpSamples of kWpSamples * (512 /
+// quads) positions spread over it
+struct Sample { v4f v[kWpSamples]; unsigned quad; bool any; };
+__device__ __forceinline__ Sample sample_maps(const float* t, long positions, int C, int c0, int quads)
 {
-    for (int q0 = 0; q0 < quads; q0 += kWpThreads) {
-        const unsigned nq = quads - q0 < kWpThreads ? quads - q0 : kWpThreads, rows = kWpThreads / nq, row = threadIdx.x / nq, q = q0 + threadIdx.x - row * nq;
-        const int c = c0 + 4 * (int)q;
-        if (row < rows && c < C) {
-            const float stretch = (float)positions / (float)(kWpSamples * rows);
-            v4f v[kWpSamples];
+    Sample s;
+    const unsigned rows = kWpThreads / quads, row = threadIdx.x / (unsigned)quads;
+    s.quad = threadIdx.x - row * quads;
+    const int c = c0 + 4 * (int)s.quad;
+    s.any = row < rows && c < C;
+    const float stretch = (float)positions / (float)(kWpSamples * rows);
 #pragma unroll
-            for (int j = 0; j < kWpSamples; ++j) {    // (all at once)
-                // (inside their stretches the positions are irregular: in step with no map's rows or columns)
-                const unsigned n = row + rows * j;
-                const long at = (long)(((float)n + (float)(n * 40503u & 0xffffu) * 0x1p-16f) * stretch);
-                v[j] = *reinterpret_cast<const v4f*>(t + (at < positions ? at : positions - 1) * C + c);
-            }
-            unsigned m[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int j = 0; j < kWpSamples; ++j)
-#pragma unroll
-                for (int z = 0; z < 4; ++z) {
-                    const unsigned b = bits_of(v[j][z]) & 0x7fffffffu;   // (a NaN is above infinity)
-                    m[z] = b > m[z] ? b : m[z];
-                }
-#pragma unroll
-            for (int z = 0; z < 4; ++z) atomicMax(most + 4 * q + z, m[z]);
-        }
+    for (int j = 0; j < kWpSamples; ++j) {            // (all at once)
+        // (inside their stretches the positions are irregular: in step with no map's rows or columns)
+        const unsigned n = row + rows * j;
+        const long at = (long)(((float)n + (float)(n * 40503u & 0xffffu) * 0x1p-16f) * stretch);
+        s.v[j] = s.any ? *reinterpret_cast<const v4f*>(t + (at < positions ? at : positions - 1) * C + c) : (v4f){0.f, 0.f, 0.f, 0.f};
     }
+    return s;
+}
+// Bits of the largest magnitudes, into most[4 quads] (which is clear)
+__device__ __forceinline__ void largest_of(const Sample& s, unsigned* most)
+{
+    if (!s.any) return;
+    unsigned m[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < kWpSamples; ++j)
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            const unsigned b = bits_of(s.v[j][z]) & 0x7fffffffu;   // (a NaN is above infinity)
+            m[z] = b > m[z] ? b : m[z];
+        }
+#pragma unroll
+    for (int z = 0; z < 4; ++z) atomicMax(most + 4 * s.quad + z, m[z]);
 }
 // The factors of this workgroup's columns with the slab's sign, left in up[32 wn] (three words behind them are used too); `one`: that of
 // all columns but those that need their own. Logistic outputs may be small in a whole map: all of this workgroup's have to reach 2^-12 in
@@ -156,12 +161,17 @@ __device__ __forceinline__ Raised raise_maps(const WgradPartsArgs& a, float turn
 {
     const int cols = 32 * a.wn, c0 = 16 * ((blockIdx.y / a.ntg) * a.ppg), n = a.Ci - c0 < 16 * a.ppg ? a.Ci - c0 : 16 * a.ppg;
     unsigned* const some = reinterpret_cast<unsigned*>(up + cols);   // columns that are not 0 / numbers that do not suit / columns with a factor of their own
+    // (words and sample are on their way together: a trip to memory each would be 2 us of a launch)
+    const PeakTrip words = peak_trip(a.dy_peak, a.dy_words, 0);
+    const Sample deltas = sample_maps(static_cast<const float*>(a.dY), (long)a.B * a.Ho * a.Wo, a.Co, cols * blockIdx.z, cols / 4);
     for (int i = threadIdx.x; i < cols + (a.logistic ? n : 0); i += kWpThreads) most[i] = 0;
     if (threadIdx.x < 3) some[threadIdx.x] = 0;
     __syncthreads();
-    sample_maps(static_cast<const float*>(a.dY), (long)a.B * a.Ho * a.Wo, a.Co, cols * blockIdx.z, cols / 4, most);
-    if (a.logistic) sample_maps(static_cast<const float*>(a.in), (long)a.B * a.Hi * a.Wi, a.Ci, c0, n / 4, most + cols);
-    const unsigned peak = peak_of(a.dy_peak, a.dy_words);
+    const unsigned peak = peak_of(a.dy_peak, a.dy_words, words);
+    largest_of(deltas, most);
+    if (a.logistic)
+        for (int q = 0; q < n / 4; q += kWpThreads)
+            largest_of(sample_maps(static_cast<const float*>(a.in), (long)a.B * a.Hi * a.Wi, a.Ci, c0 + 4 * q, n / 4 - q < kWpThreads ? n / 4 - q : kWpThreads), most + cols + 4 * q);
     const int all = raise_of(peak, a.dy_margin);
     __syncthreads();
     for (int i = threadIdx.x; i < cols + (a.logistic ? n : 0); i += kWpThreads) {
@@ -179,7 +189,9 @@ __device__ __forceinline__ Raised raise_maps(const WgradPartsArgs& a, float turn
     }
     __syncthreads();
     one = turn * power_of_two(all);
-    return !some[0] || some[1] ? kNotRaised : some[2] ? kRaisedEach : kRaisedAlike;
+    const Raised raised = !some[0] || some[1] ? kNotRaised : some[2] ? kRaisedEach : kRaisedAlike;
+    __syncthreads();                                  // (three parts may lay their tiles over these words)
+    return raised;
 }
 
 // Two parts: false if a sum is not finite (nothing is lost: three parts write every result again)

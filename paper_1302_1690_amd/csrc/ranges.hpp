@@ -43,22 +43,30 @@ __device__ __forceinline__ unsigned wave_largest(unsigned m)
     m = larger_moved<0x143, 0xc>(m);   // row_bcast:31 into rows 2 and 3
     return (unsigned)__builtin_amdgcn_readlane((int)m, 63);
 }
-// The largest of a tensor's words (called by whole waves; one trip for 512 words)
-__device__ __forceinline__ unsigned peak_of(const unsigned* words, int n)
+// The largest of a tensor's words (called by whole waves; one trip for 512 words, the first of which a caller may have sent ahead)
+struct PeakTrip { unsigned v[8]; };
+__device__ __forceinline__ PeakTrip peak_trip(const unsigned* words, int n, int i)
+{
+    PeakTrip t;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int at = i + 64 * j + (threadIdx.x & 63);
+        t.v[j] = words[at < n ? at : 0];
+    }
+    return t;
+}
+__device__ __forceinline__ unsigned peak_of(const unsigned* words, int n, PeakTrip t)
 {
     unsigned m = 0;
-    for (int i = 0; i < n; i += 512) {
-        unsigned v[8];
+    for (int i = 512;; i += 512) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int at = i + 64 * j + (threadIdx.x & 63);
-            v[j] = words[at < n ? at : 0];
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) m = v[j] > m ? v[j] : m;
+        for (int j = 0; j < 8; ++j) m = t.v[j] > m ? t.v[j] : m;
+        if (i >= n) break;
+        t = peak_trip(words, n, i);
     }
     return wave_largest(m);
 }
+__device__ __forceinline__ unsigned peak_of(const unsigned* words, int n) { return peak_of(words, n, peak_trip(words, n, 0)); }
 // The exponent that takes numbers of at most `peak` * 2^margin below 2^15
 __device__ __forceinline__ int raise_of(unsigned peak, int margin)
 {
