@@ -673,9 +673,9 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
     unsigned most = 0;
     if constexpr (TRAIN && sizeof(T) == 4) {
         most = wave_largest(bits_of(peak));
-        if (a.peak) {
-            // a map of which the classes see far less than of another has deltas that far below the other's: not for two parts of one raised power (as the
-            // data gradient's kernel, weights_wide)
+        if (a.peak && blockIdx.x == 0) {              // (one word says it for the tensor)
+            // a map of which the classes see far less than of another has deltas that far below the other's: not for two parts raised
+            // by one power of two (as the data gradient's kernel, weights_wide)
             unsigned large = 0, small = 0;            // (small: turned round, so that the smallest comes out as the largest)
 #pragma unroll
             for (int v = 0; v < KV; ++v)
