@@ -37,7 +37,7 @@
 // conversions lie under the other's instructions.
 //
 // Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), three parts -> two: 522, 1005, 710,
-// 1325 us -> 330, 616, 474, 851 (316, 327, 293, 215 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
+// 1325 us -> 317, 591, 432, 847 (329, 341, 322, 216 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
 // 1.01e-7, with cancelling deltas 1.36e-6, 1.93e-6, 6.3e-7 -> 1.28e-6, 1.72e-6, 5.5e-7. Before (fp32 instruction) and in three parts: 985,
 // 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on random data is 240-260,
 // the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %. Splitting numbers 2^16 times as large (two
@@ -103,7 +103,7 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
 // the work again, as they do at once where the sample is not finite or nothing but zeros. Two parts of a number have all their bits down to
 // 2^-3 and an error of 2^-26 (rms) below, so of a map's deltas those that matter lose nothing. 64 -> 128, 3 x 3, deltas 2^-20, 2^-24,
 // 2^-30, 2^-40 of the others': error of a map's gradient 6e-7, 2e-6, 1e-3, 1 with one power of two for all, 1e-7 and less in each now. 64
-// -> 100, 3 x 3, 213 x 213 positions: 42 us without samples, 45 with.
+// -> 100, 3 x 3, 213 x 213 positions: 40.6 us without samples, 43.4 with.
 constexpr int kWpSampled = 12, kWpPlace = 4, kWpSamples = 8;
 
 // Whether any thread of the workgroup says so (*word: in LDS, for this alone)
