@@ -8,6 +8,13 @@
 // LDS's rate times the matrix pipes'.  3 x 501 x 389, 16 -> 32, 5 x 5: 150 -> 48 us (94 -> 295 TFLOP/s); error in the 2-norm on 1500 x 1400
 // 4.1e-8 -> 2.7e-8, 48 -> 64 k4 on 700 x 640 3.9e-8 -> 3.0e-8, smaller maps 2.3e-8 to 3.2e-8 both.
 //
+// Range of two parts.  One accumulator takes all three products, so y1, a delta's second part, can only be 2^11 times as large (as in
+// kernels_conv_parts.hpp) where its partner is 2^-11 as large: x0 2^-11 is made in registers, four multiplications of eight halves for
+// three instructions of 32 cycles.  Deltas keep their bits down to 2^-28 of the tensor's largest, so a map of them that far below the
+// others is as good as they are.  Maps below that come from weights that far apart, of which their writers tell (ranges.hpp), or from
+// slopes: tanh's are 2^-23 at least and off by as much, logistic ones are looked at (logistic_maps_reach).  The inputs' second parts stay
+// as they are: tanh leaves multiples of 2^-24, logistic maps are looked at as well.
+//
 // Accuracy.  All six products go to one accumulator, as there is no room for two, and the instruction's results are a little too low
 // whatever their sign: over the slabs of a large map such offsets add up where roundings cancel.  So every other slab has the signs of its
 // deltas turned, and its sums' signs turned back.  Error of the gradient in the 2-norm, fp32 instruction / without turns / now: 32 -> 64 k5
@@ -37,7 +44,7 @@
 // conversions lie under the other's instructions.
 //
 // Measured on the deep net (1 x 1024 x 1024, 32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), three parts -> two: 522, 1005, 710,
-// 1325 us -> 317, 591, 432, 847 (329, 341, 322, 216 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
+// 1325 us -> 324, 615, 456, 866 (322, 327, 305, 211 TFLOP/s); errors 1.04e-7, 1.61e-7 (k3), 1.09e-7 (k2, 700 x 640) -> 1.01e-7, 1.57e-7,
 // 1.01e-7, with cancelling deltas 1.36e-6, 1.93e-6, 6.3e-7 -> 1.28e-6, 1.72e-6, 5.5e-7. Before (fp32 instruction) and in three parts: 985,
 // 1780, 1210, 2030 us -> 512, 975, 700, 1293 us (204, 206, 199, 142 TFLOP/s; what the split instruction sustains on random data is 240-260,
 // the last layer pads 200 maps to 256 and 59 columns to 64).  Matrix pipes busy 47-67 %. Splitting numbers 2^16 times as large (two
@@ -69,7 +76,7 @@ struct WgradPartsArgs {
     int ppg, tpg, ntg;   // planes and taps per group; groups along the taps (blockIdx.y = plane group * ntg + tap group)
     const unsigned* dy_peak;             // dY's dy_words words (ranges.hpp), or null: not known, or `in` is no output of a squashing function
     int dy_words, dy_margin;             // dY is at most 2^dy_margin times as large as they say
-    int logistic;                        // that function
+    const float* out;                    // the layer's outputs if that function is the logistic one, else null
     unsigned mg_nqh, mg_hwp, mg_txp, mg_tpg, mg_k2, mg_ntx, mg_nty, mg_d, mg_d2;   // ceil(2^32 / x)
 };
 
@@ -96,28 +103,14 @@ __host__ __device__ inline WpGeom wp_geom(int R, int nch, int k, int k2, int ppg
     return g;
 }
 
-// ---- two parts: what deltas are raised by.  One power of two per map (column of the result, where it is undone), so that a map far below
-// the others keeps its bits.  The largest of a map's deltas is not known; that of all of them is (ranges.hpp), and a sample of positions
-// shows what a map has.  One that reaches within kWpSampled octaves of the largest of all is raised like that.  What was found in one below
-// goes to 2^kWpPlace, with room for numbers 2^12 times as large; if there are larger ones, infinities appear in the sums and three parts do
-// the work again, as they do at once where the sample is not finite or nothing but zeros. Two parts of a number have all their bits down to
-// 2^-3 and an error of 2^-26 (rms) below, so of a map's deltas those that matter lose nothing. 64 -> 128, 3 x 3, deltas 2^-20, 2^-24,
-// 2^-30, 2^-40 of the others': error of a map's gradient 6e-7, 2e-6, 1e-3, 1 with one power of two for all, 1e-7 and less in each now. 64
-// -> 100, 3 x 3, 213 x 213 positions: 40.6 us without samples, 43.4 with.
-constexpr int kWpSampled = 12, kWpPlace = 4, kWpSamples = 8;
+// ---- logistic nets in two parts.  A map of logistic units that are off has outputs, and slopes and so deltas, as small as it likes, with
+// all their bits (tanh leaves multiples of 2^-24, and a slope is off by as much).  A sample of positions finds such maps, and three parts are
+// taken: input maps that do not reach 2^-12 and maps of the layer's own outputs that do not reach 2^-20.  (Not of deltas: few positions may
+// have any.)  3 us of a launch.
+constexpr int kWpSamples = 8;
+constexpr float kWpLeastIn = 0x1p-12f, kWpLeastOut = 0x1p-20f;
+constexpr int kWpSampled = 2048;  // most channels of both: their words lie where the first tiles go
 
-// Whether any thread of the workgroup says so (*word: in LDS, for this alone)
-__device__ __forceinline__ bool any_thread(bool yes, unsigned* word)
-{
-    __syncthreads();
-    if (threadIdx.x == 0) *word = 0;
-    __syncthreads();
-    if (yes) atomicOr(word, 1u);
-    __syncthreads();
-    const bool any = *word != 0;
-    __syncthreads();
-    return any;
-}
 // A sample of a tensor [positions][C]: this thread's quad of the `quads` from channel c0 on (up to 512; C a multiple of 4) at kWpSamples of kWpSamples * (512 /
 // quads) positions spread over it
 struct Sample { v4f v[kWpSamples]; unsigned quad; bool any; };
@@ -153,50 +146,31 @@ __device__ __forceinline__ void largest_of(const Sample& s, unsigned* most)
 #pragma unroll
     for (int z = 0; z < 4; ++z) atomicMax(most + 4 * s.quad + z, m[z]);
 }
-// The factors of this workgroup's columns with the slab's sign, left in up[32 wn] (three words behind them are used too); `one`: that of
-// all columns but those that need their own. Logistic outputs may be small in a whole map: all of this workgroup's have to reach 2^-12 in
-// the sample.
-enum Raised { kNotRaised, kRaisedAlike, kRaisedEach };
-__device__ __forceinline__ Raised raise_maps(const WgradPartsArgs& a, float turn, float* up, unsigned* most, float& one)
+// Whether the maps suit two parts (all threads call it; words: LDS)
+__device__ __forceinline__ bool logistic_maps_reach(const WgradPartsArgs& a, unsigned* words)
 {
-    const int cols = 32 * a.wn, c0 = 16 * ((blockIdx.y / a.ntg) * a.ppg), n = a.Ci - c0 < 16 * a.ppg ? a.Ci - c0 : 16 * a.ppg;
-    unsigned* const some = reinterpret_cast<unsigned*>(up + cols);   // columns that are not 0 / numbers that do not suit / columns with a factor of their own
-    // (words and sample are on their way together: a trip to memory each would be 2 us of a launch)
-    const PeakTrip words = peak_trip(a.dy_peak, a.dy_words, 0);
-    const Sample deltas = sample_maps(static_cast<const float*>(a.dY), (long)a.B * a.Ho * a.Wo, a.Co, cols * blockIdx.z, cols / 4);
-    for (int i = threadIdx.x; i < cols + (a.logistic ? n : 0); i += kWpThreads) most[i] = 0;
-    if (threadIdx.x < 3) some[threadIdx.x] = 0;
+    const int c0 = 16 * ((blockIdx.y / a.ntg) * a.ppg), n = a.Ci - c0 < 16 * a.ppg ? a.Ci - c0 : 16 * a.ppg;
+    if (n + a.Co > kWpSampled) return false;
+    unsigned *const low = words, *const out_most = words + 1, *const in_most = out_most + a.Co;
+    for (int i = threadIdx.x; i < 1 + n + a.Co; i += kWpThreads) words[i] = 0;
     __syncthreads();
-    const unsigned peak = peak_of(a.dy_peak, a.dy_words, words);
-    largest_of(deltas, most);
-    if (a.logistic)
-        for (int q = 0; q < n / 4; q += kWpThreads)
-            largest_of(sample_maps(static_cast<const float*>(a.in), (long)a.B * a.Hi * a.Wi, a.Ci, c0 + 4 * q, n / 4 - q < kWpThreads ? n / 4 - q : kWpThreads), most + cols + 4 * q);
-    const int all = raise_of(peak, a.dy_margin);
+    for (int q = 0; q < a.Co / 4; q += kWpThreads)
+        largest_of(sample_maps(a.out, (long)a.B * a.Ho * a.Wo, a.Co, 4 * q, a.Co / 4 - q < kWpThreads ? a.Co / 4 - q : kWpThreads), out_most + 4 * q);
+    for (int q = 0; q < n / 4; q += kWpThreads)
+        largest_of(sample_maps(static_cast<const float*>(a.in), (long)a.B * a.Hi * a.Wi, a.Ci, c0 + 4 * q, n / 4 - q < kWpThreads ? n / 4 - q : kWpThreads), in_most + 4 * q);
     __syncthreads();
-    for (int i = threadIdx.x; i < cols + (a.logistic ? n : 0); i += kWpThreads) {
-        const unsigned m = most[i];
-        bool odd = peak >= kNoPeak || m >= kNoPeak;
-        if (i < cols) {
-            const int e = (int)(m >> 23) - 127, own = kWpPlace - e < 127 ? kWpPlace - e : 127;
-            const bool alike = e + all >= 14 - kWpSampled || cols * (int)blockIdx.z + i >= a.Co;
-            up[i] = turn * power_of_two(alike ? all : own);
-            if (m > 0) some[0] = 1;
-            if (!alike) some[2] = 1;
-        } else
-            odd |= m < bits_of(0x1p-12f);
-        if (odd) some[1] = 1;
-    }
+    bool is = false;
+    for (int i = threadIdx.x; i < a.Co; i += kWpThreads) is |= out_most[i] < bits_of(kWpLeastOut);
+    for (int i = threadIdx.x; i < n; i += kWpThreads) is |= in_most[i] < bits_of(kWpLeastIn);
+    if (is) *low = 1;
     __syncthreads();
-    one = turn * power_of_two(all);
-    const Raised raised = !some[0] || some[1] ? kNotRaised : some[2] ? kRaisedEach : kRaisedAlike;
-    __syncthreads();                                  // (three parts may lay their tiles over these words)
-    return raised;
+    const bool reach = *low == 0;
+    __syncthreads();
+    return reach;
 }
 
-// Two parts: false if a sum is not finite (nothing is lost: three parts write every result again)
 template <int PM, int P, typename T>
-__device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
+__device__ __forceinline__ void wgrad_parts_body(const WgradPartsArgs a, unsigned dy_peak)
 {
     constexpr int kWpPos = wp_pos(P);
     constexpr int SI = kWpItems;
@@ -258,14 +232,9 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
     // signs of this slab's deltas (see Accuracy above)
     const float turn = blockIdx.x & 1 ? -1.f : 1.f;
     // what numbers are split after being multiplied by, and what takes their products' sums back
-    const float in_up = P == 2 ? power_of_two(kActRaise) : kPartsUp;
-    float dy_up = turn * kPartsUp;
-    // the factors of this thread's octet of deltas, where registers are left (128 -> 200, 2 x 2, 1024 x 1024: 852 us; read from LDS for every item 890)
-    float own_up[8] = {};
-    bool each = false;                                // two parts: not all columns' factors are dy_up (uniform)
-    // (two parts: the columns' factors and three words lie behind two parts' two buffers, 128 wn + 12 bytes; the plan has room for three
-    // parts' buffers, whose 4 wn delta planes alone are larger by 32 * 16 + 288 bytes and more each)
-    float* const col_up = reinterpret_cast<float*>(ldsb + 2 * g.buf_b);
+    const int in_raise = P == 2 ? kActRaise : 0, dy_raise = P == 2 ? raise_of(dy_peak, a.dy_margin) : 0;
+    const float in_up = P == 2 ? power_of_two(in_raise) : kPartsUp, dy_up = turn * (P == 2 ? power_of_two(dy_raise) : kPartsUp);
+    const Lower down = P == 2 ? lower_by(in_raise + dy_raise) : Lower{P == 3 ? kPartsDown : 1.f, 1.f};
     float bsum[8];                                    // this thread's share of the bias gradient: channels 8 qd .. of its delta items
 #pragma unroll
     for (int j = 0; j < 8; ++j) bsum[j] = 0.f;
@@ -336,13 +305,8 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
             u32x4 p[P];
             const float up = first >= g.nh ? dy_up : in_up;
             if constexpr (P == 2) {
-                if (first >= g.nh && each) {
-                    float ups[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) ups[j] = PM < 9 ? own_up[j] : col_up[8 * qd + j];
-                    split_halves<false>(x, p, ups);
-                } else
-                    split_halves<false>(x, p, {up, up, up, up, up, up, up, up});
+                if (first >= g.nh) split_halves<true>(x, p, {up, up, up, up, up, up, up, up});
+                else split_halves<false>(x, p, {up, up, up, up, up, up, up, up});
             } else if constexpr (P == 3) split_parts(x, p, up);
             else p[0] = pre[u][0] ^ (first >= g.nh && blockIdx.x & 1 ? 0x80008000u : 0u);   // (the deltas' turned signs)
             char* dst = buf + i_dst[u];
@@ -387,9 +351,11 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
     };
     auto mul = [&](const Op& A, const Op& Bo, v16f& c) {
         if constexpr (P == 2) {
-#define MPCNN_MUL(i, j) c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, A.part[i]), __builtin_bit_cast(f16x8, Bo.part[j]), c, 0, 0, 0)
-            MPCNN_MUL(1, 0); MPCNN_MUL(0, 1); MPCNN_MUL(0, 0);
-#undef MPCNN_MUL
+            const f16x8 x0 = __builtin_bit_cast(f16x8, A.part[0]), x1 = __builtin_bit_cast(f16x8, A.part[1]);
+            const f16x8 y0 = __builtin_bit_cast(f16x8, Bo.part[0]), y1 = __builtin_bit_cast(f16x8, Bo.part[1]);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_f16(x1, y0, c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0 * (_Float16)kLowDown, y1, c, 0, 0, 0);   // (y1: kLowUp times as large)
+            c = __builtin_amdgcn_mfma_f32_32x32x16_f16(x0, y0, c, 0, 0, 0);
             return;
         }
 #define MPCNN_MUL(i, j) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.part[i], Bo.part[j], c, 0, 0, 0)
@@ -450,17 +416,10 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
     int tile_end = tile_begin + a.tiles_per_slab;
     if (tile_end > a.tiles_total) tile_end = a.tiles_total;
     const bool early = wave < 4;
-    if (tile_begin < tile_end) issue(tile_begin, true);
-    float mine = 0.f;                                 // two parts: the factor of this lane's column of the result
-    if constexpr (P == 2) {
-        const int raised = __builtin_amdgcn_readfirstlane(raise_maps(a, turn, col_up, reinterpret_cast<unsigned*>(lds), dy_up));
-        if (raised == kNotRaised) return false;
-        each = raised == kRaisedEach;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) own_up[j] = col_up[8 * qd + j];
-        mine = col_up[32 * nidx + (lane & 31)];
+    if (tile_begin < tile_end) {
+        issue(tile_begin, true);
+        to_lds(ldsb);
     }
-    if (tile_begin < tile_end) to_lds(ldsb);
     if (early) issue(tile_begin + 1 < tile_end ? tile_begin + 1 : tile_begin, tile_begin + 1 < tile_end);
     __syncthreads();
     int cur = 0;
@@ -510,15 +469,13 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
     const int groups = gridDim.y;
     const long plen = (long)groups * a.RT * a.Nt * 1024 + a.Nt * 32;
     float* out = a.partial + (long)blockIdx.x * plen;
-    bool odd = false;
     if (active && kidx == 0) {
         float z = 0.f;                                // NaN as soon as one of the sums is not finite
 #pragma unroll
         for (int p = 0; p < PM; ++p)
 #pragma unroll
             for (int r = 0; r < 16; ++r) z = fmaf(acc[p][r], 0.f, z);
-        odd = __any(z != z);
-        const Lower down = P == 2 ? lower_by(kActRaise + (int)(bits_of(mine) >> 23 & 255) - 127) : Lower{P == 3 ? kPartsDown : 1.f, 1.f};
+        const bool odd = P == 3 && __any(z != z);      // (two parts: every number is finite, and no sum overflows)
 #pragma unroll
         for (int p = 0; p < PM; ++p)
             if (midx * PM + p < a.RT) {
@@ -601,7 +558,6 @@ __device__ __forceinline__ bool wgrad_parts_body(const WgradPartsArgs a)
             if (bt < a.Nt) out[(long)groups * a.RT * a.Nt * 1024 + bt * 32 + (tid & 31)] = s;
         }
     }
-    return P != 2 || !any_thread(odd, reinterpret_cast<unsigned*>(lds));
 }
 
 // fp32 storage: in two parts where both tensors suit them
@@ -609,9 +565,14 @@ template <int PM, typename T>
 __global__ __launch_bounds__(kWpThreads, 1) void wgrad_parts_kernel(WgradPartsArgs a)
 {
     if constexpr (sizeof(T) == 4) {
-        if (!a.dy_peak || !wgrad_parts_body<PM, 2, T>(a)) wgrad_parts_body<PM, 3, T>(a);
+        extern __shared__ __attribute__((aligned(16))) float lds[];
+        unsigned peak = kNoPeak;
+        if (a.dy_peak) peak = peak_of(a.dy_peak, a.dy_words);
+        if (peak < kNoPeak && a.out && !logistic_maps_reach(a, reinterpret_cast<unsigned*>(lds))) peak = kNoPeak;
+        if (peak < kNoPeak) wgrad_parts_body<PM, 2, T>(a, peak);
+        else wgrad_parts_body<PM, 3, T>(a, peak);
     } else
-        wgrad_parts_body<PM, 1, T>(a);
+        wgrad_parts_body<PM, 1, T>(a, 0);
 }
 
 }  // namespace mpcnn

@@ -1335,7 +1335,8 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
                     a.tiles_total = wp.tiles_total; a.tiles_per_slab = wp.tiles_per_slab;
                     a.Nt = wp.Nt; a.RT = wp.RT; a.wm = wp.wm; a.wn = wp.wn; a.wk = wp.wk;
                     a.ppg = wp.ppg; a.tpg = wp.tpg; a.ntg = wp.ntg;
-                    a.dy_peak = delta_words(g, ws, li); a.dy_words = g.delta_words[li]; a.dy_margin = g.delta_margin[li]; a.logistic = net->logistic;
+                    a.dy_peak = delta_words(g, ws, li); a.dy_words = g.delta_words[li]; a.dy_margin = g.delta_margin[li];
+                    a.out = net->logistic && kF32 && ly.tanh_out ? (const float*)(ws + g.act_off[li]) : nullptr;
                     if (!wp.two) a.dy_peak = nullptr;
                     a.mg_nqh = magic_of(2 * wp.ppg); a.mg_hwp = magic_of(16 * wp.nch + ly.k2 - 1); a.mg_txp = magic_of(16 * wp.nch);
                     a.mg_tpg = magic_of(wp.tpg); a.mg_k2 = magic_of(ly.k2); a.mg_ntx = magic_of(wp.ntx); a.mg_nty = magic_of(wp.nty);

@@ -6,9 +6,9 @@
 // largest magnitude it has written, as the bits of |x| (which as unsigned numbers have the same order): each workgroup stores one word into
 // the caller's workspace, a reader takes the largest of the words.  Every word is stored in every pass: nothing to clear, and no atomics
 // (2048 waves that end together take 20 us to meet in one word).  A word at or above kNoPeak, as an infinity leaves it or a writer whose
-// weights may put maps too far below each other, says that the tensor does not suit fp16 parts of one power of two.  The weight gradient
-// looks at the maps themselves (kernels_wgrad_parts.hpp). NaN is passed over: it is one in any number of parts, and so is every sum it
-// belongs to.
+// weights may put maps too far below each other, says that the tensor does not suit fp16 parts of one power of two.  In logistic nets
+// the weight gradient looks at the maps as well (kernels_wgrad_parts.hpp).  NaN is passed over: it is one in any number of parts, and so is
+// every sum it belongs to.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -16,9 +16,9 @@ namespace mpcnn {
 
 constexpr unsigned kNoPeak = 0x7f800000u;      // infinity
 constexpr int kActRaise = 14;
-// Where products with a second part have an accumulator of their own (kernels_conv_parts.hpp), second parts are raised by 2^11 more, to the
-// size of the first: numbers down to 2^-28 of the tensor's largest then keep all bits that two parts hold, smaller ones lose those below
-// 2^-51 of it (2^-16 and 2^-40 without).
+// Second parts are raised by 2^11 more, to the size of the first: numbers down to 2^-28 of the tensor's largest then keep all bits that two
+// parts hold, smaller ones lose those below 2^-51 of it (2^-16 and 2^-40 without).  Their products go to an accumulator of their own
+// (kernels_conv_parts.hpp) or have a partner that much smaller (kernels_wgrad_parts.hpp: deltas; its inputs' second parts stay as they are).
 constexpr float kLowUp = 0x1p11f, kLowDown = 0x1p-11f;
 constexpr int kSmallOctaves = 26;              // weights that far below the largest are counted as small (weights_wide)
 constexpr int kDeltaWords = 2048;              // of a tensor, at most
@@ -43,30 +43,22 @@ __device__ __forceinline__ unsigned wave_largest(unsigned m)
     m = larger_moved<0x143, 0xc>(m);   // row_bcast:31 into rows 2 and 3
     return (unsigned)__builtin_amdgcn_readlane((int)m, 63);
 }
-// The largest of a tensor's words (called by whole waves; one trip for 512 words, the first of which a caller may have sent ahead)
-struct PeakTrip { unsigned v[8]; };
-__device__ __forceinline__ PeakTrip peak_trip(const unsigned* words, int n, int i)
-{
-    PeakTrip t;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int at = i + 64 * j + (threadIdx.x & 63);
-        t.v[j] = words[at < n ? at : 0];
-    }
-    return t;
-}
-__device__ __forceinline__ unsigned peak_of(const unsigned* words, int n, PeakTrip t)
+// The largest of a tensor's words (called by whole waves; one trip for 512 words)
+__device__ __forceinline__ unsigned peak_of(const unsigned* words, int n)
 {
     unsigned m = 0;
-    for (int i = 512;; i += 512) {
+    for (int i = 0; i < n; i += 512) {
+        unsigned v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) m = t.v[j] > m ? t.v[j] : m;
-        if (i >= n) break;
-        t = peak_trip(words, n, i);
+        for (int j = 0; j < 8; ++j) {
+            const int at = i + 64 * j + (threadIdx.x & 63);
+            v[j] = words[at < n ? at : 0];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m = v[j] > m ? v[j] : m;
     }
     return wave_largest(m);
 }
-__device__ __forceinline__ unsigned peak_of(const unsigned* words, int n) { return peak_of(words, n, peak_trip(words, n, 0)); }
 // The exponent that takes numbers of at most `peak` * 2^margin below 2^15
 __device__ __forceinline__ int raise_of(unsigned peak, int margin)
 {
