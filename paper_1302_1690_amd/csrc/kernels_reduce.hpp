@@ -21,7 +21,8 @@ struct ReduceSeg {
     long plen;          // floats per partial
     int items, n, block0;
     int tiled, Nt, rows_total, Co;   // tiled: 0 flat, 1 tiled, 2 the per-workgroup loss shares (fp64), 3 tiled with the bias as row rows_total,
-                                     // 4 tiled with row tiles of two units (wgrad_parts_kernel), which the rest describes
+                                     // 4 tiled with row tiles of two units (wgrad_parts_kernel), which the rest describes; 5 flat,
+                                     // 16 items per workgroup, the partials dealt to 16 thread rows (few items, many partials)
     int RT, ppg, tpg, ntg, Ci, kk;   // row tiles, planes and taps per group, groups along the taps; layer inputs, taps
 };
 struct ReduceArgs {
@@ -55,6 +56,35 @@ __global__ __launch_bounds__(256) void reduce_all_kernel(ReduceArgs a)
         if (threadIdx.x == 0) {
             double* o = reinterpret_cast<double*>(sg.out);
             *o = a.accumulate ? *o + tree[0] : tree[0];
+        }
+        return;
+    }
+    if (sg.tiled == 5) {
+        double* sums = &red[0][0][0];
+        const int own = threadIdx.x & 15, deal = threadIdx.x >> 4, at = ((int)blockIdx.x - sg.block0) * 16 + own;
+        double s0 = 0.0, s1 = 0.0;
+        if (at < sg.items) {
+            int i = deal;
+            for (; i + 112 < n; i += 128) {           // 8 loads in flight
+                float u[8];
+#pragma unroll
+                for (int z = 0; z < 8; ++z) u[z] = partial[(long)(i + 16 * z) * plen + at];
+#pragma unroll
+                for (int z = 0; z < 8; z += 2) { s0 += (double)u[z]; s1 += (double)u[z + 1]; }
+            }
+            float u[8];
+#pragma unroll
+            for (int z = 0; z < 8; ++z) u[z] = i + 16 * z < n ? partial[(long)(i + 16 * z) * plen + at] : 0.f;
+#pragma unroll
+            for (int z = 0; z < 8; z += 2) { s0 += (double)u[z]; s1 += (double)u[z + 1]; }
+        }
+        sums[threadIdx.x] = s0 + s1;
+        __syncthreads();
+        if (deal == 0 && at < sg.items) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s += sums[16 * i + own];
+            sg.out[at] = a.accumulate ? sg.out[at] + (float)s : (float)s;
         }
         return;
     }

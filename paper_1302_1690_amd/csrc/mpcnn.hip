@@ -32,6 +32,7 @@
 #include "kernels_first_f32.hpp"
 #include "kernels_l0_wgrad.hpp"
 #include "kernels_fused.hpp"
+#include "kernels_small.hpp"
 
 // Device memory of mpcnn_seg_forward_static: a fixed array in the library's device image, so that
 // the call needs no allocation.  Every GPU the library runs on holds its own copy, at its own
@@ -167,6 +168,11 @@ struct Geom {
     bool l0_fused = false;
     int l0_blocks = 0, l0_nty = 0, l0_ntx = 0;
     size_t l0_lds = 0;
+    // nets of few maps: the whole pass in one launch (small_net_kernel; what depends on a call's buffers is filled in then)
+    bool small_net = false;
+    mpcnn::SmallArgs small{};
+    int small_wgs = 0;
+    size_t small_lds = 0, small_partial_off = 0;
     size_t total = 0;
 };
 
@@ -696,6 +702,88 @@ bool squashed_input(const Geom& g, size_t l) { return l > 0 && g.squashed[l - 1]
 bool two_part_forward(const mpcnn_net* net, const Geom& g, size_t l) { return net->layers[l].fwd_half && squashed_input(g, l); }
 bool two_part_dgrad(const mpcnn_net* net, const Geom& g, size_t l) { return net->layers[l].dgrad_half && g.delta_peak[l] >= 0; }
 
+// Places in LDS of small_net_kernel's maps above a square of T x T pixels; its bytes, and the multiply-adds of a forward pass over it
+size_t small_places(const mpcnn_net* net, int T, bool training, mpcnn::SmallArgs* a, double* work)
+{
+    const int L = (int)net->layers.size();
+    int ex = 0;
+    for (int l = L; l-- > 0;) {
+        const Layer& ly = net->layers[l];
+        mpcnn::SmallLayer& s = a->layer[l];
+        s.pool = ly.kind == MPCNN_MP; s.k = ly.k; s.d = ly.dil; s.ci = ly.cin; s.co = ly.cout; s.squash = ly.tanh_out;
+        s.w = (int)ly.p_off; s.ex = ex; s.side = T + ex;
+        s.mg_co = magic_of(ly.cout); s.mg_ci = magic_of(ly.cin); s.mg_k = magic_of(ly.k); s.mg_side = magic_of(s.side);
+        s.mg_items = s.pool ? 0 : magic_of((unsigned)ly.p_len);
+        ex += (ly.k - 1 + ly.drop) * ly.dil;
+    }
+    a->T = T; a->ex0 = ex; a->side0 = T + ex; a->mg_side0 = magic_of(a->side0); a->C = net->in_ch; a->mg_c = magic_of(a->C);
+    a->n_layers = L; a->n_params = (int)net->n_params; a->n_cls = net->n_cls; a->training = training ? 1 : 0;
+    a->mg_t = magic_of(T);
+    size_t off = net->n_params, deltas = (size_t)T * T * net->n_cls;
+    a->table = (int)off; off += (size_t)64 * L;
+    a->grad = (int)off;
+    if (training) off += net->n_params;
+    a->red = (int)off;
+    if (training) off += mpcnn::kSmallRed;
+    a->img = (int)off; off += (size_t)a->side0 * a->side0 * a->C;
+    *work = 0;
+    for (int l = 0; l < L; ++l) {
+        mpcnn::SmallLayer& s = a->layer[l];
+        const size_t n = (size_t)s.side * s.side * s.co;
+        s.act = (int)off; off += n;
+        if (l + 1 < L) deltas = std::max(deltas, n);
+        *work += (double)n * s.k * s.k * (s.pool ? 1 : s.ci);
+    }
+    for (int i = 0; i < 2; ++i) { a->delta[i] = (int)off; if (training) off += deltas; }
+    off *= sizeof(float);
+    for (int l = 0; l < L; ++l)
+        if (a->layer[l].pool) { a->layer[l].code = (int)off; off += (size_t)a->layer[l].side * a->layer[l].side * a->layer[l].co; }
+    return align_up(off, 16);
+}
+constexpr size_t kSmallLds = 64 * 1024 - 2048;   // (the arguments and the sums of the loss lie beside)
+// Nets that small_net_kernel takes, at every size (so that a pixel's probabilities do not depend on the call that computes them): fp32 storage,
+// square windows and filters, nothing for the convolutions' matrix instruction, and a square whose halo costs no more than the pixels themselves.
+bool small_net_fits(const mpcnn_net* net)
+{
+    if (net->bf16 || net->layers.size() > (size_t)mpcnn::kSmallLayers || net->n_params > mpcnn::kSmallParams || net->hint_pt || net->hint_mp) return false;
+    for (const Layer& ly : net->layers)
+        if (ly.rect || ly.k2 != ly.k || ly.drop2 != ly.drop || ly.dil2 != ly.dil || ly.k > 32 || ly.fwd_mfma || ly.cin > mpcnn::kSmallChannels ||
+            ly.cout > mpcnn::kSmallChannels) return false;
+    mpcnn::SmallArgs a{};
+    double pixel = 0;
+    for (const Layer& ly : net->layers) pixel += (double)ly.cout * ly.k * ly.k * (ly.kind == MPCNN_MP ? 1 : ly.cin);
+    for (int T = 4; T <= mpcnn::kSmallSide; T += 2) {
+        double work = 0;
+        if (small_places(net, T, true, &a, &work) > kSmallLds) break;
+        if (work <= 2 * pixel * T * T) return true;
+    }
+    return false;
+}
+void plan_small(const mpcnn_net* net, Geom* g, int out_r, int out_c)
+{
+    g->small_net = false;
+    if (!small_net_fits(net)) return;
+    double best = -1;
+    for (int T = 4; T <= mpcnn::kSmallSide; T += 2) {
+        mpcnn::SmallArgs a{};
+        double work = 0;
+        const size_t lds = small_places(net, T, g->training, &a, &work);
+        if (lds > kSmallLds) break;
+        a.nty = ceil_div(out_r, T); a.ntx = ceil_div(out_c, T);
+        const long tiles = (long)g->B * a.nty * a.ntx;
+        if (tiles * std::max(a.nty, a.ntx) >= (1l << 31)) continue;
+        // A square takes as long as its multiply-adds and some 7600 more per layer (steps and barriers); two that share a compute unit take 1.35
+        // times as long as one.
+        const long per_cu = (tiles + kNumCU - 1) / kNumCU;
+        const double cost = (per_cu / 2 * 1.35 + per_cu % 2) * (7600.0 * net->layers.size() + work);
+        if (best >= 0 && cost >= best) continue;
+        best = cost;
+        a.tiles = (int)tiles; a.mg_ntx = magic_of(a.ntx); a.mg_nty = magic_of(a.nty);
+        g->small_net = true; g->small = a; g->small_lds = lds;
+        g->small_wgs = (int)std::min<long>(tiles, mpcnn::kSmallWgs);
+    }
+}
+
 bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g, bool mirrored = false,
                bool fixed_partials = false)
 {
@@ -715,6 +803,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         g->staged_off = off;
         off = align_up(off + es * (size_t)B * H * W * net->in_ch);
     }
+    plan_small(net, g, H - net->patch + 1, W - net->patch + 1);
     int r = H, c = W;
     for (size_t l = 0; l < L; ++l) {
         const Layer& ly = net->layers[l];
@@ -727,7 +816,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         g->rows[l] = r; g->cols[l] = c;
         size_t bytes = es * (size_t)B * r * c * ly.cout;
         max_act = std::max(max_act, bytes);
-        if (ly.kind == MPCNN_MP) continue;
+        if (ly.kind == MPCNN_MP || g->small_net) continue;
         if (ly.fwd_mfma)
             g->fwd[l] = plan_conv_parts(B, in_c, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct,
                                         net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false, net->hint_pt, net->hint_mp);
@@ -741,6 +830,22 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         }
     }
     if (r != H - net->patch + 1 || c != W - net->patch + 1) return false;
+    if (g->small_net) {
+        off = 0;                                      // (the image is read as it comes)
+        for (size_t l = 0; training && l < L; ++l) {
+            const size_t elems = (size_t)B * g->rows[l] * g->cols[l] * net->layers[l].cout;
+            g->act_off[l] = off; off = align_up(off + sizeof(float) * elems);
+            if (net->layers[l].kind == MPCNN_MP) { g->code_off[l] = off; off = align_up(off + elems); }
+            g->small.layer[l].rows = g->rows[l]; g->small.layer[l].cols = g->cols[l];
+        }
+        g->small_partial_off = off;
+        if (training) off = align_up(off + sizeof(float) * net->n_params * (fixed_partials ? mpcnn::kSmallWgs : g->small_wgs));
+        g->loss_partial_off = off;
+        g->total = align_up(off + sizeof(double) * mpcnn::kSmallWgs);
+        g->label_h = H; g->probs_rows = r; g->accumulate = false;
+        g->small.B = B; g->small.W = W; g->small.Ho = r; g->small.Wo = c; g->small.ctr = (net->patch - 1) / 2;
+        return true;
+    }
     plan_peaks(net, g);
     for (size_t l = 0; training && l < L; ++l) {
         const Layer& ly = net->layers[l];
@@ -1085,6 +1190,30 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
     constexpr double es = sizeof(T);
     mpcnn_status rc = refresh_packs(net, st);
     if (rc != MPCNN_OK) return rc;
+    if constexpr (kF32)
+        if (g.small_net) {
+            SmallArgs a = g.small;
+            a.image = image; a.params = net->d_params; a.labels = labels; a.pixw = pixw; a.probs = probs;
+            a.partial = (float*)(ws + g.small_partial_off);
+            a.loss_partial = labels && loss_dev ? (double*)(ws + g.loss_partial_off) : nullptr;
+            a.Hs = g.src_h; a.Ws = g.src_w; a.top = g.pad_top; a.left = g.pad_left;
+            a.label_h = g.label_h; a.probs_rows = g.probs_rows;
+            a.mse = net->loss_kind == MPCNN_LOSS_MSE; a.logistic = net->logistic;
+            double flops = 0;
+            for (int l = 0; l < a.n_layers; ++l) {
+                const Layer& ly = net->layers[l];
+                if (ly.kind != MPCNN_MP) flops += 2.0 * g.B * g.rows[l] * g.cols[l] * ly.cout * ly.k * ly.k * ly.cin * (g.training ? (l ? 3.0 : 2.0) : 1.0);
+                if (!g.training) continue;
+                a.layer[l].act_out = (float*)(ws + g.act_off[l]);
+                if (a.layer[l].pool) a.layer[l].code_out = (uint8_t*)(ws + g.code_off[l]);
+            }
+            net->loss_out = loss_dev;
+            net->loss_shares = a.loss_partial ? g.small_wgs : 0;
+            LAUNCH("small_net", -1, 1, flops, 4.0 * g.B * ((double)a.C * g.H * g.W + (double)net->n_cls * a.Ho * a.Wo),
+                   small_net_kernel<<<(unsigned)g.small_wgs, kSmallThreads, g.small_lds, st>>>(a));
+            HIP_TRY(hipGetLastError());
+            return MPCNN_OK;
+        }
     const int B = g.B;
     T* dZ = static_cast<T*>(dZ_);
     const T* in = nullptr;
@@ -1238,8 +1367,8 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
     else if constexpr (kF32) in0 = image;
     T* dbuf[2] = {(T*)(ws + g.delta_off[0]), (T*)(ws + g.delta_off[1])};
     int cur = 0;  // dbuf[cur] holds dL/d(pre-activation) of layer l's output (dL/d(output) for MP)
-    // a fused class layer has already done its own backward and left the delta below it
-    for (size_t li = net->layers[L - 1].class_fused ? L - 1 : L; li-- > 0;) {
+    // a fused class layer has already done its own backward and left the delta below it (a small net's pass has done all)
+    for (size_t li = g.small_net ? 0 : net->layers[L - 1].class_fused ? L - 1 : L; li-- > 0;) {
         const Layer& ly = net->layers[li];
         const int Ho = g.rows[li], Wo = g.cols[li];
         const T* A = li == 0 ? in0 : (const T*)(ws + g.act_off[li - 1]);
@@ -1443,6 +1572,14 @@ mpcnn_status run_backward(mpcnn_net* net, const Geom& g, const float* image, cha
     ReduceArgs ra{};
     ra.accumulate = g.accumulate ? 1 : 0;
     double rbytes = 0;
+    if (g.small_net) {
+        ReduceSeg& sg = ra.seg[ra.n_seg++];
+        sg.partial = (const float*)(ws + g.small_partial_off);
+        sg.out = net->d_grads;
+        sg.plen = (long)net->n_params; sg.n = g.small_wgs; sg.tiled = 5; sg.items = (int)net->n_params;
+        ra.total_blocks = ceil_div(sg.items, 16);
+        rbytes = 4.0 * net->n_params * (g.small_wgs + 1.0);
+    }
     for (size_t l = 0; l < L; ++l) {
         if (!g.partial_n[l] || ra.n_seg >= kMaxReduceSegs) continue;
         const Layer& ly = net->layers[l];
@@ -1787,12 +1924,14 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
             tp.in.CB, tp.kr, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
     };
     put("workspace %zu bytes\n", g.total);
+    if (g.small_net) put("whole net in one launch: squares of %d x %d pixels, %d x %d of them, %d workgroups, %zu B LDS\n",
+                         g.small.T, g.small.T, g.small.nty, g.small.ntx, g.small_wgs, g.small_lds);
     for (size_t l = 0; l < net->layers.size(); ++l) {
         const Layer& ly = net->layers[l];
         put("layer %zu: %s %d -> %d channels, k %d x %d, spacing %d x %d, map %d x %d\n", l,
             ly.kind == MPCNN_MP ? "MP" : (ly.kind == MPCNN_C ? "C" : "FC"), ly.cin, ly.cout, ly.k, ly.k2, ly.dil, ly.dil2,
             g.rows[l], g.cols[l]);
-        if (ly.kind == MPCNN_MP) continue;
+        if (ly.kind == MPCNN_MP || g.small_net) continue;
         if (ly.class_fused) { put("  fused class layer, %d workgroups\n", g.partial_n[l]); continue; }
         const bool img_sides = ly.dil == 1 && !ly.rect && (ly.k == 3 || ly.k == 5 || ly.k == 7);
         if (!g.fwd[l].ok && l == 0 && net->bf16 && img_sides && ly.cin <= 4 && ly.cout <= 64)
