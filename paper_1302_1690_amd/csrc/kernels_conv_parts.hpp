@@ -53,11 +53,20 @@
 //     layer's forward, one image, 1814 whole: without stores 1249, without the next halos 1255, without weights 1616, without the multiplications 1390.
 //   Slower than the fp32 instruction's kernel: fp32 launches on one or two thousand positions with at most 16 channels (9 against 7).
 //
+// THE CLASS LAYER AT THE END (HEAD; forward passes that keep nothing).  The hidden layer's outputs are read once, by the class layer: written and read
+// again they were a third of this layer's time with bf16 storage.  Here all channels lie in one workgroup (eight waves for more than 128 with fp32
+// storage), a lane multiplies its sixteen of a position by the classes' weights, a half of the wave adds to the other, the waves meet in LDS and a
+// thread per position ends with softmax and loss: the sums in class_layer_kernel's order, equal bits.  The halo is then staged once, not once per 128
+// channels.  Both launches -> one, microseconds: 128 -> 200, 2 x 2, bf16 2048 x 2048 1756 + 375 -> 1366; fp32 1024 x 1024 1065 + 164 -> 1007; 64 -> 100,
+// 3 x 3, fp32 301 x 293 58.8 + 9.4 -> 59.9.
+//
 // Summation order is the step order for every output element, whatever the tiling: equal inputs give bit-equal outputs (exact pooling ties
 // stay exact) and a position's value does not depend on how the map is cut.  A data gradient in two parts does depend on the tensor's
 // largest delta: by powers of two that change no bit of numbers down to 2^-28 of it, and by the choice of three parts for the whole tensor
 // where it is infinite.
 #pragma once
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "kernels_mfma.hpp"
@@ -71,8 +80,8 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 // Geometry shared with the host's plan.
-constexpr int kPartsThreads = 256;   // four waves
-__host__ __device__ constexpr int parts_round(int CB) { return kPartsThreads / (CB / 8); }                  // halo positions one round of the threads stages
+constexpr int kPartsThreads = 256;   // four waves (a wide class layer's: eight)
+__host__ __device__ constexpr int parts_round(int CB, int waves = 4) { return 64 * waves / (CB / 8); }      // halo positions one round of the threads stages
 __host__ __device__ constexpr int parts_wgs(int parts, int tiles) { return parts == 1 && tiles <= 4 ? 3 : 2; }   // workgroups that share a compute unit
 __host__ __device__ constexpr int parts_items(int parts, int tiles)                                         // rounds, at most: what waits in registers; one part: fits in LDS
 {
@@ -100,6 +109,9 @@ __host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps
 {
     return parts != 1 ? 0 : taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
 }
+// With the class layer, behind the table, in floats: the threads' losses (fp64), its weights, one class after the other, the waves' sums of a tile
+__host__ __device__ inline int parts_head_at(int parts, int CB, int rpad, int taps) { return (parts_table(parts, CB, rpad, taps) + 3) / 4 * 4; }
+__host__ __device__ inline int parts_head(int n, int WO, int MO, int positions) { return 2 * positions + n * 32 * WO * MO + WO * n * positions; }
 // steps of weights that follow the last in a pack, the first ones again: the ring runs ahead without a look at the end
 __host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4 : 8; }
 
@@ -169,14 +181,15 @@ __device__ __forceinline__ bool weights_wide(const ConvArgs& a)
 // products and weights of 16 are off by 2^-26.
 __device__ __forceinline__ bool weights_large(const ConvArgs& a) { return a.logistic && a.w_peak[0] >= bits_of(16.f); }
 
-template <typename T, int P, bool BACK, int CB, int WO, int WP, int MO, int MP>
+template <typename T, int P, bool BACK, int CB, int WO, int WP, int MO, int MP, bool HEAD>
 __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_peak)
 {
-    static_assert(WO * WP == 4, "four waves");
+    static_assert(WO * WP == 4 || (HEAD && WO * WP == 8), "four waves");
+    constexpr int kThreads = 64 * WO * WP;
     constexpr bool kF32 = sizeof(T) == 4;
     static_assert(kF32 ? P == 2 || P == 3 : P == 1, "parts of the storage type");
     constexpr int QN = CB / 8, NSUB = CB / 16, NS = parts_ring(P, MO * MP);
-    constexpr int RP = parts_round(CB), SI = parts_items(P, MO * MP), PITCH = parts_pitch(P, CB);
+    constexpr int RP = parts_round(CB, WO * WP), SI = parts_items(P, MO * MP), PITCH = parts_pitch(P, CB);
     constexpr int GO = parts_group(CB), POSB = 16 * GO;   // one part: octets of a group, bytes of a position in it
     constexpr unsigned kNone = 0x80000000u;           // byte offset no buffer reaches: the load returns zeros
     const T* in_t = static_cast<const T*>(a.in);
@@ -286,7 +299,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             const_cast<T*>(in_t + (((long)g.b * a.Hi + iy0) * a.Wi + ix0) * a.Cr), 0, 0x7fffffff, 0x00020000);
         const int mine = lane / GO;
         const unsigned oct = (unsigned)(swapped(mine * POSB + lane % GO * 16) >> 4) % GO;   // (LP positions on, an octet's place is the same)
-        for (int at = LP * wave; at < npos; at += 4 * LP) {
+        for (int at = LP * wave; at < npos; at += WO * WP * LP) {
             const unsigned pos = at + mine;
             const unsigned ha = parts_div(pos, a.mg_hw, hw), hb = pos - ha * hw;
             const int iy = iy0 + (int)ha * a.d, ix = ix0 + (int)hb * a.d2;
@@ -309,7 +322,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         else __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
         const int oct = (a.Cr >> 3) - cb * QN;
         if ((a.Cr & 7) && oct >= 0 && oct < QN)
-            for (int at = LP * wave; at < npos; at += 4 * LP)
+            for (int at = LP * wave; at < npos; at += WO * WP * LP)
                 if (lane < LP) *reinterpret_cast<u32x2*>(ldsb + oct / GO * GB + swapped((at + lane) * POSB + oct % GO * 16) + 8) = (u32x2){0, 0};
     };
 
@@ -325,10 +338,33 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     int* const table = reinterpret_cast<int*>(bias_l + 32 * WO * MO);
     if constexpr (P == 1) {
         const int taps = a.kr * a.k2, all = taps * ((CB < a.CrPad ? CB : a.CrPad) / 16);
-        for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kPartsThreads) {
+        for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kThreads) {
             const int sub = i / taps, r = i - sub * taps, ta = r / a.k2, tb = r - ta * a.k2;
             table[i] = i < all ? (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16 : 0;
         }
+    }
+
+    // ---- the class layer's weights, zeros for channels that do not exist; its outputs' sums, [wave's channels][class][position]
+    constexpr int kChannels = 32 * WO * MO, kPositions = 32 * WP * MP;
+    static_assert(!HEAD || kPositions <= kThreads, "a thread a position");
+    float* const head_w = bias_l + kChannels + (HEAD ? parts_head_at(P, CB, a.CrPad, a.kr * a.k2) : 0);
+    // (the arguments are read where they are used, and a thread's loss stays in LDS: there are no registers left in the loop)
+    typedef const __attribute__((address_space(4))) HeadArgs* HeadPtr;
+    auto head_args = [&] {
+        unsigned at = offsetof(ConvArgs, head);
+        asm volatile("" : "+s"(at));
+        return (HeadPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + at);
+    };
+    double* const head_loss = reinterpret_cast<double*>(head_w);
+    float* const head_wl = head_w + 2 * kPositions;
+    if constexpr (HEAD) {
+        const HeadPtr h = head_args();
+        const int n = h->n;
+        for (int i = tid; i < n * kChannels; i += kThreads) {
+            const int o = i / kChannels, c = i % kChannels;
+            head_wl[i] = c < a.Co ? h->Wk[c * n + o] : 0.f;
+        }
+        if (tid < kPositions) head_loss[tid] = 0.0;
     }
 
     // ---- per lane: LDS address of the positions it feeds as the B operand, at tap 0
@@ -768,6 +804,125 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         }
     };
 
+    // ---- the class layer, on the outputs as they would be stored: sums over each tile's channels in the order of class_layer_kernel, so that
+    // the probabilities are the same bits.  `kept`: the outputs of this tile are in memory (sums that were not finite have been repaired there).
+    auto head_part = [&](const Tile& g, int fh, int fw, bool kept) {
+#pragma unroll
+        for (int p = 0; p < MP; ++p) {
+            const unsigned m = 32 * (wp * MP + p) + lt;
+            const int ty = (int)parts_div(m, a.mg_tx, a.Tx), tx = (int)m - ty * a.Tx;
+            const int fy = g.ty0 + ty, fx = g.tx0 + tx;
+            const bool exists = ty < a.Ty && fy < fh && fx < fw;
+            const T* const mine = out_t + (((long)g.b * a.Ho + (fy * a.d + g.ry)) * a.Wo + (fx * a.d2 + g.rx)) * a.Co;
+#pragma unroll
+            for (int o = 0; o < MO; ++o)
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const int oc = oc0 + 32 * o + 8 * n + 4 * lg;
+                    const v4f bias = *reinterpret_cast<const v4f*>(bias_l + oc);
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        float v = acc[o][p][4 * n + z];
+                        if constexpr (P == 2) v *= down.first;
+                        acc[o][p][4 * n + z] = (float)(T)finish(v, P == 2 ? down.second : P == 3 ? kPartsDown : 1.f, bias[z]);
+                        if (P == 3 && kept && exists && oc + z < a.Co) acc[o][p][4 * n + z] = load1(mine + oc + z);
+                    }
+                }
+        }
+        const int n_cls = head_args()->n;
+        float* const sums = head_wl + n_cls * kChannels;
+        for (int c = 0; c < n_cls; ++c) {
+            const float* const w_c = head_wl + c * kChannels + oc0 + 4 * lg;
+            float sum[MP];
+#pragma unroll
+            for (int o = 0; o < MO; ++o) {
+                float quad[4][MP];
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const v4f wv = *reinterpret_cast<const v4f*>(w_c + 32 * o + 8 * n);
+#pragma unroll
+                    for (int p = 0; p < MP; ++p) {
+                        quad[n][p] = acc[o][p][4 * n] * wv[0];
+#pragma unroll
+                        for (int z = 1; z < 4; ++z) quad[n][p] = fmaf(acc[o][p][4 * n + z], wv[z], quad[n][p]);
+                    }
+                }
+                // both lane groups' quads of n (neighbours), then n = 0 + 1, 2 + 3, and these: a half of the wave adds one pair, the other the next
+                auto halves = [](float u, float v) {
+                    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, u), __builtin_bit_cast(unsigned, v), false, false);
+                    return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+                };
+#pragma unroll
+                for (int p = 0; p < MP; ++p) {
+                    const float pairs = halves(halves(quad[0][p], quad[1][p]), halves(quad[2][p], quad[3][p]));
+                    const float tile = halves(pairs, pairs);
+                    sum[p] = o ? sum[p] + tile : tile;
+                }
+            }
+            if (lg == 0)
+#pragma unroll
+                for (int p = 0; p < MP; ++p) sums[(wo * n_cls + c) * kPositions + 32 * (wp * MP + p) + lt] = sum[p];
+        }
+    };
+    // a thread's position: the waves' sums in pairs, fours and eights, softmax, loss
+    auto head_end = [&](const Tile& g) {
+        if (tid >= kPositions) return;
+        const int fh = g.ry < a.Ho ? (int)parts_div(a.Ho - g.ry + a.d - 1, a.mg_d, a.d) : 0;
+        const int fw = g.rx < a.Wo ? (int)parts_div(a.Wo - g.rx + a.d2 - 1, a.mg_d2, a.d2) : 0;
+        const int ty = (int)parts_div(tid, a.mg_tx, a.Tx), tx = tid - ty * a.Tx;
+        const int fy = g.ty0 + ty, fx = g.tx0 + tx;
+        if (ty >= a.Ty || fy >= fh || fx >= fw) return;
+        const int y = fy * a.d + g.ry, x = fx * a.d2 + g.rx;
+        constexpr int kMost = 4;                      // classes
+        float z[kMost], pr[kMost];
+        const HeadPtr h = head_args();
+        const int n = h->n;
+        const float* const sums = head_wl + n * kChannels;
+#pragma unroll
+        for (int c = 0; c < kMost; ++c) {
+            if (c >= n) break;
+            float s[WO];
+#pragma unroll
+            for (int i = 0; i < WO; ++i) s[i] = 32 * MO * i < a.Co ? sums[(i * n + c) * kPositions + tid] : 0.f;
+#pragma unroll
+            for (int w = 1; w < WO; w *= 2)
+#pragma unroll
+                for (int i = 0; i < WO; i += 2 * w) s[i] += s[i + w];
+            z[c] = s[0] + h->Wk[a.Co * n + c];
+        }
+        float zmax = z[0], sum = 0.f;
+#pragma unroll
+        for (int c = 1; c < kMost; ++c) if (c < n) zmax = fmaxf(zmax, z[c]);
+#pragma unroll
+        for (int c = 0; c < kMost; ++c) {
+            if (c >= n) break;
+            z[c] -= zmax;
+            pr[c] = __builtin_amdgcn_exp2f(1.4426950408889634f * z[c]);
+            sum += pr[c];
+        }
+        const float inv = h->mse ? 1.f : __builtin_amdgcn_rcpf(sum);
+#pragma unroll
+        for (int c = 0; c < kMost; ++c) {
+            if (c >= n) break;
+            pr[c] = (h->mse ? z[c] + zmax : pr[c]) * inv;
+            if (h->probs) h->probs[((long)(g.b * n + c) * h->probs_rows + y) * a.Wo + x] = pr[c];
+        }
+        if (!h->labels) return;
+        const long at = (long)(g.b * h->H + y + h->ctr) * h->W + x + h->ctr;
+        const int label = h->labels[at];
+        if (label < 0 || label >= n) return;
+        const float wt = h->pixw ? h->pixw[at] : 1.f;
+        float zt = 0.f, sq = 0.f;
+#pragma unroll
+        for (int c = 0; c < kMost; ++c) {
+            if (c >= n) break;
+            const float e = pr[c] - (c == label ? 1.f : 0.f);
+            if (c == label) zt = z[c];
+            sq += e * e;
+        }
+        head_loss[tid] += h->mse ? (double)wt * 0.5 * (double)sq : (double)wt * ((double)logf(sum) - (double)zt);
+    };
+
     // ---- walk the tiles
     int t = blockIdx.x;
     if (t >= a.tiles_total) return;                   // (uniform; the host launches no such workgroup)
@@ -846,7 +1001,9 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                             for (int r = 0; r < 16; ++r) z = fmaf(acc[o][p][r], 0.f, z);
                     odd = __any(z != z);
                 }
-                if constexpr (kF32) epilogue(cur, fh, fw);
+                if constexpr (HEAD) {
+                    if (P == 3 && odd) epilogue(cur, fh, fw);
+                } else if constexpr (kF32) epilogue(cur, fh, fw);
                 else epilogue_pieces(cur, fh, fw);
                 if constexpr (P == 3) {
                     if (odd) {
@@ -862,6 +1019,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                         repair(cur, fh, fw, bad);
                     }
                 }
+                if constexpr (HEAD) head_part(cur, fh, fw, odd);
             }
             if constexpr (P == 1) {
                 int stored = BACK && last && live && (a.Co & 7) == 0;
@@ -869,14 +1027,32 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 brought(cn, stored != 0);
             } else {
                 __syncthreads();                      // every wave has left this block's halo
+                if constexpr (HEAD)
+                    if (last) head_end(cur);
                 to_lds();
             }
             __syncthreads();
+            if constexpr (HEAD && P == 1)             // (the next tile's sums come behind a barrier of its own)
+                if (last) head_end(cur);
             cb = cn; row0 = rn;
         } while (!last);
         wq -= live ? wend : 0;                        // (the ring holds the first steps again)
         cur = nxt;
     }
+    if constexpr (HEAD)
+        if (head_args()->loss_partial) {              // (uniform; the threads' losses are behind the last barrier)
+            __syncthreads();
+            double sum = tid < kPositions ? head_loss[tid] : 0.0;
+            double* const each = reinterpret_cast<double*>(lds);
+#pragma unroll
+            for (int w = 1; w < 64; w *= 2) sum += __shfl_xor(sum, w, 64);
+            if (lane == 0) each[wave] = sum;
+            __syncthreads();
+            if (tid == 0) {
+                for (int i = 1; i < WO * WP; ++i) sum += each[i];
+                head_args()->loss_partial[blockIdx.x] = sum;
+            }
+        }
     if (kF32 && BACK && a.out_peak) {                 // (uniform)
         unsigned* const four = reinterpret_cast<unsigned*>(lds);   // (the last barrier above is behind every read of the LDS)
         unsigned most = wave_largest(bits_of(peak));
@@ -891,16 +1067,16 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
 }
 
 // fp32 storage: in two parts where everything is known to suit them
-template <typename T, bool BACK, int CB, int WO, int WP, int MO, int MP>
-__global__ __launch_bounds__(kPartsThreads, parts_wgs(sizeof(T) == 4 ? 3 : 1, MO * MP)) void conv_parts_kernel(ConvArgs a)
+template <typename T, bool BACK, int CB, int WO, int WP, int MO, int MP, bool HEAD = false>
+__global__ __launch_bounds__(64 * WO * WP, parts_wgs(sizeof(T) == 4 ? 3 : 1, MO * MP)) void conv_parts_kernel(ConvArgs a)
 {
     if constexpr (sizeof(T) == 4) {
         unsigned peak = kNoPeak;
         if (a.wpack2) peak = weights_wide(a) || (!BACK && weights_large(a)) ? kNoPeak : BACK ? peak_of(a.in_peak, a.in_words) : 0;
-        if (peak < kNoPeak) conv_parts_body<T, 2, BACK, CB, WO, WP, MO, MP>(a, peak);
-        else conv_parts_body<T, 3, BACK, CB, WO, WP, MO, MP>(a, peak);
+        if (peak < kNoPeak) conv_parts_body<T, 2, BACK, CB, WO, WP, MO, MP, HEAD>(a, peak);
+        else conv_parts_body<T, 3, BACK, CB, WO, WP, MO, MP, HEAD>(a, peak);
     } else
-        conv_parts_body<T, 1, BACK, CB, WO, WP, MO, MP>(a, 0);
+        conv_parts_body<T, 1, BACK, CB, WO, WP, MO, MP, HEAD>(a, 0);
 }
 
 }  // namespace mpcnn

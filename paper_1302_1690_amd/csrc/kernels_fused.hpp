@@ -456,7 +456,7 @@ struct ClassArgs {
 // 16 lanes share one position: lane j holds KV quads of channels, quad v = channels
 // 4Q(j + 16(v/Q)) + 4(v%Q) .. +3 - with Q = 1 every quad is a 128-bit access of its own (fp32), with
 // Q = 2 two neighbouring quads are one (8 bf16 values; K a multiple of 8); dot products meet
-// by xor-shuffles in a fixed order.  A workgroup walks 16 positions at a time.
+// by lane moves in a fixed order.  A workgroup walks 16 positions at a time.
 // Q quads as they come from memory (expanded to fp32 only when their turn comes)
 template <int Q, typename T> struct RawQuads { typedef v4f type; };
 template <> struct RawQuads<1, bf16> { typedef bf16x4 type; };
@@ -473,21 +473,19 @@ __device__ __forceinline__ void expand_quads(const typename RawQuads<Q, bf16>::t
         v[0] = __builtin_convertvector(r, v4f);
     }
 }
-// Sum over each aligned group of 16 lanes, left in all of them: four rotations inside the row of the
-// data-parallel-primitive modifier (no LDS round trip).  Every lane's additions pair the same partial
-// sums as a butterfly over lane ^ 8, 4, 2, 1 would, so all 16 results are the same bits.
+// Sums over aligned groups of lanes, left in all of them: moves inside a row of 16 lanes by the data-parallel-primitive modifier (no LDS round
+// trip).  Both lanes of a pair add the same two numbers, so all results are the same bits.
 template <int CTRL>
 __device__ __forceinline__ float row_rotated(float x)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float row16_sum(float x)
+// x and lane ^ STEP's, lanes below STEP (of 4: of every lane ^ 1, ^ 2 .. below it) having their sums already
+template <int STEP>
+__device__ __forceinline__ float row_pair_sum(float x)
 {
-    x += row_rotated<0x128>(x);   // row_ror:8
-    x += row_rotated<0x124>(x);   // row_ror:4
-    x += row_rotated<0x122>(x);   // row_ror:2
-    x += row_rotated<0x121>(x);   // row_ror:1
-    return x;
+    constexpr int kMove = STEP == 1 ? 0xb1 : STEP == 2 ? 0x4e : STEP == 4 ? 0x141 : 0x140;   // quad_perm 1 0 3 2, 2 3 0 1; row_half_mirror, row_mirror
+    return x + row_rotated<kMove>(x);
 }
 // positions fetched ahead per 16-lane group: the pass keeps only two waves per SIMD, and what bounds it
 // is the number of bytes those waves have in flight (about 40-50 KB per compute unit with these
@@ -499,6 +497,8 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
 {
     static_assert(KV % Q == 0, "whole accesses");
     static_assert(Q == 1 || sizeof(T) == 2, "pairs of quads: 2-byte storage only");
+    // Channel of quad v.  Sums are taken in the order of channels in pairs of pairs - a quad's four products, quads in twos, fours, eights (32
+    // channels, a tile of conv_parts_kernel's, which forms the class outputs itself where nothing is kept and adds in the same order), sixteens ..
     auto chan = [](int lane16, int v) { return 4 * Q * (lane16 + 16 * (v / Q)) + 4 * (v % Q); };
     const T* h_t = static_cast<const T*>(a.h);
     T* dh_t = static_cast<T*>(a.dH);
@@ -585,22 +585,28 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
         v4f hv[KV];
         float z[NCLS];
 #pragma unroll
-        for (int o = 0; o < NCLS; ++o) z[o] = 0.f;
-#pragma unroll
         for (int v = 0; v < KV / Q; ++v) expand_quads<Q>(ring[slot][v], *reinterpret_cast<v4f(*)[Q]>(&hv[v * Q]));
         int t = ring_t[slot];
         const float wt_in = ring_w[slot];
         fetch_h(m + AH * stride, ring[slot], ring_t[slot], ring_w[slot]);
 #pragma unroll
-        for (int v = 0; v < KV; ++v) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int o = 0; o < NCLS; ++o) z[o] = fmaf(hv[v][s], w[v][s][o], z[o]);
-        }
-#pragma unroll
         for (int o = 0; o < NCLS; ++o) {
-            z[o] = row16_sum(z[o]) + bias[o];
+            float quad[KV];
+#pragma unroll
+            for (int v = 0; v < KV; ++v) {
+                quad[v] = hv[v][0] * w[v][0][o];
+#pragma unroll
+                for (int s = 1; s < 4; ++s) quad[v] = fmaf(hv[v][s], w[v][s][o], quad[v]);
+            }
+            float part[KV / Q];                       // 64 channels each (Q = 2: 128)
+#pragma unroll
+            for (int i = 0; i < KV / Q; ++i)
+                part[i] = row_pair_sum<8>(row_pair_sum<4>(row_pair_sum<2>(row_pair_sum<1>(Q == 2 ? quad[Q * i] + quad[Q * i + Q - 1] : quad[i]))));
+#pragma unroll
+            for (int step = 1; step < KV / Q; step *= 2)
+#pragma unroll
+                for (int i = 0; i < KV / Q; i += 2 * step) part[i] += part[i + step];
+            z[o] = part[0] + bias[o];
         }
         float zmax = z[0];
 #pragma unroll

@@ -16,6 +16,15 @@ namespace mpcnn {
 
 enum ConvMode { kFwdTanh = 0, kFwdLinear = 1, kDgradTanh = 2, kDgradPlain = 3 };
 
+// What a class layer does with the outputs of the layer below it (conv_parts_kernel with HEAD; the fields as in ClassArgs)
+struct HeadArgs {
+    const float* Wk;     // [K][n] then bias [n]
+    float* probs;        // [B][n][probs_rows][Wo] or null
+    const int32_t* labels;
+    const float* pixw;
+    double* loss_partial;   // [workgroups], or null
+    int n, mse, H, W, ctr, probs_rows;
+};
 struct ConvArgs {
     // tensors are fp32 or bf16 (the kernel's template parameter T)
     const void* in;      // [B][Hi][Wi][Cr]   tensor the taps read (activations, or deltas for dgrad)
@@ -43,6 +52,7 @@ struct ConvArgs {
     const unsigned *w_peak, *in_peak;
     unsigned* out_peak;
     int in_words, in_margin, small_limit;
+    HeadArgs head;
     const float* wraw;   // [k*k2][layer input][layer output], the parameters as they are (conv_parts_kernel: sums that are not finite)
 };
 

@@ -171,6 +171,7 @@ struct Geom {
     // nets of few maps: the whole pass in one launch (small_net_kernel; what depends on a call's buffers is filled in then)
     bool small_net = false;
     mpcnn::SmallArgs small{};
+    bool head = false;        // forward only: the hidden layer below the class layer ends with it (conv_parts_kernel, HEAD)
     int small_wgs = 0;
     size_t small_lds = 0, small_partial_off = 0;
     size_t total = 0;
@@ -289,23 +290,25 @@ struct ProfScope {
 // products per step and tile - three parts' plans serve two parts as well -, es bytes per stored element).  Cost of the busiest compute
 // unit in cycles: its tiles' matrix instructions on its four SIMDs, a quarter of their staging and stores (most of it lies under the other
 // resident workgroup's instructions), and one tile's staging in full at the start.
+// `head` classes: with the class layer behind it, all channels in one workgroup.
 TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, int k, int k2, int cr, int rpad, int co,
-                         const ChanTiling& ct, int P, int mults, size_t es, bool back, int hint_pt, int hint_mp)
+                         const ChanTiling& ct, int P, int mults, size_t es, bool back, int hint_pt, int hint_mp, int head = 0)
 {
     TilePlan best;
     double best_cost = 0;
     const int fh = ceil_div(out_r, d), fw = ceil_div(out_c, d2);
     const int steps = k * k2 * rpad / 16;
-    const mpcnn::PartsInstance* const list = P == 3 ? mpcnn::kParts3 : mpcnn::kParts1;
-    const int n_list = P == 3 ? (int)(sizeof(mpcnn::kParts3) / sizeof(list[0])) : (int)(sizeof(mpcnn::kParts1) / sizeof(list[0]));
+    const mpcnn::PartsInstance* const list = head ? (P == 3 ? mpcnn::kHead3 : mpcnn::kHead1) : P == 3 ? mpcnn::kParts3 : mpcnn::kParts1;
+    const int n_list = (int)((head ? (P == 3 ? sizeof(mpcnn::kHead3) : sizeof(mpcnn::kHead1)) : P == 3 ? sizeof(mpcnn::kParts3) : sizeof(mpcnn::kParts1)) / sizeof(list[0]));
     for (int li = 0; li < n_list; ++li) {
         const mpcnn::PartsInstance& in = list[li];
-        const int CB = in.CB, RP = mpcnn::parts_round(CB), nblk = ceil_div(rpad, CB);
-        const int PT = in.WP * in.MP, per_wave = in.MO * in.MP, resident = mpcnn::parts_wgs(P, per_wave);
+        const int waves = in.WO * in.WP, OT = in.WO * in.MO, split = head ? 1 : ct.split;
+        const int CB = in.CB, RP = mpcnn::parts_round(CB, waves), nblk = ceil_div(rpad, CB);
+        const int PT = in.WP * in.MP, per_wave = in.MO * in.MP, resident = mpcnn::parts_wgs(P, per_wave) * 4 / waves;
         const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);   // (two parts take less)
-        if (in.WO * in.MO != ct.OT || (CB > 16 && rpad <= CB / 2)) continue;
+        if ((head ? 32 * OT < co || 16 * OT >= co || 32 * OT > ct.pad : OT != ct.OT) || (CB > 16 && rpad <= CB / 2)) continue;
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
-        if (in.MO == 2 && per_wave <= 4 && ceil_div(co, 32) % 2) continue;
+        if (!head && in.MO == 2 && per_wave <= 4 && ceil_div(co, 32) % 2) continue;
         if (per_wave > 4 && (hint_pt || hint_mp || !mpcnn::half_filter(k, k2))) continue;
         if ((hint_pt && PT != hint_pt) || (hint_mp && in.MP != hint_mp)) continue;
         // Time per matrix instruction against four tiles' per wave.  One part: 2 x 4 tiles take 0.86-0.88 of the time (2 x 2048 x 2048, us,
@@ -315,7 +318,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         // compute unit, its waits in the open, takes 1.4 times as long with one part.
         const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave > 4 ? 0.88 : per_wave == 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
         const double alone = P == 3 ? 1.15 : 1.4;
-        const double t_mul = (double)steps * mults * ct.OT * PT * 8.0 * eff;
+        const double t_mul = (double)steps * mults * OT * PT * 8.0 * eff * 4 / waves;
         // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640
         // positions (fp32) holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions,
         // forward / data gradient, microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32
@@ -324,8 +327,9 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128}) {
             if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
             const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
-            const size_t beside = (32 * ct.OT + mpcnn::parts_table(P, CB, rpad, kr * k2)) * sizeof(float);   // the bias, the steps' places
-            const size_t room_lds = (size_t)160 * 1024 / resident;
+            const size_t beside = (32 * OT + (head ? mpcnn::parts_head_at(P, CB, rpad, kr * k2) + mpcnn::parts_head(head, in.WO, in.MO, 32 * PT)
+                                                   : mpcnn::parts_table(P, CB, rpad, kr * k2))) * sizeof(float);   // the bias, the steps' places, the class layer's
+            const size_t room_lds = std::min((size_t)160 * 1024 / resident, (size_t)(head ? 64 : 160) * 1024);   // (more has to be asked for, some 10 us an instance)
             if (beside + RP * pitch > room_lds) continue;
             const int lds_pos = (int)((room_lds - beside) / (RP * pitch)) * RP;
             const int max_pos = std::min(lds_pos, mpcnn::parts_items(P, per_wave) * RP);   // positions of the halo
@@ -346,9 +350,9 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                 if (P == 1 && ((size_t)ty * d * out_c + (size_t)tx * d2) * co * es >= (1ull << 31)) continue;
                 const long tiles = (long)B * d * d2 * nty * ntx;
                 if (tiles * std::max(std::max(ntx, nty), std::max(d, d2)) >= (1ll << 31)) continue;
-                const long wgs = std::min<long>(tiles, std::max(1, resident * kNumCU / ct.split));
-                const double per_cu = std::ceil((double)tiles * ct.split / kNumCU);
-                const double t_rest = (double)nkr * npos * cr * es / 10 + 2500.0 * nblk * nkr + (double)ty * tx * ct.OT * 32 * es * (back ? 2 : 1) / 10 + 1500.0;
+                const long wgs = std::min<long>(tiles, std::max(1, resident * kNumCU / split));
+                const double per_cu = std::ceil((double)tiles * split / kNumCU);
+                const double t_rest = (double)nkr * npos * cr * es / 10 + 2500.0 * nblk * nkr + (head ? 0 : (double)ty * tx * OT * 32 * es * (back ? 2 : 1) / 10) + 1500.0;
                 // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
                 // only successive positions are sure to lie on different LDS banks)
                 const double cost = per_cu * ((per_cu < 2 ? alone : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
@@ -830,6 +834,14 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         }
     }
     if (r != H - net->patch + 1 || c != W - net->patch + 1) return false;
+    g->head = false;
+    if (!training && !g->small_net && L >= 2 && net->layers[L - 1].class_fused && g->fwd[L - 2].ok && !net->hint_pt && !net->hint_mp) {
+        // Nothing of the hidden layer is kept, so it need not pass through memory on its way to the classes.
+        const Layer& ly = net->layers[L - 2];
+        const TilePlan tp = plan_conv_parts(B, L > 2 ? g->cols[L - 3] : W, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct,
+                                            net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false, 0, 0, net->n_cls);
+        if (tp.ok) { g->fwd[L - 2] = tp; g->head = true; }
+    }
     if (g->small_net) {
         off = 0;                                      // (the image is read as it comes)
         for (size_t l = 0; training && l < L; ++l) {
@@ -1302,7 +1314,17 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                     a.wpack2 = (const v4f*)(net->d_packs + ly.fwd_half_off);
                 }
                 bool launched = false;
-                LAUNCH(kF32 ? "conv_fwd_parts" : "conv_fwd_bm", l, step, flops, bytes, launched = launch_conv<T>(a, tp, grid, st));
+                if (g.head && l == L - 2) {
+                    const Layer& last = net->layers[L - 1];
+                    grid.y = 1;
+                    a.head = {net->d_wread + last.p_off, probs, labels, pixw, want_loss ? lp : nullptr, net->n_cls, net->loss_kind == MPCNN_LOSS_MSE,
+                              g.label_h, g.W, (net->patch - 1) / 2, g.probs_rows};
+                    const double n_probs = (double)B * Ho * Wo * last.cout;
+                    LAUNCH(kF32 ? "conv_class_parts" : "conv_class_bm", l, step, flops + 2.0 * n_probs * ly.cout, es * n_in + 4.0 * (ly.p_len + n_probs),
+                           launched = (kF32 ? mpcnn::launch_conv_head_f32 : mpcnn::launch_conv_head_b16)(a, tp.in, grid, tp.lds, st));
+                    if (want_loss) net->loss_shares = tp.wgs;
+                } else
+                    LAUNCH(kF32 ? "conv_fwd_parts" : "conv_fwd_bm", l, step, flops, bytes, launched = launch_conv<T>(a, tp, grid, st));
                 if (!launched)   // a plan without a kernel instance: a planner bug, never a silent skip
                     return fail(MPCNN_EUNSUPPORTED, "layer %zu: no convolution kernel instance for its forward plan", l);
             } else if (!kF32 && l == 0 && ly.dil == 1 && Ci <= 4 && ly.cout <= 64 && (ly.k == 3 || ly.k == 5 || ly.k == 7)) {
@@ -1336,6 +1358,7 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                            w_in_lds));
             }
         }
+        if (g.head && l == L - 2) break;              // (the class layer's work is done)
         in = out; Hi = Ho; Wi = Wo; Ci = ly.cout;
     }
     if (!net->layers[L - 1].class_fused) {
@@ -1920,7 +1943,7 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         if (!tp.ok) { put("  %s: plain kernel\n", what); return; }
         put("  %s: bf16 MFMA, %s, %d channel tiles x %d groups, %d position tiles, waves %d x %d of %d x %d tiles, "
             "%d channels and %d filter rows per block, tile %d x %d of a residue class, %d x %d tiles, %d workgroups, %zu B LDS\n", what,
-            parts(half), ct.OT, ct.split, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
+            parts(half), tp.in.WO * tp.in.MO, tp.in.WO * tp.in.MO == ct.OT ? ct.split : 1, tp.PT, tp.in.WO, tp.in.WP, tp.in.MO, tp.in.MP,
             tp.in.CB, tp.kr, tp.Ty, tp.Tx, tp.nty, tp.ntx, tp.wgs, tp.lds);
     };
     put("workspace %zu bytes\n", g.total);
@@ -1932,6 +1955,7 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
             ly.kind == MPCNN_MP ? "MP" : (ly.kind == MPCNN_C ? "C" : "FC"), ly.cin, ly.cout, ly.k, ly.k2, ly.dil, ly.dil2,
             g.rows[l], g.cols[l]);
         if (ly.kind == MPCNN_MP || g.small_net) continue;
+        if (ly.class_fused && g.head) { put("  class layer: at the end of the layer below\n"); continue; }
         if (ly.class_fused) { put("  fused class layer, %d workgroups\n", g.partial_n[l]); continue; }
         const bool img_sides = ly.dil == 1 && !ly.rect && (ly.k == 3 || ly.k == 5 || ly.k == 7);
         if (!g.fwd[l].ok && l == 0 && net->bf16 && img_sides && ly.cin <= 4 && ly.cout <= 64)
