@@ -241,6 +241,11 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     // beside the accumulators: there are none left)
     auto fresh = [](int v) { asm volatile("" : "+v"(v)); return v; };
     auto aim = [&](const Tile& g, bool any, int row0) {   // this thread's items of tile g, filter rows row0 ..
+        if (!any) {                                   // (uniform)
+#pragma unroll
+            for (int u = 0; u < SI; ++u) voff[u] = kNone;
+            return;
+        }
         const int first = fresh(pos0);
         const unsigned row_b = (unsigned)(a.d * a.Wi * a.Cr) * (unsigned)sizeof(T), col_b = (unsigned)(a.d2 * a.Cr) * (unsigned)sizeof(T);
         const int iy0 = (g.ty0 + a.origin + row0) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
@@ -250,7 +255,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             const unsigned pos = first + RP * u;
             const unsigned ha = parts_div(pos, a.mg_hw, hw), hb = pos - ha * hw;
             const int iy = iy0 + (int)ha * a.d, ix = ix0 + (int)hb * a.d2;
-            const bool ok = any && pos < (unsigned)npos && (unsigned)iy < (unsigned)a.Hi && (unsigned)ix < (unsigned)a.Wi;
+            const bool ok = pos < (unsigned)npos && (unsigned)iy < (unsigned)a.Hi && (unsigned)ix < (unsigned)a.Wi;
             voff[u] = ok ? ha * row_b + hb * col_b + 8u * q * (unsigned)sizeof(T) : kNone;
         }
     };
@@ -473,12 +478,21 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 product(s, 0, 2, 0); fetch_w(s, 2);
                 product(s, 0, 1, 0); fetch_w(s, 1);
                 product(s, 0, 0, 0); fetch_x(0, 0, soff); fetch_w(s, 0);
-            } else if constexpr (P == 2) {            // activations a whole step ahead
-                next_x();
-                fetch_x((s + 1) % XS, 1, soff); fetch_x((s + 1) % XS, 0, soff);
-                __builtin_amdgcn_sched_barrier(0);    // (else the reads sink to where they are used, and every step waits for them)
-                product(s, s % XS, 0, 1); product(s, s % XS, 1, 0); fetch_w(s, 1);
-                product(s, s % XS, 0, 0); fetch_w(s, 0);
+            } else if constexpr (P == 2) {
+                // Activations a step ahead.  What is no matrix instruction stands between pairs of those, which cover it: in one place, before the
+                // first, it left the matrix pipe empty for as long (64 -> 100, 3 x 3, a wave alone on its SIMD 400 cycles per step, of which 192 are
+                // products, now 340; two waves 425, now 385).  The barriers keep it there: reads sink to where they are used, and are waited for.
+                product(s, s % XS, 0, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                next_x(); fetch_x((s + 1) % XS, 1, soff);
+                __builtin_amdgcn_sched_barrier(0);
+                product(s, s % XS, 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_x((s + 1) % XS, 0, soff); fetch_w(s, 1);
+                __builtin_amdgcn_sched_barrier(0);
+                product(s, s % XS, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_w(s, 0);
                 if (--run_left == 0) add_run();
             } else {                                  // activations XS - 1 steps ahead, their places TS more
                 fetch_x((s + XS - 1) % XS, 0, at[s % TS]);
@@ -1029,7 +1043,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 __syncthreads();                      // every wave has left this block's halo
                 if constexpr (HEAD)
                     if (last) head_end(cur);
-                to_lds();
+                if (!last || t + (int)gridDim.x < a.tiles_total) to_lds();
             }
             __syncthreads();
             if constexpr (HEAD && P == 1)             // (the next tile's sums come behind a barrier of its own)
