@@ -297,6 +297,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     constexpr int LP = 64 / GO;                       // positions of an instruction
     auto swapped = [](int at) { return at ^ (at >> 4 & 16 * (GO - 1)); };   // place of an octet, from position * POSB + 16 * octet
     auto bring = [&](const Tile& g, bool any, int row0, int cb) {
+        if (!any) return;                             // (uniform; no such tile)
         typedef __attribute__((address_space(3))) void* lds_ptr;
         const unsigned row_b = (unsigned)(a.d * a.Wi * a.Cr) * (unsigned)sizeof(T), col_b = (unsigned)(a.d2 * a.Cr) * (unsigned)sizeof(T);
         const int iy0 = (g.ty0 + a.origin + row0) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
@@ -308,7 +309,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             const unsigned pos = at + mine;
             const unsigned ha = parts_div(pos, a.mg_hw, hw), hb = pos - ha * hw;
             const int iy = iy0 + (int)ha * a.d, ix = ix0 + (int)hb * a.d2;
-            const bool ok = any && pos < (unsigned)npos && (unsigned)iy < (unsigned)a.Hi && (unsigned)ix < (unsigned)a.Wi;
+            const bool ok = pos < (unsigned)npos && (unsigned)iy < (unsigned)a.Hi && (unsigned)ix < (unsigned)a.Wi;
             const unsigned off = ha * row_b + hb * col_b + 16 * oct;
 #pragma unroll
             for (int j = 0; j < QN / GO; ++j) {

@@ -13,6 +13,7 @@ bool launch_conv_parts_b16_fwd(const ConvArgs& a, const PartsInstance& in, dim3 
     }
     MPCNN_PARTS1(CASE)
     MPCNN_PARTS1_WIDE(CASE)
+    MPCNN_PARTS1_ALL(CASE)
 #undef CASE
     return false;
 }
@@ -26,6 +27,7 @@ hipError_t conv_parts_attrs_b16_fwd()
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     MPCNN_PARTS1(ATTR)
     MPCNN_PARTS1_WIDE(ATTR)
+    MPCNN_PARTS1_ALL(ATTR)
 #undef ATTR
     return e;
 }

@@ -298,15 +298,21 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
     double best_cost = 0;
     const int fh = ceil_div(out_r, d), fw = ceil_div(out_c, d2);
     const int steps = k * k2 * rpad / 16;
-    const mpcnn::PartsInstance* const list = head ? (P == 3 ? mpcnn::kHead3 : mpcnn::kHead1) : P == 3 ? mpcnn::kParts3 : mpcnn::kParts1;
-    const int n_list = (int)((head ? (P == 3 ? sizeof(mpcnn::kHead3) : sizeof(mpcnn::kHead1)) : P == 3 ? sizeof(mpcnn::kParts3) : sizeof(mpcnn::kParts1)) / sizeof(list[0]));
+    const mpcnn::PartsInstance* list = mpcnn::kParts1;
+    size_t list_bytes = sizeof(mpcnn::kParts1);
+#define LIST(name) { list = mpcnn::name; list_bytes = sizeof(mpcnn::name); }
+    if (head && P == 3) LIST(kHead3) else if (head) LIST(kHead1) else if (P == 3) LIST(kParts3) else if (!back) LIST(kParts1Fwd)
+#undef LIST
+    const int n_list = (int)(list_bytes / sizeof(list[0]));
     for (int li = 0; li < n_list; ++li) {
         const mpcnn::PartsInstance& in = list[li];
-        const int waves = in.WO * in.WP, OT = in.WO * in.MO, split = head ? 1 : ct.split;
+        const int waves = in.WO * in.WP, OT = in.WO * in.MO;
+        const bool all = !head && OT == 8;            // (one group where the list's others need two)
+        const int split = head || all ? 1 : ct.split;
         const int CB = in.CB, RP = mpcnn::parts_round(CB, waves), nblk = ceil_div(rpad, CB);
         const int PT = in.WP * in.MP, per_wave = in.MO * in.MP, resident = mpcnn::parts_wgs(P, per_wave) * 4 / waves;
         const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);   // (two parts take less)
-        if ((head ? 32 * OT < co || 16 * OT >= co || 32 * OT > ct.pad : OT != ct.OT) || (CB > 16 && rpad <= CB / 2)) continue;
+        if ((head ? 32 * OT < co || 16 * OT >= co || 32 * OT > ct.pad : all ? ct.OT * ct.split != 8 : OT != ct.OT) || (CB > 16 && rpad <= CB / 2)) continue;
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
         if (!head && in.MO == 2 && per_wave <= 4 && ceil_div(co, 32) % 2) continue;
         if (per_wave > 4 && (hint_pt || hint_mp || !mpcnn::half_filter(k, k2))) continue;
@@ -1307,7 +1313,7 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.k = ly.k; a.d = ly.dil; a.origin = 0; a.k2 = ly.k2; a.d2 = ly.dil2; a.origin2 = 0;
                 a.Ty = tp.Ty; a.Tx = tp.Tx; a.nty = tp.nty; a.ntx = tp.ntx;
                 a.mode = ly.tanh_out ? kFwdTanh : kFwdLinear; a.logistic = net->logistic;
-                dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)ly.fwd_ct.split);
+                dim3 grid((unsigned)(B * ly.dil * ly.dil2 * tp.nty * tp.ntx), (unsigned)(tp.in.WO * tp.in.MO == ly.fwd_ct.OT ? ly.fwd_ct.split : 1));
                 parts_grid(&a, &grid, tp); a.wraw = Wk;
                 if (two_part_forward(net, g, l)) {
                     weights_of(&a, net, l);
@@ -1316,7 +1322,6 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 bool launched = false;
                 if (g.head && l == L - 2) {
                     const Layer& last = net->layers[L - 1];
-                    grid.y = 1;
                     a.head = {net->d_wread + last.p_off, probs, labels, pixw, want_loss ? lp : nullptr, net->n_cls, net->loss_kind == MPCNN_LOSS_MSE,
                               g.label_h, g.W, (net->patch - 1) / 2, g.probs_rows};
                     const double n_probs = (double)B * Ho * Wo * last.cout;

@@ -90,3 +90,29 @@ def test_sums_that_are_not_finite(hidden):
     assert np.isfinite(want).all()
     params[3] = np.nan
     check(layers, patch, 1, H, W, "f32", "mcce", "tanh", params=params)
+
+
+@pytest.mark.parametrize("below,k,hidden,size", [(64, 2, 200, 300), (128, 2, 200, 310), (100, 3, 132, 300), (128, 2, 256, 400)])
+def test_all_channels_in_one_workgroup(below, k, hidden, size):
+    """bf16 storage, training: 129 .. 256 channels in one group of workgroups against two groups of four tiles (by a tiling hint), bit for bit."""
+    layers = ((C, 8, 3), (MP, 0, 2), (C, below, 3), (FC, hidden, 0), (FC, 3, 0))
+    patch = 2 * (k + 2) + 2
+    H, W = patch + size, patch + size + 13
+    rng = np.random.default_rng(below + hidden)
+    n = [8 * 9 + 8, below * 8 * 9 + below, hidden * below * k * k + hidden, 3 * hidden + 3]
+    params = np.concatenate([rng.uniform(-1, 1, m) * s for m, s in zip(n, (0.5, 0.2, 0.08, 0.2))]).astype(np.float32)
+    image = torch.from_numpy(rng.uniform(0, 1, (1, 1, H, W)).astype(np.float32)).cuda()
+    labels = torch.from_numpy(rng.integers(0, 3, (1, H, W)).astype(np.int32)).cuda()
+    out = []
+    for hint in ((0, 0), (4, 4)):
+        net = mpcnn.Net(layers, 1, patch, mpcnn.BF16)
+        net.set_conv_tiling(*hint)
+        line = [l for l in net.plan_describe(1, H, W, True).splitlines() if "forward:" in l][-1]
+        assert ("8 channel tiles x 1 groups" in line) == (hint == (0, 0)), line
+        net.set_params(params)
+        probs = torch.empty((1, 3, H - patch + 1, W - patch + 1), device="cuda")
+        net.seg_backward(image, labels, probs=probs)
+        out.append((probs.cpu().numpy(), net.get_grads()))
+        net.close()
+    assert np.isfinite(out[0][1]).all() and np.any(out[0][1])
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
