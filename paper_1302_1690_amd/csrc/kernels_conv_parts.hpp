@@ -41,8 +41,9 @@
 // lanes (16 bytes of 64 positions: the last layer's forward 3338 instead of 3040 us), which leaves registers for three workgroups of four
 // tiles per wave, or two of eight. Weights run through a ring of parts_ring steps that never drains: the pack is in step order - chunks of
 // 16 channels, the taps of each, whatever CB is - and its first steps follow its last once more, so that no fetch looks at the end; behind
-// a tile's last step the pointer goes back to its first. One part: the LDS offsets of a block's steps come from a table in LDS, as counting
-// taps took more scalar instructions than a step has issue slots for. The bias waits in LDS (its loads queued behind the halo's: bf16
+// a tile's last step the pointer goes back to its first. One and two parts: the LDS offsets of a block's steps come from a table in LDS, as counting
+// taps took more scalar instructions than a step has issue slots for (two parts, 128 -> 200, 2 x 2, 1024 x 1024: 1007 -> 940 us).  Places of a halo's items
+// are worked out again only where a tile or the one before it reaches past the tensor. The bias waits in LDS (its loads queued behind the halo's: bf16
 // forward 8.8 -> 7.9 ms).
 //
 // MEASURED, deep net (32 -> 64 k5, 64 -> 64 k5, 64 -> 128 k3, 128 -> 200 k2), microseconds:
@@ -102,12 +103,13 @@ __host__ __device__ constexpr int parts_ring(int parts, int tiles) { return part
 // at 2^-133, fp32's at 2^-149.
 constexpr float kPartsUp = 0x1p16f, kPartsDown = 0x1p-32f;
 
-// One part: LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
+// One and two parts: LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
 __host__ __device__ constexpr int parts_sets(int parts, int tiles) { return parts == 3 ? 1 : parts == 2 || tiles > 2 ? 2 : 4; }   // activations in registers
 constexpr int kPartsTabAhead = 2;
 __host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps)
 {
-    return parts != 1 ? 0 : taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
+    (void)parts;                                      // (three parts' plans serve two as well)
+    return taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
 }
 // With the class layer, behind the table, in floats: the threads' losses (fp64), its weights, one class after the other, the waves' sums of a tile
 __host__ __device__ inline int parts_head_at(int parts, int CB, int rpad, int taps) { return (parts_table(parts, CB, rpad, taps) + 3) / 4 * 4; }
@@ -240,16 +242,21 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     // (an empty asm keeps what depends on the lane alone from being computed once for all tiles and held in registers
     // beside the accumulators: there are none left)
     auto fresh = [](int v) { asm volatile("" : "+v"(v)); return v; };
+    bool inner = false;                               // `voff` is that of a halo inside the tensor, the same for all of them
     auto aim = [&](const Tile& g, bool any, int row0) {   // this thread's items of tile g, filter rows row0 ..
         if (!any) {                                   // (uniform)
 #pragma unroll
             for (int u = 0; u < SI; ++u) voff[u] = kNone;
+            inner = false;
             return;
         }
-        const int first = fresh(pos0);
         const unsigned row_b = (unsigned)(a.d * a.Wi * a.Cr) * (unsigned)sizeof(T), col_b = (unsigned)(a.d2 * a.Cr) * (unsigned)sizeof(T);
         const int iy0 = (g.ty0 + a.origin + row0) * a.d + g.ry, ix0 = (g.tx0 + a.origin2) * a.d2 + g.rx;
         st_base = in_t + (((long)g.b * a.Hi + iy0) * a.Wi + ix0) * a.Cr;
+        const bool was = inner;
+        inner = iy0 >= 0 && ix0 >= 0 && iy0 + (hh - 1) * a.d < a.Hi && ix0 + (hw - 1) * a.d2 < a.Wi;   // (uniform)
+        if (was && inner) return;
+        const int first = fresh(pos0);
 #pragma unroll
         for (int u = 0; u < SI; ++u) {
             const unsigned pos = first + RP * u;
@@ -340,13 +347,15 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             bias_l[tid] = c < a.Co ? a.bias[c] : 0.f;
         }
 
-    // ---- one part: the LDS offsets of a block's steps, behind the bias
+    // ---- one and two parts: the LDS offsets of a block's steps, behind the bias
     int* const table = reinterpret_cast<int*>(bias_l + 32 * WO * MO);
-    if constexpr (P == 1) {
+    if constexpr (P != 3) {
         const int taps = a.kr * a.k2, all = taps * ((CB < a.CrPad ? CB : a.CrPad) / 16);
+        const float per_tap = __builtin_amdgcn_rcpf((float)taps), per_row = __builtin_amdgcn_rcpf((float)a.k2);
         for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kThreads) {
-            const int sub = i / taps, r = i - sub * taps, ta = r / a.k2, tb = r - ta * a.k2;
-            table[i] = i < all ? (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16 : 0;
+            // (quotients of numbers below 2^20, half a step from the next whole one: exact)
+            const int sub = (int)(((float)i + 0.5f) * per_tap), r = i - sub * taps, ta = (int)(((float)r + 0.5f) * per_row), tb = r - ta * a.k2;
+            table[i] = i >= all ? 0 : P == 2 ? (ta * hw + tb) * PITCH + sub * (P * 32) : (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16;
         }
     }
 
@@ -485,11 +494,12 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 // products, now 340; two waves 425, now 385).  The barriers keep it there: reads sink to where they are used, and are waited for.
                 product(s, s % XS, 0, 1);
                 __builtin_amdgcn_sched_barrier(0);
-                next_x(); fetch_x((s + 1) % XS, 1, soff);
+                const int off = at[s % TS];
+                fetch_x((s + 1) % XS, 1, off); at[s % TS] = tv[s + XS - 1 + TS];
                 __builtin_amdgcn_sched_barrier(0);
                 product(s, s % XS, 1, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                fetch_x((s + 1) % XS, 0, soff); fetch_w(s, 1);
+                fetch_x((s + 1) % XS, 0, off); fetch_w(s, 1);
                 __builtin_amdgcn_sched_barrier(0);
                 product(s, s % XS, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
@@ -508,7 +518,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             for (int t = 0; t < XS; ++t)
                 if (phase % XS == t) {
                     static_assert(XS == 2 && TS == 2, "the other set, the other place");
-                    if constexpr (P == 2) { fetch_x(t, 1, 0); fetch_x(t, 0, 0); }
+                    if constexpr (P == 2) { at[t] = tv[1]; at[t ^ 1] = tv[2]; fetch_x(t, 1, 0); fetch_x(t, 0, 0); }
                     else { fetch_x(t, 0, head[0]); at[t] = head[1]; at[t ^ 1] = head[2]; }
                 }
             tv -= phase;
