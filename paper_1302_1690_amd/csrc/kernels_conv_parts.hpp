@@ -41,7 +41,7 @@
 // lanes (16 bytes of 64 positions: the last layer's forward 3338 instead of 3040 us), which leaves registers for three workgroups of four
 // tiles per wave, or two of eight. Weights run through a ring of parts_ring steps that never drains: the pack is in step order - chunks of
 // 16 channels, the taps of each, whatever CB is - and its first steps follow its last once more, so that no fetch looks at the end; behind
-// a tile's last step the pointer goes back to its first. One and two parts: the LDS offsets of a block's steps come from a table in LDS, as counting
+// a tile's last step the pointer goes back to its first. The LDS offsets of a block's steps come from a table in LDS, as counting
 // taps took more scalar instructions than a step has issue slots for (two parts, 128 -> 200, 2 x 2, 1024 x 1024: 1007 -> 940 us).  Places of a halo's items
 // are worked out again only where a tile or the one before it reaches past the tensor. The bias waits in LDS (its loads queued behind the halo's: bf16
 // forward 8.8 -> 7.9 ms).
@@ -103,12 +103,12 @@ __host__ __device__ constexpr int parts_ring(int parts, int tiles) { return part
 // at 2^-133, fp32's at 2^-149.
 constexpr float kPartsUp = 0x1p16f, kPartsDown = 0x1p-32f;
 
-// One and two parts: LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
+// LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
 __host__ __device__ constexpr int parts_sets(int parts, int tiles) { return parts == 3 ? 1 : parts == 2 || tiles > 2 ? 2 : 4; }   // activations in registers
 constexpr int kPartsTabAhead = 2;
 __host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps)
 {
-    (void)parts;                                      // (three parts' plans serve two as well)
+    (void)parts;
     return taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
 }
 // With the class layer, behind the table, in floats: the threads' losses (fp64), its weights, one class after the other, the waves' sums of a tile
@@ -347,15 +347,15 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             bias_l[tid] = c < a.Co ? a.bias[c] : 0.f;
         }
 
-    // ---- one and two parts: the LDS offsets of a block's steps, behind the bias
+    // ---- the LDS offsets of a block's steps, behind the bias
     int* const table = reinterpret_cast<int*>(bias_l + 32 * WO * MO);
-    if constexpr (P != 3) {
+    {
         const int taps = a.kr * a.k2, all = taps * ((CB < a.CrPad ? CB : a.CrPad) / 16);
         const float per_tap = __builtin_amdgcn_rcpf((float)taps), per_row = __builtin_amdgcn_rcpf((float)a.k2);
         for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kThreads) {
             // (quotients of numbers below 2^20, half a step from the next whole one: exact)
             const int sub = (int)(((float)i + 0.5f) * per_tap), r = i - sub * taps, ta = (int)(((float)r + 0.5f) * per_row), tb = r - ta * a.k2;
-            table[i] = i >= all ? 0 : P == 2 ? (ta * hw + tb) * PITCH + sub * (P * 32) : (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16;
+            table[i] = i >= all ? 0 : P != 1 ? (ta * hw + tb) * PITCH + sub * (P * 32) : (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16;
         }
     }
 
@@ -448,19 +448,8 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                 if constexpr (P == 1) x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + swapped(lbase[p] + off));
                 else x[s][i][p] = *reinterpret_cast<const v4f*>(ldsb + lbase[p] + off + 32 * i);
         };
-        // two and three parts: the next step's place, counted (past the last one: the first one's, read for nothing)
-        int left = n, ta = 0, tb = 0, soff = 0;
-        const int rowskip = (hw - a.k2) * PITCH, subskip = P * 32 - (rows * hw) * PITCH;
-        auto next_x = [&]() {
-            soff += PITCH;
-            if (++tb == a.k2) {
-                tb = 0; soff += rowskip;
-                if (++ta == rows) { ta = 0; soff += subskip; }
-            }
-            if (--left <= 0) soff = 0;
-        };
-        // one part: from the table.  A step is two or four instructions of 32 cycles, and a wave alone on its SIMD issues something every four to
-        // five cycles: counting cost 21 scalar instructions per step, twice what the matrix pipe leaves time for.
+        // The steps' places, from the table.  A step is two to twelve instructions of 32 cycles, and a wave alone on its SIMD issues something every four
+        // to five cycles: counting cost some 20 scalar instructions per step, with few tiles more than the matrix pipe leaves time for.
         const int* tv = table;
         int at[TS];
         auto product = [&](int s, int t, int i, int j) {   // weight part i, activation part j
@@ -479,15 +468,16 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
         };
         auto step = [&](int s) {
             if constexpr (P == 3) {
-                next_x();
+                const int off = at[0];
+                at[0] = tv[s + 2];
                 // A step's operands are fetched for the next one as soon as they are free: the activations' third part
                 // behind the first product, its second behind the third, its first behind the last (three products
                 // before it is needed).
-                product(s, 0, 0, 2); fetch_x(0, 2, soff);
-                product(s, 0, 1, 1); product(s, 0, 0, 1); fetch_x(0, 1, soff);
+                product(s, 0, 0, 2); fetch_x(0, 2, off);
+                product(s, 0, 1, 1); product(s, 0, 0, 1); fetch_x(0, 1, off);
                 product(s, 0, 2, 0); fetch_w(s, 2);
                 product(s, 0, 1, 0); fetch_w(s, 1);
-                product(s, 0, 0, 0); fetch_x(0, 0, soff); fetch_w(s, 0);
+                product(s, 0, 0, 0); fetch_x(0, 0, off); fetch_w(s, 0);
             } else if constexpr (P == 2) {
                 // Activations a step ahead.  What is no matrix instruction stands between pairs of those, which cover it: in one place, before the
                 // first, it left the matrix pipe empty for as long (64 -> 100, 3 x 3, a wave alone on its SIMD 400 cycles per step, of which 192 are
@@ -550,6 +540,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
             return;
         }
         if constexpr (P == 3) {
+            at[0] = tv[1];
 #pragma unroll
             for (int i = P - 1; i >= 0; --i) fetch_x(0, i, 0);
         } else if constexpr (P == 1) {
