@@ -2312,9 +2312,7 @@ mpcnn_status mpcnn_armijo_step(mpcnn_net* net, const float* image_dev, const int
     if (!net->d_scalar) HIP_TRY(hipMalloc((void**)&net->d_scalar, 8 * sizeof(double)));
     HIP_TRY(hipMemcpyAsync(net->d_params0, net->d_params, sizeof(float) * n, hipMemcpyDeviceToDevice, st));
     mpcnn::sqnorm_kernel<<<1, 1024, 0, st>>>(net->d_grads, n, net->d_scalar);
-    double gg = 0.0;
-    HIP_TRY(hipMemcpyAsync(&gg, net->d_scalar, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    double both[2];           // |g|^2, and the loss of a trial: read back together, so that the host waits once per trial
     float alpha = alpha0;
     double f = f0;
     int trial = 0;
@@ -2326,9 +2324,10 @@ mpcnn_status mpcnn_armijo_step(mpcnn_net* net, const float* image_dev, const int
         net->packs_stale = true; net->wread_stale = true;
         rc = loss_only(net, g, image_dev, labels_dev, pixw_dev, net->d_scalar + 1, (char*)ws_dev, st);
         if (rc != MPCNN_OK) break;
-        HIP_TRY(hipMemcpyAsync(&f, net->d_scalar + 1, sizeof(double), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(both, net->d_scalar, sizeof both, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        if (f <= f0 - (double)c * (double)alpha * (double)grad_scale * gg) { ok = true; break; }
+        f = both[1];
+        if (f <= f0 - (double)c * (double)alpha * (double)grad_scale * both[0]) { ok = true; break; }
         alpha *= beta;
     }
     if (!ok) {   // also after an error: the parameters the call started from
