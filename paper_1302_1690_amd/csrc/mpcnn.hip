@@ -1053,20 +1053,36 @@ void launch_first_bm(const mpcnn::FirstBmArgs& a, unsigned wgs, hipStream_t st)
 #undef CASE
 }
 // fp32 storage, the image layer on the fp32 matrix instruction: instance by filter side, channels and rows per wave
-bool launch_first_mfma(const mpcnn::FirstMfmaArgs& a0, int k, int ci, int B, hipStream_t st)
+bool launch_first_mfma(const mpcnn::FirstMfmaArgs& a0, int k, int ci, int B, bool pool, hipStream_t st)
 {
     mpcnn::FirstMfmaArgs a = a0;
-    const int ct = ceil_div(a.Co, 32);
+    const int ct = ceil_div(a.Co, 32), rows = pool ? a.Hp : a.Ho, cols = pool ? a.Wp : a.Wo, less = pool ? 1 : 0;
     int mp = 4;   // rows per wave: as many as still give every compute unit two workgroups
-    while (mp > 1 && (long)B * ceil_div(a.Ho, 4 * mp) * ceil_div(a.Wo, 32) * ct < 2L * kNumCU) mp >>= 1;
-    a.nty = ceil_div(a.Ho, 4 * mp); a.ntx = ceil_div(a.Wo, 32);
+    while (mp > 1 && (long)B * ceil_div(rows, 4 * mp - less) * ceil_div(cols, 32 - less) * ct < 2L * kNumCU) mp >>= 1;
+    a.nty = ceil_div(rows, 4 * mp - less); a.ntx = ceil_div(cols, 32 - less);
     const dim3 grid((unsigned)(B * a.nty * a.ntx), (unsigned)ct);
-#define CASE(kk, cc, mm) if (k == kk && ci == cc && mp == mm) { mpcnn::first_layer_mfma_kernel<kk, cc, mm><<<grid, 256, 0, st>>>(a); return true; }
+#define CASE(kk, cc, mm)                                                                              \
+    if (k == kk && ci == cc && mp == mm) {                                                            \
+        if (pool) mpcnn::first_layer_mfma_kernel<kk, cc, mm, true><<<grid, 256, 0, st>>>(a);          \
+        else mpcnn::first_layer_mfma_kernel<kk, cc, mm><<<grid, 256, 0, st>>>(a);                     \
+        return true;                                                                                  \
+    }
 #define CASES(kk, cc) CASE(kk, cc, 1) CASE(kk, cc, 2) CASE(kk, cc, 4)
     CASES(3, 1) CASES(5, 1) CASES(7, 1) CASES(3, 3) CASES(5, 3) CASES(7, 3)
 #undef CASES
 #undef CASE
     return false;
+}
+// The image layer's kernel with fp32 storage (else the plain one), and whether the pool behind it comes with it: nothing kept, 2 x 2
+bool first_on_mfma(const mpcnn_net* net, const Geom& g)
+{
+    const Layer& ly = net->layers[0];
+    return !net->bf16 && ly.kind != MPCNN_MP && !ly.class_fused && !g.fwd[0].ok && !ly.rect && ly.dil == 1 && (ly.cin == 1 || ly.cin == 3) &&
+           (ly.k == 3 || ly.k == 5 || ly.k == 7) && (long)g.B * g.rows[0] * g.cols[0] < (1l << 31) / 32;
+}
+bool first_with_pool(const mpcnn_net* net, const Geom& g)
+{
+    return !g.training && net->layers.size() > 1 && first_on_mfma(net, g) && net->layers[1].kind == MPCNN_MP && !net->layers[1].rect && net->layers[1].k == 2;
 }
 template <typename T>
 bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipStream_t st)
@@ -1236,7 +1252,9 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
     T* dZ = static_cast<T*>(dZ_);
     const T* in = nullptr;
     int Hi = g.H, Wi = g.W, Ci = net->in_ch;
-    if (g.staged) {
+    const bool pooled_first = kF32 && first_with_pool(net, g);
+    if (pooled_first) in = reinterpret_cast<const T*>(image);
+    else if (g.staged) {
         T* staged = (T*)(ws + g.staged_off);
         long total = (long)B * Ci * Hi * Wi;
         LAUNCH("stage_input", -1, 0, 0, (4.0 + es) * total,
@@ -1341,16 +1359,26 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.nty = ceil_div(Ho, kFirstBmTy); a.ntx = ceil_div(Wo, kFirstBmTx);
                 const unsigned wgs = (unsigned)std::min<long>((long)B * a.nty * a.ntx, 4L * kNumCU);
                 LAUNCH("first_layer_bm", l, step, flops, bytes, launch_first_bm(a, wgs, st));
-            } else if (kF32 && !ly.rect && ly.dil == 1 && (Ci == 1 || Ci == 3) && (ly.k == 3 || ly.k == 5 || ly.k == 7) &&
-                       (long)B * Ho * Wo < (1l << 31) / 32) {
+            } else if (kF32 && l == 0 && first_on_mfma(net, g)) {
                 // fp32 storage, the image layer: short reduction on the fp32 matrix instruction
                 FirstMfmaArgs a{};
                 a.in = (const float*)in; a.Wk = Wk; a.out = (float*)out;
                 a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ho = Ho; a.Wo = Wo; a.Co = ly.cout;
                 a.squash = ly.tanh_out ? 1 + net->logistic : 0;
                 bool launched = false;
-                LAUNCH("first_layer_mfma", l, step, flops, bytes, launched = launch_first_mfma(a, ly.k, Ci, B, st));
+                if (pooled_first) {
+                    a.Hs = g.src_h; a.Ws = g.src_w; a.top = g.pad_top; a.left = g.pad_left;
+                    a.Hp = g.rows[1]; a.Wp = g.cols[1];
+                    a.out = (float*)(ws + g.act_off[1]);
+                }
+                LAUNCH(pooled_first ? "first_pool_mfma" : "first_layer_mfma", l, step, flops, pooled_first ? es * (n_in + (double)B * a.Hp * a.Wp * a.Co) : bytes,
+                       launched = launch_first_mfma(a, ly.k, Ci, B, pooled_first, st));
                 if (!launched) return fail(MPCNN_EUNSUPPORTED, "layer %zu: no image-layer kernel instance", l);
+                if (pooled_first) {                   // (the next layer's work is done)
+                    in = (const T*)a.out; Hi = a.Hp; Wi = a.Wp; Ci = ly.cout;
+                    ++l;
+                    continue;
+                }
             } else {
                 const int og = ceil_div(ly.cout, 4);
                 const long total = (long)B * Ho * Wo * og;
@@ -1965,9 +1993,8 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         const bool img_sides = ly.dil == 1 && !ly.rect && (ly.k == 3 || ly.k == 5 || ly.k == 7);
         if (!g.fwd[l].ok && l == 0 && net->bf16 && img_sides && ly.cin <= 4 && ly.cout <= 64)
             put("  forward: image-layer kernel on the bf16 MFMA\n");
-        else if (!g.fwd[l].ok && !net->bf16 && img_sides && (ly.cin == 1 || ly.cin == 3) &&
-                 (long)B * g.rows[l] * g.cols[l] < (1l << 31) / 32)
-            put("  forward: image-layer kernel on the fp32 MFMA\n");
+        else if (l == 0 && first_on_mfma(net, g))
+            put("  forward: image-layer kernel on the fp32 MFMA%s\n", first_with_pool(net, g) ? ", the pool behind it in the same launch" : "");
         else
             conv("forward", g.fwd[l], ly.fwd_ct, two_part_forward(net, g, l));
         if (!training) continue;
