@@ -849,7 +849,9 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         if (tp.ok) { g->fwd[L - 2] = tp; g->head = true; }
     }
     if (g->small_net) {
-        off = 0;                                      // (the image is read as it comes)
+        // (A forward pass needs none of it, but asks for what it did layer by layer: what a caller's workspace, or the static one, is too small for does
+        // not depend on the kernel that runs.)
+        off = training ? 0 : off + 2 * align_up(max_act);
         for (size_t l = 0; training && l < L; ++l) {
             const size_t elems = (size_t)B * g->rows[l] * g->cols[l] * net->layers[l].cout;
             g->act_off[l] = off; off = align_up(off + sizeof(float) * elems);
@@ -859,7 +861,7 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
         g->small_partial_off = off;
         if (training) off = align_up(off + sizeof(float) * net->n_params * (fixed_partials ? mpcnn::kSmallWgs : g->small_wgs));
         g->loss_partial_off = off;
-        g->total = align_up(off + sizeof(double) * mpcnn::kSmallWgs);
+        g->total = align_up(off + sizeof(double) * kLossBlocks);
         g->label_h = H; g->probs_rows = r; g->accumulate = false;
         g->small.B = B; g->small.W = W; g->small.Ho = r; g->small.Wo = c; g->small.ctr = (net->patch - 1) / 2;
         return true;
