@@ -841,10 +841,20 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
                         float v = acc[o][p][4 * n + z];
                         if constexpr (P == 2) v *= down.first;
                         acc[o][p][4 * n + z] = (float)(T)finish(v, P == 2 ? down.second : P == 3 ? kPartsDown : 1.f, bias[z]);
-                        if (P == 3 && kept && exists && oc + z < a.Co) acc[o][p][4 * n + z] = load1(mine + oc + z);
+                        if (P == 3 && kept && exists && oc < a.Co) acc[o][p][4 * n + z] = load1(mine + oc + z);
                     }
                 }
         }
+        if (oc0 + 32 * MO > a.Co)                     // channels that do not exist: zeros (an infinite input times no weight is not a number; uniform)
+#pragma unroll
+            for (int o = 0; o < MO; ++o)
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    if (oc0 + 32 * o + 8 * n + 4 * lg >= a.Co)
+#pragma unroll
+                        for (int p = 0; p < MP; ++p)
+#pragma unroll
+                            for (int z = 0; z < 4; ++z) acc[o][p][4 * n + z] = 0.f;
         const int n_cls = head_args()->n;
         float* const sums = head_wl + n_cls * kChannels;
         for (int c = 0; c < n_cls; ++c) {

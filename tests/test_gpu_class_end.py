@@ -92,6 +92,25 @@ def test_sums_that_are_not_finite(hidden):
     check(layers, patch, 1, H, W, "f32", "mcce", "tanh", params=params)
 
 
+@pytest.mark.parametrize("hidden", [100, 200])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_infinite_pixels(hidden, dtype):
+    """A hidden layer on the image itself: infinite inputs reach units that exist, and none of the channels that only fill the tiles."""
+    net = mpcnn.Net(((FC, hidden, 0), (FC, 2, 0)), 20, 3, mpcnn.BF16 if dtype == "bf16" else mpcnn.F32)
+    assert AT_END in net.plan_describe(1, 30, 41, False)
+    rng = np.random.default_rng(hidden)
+    net.set_params(rng.uniform(-0.2, 0.2, net.param_count).astype(np.float32))
+    image = rng.uniform(0, 1, (1, 20, 30, 41)).astype(np.float32)
+    image[0, 3, 7, 9], image[0, 5, 20, 30] = np.inf, -np.inf
+    image = torch.from_numpy(image).cuda()
+    probs = torch.empty((1, 2, 28, 39), device="cuda")
+    net.seg_backward(image, torch.zeros((1, 30, 41), dtype=torch.int32, device="cuda"), probs=probs)
+    want = probs.cpu().numpy()
+    assert np.isfinite(want).all()
+    assert np.array_equal(net.seg_forward(image, torch.full_like(probs, -1.0)).cpu().numpy(), want)
+    net.close()
+
+
 @pytest.mark.parametrize("below,k,hidden,size", [(64, 2, 200, 300), (128, 2, 200, 310), (100, 3, 132, 300), (128, 2, 256, 400)])
 def test_all_channels_in_one_workgroup(below, k, hidden, size):
     """bf16 storage, training: 129 .. 256 channels in one group of workgroups against two groups of four tiles (by a tiling hint), bit for bit."""
