@@ -1075,16 +1075,18 @@ bool launch_first_mfma(const mpcnn::FirstMfmaArgs& a0, int k, int ci, int B, boo
 #undef CASE
     return false;
 }
-// The image layer's kernel with fp32 storage (else the plain one), and whether the pool behind it comes with it: nothing kept, 2 x 2
-bool first_on_mfma(const mpcnn_net* net, const Geom& g)
+// fp32 storage: layers of one or three channels at spacing 1 - the image's, and any other layer that narrow before the first pool - on the fp32
+// matrix instruction; they are too narrow for conv_parts_kernel, and the plain kernel multiplies on the vector ALU.
+bool narrow_on_mfma(const mpcnn_net* net, const Geom& g, size_t l)
 {
-    const Layer& ly = net->layers[0];
-    return !net->bf16 && ly.kind != MPCNN_MP && !ly.class_fused && !g.fwd[0].ok && !ly.rect && ly.dil == 1 && (ly.cin == 1 || ly.cin == 3) &&
-           (ly.k == 3 || ly.k == 5 || ly.k == 7) && (long)g.B * g.rows[0] * g.cols[0] < (1l << 31) / 32;
+    const Layer& ly = net->layers[l];
+    return !net->bf16 && ly.kind != MPCNN_MP && !ly.class_fused && !g.fwd[l].ok && !ly.rect && ly.dil == 1 && (ly.cin == 1 || ly.cin == 3) &&
+           (ly.k == 3 || ly.k == 5 || ly.k == 7) && (long)g.B * g.rows[l] * g.cols[l] < (1l << 31) / 32;
 }
+// ... the image layer's with the pool behind it: nothing kept, 2 x 2
 bool first_with_pool(const mpcnn_net* net, const Geom& g)
 {
-    return !g.training && net->layers.size() > 1 && first_on_mfma(net, g) && net->layers[1].kind == MPCNN_MP && !net->layers[1].rect && net->layers[1].k == 2;
+    return !g.training && net->layers.size() > 1 && narrow_on_mfma(net, g, 0) && net->layers[1].kind == MPCNN_MP && !net->layers[1].rect && net->layers[1].k == 2;
 }
 template <typename T>
 bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipStream_t st)
@@ -1361,8 +1363,8 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
                 a.nty = ceil_div(Ho, kFirstBmTy); a.ntx = ceil_div(Wo, kFirstBmTx);
                 const unsigned wgs = (unsigned)std::min<long>((long)B * a.nty * a.ntx, 4L * kNumCU);
                 LAUNCH("first_layer_bm", l, step, flops, bytes, launch_first_bm(a, wgs, st));
-            } else if (kF32 && l == 0 && first_on_mfma(net, g)) {
-                // fp32 storage, the image layer: short reduction on the fp32 matrix instruction
+            } else if (kF32 && narrow_on_mfma(net, g, l)) {
+                // short reduction on the fp32 matrix instruction
                 FirstMfmaArgs a{};
                 a.in = (const float*)in; a.Wk = Wk; a.out = (float*)out;
                 a.B = B; a.Hi = Hi; a.Wi = Wi; a.Ho = Ho; a.Wo = Wo; a.Co = ly.cout;
@@ -1995,8 +1997,8 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         const bool img_sides = ly.dil == 1 && !ly.rect && (ly.k == 3 || ly.k == 5 || ly.k == 7);
         if (!g.fwd[l].ok && l == 0 && net->bf16 && img_sides && ly.cin <= 4 && ly.cout <= 64)
             put("  forward: image-layer kernel on the bf16 MFMA\n");
-        else if (l == 0 && first_on_mfma(net, g))
-            put("  forward: image-layer kernel on the fp32 MFMA%s\n", first_with_pool(net, g) ? ", the pool behind it in the same launch" : "");
+        else if (narrow_on_mfma(net, g, l))
+            put("  forward: image-layer kernel on the fp32 MFMA%s\n", l == 0 && first_with_pool(net, g) ? ", the pool behind it in the same launch" : "");
         else
             conv("forward", g.fwd[l], ly.fwd_ct, two_part_forward(net, g, l));
         if (!training) continue;

@@ -25,3 +25,13 @@ def test_weight_gradient_with_bf16_storage(k, ci, maps, height, width, batch):
     assert "image-layer kernel on the %s MFMA, " % ("bf16" if maps % 8 == 0 else "fp32") in plan
     full_parity(wl.Workload("image_layer_bf16_k%d_c%d_m%d" % (k, ci, maps), layers, k + 5, ci, 2, batch, height, width, 0.2,
                             "ellipses", dtype="bf16", seed_image=1401, seed_label=2401, seed_param=3401), with_pixw=True)
+
+
+@pytest.mark.parametrize("maps,k", [(1, 5), (3, 3), (3, 7)])
+def test_a_later_layer_as_narrow(maps, k):
+    """fp32 storage: a second convolution on one or three maps takes the image layer's kernel."""
+    layers = ((C, maps, 3), (C, 12, k), (MP, 0, 2), (FC, 6, 0), (FC, 2, 0))
+    plan = mpcnn.Net(layers, 3, k + 5).plan_describe(2, 60, 77, True)
+    assert "on the fp32 MFMA" in plan[plan.index("layer 1:"):plan.index("layer 2:")].split("gradient")[0]
+    full_parity(wl.Workload("narrow_k%d_m%d" % (k, maps), layers, k + 5, 3, 2, 2, 60, 77, 0.3, "ellipses",
+                            seed_image=1402, seed_label=2402, seed_param=3402), with_pixw=True)

@@ -63,3 +63,19 @@ def test_two_parts_where_a_launch_may_take_them(classes):
     known = classes <= 4
     assert said[1, "forward"] and said[1, "data gradient"] and said[2, "forward"], plan
     assert said[2, "data gradient"] == known and said[2, "weight gradient"] == known, plan
+
+
+@pytest.mark.parametrize("training", [True, False])
+@pytest.mark.parametrize("maps,k", [(1, 3), (3, 5), (3, 7)])
+def test_narrow_layers_are_on_the_matrix_cores(maps, k, training):
+    """A second convolution on one or three maps is the fp32 instruction's, as the image layer is; behind a pool (spacing 2) it is not."""
+    def forward(layers, patch, layer):
+        net = mpcnn.Net(layers, 3, patch)
+        plan = net.plan_describe(1, 512, 512, training)
+        net.close()
+        own = plan[plan.index("layer %d:" % layer):plan.index("layer %d:" % (layer + 1))]
+        return [line for line in own.splitlines() if "forward:" in line][0]
+
+    rest = ((MP, 0, 2), (FC, 20, 0), (FC, 2, 0))
+    assert "on the fp32 MFMA" in forward(((C, maps, 3), (C, 64, k)) + rest, k + 5, 1)
+    assert "plain kernel" in forward(((C, maps, 3), (MP, 0, 2), (C, 64, k)) + rest, 2 * k + 4, 2)
