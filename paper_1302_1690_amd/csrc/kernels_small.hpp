@@ -1,10 +1,10 @@
 // Whole nets of few maps and parameters in one launch: a workgroup takes a square of output pixels through every layer, forward and back, in LDS.
 //
-// A net of one to seven maps per layer has nothing for the matrix cores, and layer by layer its pass is a dozen launches of 4 to 10 us each, whatever
+// A net of one to eight maps per layer has nothing for the matrix cores, and layer by layer its pass is a dozen launches of 4 to 10 us each, whatever
 // they compute: a chain of dependent loads behind a start-up, an end and the wait for both.  A pixel depends on its patch only, so the maps above a
 // square of T x T pixels - (T + what the filters and windows above take)^2 positions each, a few thousand numbers - and their deltas fit in LDS
 // together, and squares need nothing of each other: neighbours compute the positions between them twice, which costs less than a launch as long
-// as T is not small against the patch (small_net_fits, plan_small).  Gradients are linear in the deltas, so a square's are the sums over its own pixels.
+// as T is not small against the patch (which nets: small_net_fits; T: plan_small).  Gradients are linear in the deltas, so a square's are the sums over its own pixels.
 // A thread owns an element of a map (forward, data gradient, routing) or a parameter and some of the rows (weight gradient); a tap's channels come
 // in few wide reads, several taps ahead of the sums.  Bound by instructions and by a microsecond per step and layer (its fields, a barrier).
 // Sums are in tap order for every element, wherever the square lies and however large it is: equal bits for a position in every call.
@@ -24,7 +24,6 @@ namespace mpcnn {
 
 constexpr int kSmallThreads = 512;
 constexpr int kSmallLayers = 12, kSmallSide = 22;   // layers; side of a square, whose pixels are no more than the threads
-constexpr size_t kSmallParams = 2048;   // parameters, at most
 constexpr int kSmallWgs = 512;          // workgroups, at most (two share a compute unit); they walk the squares
 constexpr int kSmallRed = 2 * kSmallThreads;
 

@@ -751,21 +751,41 @@ size_t small_places(const mpcnn_net* net, int T, bool training, mpcnn::SmallArgs
     return align_up(off, 16);
 }
 constexpr size_t kSmallLds = 64 * 1024 - 2048;   // (the arguments and the sums of the loss lie beside)
-// Nets that small_net_kernel takes, at every size (so that a pixel's probabilities do not depend on the call that computes them): fp32 storage,
-// square windows and filters, nothing for the convolutions' matrix instruction, and a square whose halo costs no more than the pixels themselves.
+// Nets that small_net_kernel takes, at every size (so that a pixel's probabilities do not depend on the call that computes
+// them): fp32 storage, square windows and filters, nothing for the convolutions' matrix instruction, and of these the ones that it does not slow down on
+// large images, where launches cost nothing.  235 nets drawn at random, one image of 1536 x 1536 or 2048 x 2048, time of training / probabilities
+// against layer by layer:
+//   three layers with parameters or more.  Two are four launches (hidden 8, filter 6 x 6 on one map 1.44 / 1.40, on 3 x 3 .62 / .66; 3, 3 x 3, behind it 5,
+//     5 x 5 .61 / 1.07), one is two (.53 / 1.17);
+//   no convolution of four or eight maps: the layers' kernels take four maps per thread (8, 3 x 3, pool, 2 on 6 x 6 1.70 / .51; 8, 5 x 5, pool, 7 on 5 x 5
+//     1.43 / .79; 4, 3 x 3, pool, 4 on 4 x 4 1.09 / .66);
+//   150 filter taps, of which 64 on a single map: with one channel a product costs two reads of LDS (7, 7 x 7, 5, 2 .87 / 1.26; 1, 5 x 5, pool, 6 on 6 x 6
+//     .75 / 1.26; 6, 7 x 7, 6, 4 x 4, 5, 2 1.16 / .77; 6, 5 x 5, pool, 7 on 5 x 5 1.08 / .96);
+//   LDS for training's squares of 14 x 14 (5, 3 x 3, pool of 3, 4 on 4 x 4, 2 in squares of 12 x 12 1.24 / 1.02), at a halo of two thirds more than the
+//     pixels themselves at most (5, 2 x 2, between pools of 3 and 2 1.07 / .87).
+// The 93 nets that are left: 1.00 / 1.01 at most, .52 / .64 in the middle; on 64 x 64 pixels .3 to .6.
+constexpr int kSmallTaps = 150, kSmallTapsOnOne = 64, kSmallLeast = 14;
 bool small_net_fits(const mpcnn_net* net)
 {
-    if (net->bf16 || net->layers.size() > (size_t)mpcnn::kSmallLayers || net->n_params > mpcnn::kSmallParams || net->hint_pt || net->hint_mp) return false;
-    for (const Layer& ly : net->layers)
+    if (net->bf16 || net->layers.size() > (size_t)mpcnn::kSmallLayers || net->hint_pt || net->hint_mp) return false;
+    long taps = 0, on_one = 0;
+    int with_params = 0;
+    for (const Layer& ly : net->layers) {
         if (ly.rect || ly.k2 != ly.k || ly.drop2 != ly.drop || ly.dil2 != ly.dil || ly.k > 32 || ly.fwd_mfma || ly.cin > mpcnn::kSmallChannels ||
-            ly.cout > mpcnn::kSmallChannels) return false;
+            ly.cout > mpcnn::kSmallChannels || (ly.kind == MPCNN_C && ly.cout % 4 == 0)) return false;
+        if (ly.kind == MPCNN_MP) continue;
+        ++with_params;
+        taps += (long)ly.k * ly.k * ly.cout;
+        if (ly.cin == 1) on_one += (long)ly.k * ly.k * ly.cout;
+    }
+    if (with_params < 3 || taps > kSmallTaps || on_one > kSmallTapsOnOne) return false;
     mpcnn::SmallArgs a{};
     double pixel = 0;
     for (const Layer& ly : net->layers) pixel += (double)ly.cout * ly.k * ly.k * (ly.kind == MPCNN_MP ? 1 : ly.cin);
-    for (int T = 4; T <= mpcnn::kSmallSide; T += 2) {
+    for (int T = kSmallLeast; T <= mpcnn::kSmallSide; T += 2) {
         double work = 0;
         if (small_places(net, T, true, &a, &work) > kSmallLds) break;
-        if (work <= 2 * pixel * T * T) return true;
+        if (3 * work <= 5 * pixel * T * T) return true;
     }
     return false;
 }

@@ -79,3 +79,26 @@ def test_narrow_layers_are_on_the_matrix_cores(maps, k, training):
     rest = ((MP, 0, 2), (FC, 20, 0), (FC, 2, 0))
     assert "on the fp32 MFMA" in forward(((C, maps, 3), (C, 64, k)) + rest, k + 5, 1)
     assert "plain kernel" in forward(((C, maps, 3), (MP, 0, 2), (C, 64, k)) + rest, 2 * k + 4, 2)
+
+
+def test_nets_in_one_launch_are_those_it_is_faster_for():
+    """Nothing for the convolutions' matrix instruction and eight channels at most; of these, nets of three layers and more, without convolutions of four or
+    eight maps, of 150 filter taps and 64 on a single map, whose squares hold 14 x 14 pixels at two thirds of halo: at every size, in every call."""
+    def small(layers, patch, size, training, ch=1):
+        net = mpcnn.Net(layers, ch, patch)
+        plan = net.plan_describe(1, size, size, training)
+        net.close()
+        return "whole net in one launch" in plan
+
+    tiny = wl.CONFIGS[0]
+    refused = [(((C, 8, 5), (MP, 0, 2), (FC, 7, 0), (FC, 2, 0)), 14), (((C, 8, 3), (MP, 0, 2), (FC, 2, 0), (FC, 3, 0)), 14),
+               (((C, 4, 3), (MP, 0, 2), (FC, 4, 0), (FC, 2, 0)), 10), (((FC, 3, 0),), 4), (((FC, 8, 0), (FC, 2, 0)), 6),
+               (((C, 7, 7), (FC, 5, 0), (FC, 2, 0)), 7), (((C, 1, 5), (MP, 0, 3), (FC, 6, 0), (FC, 2, 0)), 22), (((C, 5, 3), (MP, 0, 3), (FC, 4, 0), (FC, 2, 0)), 14),
+               (((MP, 0, 3), (C, 5, 2), (MP, 0, 2), (FC, 4, 0), (FC, 2, 0)), 17), (((C, 9, 3), (FC, 3, 0), (FC, 2, 0)), 4),
+               (((C, 8, 3), (C, 8, 3), (FC, 2, 0)), 6), (((C, 7, 9), (C, 7, 9), (FC, 2, 0)), 17)]
+    for size in (40, 64, 301, 1024, 2048):
+        for training in (False, True):
+            assert small(tiny.layers, tiny.patch, size, training)
+            assert small(((C, 7, 2), (C, 3, 5), (FC, 5, 0), (FC, 2, 0)), 6, size, training, 3)
+            for layers, patch in refused:
+                assert not small(layers, patch, size, training, 2 if patch == 17 else 1), layers
