@@ -145,8 +145,7 @@ mpcnn_status mpcnn_set_activation(mpcnn_net* net, mpcnn_activation kind);
  * planner (the default), which weighs matrix-instruction time against staging per layer and
  * image size.  A pair that no kernel instance serves for a layer's channel count leaves that
  * layer to the planner.  Results do not depend on the tiling: every output
- * element is the same sum in the same order.  (Nets of at most eight maps per layer and 2048
- * parameters, whose whole pass is one launch, run layer by layer with a tiling: sums in another order.)  Takes effect at the next forward / backward
+ * element is the same sum in the same order.  Takes effect at the next forward / backward
  * call.  EINVAL unless position_tiles is 0, 2, 4, 8 or 16 and tiles_per_wave 0, 1, 2 or 4. */
 mpcnn_status mpcnn_set_conv_tiling(mpcnn_net* net, int position_tiles, int tiles_per_wave);
 

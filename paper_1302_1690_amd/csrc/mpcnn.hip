@@ -751,7 +751,7 @@ size_t small_places(const mpcnn_net* net, int T, bool training, mpcnn::SmallArgs
     return align_up(off, 16);
 }
 constexpr size_t kSmallLds = 64 * 1024 - 2048;   // (the arguments and the sums of the loss lie beside)
-// Nets that small_net_kernel takes, at every size (so that a pixel's probabilities do not depend on the call that computes
+// Nets that small_net_kernel takes, at every size and with any tiling hint (so that a pixel's probabilities do not depend on the call that computes
 // them): fp32 storage, square windows and filters, nothing for the convolutions' matrix instruction, and of these the ones that it does not slow down on
 // large images, where launches cost nothing.  235 nets drawn at random, one image of 1536 x 1536 or 2048 x 2048, time of training / probabilities
 // against layer by layer:
@@ -767,7 +767,7 @@ constexpr size_t kSmallLds = 64 * 1024 - 2048;   // (the arguments and the sums 
 constexpr int kSmallTaps = 150, kSmallTapsOnOne = 64, kSmallLeast = 14;
 bool small_net_fits(const mpcnn_net* net)
 {
-    if (net->bf16 || net->layers.size() > (size_t)mpcnn::kSmallLayers || net->hint_pt || net->hint_mp) return false;
+    if (net->bf16 || net->layers.size() > (size_t)mpcnn::kSmallLayers) return false;
     long taps = 0, on_one = 0;
     int with_params = 0;
     for (const Layer& ly : net->layers) {

@@ -1,6 +1,6 @@
 """Nets of few maps and parameters, whose whole pass is one launch (squares of output pixels through every layer, forward and back): against the
 oracle, at sizes of one square and less, a ragged last one and several per workgroup, over the filters, windows, spacings and channel counts the
-kernel takes; and against the layer-by-layer kernels, which a tiling hint leaves such a net to."""
+kernel takes; and against the layer-by-layer kernels, which a twin with more hidden units, all of them zeros, is left to."""
 from dataclasses import replace
 
 import numpy as np
@@ -57,17 +57,27 @@ def test_against_the_layers_one_by_one(batch, height, width, loss, squash):
     d_img, d_lab = torch.from_numpy(img).cuda(), torch.from_numpy(lab).cuda()
     pixw = torch.rand(d_lab.shape, device="cuda") + 0.5
     out = []
-    for hint in ((0, 0), (4, 1)):
-        net = mpcnn.Net(cfg.layers, cfg.in_channels, cfg.patch)
-        net.set_conv_tiling(*hint)
-        assert ("whole net" in net.plan_describe(batch, height, width, True)) == (hint == (0, 0))
-        net.set_params(params)
+    for hidden in (8, 12):                             # (the twin: four hidden units without weights, into them or out of them)
+        layers = cfg.layers[:-2] + ((FC, hidden, 0), cfg.layers[-1])
+        net = mpcnn.Net(layers, cfg.in_channels, cfg.patch)
+        assert ("whole net" in net.plan_describe(batch, height, width, True)) == (hidden == 8)
+        own = np.ones(net.param_count, dtype=bool)     # places of the smaller net's parameters
+        if hidden == 12:
+            n_in = 3 * 3 * 3                           # W[o][c][u][v], b[o] of the hidden layer, then W[o][unit], b[o]
+            at = net.param_count - (12 * n_in + 12) - (2 * 12 + 2)
+            own[at + 8 * n_in:at + 12 * n_in] = False
+            own[at + 12 * n_in + 8:at + 12 * n_in + 12] = False
+            for o in range(2):
+                own[net.param_count - 26 + 12 * o + 8:net.param_count - 26 + 12 * o + 12] = False
+        wide = np.zeros(net.param_count, dtype=np.float32)
+        wide[own] = params
+        net.set_params(wide)
         net.set_loss(loss)
         net.set_activation(squash)
         probs = torch.empty((batch, cfg.n_classes, cfg.out_h, cfg.out_w), device="cuda")
         total = torch.zeros(1, dtype=torch.float64, device="cuda")
         net.seg_backward(d_img, d_lab, pixw=pixw, probs=probs, loss=total)
-        grads = net.get_grads()
+        grads = net.get_grads()[own]
         same = net.seg_forward_same(d_img).cpu().numpy()
         only = net.seg_forward(d_img).cpu().numpy()
         p = probs.cpu().numpy()
@@ -77,7 +87,7 @@ def test_against_the_layers_one_by_one(batch, height, width, loss, squash):
         net.seg_backward_banded(d_img, d_lab, 37, pixw=pixw, probs=probs, loss=banded)
         assert np.array_equal(probs.cpu().numpy(), p)
         assert abs(banded.item() - total.item()) <= 1e-6 * abs(total.item())
-        g2 = net.get_grads()
+        g2 = net.get_grads()[own]
         assert np.abs(g2 - grads).max() <= 1e-5 * np.abs(grads).max()
         out.append((p, same, total.item(), grads))
         net.close()
@@ -85,6 +95,19 @@ def test_against_the_layers_one_by_one(batch, height, width, loss, squash):
     assert np.abs(p0 - p1).max() <= 2e-6 and np.abs(s0 - s1).max() <= 2e-6
     assert abs(l0 - l1) <= 1e-6 * abs(l1)
     assert np.abs(g0 - g1).max() <= 1e-4 * np.abs(g1).max()
+
+
+@pytest.mark.parametrize("hint", [(4, 1), (16, 4), (2, 0)])
+def test_a_tiling_changes_nothing(hint):
+    """mpcnn_set_conv_tiling promises the same sums in the same order."""
+    cfg = replace(wl.crop(wl.CONFIGS[0], 2, 75, 90), name="small_hint")
+    img, lab = wl.make_inputs(cfg)
+    out = []
+    for h in ((0, 0), hint):
+        net, probs, loss, grads = run_gpu(cfg, img, lab, wl.make_params(cfg), tiling=h)
+        out.append((probs, grads, loss))
+        net.close()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]) and out[0][2] == out[1][2]
 
 
 def test_nan_stays_where_it_is():

@@ -83,9 +83,11 @@ def test_narrow_layers_are_on_the_matrix_cores(maps, k, training):
 
 def test_nets_in_one_launch_are_those_it_is_faster_for():
     """Nothing for the convolutions' matrix instruction and eight channels at most; of these, nets of three layers and more, without convolutions of four or
-    eight maps, of 150 filter taps and 64 on a single map, whose squares hold 14 x 14 pixels at two thirds of halo: at every size, in every call."""
-    def small(layers, patch, size, training, ch=1):
+    eight maps, of 150 filter taps and 64 on a single map, whose squares hold 14 x 14 pixels at two thirds of halo: at every size, in every call, and with a tiling,
+    which promises the same bits."""
+    def small(layers, patch, size, training, ch=1, hint=(0, 0)):
         net = mpcnn.Net(layers, ch, patch)
+        net.set_conv_tiling(*hint)
         plan = net.plan_describe(1, size, size, training)
         net.close()
         return "whole net in one launch" in plan
@@ -98,7 +100,7 @@ def test_nets_in_one_launch_are_those_it_is_faster_for():
                (((C, 8, 3), (C, 8, 3), (FC, 2, 0)), 6), (((C, 7, 9), (C, 7, 9), (FC, 2, 0)), 17)]
     for size in (40, 64, 301, 1024, 2048):
         for training in (False, True):
-            assert small(tiny.layers, tiny.patch, size, training)
+            assert small(tiny.layers, tiny.patch, size, training) and small(tiny.layers, tiny.patch, size, training, hint=(4, 1))
             assert small(((C, 7, 2), (C, 3, 5), (FC, 5, 0), (FC, 2, 0)), 6, size, training, 3)
             for layers, patch in refused:
                 assert not small(layers, patch, size, training, 2 if patch == 17 else 1), layers
