@@ -1074,13 +1074,33 @@ void launch_first_bm(const mpcnn::FirstBmArgs& a, unsigned wgs, hipStream_t st)
     CASE(1, 3) CASE(1, 5) CASE(1, 7) CASE(2, 3) CASE(2, 5) CASE(2, 7)
 #undef CASE
 }
+// Rows per wave of the image layer with the pool behind it: the least time of a compute unit's workgroups - their matrix instructions, and for every round
+// of resident ones what a round takes besides (image in, LDS, squashing, pool, stores).  Whole forward passes, us, 1 / 2 / 4 rows: 16 maps, 3 x 3, 256 x 265
+// 27.3 / 28.2 / 29.4, 512 x 521 56.0 / 55.8 / 59.8; 64 maps, 5 x 5 of three channels, 360 x 369 67.4 / 63.9 / 72.0; 7 x 7 of three channels, 32 maps, 300 x 309
+// 50.1 / 47.0 / 49.3, 420 x 429 76.2 / 73.7 / 71.5, 512 x 521 101 / 88 / 98, 128 maps, 1024 x 1033 1127 / 903 / 868.  (The most rows that leave two workgroups
+// per unit, as without the pool, were up to 13 % slower than two launches.)
+int pooled_rows(int k, int ci, int B, int rows, int cols, int ct)
+{
+    const bool large = k == 7 && ci == 3;             // (its filters take the registers)
+    const double mul = 64.0 * k * ceil_div(k * ci, 2);
+    int best = 1;
+    double best_cost = -1;
+    for (int mp : {1, 2, 4}) {
+        const int resident = mp == 4 ? 2 : large ? 3 : mp == 2 ? 4 : 5;
+        const long per_cu = ((long)B * ceil_div(rows, 4 * mp - 1) * ceil_div(cols, 31) * ct + kNumCU - 1) / kNumCU;
+        const double cost = per_cu * mp * mul + (per_cu + resident - 1) / resident * (2000.0 + 1500.0 * mp);
+        if (best_cost < 0 || cost < best_cost) { best = mp; best_cost = cost; }
+    }
+    return best;
+}
 // fp32 storage, the image layer on the fp32 matrix instruction: instance by filter side, channels and rows per wave
 bool launch_first_mfma(const mpcnn::FirstMfmaArgs& a0, int k, int ci, int B, bool pool, hipStream_t st)
 {
     mpcnn::FirstMfmaArgs a = a0;
     const int ct = ceil_div(a.Co, 32), rows = pool ? a.Hp : a.Ho, cols = pool ? a.Wp : a.Wo, less = pool ? 1 : 0;
     int mp = 4;   // rows per wave: as many as still give every compute unit two workgroups
-    while (mp > 1 && (long)B * ceil_div(rows, 4 * mp - less) * ceil_div(cols, 32 - less) * ct < 2L * kNumCU) mp >>= 1;
+    while (mp > 1 && (long)B * ceil_div(rows, 4 * mp) * ceil_div(cols, 32) * ct < 2L * kNumCU) mp >>= 1;
+    if (pool) mp = pooled_rows(k, ci, B, rows, cols, ct);
     a.nty = ceil_div(rows, 4 * mp - less); a.ntx = ceil_div(cols, 32 - less);
     const dim3 grid((unsigned)(B * a.nty * a.ntx), (unsigned)ct);
 #define CASE(kk, cc, mm)                                                                              \
@@ -2018,7 +2038,12 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         if (!g.fwd[l].ok && l == 0 && net->bf16 && img_sides && ly.cin <= 4 && ly.cout <= 64)
             put("  forward: image-layer kernel on the bf16 MFMA\n");
         else if (narrow_on_mfma(net, g, l))
-            put("  forward: image-layer kernel on the fp32 MFMA%s\n", l == 0 && first_with_pool(net, g) ? ", the pool behind it in the same launch" : "");
+            {
+            put("  forward: image-layer kernel on the fp32 MFMA");
+            if (l == 0 && first_with_pool(net, g))
+                put(", the pool behind it in the same launch, %d rows per wave", pooled_rows(ly.k, ly.cin, B, g.rows[1], g.cols[1], ceil_div(ly.cout, 32)));
+            put("\n");
+        }
         else
             conv("forward", g.fwd[l], ly.fwd_ct, two_part_forward(net, g, l));
         if (!training) continue;

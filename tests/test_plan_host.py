@@ -104,3 +104,14 @@ def test_nets_in_one_launch_are_those_it_is_faster_for():
             assert small(((C, 7, 2), (C, 3, 5), (FC, 5, 0), (FC, 2, 0)), 6, size, training, 3)
             for layers, patch in refused:
                 assert not small(layers, patch, size, training, 2 if patch == 17 else 1), layers
+
+
+@pytest.mark.parametrize("channels,k,maps,rows_of", [
+    (1, 3, 16, {80: 1, 256: 1, 600: 2, 1400: 2}), (1, 7, 64, {150: 1, 256: 2, 512: 2, 1024: 2}), (3, 5, 64, {112: 1, 360: 2, 1024: 2}),
+    (3, 7, 32, {256: 1, 300: 2, 420: 4, 512: 2}), (3, 7, 128, {112: 2, 256: 2, 420: 2, 1024: 4})])
+def test_rows_per_wave_of_the_image_layer_with_the_pool(channels, k, maps, rows_of):
+    """The one that was measured to be the fastest, at sizes where the others take 2 to 20 % more of a forward pass."""
+    net = mpcnn.Net(((C, maps, k), (MP, 0, 2), (FC, 12, 0), (FC, 2, 0)), channels, k + 5)
+    for size, rows in rows_of.items():
+        assert "same launch, %d rows per wave" % rows in net.plan_describe(1, size, size + 9, False), size
+    net.close()
