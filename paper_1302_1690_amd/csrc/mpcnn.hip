@@ -117,6 +117,7 @@ struct TilePlan {          // conv_parts_kernel: 32 PT positions per workgroup, 
     int PT = 0, Ty = 0, Tx = 0, nty = 0, ntx = 0, wgs = 0, kr = 0;
     mpcnn::PartsInstance in{};
     size_t lds = 0;
+    double cost = 0;       // cycles, by the planner's estimate
     bool ok = false;
 };
 struct WgradPlan {
@@ -295,7 +296,6 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                          const ChanTiling& ct, int P, int mults, size_t es, bool back, int hint_pt, int hint_mp, int head = 0)
 {
     TilePlan best;
-    double best_cost = 0;
     const int fh = ceil_div(out_r, d), fw = ceil_div(out_c, d2);
     const int steps = k * k2 * rpad / 16;
     const mpcnn::PartsInstance* list = mpcnn::kParts1;
@@ -324,7 +324,7 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         // compute unit, its waits in the open, takes 1.4 times as long with one part.
         const double eff = P == 3 ? (per_wave == 2 ? 1.08 : 1.3) : (per_wave > 4 ? 0.88 : per_wave == 4 ? (in.MO == 2 ? 0.98 : 1.0) : 1.2);
         const double alone = P == 3 ? 1.15 : 1.4;
-        const double t_mul = (double)steps * mults * OT * PT * 8.0 * eff * 4 / waves;
+        const double t_mul = (double)steps * mults * OT * PT * 8.0 * eff;   // (on four SIMDs, whatever the waves)
         // filter rows of a block.  All of them, or, from 8 rows on, where blocks are 16 channels, a half, a third ..: a halo of 640
         // positions (fp32) holds a 25 x 25 filter and one position; in rows it holds any.  (32 channels in and out, 160 x 160 positions,
         // forward / data gradient, microseconds whole -> in rows: fp32 20 x 20 435 / 446 -> 207 / 257, 24 x 24 4174 / 5239 -> 401 / 466, 32
@@ -362,11 +362,11 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
                 // (narrow tiles count a tenth more: the 32 positions of an operand then lie in more than four rows of the halo, and
                 // only successive positions are sure to lie on different LDS banks)
                 const double cost = per_cu * ((per_cu < 2 ? alone : 1.0) * (tx >= 8 ? 1.0 : 1.1) * t_mul + 0.25 * t_rest) + t_rest;
-                if (!best.ok || cost < best_cost) {
+                if (!best.ok || cost < best.cost) {
                     best.PT = PT; best.Ty = ty; best.Tx = tx; best.kr = kr;
                     best.nty = nty; best.ntx = ntx; best.lds = lds; best.ok = true;
                     best.wgs = (int)wgs; best.in = in;
-                    best_cost = cost;
+                    best.cost = cost;
                 }
             }
         }
@@ -862,11 +862,18 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
     if (r != H - net->patch + 1 || c != W - net->patch + 1) return false;
     g->head = false;
     if (!training && !g->small_net && L >= 2 && net->layers[L - 1].class_fused && g->fwd[L - 2].ok && !net->hint_pt && !net->hint_mp) {
-        // Nothing of the hidden layer is kept, so it need not pass through memory on its way to the classes.
+        // Nothing of the hidden layer is kept, so it need not pass through memory on its way to the classes - where that way takes longer than the wait for
+        // all channels in one workgroup.  A map of few tiles does not fill the chip with these: 64 -> 200, 5 x 5, 60 x 67, whole passes, us, two launches /
+        // one 36.1 / 41.1, bf16 64 -> 68, 40 x 47 33.5 / 36.4; but 128 -> 200, 2 x 2, 97 x 104 43 / 33, bf16 1000 x 1007 526 / 397.  The pass over the hidden
+        // layer counts 0.006 cycles per element; of 1400 plans of 68 .. 232 units, 34 x 41 .. 1000 x 1007, one is slower by 2 %, four by less than 0.8 us.
+        // Five tiles of 32 units on the eight waves of fp32 storage leave three SIMDs half empty (32 -> 132, 3 x 3, 600 x 607 286 / 317, 32 -> 160 in three
+        // parts, 430 x 437 180 / 185, 64 -> 132 192 / 196): not below four and a half, and in two parts only (64 -> 148 112 / 110, 64 -> 160, 1000 x 1007 1085 / 990).
         const Layer& ly = net->layers[L - 2];
+        const TilePlan& apart = g->fwd[L - 2];
         const TilePlan tp = plan_conv_parts(B, L > 2 ? g->cols[L - 3] : W, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct,
                                             net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false, 0, 0, net->n_cls);
-        if (tp.ok) { g->fwd[L - 2] = tp; g->head = true; }
+        const bool half_empty = !net->bf16 && ceil_div(ly.cout, 32) == 5 && (ly.cout <= 144 || !ly.fwd_half);
+        if (tp.ok && !half_empty && tp.cost <= apart.cost + 0.006 * B * r * c * ly.cout) { g->fwd[L - 2] = tp; g->head = true; }
     }
     if (g->small_net) {
         // (A forward pass needs none of it, but asks for what it did layer by layer: what a caller's workspace, or the static one, is too small for does

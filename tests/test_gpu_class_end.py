@@ -62,7 +62,7 @@ def check(layers, patch, B, H, W, dtype, loss, squash, seen=None, params=None):
 def test_bits_of_the_training_pass(dtype):
     seen = set()
     for hidden, classes, below, k, sizes in (
-            (100, 2, 64, 3, ((40, 47), (200, 171))), (200, 3, 128, 2, ((36, 70), (300, 410))), (128, 2, 32, 2, ((61, 40),)), (160, 3, 32, 4, ((50, 55),)), (132, 2, 20, 2, ((44, 39),)), (256, 4, 48, 2, ((45, 38), (500, 470))),
+            (100, 2, 64, 3, ((50, 55), (200, 171))), (200, 3, 128, 2, ((75, 60), (300, 410))), (128, 2, 32, 2, ((61, 40),)), (160, 3, 32, 4, ((90, 71),)), (164, 2, 20, 2, ((57, 49),)), (256, 4, 48, 2, ((50, 55), (500, 470))),
             (68, 2, 16, 3, ((39, 41),)), (100, 2, 64, 2, ((900, 830),))):
         if below == 16 and dtype == "bf16":
             continue                                   # (no instance of such narrow blocks)
@@ -80,7 +80,7 @@ def test_bits_of_the_training_pass(dtype):
 def test_sums_that_are_not_finite(hidden):
     """Infinite weights: outputs as they are without parts, repaired in memory on their way to the classes; a NaN pixel: its patches alone."""
     layers = ((C, 16, 3), (C, 64, 3), (FC, hidden, 0), (FC, 2, 0))
-    patch, H, W = 8, 60, 51
+    patch, H, W = 8, 140, 131
     rng = np.random.default_rng(hidden)
     n = [16 * 9 + 16, 64 * 16 * 9 + 64, hidden * 64 * 16 + hidden, 2 * hidden + 2]
     params = np.concatenate([rng.uniform(-1, 1, m) * s for m, s in zip(n, (0.5, 0.1, 0.05, 0.2))])
@@ -97,14 +97,15 @@ def test_sums_that_are_not_finite(hidden):
 def test_infinite_pixels(hidden, dtype):
     """A hidden layer on the image itself: infinite inputs reach units that exist, and none of the channels that only fill the tiles."""
     net = mpcnn.Net(((FC, hidden, 0), (FC, 2, 0)), 20, 3, mpcnn.BF16 if dtype == "bf16" else mpcnn.F32)
-    assert AT_END in net.plan_describe(1, 30, 41, False)
+    H, W = 80, 71
+    assert AT_END in net.plan_describe(1, H, W, False)
     rng = np.random.default_rng(hidden)
     net.set_params(rng.uniform(-0.2, 0.2, net.param_count).astype(np.float32))
-    image = rng.uniform(0, 1, (1, 20, 30, 41)).astype(np.float32)
+    image = rng.uniform(0, 1, (1, 20, H, W)).astype(np.float32)
     image[0, 3, 7, 9], image[0, 5, 20, 30] = np.inf, -np.inf
     image = torch.from_numpy(image).cuda()
-    probs = torch.empty((1, 2, 28, 39), device="cuda")
-    net.seg_backward(image, torch.zeros((1, 30, 41), dtype=torch.int32, device="cuda"), probs=probs)
+    probs = torch.empty((1, 2, H - 2, W - 2), device="cuda")
+    net.seg_backward(image, torch.zeros((1, H, W), dtype=torch.int32, device="cuda"), probs=probs)
     want = probs.cpu().numpy()
     assert np.isfinite(want).all()
     assert np.array_equal(net.seg_forward(image, torch.full_like(probs, -1.0)).cpu().numpy(), want)

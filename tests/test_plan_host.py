@@ -115,3 +115,17 @@ def test_rows_per_wave_of_the_image_layer_with_the_pool(channels, k, maps, rows_
     for size, rows in rows_of.items():
         assert "same launch, %d rows per wave" % rows in net.plan_describe(1, size, size + 9, False), size
     net.close()
+
+
+@pytest.mark.parametrize("dtype,below,k,units,at_end", [
+    (mpcnn.F32, 64, 3, 100, {50: True, 97: True, 300: True, 1000: True}), (mpcnn.F32, 128, 2, 200, {40: False, 97: True, 600: True}),
+    (mpcnn.F32, 64, 5, 200, {40: False, 60: False, 200: True, 600: True}), (mpcnn.F32, 32, 3, 132, {40: False, 300: False, 600: False, 1000: False}),
+    (mpcnn.F32, 32, 3, 160, {40: False, 430: False}), (mpcnn.F32, 64, 3, 132, {300: False}), (mpcnn.F32, 64, 3, 160, {97: True, 300: True, 1000: True}),
+    (mpcnn.BF16, 64, 5, 68, {40: False, 60: False, 300: True}), (mpcnn.BF16, 128, 2, 68, {40: False, 60: False, 200: True}),
+    (mpcnn.BF16, 32, 3, 132, {97: True, 600: True}), (mpcnn.BF16, 128, 2, 200, {97: True, 300: True, 1000: True})])
+def test_class_layer_at_the_end_where_it_is_faster(dtype, below, k, units, at_end):
+    """Not on maps of few tiles behind long sums, nor where five tiles leave the eight waves of fp32 storage half empty."""
+    net = mpcnn.Net(((C, 8, 3), (MP, 0, 2), (C, below, 3), (FC, units, 0), (FC, 2, 0)), 1, 2 * (k + 2) + 2, dtype)
+    for size, want in at_end.items():
+        assert ("class layer: at the end of the layer below" in net.plan_describe(1, size, size + 7, False)) == want, size
+    net.close()
