@@ -26,8 +26,9 @@ struct PartsInstance { int CB, WO, WP, MO, MP; };
     X(128, 2, 2, 1, 2) X(128, 4, 1, 1, 2) X(128, 4, 1, 1, 4) X(128, 2, 2, 2, 2)
 // bf16 storage, eight tiles per wave: large maps (two workgroups per compute unit instead of three; never by a tiling hint)
 #define MPCNN_PARTS1_WIDE(X) X(32, 1, 4, 2, 4) X(64, 1, 4, 2, 4) X(32, 2, 2, 2, 4) X(64, 2, 2, 2, 4) X(128, 2, 2, 2, 4)
-// bf16 storage, forward, 129 .. 256 channels in one workgroup instead of two groups that bring the same halo and write halves of the same lines
-// (128 -> 200, 2 x 2, 2 x 2048 x 2048: 3020 -> 2706 us; 2 x 200 x 300 no slower)
+// bf16 storage, forward, 161 .. 256 channels in one workgroup instead of two groups that bring the same halo and write halves of the same lines
+// (128 -> 200, 2 x 2, 2 x 2048 x 2048: 3020 -> 2706 us; 2 x 200 x 300 no slower).  Five tiles keep three of the four waves busy: whole training
+// steps of 64 -> 132, 3 x 3, 2 x 1400 x 1407 4295 -> 4466, 128 -> 132, 2 x 2 5036 -> 5139, 64 -> 160 4344 -> 4386, 128 -> 160 5003 -> 4986.
 #define MPCNN_PARTS1_ALL(X) X(64, 4, 1, 2, 4) X(128, 4, 1, 2, 4)
 // Forward with the class layer behind it, nothing kept: all channels in one workgroup (a hidden layer of 65 .. 128, 129 .. 256 units; eight waves
 // where four of fp32 storage's tiles do not hold them)

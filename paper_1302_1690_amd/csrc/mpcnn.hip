@@ -307,12 +307,12 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
     for (int li = 0; li < n_list; ++li) {
         const mpcnn::PartsInstance& in = list[li];
         const int waves = in.WO * in.WP, OT = in.WO * in.MO;
-        const bool all = !head && OT == 8;            // (one group where the list's others need two)
+        const bool all = !head && OT == 8;            // (one group where the list's others need two: six tiles and more)
         const int split = head || all ? 1 : ct.split;
         const int CB = in.CB, RP = mpcnn::parts_round(CB, waves), nblk = ceil_div(rpad, CB);
         const int PT = in.WP * in.MP, per_wave = in.MO * in.MP, resident = mpcnn::parts_wgs(P, per_wave) * 4 / waves;
         const size_t pitch = (size_t)mpcnn::parts_pitch(P, CB);   // (two parts take less)
-        if ((head ? 32 * OT < co || 16 * OT >= co || 32 * OT > ct.pad : all ? ct.OT * ct.split != 8 : OT != ct.OT) || (CB > 16 && rpad <= CB / 2)) continue;
+        if ((head ? 32 * OT < co || 16 * OT >= co || 32 * OT > ct.pad : all ? ct.OT * ct.split != 8 || co <= 160 : OT != ct.OT) || (CB > 16 && rpad <= CB / 2)) continue;
         // two channel tiles per wave where the last group fills them (a wave skips its tiles only together)
         if (!head && in.MO == 2 && per_wave <= 4 && ceil_div(co, 32) % 2) continue;
         if (per_wave > 4 && (hint_pt || hint_mp || !mpcnn::half_filter(k, k2))) continue;

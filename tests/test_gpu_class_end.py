@@ -112,9 +112,9 @@ def test_infinite_pixels(hidden, dtype):
     net.close()
 
 
-@pytest.mark.parametrize("below,k,hidden,size", [(64, 2, 200, 300), (128, 2, 200, 310), (100, 3, 132, 300), (128, 2, 256, 400)])
+@pytest.mark.parametrize("below,k,hidden,size", [(64, 2, 200, 300), (128, 2, 200, 310), (100, 3, 164, 300), (128, 2, 256, 400)])
 def test_all_channels_in_one_workgroup(below, k, hidden, size):
-    """bf16 storage, training: 129 .. 256 channels in one group of workgroups against two groups of four tiles (by a tiling hint), bit for bit."""
+    """bf16 storage, training: 161 .. 256 channels in one group of workgroups against two groups of four tiles (by a tiling hint), bit for bit."""
     layers = ((C, 8, 3), (MP, 0, 2), (C, below, 3), (FC, hidden, 0), (FC, 3, 0))
     patch = 2 * (k + 2) + 2
     H, W = patch + size, patch + size + 13

@@ -129,3 +129,11 @@ def test_class_layer_at_the_end_where_it_is_faster(dtype, below, k, units, at_en
     for size, want in at_end.items():
         assert ("class layer: at the end of the layer below" in net.plan_describe(1, size, size + 7, False)) == want, size
     net.close()
+
+
+@pytest.mark.parametrize("below,k", [(64, 3), (128, 2)])
+@pytest.mark.parametrize("units,groups", [(132, 2), (160, 2), (164, 1), (200, 1), (256, 1)])
+def test_wide_layers_in_one_group_where_its_waves_are_busy(below, k, units, groups):
+    """bf16 storage, large maps: two groups of four tiles where one of eight would have no more than five."""
+    forward = conv_lines(((C, 8, 3), (MP, 0, 2), (C, below, 3), (FC, units, 0), (FC, 2, 0)), 2 * (k + 2) + 2, 1400, mpcnn.BF16, 3)[0]
+    assert "x %d groups" % groups in forward, forward
