@@ -454,9 +454,15 @@ struct ClassArgs {
 // dW += h delta_z^T, db += delta_z, and dH = (W^T delta_z) (1 - h^2)   (Results: MCCE per
 // pixel; Method: first step of back-propagation; Alg. 2 for the sums).
 // 16 lanes share one position: lane j holds KV quads of channels, quad v = channels
-// 4Q(j + 16(v/Q)) + 4(v%Q) .. +3 - with Q = 1 every quad is a 128-bit access of its own (fp32), with
-// Q = 2 two neighbouring quads are one (8 bf16 values; K a multiple of 8); dot products meet
+// 4G(j + 16(v/G)) + 4(v%G) .. +3, G = class_group.  With Q = 1 every quad is an access of its own (fp32: 128 bits),
+// with Q = 2 two neighbouring quads are one (8 bf16 values; K a multiple of 8); dot products meet
 // by lane moves in a fixed order.  A workgroup walks 16 positions at a time.
+// Bound by memory with two classes and many channels, else by instructions: the fixed order takes four lane moves per class and 16 G quads.  So lanes hold
+// no more quads than K has (K = 24 -> 3 classes, fp32, training, 1200 x 1200 positions 155 -> 111 us; 132 -> 4, bf16 300 -> 257), and the logarithms
+// of a round's losses come together, one per lane (24 -> 2, bf16, 117 -> 112).
+// Neighbouring quads with Q = 1 halve the moves, but every line is then reached twice: ahead with four classes (bf16, 100 -> 4 212 -> 194),
+// not with two, nor with fp32 storage (200 -> 2 482 -> 494).
+template <typename T> constexpr int class_group(int NCLS, int KV, int Q) { return Q == 2 || (sizeof(T) == 2 && KV % 2 == 0 && NCLS * KV >= 8) ? 2 : 1; }
 // Q quads as they come from memory (expanded to fp32 only when their turn comes)
 template <int Q, typename T> struct RawQuads { typedef v4f type; };
 template <> struct RawQuads<1, bf16> { typedef bf16x4 type; };
@@ -491,15 +497,16 @@ __device__ __forceinline__ float row_pair_sum(float x)
 // is the number of bytes those waves have in flight (about 40-50 KB per compute unit with these
 // depths); one less where the weights and their sums leave no registers for it
 template <typename T, int NCLS, int KV>
-constexpr int kClassAhead = (sizeof(T) == 2 ? 3 : 2) - (NCLS * KV >= 16 ? 1 : 0);
+constexpr int kClassAhead = KV == 1 ? 4 : (sizeof(T) == 2 ? 3 : 2) - (NCLS * KV >= 16 ? 1 : 0);
 template <int NCLS, int KV, bool TRAIN, typename T, int Q = 1>
 __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
 {
-    static_assert(KV % Q == 0, "whole accesses");
+    constexpr int G = class_group<T>(NCLS, KV, Q);
+    static_assert(KV % Q == 0 && KV % G == 0, "whole accesses, whole groups");
     static_assert(Q == 1 || sizeof(T) == 2, "pairs of quads: 2-byte storage only");
     // Channel of quad v.  Sums are taken in the order of channels in pairs of pairs - a quad's four products, quads in twos, fours, eights (32
     // channels, a tile of conv_parts_kernel's, which forms the class outputs itself where nothing is kept and adds in the same order), sixteens ..
-    auto chan = [](int lane16, int v) { return 4 * Q * (lane16 + 16 * (v / Q)) + 4 * (v % Q); };
+    auto chan = [](int lane16, int v) { return 4 * G * (lane16 + 16 * (v / G)) + 4 * (v % G); };
     const T* h_t = static_cast<const T*>(a.h);
     T* dh_t = static_cast<T*>(a.dH);
     __shared__ float red[4][KV * 4 * NCLS + NCLS][16];
@@ -535,6 +542,7 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
     // group 0 - its weights are zero, and nothing of it is stored.
     typedef typename RawQuads<Q, T>::type Raw;
     constexpr int AH = kClassAhead<T, NCLS, KV>;
+    static_assert(AH <= 4, "the lanes that keep a loss");
     const long stride = (long)gridDim.x * 16;
     Raw ring[AH][KV / Q];
     int coff[KV / Q];
@@ -577,6 +585,8 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
     // (the ring's slots are taken in turn by an unrolled inner loop: moving a slot's registers
     // along would wait for its load; a turn past the last position works on the last position
     // again with label "ignore" and stores nothing - no exit from the middle of the round)
+    int loss_t = -1;
+    float loss_of = 1.f, loss_z = 0.f, loss_w = 0.f;
     for (long mo = m0; mo < M; mo += AH * stride)
 #pragma unroll
     for (int slot = 0; slot < AH; ++slot) {
@@ -598,14 +608,14 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
 #pragma unroll
                 for (int s = 1; s < 4; ++s) quad[v] = fmaf(hv[v][s], w[v][s][o], quad[v]);
             }
-            float part[KV / Q];                       // 64 channels each (Q = 2: 128)
+            float part[KV / G];                       // 64 channels each (G = 2: 128)
 #pragma unroll
-            for (int i = 0; i < KV / Q; ++i)
-                part[i] = row_pair_sum<8>(row_pair_sum<4>(row_pair_sum<2>(row_pair_sum<1>(Q == 2 ? quad[Q * i] + quad[Q * i + Q - 1] : quad[i]))));
+            for (int i = 0; i < KV / G; ++i)
+                part[i] = row_pair_sum<8>(row_pair_sum<4>(row_pair_sum<2>(row_pair_sum<1>(G == 2 ? quad[G * i] + quad[G * i + G - 1] : quad[i]))));
 #pragma unroll
-            for (int step = 1; step < KV / Q; step *= 2)
+            for (int step = 1; step < KV / G; step *= 2)
 #pragma unroll
-                for (int i = 0; i < KV / Q; i += 2 * step) part[i] += part[i + step];
+                for (int i = 0; i + step < KV / G; i += 2 * step) part[i] += part[i + step];
             z[o] = part[0] + bias[o];
         }
         float zmax = z[0];
@@ -645,8 +655,10 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
                 gb[o] += dz[o];
                 sq += e * e;
             }
-            if (t >= 0 && j == 0)
-                my_loss += a.mse ? (double)wt * 0.5 * (double)sq : (double)wt * ((double)logf(sum) - (double)zt);
+            // (lane `slot` keeps what the loss takes: a round's logarithms come together)
+            if (j == slot) { loss_t = t; loss_of = a.mse ? sq : sum; loss_z = zt; loss_w = wt; }
+            if (slot == AH - 1 && j < AH && loss_t >= 0)
+                my_loss += a.mse ? (double)loss_w * 0.5 * (double)loss_of : (double)loss_w * ((double)logf(loss_of) - (double)loss_z);
             v4f dh[KV];
 #pragma unroll
             for (int v = 0; v < KV; ++v) {
@@ -717,8 +729,8 @@ __global__ __launch_bounds__(256, 2) void class_layer_kernel(ClassArgs a)
             vals[i] += __shfl_xor(vals[i], 32, 64);
             if ((tid & 63) < 16) red[wave][i][j] = vals[i];
         }
-        my_loss += __shfl_xor(my_loss, 16, 64);   // only lanes with j == 0 hold a share
-        my_loss += __shfl_xor(my_loss, 32, 64);
+#pragma unroll
+        for (int m = 1; m < 64; m = m == 2 ? 16 : 2 * m) my_loss += __shfl_xor(my_loss, m, 64);   // (only lanes with j < AH <= 4 hold shares)
         __shared__ unsigned pred[4];
         if ((tid & 63) == 0) { lred[wave] = my_loss; pred[wave] = most; }
         __syncthreads();

@@ -1160,11 +1160,17 @@ mpcnn_status set_lds_attrs(bool bf16_storage)
     return MPCNN_OK;
 }
 
+// Quads of channels per lane of class_layer_kernel, 16 lanes a position.  (Three classes and more in bf16 are bound by instructions: three quads of 64 bits
+// rather than two accesses of 128 where these are a quarter empty and more: 160 -> 3, 1200 x 1200 positions, 243 -> 223 us.  Two are bound by memory.)
+int class_quads(int K, int ncls, bool bf16)
+{
+    return bf16 && K % 8 == 0 && !(ncls > 2 && K > 128 && K <= 192) ? (K <= 128 ? 2 : 4) : (K + 63) / 64;
+}
 // bf16 storage with a multiple of 8 channels: 8 channels per 128-bit access (Q = 2)
 template <int NCLS, int KV, typename T>
 void launch_class_inst(const mpcnn::ClassArgs& a, bool train, int blocks, hipStream_t st)
 {
-    constexpr bool kPairs = sizeof(T) == 2;
+    constexpr bool kPairs = sizeof(T) == 2 && KV % 2 == 0;
     if (kPairs && a.K % 8 == 0) {
         if (train) mpcnn::class_layer_kernel<NCLS, KV, true, T, kPairs ? 2 : 1><<<blocks, 256, 0, st>>>(a);
         else mpcnn::class_layer_kernel<NCLS, KV, false, T, kPairs ? 2 : 1><<<blocks, 256, 0, st>>>(a);
@@ -1176,7 +1182,7 @@ void launch_class_inst(const mpcnn::ClassArgs& a, bool train, int blocks, hipStr
 template <int NCLS, int KV, typename T>
 int class_occupancy_inst(int K)
 {
-    constexpr bool kPairs = sizeof(T) == 2;
+    constexpr bool kPairs = sizeof(T) == 2 && KV % 2 == 0;
     int n = 0;
     hipError_t e;
     if (kPairs && K % 8 == 0)
@@ -1190,7 +1196,7 @@ template <typename T>
 int class_occupancy(int ncls, int KV, int K)
 {
 #define CASE(n, v) if (ncls == n && KV == v) return class_occupancy_inst<n, v, T>(K)
-    CASE(2, 2); CASE(3, 2); CASE(4, 2); CASE(2, 4); CASE(3, 4); CASE(4, 4);
+    CASE(2, 1); CASE(3, 1); CASE(4, 1); CASE(2, 2); CASE(3, 2); CASE(4, 2); CASE(2, 3); CASE(3, 3); CASE(4, 3); CASE(2, 4); CASE(3, 4); CASE(4, 4);
 #undef CASE
     return 0;
 }
@@ -1198,7 +1204,7 @@ template <typename T>
 void launch_class(const mpcnn::ClassArgs& a, int ncls, int KV, bool train, int blocks, hipStream_t st)
 {
 #define CASE(n, v) if (ncls == n && KV == v) return launch_class_inst<n, v, T>(a, train, blocks, st)
-    CASE(2, 2); CASE(3, 2); CASE(4, 2); CASE(2, 4); CASE(3, 4); CASE(4, 4);
+    CASE(2, 1); CASE(3, 1); CASE(4, 1); CASE(2, 2); CASE(3, 2); CASE(4, 2); CASE(2, 3); CASE(3, 3); CASE(4, 3); CASE(2, 4); CASE(3, 4); CASE(4, 4);
 #undef CASE
 }
 
@@ -1364,7 +1370,7 @@ mpcnn_status run_forward(mpcnn_net* net, const Geom& g, const float* image, char
             const double flops = 2.0 * M * Ci * ly.cout * (train ? 3.0 : 1.0);
             const double bytes = es * n_in * (train ? 2.0 : 1.0) + 4.0 * n_out;
             LAUNCH("class_layer", l, train ? 4 : 3, flops, bytes,
-                   launch_class<T>(a, ly.cout, Ci <= 128 ? 2 : 4, train, blocks, st));
+                   launch_class<T>(a, ly.cout, class_quads(Ci, ly.cout, !kF32), train, blocks, st));
             // (in training the shares are added by the reduce launch that ends the backward)
             if (train && want_loss) net->loss_shares = blocks;
         } else {
@@ -2086,7 +2092,7 @@ mpcnn_status mpcnn_set_params(mpcnn_net* net, const float* params_host, size_t n
         }
         const Layer& last = net->layers.back();
         if (last.class_fused) {
-            const int kv = last.cin <= 128 ? 2 : 4;
+            const int kv = class_quads(last.cin, last.cout, net->bf16);
             const int occ = net->bf16 ? class_occupancy<mpcnn::bf16>(last.cout, kv, last.cin) : class_occupancy<float>(last.cout, kv, last.cin);
             if (occ > 0) net->class_max_blocks = std::min(kLossBlocks, kNumCU * occ);
         }

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 from paper_1302_1690_amd import mpcnn, workloads as wl
+from test_gpu_parity import full_parity
 
 C, MP, FC = wl.C, wl.MP, wl.FC
 pytestmark = pytest.mark.gpu
@@ -136,3 +137,13 @@ def test_all_channels_in_one_workgroup(below, k, hidden, size):
         net.close()
     assert np.isfinite(out[0][1]).all() and np.any(out[0][1])
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("hidden,classes", [(4, 2), (24, 3), (60, 4), (64, 2), (68, 3), (100, 4), (128, 2), (132, 3), (136, 4), (160, 2), (180, 4), (192, 3), (196, 2), (200, 4), (256, 3)])
+def test_class_layer_of_its_own(hidden, classes, dtype):
+    """Training: one to four quads of channels per lane, whole and not, every number of classes; against the oracle."""
+    layers = ((C, 8, 3), (MP, 0, 2), (FC, hidden, 0), (FC, classes, 0))
+    full_parity(wl.Workload("class_%d_%d_%s" % (hidden, classes, dtype), layers, 6, 1, classes, 2, 31, 24, 0.3, "ellipses", dtype=dtype,
+                            seed_image=1611 + hidden, seed_label=2611, seed_param=3611), with_pixw=True, ignore_some=True,
+                loss_fn="mse" if hidden % 16 else "mcce")
