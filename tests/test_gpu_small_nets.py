@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_1302_1690_amd import mpcnn, workloads as wl
 from test_gpu_parity import full_parity, run_gpu
 
@@ -46,6 +47,24 @@ def test_against_the_oracle(name, layers, patch, ch, over):
                             seed_image=1211, seed_label=2211, seed_param=3211), with_pixw=True, ignore_some=over[0] > 20)
 
 
+def net_or_twin(cfg, params, hidden):
+    """cfg's net, or its twin that is run layer by layer: 12 hidden units instead of 8, four of them without weights into them or out of them.
+    And which of its parameters are cfg's."""
+    net = mpcnn.Net(cfg.layers[:-2] + ((FC, hidden, 0), cfg.layers[-1]), cfg.in_channels, cfg.patch)
+    own = np.ones(net.param_count, dtype=bool)
+    if hidden == 12:
+        n_in = 3 * 3 * 3                               # W[o][c][u][v], b[o] of the hidden layer, then W[o][unit], b[o]
+        at = net.param_count - (12 * n_in + 12) - (2 * 12 + 2)
+        own[at + 8 * n_in:at + 12 * n_in] = False
+        own[at + 12 * n_in + 8:at + 12 * n_in + 12] = False
+        for o in range(2):
+            own[net.param_count - 26 + 12 * o + 8:net.param_count - 26 + 12 * o + 12] = False
+    wide = np.zeros(net.param_count, dtype=np.float32)
+    wide[own] = params
+    net.set_params(wide)
+    return net, own
+
+
 @pytest.mark.parametrize("loss,squash", [("mcce", "tanh"), ("mse", "logistic")])
 @pytest.mark.parametrize("batch,height,width", [(1, 150, 133), (3, 300, 222)])
 def test_against_the_layers_one_by_one(batch, height, width, loss, squash):
@@ -57,21 +76,9 @@ def test_against_the_layers_one_by_one(batch, height, width, loss, squash):
     d_img, d_lab = torch.from_numpy(img).cuda(), torch.from_numpy(lab).cuda()
     pixw = torch.rand(d_lab.shape, device="cuda") + 0.5
     out = []
-    for hidden in (8, 12):                             # (the twin: four hidden units without weights, into them or out of them)
-        layers = cfg.layers[:-2] + ((FC, hidden, 0), cfg.layers[-1])
-        net = mpcnn.Net(layers, cfg.in_channels, cfg.patch)
+    for hidden in (8, 12):
+        net, own = net_or_twin(cfg, params, hidden)
         assert ("whole net" in net.plan_describe(batch, height, width, True)) == (hidden == 8)
-        own = np.ones(net.param_count, dtype=bool)     # places of the smaller net's parameters
-        if hidden == 12:
-            n_in = 3 * 3 * 3                           # W[o][c][u][v], b[o] of the hidden layer, then W[o][unit], b[o]
-            at = net.param_count - (12 * n_in + 12) - (2 * 12 + 2)
-            own[at + 8 * n_in:at + 12 * n_in] = False
-            own[at + 12 * n_in + 8:at + 12 * n_in + 12] = False
-            for o in range(2):
-                own[net.param_count - 26 + 12 * o + 8:net.param_count - 26 + 12 * o + 12] = False
-        wide = np.zeros(net.param_count, dtype=np.float32)
-        wide[own] = params
-        net.set_params(wide)
         net.set_loss(loss)
         net.set_activation(squash)
         probs = torch.empty((batch, cfg.n_classes, cfg.out_h, cfg.out_w), device="cuda")
@@ -111,14 +118,20 @@ def test_a_tiling_changes_nothing(hint):
 
 
 def test_nan_stays_where_it_is():
-    """A pixel that is not a number: outputs whose patches hold it, and no others."""
+    """A pixel that is not a number: outputs whose patches hold it are the oracle's (the pools pass over it in all places of a window but the first),
+    all others are as they were; gradients are not numbers where the oracle's are not."""
     cfg = wl.crop(wl.CONFIGS[0], 1, 70, 61)
     img, lab = wl.make_inputs(cfg)
     params = wl.make_params(cfg)
     net, probs, _, _ = run_gpu(cfg, img, lab, params)
     img[0, 0, 33, 30] = np.nan
-    _, bad, _, grads = run_gpu(cfg, img, lab, params, net=net)
+    _, bad, loss, grads = run_gpu(cfg, img, lab, params, net=net)
+    net.close()
     hit = np.zeros((cfg.out_h, cfg.out_w), dtype=bool)
     hit[33 - cfg.patch + 1:34, 30 - cfg.patch + 1:31] = True
     assert np.array_equal(bad[:, :, ~hit], probs[:, :, ~hit])
-    net.close()
+    ref = oracle.run(cfg.layers, cfg.in_channels, cfg.patch, params.astype(np.float64), img.astype(np.float64), lab, want_grads=True)
+    assert np.isnan(bad[:, :, hit]).any() and np.array_equal(np.isnan(bad), np.isnan(ref["probs"]))
+    assert np.nanmax(np.abs(bad - ref["probs"])) <= 1e-6
+    assert np.isnan(loss) == np.isnan(ref["loss"])
+    assert np.isnan(grads).any() and np.array_equal(np.isnan(grads), np.isnan(ref["grads"]))
