@@ -106,13 +106,12 @@ constexpr float kPartsUp = 0x1p16f, kPartsDown = 0x1p-32f;
 // LDS offsets of a block's steps, from a position's, in a table (kernel below), and the entries read past its end
 __host__ __device__ constexpr int parts_sets(int parts, int tiles) { return parts == 3 ? 1 : parts == 2 || tiles > 2 ? 2 : 4; }   // activations in registers
 constexpr int kPartsTabAhead = 2;
-__host__ __device__ inline int parts_table(int parts, int CB, int rpad, int taps)
+__host__ __device__ inline int parts_table(int CB, int rpad, int taps)
 {
-    (void)parts;
     return taps * ((CB < rpad ? CB : rpad) / 16) + 4 + kPartsTabAhead;
 }
 // With the class layer, behind the table, in floats: the threads' losses (fp64), its weights, one class after the other, the waves' sums of a tile
-__host__ __device__ inline int parts_head_at(int parts, int CB, int rpad, int taps) { return (parts_table(parts, CB, rpad, taps) + 3) / 4 * 4; }
+__host__ __device__ inline int parts_head_at(int CB, int rpad, int taps) { return (parts_table(CB, rpad, taps) + 3) / 4 * 4; }
 __host__ __device__ inline int parts_head(int n, int WO, int MO, int positions) { return 2 * positions + n * 32 * WO * MO + WO * n * positions; }
 // steps of weights that follow the last in a pack, the first ones again: the ring runs ahead without a look at the end
 __host__ __device__ constexpr int parts_ahead(int parts) { return parts == 3 ? 4 : 8; }
@@ -352,7 +351,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     {
         const int taps = a.kr * a.k2, all = taps * ((CB < a.CrPad ? CB : a.CrPad) / 16);
         const float per_tap = __builtin_amdgcn_rcpf((float)taps), per_row = __builtin_amdgcn_rcpf((float)a.k2);
-        for (int i = tid; i < parts_table(P, CB, a.CrPad, taps); i += kThreads) {
+        for (int i = tid; i < parts_table(CB, a.CrPad, taps); i += kThreads) {
             // (quotients of numbers below 2^20, half a step from the next whole one: exact)
             const int sub = (int)(((float)i + 0.5f) * per_tap), r = i - sub * taps, ta = (int)(((float)r + 0.5f) * per_row), tb = r - ta * a.k2;
             table[i] = i >= all ? 0 : P != 1 ? (ta * hw + tb) * PITCH + sub * (P * 32) : (ta * hw + tb) * POSB + (2 * sub / GO) * GB + (2 * sub % GO) * 16;
@@ -362,7 +361,7 @@ __device__ __forceinline__ void conv_parts_body(const ConvArgs a, unsigned in_pe
     // ---- the class layer's weights, zeros for channels that do not exist; its outputs' sums, [wave's channels][class][position]
     constexpr int kChannels = 32 * WO * MO, kPositions = 32 * WP * MP;
     static_assert(!HEAD || kPositions <= kThreads, "a thread a position");
-    float* const head_w = bias_l + kChannels + (HEAD ? parts_head_at(P, CB, a.CrPad, a.kr * a.k2) : 0);
+    float* const head_w = bias_l + kChannels + (HEAD ? parts_head_at(CB, a.CrPad, a.kr * a.k2) : 0);
     // (the arguments are read where they are used, and a thread's loss stays in LDS: there are no registers left in the loop)
     typedef const __attribute__((address_space(4))) HeadArgs* HeadPtr;
     auto head_args = [&] {

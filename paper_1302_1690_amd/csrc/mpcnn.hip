@@ -333,8 +333,8 @@ TilePlan plan_conv_parts(int B, int in_c, int out_r, int out_c, int d, int d2, i
         for (int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64, 128}) {
             if (parts > 1 && (k < 8 || CB > 16 || parts > k)) break;
             const int kr = ceil_div(k, parts), nkr = ceil_div(k, kr);
-            const size_t beside = (32 * OT + (head ? mpcnn::parts_head_at(P, CB, rpad, kr * k2) + mpcnn::parts_head(head, in.WO, in.MO, 32 * PT)
-                                                   : mpcnn::parts_table(P, CB, rpad, kr * k2))) * sizeof(float);   // the bias, the steps' places, the class layer's
+            const size_t beside = (32 * OT + (head ? mpcnn::parts_head_at(CB, rpad, kr * k2) + mpcnn::parts_head(head, in.WO, in.MO, 32 * PT)
+                                                   : mpcnn::parts_table(CB, rpad, kr * k2))) * sizeof(float);   // the bias, the steps' places, the class layer's
             const size_t room_lds = std::min((size_t)160 * 1024 / resident, (size_t)(head ? 64 : 160) * 1024);   // (more has to be asked for, some 10 us an instance)
             if (beside + RP * pitch > room_lds) continue;
             const int lds_pos = (int)((room_lds - beside) / (RP * pitch)) * RP;
@@ -863,17 +863,20 @@ bool make_geom(const mpcnn_net* net, int B, int H, int W, bool training, Geom* g
     g->head = false;
     if (!training && !g->small_net && L >= 2 && net->layers[L - 1].class_fused && g->fwd[L - 2].ok && !net->hint_pt && !net->hint_mp) {
         // Nothing of the hidden layer is kept, so it need not pass through memory on its way to the classes - where that way takes longer than the wait for
-        // all channels in one workgroup.  A map of few tiles does not fill the chip with these: 64 -> 200, 5 x 5, 60 x 67, whole passes, us, two launches /
-        // one 36.1 / 41.1, bf16 64 -> 68, 40 x 47 33.5 / 36.4; but 128 -> 200, 2 x 2, 97 x 104 43 / 33, bf16 1000 x 1007 526 / 397.  The pass over the hidden
-        // layer counts 0.006 cycles per element; of 1400 plans of 68 .. 232 units, 34 x 41 .. 1000 x 1007, one is slower by 2 %, four by less than 0.8 us.
-        // Five tiles of 32 units on the eight waves of fp32 storage leave three SIMDs half empty (32 -> 132, 3 x 3, 600 x 607 286 / 317, 32 -> 160 in three
-        // parts, 430 x 437 180 / 185, 64 -> 132 192 / 196): not below four and a half, and in two parts only (64 -> 148 112 / 110, 64 -> 160, 1000 x 1007 1085 / 990).
+        // all channels in one workgroup.  Whole passes, us, two launches / one: a map of few tiles does not fill the chip (64 -> 200, 5 x 5, 60 x 67
+        // 36.1 / 41.1, bf16 64 -> 68, 40 x 47 33.5 / 36.4), larger ones do (128 -> 200, 2 x 2, 97 x 104 43 / 33, bf16 1000 x 1007 526 / 397; behind four pools
+        // 81 x 98, 256 tiles, 71.3 / 69.7).  The pass over the hidden layer counts 0.006 cycles per element, and 3000 where bf16 would have two groups.
+        // Five tiles of 32 units on the eight waves of fp32 storage leave three SIMDs half empty, which many tiles per compute unit show (32 -> 132, 3 x 3,
+        // 600 x 607 286 / 317, 32 -> 160 in three parts, 430 x 437 180 / 185, 64 -> 132 192 / 196; few of them 97 x 104 34 / 28): there only from four and a half
+        // tiles on and in two parts (64 -> 160, 1000 x 1007 1085 / 990).  Of 900 plans of 68 .. 200 units, 40 x 47 .. 1000 x 1007, two are slower by 2 %.
         const Layer& ly = net->layers[L - 2];
         const TilePlan& apart = g->fwd[L - 2];
         const TilePlan tp = plan_conv_parts(B, L > 2 ? g->cols[L - 3] : W, r, c, ly.dil, ly.dil2, ly.k, ly.k2, ly.cin, ly.fwd_rpad, ly.cout, ly.fwd_ct,
                                             net->bf16 ? 1 : 3, net->bf16 ? 1 : ly.fwd_half ? 3 : 6, es, false, 0, 0, net->n_cls);
-        const bool half_empty = !net->bf16 && ceil_div(ly.cout, 32) == 5 && (ly.cout <= 144 || !ly.fwd_half);
-        if (tp.ok && !half_empty && tp.cost <= apart.cost + 0.006 * B * r * c * ly.cout) { g->fwd[L - 2] = tp; g->head = true; }
+        const long tiles = (long)B * ly.dil * ly.dil2 * tp.nty * tp.ntx;
+        const bool half_empty = !net->bf16 && ceil_div(ly.cout, 32) == 5 && (ly.cout <= 144 || !ly.fwd_half) && tiles > 4 * kNumCU;
+        const double apart_cost = apart.cost + 0.006 * B * r * c * ly.cout + (net->bf16 && ly.cout > 128 ? 3000 : 0);
+        if (tp.ok && !half_empty && (tiles >= kNumCU || tp.cost <= apart_cost)) { g->fwd[L - 2] = tp; g->head = true; }
     }
     if (g->small_net) {
         // (A forward pass needs none of it, but asks for what it did layer by layer: what a caller's workspace, or the static one, is too small for does

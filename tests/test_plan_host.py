@@ -119,10 +119,10 @@ def test_rows_per_wave_of_the_image_layer_with_the_pool(channels, k, maps, rows_
 
 @pytest.mark.parametrize("dtype,below,k,units,at_end", [
     (mpcnn.F32, 64, 3, 100, {50: True, 97: True, 300: True, 1000: True}), (mpcnn.F32, 128, 2, 200, {40: False, 97: True, 600: True}),
-    (mpcnn.F32, 64, 5, 200, {40: False, 60: False, 200: True, 600: True}), (mpcnn.F32, 32, 3, 132, {40: False, 300: False, 600: False, 1000: False}),
+    (mpcnn.F32, 64, 5, 200, {40: False, 60: False, 200: True, 600: True}), (mpcnn.F32, 32, 3, 132, {40: False, 97: True, 300: False, 600: False, 1000: False}),
     (mpcnn.F32, 32, 3, 160, {40: False, 430: False}), (mpcnn.F32, 64, 3, 132, {300: False}), (mpcnn.F32, 64, 3, 160, {97: True, 300: True, 1000: True}),
     (mpcnn.BF16, 64, 5, 68, {40: False, 60: False, 300: True}), (mpcnn.BF16, 128, 2, 68, {40: False, 60: False, 200: True}),
-    (mpcnn.BF16, 32, 3, 132, {97: True, 600: True}), (mpcnn.BF16, 128, 2, 200, {97: True, 300: True, 1000: True})])
+    (mpcnn.BF16, 32, 3, 132, {97: True, 600: True}), (mpcnn.BF16, 64, 3, 200, {40: True, 300: True}), (mpcnn.BF16, 128, 2, 200, {97: True, 300: True, 1000: True})])
 def test_class_layer_at_the_end_where_it_is_faster(dtype, below, k, units, at_end):
     """Not on maps of few tiles behind long sums, nor where five tiles leave the eight waves of fp32 storage half empty."""
     net = mpcnn.Net(((C, 8, 3), (MP, 0, 2), (C, below, 3), (FC, units, 0), (FC, 2, 0)), 1, 2 * (k + 2) + 2, dtype)
@@ -137,3 +137,11 @@ def test_wide_layers_in_one_group_where_its_waves_are_busy(below, k, units, grou
     """bf16 storage, large maps: two groups of four tiles where one of eight would have no more than five."""
     forward = conv_lines(((C, 8, 3), (MP, 0, 2), (C, below, 3), (FC, units, 0), (FC, 2, 0)), 2 * (k + 2) + 2, 1400, mpcnn.BF16, 3)[0]
     assert "x %d groups" % groups in forward, forward
+
+
+@pytest.mark.parametrize("dtype", [mpcnn.F32, mpcnn.BF16])
+def test_class_layer_at_the_end_of_few_positions_of_many_residue_classes(dtype):
+    """Behind four pools even a map of 4 x 21 positions has a workgroup for every compute unit."""
+    net = mpcnn.Net(((C, 32, 7), (MP, 0, 2), (C, 64, 5), (MP, 0, 2), (C, 64, 5), (MP, 0, 2), (C, 128, 3), (MP, 0, 2), (FC, 200, 0), (FC, 2, 0)), 1, 78, dtype)
+    assert "class layer: at the end of the layer below" in net.plan_describe(1, 81, 98, False)
+    net.close()
