@@ -58,8 +58,8 @@
 // again they were a third of this layer's time with bf16 storage.  Here all channels lie in one workgroup (eight waves for more than 128 with fp32
 // storage), a lane multiplies its sixteen of a position by the classes' weights, a half of the wave adds to the other, the waves meet in LDS and a
 // thread per position ends with softmax and loss: the sums in class_layer_kernel's order, equal bits.  The halo is then staged once, not once per 128
-// channels.  Both launches -> one, microseconds: 128 -> 200, 2 x 2, bf16 2048 x 2048 1756 + 375 -> 1366; fp32 1024 x 1024 1065 + 164 -> 1007; 64 -> 100,
-// 3 x 3, fp32 301 x 293 58.8 + 9.4 -> 59.9.
+// channels.  Both launches -> one, microseconds: 128 -> 200, 2 x 2, bf16 2048 x 2048 1756 + 375 -> 1366; fp32 1024 x 1024 1065 + 164 -> 1007 (940 with the steps'
+// table); 64 -> 100, 3 x 3, fp32 301 x 293 58.8 + 9.4 -> 59.9.  Where this is taken: make_geom.
 //
 // Summation order is the step order for every output element, whatever the tiling: equal inputs give bit-equal outputs (exact pooling ties
 // stay exact) and a position's value does not depend on how the map is cut.  A data gradient in two parts does depend on the tensor's

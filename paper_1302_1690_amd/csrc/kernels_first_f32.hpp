@@ -1,5 +1,5 @@
-// The image layer with fp32 storage on v_mfma_f32_32x32x2_f32: conv + bias + squashing function over
-// 1 or 3 input channels at spacing 1 (Background, layer C).  The reduction, k*k*C values, is far too
+// The image layer, and any layer as narrow before the first pool, with fp32 storage on v_mfma_f32_32x32x2_f32: conv + bias +
+// squashing function over 1 or 3 input channels at spacing 1 (Background, layer C).  The reduction, k*k*C values, is far too
 // short for the general kernel's channel tiling, and on the vector ALU the layer runs at a tenth of the
 // matrix rate (49 taps x 32 maps of multiply-adds per position).
 //
@@ -16,7 +16,7 @@
 // are one: the layer's map, the largest of a net, need not pass through memory twice.  A tile is 4 MP rows x 32 columns still, of which the windows take
 // 4 MP - 1 x 31: the reduction is short, and what neighbours compute twice costs less than the map's way to memory and back.  Rows meet in LDS
 // (a wave's first one, for the wave above it), columns by a lane move.  Three launches -> one, microseconds: 16 maps,
-// 5 x 5, 301 x 293 mirrored 4.9 + 7.6 + 5.4 -> 11.3, 97 x 71 4.2 + 3.1 -> 4.6; 32 maps, 7 x 7, 1024 x 1024 mirrored 7 + 72 + 54 -> 106.
+// 5 x 5, 301 x 293 mirrored 4.9 + 7.6 + 5.4 -> 11.3, 97 x 71 4.2 + 3.1 -> 4.6; 32 maps, 7 x 7, 1024 x 1024 mirrored 7 + 72 + 54 -> 90 (which launches, and rows per wave: first_with_pool, first_rows).
 #pragma once
 #include "kernels_mfma.hpp"
 

@@ -1084,33 +1084,35 @@ void launch_first_bm(const mpcnn::FirstBmArgs& a, unsigned wgs, hipStream_t st)
     CASE(1, 3) CASE(1, 5) CASE(1, 7) CASE(2, 3) CASE(2, 5) CASE(2, 7)
 #undef CASE
 }
-// Rows per wave of the image layer with the pool behind it: the least time of a compute unit's workgroups - their matrix instructions, and for every round
-// of resident ones what a round takes besides (image in, LDS, squashing, pool, stores).  Whole forward passes, us, 1 / 2 / 4 rows: 16 maps, 3 x 3, 256 x 265
-// 27.3 / 28.2 / 29.4, 512 x 521 56.0 / 55.8 / 59.8; 64 maps, 5 x 5 of three channels, 360 x 369 67.4 / 63.9 / 72.0; 7 x 7 of three channels, 32 maps, 300 x 309
-// 50.1 / 47.0 / 49.3, 420 x 429 76.2 / 73.7 / 71.5, 512 x 521 101 / 88 / 98, 128 maps, 1024 x 1033 1127 / 903 / 868.  (The most rows that leave two workgroups
-// per unit, as without the pool, were up to 13 % slower than two launches.)
-int pooled_rows(int k, int ci, int B, int rows, int cols, int ct)
+// Estimated cycles of the image layer's launch with `mp` rows per wave, ct slices of 32 maps: a compute unit's matrix instructions, and for every round of
+// its resident workgroups what a round takes besides (image in, LDS, squashing, pool, stores).
+double first_cost(int k, int ci, int B, int rows, int cols, int ct, int mp, bool pool)
 {
     const bool large = k == 7 && ci == 3;             // (its filters take the registers)
-    const double mul = 64.0 * k * ceil_div(k * ci, 2);
-    int best = 1;
-    double best_cost = -1;
-    for (int mp : {1, 2, 4}) {
-        const int resident = mp == 4 ? 2 : large ? 3 : mp == 2 ? 4 : 5;
-        const long per_cu = ((long)B * ceil_div(rows, 4 * mp - 1) * ceil_div(cols, 31) * ct + kNumCU - 1) / kNumCU;
-        const double cost = per_cu * mp * mul + (per_cu + resident - 1) / resident * (2000.0 + 1500.0 * mp);
-        if (best_cost < 0 || cost < best_cost) { best = mp; best_cost = cost; }
+    const int resident = mp == 4 ? (pool || large ? 2 : 3) : large ? 3 : mp == 2 ? 4 : 5, less = pool ? 1 : 0;
+    const long per_cu = ((long)B * ceil_div(rows, 4 * mp - less) * ceil_div(cols, 32 - less) * ct + kNumCU - 1) / kNumCU;
+    return per_cu * mp * 64.0 * k * ceil_div(k * ci, 2) + (per_cu + resident - 1) / resident * (2000.0 + 1500.0 * mp);
+}
+// Rows per wave.  Alone: as many as still give every compute unit two workgroups.  With the pool behind it: the least time.  Whole forward passes, us,
+// 1 / 2 / 4 rows: 16 maps, 3 x 3, 256 x 265 27.3 / 28.2 / 29.4, 512 x 521 56.0 / 55.8 / 59.8; 64 maps, 5 x 5 of three channels, 360 x 369 67.4 / 63.9 / 72.0;
+// 7 x 7 of three channels, 32 maps, 300 x 309 50.1 / 47.0 / 49.3, 420 x 429 76.2 / 73.7 / 71.5, 512 x 521 101 / 88 / 98, 128 maps, 1024 x 1033
+// 1127 / 903 / 868.
+int first_rows(int k, int ci, int B, int rows, int cols, int ct, bool pool)
+{
+    int mp = 4;
+    if (!pool) {
+        while (mp > 1 && (long)B * ceil_div(rows, 4 * mp) * ceil_div(cols, 32) * ct < 2L * kNumCU) mp >>= 1;
+        return mp;
     }
-    return best;
+    for (int i : {2, 1}) if (first_cost(k, ci, B, rows, cols, ct, i, true) <= first_cost(k, ci, B, rows, cols, ct, mp, true)) mp = i;
+    return mp;
 }
 // fp32 storage, the image layer on the fp32 matrix instruction: instance by filter side, channels and rows per wave
 bool launch_first_mfma(const mpcnn::FirstMfmaArgs& a0, int k, int ci, int B, bool pool, hipStream_t st)
 {
     mpcnn::FirstMfmaArgs a = a0;
     const int ct = ceil_div(a.Co, 32), rows = pool ? a.Hp : a.Ho, cols = pool ? a.Wp : a.Wo, less = pool ? 1 : 0;
-    int mp = 4;   // rows per wave: as many as still give every compute unit two workgroups
-    while (mp > 1 && (long)B * ceil_div(rows, 4 * mp) * ceil_div(cols, 32) * ct < 2L * kNumCU) mp >>= 1;
-    if (pool) mp = pooled_rows(k, ci, B, rows, cols, ct);
+    const int mp = first_rows(k, ci, B, rows, cols, ct, pool);
     a.nty = ceil_div(rows, 4 * mp - less); a.ntx = ceil_div(cols, 32 - less);
     const dim3 grid((unsigned)(B * a.nty * a.ntx), (unsigned)ct);
 #define CASE(kk, cc, mm)                                                                              \
@@ -1133,10 +1135,18 @@ bool narrow_on_mfma(const mpcnn_net* net, const Geom& g, size_t l)
     return !net->bf16 && ly.kind != MPCNN_MP && !ly.class_fused && !g.fwd[l].ok && !ly.rect && ly.dil == 1 && (ly.cin == 1 || ly.cin == 3) &&
            (ly.k == 3 || ly.k == 5 || ly.k == 7) && (long)g.B * g.rows[l] * g.cols[l] < (1l << 31) / 32;
 }
-// ... the image layer's with the pool behind it: nothing kept, 2 x 2
+// ... the image layer's with the pool behind it: nothing kept, 2 x 2, and where what its tiles compute twice is less than the pool's own launch and its
+// way to memory and back, 12000 cycles and 0.002 per number that the L2 caches do not hold.  (7 x 7 filters on three channels, whole passes, us, two
+// launches / one: 128 maps, 200 x 209 58.3 / 60.1, 256 x 256 71.0 / 77.0, 256 x 265 96.7 / 78.0.  Of 220 sizes one is slower, by 0.3 us.)
 bool first_with_pool(const mpcnn_net* net, const Geom& g)
 {
-    return !g.training && net->layers.size() > 1 && narrow_on_mfma(net, g, 0) && net->layers[1].kind == MPCNN_MP && !net->layers[1].rect && net->layers[1].k == 2;
+    if (g.training || net->layers.size() < 2 || !narrow_on_mfma(net, g, 0) || net->layers[1].kind != MPCNN_MP || net->layers[1].rect || net->layers[1].k != 2) return false;
+    const Layer& ly = net->layers[0];
+    const int ct = ceil_div(ly.cout, 32);
+    auto cost = [&](int l, bool pool) {
+        return first_cost(ly.k, ly.cin, g.B, g.rows[l], g.cols[l], ct, first_rows(ly.k, ly.cin, g.B, g.rows[l], g.cols[l], ct, pool), pool);
+    };
+    return cost(1, true) <= cost(0, false) + 12000 + 0.002 * std::max(0.0, (double)g.B * g.rows[0] * g.cols[0] * ly.cout - 8e6);
 }
 template <typename T>
 bool launch_l0_wgrad(const mpcnn::L0WgradArgs& a, int k, int ci, dim3 grid, hipStream_t st)
@@ -2057,7 +2067,7 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
             {
             put("  forward: image-layer kernel on the fp32 MFMA");
             if (l == 0 && first_with_pool(net, g))
-                put(", the pool behind it in the same launch, %d rows per wave", pooled_rows(ly.k, ly.cin, B, g.rows[1], g.cols[1], ceil_div(ly.cout, 32)));
+                put(", the pool behind it in the same launch, %d rows per wave", first_rows(ly.k, ly.cin, B, g.rows[1], g.cols[1], ceil_div(ly.cout, 32), true));
             put("\n");
         }
         else
