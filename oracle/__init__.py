@@ -264,7 +264,8 @@ def lbfgs_step(f, theta, g, f0, state, alpha0=1.0, c=1e-4, beta=0.5, max_trials=
          stored (the oldest dropped beyond `history`) iff s.y > curvature * |s| |y|.
       2. p = lbfgs_direction(g, pairs); if g.p >= 0 the pairs are dropped and p = -g.
       3. alpha = alpha0, beta*alpha0, ...: the first with f(theta + alpha p) <= f0 + c alpha g.p
-         is accepted; theta and g become the previous iterate.
+         is accepted; theta and g become the previous iterate.  (To two units in f0's last place:
+         next to the minimum the decrease is less than f's own rounding.)
       4. If no trial passes: parameters unchanged, alpha = 0, history and previous iterate dropped.
     Returns (new theta, alpha, f(new theta), trials, pairs in use)."""
     theta = np.asarray(theta, dtype=np.float64)
@@ -282,10 +283,11 @@ def lbfgs_step(f, theta, g, f0, state, alpha0=1.0, c=1e-4, beta=0.5, max_trials=
         p, slope = -g, -float(np.dot(g, g))
     used = len(pairs)
     alpha = float(alpha0)
+    rounding = 2.0 * float(np.spacing(abs(float(f0))))
     for trial in range(1, max_trials + 1):
         cand = theta + alpha * p
         fc = float(f(cand))
-        if fc <= f0 + c * alpha * slope:
+        if fc <= f0 + c * alpha * slope + rounding:
             state["theta_prev"], state["g_prev"] = theta.copy(), g.copy()
             return cand, alpha, fc, trial, used
         alpha *= beta

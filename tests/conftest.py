@@ -1,6 +1,10 @@
 import os
 import sys
 
+# numpy's products in the same order on every host (before numpy is loaded): OpenBLAS chooses its kernels by the CPU, and the last iterations of a
+# minimisation in fp64 go one way or the other by the last bit (test_lbfgs_step_rules_and_convergence passed on hosts with AVX-512 only)
+os.environ.setdefault("OPENBLAS_CORETYPE", "Prescott")
+
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
