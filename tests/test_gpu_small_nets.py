@@ -117,6 +117,14 @@ def test_a_tiling_changes_nothing(hint):
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]) and out[0][2] == out[1][2]
 
 
+def test_which_nets():
+    """Nothing for the convolutions' matrix instruction, eight channels, 2048 parameters, a halo no dearer than the pixels; fp32."""
+    tiny = wl.CONFIGS[0]
+    assert small(tiny.layers, tiny.patch, 1, 1, 40, 40) and small(tiny.layers, tiny.patch, 1, 4, 900, 900, False)
+    for layers, patch in ((((C, 9, 3), (FC, 2, 0)), 4), (((C, 8, 3), (C, 8, 3), (FC, 2, 0)), 6), (((C, 7, 9), (C, 7, 9), (FC, 2, 0)), 17)):
+        assert not small(layers, patch, 1, 1, 60, 60), layers
+
+
 def test_nan_stays_where_it_is():
     """A pixel that is not a number: outputs whose patches hold it are the oracle's (the pools pass over it in all places of a window but the first),
     all others are as they were; gradients are not numbers where the oracle's are not."""
