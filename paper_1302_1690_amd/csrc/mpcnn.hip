@@ -2063,14 +2063,12 @@ mpcnn_status mpcnn_plan_describe(const mpcnn_net* net, int B, int H, int W, int 
         const bool img_sides = ly.dil == 1 && !ly.rect && (ly.k == 3 || ly.k == 5 || ly.k == 7);
         if (!g.fwd[l].ok && l == 0 && net->bf16 && img_sides && ly.cin <= 4 && ly.cout <= 64)
             put("  forward: image-layer kernel on the bf16 MFMA\n");
-        else if (narrow_on_mfma(net, g, l))
-            {
+        else if (narrow_on_mfma(net, g, l)) {
             put("  forward: image-layer kernel on the fp32 MFMA");
             if (l == 0 && first_with_pool(net, g))
                 put(", the pool behind it in the same launch, %d rows per wave", first_rows(ly.k, ly.cin, B, g.rows[1], g.cols[1], ceil_div(ly.cout, 32), true));
             put("\n");
-        }
-        else
+        } else
             conv("forward", g.fwd[l], ly.fwd_ct, two_part_forward(net, g, l));
         if (!training) continue;
         if (l > 0) conv("data gradient", g.dgrad[l], ly.dgrad_ct, two_part_dgrad(net, g, l));
